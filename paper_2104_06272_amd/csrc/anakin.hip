@@ -243,7 +243,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     }
     int fan = 1;
     bool one_stage = false;
-    if (!ns.bf16 && ns.dims[ns.L] % 64 == 0 && M % 32 == 0) {
+    if (!ns.bf16 && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
         // matrix-core head pass: two workgroups per CU stream enough on their own, and their partials go straight to Adam
         const int s = pick_divisor_splits(M, 32, 512);
         if (s >= 64) { splits[ns.L] = s; one_stage = true; }

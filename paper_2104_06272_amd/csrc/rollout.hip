@@ -1104,7 +1104,7 @@ static bool mfma_tile_ok(const NetShape& net, int TM)
 {
     if (net.bf16 || net.L < 2) return false;
     if (TM != 16 && TM != 32 && TM != 64) return false;
-    if (TM * net.dims[1] > 16 * 1024) return false;                 // first-layer register tile
+    if (TM * net.dims[1] > 16 * 1024 || TM * net.dims[1] < 1024) return false;   // first-layer register tile: 1 to 16 rows per thread
     for (int l = 2; l <= net.L; ++l) {
         const int N = net.dims[l];
         if (TM == 16 ? N < 64 : N < 128) return false;              // at least one MFMA tile per wavefront
