@@ -96,22 +96,18 @@ static int build_shapes(const anakin_env_cfg* env, const anakin_net_cfg* net, in
 }
 
 // split-K factor for a reduction over M samples feeding `tiles` output tiles:
-// chunks are multiples of 16 rows; aim for about 1024 workgroups, at most max_splits splits
+// chunks are multiples of `quantum` rows (the last one may be shorter); aim for about 1024 workgroups, at most
+// max_splits splits.  The count must not depend on M being a product of powers of two: halving until the cap was
+// reached gave an M with an odd factor (B = 2000, T = 15: 1875 chunks of 16) one partial sum per chunk of it, 983 MB
+// for a 512 x 256 layer, written here and read again by Adam.
 static int pick_splits(int M, int tiles, int max_splits, int quantum = 16)
 {
     int cap = 1024 / (tiles > 0 ? tiles : 1);
     if (cap > max_splits) cap = max_splits;
     if (cap < 1) cap = 1;
-    int s = M / quantum;
-    while (s > cap && s % 2 == 0) s /= 2;
-    return s > 0 ? s : 1;
-}
-
-// largest split count <= cap whose chunks are whole multiples of `quantum` rows (1 if none)
-static int pick_divisor_splits(int M, int quantum, int cap)
-{
-    for (int s = cap; s > 1; --s) if (M % (s * quantum) == 0) return s;
-    return M % quantum == 0 ? 1 : 0;
+    const int q = (M + quantum - 1) / quantum;
+    const int per = (q + cap - 1) / cap;                         // quanta per chunk
+    return (q + per - 1) / per;
 }
 
 // The scratch of the backward pass: per-sample head gradients, dZ_l, split-K partial sums, first-stage partials
@@ -184,36 +180,29 @@ static void carve(const EnvDims& ed, const NetShape& ns, int B, int T, const int
     L.total = off;
 }
 
-static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* splits, int* splits_w, int* head_fan, int* loss_blocks)
+static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* splits, int* quanta, int* splits_w, int* head_fan, int* loss_blocks)
 {
     const int M = B * T;
-    for (int l = 0; l < MAX_REGIONS; ++l) splits[l] = 0;
-    for (int l = 0; l < ns.L; ++l) {
-        const int tiles = ((ns.dims[l] + 127) / 128) * ((ns.dims[l + 1] + 127) / 128);
-        splits[l] = pick_splits(M, tiles, 256);
-    }
-    splits[ns.L] = pick_splits(M, (ns.dims[ns.L] + 127) / 128, 256);
+    for (int l = 0; l < MAX_REGIONS; ++l) { splits[l] = 0; quanta[l] = 16; }
+    auto set = [&](int l, int tiles, int cap, int quantum) { quanta[l] = quantum; splits[l] = pick_splits(M, tiles, cap, quantum); };
+    const bool bfp = rollout_bf16_ok(ns, ed, B);
+    const int q32 = bfp ? 64 : M % 32 == 0 ? 32 : 16;
+    for (int l = 0; l < ns.L; ++l) set(l, ((ns.dims[l] + 127) / 128) * ((ns.dims[l + 1] + 127) / 128), 256, q32);
     if (!ns.bf16)
         for (int l = 1; l < ns.L; ++l)
-            if (ns.dims[l] == 256 && ns.dims[l + 1] == 256) {
+            if (ns.dims[l] == 256 && ns.dims[l + 1] == 256 && M % 32 == 0) {
                 // persistent 256 x 256 dW kernel, 32-sample steps.  It shares its launch with the dX kernel of the
                 // layer and the two kinds of workgroup run side by side, one per compute unit: half the units take
                 // a dW chunk each, the other half a dX row range each (their costs per sample are within 10 %).
                 // Compared with one chunk per unit followed by one row range per unit this halves the partial sums
                 // (256 KB per chunk, written here, read by Adam) and every unit pays one prologue instead of two.
-                const int s = pick_divisor_splits(M, 32, 128);
-                // a sample count without a usable divisor (few, long chunks) stays with the tiled kernels
-                const int tiles32 = M / 32;
-                if (s > 0 && s >= (tiles32 < 64 ? tiles32 : 64)) splits[l] = s;
+                set(l, 1, 128, 32);
             }
-    if (ed.kind != ENV_MAZE) splits[0] = pick_splits(M, 2 * ((ns.dims[1] + WG - 1) / WG), 512);   // scatter kernel: more, smaller chunks
-    if (ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16) {
-        // matrix-core scatter: 64-sample steps, about two workgroups (of 128 columns) per CU
-        const int s = pick_divisor_splits(M, 64, 256);
-        if (s > 0) splits[0] = s;
-    }
-    if (const int s = first_fused_splits(ns, ed.kind, M, splits[1])) splits[0] = s;                           // first layer folded into the dX product of the second
-    if (ns.L == 1 && ed.kind != ENV_MAZE) { splits[0] = pick_splits(M, 1, 1024); splits[1] = splits[0]; }                                     // fused one-layer update: one chunking for both regions
+    if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // scatter kernel: more, smaller chunks
+    if (ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0) set(0, 1, 256, 64);   // matrix-core scatter: 64-sample steps, about two workgroups (of 128 columns) per CU
+    if (const int s = first_fused_splits(ns, ed.kind, M, splits[1])) { splits[0] = s; quanta[0] = 32; }   // first layer folded into the dX product of the second
+    set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
+    if (ns.L == 1 && ed.kind != ENV_MAZE) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
         // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
         // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the
@@ -224,40 +213,32 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         while (s > 512 && s % 2 == 0) s /= 2;
         if (s <= 1024) { splits[0] = s; splits[1] = s; }
     }
-    // the head-gradient pass streams the last hidden layer: many small workgroups, summed in two levels
-    const bool bfp = rollout_bf16_ok(ns, ed, B);
-    const int hq = bfp ? 64 : (M % 32 == 0 ? 32 : 16);  // row quantum of the head pass
-    if (bfp) splits[ns.L] = pick_splits(M, (ns.dims[ns.L] + 127) / 128, 256, 64);
     *splits_w = 0;
     if (bfp) {
         // 256 x 256 tiles where both sides of a layer are multiples of 256: about one workgroup per CU
         for (int l = 1; l < ns.L; ++l)
             if (ns.dims[l] % 256 == 0 && ns.dims[l + 1] % 256 == 0)
-                splits[l] = pick_splits(M, (ns.dims[l] / 256) * (ns.dims[l + 1] / 256), 64, 128);   // chunks: pairs of 64-sample stages
+                set(l, (ns.dims[l] / 256) * (ns.dims[l + 1] / 256), 64, 128);   // chunks: pairs of 64-sample stages
         const int cells = ed.rows * ed.cols;
-        if (ed.kind == ENV_MAZE && cells % 256 == 0 && ns.dims[1] % 256 == 0 && M % 128 == 0) {
+        if (ed.kind == ENV_MAZE && cells % 256 == 0 && ns.dims[1] % 256 == 0) {
             const int tiles = (cells / 256) * (ns.dims[1] / 256);
-            splits[0] = pick_splits(M, tiles, 128, 128);           // agent plane: all B*T samples
+            set(0, tiles, 128, 128);                               // agent plane: all B*T samples
             *splits_w = pick_splits(2 * B, tiles, 64, 128);        // wall plane: time-summed, two bf16 terms per env
         }
     }
+    // the head-gradient pass streams the last hidden layer: many small workgroups, summed in two levels
     int fan = 1;
     bool one_stage = false;
     if (!ns.bf16 && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
         // matrix-core head pass: two workgroups per CU stream enough on their own, and their partials go straight to Adam
-        const int s = pick_divisor_splits(M, 32, 512);
-        if (s >= 64) { splits[ns.L] = s; one_stage = true; }
+        set(ns.L, 1, 512, 32);
+        one_stage = true;
     }
-    if (heads_fused_shape(ns, M)) {
+    if (heads_fused_shape(ns, M) || (bfp && bf16_top_fused(ns, M))) {
         // the head gradients come out of the top layer's dW product: same chunks, one partial per chunk
-        const int st = splits[ns.L - 1];
-        if (st > 0 && M % st == 0 && (M / st) % 32 == 0) { splits[ns.L] = st; one_stage = true; }
+        splits[ns.L] = splits[ns.L - 1]; quanta[ns.L] = quanta[ns.L - 1]; one_stage = true;
     }
-    if (bfp && bf16_top_fused(ns, M, splits[ns.L - 1])) {
-        // the head gradients come out of the top layer's dW product here too
-        splits[ns.L] = splits[ns.L - 1]; one_stage = true;
-    }
-    while (!one_stage && fan < 16 && (M / hq) % (splits[ns.L] * fan * 2) == 0 && M / (splits[ns.L] * fan * 2) >= 2 * hq) fan *= 2;
+    while (!one_stage && fan < 16 && (M / q32) % (splits[ns.L] * fan * 2) == 0 && M / (splits[ns.L] * fan * 2) >= 2 * q32) fan *= 2;
     *head_fan = fan;
     *loss_blocks = (M + WG - 1) / WG;
 }
@@ -266,8 +247,8 @@ extern "C" size_t anakin_workspace_bytes(const anakin_env_cfg* env, const anakin
 {
     EnvDims ed; NetShape ns; std::string err;
     if (build_shapes(env, net, B, T, ed, ns, err) != ANAKIN_OK) return 0;
-    int splits[MAX_REGIONS], sw, lb, fan;
-    plan(ed, ns, B, T, splits, &sw, &fan, &lb);
+    int splits[MAX_REGIONS], quanta[MAX_REGIONS], sw, lb, fan;
+    plan(ed, ns, B, T, splits, quanta, &sw, &fan, &lb);
     if (lb < B / 8) lb = B / 8;                                  // as in anakin_create
     Layout L;
     carve(ed, ns, B, T, splits, sw, fan, lb, L);
@@ -399,7 +380,7 @@ extern "C" int32_t anakin_create(anakin_t** out, const anakin_env_cfg* env, cons
     h->ws = static_cast<char*>(d_workspace); h->ws_bytes = workspace_bytes;
     h->scratch = nullptr;
     h->stream = static_cast<hipStream_t>(hip_stream);
-    plan(ed, ns, B, T, h->splits, &h->splits_w, &h->head_fan, &h->loss_blocks);
+    plan(ed, ns, B, T, h->splits, h->quanta, &h->splits_w, &h->head_fan, &h->loss_blocks);
     // returns and loss in one launch write one block of sums per eight envs where the unroll is short
     if (h->loss_blocks < B / 8) h->loss_blocks = B / 8;
     carve(ed, ns, B, T, h->splits, h->splits_w, h->head_fan, h->loss_blocks, h->lay);
@@ -632,8 +613,8 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         HIPCHK(h, hipMemcpyAsync(h->ws + full.theta0, h->ws + full.theta, (size_t)n.P * 4, hipMemcpyDeviceToDevice, h->stream));
         if (n.bf16) HIPCHK(h, hipMemcpyAsync(h->ws + full.w0_bf16, h->ws + full.w_bf16, (size_t)n.P * 2, hipMemcpyDeviceToDevice, h->stream));
     }
-    int full_splits[MAX_REGIONS];
-    for (int l = 0; l < MAX_REGIONS; ++l) full_splits[l] = h->splits[l];
+    int full_splits[MAX_REGIONS], full_quanta[MAX_REGIONS];
+    for (int l = 0; l < MAX_REGIONS; ++l) { full_splits[l] = h->splits[l]; full_quanta[l] = h->quanta[l]; }
     const int full_sw = h->splits_w, full_fan = h->head_fan, full_lb = h->loss_blocks;
     int32_t rc = ANAKIN_OK;
     for (int k = 0; k < h->n_updates && rc == ANAKIN_OK; ++k) {
@@ -646,7 +627,7 @@ extern "C" int32_t anakin_learn(anakin_t* h)
             if (e == hipSuccess) e = launch_eps_now(h);
             if (e != hipSuccess) { h->err = std::string("replay of the forward pass: ") + hipGetErrorString(e); rc = ANAKIN_E_HIP; break; }
         }
-        for (int l = 0; l < MAX_REGIONS; ++l) h->splits[l] = h->sub_splits[l];
+        for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = h->sub_splits[l]; h->quanta[l] = h->sub_quanta[l]; }
         h->splits_w = h->sub_splits_w; h->head_fan = h->sub_head_fan; h->loss_blocks = h->sub_loss_blocks;
         h->T = Ts;
         const size_t r0 = (size_t)k * Ts * B;                         // first sample of the chunk
@@ -665,11 +646,11 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         for (int l = 0; l < n.L; ++l) { L.act[l] += r0 * n.dims[l + 1] * (h->traj_packed ? 2 : 4); L.mask[l] += r0 * n.dims[l + 1] / 4; }
         L.loss_part += (size_t)k * h->sub_loss_blocks * 8 * 4;
         rc = run_update(h);
-        for (int l = 0; l < MAX_REGIONS; ++l) h->splits[l] = full_splits[l];
+        for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = full_splits[l]; h->quanta[l] = full_quanta[l]; }
         h->splits_w = full_sw; h->head_fan = full_fan; h->loss_blocks = full_lb;
     }
     h->lay = full; h->T = T;
-    for (int l = 0; l < MAX_REGIONS; ++l) h->splits[l] = full_splits[l];
+    for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = full_splits[l]; h->quanta[l] = full_quanta[l]; }
     h->splits_w = full_sw; h->head_fan = full_fan; h->loss_blocks = full_lb;
     if (rc != ANAKIN_OK) return rc;
     h->have_traj = 0;
@@ -720,14 +701,14 @@ extern "C" int32_t anakin_set_updates_per_unroll(anakin_t* h, int32_t n_updates)
     if (n_updates < 1 || h->T % n_updates != 0) { h->err = "updates per unroll: T must be a positive multiple of it"; return ANAKIN_E_BAD_CONFIG; }
     if (n_updates == 1) { h->n_updates = 1; return ANAKIN_OK; }
     int sw = 0, fan = 1, lb = 0;
-    int sp[MAX_REGIONS];
-    plan(h->env, h->net, h->B, h->T / n_updates, sp, &sw, &fan, &lb);
+    int sp[MAX_REGIONS], qu[MAX_REGIONS];
+    plan(h->env, h->net, h->B, h->T / n_updates, sp, qu, &sw, &fan, &lb);
     // the scratch buffers were sized for the full unroll: a chunk's plan has to fit them
     bool ok = (sw > 0) == (h->splits_w > 0) && lb * n_updates <= h->loss_blocks + h->T && sp[h->net.L] * fan <= h->splits[h->net.L] * h->head_fan;
     for (int l = 0; l <= h->net.L && ok; ++l) ok = sp[l] > 0 && sp[l] <= h->splits[l];
     if (ok && sw > 0) ok = sw <= h->splits_w;
     if (!ok) { h->err = "updates per unroll: the chunk size does not fit the kernels' row granularity for this B and T"; return ANAKIN_E_BAD_CONFIG; }
-    for (int l = 0; l < MAX_REGIONS; ++l) h->sub_splits[l] = sp[l];
+    for (int l = 0; l < MAX_REGIONS; ++l) { h->sub_splits[l] = sp[l]; h->sub_quanta[l] = qu[l]; }
     h->sub_splits_w = sw; h->sub_head_fan = fan; h->sub_loss_blocks = lb;
     h->n_updates = n_updates;
     return ANAKIN_OK;

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(WG) void gemm_tn_splitk_valu(const GemmTnArgs a)
     const int ti = blockIdx.x % a.tiles_i, tj = blockIdx.x / a.tiles_i;
     const int i0 = ti * TS, j0 = tj * TS;
     const int split = blockIdx.y;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     const int lr = tid >> 4, lc = (tid & 15) << 2;           // loader: row 0..15, 4 consecutive columns
     const int ty = tid >> 4, tx = tid & 15;
     float acc[4][4] = {};
@@ -176,7 +176,7 @@ hipError_t launch_backward(anakin* h)
     {
         const int lt = n.L - 1;
         const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
-        if (mfma && heads_fused_shape(n, M) && h->head_fan == 1 && h->splits[n.L] == h->splits[lt] && (M / h->splits[lt]) % 32 == 0) {
+        if (mfma && heads_fused_shape(n, M) && h->head_fan == 1 && h->splits[n.L] == h->splits[lt] && h->quanta[lt] % 32 == 0) {
             hf.hl = at<const float>(h, L.act[lt]); hf.dhead = at<const float>(h, L.dhead);
             hf.wh = at<const float>(h, L.w_src) + n.wh_off; hf.NH = n.NH; hf.NHP = n.NHP;
             hf.head_partial = at<float>(h, L.part[n.L]);
@@ -199,7 +199,7 @@ hipError_t launch_backward(anakin* h)
         }
         GemmTnArgs t;
         t.M = M; t.K = n.dims[l]; t.N = n.dims[l + 1]; t.ldy = t.N;
-        t.splits = h->splits[l]; t.rows = M / t.splits;
+        t.splits = h->splits[l]; t.rows = chunk_rows(M, t.splits, h->quanta[l]);
         t.dy = at<const float>(h, L.dz[l]);
         t.partial = at<float>(h, L.part[l]);
         t.use_obs = (l == 0);
@@ -227,7 +227,7 @@ hipError_t launch_backward(anakin* h)
                 // the kernel writes one partial per workgroup along the samples: that count has to be the planned one
                 int rpb;
                 const int bx = gemm_nt_res_blocks(M, merged ? gemm_nt_res_cap(t.splits) : 256, &rpb);
-                if (bx == h->splits[0] && (long long)bx * rpb == M) {
+                if (bx == h->splits[0]) {
                     g.ff.f0 = at<const float>(h, L.tr_f0); g.ff.f1 = at<const float>(h, L.tr_f1);
                     g.ff.partial = at<float>(h, L.part[0]);
                     first_fused = true;

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(WG) void gemm_tn_splitk_mfma(const GemmTnArgs a)
     const int ti = blockIdx.x % a.tiles_i, tj = blockIdx.x / a.tiles_i;
     const int i0 = ti * BT, j0 = tj * BT;
     const int split = blockIdx.y;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     const int lrow = tid >> 4, lc = (tid & 15) * 8;                // loader: one sample row, 8 consecutive columns
     const bool x_ok = i0 + lc < a.K, y_ok = j0 + lc < a.ldy;      // K is a multiple of 8 on the dense path, ldy of 4
     const float4 zero = make_float4(0, 0, 0, 0);

@@ -206,7 +206,7 @@ __device__ __forceinline__ void gemm_tn_res256_body(const GemmTnArgs& a, const i
     constexpr int K = 256, N = 256;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
     const int wm = wave >> 2, wn = wave & 3;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     const int lrow = __builtin_amdgcn_readfirstlane(tid >> 6), lc = (tid & 63) << 2;
     f4v_r sx[4], sy[4], dh[HEADS ? 4 : 1];
     f4v_r bsum = {0.0f, 0.0f, 0.0f, 0.0f};

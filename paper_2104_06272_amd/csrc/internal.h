@@ -91,6 +91,14 @@ __device__ __forceinline__ void xcd_map(int L, int n_outer, int n_inner, int& ou
     else { const int r = L - full; outer = whole + r / n_inner; inner = r % n_inner; }
 }
 
+// Rows of a reduction over M samples that each of `splits` chunks takes: whole multiples of `quantum`, the last chunk
+// whatever is left.  Every chunk count that pick_splits returns is reached exactly (no chunk is empty).
+inline int chunk_rows(int M, int splits, int quantum)
+{
+    const int tiles = (M + quantum - 1) / quantum;
+    return (tiles + splits - 1) / splits * quantum;
+}
+
 // state snapshots the first layer's input is rebuilt from (row m = t*B + b of the trajectory)
 struct ObsLite { EnvDims env; const uint32_t* s0; const float* f0; const float* f1; };
 
@@ -154,12 +162,13 @@ struct anakin {
     int TM_mfma;                  // envs per workgroup in the matrix-core rollout kernel (0: not applicable)
     int TM_res;                   // envs per workgroup in the weights-resident rollout kernel (0: not applicable)
     int splits[ank::MAX_REGIONS]; // split-K factor per parameter region
+    int quanta[ank::MAX_REGIONS]; // rows of a region's chunks are multiples of this (chunk_rows)
     int loss_blocks;
     int metric_blocks;            // blocks of loss partials the last update wrote (0 before the first)
     int head_fan;                 // first-stage workgroups per split of the head-gradient pass
     int chunks_sequential;        // several updates per unroll: chunk k's gradient at the parameters after k updates (else at the acting ones)
     int n_updates;                // Adam updates per unroll (consecutive time chunks of the unroll), 1 by default
-    int sub_splits[ank::MAX_REGIONS], sub_splits_w, sub_head_fan, sub_loss_blocks;   // split plan of one chunk
+    int sub_splits[ank::MAX_REGIONS], sub_quanta[ank::MAX_REGIONS], sub_splits_w, sub_head_fan, sub_loss_blocks;   // split plan of one chunk
     int splits_w;                 // maze first layer of a bf16 net: split count of the wall-plane product (0: one product
                                   // over all observation rows); splits[0] is then the split count of the agent-plane product
     int bf16_path;                // the bf16 matrix-core kernels support this net
@@ -229,7 +238,7 @@ hipError_t launch_replay_bf16(anakin* h);
 hipError_t launch_backward_bf16(anakin* h);
 hipError_t launch_refresh_bf16(anakin* h);
 int bf16_dx_rows_per_workgroup(int M, int K, int N);
-bool bf16_top_fused(const NetShape& n, int M, int splits_top);
+bool bf16_top_fused(const NetShape& n, int M);
 bool bf16_dx_resident(const NetShape& n, int M, int l);
 bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
 // bf16 network running on the matrix-core path (packed bf16 activations) rather than the fp32 reference path
@@ -241,14 +250,14 @@ inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANA
 inline bool heads_fused_shape(const NetShape& n, int M) { return !n.bf16 && n.L >= 2 && n.NH <= 4 && n.dims[n.L] == 256 && n.dims[n.L - 1] == 256 && M % 32 == 0; }
 // the pendulum's first-layer gradient can ride in the epilogue of the resident dX product that forms dZ_1 (second
 // layer n x 256 with n a multiple of 256); returns the number of partials that kernel writes (its workgroups along
-// the samples, which must cut the samples evenly so that the chunking also serves the other kernels), else 0
+// the samples), else 0
 inline int first_fused_splits(const NetShape& n, int env_kind, int M, int tn_splits)
 {
     if (env_kind != ENV_PENDULUM || n.bf16 || n.L < 2 || n.dims[0] != 3 || n.dims[1] % 256 != 0 || n.dims[2] != 256 || M % 32 != 0) return 0;
     // a 256 -> 256 second layer shares its launch with the dW kernel, which then leaves it only part of the compute units
     const int cap = n.dims[1] == 256 ? (tn_splits > 0 && tn_splits < 256 ? 256 - tn_splits : 256) : 256;
-    const int tiles = M / 32, blocks = tiles < cap ? tiles : cap;
-    return tiles % blocks == 0 ? blocks : 0;
+    const int tiles = M / 32, per = (tiles + cap - 1) / cap;      // as gemm_nt_res_blocks
+    return (tiles + per - 1) / per;
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, int B);

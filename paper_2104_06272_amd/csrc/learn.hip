@@ -335,7 +335,7 @@ __global__ __launch_bounds__(WG) void head_backward(const HeadBwdArgs a)
     const int groups = WG / hw;                             // rows processed side by side
     const int g = threadIdx.x / hw, j = (threadIdx.x % hw) << 2;
     const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     float w[4][8], dw[4][8], db[8];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(WG) void head_backward_mfma(const HeadBwdArgs a)
     const int jw = blockIdx.y * 256 + wave * 64;             // first unit of this wavefront
     const bool active = jw < H;                              // H is a multiple of 64
     const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     // Wh of this lane's unit in both tiles, as B operand of the dZ product: step i takes heads 2i + kg
     float wB[2][4];
 #pragma unroll
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(WG) void first_layer_grad(const FirstGradArgs a)
     const int g = threadIdx.x / cw, jl = threadIdx.x % cw;
     const int j = blockIdx.y * WG + jl;
     const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     float* mine = accs + (size_t)g * K * cw + jl;            // this lane's column, stride cw between cells
     if (ENV == ENV_CATCH) for (int k = 0; k < K; ++k) mine[k * cw] = 0.0f;
     float bsum = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
@@ -605,7 +605,7 @@ __global__ __launch_bounds__(WG) void first_layer_grad_pendulum(const FirstGradA
     const int N = a.N;
     const int j = blockIdx.y * WG + threadIdx.x;
     const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     float bsum = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
     const float* __restrict__ dy = a.dy + j;
     for (int mb = m_begin; mb < m_end; mb += WG) {
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(512) void first_layer_grad_mfma(const FirstGradArgs
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     const int j = blockIdx.y * 256 + wave * 32 + l32;
     const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows;   // a.rows is a multiple of 64, N of 256
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;   // M and a.rows: multiples of 64, N of 256
     f16v_l acc0, acc1;
 #pragma unroll
     for (int r = 0; r < 16; ++r) { acc0[r] = 0.0f; acc1[r] = 0.0f; }
@@ -776,14 +776,14 @@ hipError_t launch_first_layer_grad(anakin* h)
     const NetShape& n = h->net;
     FirstGradArgs a;
     a.M = h->B * h->T; a.K = n.dims[0]; a.N = n.dims[1];
-    a.rows = a.M / h->splits[0];
+    a.rows = chunk_rows(a.M, h->splits[0], h->quanta[0]);
     a.dy = at<const float>(h, L.dz[0]); a.partial = at<float>(h, L.part[0]);
     a.obs.env = h->env; a.obs.s0 = at<const uint32_t>(h, L.tr_s0);
     a.obs.f0 = at<const float>(h, L.tr_f0); a.obs.f1 = at<const float>(h, L.tr_f1);
     const size_t lds = (size_t)WG * a.K * sizeof(float);
     const dim3 grid(h->splits[0], (a.N + WG - 1) / WG);
     ProfScope prof(h, "first_layer_grad");
-    if (h->env.kind == ENV_CATCH && a.K < 64 && a.rows % 64 == 0 && a.N % 256 == 0 && !(h->mode & ANAKIN_MODE_VALU_GEMM)) {
+    if (h->env.kind == ENV_CATCH && a.K < 64 && a.M % 64 == 0 && a.rows % 64 == 0 && a.N % 256 == 0 && !(h->mode & ANAKIN_MODE_VALU_GEMM)) {
         hipLaunchKernelGGL(first_layer_grad_mfma, dim3(h->splits[0], a.N / 256), dim3(512), 0, h->stream, a);
     } else if (h->env.kind == ENV_CATCH) {
         auto kern = first_layer_grad<ENV_CATCH>;
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
     const float b1 = a.theta[a.b1_off + j];
     float db1 = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
     __syncthreads();
-    const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     const float* w1c = w1s + j;
     constexpr int RB = 8;
     for (int mb = m_begin + g; mb < m_end; mb += RB * groups) {
@@ -1184,7 +1184,7 @@ hipError_t launch_learn_one_layer(anakin* h)
     const NetShape& n = h->net;
     OneLayerArgs a;
     a.M = h->B * h->T; a.D = n.dims[0]; a.H = n.dims[1]; a.NH = n.NH; a.NHP = n.NHP;
-    a.rows = a.M / h->splits[0];
+    a.rows = chunk_rows(a.M, h->splits[0], h->quanta[0]);
     a.theta = at<const float>(h, L.w_src); a.w1_off = n.w_off[0]; a.b1_off = n.b_off[0]; a.wh_off = n.wh_off;
     a.dhead = at<const float>(h, L.dhead);
     a.partial0 = at<float>(h, L.part[0]); a.partial1 = at<float>(h, L.part[1]);
@@ -1200,7 +1200,7 @@ hipError_t launch_learn_one_layer(anakin* h)
         return hipGetLastError();
     };
     const int cw = a.H < OLW ? a.H : OLW;
-    const bool full = a.rows % (8 * (OLW / cw)) == 0;             // RB x groups samples per loop trip
+    const bool full = a.rows % (8 * (OLW / cw)) == 0 && a.M % (8 * (OLW / cw)) == 0;   // RB x groups samples per loop trip
     if (h->env.kind == ENV_CATCH) {
         if (full && a.H == 32) return go(learn_one_layer<ENV_CATCH, 4, true, 32>);
         return full ? go(learn_one_layer<ENV_CATCH, 4, true, 0>) : go(learn_one_layer<ENV_CATCH, 4, false, 0>);
@@ -1513,7 +1513,7 @@ hipError_t launch_head_backward(anakin* h)
     a.M = h->B * h->T; a.H = n.dims[n.L]; a.NH = n.NH; a.NHP = n.NHP;
     const int splits = h->splits[n.L], fan = h->head_fan;
     const int stage1 = splits * fan;                        // workgroups of the streaming pass
-    a.rows = a.M / stage1;
+    a.rows = chunk_rows(a.M, stage1, h->quanta[n.L]);
     a.h = at<const float>(h, L.act[n.L - 1]); a.dhead = at<const float>(h, L.dhead);
     a.wh = at<const float>(h, L.w_src) + n.wh_off;
     a.dz = at<float>(h, L.dz[n.L - 1]);
@@ -1524,7 +1524,7 @@ hipError_t launch_head_backward(anakin* h)
     const size_t lds = (size_t)groups * stride * sizeof(float);
     {
         ProfScope prof(h, "head_backward");
-        if (a.H % 64 == 0 && a.rows % 32 == 0 && !(h->mode & ANAKIN_MODE_VALU_GEMM))
+        if (a.H % 64 == 0 && a.rows % 32 == 0 && a.M % 32 == 0 && !(h->mode & ANAKIN_MODE_VALU_GEMM))
             hipLaunchKernelGGL(head_backward_mfma, dim3(stage1, (a.H + 255) / 256), dim3(WG), 0, h->stream, a);
         else
             hipLaunchKernelGGL(head_backward, dim3(stage1), dim3(WG), lds, h->stream, a);

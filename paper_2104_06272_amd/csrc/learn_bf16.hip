@@ -80,7 +80,7 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     const int H = a.H, NH = a.NH, NHP = a.NHP;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
     const int jb = blockIdx.y * WG, jw = jb + wave * 64;
-    const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows;
+    const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     bf8 wB[2];
     bool live[2];
 #pragma unroll
@@ -641,7 +641,8 @@ __global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a)
     const int ti = blockIdx.x % a.tiles_i, tj = blockIdx.x / a.tiles_i;
     const int i0 = ti * 128, j0 = tj * 128;
     const int split = blockIdx.y;
-    const int g_begin = (split * a.rows) >> 3, g_end = g_begin + (a.rows >> 3);
+    const int g_begin = (split * a.rows) >> 3;
+    const int g_end = (split + 1) * a.rows < a.M ? g_begin + (a.rows >> 3) : a.M >> 3;
     // loader: TB_G groups x 128 columns = 2048 pieces per matrix, 8 per thread: piece p -> group p/128, column p%128
     uint4 rx[8], ry[8];
     auto fetch = [&](int g0) {
@@ -725,8 +726,8 @@ constexpr int TB_BG = 8;      // sample groups (of 8) per LDS stage: 64 samples
 // i + 1 into the other half -- its four (X, Y) pieces per thread go between the four MFMA steps, so
 // the LDS stores and the vector work behind them (the one-hot, the sums) run in the shadow of the
 // matrix cores -- and then ask for stage i + 3 into the registers just emptied: every load has two
-// stages to arrive, and there is one barrier per stage.  Chunks are whole pairs of stages of 64
-// samples (a.rows % 128 == 0).
+// stages to arrive, and there is one barrier per stage.  Chunks are pairs of stages of 64 samples
+// (a.rows % 128 == 0); the last one may be shorter and end after an odd stage.
 template <int XMODE>
 __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a)
 {
@@ -739,7 +740,8 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
     xcd_map((int)blockIdx.x, a.splits, a.tiles_i * (a.N / 256), split, tile);   // the tiles of one split share its samples
     const int ti = tile % a.tiles_i, tj = tile / a.tiles_i;
     const int i0 = ti * 256, j0 = tj * 256;
-    const int n_stages = a.rows >> 6;
+    // the last chunk may be shorter, and then end in the middle of a pair of stages
+    const int n_stages = (a.rows < a.M - split * a.rows ? a.rows : a.M - split * a.rows) >> 6;
     const bool by_env = XMODE == 1 && a.sP != nullptr;
     // first sample group of stage i of this chunk.  Sample ranges: consecutive stages.  Blocks of environments: the 64
     // environments of one stage at t = 0 .. T-1, then the next 64 (so a thread meets every time step of its samples
@@ -904,10 +906,12 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
     __syncthreads();
     // two steps per trip without a branch between them: with a conditional second step the wait-count pass gives up
     // counting in the same way
-    for (int i = 0; i < n_stages; i += 2) {
+    int i = 0;
+    for (; i + 1 < n_stages; i += 2) {
         step(S1, S0, i);
         step(S0, S1, i + 1);
     }
+    if (i < n_stages) step(S1, S0, i);                       // an odd stage, outside the loop for the same reason
     float* out = a.partial + (size_t)split * a.split_stride;
 #pragma unroll
     for (int tr = 0; tr < 4; ++tr)
@@ -938,7 +942,7 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
 // dWh = h_L^T d for their 256 columns (the same pieces of h_L are the A operand, see
 // head_backward_bf16 for the sample order) and, in the first of them, dbh; those of the second
 // row the column sums of dZ_L (the layer's bias gradient).  K and N multiples of 256; chunks are
-// whole pairs of stages (rows % 128 == 0).
+// pairs of stages (rows % 128 == 0), the last one may be shorter and odd.
 // ---------------------------------------------------------------------------
 struct GemmTnTopArgs {
     int M, K, N, splits, rows, tiles_i, NH, NHP;
@@ -975,7 +979,8 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_top(const GemmTnTopArgs a)
     xcd_map((int)blockIdx.x, a.splits, a.tiles_i * (a.N / 256), split, tile);
     const int ti = tile % a.tiles_i, tj = tile / a.tiles_i;
     const int i0 = ti * 256, j0 = tj * 256;
-    const int n_stages = a.rows >> 6;
+    // as in gemm_tn_bf16_big, the last chunk may end in the middle of a pair of stages
+    const int n_stages = (a.rows < a.M - split * a.rows ? a.rows : a.M - split * a.rows) >> 6;
     const int g_first = (split * a.rows) >> 3;
     // extras, one kind per row of tiles so that no workgroup carries both: the first row adds up dWh (and dbh), the
     // second (the first, if there is only one) the column sums of dZ_L
@@ -1101,17 +1106,19 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_top(const GemmTnTopArgs a)
     reinterpret_cast<uint4*>(Bhl)[tid] = make_uint4(0, 0, 0, 0);  // output columns 16..31 of the dWh product stay zero
     __syncthreads();
     stage_d(S0, 0); stage_d(S1, 1);
-    dbsum += S0.d + S1.d;
+    dbsum += S0.d + (n_stages > 1 ? S1.d : 0.0f);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 4; ++k) store_part(S0, 0, 0, k, true);
     __builtin_amdgcn_sched_barrier(0);
     fetch(S0, 2);
     __syncthreads();
-    for (int i = 0; i < n_stages; i += 2) {                   // no branch between the two steps (see gemm_tn_bf16_big)
+    int i = 0;
+    for (; i + 1 < n_stages; i += 2) {                        // no branch between the two steps (see gemm_tn_bf16_big)
         step(S1, S0, i);
         step(S0, S1, i + 1);
     }
+    if (i < n_stages) step(S1, S0, i);
     float* out = a.partial + (size_t)split * a.split_stride;
 #pragma unroll
     for (int tr = 0; tr < 4; ++tr)
@@ -1230,13 +1237,12 @@ bool bf16_dx_resident(const NetShape& n, int M, int l)
 }
 
 // Whether the top layer's products form dZ_L themselves (no head pass, no dZ_L in memory): both sides of the layer
-// multiples of 256, the dX product weights-resident, chunks of whole 64-sample stages.
-bool bf16_top_fused(const NetShape& n, int M, int splits_top)
+// multiples of 256, the dX product weights-resident.
+bool bf16_top_fused(const NetShape& n, int M)
 {
     if (!n.bf16 || n.L < 2 || n.NH > 8) return false;
     if (n.dims[n.L] % 256 != 0 || n.dims[n.L - 1] % 256 != 0) return false;
-    if (!bf16_dx_resident(n, M, n.L - 1)) return false;
-    return splits_top > 0 && M % splits_top == 0 && (M / splits_top) % 128 == 0;
+    return bf16_dx_resident(n, M, n.L - 1);
 }
 
 hipError_t launch_backward_bf16(anakin* h)
@@ -1250,12 +1256,12 @@ hipError_t launch_backward_bf16(anakin* h)
     auto actP = [&](int l) { return at<uint16_t>(h, L.act[l]); };
     // dZ_l is kept sample-packed; the row-major copy exists only where the tiled dX kernel of layer l + 1 reads it
     auto needs_rows = [&](int l) { return l >= 1 && !bf16_dx_resident(n, M, l); };
-    const bool top_fused = bf16_top_fused(n, M, h->splits[n.L - 1]) && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
+    const bool top_fused = bf16_top_fused(n, M) && h->quanta[n.L - 1] == 128 && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
     if (!top_fused) {   // heads
         HeadBwdBf16Args a;
         a.M = M; a.H = n.dims[n.L]; a.NH = n.NH; a.NHP = n.NHP;
         const int stage1 = h->splits[n.L] * h->head_fan;
-        a.rows = M / stage1;
+        a.rows = chunk_rows(M, stage1, h->quanta[n.L]);
         a.hP = actP(n.L - 1); a.dhead = at<const float>(h, L.dhead);
         a.wh16 = at<const uint16_t>(h, L.w16_src) + n.wh_off;
         a.dzR = needs_rows(n.L - 1) ? dzR(n.L - 1) : nullptr; a.dzP = dzP(n.L - 1);
@@ -1315,7 +1321,7 @@ hipError_t launch_backward_bf16(anakin* h)
             float* pa = pw + (size_t)plane * h->splits_w;
             float* pg = pa + (size_t)plane * h->splits[0];
             // the agent product adds dZ1 up over time on its way when its chunks can be blocks of 64 k environments
-            const bool sum_in_product = h->B % (64 * h->splits[0]) == 0;
+            const bool sum_in_product = h->B % (64 * h->splits[0]) == 0 && M % (h->splits[0] * 128) == 0;
             if (!sum_in_product) {
                 ProfScope prof(h, "time_sum");
                 hipLaunchKernelGGL(time_sum_bf16, dim3(((h->B >> 3) * H1 + WG - 1) / WG), dim3(WG), 0, h->stream,
@@ -1323,13 +1329,13 @@ hipError_t launch_backward_bf16(anakin* h)
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             GemmTnBf16Args t;
-            t.M = M; t.K = cells; t.N = H1; t.splits = h->splits[0]; t.rows = t.M / t.splits;
+            t.M = M; t.K = cells; t.N = H1; t.splits = h->splits[0]; t.rows = chunk_rows(M, t.splits, h->quanta[0]);
             t.use_obs = 1; t.obs_row0 = cells; t.xP = nullptr; t.dyP = dzP(0);
             t.partial = pa; t.split_stride = (size_t)plane; t.bias_out = nullptr; t.bias_stride = 0;
             t.obs = obs_src();
             t.sP = sum_in_product ? sP : nullptr; t.T = h->T; t.env_block = h->B / h->splits[0];
             if ((e = run_tn(t, true, "gemm_tn_agent")) != hipSuccess) return e;
-            t.M = 2 * h->B; t.splits = h->splits_w; t.rows = t.M / t.splits;
+            t.M = 2 * h->B; t.splits = h->splits_w; t.rows = chunk_rows(t.M, t.splits, 128);
             t.obs_row0 = 0; t.dyP = sP;
             t.partial = pw; t.bias_out = pg; t.bias_stride = (size_t)H1;
             t.sP = nullptr;
@@ -1338,7 +1344,7 @@ hipError_t launch_backward_bf16(anakin* h)
         }
         GemmTnBf16Args t;
         t.M = M; t.K = n.dims[l]; t.N = n.dims[l + 1];
-        t.splits = h->splits[l]; t.rows = M / t.splits;
+        t.splits = h->splits[l]; t.rows = chunk_rows(M, t.splits, h->quanta[l]);
         t.use_obs = (l == 0); t.obs_row0 = 0;
         t.xP = l > 0 ? actP(l - 1) : nullptr;
         t.dyP = dzP(l);
@@ -1347,7 +1353,7 @@ hipError_t launch_backward_bf16(anakin* h)
         t.bias_out = t.partial + (size_t)t.K * t.N; t.bias_stride = t.split_stride;
         t.obs = obs_src();
         t.sP = nullptr; t.T = h->T; t.env_block = 0;
-        const bool big = l > 0 && t.K % 256 == 0 && t.N % 256 == 0 && t.M % t.splits == 0 && t.rows % 128 == 0;
+        const bool big = l > 0 && t.K % 256 == 0 && t.N % 256 == 0 && t.rows % 128 == 0;
         if (l == n.L - 1 && top_fused) {
             GemmTnTopArgs u;
             u.M = M; u.K = t.K; u.N = t.N; u.splits = t.splits; u.rows = t.rows; u.tiles_i = t.K / 256;

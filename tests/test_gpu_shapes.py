@@ -8,6 +8,7 @@ import parity as PT
 pytestmark = pytest.mark.gpu
 
 TOL_F32 = 1e-4
+TOL_BF16 = 2e-2
 
 
 @pytest.fixture(scope="module")
@@ -41,6 +42,27 @@ def lockstep(gpu, orc, cfg, seed, updates=2, tol=TOL_F32):
     g.close()
 
 
+def forced_lockstep(gpu, orc, cfg, seed, updates=2):
+    """bf16 nets on the matrix-core path: the oracle samples and steps from the GPU's head outputs, which are checked
+    against its own forward pass"""
+    kind = cfg["env"]["kind"]
+    print(f"[bf16 {kind}] hidden={cfg['net']['hidden']} B={cfg['B']} T={cfg['T']}", flush=True)
+    g = gpu.Anakin(cfg, seed=seed)
+    o = orc.Oracle(cfg, seed=seed)
+    assert g.plan()["bf16_matrix_path"] == 1
+    for _ in range(updates):
+        PT.sync_oracle_from_gpu(g, o)
+        g.rollout()
+        tr = g.trajectory()
+        o.rollout(forced_head=tr["head"])
+        PT.assert_rollout_equal(g, o, kind, forced=True)
+        PT.assert_final_state_equal(g, o, kind)
+        PT.assert_heads_close(g, o, tr, TOL_BF16)
+        g.learn(); o.learn()
+        PT.assert_learn_close(g, o, TOL_BF16)
+    g.close()
+
+
 # one hidden layer of 64 or 128 units with many samples: every chunk's head gradient is summed
 @pytest.mark.parametrize("name,hidden,B,T", [("catch_262144", 64, 512, 8), ("catch_262144", 128, 256, 16), ("pendulum_8192", 64, 1024, 4)])
 def test_one_layer_many_samples(gpu, orc, name, hidden, B, T):
@@ -51,3 +73,18 @@ def test_one_layer_many_samples(gpu, orc, name, hidden, B, T):
 @pytest.mark.parametrize("name,hidden,B", [("pendulum_8192", [32, 64], 320), ("catch_small", [32, 512], 64)])
 def test_narrow_first_layer(gpu, orc, name, hidden, B):
     lockstep(gpu, orc, variant(name, hidden, B, 6), 4)
+
+
+# sample counts with odd factors: the last chunk of every split reduction is shorter than the others
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [512, 256], 400, 15), ("catch_4096", [256, 256], 288, 19), ("pendulum_8192", [256, 256], 352, 13),
+                                             ("pendulum_8192", [64, 128], 1808, 3), ("maze_16384", [64, 64], 208, 11)])
+def test_ragged_chunks(gpu, orc, name, hidden, B, T):
+    env = dict(rows=5, cols=7, max_steps=9) if name.startswith("maze") else {}
+    lockstep(gpu, orc, variant(name, hidden, B, T, **env), 5)
+
+
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 256], 192, 7), ("pendulum_8192", [256, 256, 256], 64, 1), ("maze_16384", [256, 256], 192, 3),
+                                             ("pendulum_8192", [512, 256, 128], 320, 3)])
+def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
+    env = dict(max_steps=9) if not name.startswith("catch") else {}
+    forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 6)
