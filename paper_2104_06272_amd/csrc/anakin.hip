@@ -463,7 +463,7 @@ void fill_rollout_args(anakin* h, RolloutArgs& a)
     const Layout& L = h->lay;
     a.env = h->env; a.net = h->net; a.theta = at<const float>(h, L.theta);
     a.B = h->B; a.T = h->T; a.seed = h->seed; a.gstep = h->gstep;
-    a.keep_acts = one_layer_fused(h) ? 0 : 1;
+    a.keep_acts = one_layer_fused(h) ? 0 : 1; a.maze_prefix = 0;
     rollout_lds_bytes(h->net, h->env, h->TM, &a.ldx);
     TrajPtrs& t = a.tp;
     t.s0 = at<uint32_t>(h, L.s0); t.f0 = at<float>(h, L.f0); t.f1 = at<float>(h, L.f1); t.walls = at<const uint32_t>(h, L.walls);

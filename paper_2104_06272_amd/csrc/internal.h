@@ -53,6 +53,7 @@ struct RolloutArgs {
     const float* theta;
     int B, T, ldx;
     int keep_acts;               // store hidden activations for the update (0: the update rebuilds them)
+    int maze_prefix;             // maze: the wall plane's share of the first layer is summed once per launch, in LDS
     uint64_t seed, gstep;
 };
 

@@ -92,12 +92,28 @@ constexpr int OBS_WORDS = 12;
 template <int ENV, int RM, bool BF>
 __device__ __forceinline__ void first_layer(const RolloutArgs& a, const uint32_t* __restrict__ obs,
                                             float* __restrict__ Y, int ldx, int tid, float* __restrict__ gout,
-                                            const float* w1, const float* b1)
+                                            const float* w1, const float* b1, const float* pre)
 {
     const int N = a.net.dims[1];
     const int CG = N >> 2, tn = tid % CG, m0 = (tid / CG) * RM, c0 = tn << 2;
     const float* wp = w1 + c0;
     float acc[RM][4];
+    if (ENV == ENV_MAZE && pre) {
+        // bias and wall plane come summed (maze_prefix); what changes from step to step is one row per environment
+        const int n = a.env.rows * a.env.cols;
+        float4 w[RM];
+#pragma unroll
+        for (int r = 0; r < RM; ++r) w[r] = ldw4<BF>(wp + (size_t)(n + (int)obs[(m0 + r) * OBS_WORDS + 8]) * N);
+        const float4 g = ldw4<BF>(wp + (size_t)(3 * n - 1) * N);
+#pragma unroll
+        for (int r = 0; r < RM; ++r) {
+            const float4 p = ld4(pre + (m0 + r) * N + c0);
+            acc[r][0] = (p.x + w[r].x) + g.x; acc[r][1] = (p.y + w[r].y) + g.y;
+            acc[r][2] = (p.z + w[r].z) + g.z; acc[r][3] = (p.w + w[r].w) + g.w;
+        }
+        finish_rows<RM, BF>(acc, Y, ldx, m0, c0, gout, N);
+        return;
+    }
     const float4 b = ld4(b1 + c0);
 #pragma unroll
     for (int r = 0; r < RM; ++r) { acc[r][0] = b.x; acc[r][1] = b.y; acc[r][2] = b.z; acc[r][3] = b.w; }
@@ -149,18 +165,48 @@ __device__ __forceinline__ void first_layer(const RolloutArgs& a, const uint32_t
     finish_rows<RM, BF>(acc, Y, ldx, m0, c0, gout, N);
 }
 
+// Maze: pre[TM][H1] = b1 + the wall rows of the environment's maze, cells ascending -- the part of the first layer
+// that never changes within a launch.  The dense scan of the wall plane used to run in every step of the unroll (14 of
+// 15 us per step of the 117-cell maze with a 128-64 net); it now runs once per launch, and the sums stay in LDS in the
+// canonical order, so the logits are the same bits.
+template <bool BF>
+__device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const uint32_t* __restrict__ obs, const float* __restrict__ w1,
+                                            const float* __restrict__ b1, float* __restrict__ pre, int tid)
+{
+    const int N = a.net.dims[1], n = a.env.rows * a.env.cols, groups = TM * N / 4;
+    constexpr int CB = 8;                                        // weight rows in flight
+    for (int i = tid; i < groups; i += WG) {
+        const int c0 = (i % (N >> 2)) << 2, m = i / (N >> 2);
+        const float* wp = w1 + c0;
+        float4 acc = ld4(b1 + c0);
+        for (int cb = 0; cb < n; cb += CB) {
+            float4 w[CB];
+#pragma unroll
+            for (int u = 0; u < CB; ++u) w[u] = ldw4<BF>(wp + (size_t)(cb + u < n ? cb + u : n - 1) * N);
+            const uint32_t bits = obs[m * OBS_WORDS + (cb >> 5)] >> (cb & 31);   // bits past the last cell are zero
+#pragma unroll
+            for (int u = 0; u < CB; ++u) {
+                const float x = (bits >> u) & 1u ? 1.0f : 0.0f;
+                acc.x = fmaf(x, w[u].x, acc.x); acc.y = fmaf(x, w[u].y, acc.y);
+                acc.z = fmaf(x, w[u].z, acc.z); acc.w = fmaf(x, w[u].w, acc.w);
+            }
+        }
+        *reinterpret_cast<float4*>(pre + m * N + c0) = acc;
+    }
+}
+
 template <int ENV, bool BF>
 __device__ __forceinline__ void run_first_layer(const RolloutArgs& a, int TM, const uint32_t* obs, float* Y, int tid, float* gout,
-                                                const float* w1)
+                                                const float* w1, const float* pre)
 {
     const float* b1 = a.theta + a.net.b_off[0];
     const int RM = TM * a.net.dims[1] / 1024;
     switch (RM) {
-        case 1: first_layer<ENV, 1, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1); break;
-        case 2: first_layer<ENV, 2, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1); break;
-        case 4: first_layer<ENV, 4, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1); break;
-        case 8: first_layer<ENV, 8, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1); break;
-        default: first_layer<ENV, 16, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1); break;
+        case 1: first_layer<ENV, 1, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1, pre); break;
+        case 2: first_layer<ENV, 2, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1, pre); break;
+        case 4: first_layer<ENV, 4, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1, pre); break;
+        case 8: first_layer<ENV, 8, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1, pre); break;
+        default: first_layer<ENV, 16, BF>(a, obs, Y, a.ldx, tid, gout, w1, b1, pre); break;
     }
 }
 
@@ -473,6 +519,7 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
     float* heads = bhs + 8;                       // [TM][NHP]
     uint32_t* obs = reinterpret_cast<uint32_t*>(heads + TM * NHP);   // [TM][OBS_WORDS]
     uint32_t* rng = obs + TM * OBS_WORDS;                            // [TM][4] draws of the current step
+    float* pre = ENV == ENV_MAZE && a.maze_prefix ? reinterpret_cast<float*>(rng + TM * 4) : nullptr;   // [TM][H1]
 
     const int tid = threadIdx.x;
     const int b0 = blockIdx.x * TM;
@@ -501,6 +548,10 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
         if (ENV == ENV_MAZE) {
             for (int w = 0; w < 8; ++w) obs[tid * OBS_WORDS + w] = tp.walls[(size_t)w * B + b];
         }
+    }
+    if (ENV == ENV_MAZE && pre) {
+        __syncthreads();
+        maze_prefix<BF>(a, TM, obs, a.theta + a.net.w_off[0], a.theta + a.net.b_off[0], pre, tid);
     }
 
     for (int t = 0; t <= T; ++t) {
@@ -533,7 +584,7 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
         // ---- forward -------------------------------------------------------
         const bool keep = t < T && a.keep_acts;  // the bootstrap evaluation keeps no activations
         float* g0 = keep ? tp.act[0] + ((size_t)t * B + b0) * a.net.dims[1] : nullptr;
-        run_first_layer<ENV, BF>(a, TM, obs, bufA, tid, g0, a.theta + a.net.w_off[0]);
+        run_first_layer<ENV, BF>(a, TM, obs, bufA, tid, g0, a.theta + a.net.w_off[0], pre);
         __syncthreads();
         float* cur = bufA;
         float* nxt = bufB;
@@ -721,7 +772,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
     uint32_t* rng = obs + TM * OBS_WORDS;                            // [TM][4] draws of the current step
     float* b1s = reinterpret_cast<float*>(rng + TM * 4);             // [RK], [RN] biases of the two hidden layers
     float* b2s = b1s + RK;
-    float* w1s = b2s + RN;                                           // [D][RK] first-layer weights
+    float* w1s = b2s + RN;                                           // [D][RK] first-layer weights (maze: [TM][RK] prefix)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b0 = blockIdx.x * TM;
@@ -805,6 +856,10 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
             for (int w = 0; w < 8; ++w) obs[tid * OBS_WORDS + w] = tp.walls[(size_t)w * B + b];
         }
     }
+    if (ENV == ENV_MAZE) {
+        __syncthreads();
+        maze_prefix<false>(a, TM, obs, w1, b1s, w1s, tid);
+    }
 
     // Everything loaded so far (weights, the envs' states) has arrived before the loop starts.  Inside the
     // loop the acting path then only stores to memory, and no step waits for an earlier step's stores: a
@@ -839,7 +894,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
         __syncthreads();
         const bool keep = t < T && a.keep_acts;
         float* g0 = keep ? tp.act[0] + ((size_t)t * B + b0) * RK : nullptr;
-        first_layer<ENV, TM * RK / 1024, false>(a, obs, bufA, ldx, tid, g0, w1, b1s);
+        first_layer<ENV, TM * RK / 1024, false>(a, obs, bufA, ldx, tid, g0, w1, b1s, ENV == ENV_MAZE ? w1s : nullptr);
         __syncthreads();
         float* g1 = keep ? tp.act[1] + ((size_t)t * B + b0) * RN : nullptr;
         if (M32) resident_m32<KS, NT>(wreg, bufA, bufB, ldx, b2s, RN, tid, g1);
@@ -1095,7 +1150,7 @@ int rollout_resident_tile(const NetShape& net, int env_kind, int B)
     // besides the tile's own buffers the kernel keeps both bias vectors and (Catch, pendulum) the whole first-layer
     // matrix in LDS: a board too large for that runs on the streaming kernels instead
     size_t lds = rollout_lds_bytes(net, EnvDims{}, tm, nullptr) + (size_t)2 * w * 4;
-    if (env_kind != ENV_MAZE) lds += (size_t)net.dims[0] * w * 4;
+    lds += (size_t)(env_kind == ENV_MAZE ? tm : net.dims[0]) * w * 4;   // (maze: the tile's wall sums)
     return lds <= 160 * 1024 ? tm : 0;
 }
 
@@ -1164,9 +1219,16 @@ int rollout_pick_tile(const NetShape& net, int B)
 }
 
 template <int ENV, bool BF, bool MF, bool REPLAY>
-static hipError_t launch_one(anakin* h, const RolloutArgs& a, int TM)
+static hipError_t launch_one(anakin* h, const RolloutArgs& args, int TM)
 {
-    const size_t lds = rollout_lds_bytes(h->net, h->env, TM, nullptr);
+    size_t lds = rollout_lds_bytes(h->net, h->env, TM, nullptr);
+    RolloutArgs a = args;
+    if (ENV == ENV_MAZE) {
+        // the wall sums of the tile stay in LDS where they fit beside the activations (all but the widest layers)
+        const size_t pre = (size_t)TM * h->net.dims[1] * 4;
+        a.maze_prefix = lds + pre <= 160 * 1024 ? 1 : 0;
+        if (a.maze_prefix) lds += pre;
+    }
     auto kern = rollout_kernel<ENV, BF, MF, REPLAY>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -1183,7 +1245,7 @@ static hipError_t launch_resident(anakin* h, const RolloutArgs& a)
     constexpr int TM = M32 ? 32 : 16;
     size_t lds = rollout_lds_bytes(h->net, h->env, TM, nullptr);
     lds += (size_t)2 * RW * 4;                                     // the hidden layers' biases
-    if (ENV != ENV_MAZE) lds += (size_t)h->net.dims[0] * RW * 4;
+    lds += (size_t)(ENV == ENV_MAZE ? TM : h->net.dims[0]) * RW * 4;
     auto kern = rollout_resident_kernel<ENV, M32, RW, RW, REPLAY>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
