@@ -162,6 +162,7 @@ static void carve(const EnvDims& ed, const NetShape& ns, int B, int T, const int
         L.mask[l] = L.act[l] + tn * w * 2;                       // packed bf16 activations use the lower half only
     }
     off += carve_update_scratch(ed, ns, B, T, splits, splits_w, head_fan, L, off);
+    for (int l = 0; l < MAX_LAYERS; ++l) L.w3[l] = take(split_gemm_shape(ns, l) ? (size_t)ns.dims[l] * ns.dims[l + 1] * 6 : 0);
     L.prefix = take(ns.bf16 ? (size_t)B * ns.dims[1] * 4 : 0);
     L.loss_part = take((size_t)(loss_blocks + T) * 8 * 4);     // + T: with N updates per unroll every chunk rounds its block count up
     // decoupled steps: behaviour parameters, second record set, the learner's forward results
@@ -190,17 +191,17 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     for (int l = 0; l < ns.L; ++l) set(l, ((ns.dims[l] + 127) / 128) * ((ns.dims[l + 1] + 127) / 128), 256, q32);
     if (!ns.bf16)
         for (int l = 1; l < ns.L; ++l)
-            if (ns.dims[l] == 256 && ns.dims[l + 1] == 256 && M % 32 == 0) {
-                // persistent 256 x 256 dW kernel, 32-sample steps.  It shares its launch with the dX kernel of the
-                // layer and the two kinds of workgroup run side by side, one per compute unit: half the units take
-                // a dW chunk each, the other half a dX row range each (their costs per sample are within 10 %).
-                // Compared with one chunk per unit followed by one row range per unit this halves the partial sums
-                // (256 KB per chunk, written here, read by Adam) and every unit pays one prologue instead of two.
-                set(l, 1, 128, 32);
+            if (split_gemm_shape(ns, l)) {
+                // the dW product shares its launch with the dX product of the layer and the two kinds of workgroup run
+                // side by side, one per compute unit: half the units take a dW chunk each, the other half a dX row range
+                // each (their costs per sample are alike).  Compared with one chunk per unit followed by one row range
+                // per unit this halves the partial sums (256 KB per chunk, written here, read by Adam) and every unit
+                // pays one prologue instead of two.
+                set(l, 1, split_tn_cap(ns, l), 16);
             }
     if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // scatter kernel: more, smaller chunks
     if (ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0) set(0, 1, 256, 64);   // matrix-core scatter: 64-sample steps, about two workgroups (of 128 columns) per CU
-    if (const int s = first_fused_splits(ns, ed.kind, M, splits[1])) { splits[0] = s; quanta[0] = 32; }   // first layer folded into the dX product of the second
+    if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = SPLIT_NT_ROWS; }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
     if (ns.L == 1 && ed.kind != ENV_MAZE) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
@@ -234,7 +235,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         set(ns.L, 1, 512, 32);
         one_stage = true;
     }
-    if (heads_fused_shape(ns, M) || (bfp && bf16_top_fused(ns, M))) {
+    if (heads_fused_shape(ns) || (bfp && bf16_top_fused(ns, M))) {
         // the head gradients come out of the top layer's dW product: same chunks, one partial per chunk
         splits[ns.L] = splits[ns.L - 1]; quanta[ns.L] = quanta[ns.L - 1]; one_stage = true;
     }

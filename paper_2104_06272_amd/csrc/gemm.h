@@ -32,19 +32,6 @@ struct FirstFuse {
     const float* f0; const float* f1;   // [M] stored angle and angular velocity (null: not folded)
     float* partial;                     // [workgroups][3*K + K]
 };
-// workgroups (along the samples) the resident dX kernel is launched with: at most `cap`, whole 32-sample stages each
-inline int gemm_nt_res_blocks(int M, int cap, int* rows_per_block_out = nullptr)
-{
-    const int tiles = (M + 31) / 32;
-    const int blocks = tiles < cap ? tiles : cap;
-    const int rows_per_block = ((tiles + blocks - 1) / blocks) * 32;
-    if (rows_per_block_out) *rows_per_block_out = rows_per_block;
-    return (M + rows_per_block - 1) / rows_per_block;
-}
-// In a launch shared with the dW kernel the two kinds of workgroup run side by side, one per compute unit: the dX
-// kernel gets the units the dW chunks leave free.
-inline int gemm_nt_res_cap(int tn_splits) { return tn_splits > 0 && tn_splits < 256 ? 256 - tn_splits : 256; }
-
 struct GemmNtArgs {
     int M, K, N, bf16;
     HeadFuse hf;
@@ -53,7 +40,11 @@ struct GemmNtArgs {
     const float* w;       // [K][N]
     const float* x;       // [M][K] forward activations (relu mask)
     float* dx;            // [M][K]
+    const void* w3;       // W as three bfloat16 terms in operand order (split_weights)
 };
+
+// weights of the layers whose dX product runs on split operands
+struct SplitWeightsArgs { int n; int K[MAX_LAYERS], N[MAX_LAYERS]; const float* w[MAX_LAYERS]; void* out[MAX_LAYERS]; };
 
 // partial[s][i][j] = sum over rows of chunk s of x[m][i] dY[m][j]; partial[s][K*N + j] = column sums of dY
 struct GemmTnArgs {
@@ -69,11 +60,8 @@ hipError_t launch_gemm_nt_valu(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_valu(GemmTnArgs a, hipStream_t s);
 hipError_t launch_gemm_nt_mfma(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_mfma(GemmTnArgs a, hipStream_t s);
-// persistent, operand-resident kernels for 256-wide layers
-bool gemm_nt_res_ok(const GemmNtArgs& a);
-bool gemm_tn_res_ok(const GemmTnArgs& a);
-hipError_t launch_gemm_nt_res(const GemmNtArgs& a, hipStream_t s);
-hipError_t launch_gemm_tn_res(const GemmTnArgs& a, hipStream_t s);
-hipError_t launch_gemm_tn_nt_res(const GemmTnArgs& t, const GemmNtArgs& n, hipStream_t s);   // both products of a layer, one launch
+// both products of a layer whose sides are multiples of 256, on split operands (gemm_split.hip)
+hipError_t launch_split_weights(const SplitWeightsArgs& a, hipStream_t s);
+hipError_t launch_gemm_tn_nt_split(GemmTnArgs t, const GemmNtArgs& n, int nt_blocks, hipStream_t s);
 
 }  // namespace ank

@@ -10,8 +10,8 @@
 // state snapshot while the tile is loaded.
 //
 // This file holds the vector-ALU versions (64x64 tiles, 4x4 per lane); the
-// matrix-core versions are in gemm_mfma.hip (tiled) and gemm_resident.hip
-// (persistent, 256-wide layers) and share the argument blocks.
+// matrix-core versions are in gemm_mfma.hip (tiled) and gemm_split.hip (layers
+// in whole 256-wide tiles) and share the argument blocks.
 #include "gemm.h"
 
 namespace ank {
@@ -168,27 +168,34 @@ hipError_t launch_backward(anakin* h)
     const NetShape& n = h->net;
     const int M = h->B * h->T;
     hipError_t e;
-    // Top hidden layer 256 -> 256 on the matrix cores: its dW and dX products form dZ_L on the way in from the
-    // layer's forward activations and the head gradient, and the dW product also sums the head matrix's gradient,
-    // so dZ_L is neither written nor read and the head pass is no kernel of its own.
+    const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
+    // Top hidden layer in whole 256-wide tiles: its dW and dX products form dZ_L on the way in from the layer's forward
+    // activations and the head gradient, and the dW product also sums the head matrix's gradient, so dZ_L is neither
+    // written nor read and the head pass is no kernel of its own.
     HeadFuse hf{};
     hf.hl = nullptr;
-    {
-        const int lt = n.L - 1;
-        const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
-        if (mfma && heads_fused_shape(n, M) && h->head_fan == 1 && h->splits[n.L] == h->splits[lt] && h->quanta[lt] % 32 == 0) {
-            hf.hl = at<const float>(h, L.act[lt]); hf.dhead = at<const float>(h, L.dhead);
-            hf.wh = at<const float>(h, L.w_src) + n.wh_off; hf.NH = n.NH; hf.NHP = n.NHP;
-            hf.head_partial = at<float>(h, L.part[n.L]);
-        }
-    }
-    if (!hf.hl) {
+    if (mfma && heads_fused_shape(n)) {
+        hf.hl = at<const float>(h, L.act[n.L - 1]); hf.dhead = at<const float>(h, L.dhead);
+        hf.wh = at<const float>(h, L.w_src) + n.wh_off; hf.NH = n.NH; hf.NHP = n.NHP;
+        hf.head_partial = at<float>(h, L.part[n.L]);
+    } else {
         e = launch_head_backward(h);
         if (e != hipSuccess) return e;
     }
+    SplitWeightsArgs sw;
+    sw.n = 0;
+    for (int l = 1; l < n.L && mfma; ++l)
+        if (split_gemm_shape(n, l)) {
+            sw.K[sw.n] = n.dims[l]; sw.N[sw.n] = n.dims[l + 1];
+            sw.w[sw.n] = at<const float>(h, L.w_src) + n.w_off[l]; sw.out[sw.n] = at<void>(h, L.w3[l]);
+            ++sw.n;
+        }
+    if (sw.n > 0) {
+        ProfScope prof(h, "split_weights");
+        if ((e = launch_split_weights(sw, h->stream)) != hipSuccess) return e;
+    }
     // pendulum: the first layer's gradient is summed in the epilogue of the dX product that forms dZ_1
-    const bool first_shape = !(h->mode & ANAKIN_MODE_VALU_GEMM) && first_fused_splits(n, h->env.kind, M, h->splits[1]) > 0;
-    bool first_fused = false;
+    const bool first_fused = mfma && first_fused_splits(n, h->env.kind, M) > 0;
     for (int l = n.L - 1; l >= 0; --l) {
         if (l == 0 && first_fused) continue;
         // one-hot boards (Catch) and the 3-feature pendulum need no GEMM for the first layer
@@ -210,7 +217,6 @@ hipError_t launch_backward(anakin* h)
         t.bf16 = n.bf16; t.tiles_i = 0;
         t.hf = HeadFuse{}; t.hf.hl = nullptr;
         if (l == n.L - 1 && hf.hl) t.hf = hf;
-        const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
         GemmNtArgs g;
         if (l > 0) {
             g.M = M; g.K = n.dims[l]; g.N = n.dims[l + 1];
@@ -219,36 +225,30 @@ hipError_t launch_backward(anakin* h)
             g.x = at<const float>(h, L.act[l - 1]);
             g.dx = at<float>(h, L.dz[l - 1]);
             g.bf16 = n.bf16;
-            g.hf = HeadFuse{}; g.hf.hl = nullptr;
-            if (l == n.L - 1 && hf.hl) g.hf = hf;
+            g.hf = t.hf;
             g.ff = FirstFuse{nullptr, nullptr, nullptr};
-            const bool merged = mfma && gemm_tn_res_ok(t) && gemm_nt_res_ok(g);
-            if (l == 1 && first_shape && gemm_nt_res_ok(g)) {
-                // the kernel writes one partial per workgroup along the samples: that count has to be the planned one
-                int rpb;
-                const int bx = gemm_nt_res_blocks(M, merged ? gemm_nt_res_cap(t.splits) : 256, &rpb);
-                if (bx == h->splits[0]) {
+            g.w3 = nullptr;
+            if (mfma && split_gemm_shape(n, l)) {
+                // the layer's two products share one launch
+                g.w3 = at<const void>(h, L.w3[l]);
+                if (l == 1 && first_fused) {
                     g.ff.f0 = at<const float>(h, L.tr_f0); g.ff.f1 = at<const float>(h, L.tr_f1);
                     g.ff.partial = at<float>(h, L.part[0]);
-                    first_fused = true;
                 }
-            }
-            if (merged) {
-                // the layer's two resident products share one launch
                 ProfScope prof(h, "gemm_tn_nt");
-                e = launch_gemm_tn_nt_res(t, g, h->stream);
+                e = launch_gemm_tn_nt_split(t, g, split_nt_blocks(n, M, l), h->stream);
                 if (e != hipSuccess) return e;
                 continue;
             }
         }
         {
             ProfScope prof(h, l == 0 ? "gemm_tn_obs" : "gemm_tn");
-            e = !mfma ? launch_gemm_tn_valu(t, h->stream) : gemm_tn_res_ok(t) ? launch_gemm_tn_res(t, h->stream) : launch_gemm_tn_mfma(t, h->stream);
+            e = mfma ? launch_gemm_tn_mfma(t, h->stream) : launch_gemm_tn_valu(t, h->stream);
         }
         if (e != hipSuccess) return e;
         if (l > 0) {
             ProfScope prof(h, "gemm_nt_mask");
-            e = !mfma ? launch_gemm_nt_valu(g, h->stream) : gemm_nt_res_ok(g) ? launch_gemm_nt_res(g, h->stream) : launch_gemm_nt_mfma(g, h->stream);
+            e = mfma ? launch_gemm_nt_mfma(g, h->stream) : launch_gemm_nt_valu(g, h->stream);
             if (e != hipSuccess) return e;
         }
     }

@@ -126,6 +126,7 @@ struct Layout {
     size_t act[MAX_LAYERS], dz[MAX_LAYERS];
     size_t mask[MAX_LAYERS];      // bf16 matrix-core path: ReLU masks, inside the unused upper half of act[l]
     size_t part[MAX_REGIONS];
+    size_t w3[MAX_LAYERS];       // fp32 nets: weights of layer l as split operands of the dX product (split_weights)
     size_t head_stage;           // first-stage partials of the head gradient
     size_t prefix;               // bf16 acting: per-env first-layer prefix [B][H1] fp32
     size_t loss_part;
@@ -246,19 +247,23 @@ bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
 // the stored unroll was produced by the bf16 matrix-core kernels and the maze first layer is reduced in pieces
 inline bool first_layer_split(const anakin* h) { return h->splits_w > 0 && h->traj_packed; }
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
-// the head backward pass can ride in the loaders of the top hidden layer's two resident products: a 256 -> 256 top
-// layer, at most four head outputs, sample count in whole 32-row stages
-inline bool heads_fused_shape(const NetShape& n, int M) { return !n.bf16 && n.L >= 2 && n.NH <= 4 && n.dims[n.L] == 256 && n.dims[n.L - 1] == 256 && M % 32 == 0; }
-// the pendulum's first-layer gradient can ride in the epilogue of the resident dX product that forms dZ_1 (second
-// layer n x 256 with n a multiple of 256); returns the number of partials that kernel writes (its workgroups along
-// the samples), else 0
-inline int first_fused_splits(const NetShape& n, int env_kind, int M, int tn_splits)
+// both sides of layer l + 1 (l >= 1) are whole 256-wide tiles: its two products share a launch (gemm_split.hip)
+inline bool split_gemm_shape(const NetShape& n, int l) { return !n.bf16 && l >= 1 && l < n.L && n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }
+constexpr int SPLIT_NT_ROWS = 128;   // samples per tile of the dX product
+// Compute units the dW and the dX product of such a layer get in their shared launch (their costs per sample are alike):
+// chunks of the dW product per tile, and workgroups of the dX product along the samples per 256 output columns.
+inline int split_tn_cap(const NetShape& n, int l) { const int c = 128 / ((n.dims[l] / 256) * (n.dims[l + 1] / 256)); return c > 1 ? c : 1; }
+inline int split_nt_blocks(const NetShape& n, int M, int l)
 {
-    if (env_kind != ENV_PENDULUM || n.bf16 || n.L < 2 || n.dims[0] != 3 || n.dims[1] % 256 != 0 || n.dims[2] != 256 || M % 32 != 0) return 0;
-    // a 256 -> 256 second layer shares its launch with the dW kernel, which then leaves it only part of the compute units
-    const int cap = n.dims[1] == 256 ? (tn_splits > 0 && tn_splits < 256 ? 256 - tn_splits : 256) : 256;
-    const int tiles = M / 32, per = (tiles + cap - 1) / cap;      // as gemm_nt_res_blocks
+    const int c = 128 / (n.dims[l] / 256), cap = c > 1 ? c : 1, tiles = (M + SPLIT_NT_ROWS - 1) / SPLIT_NT_ROWS, per = (tiles + cap - 1) / cap;
     return (tiles + per - 1) / per;
+}
+inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 4 && split_gemm_shape(n, n.L - 1); }
+// the pendulum's first-layer gradient can ride in the epilogue of the dX product that forms dZ_1; returns the number of
+// partials that kernel writes (its workgroups along the samples), else 0
+inline int first_fused_splits(const NetShape& n, int env_kind, int M)
+{
+    return env_kind == ENV_PENDULUM && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, int B);

@@ -8,8 +8,8 @@
 //   learn_one_layer       the whole backward pass of a one-hidden-layer net
 //   adam_reduce(_narrow, _flat)  fixed-order sum of split-K partials fused with Adam
 // Hidden-layer GEMMs live in gemm.hip (vector ALU), gemm_mfma.hip (tiled) and
-// gemm_resident.hip (persistent, 256-wide layers, which also take over the head
-// pass of a 256-wide top layer); the bf16 update in learn_bf16.hip; the reverse
+// gemm_split.hip (layers in whole 256-wide tiles, which also take over the head
+// pass of such a top layer); the bf16 update in learn_bf16.hip; the reverse
 // sweep of the pathwise policy gradient in pathwise.hip.
 // No floating-point atomics anywhere: every reduction has a fixed order, so runs
 // are reproducible bit for bit.

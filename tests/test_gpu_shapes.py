@@ -88,3 +88,10 @@ def test_ragged_chunks(gpu, orc, name, hidden, B, T):
 def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
     env = dict(max_steps=9) if not name.startswith("catch") else {}
     forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 6)
+
+
+# 256-wide tiles on split operands: one row tile or less, ends in the middle of a tile, several tiles side by side
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 256], 16, 1), ("pendulum_8192", [256, 256], 48, 3), ("pendulum_8192", [256, 512], 80, 5),
+                                             ("catch_4096", [512, 512], 112, 5), ("pendulum_8192", [512, 256, 256], 144, 2)])
+def test_split_operand_products(gpu, orc, name, hidden, B, T):
+    lockstep(gpu, orc, variant(name, hidden, B, T), 8)
