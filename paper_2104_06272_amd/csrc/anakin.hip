@@ -402,7 +402,7 @@ extern "C" int32_t anakin_create(anakin_t** out, const anakin_env_cfg* env, cons
     }
     h->n_updates = 1; h->chunks_sequential = 0;
     h->TM = rollout_pick_tile(ns, B);
-    h->TM_mfma = rollout_pick_tile_mfma(ns, B);
+    h->TM_mfma = rollout_pick_tile_mfma(ns, ed, B);
     h->TM_res = rollout_resident_tile(ns, ed.kind, B);
     h->bf16_path = rollout_bf16_ok(ns, ed, B) ? 1 : 0;
 
@@ -464,7 +464,7 @@ void fill_rollout_args(anakin* h, RolloutArgs& a)
     const Layout& L = h->lay;
     a.env = h->env; a.net = h->net; a.theta = at<const float>(h, L.theta);
     a.B = h->B; a.T = h->T; a.seed = h->seed; a.gstep = h->gstep;
-    a.keep_acts = one_layer_fused(h) ? 0 : 1; a.maze_prefix = 0;
+    a.keep_acts = one_layer_fused(h) ? 0 : 1; a.maze_prefix = 0; a.bootstrap = 1;
     rollout_lds_bytes(h->net, h->env, h->TM, &a.ldx);
     TrajPtrs& t = a.tp;
     t.s0 = at<uint32_t>(h, L.s0); t.f0 = at<float>(h, L.f0); t.f1 = at<float>(h, L.f1); t.walls = at<const uint32_t>(h, L.walls);

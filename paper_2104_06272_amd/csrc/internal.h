@@ -53,6 +53,7 @@ struct RolloutArgs {
     const float* theta;
     int B, T, ldx;
     int keep_acts;               // store hidden activations for the update (0: the update rebuilds them)
+    int bootstrap;               // REPLAY: the state after the last step is evaluated too
     int maze_prefix;             // maze: the wall plane's share of the first layer is summed once per launch, in LDS
     uint64_t seed, gstep;
 };
@@ -266,7 +267,7 @@ inline int first_fused_splits(const NetShape& n, int env_kind, int M)
     return env_kind == ENV_PENDULUM && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
 }
 int rollout_pick_tile(const NetShape& net, int B);
-int rollout_pick_tile_mfma(const NetShape& net, int B);
+int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);
 size_t rollout_lds_bytes(const NetShape& net, const EnvDims& env, int TM, int* ldx);
 

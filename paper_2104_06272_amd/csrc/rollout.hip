@@ -14,7 +14,7 @@
 // turn the first layer into a gather-sum of weight rows in ascending row
 // order: fma(0,w,acc) = acc and fma(1,w,acc) = acc + w, the same bits.
 //
-// Kernels: rollout_kernel (weights streamed, vector ALU or matrix cores),
+// Kernels: rollout_kernel (vector ALU), rollout_stream_kernel (matrix cores, weights streamed),
 // rollout_resident_kernel (two-layer nets up to 256 wide, W2 in registers),
 // rollout_lane_kernel (one hidden layer: one lane per env).  Each has a REPLAY
 // form, the learner's forward pass over a stored unroll for decoupled steps.
@@ -169,13 +169,13 @@ __device__ __forceinline__ void first_layer(const RolloutArgs& a, const uint32_t
 // that never changes within a launch.  The dense scan of the wall plane used to run in every step of the unroll (14 of
 // 15 us per step of the 117-cell maze with a 128-64 net); it now runs once per launch, and the sums stay in LDS in the
 // canonical order, so the logits are the same bits.
-template <bool BF>
+template <bool BF, int NTHR>
 __device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const uint32_t* __restrict__ obs, const float* __restrict__ w1,
                                             const float* __restrict__ b1, float* __restrict__ pre, int tid)
 {
     const int N = a.net.dims[1], n = a.env.rows * a.env.cols, groups = TM * N / 4;
     constexpr int CB = 8;                                        // weight rows in flight
-    for (int i = tid; i < groups; i += WG) {
+    for (int i = tid; i < groups; i += NTHR) {
         const int c0 = (i % (N >> 2)) << 2, m = i / (N >> 2);
         const float* wp = w1 + c0;
         float4 acc = ld4(b1 + c0);
@@ -227,20 +227,6 @@ __device__ __forceinline__ void run_dense_layer(const RolloutArgs& a, int TM, in
 }
 
 
-// ---------------------------------------------------------------------------
-// Hidden layers on the matrix cores.  On gfx950 the fp32 MFMA instructions add
-// their products one k at a time with a fused multiply-add, ascending in k, and
-// chain through the accumulator operand -- measured bit-identical to the
-// sequential fmaf chain on random, wide-range and integer inputs -- so starting
-// the accumulator from the bias and feeding k in ascending order reproduces
-// the canonical order exactly while running at matrix-core rate.
-//
-// Wavefront w owns output columns [w N/4, (w+1) N/4); lane l feeds column
-// w N/4 + NT (l % 16|32) + t of tile t, so one vector load of NT consecutive
-// weights per k serves all of the lane's tiles and the epilogue stores NT
-// consecutive outputs.  The weights of the next block of k are fetched from L2
-// into registers while the current block is multiplied.
-// ---------------------------------------------------------------------------
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
@@ -266,143 +252,6 @@ __device__ __forceinline__ void store_nt(float* __restrict__ p, const float (&b)
 #pragma unroll
         for (int q = 0; q < NT / 4; ++q)
             *reinterpret_cast<float4*>(p + 4 * q) = make_float4(b[4 * q + 0], b[4 * q + 1], b[4 * q + 2], b[4 * q + 3]);
-    }
-}
-
-// 16 envs per workgroup: v_mfma_f32_16x16x4_f32.  Lane l feeds A[row l%16][k l/16] and
-// B[k l/16][col l%16]; accumulator register r of lane l is D[row 4*(l/16) + r][col l%16].
-template <int NT>
-__device__ __forceinline__ void mfma_layer_m16(const float* __restrict__ X, float* __restrict__ Y, int ldx,
-                                               const float* __restrict__ W, const float* __restrict__ bias,
-                                               int K, int N, int tid, float* __restrict__ gout)
-{
-    constexpr int U = NT <= 4 ? 8 : (NT == 8 ? 4 : 2);          // k-steps (of 4) per prefetch block
-    const int lane = tid & 63, wave = tid >> 6;
-    const int col0 = wave * (N >> 2) + NT * (lane & 15), kq = lane >> 4;
-    f4v acc[NT];
-    {
-        float bv[NT];
-        load_nt<NT>(bias + col0, bv);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) { acc[t][0] = bv[t]; acc[t][1] = bv[t]; acc[t][2] = bv[t]; acc[t][3] = bv[t]; }
-    }
-    const float* wp = W + (size_t)kq * N + col0;
-    const float* xp = X + (lane & 15) * ldx + kq;
-    float bc[U][NT], bn[U][NT];
-#pragma unroll
-    for (int u = 0; u < U; ++u) load_nt<NT>(wp + (size_t)(4 * u) * N, bc[u]);
-    for (int k0 = 0; k0 < K; k0 += 4 * U) {
-        if (k0 + 4 * U < K) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) load_nt<NT>(wp + (size_t)(k0 + 4 * U + 4 * u) * N, bn[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float av = xp[k0 + 4 * u];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bc[u][t], acc[t], 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) bc[u][t] = bn[u][t];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = 4 * kq + r;
-        float o[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) o[t] = acc[t][r] > 0.0f ? acc[t][r] : 0.0f;
-        store_nt<NT>(Y + row * ldx + col0, o);
-        if (gout) store_nt<NT>(gout + (size_t)row * N + col0, o);
-    }
-}
-
-// 32*MT envs per workgroup: v_mfma_f32_32x32x2_f32.  Lane l feeds A[row l%32][k l/32] and
-// B[k l/32][col l%32]; accumulator register r is D[row 8*(r/4) + 4*(l/32) + r%4][col l%32].
-template <int MT, int NT>
-__device__ __forceinline__ void mfma_layer_m32(const float* __restrict__ X, float* __restrict__ Y, int ldx,
-                                               const float* __restrict__ W, const float* __restrict__ bias,
-                                               int K, int N, int tid, float* __restrict__ gout)
-{
-    constexpr int U = NT <= 2 ? 8 : (NT == 4 ? 4 : 2);          // k-steps (of 2) per prefetch block
-    const int lane = tid & 63, wave = tid >> 6;
-    const int col0 = wave * (N >> 2) + NT * (lane & 31), kq = lane >> 5;
-    f16v acc[MT][NT];
-    {
-        float bv[NT];
-        load_nt<NT>(bias + col0, bv);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mt][t][r] = bv[t];
-    }
-    const float* wp = W + (size_t)kq * N + col0;
-    const float* xp = X + (lane & 31) * ldx + kq;
-    float bc[U][NT], bn[U][NT];
-#pragma unroll
-    for (int u = 0; u < U; ++u) load_nt<NT>(wp + (size_t)(2 * u) * N, bc[u]);
-    for (int k0 = 0; k0 < K; k0 += 2 * U) {
-        if (k0 + 2 * U < K) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) load_nt<NT>(wp + (size_t)(k0 + 2 * U + 2 * u) * N, bn[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const float av = xp[mt * 32 * ldx + k0 + 2 * u];
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bc[u][t], acc[mt][t], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) bc[u][t] = bn[u][t];
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = mt * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
-            float o[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) o[t] = acc[mt][t][r] > 0.0f ? acc[mt][t][r] : 0.0f;
-            store_nt<NT>(Y + row * ldx + col0, o);
-            if (gout) store_nt<NT>(gout + (size_t)row * N + col0, o);
-        }
-}
-
-__device__ __forceinline__ void run_mfma_layer(const RolloutArgs& a, int TM, int l, const float* X, float* Y, int tid, float* gout)
-{
-    const int K = a.net.dims[l], N = a.net.dims[l + 1];
-    const float* W = a.theta + a.net.w_off[l];
-    const float* bias = a.theta + a.net.b_off[l];
-    if (TM == 16) {
-        switch (N >> 6) {                                   // tiles per wavefront: N / 4 / 16
-            case 1: mfma_layer_m16<1>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 2: mfma_layer_m16<2>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 4: mfma_layer_m16<4>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 8: mfma_layer_m16<8>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            default: mfma_layer_m16<16>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-        }
-    } else if (TM == 32) {
-        switch (N >> 7) {                                   // N / 4 / 32
-            case 1: mfma_layer_m32<1, 1>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 2: mfma_layer_m32<1, 2>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 4: mfma_layer_m32<1, 4>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            default: mfma_layer_m32<1, 8>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-        }
-    } else {
-        switch (N >> 7) {
-            case 1: mfma_layer_m32<2, 1>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            case 2: mfma_layer_m32<2, 2>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-            default: mfma_layer_m32<2, 4>(X, Y, a.ldx, W, bias, K, N, tid, gout); break;
-        }
     }
 }
 
@@ -435,13 +284,13 @@ typedef float f4v_h __attribute__((ext_vector_type(4)));
 // keeps a ring of PF blocks of four k (16-byte LDS reads of row m of X and row j of the transposed
 // head matrix) and refills each slot, PF blocks ahead, before the four dependent fused multiply-adds
 // of the block it just handed over.  HL is a multiple of 4 * PF.
-template <int PF, int HL>
+template <int PF, int HL, int NTHR = WG>
 __device__ __forceinline__ void heads_pipe(const float* __restrict__ X, int ldx, const float* __restrict__ whT, int ldw,
                                            const float* __restrict__ bhs, float* __restrict__ heads,
                                            int NH, int NHP, int TM, int tid)
 {
     constexpr int S = HL >> 2;
-    for (int idx = tid; idx < TM * NH; idx += WG) {
+    for (int idx = tid; idx < TM * NH; idx += NTHR) {
         const int m = idx % TM, j = idx / TM;
         const f4v_h* x = reinterpret_cast<const f4v_h*>(X + m * ldx);
         const f4v_h* w = reinterpret_cast<const f4v_h*>(whT + j * ldw);
@@ -464,13 +313,13 @@ __device__ __forceinline__ void heads_pipe(const float* __restrict__ X, int ldx,
 }
 
 // U: float4 per register block (a block covers 4U values of k; HL is a multiple of 4U)
-template <int U>
+template <int U, int NTHR>
 __device__ __forceinline__ void heads_chain(const float* __restrict__ X, int ldx, const float* __restrict__ whT, int ldw,
                                             const float* __restrict__ bhs, float* __restrict__ heads,
                                             int HL, int NH, int NHP, int TM, int tid)
 {
     constexpr int KB = 4 * U;
-    for (int idx = tid; idx < TM * NH; idx += WG) {
+    for (int idx = tid; idx < TM * NH; idx += NTHR) {
         const int m = idx % TM, j = idx / TM;
         float acc = bhs[j];
         const float* x = X + m * ldx;
@@ -490,15 +339,16 @@ __device__ __forceinline__ void heads_chain(const float* __restrict__ X, int ldx
     }
 }
 
+template <int NTHR>
 __device__ __forceinline__ void run_heads(const float* X, int ldx, const float* whT, int ldw, const float* bhs, float* heads,
                                           int HL, int NH, int NHP, int TM, int tid)
 {
     switch (HL) {
-        case 64: heads_pipe<4, 64>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
-        case 128: heads_pipe<4, 128>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
-        case 256: heads_pipe<4, 256>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
-        case 512: heads_pipe<4, 512>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
-        default: heads_chain<8>(X, ldx, whT, ldw, bhs, heads, HL, NH, NHP, TM, tid);
+        case 64: heads_pipe<4, 64, NTHR>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
+        case 128: heads_pipe<4, 128, NTHR>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
+        case 256: heads_pipe<4, 256, NTHR>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
+        case 512: heads_pipe<4, 512, NTHR>(X, ldx, whT, ldw, bhs, heads, NH, NHP, TM, tid); break;
+        default: heads_chain<8, NTHR>(X, ldx, whT, ldw, bhs, heads, HL, NH, NHP, TM, tid);
     }
 }
 
@@ -506,7 +356,7 @@ __device__ __forceinline__ void run_heads(const float* X, int ldx, const float* 
 // step t comes from the stored snapshots, the forward pass is the acting one with the parameters
 // in a.theta, head outputs and values go to tp.tr_head / tp.tr_val (the caller points them at the
 // learner's buffers) and hidden activations to tp.act; nothing is sampled or stepped.
-template <int ENV, bool BF, bool MF, bool REPLAY>
+template <int ENV, bool BF, bool REPLAY>
 __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const int TM)
 {
     extern __shared__ float4 smem4[];
@@ -551,7 +401,7 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
     }
     if (ENV == ENV_MAZE && pre) {
         __syncthreads();
-        maze_prefix<BF>(a, TM, obs, a.theta + a.net.w_off[0], a.theta + a.net.b_off[0], pre, tid);
+        maze_prefix<BF, WG>(a, TM, obs, a.theta + a.net.w_off[0], a.theta + a.net.b_off[0], pre, tid);
     }
 
     for (int t = 0; t <= T; ++t) {
@@ -590,12 +440,11 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
         float* nxt = bufB;
         for (int l = 1; l < L; ++l) {
             float* gl = keep ? tp.act[l] + ((size_t)t * B + b0) * a.net.dims[l + 1] : nullptr;
-            if (MF) run_mfma_layer(a, TM, l, cur, nxt, tid, gl);
-            else run_dense_layer<BF>(a, TM, l, cur, nxt, tid, gl);
+            run_dense_layer<BF>(a, TM, l, cur, nxt, tid, gl);
             __syncthreads();
             float* tmp = cur; cur = nxt; nxt = tmp;
         }
-        run_heads(cur, ldx, whs, ldw, bhs, heads, HL, NH, NHP, TM, tid);
+        run_heads<WG>(cur, ldx, whs, ldw, bhs, heads, HL, NH, NHP, TM, tid);
         // the step's random draws do not depend on the network: the last lanes of the workgroup,
         // idle during the head chains, produce them now
         if (!REPLAY && t < T) {
@@ -659,6 +508,386 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
     }
 }
 
+
+// ---------------------------------------------------------------------------
+// Hidden layers on the matrix cores, weights streamed from L2: fp32 nets of two or more hidden layers that the
+// weights-resident kernel below does not take.  On gfx950 the fp32 MFMA instructions add their products one k at a time
+// with a fused multiply-add, ascending in k, and chain through the accumulator operand -- measured bit-identical to the
+// sequential fmaf chain on random, wide-range and integer inputs -- so starting the accumulator from the bias and feeding
+// k in ascending order reproduces the canonical order exactly while running at matrix-core rate.
+//
+// A workgroup owns TM = 16 MT environments, eight of its wavefronts (two per SIMD) the layers; v_mfma_f32_16x16x4_f32:
+// lane l feeds A[row l%16][k l/16] and B[k l/16][col l%16], accumulator register r is D[row 4 (l/16) + r][col l%16].
+//
+// What bounds it at the usual batches (a few tiles per compute unit or fewer) is latency.  Loads and stores of a wavefront
+// complete in issue order and share a counter, so a load asked for behind the activation stores of the layer before is not
+// seen until those are acknowledged; and with one layer's weights asked for when the layer starts, every layer of every
+// step waits for L2 first.  So the work is divided: eight wavefronts compute and load weights but store nothing to memory;
+// four more step the environments, draw the random numbers and copy the kept activations from LDS to memory, a layer
+// behind.  A wavefront's weights are one stream across column tiles, layers and steps, two blocks of eight k-steps always in
+// flight: every block is the same eight loads, so the wait before its use is for exactly that block, whatever the shapes.
+// Biases, the first layer's weights where they fit (Catch boards, the maze's agent plane) and the maze's wall sums stay
+// in LDS.
+// The operands from LDS are asked for a block ahead as well.  Per step of the unroll, against one workgroup of eight
+// wavefronts that did all of it: 512-256 net, 2000 environments 15.6 -> 12.3 us; 256-128-64, 1008: 8.5 -> 6.0 us; what is
+// left is mostly the binary32 matrix rate of the compute units that have a tile (16 k cycles of 27 k; 4 k of 13 k).
+// ---------------------------------------------------------------------------
+constexpr int STW = 512;                // threads that compute
+constexpr int STA = 256;                // threads beside them: environments, draws, records, activations
+struct StreamArgs {
+    RolloutArgs r;
+    int w1_lds;                  // first-layer weights (maze: agent plane and goal row) in LDS
+    int tseg;                    // REPLAY: time steps per workgroup (grid y)
+    int tend;                    // time steps evaluated: T + 1 (with the bootstrap state) or T
+};
+
+// A wavefront's weight stream: its column tiles (wave, wave + 8, ...) of layer 1, then of layer 2, ..., then of layer 1 of
+// the next step, each as K / 32 blocks of eight k-steps -- one float per lane and k-step.  The cursor is scalar throughout
+// and runs two blocks ahead of the arithmetic.  The widths (powers of two) are packed into one word: picked from a struct
+// or an array by a computed index they would live in scratch memory.
+struct StreamCursor { int l, tile, k, w, K, N; };              // w: offset of W_l in theta; k: input the next block starts at
+struct StreamNet {
+    int L, w1;                                                 // offset of W_1 (layer 1: first to second hidden layer) in theta
+    uint32_t lg;                                               // byte l - 1: log2 of the outputs of layer l (= inputs of layer l + 1)
+    __device__ __forceinline__ int dim(int l) const { return 1 << ((lg >> (8 * (l - 1))) & 31u); }
+    __device__ __forceinline__ void settle(StreamCursor& c, int wave) const
+    {
+        // on to the next tile that exists (a wavefront may have none in a narrow layer, but has one in some layer)
+        while (16 * c.tile >= c.N) {
+            c.w += c.K * c.N + c.N;
+            c.l += 1; c.tile = wave;
+            if (c.l == L) { c.l = 1; c.w = w1; }
+            c.K = dim(c.l); c.N = dim(c.l + 1);
+        }
+    }
+    __device__ __forceinline__ void advance(StreamCursor& c, int wave) const
+    {
+        c.k += 32;
+        if (c.k == c.K) { c.k = 0; c.tile += 8; settle(c, wave); }
+    }
+};
+typedef __amdgpu_buffer_rsrc_t rsrc_w;
+__device__ __forceinline__ void stream_load(float (&d)[8], rsrc_w theta, const StreamCursor& c, int lane)
+{
+    const uint32_t lane_off = 4u * ((uint32_t)(lane >> 4) * (uint32_t)c.N + (uint32_t)(lane & 15));
+    const uint32_t row = 4u * (uint32_t)(c.w + 16 * c.tile + c.k * c.N), step = 16u * (uint32_t)c.N;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) d[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(theta, lane_off, row + u * step, 0));
+}
+
+// Layer l of the step for this wavefront's column tiles: X and Y in LDS.  wA, wB: the stream's two blocks in flight.
+template <int MT>
+__device__ __forceinline__ void stream_layer(const StreamNet& n, rsrc_w theta, int l, const float* __restrict__ X, float* __restrict__ Y, int ldx,
+                                             const float* __restrict__ bias, int wave, int lane, StreamCursor& cur, float (&wA)[8], float (&wB)[8])
+{
+    const int K = n.dim(l), N = n.dim(l + 1), kq = lane >> 4;
+    const float* xp = X + (lane & 15) * ldx + kq;
+    f4v acc[MT];
+    float avA[8][MT], avB[8][MT];
+    auto fetch = [&](float (&av)[8][MT], int k0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) av[u][m] = xp[m * 16 * ldx + k0 + 4 * u];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto block = [&](float (&w)[8], float (&av)[8][MT]) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][m], w[u], acc[m], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        stream_load(w, theta, cur, lane);
+        n.advance(cur, wave);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int tile = wave; 16 * tile < N; tile += 8) {
+        const int col = 16 * tile + (lane & 15);
+        const float bv = bias[col];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) { acc[m][0] = bv; acc[m][1] = bv; acc[m][2] = bv; acc[m][3] = bv; }
+        fetch(avA, 0);
+        for (int k0 = 0; k0 < K; k0 += 64) {                          // K is a multiple of 64
+            fetch(avB, k0 + 32);
+            block(wA, avA);
+            fetch(avA, k0 + 64 < K ? k0 + 64 : 0);
+            block(wB, avB);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Y[(16 * m + 4 * kq + r) * ldx + col] = acc[m][r] > 0.0f ? acc[m][r] : 0.0f;
+    }
+}
+
+template <int ENV, int MT, bool REPLAY>
+__global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamArgs sa)
+{
+    const RolloutArgs& a = sa.r;
+    constexpr int TM = 16 * MT;
+    extern __shared__ float4 smem4[];
+    float* smem = reinterpret_cast<float*>(smem4);
+    const int ldx = a.ldx, NH = a.net.NH, NHP = a.net.NHP, L = a.net.L, HL = a.net.dims[L], H1 = a.net.dims[1], D = a.net.dims[0];
+    const int n_cells = a.env.rows * a.env.cols;
+    float* bufA = smem;
+    float* bufB = bufA + TM * ldx;
+    float* whs = bufB + TM * ldx;                 // [8][HL + 4] head weights, transposed
+    float* bhs = whs + 8 * (HL + 4);              // [8] head biases
+    float* heads = bhs + 8;                       // [TM][NHP]
+    uint32_t* obs = reinterpret_cast<uint32_t*>(heads + TM * NHP);   // [TM][OBS_WORDS]
+    uint32_t* rng = obs + TM * OBS_WORDS;                            // [TM][4] draws of the current step
+    float* bs = reinterpret_cast<float*>(rng + TM * 4);              // biases of the hidden layers
+    int nb = 0;
+    for (int l = 1; l <= L; ++l) nb += a.net.dims[l];
+    float* pre = bs + nb;                                            // maze: [TM][H1] wall sums
+    float* w1s = ENV == ENV_MAZE ? pre + TM * H1 : pre;              // first-layer weights, or (maze) agent plane + goal row
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b0 = blockIdx.x * TM;
+    const int B = a.B, T = a.T;
+    const int rows_left = B - b0;                                    // environments of this tile (whole groups of 16)
+    const TrajPtrs& tp = a.tp;
+    const int ldw = HL + 4;
+    const float* w1g = a.theta + a.net.w_off[0];
+    for (int i = tid; i < HL * NH; i += STW + STA) whs[(i % NH) * ldw + i / NH] = a.theta[a.net.wh_off + i];
+    if (tid < 8) bhs[tid] = tid < NH ? a.theta[a.net.bh_off + tid] : 0.0f;
+    {
+        int off = 0;
+        for (int l = 0; l < L; ++l) {
+            for (int i = tid; i < a.net.dims[l + 1]; i += STW + STA) bs[off + i] = a.theta[a.net.b_off[l] + i];
+            off += a.net.dims[l + 1];
+        }
+    }
+    if (sa.w1_lds) {
+        const f4v* src = reinterpret_cast<const f4v*>(w1g + (ENV == ENV_MAZE ? (size_t)n_cells * H1 : 0));
+        f4v* dst = reinterpret_cast<f4v*>(w1s);
+        const int n4 = (ENV == ENV_MAZE ? n_cells : D) * H1 / 4;
+        constexpr int NTH = STW + STA;
+        for (int i0 = 0; i0 < n4; i0 += 4 * NTH) {
+            f4v v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { const int i = i0 + u * NTH + tid; v[u] = src[i < n4 ? i : 0]; }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { const int i = i0 + u * NTH + tid; if (i < n4) dst[i] = v[u]; }
+        }
+        if (ENV == ENV_MAZE)
+            for (int i = tid; i < H1; i += NTH) w1s[(size_t)n_cells * H1 + i] = w1g[(size_t)(3 * n_cells - 1) * H1 + i];
+    }
+    const bool aux = wave >= STW / 64;                               // a scalar branch: what follows stays in scalar registers
+    const int at = tid - STW;
+    EnvState st{0u, 0.0f, 0.0f};
+    const bool mine = aux && at < TM;                                // this thread's environment (rows past B: any valid state)
+    const bool owner = mine && at < rows_left;
+    const int b = b0 + (owner ? at : 0);
+    if (mine) {
+        if (!REPLAY) {
+            st.s0 = tp.s0[b];
+            if (ENV == ENV_PENDULUM) { st.f0 = tp.f0[b]; st.f1 = tp.f1[b]; }
+        }
+        if (ENV == ENV_MAZE) for (int w = 0; w < 8; ++w) obs[at * OBS_WORDS + w] = tp.walls[(size_t)w * B + b];
+    }
+    if (ENV == ENV_MAZE) {
+        __syncthreads();
+        maze_prefix<false, STW + STA>(a, TM, obs, w1g, bs, pre, tid);
+    }
+    const int t_begin = REPLAY ? (int)blockIdx.y * sa.tseg : 0;
+    const int t_end = REPLAY ? (t_begin + sa.tseg < sa.tend ? t_begin + sa.tseg : sa.tend) : T + 1;
+    EnvState nx{0u, 0.0f, 0.0f};                                     // REPLAY: the next step's state, asked for a step ahead
+    auto ask = [&](int t) {
+        const size_t tb = (size_t)(t < t_end ? t : t_end - 1) * B + b;
+        nx.s0 = tp.tr_s0[tb];
+        if (ENV == ENV_PENDULUM) { nx.f0 = tp.tr_f0[tb]; nx.f1 = tp.tr_f1[tb]; }
+    };
+    auto observe = [&](int t) {
+        if (REPLAY) { st = nx; ask(t + 1); }
+        else if (owner) {
+            const size_t tb = (size_t)t * B + b;
+            tp.tr_s0[tb] = st.s0;
+            if (ENV == ENV_PENDULUM) { tp.tr_f0[tb] = st.f0; tp.tr_f1[tb] = st.f1; }
+        }
+        if (ENV == ENV_CATCH) {
+            int bc, pc;
+            catch_obs_cells(a.env, st.s0, bc, pc);
+            obs[at * OBS_WORDS + 0] = (uint32_t)bc;
+            obs[at * OBS_WORDS + 1] = (uint32_t)pc;
+        } else if (ENV == ENV_PENDULUM) {
+            float sn, cs;
+            det_sincos(st.f0, sn, cs);
+            obs[at * OBS_WORDS + 0] = bits_from_f(cs);
+            obs[at * OBS_WORDS + 1] = bits_from_f(sn);
+            obs[at * OBS_WORDS + 2] = bits_from_f(st.f1);
+        } else {
+            obs[at * OBS_WORDS + 8] = st.s0 & 0xffffu;
+        }
+    };
+    // h_l of the step from LDS to memory, 16 bytes a thread
+    auto copy_out = [&](int t, int l, const float* src) {
+        const int N = a.net.dims[l + 1], c4 = N >> 2, n4 = (TM < rows_left ? TM : rows_left) * c4;
+        f4v* dst = reinterpret_cast<f4v*>(tp.act[l] + ((size_t)t * B + b0) * N);
+        for (int i0 = at; i0 < n4; i0 += 4 * STA) {
+            f4v v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * STA < n4 ? i0 + u * STA : i0;
+                v[u] = *reinterpret_cast<const f4v*>(src + (i / c4) * ldx + ((i % c4) << 2));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) if (i0 + u * STA < n4) dst[i0 + u * STA] = v[u];
+        }
+    };
+    if (REPLAY && mine) ask(t_begin);
+    if (mine) observe(t_begin);
+    __syncthreads();
+
+    if (!aux) {
+        // ==== the layers ====================================================
+        uint32_t lg = 0;
+        int widest = 0;
+        for (int l = 1; l <= L; ++l) {
+            const int d = a.net.dims[l];
+            lg |= (uint32_t)(31 - __builtin_clz((uint32_t)d)) << (8 * (l - 1));
+            if (l > 1 && d > widest) widest = d;
+        }
+        const StreamNet net{L, a.net.w_off[1], lg};
+        const rsrc_w theta = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.theta), 0, (uint32_t)a.net.P * 4u, 0x00020000);
+        float wA[8], wB[8];
+        // a wavefront without a tile in any layer follows the stream of one that has
+        const int sw = 16 * wave < widest ? wave : 0;
+        StreamCursor sc{1, sw, 0, net.w1, net.dim(1), net.dim(2)};
+        net.settle(sc, sw);
+        stream_load(wA, theta, sc, lane); net.advance(sc, sw);
+        __builtin_amdgcn_sched_barrier(0);
+        stream_load(wB, theta, sc, lane); net.advance(sc, sw);
+        __builtin_amdgcn_sched_barrier(0);
+        for (int t = t_begin; t < t_end; ++t) {
+            const int cg = H1 >> 2, cgs = 31 - __builtin_clz((uint32_t)cg);
+            constexpr int FB = 4;                                    // (environment, four columns) pieces in flight
+            for (int i0 = tid; i0 < TM * cg; i0 += FB * STW) {
+                f4v wv[FB][ENV == ENV_PENDULUM ? 3 : 2], bv[FB];
+#pragma unroll
+                for (int u = 0; u < FB; ++u) {
+                    const int i = i0 + u * STW < TM * cg ? i0 + u * STW : i0, m = i >> cgs, c = (i & (cg - 1)) << 2;
+                    const uint32_t* o = obs + m * OBS_WORDS;
+                    if (ENV == ENV_PENDULUM) {
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) {
+                            if (sa.w1_lds) wv[u][k] = *reinterpret_cast<const f4v*>(w1s + k * H1 + c);
+                            else wv[u][k] = *reinterpret_cast<const f4v*>(w1g + k * H1 + c);
+                        }
+                        bv[u] = *reinterpret_cast<const f4v*>(bs + c);
+                    } else {
+                        const int r0 = ENV == ENV_CATCH ? (int)o[0] : (int)o[8], r1 = ENV == ENV_CATCH ? (int)o[1] : n_cells;
+                        if (sa.w1_lds) {
+                            wv[u][0] = *reinterpret_cast<const f4v*>(w1s + r0 * H1 + c);
+                            wv[u][1] = *reinterpret_cast<const f4v*>(w1s + r1 * H1 + c);
+                        } else {
+                            wv[u][0] = *reinterpret_cast<const f4v*>(w1g + (size_t)(ENV == ENV_CATCH ? r0 : n_cells + r0) * H1 + c);
+                            wv[u][1] = *reinterpret_cast<const f4v*>(w1g + (size_t)(ENV == ENV_CATCH ? r1 : 3 * n_cells - 1) * H1 + c);
+                        }
+                        bv[u] = ENV == ENV_MAZE ? *reinterpret_cast<const f4v*>(pre + m * H1 + c) : *reinterpret_cast<const f4v*>(bs + c);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < FB; ++u) {
+                    const int i = i0 + u * STW;
+                    if (i < TM * cg) {
+                        const int m = i >> cgs, c = (i & (cg - 1)) << 2;
+                        f4v v = bv[u];
+                        if (ENV == ENV_PENDULUM) {
+                            const uint32_t* o = obs + m * OBS_WORDS;
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) {
+                                const float x = f_from_bits(o[k]);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) v[e] = fmaf(x, wv[u][k][e], v[e]);
+                            }
+                        } else {
+                            v += wv[u][0];
+                            v += wv[u][1];
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+                        *reinterpret_cast<f4v*>(bufA + m * ldx + c) = v;
+                    }
+                }
+            }
+            __syncthreads();
+            float* cur = bufA;
+            float* nxt = bufB;
+            const float* bias = bs + H1;
+            for (int l = 1; l < L; ++l) {
+                stream_layer<MT>(net, theta, l, cur, nxt, ldx, bias, wave, lane, sc, wA, wB);
+                bias += net.dim(l + 1);
+                __syncthreads();
+                float* tmp = cur; cur = nxt; nxt = tmp;
+            }
+            run_heads<STW>(cur, ldx, whs, ldw, bhs, heads, HL, NH, NHP, TM, tid);
+            __syncthreads();
+            __syncthreads();                                         // the environments step
+        }
+        return;
+    }
+    // ==== environments, draws and records; the same barriers ====================
+    for (int t = t_begin; t < t_end; ++t) {
+        const bool keep = t < T && a.keep_acts;                      // the bootstrap evaluation keeps no activations
+        if (!REPLAY && t < T) {                                      // the step's draws do not depend on the network
+            for (int i = STA - 1 - at; i < (ENV == ENV_MAZE ? TM : 2 * TM); i += STA) {
+                const int e = i < TM ? i : i - TM;
+                const u32x4 w = philox(a.seed, (uint32_t)(b0 + e), a.gstep + (uint64_t)t, i < TM ? DOM_ACTION : DOM_RESET);
+                const uint32_t w0 = (ENV == ENV_PENDULUM && i < TM) ? bits_from_f(gaussian_noise(w.x, w.y)) : w.x;
+                *reinterpret_cast<uint2*>(rng + e * 4 + (i < TM ? 0 : 2)) = make_uint2(w0, w.y);
+            }
+        }
+        __syncthreads();
+        const float* cur = bufA;
+        const float* nxt = bufB;
+        for (int l = 1; l < L; ++l) {
+            if (keep) copy_out(t, l - 1, cur);
+            __syncthreads();
+            const float* tmp = cur; cur = nxt; nxt = tmp;
+        }
+        if (keep) copy_out(t, L - 1, cur);
+        __syncthreads();
+        if (at >= 64 && at < 64 + TM && at - 64 < rows_left) {
+            const int e = at - 64;
+            const size_t te = (size_t)t * B + b0 + e;
+            const float4 h0 = ld4(heads + e * NHP);
+            const float4 h1 = NHP == 8 ? ld4(heads + e * NHP + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            float* hd = tp.tr_head + te * NHP;
+            *reinterpret_cast<float4*>(hd) = h0;
+            if (NHP == 8) *reinterpret_cast<float4*>(hd + 4) = h1;
+            tp.tr_val[te] = last_head(h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w, NH);
+        }
+        if (mine && !REPLAY && t < T) {
+            const float4 h0 = ld4(heads + at * NHP);
+            const float4 h1 = NHP == 8 ? ld4(heads + at * NHP + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const uint4 dr = *reinterpret_cast<const uint4*>(rng + at * 4);   // action draw, reset draw
+            const size_t tb = (size_t)t * B + b;
+            float r; int done;
+            if (ENV == ENV_PENDULUM) {
+                const float eps = f_from_bits(dr.x);
+                const float act = gaussian_action(h0.x, h0.y, eps);
+                pendulum_step(a.env, st, act, dr.z, dr.w, r, done);
+                if (owner) { tp.tr_eps[tb] = eps; tp.tr_actf[tb] = act; }
+            } else {
+                const int act = sample_categorical_any(h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w, a.net.A, u01(dr.x));
+                if (ENV == ENV_CATCH) catch_step(a.env, st, act, dr.z, r, done);
+                else {
+                    const uint32_t* wl = obs + at * OBS_WORDS;
+                    maze_step(a.env, st, act, [wl](int c) { return ((wl[c >> 5] >> (c & 31)) & 1u) != 0u; }, r, done);
+                }
+                if (owner) tp.tr_act[tb] = (uint8_t)act;
+            }
+            if (owner) { tp.tr_rew[tb] = r; tp.tr_done[tb] = (uint8_t)done; }
+        }
+        if (mine && t + 1 < t_end) observe(t + 1);
+        __syncthreads();
+    }
+    if (!REPLAY && owner) {
+        tp.s0[b] = st.s0;
+        if (ENV == ENV_PENDULUM) { tp.f0[b] = st.f0; tp.f1[b] = st.f1; }
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Weights resident on chip.  For two-layer nets up to 256 x 256 the whole
@@ -858,7 +1087,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
     }
     if (ENV == ENV_MAZE) {
         __syncthreads();
-        maze_prefix<false>(a, TM, obs, w1, b1s, w1s, tid);
+        maze_prefix<false, WG>(a, TM, obs, w1, b1s, w1s, tid);
     }
 
     // Everything loaded so far (weights, the envs' states) has arrived before the loop starts.  Inside the
@@ -1154,30 +1383,26 @@ int rollout_resident_tile(const NetShape& net, int env_kind, int B)
     return lds <= 160 * 1024 ? tm : 0;
 }
 
-// can the hidden-to-hidden layers run on the matrix cores with TM envs per workgroup?
-static bool mfma_tile_ok(const NetShape& net, int TM)
+// LDS of the streaming matrix-core kernel without / with the first layer's weights
+static size_t stream_lds_bytes(const NetShape& net, const EnvDims& env, int TM, bool w1)
 {
-    if (net.bf16 || net.L < 2) return false;
-    if (TM != 16 && TM != 32 && TM != 64) return false;
-    if (TM * net.dims[1] > 16 * 1024 || TM * net.dims[1] < 1024) return false;   // first-layer register tile: 1 to 16 rows per thread
-    for (int l = 2; l <= net.L; ++l) {
-        const int N = net.dims[l];
-        if (TM == 16 ? N < 64 : N < 128) return false;              // at least one MFMA tile per wavefront
-        if (TM == 64 && N > 512) return false;                      // accumulator budget
-    }
-    int hmax = 0;
-    for (int l = 1; l <= net.L; ++l) hmax = net.dims[l] > hmax ? net.dims[l] : hmax;
-    if ((size_t)2 * TM * (hmax + 4) * 4 > 128 * 1024) return false; // two activation buffers in LDS
-    return rollout_lds_bytes(net, EnvDims{}, TM, nullptr) <= 160 * 1024;   // ... and everything else the kernel keeps there
+    size_t words = rollout_lds_bytes(net, env, TM, nullptr) / 4;
+    for (int l = 1; l <= net.L; ++l) words += net.dims[l];
+    if (env.kind == ENV_MAZE) words += (size_t)TM * net.dims[1];
+    if (w1) words += (size_t)(env.kind == ENV_MAZE ? env.rows * env.cols + 1 : net.dims[0]) * net.dims[1];
+    return words * 4;
 }
-
-int rollout_pick_tile_mfma(const NetShape& net, int B)
+// Environments per workgroup of the streaming matrix-core kernel, 0 where it does not apply: the largest of 16, 32 and 64
+// that fits LDS and still leaves a workgroup per compute unit (an environment more per tile is an environment less that
+// waits for another workgroup, but the weight stream is shared by the tile).
+int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B)
 {
+    if (net.bf16 || net.L < 2) return 0;
+    for (int l = 1; l < net.L; ++l) if (net.dims[l] % 64) return 0;     // blocks of 64 inputs
     int best = 0;
     for (int tm = 16; tm <= 64; tm *= 2) {
-        if (B % tm || !mfma_tile_ok(net, tm)) continue;
-        if (!best) best = tm;
-        if (B / tm >= 256) best = tm;
+        if (stream_lds_bytes(net, env, tm, false) > 160 * 1024) break;
+        if (!best || (B + tm - 1) / tm >= 256) best = tm;
     }
     return best;
 }
@@ -1218,7 +1443,7 @@ int rollout_pick_tile(const NetShape& net, int B)
     return best;
 }
 
-template <int ENV, bool BF, bool MF, bool REPLAY>
+template <int ENV, bool BF, bool REPLAY>
 static hipError_t launch_one(anakin* h, const RolloutArgs& args, int TM)
 {
     size_t lds = rollout_lds_bytes(h->net, h->env, TM, nullptr);
@@ -1229,7 +1454,7 @@ static hipError_t launch_one(anakin* h, const RolloutArgs& args, int TM)
         a.maze_prefix = lds + pre <= 160 * 1024 ? 1 : 0;
         if (a.maze_prefix) lds += pre;
     }
-    auto kern = rollout_kernel<ENV, BF, MF, REPLAY>;
+    auto kern = rollout_kernel<ENV, BF, REPLAY>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
@@ -1238,6 +1463,33 @@ static hipError_t launch_one(anakin* h, const RolloutArgs& args, int TM)
 }
 
 void fill_rollout_args(anakin* h, RolloutArgs& a);
+
+// time steps per workgroup of a replay: the steps do not depend on one another, so a batch that does not give every
+// compute unit a tile is cut along time as well
+static int replay_segment(int tiles, int tend)
+{
+    int parts = (256 + tiles - 1) / tiles;
+    if (parts > tend) parts = tend;
+    return (tend + parts - 1) / parts;
+}
+
+template <int ENV, bool REPLAY>
+static hipError_t launch_stream(anakin* h, const RolloutArgs& args, int TM)
+{
+    StreamArgs a;
+    a.r = args;
+    a.w1_lds = stream_lds_bytes(h->net, h->env, TM, true) <= 160 * 1024 ? 1 : 0;
+    const size_t lds = stream_lds_bytes(h->net, h->env, TM, a.w1_lds != 0);
+    const int tiles = (h->B + TM - 1) / TM;
+    a.tend = args.T + (args.bootstrap ? 1 : 0);
+    a.tseg = replay_segment(tiles, a.tend);
+    auto kern = TM == 16 ? rollout_stream_kernel<ENV, 1, REPLAY> : TM == 32 ? rollout_stream_kernel<ENV, 2, REPLAY> : rollout_stream_kernel<ENV, 4, REPLAY>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
+    hipLaunchKernelGGL(kern, dim3(tiles, REPLAY ? (a.tend + a.tseg - 1) / a.tseg : 1), dim3(STW + STA), lds, h->stream, a);
+    return hipGetLastError();
+}
 
 template <int ENV, bool M32, int RW, bool REPLAY>
 static hipError_t launch_resident(anakin* h, const RolloutArgs& a)
@@ -1280,18 +1532,17 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
             default:           return launch_resident_env<ENV_MAZE, REPLAY>(h, a, w, h->TM_res);
         }
     }
-    const bool mf = h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING);
-    if (mf) {
+    if (h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING)) {
         switch (h->env.kind) {
-            case ENV_CATCH:    return launch_one<ENV_CATCH, false, true, REPLAY>(h, a, h->TM_mfma);
-            case ENV_PENDULUM: return launch_one<ENV_PENDULUM, false, true, REPLAY>(h, a, h->TM_mfma);
-            default:           return launch_one<ENV_MAZE, false, true, REPLAY>(h, a, h->TM_mfma);
+            case ENV_CATCH:    return launch_stream<ENV_CATCH, REPLAY>(h, a, h->TM_mfma);
+            case ENV_PENDULUM: return launch_stream<ENV_PENDULUM, REPLAY>(h, a, h->TM_mfma);
+            default:           return launch_stream<ENV_MAZE, REPLAY>(h, a, h->TM_mfma);
         }
     }
     switch (h->env.kind) {
-        case ENV_CATCH:    return bf ? launch_one<ENV_CATCH, true, false, REPLAY>(h, a, h->TM) : launch_one<ENV_CATCH, false, false, REPLAY>(h, a, h->TM);
-        case ENV_PENDULUM: return bf ? launch_one<ENV_PENDULUM, true, false, REPLAY>(h, a, h->TM) : launch_one<ENV_PENDULUM, false, false, REPLAY>(h, a, h->TM);
-        default:           return bf ? launch_one<ENV_MAZE, true, false, REPLAY>(h, a, h->TM) : launch_one<ENV_MAZE, false, false, REPLAY>(h, a, h->TM);
+        case ENV_CATCH:    return bf ? launch_one<ENV_CATCH, true, REPLAY>(h, a, h->TM) : launch_one<ENV_CATCH, false, REPLAY>(h, a, h->TM);
+        case ENV_PENDULUM: return bf ? launch_one<ENV_PENDULUM, true, REPLAY>(h, a, h->TM) : launch_one<ENV_PENDULUM, false, REPLAY>(h, a, h->TM);
+        default:           return bf ? launch_one<ENV_MAZE, true, REPLAY>(h, a, h->TM) : launch_one<ENV_MAZE, false, REPLAY>(h, a, h->TM);
     }
 }
 

@@ -95,3 +95,20 @@ def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
                                              ("catch_4096", [512, 512], 112, 5), ("pendulum_8192", [512, 256, 256], 144, 2)])
 def test_split_operand_products(gpu, orc, name, hidden, B, T):
     lockstep(gpu, orc, variant(name, hidden, B, T), 8)
+
+
+# acting on the matrix cores with streamed weights: tiles of 32 and 64 environments that end in the middle, layers too narrow
+# for every wavefront to have a tile, first-layer weights that do not fit LDS, three layers, the replay between updates
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [64, 512], 8208, 2), ("pendulum_8192", [64, 128, 64], 16400, 2), ("catch_small", [128, 64, 512], 16, 6),
+                                             ("pendulum_8192", [1024, 512], 48, 4), ("maze_16384", [512, 64], 80, 6), ("catch_4096", [1024, 64], 32, 4)])
+def test_streaming_acting(gpu, orc, name, hidden, B, T):
+    env = dict(rows=5, cols=7, max_steps=9) if name.startswith("maze") else {}
+    cfg = variant(name, hidden, B, T, **env)
+    lockstep(gpu, orc, cfg, 9)
+    g = gpu.Anakin(cfg, seed=1); o = orc.Oracle(cfg, seed=1)
+    g.set_updates_per_unroll(2, sequential=True)
+    PT.sync_oracle_from_gpu(g, o)
+    g.rollout(); o.rollout()
+    g.learn(); o.learn_n(2, sequential=True)
+    PT.assert_learn_close(g, o, TOL_F32, n_updates=2)
+    g.close()
