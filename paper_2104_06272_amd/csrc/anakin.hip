@@ -619,15 +619,6 @@ extern "C" int32_t anakin_learn(anakin_t* h)
     const int full_sw = h->splits_w, full_fan = h->head_fan, full_lb = h->loss_blocks;
     int32_t rc = ANAKIN_OK;
     for (int k = 0; k < h->n_updates && rc == ANAKIN_OK; ++k) {
-        if (seq && k > 0) {
-            // sequential reading: the chunk's gradient is taken at the parameters as they are now, so the forward
-            // pass over the stored states is repeated with them (activations, head outputs, values; for the Gaussian
-            // policy also the noise that reproduces the stored sample), on the whole unroll's layout
-            h->lay = full; h->T = T;
-            hipError_t e = bf16_mfma(h) ? launch_replay_bf16(h) : launch_replay_forward(h);
-            if (e == hipSuccess) e = launch_eps_now(h);
-            if (e != hipSuccess) { h->err = std::string("replay of the forward pass: ") + hipGetErrorString(e); rc = ANAKIN_E_HIP; break; }
-        }
         for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = h->sub_splits[l]; h->quanta[l] = h->sub_quanta[l]; }
         h->splits_w = h->sub_splits_w; h->head_fan = h->sub_head_fan; h->loss_blocks = h->sub_loss_blocks;
         h->T = Ts;
@@ -636,7 +627,7 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         L = full;
         if (seq) {
             L.w_src = full.theta; L.w16_src = full.w_bf16;
-            if (k > 0) { L.tr_head = full.head_new; L.tr_eps = full.eps_new; }
+            L.head_new += r0 * n.NHP * 4; L.val_new += r0 * 4; L.eps_new += r0 * 4;
         } else {
             L.w_src = full.theta0; L.w16_src = n.bf16 ? full.w0_bf16 : full.w_bf16;
         }
@@ -646,6 +637,15 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         L.adv += r0 * 4; L.ret += r0 * 4;
         for (int l = 0; l < n.L; ++l) { L.act[l] += r0 * n.dims[l + 1] * (h->traj_packed ? 2 : 4); L.mask[l] += r0 * n.dims[l + 1] / 4; }
         L.loss_part += (size_t)k * h->sub_loss_blocks * 8 * 4;
+        if (seq && k > 0) {
+            // sequential reading: the chunk's gradient is taken at the parameters as they are now, so the forward
+            // pass over the chunk's stored states is repeated with them (activations, head outputs; for the Gaussian
+            // policy also the noise that reproduces the stored sample)
+            hipError_t e = bf16_mfma(h) ? launch_replay_bf16(h, false) : launch_replay_forward(h, false);
+            if (e == hipSuccess) e = launch_eps_now(h);
+            if (e != hipSuccess) { h->err = std::string("replay of the forward pass: ") + hipGetErrorString(e); rc = ANAKIN_E_HIP; break; }
+            L.tr_head = L.head_new; L.tr_eps = L.eps_new;
+        }
         rc = run_update(h);
         for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = full_splits[l]; h->quanta[l] = full_quanta[l]; }
         h->splits_w = full_sw; h->head_fan = full_fan; h->loss_blocks = full_lb;
@@ -778,7 +778,7 @@ extern "C" int32_t anakin_step_decoupled(anakin_t* h)
     // behind the actor, so an error leaves the handle consistent and the fresh unroll usable.
     auto learner_update = [&]() -> int32_t {
         if (!h->have_traj) return ANAKIN_OK;
-        HIPCHK(h, mc ? launch_replay_bf16(h) : launch_replay_forward(h));
+        HIPCHK(h, mc ? launch_replay_bf16(h, true) : launch_replay_forward(h, true));
         HIPCHK(h, launch_vtrace(h));
         const int no_acts = h->traj_no_acts;
         h->traj_packed = mc ? 1 : 0; h->traj_no_acts = one_layer_fused(h) ? 1 : 0;

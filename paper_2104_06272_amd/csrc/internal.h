@@ -213,7 +213,16 @@ hipError_t prof_resolve(anakin* h);
 // kernel launchers (each enqueues on h->stream and returns the HIP status)
 hipError_t launch_rollout(anakin* h);
 hipError_t launch_rollout_behaviour(anakin* h);
-hipError_t launch_replay_forward(anakin* h);
+hipError_t launch_replay_forward(anakin* h, bool bootstrap);
+// time steps per workgroup of a replay: the steps do not depend on one another, so a batch that does not give every
+// compute unit a tile is cut along time as well
+inline int replay_segment(int tiles, int tend)
+{
+    int parts = 256 / tiles;
+    if (parts < 1) parts = 1;
+    if (parts > tend) parts = tend;
+    return (tend + parts - 1) / parts;
+}
 hipError_t launch_vtrace(anakin* h);
 hipError_t launch_eps_now(anakin* h);
 hipError_t launch_pathwise(anakin* h);
@@ -237,7 +246,7 @@ inline bool one_layer_fused(const anakin* h) { return h->net.L == 1 && h->env.ki
 hipError_t launch_partial_reduce(const float* src, float* dst, int count, int fan, int splits, hipStream_t s);
 hipError_t launch_rollout_bf16(anakin* h);
 hipError_t launch_rollout_bf16_behaviour(anakin* h);
-hipError_t launch_replay_bf16(anakin* h);
+hipError_t launch_replay_bf16(anakin* h, bool bootstrap);
 hipError_t launch_backward_bf16(anakin* h);
 hipError_t launch_refresh_bf16(anakin* h);
 int bf16_dx_rows_per_workgroup(int M, int K, int N);

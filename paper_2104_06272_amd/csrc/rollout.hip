@@ -404,7 +404,8 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
         maze_prefix<BF, WG>(a, TM, obs, a.theta + a.net.w_off[0], a.theta + a.net.b_off[0], pre, tid);
     }
 
-    for (int t = 0; t <= T; ++t) {
+    const int t_end = REPLAY ? T + a.bootstrap : T + 1;
+    for (int t = 0; t < t_end; ++t) {
         const size_t tb = (size_t)t * B + b;
         // ---- observe -------------------------------------------------------
         if (owner) {
@@ -981,7 +982,7 @@ __device__ __forceinline__ void resident_m32(const float (&wreg)[KS][NT], const 
 
 
 // RK x RN: shape of the resident hidden-to-hidden layer; M32: 32 envs per workgroup, else 16
-template <int ENV, bool M32, int RK, int RN, bool REPLAY>
+template <int ENV, bool M32, int RK, int RN>
 __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs a)
 {
     constexpr int TM = M32 ? 32 : 16;
@@ -1077,10 +1078,8 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
     const bool owner = tid < TM;
     const int b = b0 + tid;
     if (owner) {
-        if (!REPLAY) {
-            st.s0 = tp.s0[b];
-            if (ENV == ENV_PENDULUM) { st.f0 = tp.f0[b]; st.f1 = tp.f1[b]; }
-        }
+        st.s0 = tp.s0[b];
+        if (ENV == ENV_PENDULUM) { st.f0 = tp.f0[b]; st.f1 = tp.f1[b]; }
         if (ENV == ENV_MAZE) {
             for (int w = 0; w < 8; ++w) obs[tid * OBS_WORDS + w] = tp.walls[(size_t)w * B + b];
         }
@@ -1093,18 +1092,13 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
     // Everything loaded so far (weights, the envs' states) has arrived before the loop starts.  Inside the
     // loop the acting path then only stores to memory, and no step waits for an earlier step's stores: a
     // wait for a load would be a wait for every older store of the wavefront as well.
-    if (!REPLAY) __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
 
     for (int t = 0; t <= T; ++t) {
         const size_t tb = (size_t)t * B + b;
         if (owner) {
-            if (REPLAY) {
-                st.s0 = tp.tr_s0[tb];
-                if (ENV == ENV_PENDULUM) { st.f0 = tp.tr_f0[tb]; st.f1 = tp.tr_f1[tb]; }
-            } else {
-                tp.tr_s0[tb] = st.s0;
-                if (ENV == ENV_PENDULUM) { tp.tr_f0[tb] = st.f0; tp.tr_f1[tb] = st.f1; }
-            }
+            tp.tr_s0[tb] = st.s0;
+            if (ENV == ENV_PENDULUM) { tp.tr_f0[tb] = st.f0; tp.tr_f1[tb] = st.f1; }
             if (ENV == ENV_CATCH) {
                 int bc, pc;
                 catch_obs_cells(a.env, st.s0, bc, pc);
@@ -1133,7 +1127,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
         // the step's random draws do not depend on the network: the last lanes of the workgroup,
         // idle during the head chains, produce them now -- the action draw of every env and the draw
         // that places the next episode, which then costs nothing where an episode ends
-        if (!REPLAY && t < T) {
+        if (t < T) {
             for (int i = WG - 1 - tid; i < (ENV == ENV_MAZE ? TM : 2 * TM); i += WG) {
                 const int e = i < TM ? i : i - TM;
                 const u32x4 w = philox(a.seed, (uint32_t)(b0 + e), a.gstep + (uint64_t)t, i < TM ? DOM_ACTION : DOM_RESET);
@@ -1161,7 +1155,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
             const float4 h0 = ld4(heads + tid * NHP);
             const float4 h1 = NHP == 8 ? ld4(heads + tid * NHP + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             const float hv[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-            if (!REPLAY && t < T) {
+            if (t < T) {
                 const uint4 dr = *reinterpret_cast<const uint4*>(rng + tid * 4);   // action draw, reset draw
                 float r; int done;
                 if (ENV == ENV_PENDULUM) {
@@ -1185,7 +1179,7 @@ __global__ __launch_bounds__(WG) void rollout_resident_kernel(const RolloutArgs 
             }
         }
     }
-    if (!REPLAY && owner) {
+    if (owner) {
         tp.s0[b] = st.s0;
         if (ENV == ENV_PENDULUM) { tp.f0[b] = st.f0; tp.f1[b] = st.f1; }
     }
@@ -1252,7 +1246,8 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
         st.s0 = tp.s0[b];
         if (ENV == ENV_PENDULUM) { st.f0 = tp.f0[b]; st.f1 = tp.f1[b]; }
     }
-    for (int t = 0; t <= T; ++t) {
+    const int t_end = REPLAY ? T + a.bootstrap : T + 1;
+    for (int t = 0; t < t_end; ++t) {
         const size_t tb = (size_t)t * B + b;
         if (REPLAY) {
             st.s0 = tp.tr_s0[tb];
@@ -1464,13 +1459,19 @@ static hipError_t launch_one(anakin* h, const RolloutArgs& args, int TM)
 
 void fill_rollout_args(anakin* h, RolloutArgs& a);
 
-// time steps per workgroup of a replay: the steps do not depend on one another, so a batch that does not give every
-// compute unit a tile is cut along time as well
-static int replay_segment(int tiles, int tend)
+// environments per workgroup of the replay: with the steps spread over workgroups as well every size can fill the chip, so
+// the one that ends first -- the longest share of steps per compute unit times the rows of a step, and about eight rows'
+// time that a step costs at any size
+static int replay_tile(const anakin* h, int tend)
 {
-    int parts = (256 + tiles - 1) / tiles;
-    if (parts > tend) parts = tend;
-    return (tend + parts - 1) / parts;
+    int best = 16;
+    long best_cost = 0;
+    for (int tm = 16; tm <= 64 && stream_lds_bytes(h->net, h->env, tm, false) <= 160 * 1024; tm *= 2) {
+        const int tiles = (h->B + tm - 1) / tm, tseg = replay_segment(tiles, tend);
+        const long wgs = (long)tiles * ((tend + tseg - 1) / tseg), cost = (wgs + 255) / 256 * tseg * (tm + 8);
+        if (!best_cost || cost <= best_cost) { best = tm; best_cost = cost; }
+    }
+    return best;
 }
 
 template <int ENV, bool REPLAY>
@@ -1491,27 +1492,27 @@ static hipError_t launch_stream(anakin* h, const RolloutArgs& args, int TM)
     return hipGetLastError();
 }
 
-template <int ENV, bool M32, int RW, bool REPLAY>
+template <int ENV, bool M32, int RW>
 static hipError_t launch_resident(anakin* h, const RolloutArgs& a)
 {
     constexpr int TM = M32 ? 32 : 16;
     size_t lds = rollout_lds_bytes(h->net, h->env, TM, nullptr);
     lds += (size_t)2 * RW * 4;                                     // the hidden layers' biases
     lds += (size_t)(ENV == ENV_MAZE ? TM : h->net.dims[0]) * RW * 4;
-    auto kern = rollout_resident_kernel<ENV, M32, RW, RW, REPLAY>;
+    auto kern = rollout_resident_kernel<ENV, M32, RW, RW>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
+    ProfScope prof(h, "rollout");
     hipLaunchKernelGGL(kern, dim3(h->B / TM), dim3(WG), lds, h->stream, a);
     return hipGetLastError();
 }
 
-template <int ENV, bool REPLAY>
+template <int ENV>
 static hipError_t launch_resident_env(anakin* h, const RolloutArgs& a, int width, int tm)
 {
-    if (width == 256) return tm == 32 ? launch_resident<ENV, true, 256, REPLAY>(h, a) : launch_resident<ENV, false, 256, REPLAY>(h, a);
-    if (width == 128) return tm == 32 ? launch_resident<ENV, true, 128, REPLAY>(h, a) : launch_resident<ENV, false, 128, REPLAY>(h, a);
-    return launch_resident<ENV, false, 64, REPLAY>(h, a);
+    if (width == 256) return tm == 32 ? launch_resident<ENV, true, 256>(h, a) : launch_resident<ENV, false, 256>(h, a);
+    if (width == 128) return tm == 32 ? launch_resident<ENV, true, 128>(h, a) : launch_resident<ENV, false, 128>(h, a);
+    return launch_resident<ENV, false, 64>(h, a);
 }
 
 template <bool REPLAY>
@@ -1524,19 +1525,20 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
             return lw == 32 ? launch_lane<ENV_PENDULUM, 32, REPLAY>(h, a) : launch_lane<ENV_PENDULUM, 64, REPLAY>(h, a);
         }
     }
-    if (h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
+    if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
         switch (h->env.kind) {
-            case ENV_CATCH:    return launch_resident_env<ENV_CATCH, REPLAY>(h, a, w, h->TM_res);
-            case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM, REPLAY>(h, a, w, h->TM_res);
-            default:           return launch_resident_env<ENV_MAZE, REPLAY>(h, a, w, h->TM_res);
+            case ENV_CATCH:    return launch_resident_env<ENV_CATCH>(h, a, w, h->TM_res);
+            case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM>(h, a, w, h->TM_res);
+            default:           return launch_resident_env<ENV_MAZE>(h, a, w, h->TM_res);
         }
     }
     if (h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING)) {
+        const int TM = REPLAY ? replay_tile(h, a.T + (a.bootstrap ? 1 : 0)) : h->TM_mfma;
         switch (h->env.kind) {
-            case ENV_CATCH:    return launch_stream<ENV_CATCH, REPLAY>(h, a, h->TM_mfma);
-            case ENV_PENDULUM: return launch_stream<ENV_PENDULUM, REPLAY>(h, a, h->TM_mfma);
-            default:           return launch_stream<ENV_MAZE, REPLAY>(h, a, h->TM_mfma);
+            case ENV_CATCH:    return launch_stream<ENV_CATCH, REPLAY>(h, a, TM);
+            case ENV_PENDULUM: return launch_stream<ENV_PENDULUM, REPLAY>(h, a, TM);
+            default:           return launch_stream<ENV_MAZE, REPLAY>(h, a, TM);
         }
     }
     switch (h->env.kind) {
@@ -1565,10 +1567,11 @@ hipError_t launch_rollout_behaviour(anakin* h)
 
 // the learner's forward pass over the stored unroll with the current parameters: hidden activations
 // for the backward pass, head outputs and values into the learner's own buffers
-hipError_t launch_replay_forward(anakin* h)
+hipError_t launch_replay_forward(anakin* h, bool bootstrap)
 {
     RolloutArgs a;
     fill_rollout_args(h, a);
+    a.bootstrap = bootstrap ? 1 : 0;
     a.tp.tr_head = at<float>(h, h->lay.head_new);
     a.tp.tr_val = at<float>(h, h->lay.val_new);
     return launch_forward<true>(h, a);

@@ -69,6 +69,7 @@ struct RolloutBf16Args {
     float* prefix;                       // [B][H1] first-layer prefix (bias + wall rows + goal row), maze only
     int B, T, ldx;                       // ldx: LDS row stride in bf16 elements
     int keep_acts;                       // store the packed hidden activations for the update
+    int tend, tseg;                      // REPLAY: steps evaluated (T, or T + 1 with the bootstrap state), steps per workgroup (grid y)
     uint64_t seed, gstep;
 };
 
@@ -368,7 +369,9 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
     }
 
     const int tid_outer = tid;
-    for (int t = 0; t <= T; ++t) {
+    const int t_begin = REPLAY ? (int)blockIdx.y * a.tseg : 0;
+    const int t_end = REPLAY ? (t_begin + a.tseg < a.tend ? t_begin + a.tseg : a.tend) : T + 1;
+    for (int t = t_begin; t < t_end; ++t) {
         // everything derived from the thread index is recomputed every step from a value the compiler
         // cannot see through: dozens of loop-invariant addresses would otherwise be kept in registers
         // across the whole time loop, on top of the 2 * EPT prefix values, and spilled
@@ -607,7 +610,7 @@ void fill_rollout_args(anakin* h, RolloutArgs& a);
 // what: 0 the acting unroll, 1 the actor of a decoupled step (behaviour copies of the parameters, its own prefix
 // buffer, no activations kept), 2 the learner's replay of the stored unroll with the current parameters
 template <bool REPLAY>
-static hipError_t launch_bf16_forward(anakin* h, int what)
+static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true)
 {
     RolloutArgs base;
     fill_rollout_args(h, base);
@@ -625,6 +628,8 @@ static hipError_t launch_bf16_forward(anakin* h, int what)
         a.tp.tr_head = at<float>(h, L.head_new); a.tp.tr_val = at<float>(h, L.val_new);
     }
     a.B = h->B; a.T = h->T; a.seed = h->seed; a.gstep = h->gstep;
+    a.tend = h->T + (bootstrap ? 1 : 0);
+    a.tseg = REPLAY ? replay_segment(h->B / BTM, a.tend) : a.tend;
     int hmax = 0;
     for (int l = 1; l <= h->net.L; ++l) hmax = h->net.dims[l] > hmax ? h->net.dims[l] : hmax;
     a.ldx = hmax + 8;
@@ -634,7 +639,7 @@ static hipError_t launch_bf16_forward(anakin* h, int what)
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
-        hipLaunchKernelGGL(kern, dim3(h->B / BTM), dim3(BWG), lds, h->stream, a);
+        hipLaunchKernelGGL(kern, dim3(h->B / BTM, REPLAY ? (a.tend + a.tseg - 1) / a.tseg : 1), dim3(BWG), lds, h->stream, a);
         return hipGetLastError();
     };
     bool uni = true;                                             // every hidden layer H1 wide: the weight stream runs across layers
@@ -652,6 +657,6 @@ static hipError_t launch_bf16_forward(anakin* h, int what)
 
 hipError_t launch_rollout_bf16(anakin* h) { return launch_bf16_forward<false>(h, 0); }
 hipError_t launch_rollout_bf16_behaviour(anakin* h) { return launch_bf16_forward<false>(h, 1); }
-hipError_t launch_replay_bf16(anakin* h) { return launch_bf16_forward<true>(h, 2); }
+hipError_t launch_replay_bf16(anakin* h, bool bootstrap) { return launch_bf16_forward<true>(h, 2, bootstrap); }
 
 }  // namespace ank
