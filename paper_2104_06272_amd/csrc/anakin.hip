@@ -175,6 +175,7 @@ static void carve(const EnvDims& ed, const NetShape& ns, int B, int T, const int
     L.alt_tr_rew = take(dec ? tn * 4 : 0); L.alt_tr_done = take(dec ? tn : 0);
     L.alt_tr_val = take(dec ? t1n * 4 : 0); L.alt_tr_head = take(dec ? t1n * ns.NHP * 4 : 0);
     L.head_new = take(dec ? t1n * ns.NHP * 4 : 0); L.val_new = take(dec ? t1n * 4 : 0); L.eps_new = take(dec ? tn * 4 : 0);
+    L.head_old = 0;
     L.path = take(ed.kind == ENV_PENDULUM && !ns.bf16 ? tn * 2 * 4 : 0);
     L.small_part = take(small_fused_part_bytes(ed, ns, B, T));
     L.counters = take(256);
@@ -201,7 +202,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
             }
     if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // scatter kernel: more, smaller chunks
     if (ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0) set(0, 1, 256, 64);   // matrix-core scatter: 64-sample steps, about two workgroups (of 128 columns) per CU
-    if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = SPLIT_NT_ROWS; }   // first layer folded into the dX product of the second
+    if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
     if (ns.L == 1 && ed.kind != ENV_MAZE) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
@@ -589,7 +590,7 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         return ANAKIN_OK;
     }
     const bool fused_loss = scan_loss_ok(h);
-    if (fused_loss) HIPCHK(h, launch_scan_loss(h));
+    if (fused_loss) HIPCHK(h, launch_scan_loss(h, false));
     else HIPCHK(h, launch_returns(h));
     if (h->pathwise) {
         if (h->n_updates != 1) { h->err = "the pathwise policy gradient takes one update per unroll (chunks would cut the adjoint)"; return ANAKIN_E_BAD_CONFIG; }
@@ -627,7 +628,7 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         L = full;
         if (seq) {
             L.w_src = full.theta; L.w16_src = full.w_bf16;
-            L.head_new += r0 * n.NHP * 4; L.val_new += r0 * 4; L.eps_new += r0 * 4;
+            L.head_new += r0 * n.NHP * 4; L.val_new += r0 * 4;
         } else {
             L.w_src = full.theta0; L.w16_src = n.bf16 ? full.w0_bf16 : full.w_bf16;
         }
@@ -640,11 +641,10 @@ extern "C" int32_t anakin_learn(anakin_t* h)
         if (seq && k > 0) {
             // sequential reading: the chunk's gradient is taken at the parameters as they are now, so the forward
             // pass over the chunk's stored states is repeated with them (activations, head outputs; for the Gaussian
-            // policy also the noise that reproduces the stored sample)
+            // policy the loss takes the noise that reproduces the stored sample)
             hipError_t e = bf16_mfma(h) ? launch_replay_bf16(h, false) : launch_replay_forward(h, false);
-            if (e == hipSuccess) e = launch_eps_now(h);
             if (e != hipSuccess) { h->err = std::string("replay of the forward pass: ") + hipGetErrorString(e); rc = ANAKIN_E_HIP; break; }
-            L.tr_head = L.head_new; L.tr_eps = L.eps_new;
+            L.head_old = L.tr_head; L.tr_head = L.head_new;
         }
         rc = run_update(h);
         for (int l = 0; l < MAX_REGIONS; ++l) { h->splits[l] = full_splits[l]; h->quanta[l] = full_quanta[l]; }
@@ -704,7 +704,13 @@ extern "C" int32_t anakin_set_updates_per_unroll(anakin_t* h, int32_t n_updates)
     int sw = 0, fan = 1, lb = 0;
     int sp[MAX_REGIONS], qu[MAX_REGIONS];
     plan(h->env, h->net, h->B, h->T / n_updates, sp, qu, &sw, &fan, &lb);
-    // the scratch buffers were sized for the full unroll: a chunk's plan has to fit them
+    // the scratch buffers were sized for the full unroll: a chunk's plan has to fit them (fewer rows can round to more
+    // pieces: 130 quanta in at most 128 pieces are 65, 128 quanta are 128)
+    for (int l = 0; l <= h->net.L; ++l)
+        if (sp[l] > h->splits[l] && h->splits[l] > 0) {
+            const int q = (h->B * (h->T / n_updates) + qu[l] - 1) / qu[l], per = (q + h->splits[l] - 1) / h->splits[l];
+            sp[l] = (q + per - 1) / per;
+        }
     bool ok = (sw > 0) == (h->splits_w > 0) && lb * n_updates <= h->loss_blocks + h->T && sp[h->net.L] * fan <= h->splits[h->net.L] * h->head_fan;
     for (int l = 0; l <= h->net.L && ok; ++l) ok = sp[l] > 0 && sp[l] <= h->splits[l];
     if (ok && sw > 0) ok = sw <= h->splits_w;
@@ -779,13 +785,10 @@ extern "C" int32_t anakin_step_decoupled(anakin_t* h)
     auto learner_update = [&]() -> int32_t {
         if (!h->have_traj) return ANAKIN_OK;
         HIPCHK(h, mc ? launch_replay_bf16(h, true) : launch_replay_forward(h, true));
-        HIPCHK(h, launch_vtrace(h));
+        HIPCHK(h, launch_vtrace_loss(h));
         const int no_acts = h->traj_no_acts;
         h->traj_packed = mc ? 1 : 0; h->traj_no_acts = one_layer_fused(h) ? 1 : 0;
-        const Layout keep = h->lay;
-        h->lay.tr_head = keep.head_new; h->lay.tr_eps = keep.eps_new;   // the loss kernel reads the learner's heads
-        const int32_t r = run_update(h);
-        h->lay = keep;
+        const int32_t r = run_update(h, true);
         h->traj_no_acts = no_acts;
         return r;
     };

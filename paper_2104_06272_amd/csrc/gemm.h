@@ -61,7 +61,7 @@ hipError_t launch_gemm_tn_valu(GemmTnArgs a, hipStream_t s);
 hipError_t launch_gemm_nt_mfma(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_mfma(GemmTnArgs a, hipStream_t s);
 // both products of a layer whose sides are multiples of 256, on split operands (gemm_split.hip)
-hipError_t launch_split_weights(const SplitWeightsArgs& a, hipStream_t s);
-hipError_t launch_gemm_tn_nt_split(GemmTnArgs t, const GemmNtArgs& n, int nt_blocks, hipStream_t s);
+SplitWeightsArgs split_weights_args(const anakin* h);   // what the update's backward pass needs split (nothing: n = 0)
+hipError_t launch_gemm_tn_nt_split(const NetShape& net, int l, const GemmTnArgs& t, const GemmNtArgs& n, int nt_blocks, hipStream_t s);
 
 }  // namespace ank

@@ -162,6 +162,21 @@ hipError_t launch_gemm_tn_valu(GemmTnArgs a, hipStream_t s)
 // already produced dZ of the last hidden layer)
 hipError_t launch_head_backward(anakin* h);
 
+SplitWeightsArgs split_weights_args(const anakin* h)
+{
+    const NetShape& n = h->net;
+    SplitWeightsArgs sw;
+    sw.n = 0;
+    if (n.bf16 || (h->mode & ANAKIN_MODE_VALU_GEMM)) return sw;
+    for (int l = 1; l < n.L; ++l)
+        if (split_gemm_shape(n, l)) {
+            sw.K[sw.n] = n.dims[l]; sw.N[sw.n] = n.dims[l + 1];
+            sw.w[sw.n] = at<const float>(h, h->lay.w_src) + n.w_off[l]; sw.out[sw.n] = at<void>(h, h->lay.w3[l]);
+            ++sw.n;
+        }
+    return sw;
+}
+
 hipError_t launch_backward(anakin* h)
 {
     const Layout& L = h->lay;
@@ -181,18 +196,6 @@ hipError_t launch_backward(anakin* h)
     } else {
         e = launch_head_backward(h);
         if (e != hipSuccess) return e;
-    }
-    SplitWeightsArgs sw;
-    sw.n = 0;
-    for (int l = 1; l < n.L && mfma; ++l)
-        if (split_gemm_shape(n, l)) {
-            sw.K[sw.n] = n.dims[l]; sw.N[sw.n] = n.dims[l + 1];
-            sw.w[sw.n] = at<const float>(h, L.w_src) + n.w_off[l]; sw.out[sw.n] = at<void>(h, L.w3[l]);
-            ++sw.n;
-        }
-    if (sw.n > 0) {
-        ProfScope prof(h, "split_weights");
-        if ((e = launch_split_weights(sw, h->stream)) != hipSuccess) return e;
     }
     // pendulum: the first layer's gradient is summed in the epilogue of the dX product that forms dZ_1
     const bool first_fused = mfma && first_fused_splits(n, h->env.kind, M) > 0;
@@ -236,7 +239,7 @@ hipError_t launch_backward(anakin* h)
                     g.ff.partial = at<float>(h, L.part[0]);
                 }
                 ProfScope prof(h, "gemm_tn_nt");
-                e = launch_gemm_tn_nt_split(t, g, split_nt_blocks(n, M, l), h->stream);
+                e = launch_gemm_tn_nt_split(n, l, t, g, l == 1 && first_fused ? h->splits[0] : split_nt_blocks(n, M, l), h->stream);
                 if (e != hipSuccess) return e;
                 continue;
             }

@@ -25,16 +25,10 @@
 // What bounds them: at 256 x 256 a sample costs 0.33 ns of matrix-core time for both products on the whole chip and 2 to
 // 3 KB of traffic, 0.4 to 0.5 ns at the rate of a copy.  Both products side by side, half the compute units each:
 // 81920 samples 200 -> 117 us, 262144 samples (pendulum) 580 -> 321 us against the binary32 kernels they replace.
-#include "gemm.h"
+#include "split_terms.h"
 #include "detmath.h"
 
 namespace ank {
-
-typedef __bf16 bf8_s __attribute__((ext_vector_type(8)));
-typedef __bf16 bf2_s __attribute__((ext_vector_type(2)));
-typedef float f16v_s __attribute__((ext_vector_type(16)));
-typedef float f4v_s __attribute__((ext_vector_type(4)));
-typedef uint32_t u4v_s __attribute__((ext_vector_type(4)));
 
 constexpr int SWG = 512;                // eight wavefronts, two per SIMD
 
@@ -42,54 +36,9 @@ __device__ __forceinline__ f16v_s mfma_s(u4v_s a, u4v_s b, f16v_s c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8_s, a), __builtin_bit_cast(bf8_s, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ uint32_t pk_bf16_s(float lo, float hi)
-{
-    bf2_s v; v[0] = (__bf16)lo; v[1] = (__bf16)hi;               // round to nearest even, one instruction for the pair
-    return __builtin_bit_cast(uint32_t, v);
-}
-// pair i of eight values as three packed terms, t[0] + t[1] + t[2] = x exactly
-__device__ __forceinline__ void split_pair(float x0, float x1, u4v_s (&t)[3], int i)
-{
-    uint32_t p = pk_bf16_s(x0, x1);
-    asm("" : "+v"(p));                                           // else the low half is rounded a second time on its own
-    t[0][i] = p;
-    const float r0 = x0 - f_from_bits(p << 16), r1 = x1 - f_from_bits(p & 0xffff0000u);
-    uint32_t q = pk_bf16_s(r0, r1);
-    asm("" : "+v"(q));
-    t[1][i] = q;
-    t[2][i] = pk_bf16_s(r0 - f_from_bits(q << 16), r1 - f_from_bits(q & 0xffff0000u));
-}
-__device__ __forceinline__ void split_terms(const float (&x)[8], u4v_s (&t)[3])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split_pair(x[2 * i], x[2 * i + 1], t, i);
-}
 // the six products, smallest first: terms of a and of b
 constexpr int PROD_A[6] = {0, 2, 1, 1, 0, 0};
 constexpr int PROD_B[6] = {2, 0, 1, 0, 1, 0};
-
-// ---------------------------------------------------------------------------
-// Weights as the B operand of gemm_nt: for every block of 32 rows i of W[K][N] and every step of 16 reduction indices j
-// the three terms of the 64 lanes' 16-byte pieces, one KiB each: piece ((ib * N/16 + ks) * 3 + term) * 64 + lane.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(WG) void split_weights(const SplitWeightsArgs a)
-{
-    int p = blockIdx.x * WG + threadIdx.x;                       // piece: eight consecutive j of one row i
-    for (int l = 0; l < a.n; ++l) {
-        const int pieces = a.K[l] * a.N[l] / 8;
-        if (p >= pieces) { p -= pieces; continue; }
-        const int ng = a.N[l] / 8, i = p / ng, jg = p % ng;
-        const f4v_s* src = reinterpret_cast<const f4v_s*>(a.w[l] + (size_t)i * a.N[l] + 8 * jg);
-        const f4v_s v0 = src[0], v1 = src[1];
-        const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        u4v_s t[3];
-        split_terms(x, t);
-        u4v_s* dst = reinterpret_cast<u4v_s*>(a.out[l]) + ((size_t)((i >> 5) * (a.N[l] >> 4) + (jg >> 1)) * 3) * 64 + 32 * (jg & 1) + (i & 31);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dst[k * 64] = t[k];
-        return;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // dW.  A workgroup owns a TI x TJ tile of the product for one chunk of samples and keeps the accumulators in registers.
@@ -274,25 +223,29 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
     }
     if (s < n_stages) step(S1, 0, s);
     float* out = a.partial + (size_t)split * ((size_t)a.K * a.N + a.N);
-    if (WK == 2) {
-        // the second half of the wavefronts hands its sums over
+    if (WK > 1) {
+        // the wavefronts that took other samples of the stages hand their sums over
         float* red = reinterpret_cast<float*>(lds) + (size_t)(wave % (WI * WJ)) * (AI * AJ * 1024);
-        if (wk == 1) {
+        constexpr int PART = WI * WJ * AI * AJ * 1024;
+        static_assert((WK - 1) * PART * 4 <= 2 * HALF * 16, "the sums fit the stages' LDS");
+        if (wk > 0) {
 #pragma unroll
             for (int i = 0; i < AI; ++i)
 #pragma unroll
                 for (int j = 0; j < AJ; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) red[((i * AJ + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+                    for (int r = 0; r < 16; ++r) red[(wk - 1) * PART + ((i * AJ + j) * 16 + r) * 64 + lane] = acc[i][j][r];
         }
         __syncthreads();
         if (wk == 0) {
 #pragma unroll
-            for (int i = 0; i < AI; ++i)
+            for (int w = 0; w < WK - 1; ++w)
 #pragma unroll
-                for (int j = 0; j < AJ; ++j)
+                for (int i = 0; i < AI; ++i)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * AJ + j) * 16 + r) * 64 + lane];
+                    for (int j = 0; j < AJ; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] += red[w * PART + ((i * AJ + j) * 16 + r) * 64 + lane];
         }
         __syncthreads();
     }
@@ -483,8 +436,8 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     // half of the next step asked for.  LAST: the step that completes a tile also asks for the first ReLU masks.
     auto step = [&](auto LAST, Set& nxt, int par, int tile, int c) {
         const int cn = c + 1 < NC ? c + 1 : 0;
-        const bool wrap = c + 3 >= NC;
-        const int t3 = wrap ? tile + 1 : tile, c3 = wrap ? c + 3 - NC : c + 3;
+        const int t3 = c + 3 < NC ? tile : c + 3 < 2 * NC ? tile + 1 : tile + 2;   // (two steps a tile where N is 64)
+        const int c3 = c + 3 - (t3 - tile) * NC;
         if (LAST.value) {
             load_mask(rows_rsrc(a.x, tile * TR, TR, a.M, a.K), 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -623,29 +576,36 @@ __global__ __launch_bounds__(SWG) void gemm_tn_nt_split(const GemmTnArgs t, cons
     gemm_nt_split_body<WN, MT, HEADS, FIRST>(n, t0, t1, by, bx);
 }
 
-hipError_t launch_split_weights(const SplitWeightsArgs& a, hipStream_t s)
+template <int WI, int WJ, int AI, int AJ, int WK, int WN, int MT>
+static hipError_t launch_split_tiles(GemmTnArgs t, const GemmNtArgs& n, int nt_blocks, hipStream_t s)
 {
-    int pieces = 0;
-    for (int l = 0; l < a.n; ++l) pieces += a.K[l] * a.N[l] / 8;
-    hipLaunchKernelGGL(split_weights, dim3((pieces + WG - 1) / WG), dim3(WG), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_tn_nt_split(GemmTnArgs t, const GemmNtArgs& n, int nt_blocks, hipStream_t s)
-{
-    constexpr int TI = 256, TJ = 256, TR = SPLIT_NT_ROWS;
+    constexpr int TI = 32 * WI * AI, TJ = 32 * WJ * AJ, TR = 32 * MT * (8 / WN), TC = 32 * WN;
     t.tiles_i = t.K / TI;
     const int tiles_j = t.N / TJ, tn = t.tiles_i * tiles_j * t.splits;
-    const int tiles = (n.M + TR - 1) / TR, per = (tiles + nt_blocks - 1) / nt_blocks, bx = (tiles + per - 1) / per, by = (n.K + 255) / 256;
-    const size_t lds_tn = (size_t)2 * 3 * 2 * (TI + TJ) * 16;
+    const int tiles = (n.M + TR - 1) / TR, per = (tiles + nt_blocks - 1) / nt_blocks, bx = (tiles + per - 1) / per, by = (n.K + TC - 1) / TC;
+    const size_t lds_tn = (size_t)2 * 3 * 2 * WK * (TI + TJ) * 16;
     const size_t lds_nt = (size_t)2 * 3 * 4 * (TR + 2) * 16 + (n.hf.hl ? n.N * 16 : 0) + (n.ff.f0 ? NTS_SEG * 12 : 0);
     const size_t lds = lds_tn > lds_nt ? lds_tn : lds_nt;
-    auto kern = n.ff.f0 ? (t.hf.hl ? gemm_tn_nt_split<2, 4, 4, 2, 1, 8, 4, true, FIRST_PENDULUM> : gemm_tn_nt_split<2, 4, 4, 2, 1, 8, 4, false, FIRST_PENDULUM>)
-                        : (t.hf.hl ? gemm_tn_nt_split<2, 4, 4, 2, 1, 8, 4, true, FIRST_NONE> : gemm_tn_nt_split<2, 4, 4, 2, 1, 8, 4, false, FIRST_NONE>);
+    auto kern = n.ff.f0 ? (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, true, FIRST_PENDULUM> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, false, FIRST_PENDULUM>)
+                        : (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, true, FIRST_NONE> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, false, FIRST_NONE>);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(tn + bx * by), dim3(SWG), lds, s, t, n, tn, tiles_j, bx, per);
     return hipGetLastError();
+}
+
+// the tile sizes of split_tile_i / split_tile_j / split_nt_rows; stages of 16 samples, 32 or 64 where a tile has fewer
+// pieces than threads, the wavefronts that the tile leaves over sharing a stage's samples
+hipError_t launch_gemm_tn_nt_split(const NetShape& net, int l, const GemmTnArgs& t, const GemmNtArgs& n, int nt_blocks, hipStream_t s)
+{
+    const int ti = split_tile_i(net, l), tj = split_tile_j(net, l);
+    if (ti == 256) return launch_split_tiles<2, 4, 4, 2, 1, 8, 4>(t, n, nt_blocks, s);
+    if (ti == 128) {
+        if (split_nt_cols(net, l) == 256)
+            return tj == 128 ? launch_split_tiles<2, 2, 2, 2, 2, 8, 4>(t, n, nt_blocks, s) : launch_split_tiles<2, 1, 2, 2, 4, 8, 4>(t, n, nt_blocks, s);
+        return tj == 128 ? launch_split_tiles<2, 2, 2, 2, 2, 4, 2>(t, n, nt_blocks, s) : launch_split_tiles<2, 1, 2, 2, 4, 4, 2>(t, n, nt_blocks, s);
+    }
+    return tj == 128 ? launch_split_tiles<1, 2, 2, 2, 4, 2, 2>(t, n, nt_blocks, s) : launch_split_tiles<1, 2, 2, 1, 4, 2, 2>(t, n, nt_blocks, s);
 }
 
 }  // namespace ank

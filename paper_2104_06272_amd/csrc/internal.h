@@ -137,6 +137,7 @@ struct Layout {
     size_t theta_b, w_bf16_b, wt_bf16_b, prefix_b;      // bf16 nets: the actor's own rounded copies and first-layer prefix
     size_t alt_tr_s0, alt_tr_f0, alt_tr_f1, alt_tr_act, alt_tr_eps, alt_tr_actf, alt_tr_rew, alt_tr_done, alt_tr_val, alt_tr_head;
     size_t head_new, val_new, eps_new;
+    size_t head_old;              // set while the loss is taken at a repeated forward pass: head outputs at acting time (0: none)
     size_t small_part;           // single-launch update of small nets: one whole gradient per workgroup, [workgroups][P]
     size_t counters;             // arrival counters of kernels whose last workgroup finishes the job (zero between launches)
     size_t path;                 // pathwise policy gradient: dL_path / d(mu, log_sigma) per sample, [T*B][2]
@@ -223,13 +224,12 @@ inline int replay_segment(int tiles, int tend)
     if (parts > tend) parts = tend;
     return (tend + parts - 1) / parts;
 }
-hipError_t launch_vtrace(anakin* h);
-hipError_t launch_eps_now(anakin* h);
 hipError_t launch_pathwise(anakin* h);
 bool pathwise_ok(const anakin* h);
 hipError_t launch_returns(anakin* h);
 bool scan_loss_ok(const anakin* h);          // returns and loss as one launch
-hipError_t launch_scan_loss(anakin* h);
+hipError_t launch_scan_loss(anakin* h, bool vtrace);
+hipError_t launch_vtrace_loss(anakin* h);
 hipError_t launch_head_grad(anakin* h);
 hipError_t launch_backward(anakin* h);
 hipError_t launch_adam(anakin* h);
@@ -257,15 +257,23 @@ bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
 // the stored unroll was produced by the bf16 matrix-core kernels and the maze first layer is reduced in pieces
 inline bool first_layer_split(const anakin* h) { return h->splits_w > 0 && h->traj_packed; }
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
-// both sides of layer l + 1 (l >= 1) are whole 256-wide tiles: its two products share a launch (gemm_split.hip)
-inline bool split_gemm_shape(const NetShape& n, int l) { return !n.bf16 && l >= 1 && l < n.L && n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }
-constexpr int SPLIT_NT_ROWS = 128;   // samples per tile of the dX product
+// both sides of layer l + 1 (l >= 1) are whole 64-wide tiles: its two products share a launch (gemm_split.hip)
+inline bool split_gemm_shape(const NetShape& n, int l) { return !n.bf16 && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }
+// tiles of the dW product: 256 x 256 where both sides allow it, else 128 or 64 on a side (128 x 256 as one tile spilled
+// registers: 54 us for both products of a 128-256 net over 28 k samples, 35 as two tiles)
+inline bool split_tile_256(const NetShape& n, int l) { return n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }
+inline int split_tile_i(const NetShape& n, int l) { return split_tile_256(n, l) ? 256 : n.dims[l] % 128 ? 64 : 128; }
+inline int split_tile_j(const NetShape& n, int l) { return split_tile_256(n, l) ? 256 : n.dims[l + 1] % 128 ? 64 : 128; }
+// the dX product: output columns and samples per tile (eight wavefronts, 32 columns each, or shared out over the samples)
+inline int split_nt_cols(const NetShape& n, int l) { return n.dims[l] % 256 == 0 ? 256 : split_tile_i(n, l); }
+inline int split_nt_rows(const NetShape& n, int l) { return split_nt_cols(n, l) == 64 ? 256 : 128; }
 // Compute units the dW and the dX product of such a layer get in their shared launch (their costs per sample are alike):
-// chunks of the dW product per tile, and workgroups of the dX product along the samples per 256 output columns.
-inline int split_tn_cap(const NetShape& n, int l) { const int c = 128 / ((n.dims[l] / 256) * (n.dims[l + 1] / 256)); return c > 1 ? c : 1; }
+// chunks of the dW product per tile, and workgroups of the dX product along the samples per tile of output columns.
+inline int split_tn_cap(const NetShape& n, int l) { const int c = 128 / ((n.dims[l] / split_tile_i(n, l)) * (n.dims[l + 1] / split_tile_j(n, l))); return c > 1 ? c : 1; }
 inline int split_nt_blocks(const NetShape& n, int M, int l)
 {
-    const int c = 128 / (n.dims[l] / 256), cap = c > 1 ? c : 1, tiles = (M + SPLIT_NT_ROWS - 1) / SPLIT_NT_ROWS, per = (tiles + cap - 1) / cap;
+    const int c = 128 / (n.dims[l] / split_nt_cols(n, l)), cap = c > 1 ? c : 1;
+    const int tiles = (M + split_nt_rows(n, l) - 1) / split_nt_rows(n, l), per = (tiles + cap - 1) / cap;
     return (tiles + per - 1) / per;
 }
 inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 4 && split_gemm_shape(n, n.L - 1); }

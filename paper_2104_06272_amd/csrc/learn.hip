@@ -15,6 +15,7 @@
 // are reproducible bit for bit.
 #include "internal.h"
 #include "loss.h"
+#include "split_terms.h"
 
 namespace ank {
 
@@ -90,12 +91,17 @@ __device__ __forceinline__ float log_softmax_at(const float (&hv)[8], int A, int
     return ha - mx - det_log(Z);
 }
 
-// first pass, one lane per sample, no order: the truncated ratio rho (parked in ret, where the scan
-// picks it up before it overwrites the slot with v) and eps_new
-__global__ __launch_bounds__(WG) void vtrace_ratio(const VtraceArgs a)
+// the noise that reproduces the stored pre-squash sample under newer head outputs: eps_new = (z - mu_new) / sigma_new
+__device__ __forceinline__ float noise_now(const float* ho, float eo, float mu, float sigma)
 {
-    const size_t i = (size_t)blockIdx.x * WG + threadIdx.x;
-    if (i >= (size_t)a.B * a.T) return;
+    const float2 o = *reinterpret_cast<const float2*>(ho);
+    const float z = fmaf(det_exp(fminf(fmaxf(o.y, -5.0f), 2.0f)), eo, o.x);       // the sampler's own expression
+    return (z - mu) / sigma;
+}
+
+// the truncated ratio rho of sample i, and the noise (Gaussian) that reproduces its action under the new head outputs
+__device__ __forceinline__ float vtrace_rho(const VtraceArgs& a, size_t i)
+{
     float hn[8], ho[8];
     load_head(a.head_new + i * a.NHP, a.NHP, hn);
     load_head(a.head_old + i * a.NHP, a.NHP, ho);
@@ -106,12 +112,19 @@ __global__ __launch_bounds__(WG) void vtrace_ratio(const VtraceArgs a)
     } else {
         const float lso = fminf(fmaxf(ho[1], -5.0f), 2.0f), lsn = fminf(fmaxf(hn[1], -5.0f), 2.0f);
         const float eo = a.eps_old[i];
-        const float z = fmaf(det_exp(lso), eo, ho[0]);       // the sampler's own expression
-        const float en = (z - hn[0]) / det_exp(lsn);
+        const float en = noise_now(a.head_old + i * a.NHP, eo, hn[0], det_exp(lsn));
         a.eps_new[i] = en;
         lw = (-0.5f * en * en - lsn) - (-0.5f * eo * eo - lso);
     }
-    if (a.ret) a.ret[i] = fminf(1.0f, det_exp(lw));          // null: only eps_new is wanted
+    return fminf(1.0f, det_exp(lw));
+}
+
+// first pass, one lane per sample, no order: the truncated ratio (parked in ret, where the scan picks it up before it
+// overwrites the slot with v) and eps_new
+__global__ __launch_bounds__(WG) void vtrace_ratio(const VtraceArgs a)
+{
+    const size_t i = (size_t)blockIdx.x * WG + threadIdx.x;
+    if (i < (size_t)a.B * a.T) a.ret[i] = vtrace_rho(a, i);
 }
 
 // second pass, one lane per env, backwards in t
@@ -148,6 +161,7 @@ struct HeadGradArgs {
     const float* rew; const uint8_t* done;
     float* dhead; float* loss_part;        // [blocks][8]
     float beta, cv, inv_m;
+    const float* head_old;                 // Gaussian, forward pass repeated with newer parameters: head outputs at acting time, else null
     const float* path;                     // pathwise policy gradient: dL/d(mu, log_sigma) per sample replaces the
                                            // score-function term, and the reported policy loss is minus the mean reward
 };
@@ -199,7 +213,9 @@ __device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const in
             const float ls = hv[1];
             const bool clamped = ls < -5.0f || ls > 2.0f;
             const float lsc = fminf(fmaxf(ls, -5.0f), 2.0f);
-            const float sigma = det_exp(lsc), ep = a.eps[i];
+            const float sigma = det_exp(lsc);
+            float ep = a.eps[i];
+            if (a.head_old) ep = noise_now(a.head_old + (size_t)i * a.NHP, ep, hv[0], sigma);
             d[0] = (-A_ * ep / sigma) * a.inv_m;
             d[1] = clamped ? 0.0f : (-A_ * (ep * ep - 1.0f) - a.beta) * a.inv_m;
             lp_term = -A_ * (-0.5f * ep * ep - lsc - 0x1.d67f1cp-1f);
@@ -240,8 +256,9 @@ __device__ __forceinline__ void loss_block_sums(float lp_term, float v_term, flo
     }
 }
 
-__global__ __launch_bounds__(WG) void head_grad(const HeadGradArgs a)
+__global__ __launch_bounds__(WG) void head_grad(const HeadGradArgs a, const SplitWeightsArgs sw, const int blocks)
 {
+    if ((int)blockIdx.x >= blocks) { split_weights(sw, (int)blockIdx.x - blocks); return; }
     __shared__ float red[WG / 64][8];
     const int i = blockIdx.x * WG + threadIdx.x;
     float lp_term = 0.0f, v_term = 0.0f, e_term = 0.0f, rsum = 0.0f, dcount = 0.0f;
@@ -256,6 +273,7 @@ __global__ __launch_bounds__(WG) void head_grad(const HeadGradArgs a)
 // returns_scan's recursion out of LDS (returns and advantages to memory, for the caller to see, and to LDS), and
 // every thread takes the samples s, s + 256, ... of the workgroup's T x E through head_grad's arithmetic.
 // One launch and no trip of the advantages through memory between the two.
+// VTRACE: the off-policy targets of a decoupled step in the same manner; the ratios take the place of the rewards' pass.
 // ---------------------------------------------------------------------------
 constexpr int SL_MAXN = 1024;            // samples of a workgroup at most (T x envs)
 struct ScanLossArgs {
@@ -264,13 +282,17 @@ struct ScanLossArgs {
     const float* val;                      // [T + 1][B]
     float gamma, lambda;
     float* adv_out; float* ret_out;
+    int blocks;                            // workgroups with environments; further ones split weights
+    VtraceArgs v;                          // VTRACE: heads and noise of both policies
 };
 
-__global__ __launch_bounds__(WG) void scan_loss(const ScanLossArgs a)
+template <bool VTRACE>
+__global__ __launch_bounds__(WG) void scan_loss(const ScanLossArgs a, const SplitWeightsArgs sw)
 {
+    if ((int)blockIdx.x >= a.blocks) { split_weights(sw, (int)blockIdx.x - a.blocks); return; }
     __shared__ float red[WG / 64][8];
     __shared__ float rews[SL_MAXN], vals[SL_MAXN + 16], discs[SL_MAXN];
-    __shared__ float advs[SL_MAXN], rets[SL_MAXN];
+    __shared__ float advs[SL_MAXN], rets[SL_MAXN], rhos[VTRACE ? SL_MAXN : 1];
     const int B = a.B, T = a.T, SL_E = a.E, tid = threadIdx.x;
     const int b0 = blockIdx.x * SL_E;
     const int n = T * SL_E;
@@ -279,9 +301,22 @@ __global__ __launch_bounds__(WG) void scan_loss(const ScanLossArgs a)
         const size_t i = (size_t)t * B + b0 + e;
         vals[s] = a.val[i];
         if (s < n) { rews[s] = a.g.rew[i]; discs[s] = a.g.done[i] ? 0.0f : a.gamma; }
+        if (VTRACE && s < n) rhos[VTRACE ? s : 0] = vtrace_rho(a.v, i);
     }
     __syncthreads();
-    if (tid < SL_E) {
+    if (VTRACE && tid < SL_E) {
+        float Vnext = vals[n + tid], tail = 0.0f;                // tail: v_{t+1} - V_{t+1}
+        for (int t = T - 1; t >= 0; --t) {
+            const int s = t * SL_E + tid;
+            const float rho = rhos[VTRACE ? s : 0], V = vals[s], r = rews[s], disc = discs[s];
+            const float c = a.lambda * rho;
+            advs[s] = rho * (fmaf(disc, Vnext + tail, r) - V);
+            tail = fmaf(disc * c, tail, rho * (fmaf(disc, Vnext, r) - V));
+            rets[s] = V + tail;
+            Vnext = V;
+        }
+    }
+    if (!VTRACE && tid < SL_E) {
         const float oml = 1.0f - a.lambda;
         float G = vals[n + tid], vnext = G;
         for (int t = T - 1; t >= 0; --t) {
@@ -1412,44 +1447,6 @@ hipError_t launch_returns(anakin* h)
     return hipGetLastError();
 }
 
-hipError_t launch_vtrace(anakin* h)
-{
-    const Layout& L = h->lay;
-    VtraceArgs a;
-    a.B = h->B; a.T = h->T; a.A = h->net.A; a.NH = h->net.NH; a.NHP = h->net.NHP; a.policy = h->net.policy;
-    a.head_old = at<const float>(h, L.tr_head); a.head_new = at<const float>(h, L.head_new); a.val_new = at<const float>(h, L.val_new);
-    a.act = at<const uint8_t>(h, L.tr_act); a.eps_old = at<const float>(h, L.tr_eps);
-    a.rew = at<const float>(h, L.tr_rew); a.done = at<const uint8_t>(h, L.tr_done);
-    a.gamma = h->net_cfg.gamma; a.lambda = h->net_cfg.lambda_;
-    a.adv = at<float>(h, L.adv); a.ret = at<float>(h, L.ret); a.eps_new = at<float>(h, L.eps_new);
-    {
-        ProfScope prof(h, "vtrace_ratio");
-        hipLaunchKernelGGL(vtrace_ratio, dim3((unsigned)(((size_t)h->B * h->T + WG - 1) / WG)), dim3(WG), 0, h->stream, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    ProfScope prof(h, "vtrace_scan");
-    hipLaunchKernelGGL(vtrace_scan, dim3((h->B + WG - 1) / WG), dim3(WG), 0, h->stream, a);
-    return hipGetLastError();
-}
-
-// Gaussian policy, forward pass repeated with newer parameters: the noise that reproduces the stored pre-squash
-// sample under the new head outputs, eps_new = (z - mu_new) / sigma_new (what the score function is taken at)
-hipError_t launch_eps_now(anakin* h)
-{
-    const Layout& L = h->lay;
-    if (h->net.policy == POLICY_CATEGORICAL) return hipSuccess;
-    VtraceArgs a;
-    a.B = h->B; a.T = h->T; a.A = h->net.A; a.NH = h->net.NH; a.NHP = h->net.NHP; a.policy = h->net.policy;
-    a.head_old = at<const float>(h, L.tr_head); a.head_new = at<const float>(h, L.head_new); a.val_new = nullptr;
-    a.act = at<const uint8_t>(h, L.tr_act); a.eps_old = at<const float>(h, L.tr_eps);
-    a.rew = nullptr; a.done = nullptr; a.gamma = 0.0f; a.lambda = 0.0f;
-    a.adv = nullptr; a.ret = nullptr; a.eps_new = at<float>(h, L.eps_new);
-    ProfScope prof(h, "eps_now");
-    hipLaunchKernelGGL(vtrace_ratio, dim3((unsigned)(((size_t)h->B * h->T + WG - 1) / WG)), dim3(WG), 0, h->stream, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_head_grad(anakin* h)
 {
     const Layout& L = h->lay;
@@ -1461,9 +1458,11 @@ hipError_t launch_head_grad(anakin* h)
     a.dhead = at<float>(h, L.dhead); a.loss_part = at<float>(h, L.loss_part);
     a.beta = h->net_cfg.entropy_coef; a.cv = h->net_cfg.value_coef; a.inv_m = (float)(1.0 / (double)a.M);
     a.path = h->pathwise ? at<const float>(h, L.path) : nullptr;
+    a.head_old = L.head_old && h->net.policy != POLICY_CATEGORICAL ? at<const float>(h, L.head_old) : nullptr;
     h->metric_blocks = h->loss_blocks;
+    const SplitWeightsArgs sw = split_weights_args(h);
     ProfScope prof(h, "head_grad");
-    hipLaunchKernelGGL(head_grad, dim3(h->loss_blocks), dim3(WG), 0, h->stream, a);
+    hipLaunchKernelGGL(head_grad, dim3(h->loss_blocks + split_weights_blocks(sw)), dim3(WG), 0, h->stream, a, sw, h->loss_blocks);
     return hipGetLastError();
 }
 
@@ -1471,17 +1470,56 @@ hipError_t launch_head_grad(anakin* h)
 // sums per workgroup
 // 16 envs per workgroup unless that leaves the second pass over the samples mostly empty (256 < 16 T < 512)
 static int scan_loss_envs(const anakin* h) { return (h->T * 16 <= WG || h->T * 16 >= 2 * WG) ? 16 : 8; }
-bool scan_loss_ok(const anakin* h)
+static bool scan_loss_shape(const anakin* h)
 {
     const int E = scan_loss_envs(h);
-    return h->n_updates == 1 && !h->pathwise && !h->traj_decoupled && h->B % E == 0 && h->T * E <= SL_MAXN &&
+    return h->B % E == 0 && h->T * E <= SL_MAXN &&
            h->B / E <= h->loss_blocks;
 }
 
-hipError_t launch_scan_loss(anakin* h)
+bool scan_loss_ok(const anakin* h) { return h->n_updates == 1 && !h->pathwise && !h->traj_decoupled && scan_loss_shape(h); }
+
+static void fill_vtrace_args(anakin* h, VtraceArgs& a)
+{
+    const Layout& L = h->lay;
+    a.B = h->B; a.T = h->T; a.A = h->net.A; a.NH = h->net.NH; a.NHP = h->net.NHP; a.policy = h->net.policy;
+    a.head_old = at<const float>(h, L.tr_head); a.head_new = at<const float>(h, L.head_new); a.val_new = at<const float>(h, L.val_new);
+    a.act = at<const uint8_t>(h, L.tr_act); a.eps_old = at<const float>(h, L.tr_eps);
+    a.rew = at<const float>(h, L.tr_rew); a.done = at<const uint8_t>(h, L.tr_done);
+    a.gamma = h->net_cfg.gamma; a.lambda = h->net_cfg.lambda_;
+    a.adv = at<float>(h, L.adv); a.ret = at<float>(h, L.ret); a.eps_new = at<float>(h, L.eps_new);
+}
+
+// V-trace targets and the loss of a decoupled step: one launch where a workgroup holds its environments' whole unroll
+hipError_t launch_vtrace_loss(anakin* h)
+{
+    if (scan_loss_shape(h)) return launch_scan_loss(h, true);
+    VtraceArgs a;
+    fill_vtrace_args(h, a);
+    {
+        ProfScope prof(h, "vtrace_ratio");
+        hipLaunchKernelGGL(vtrace_ratio, dim3((unsigned)(((size_t)h->B * h->T + WG - 1) / WG)), dim3(WG), 0, h->stream, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    {
+        ProfScope prof(h, "vtrace_scan");
+        hipLaunchKernelGGL(vtrace_scan, dim3((h->B + WG - 1) / WG), dim3(WG), 0, h->stream, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const Layout keep = h->lay;
+    h->lay.tr_head = keep.head_new; h->lay.tr_eps = keep.eps_new;        // the loss is taken at the learner's heads
+    hipError_t e = launch_head_grad(h);
+    h->lay = keep;
+    return e;
+}
+
+hipError_t launch_scan_loss(anakin* h, bool vtrace)
 {
     const Layout& L = h->lay;
     ScanLossArgs s;
+    fill_vtrace_args(h, s.v);
     HeadGradArgs& a = s.g;
     a.M = h->B * h->T; a.A = h->net.A; a.NH = h->net.NH; a.NHP = h->net.NHP; a.policy = h->net.policy;
     a.head = at<const float>(h, L.tr_head); a.act = at<const uint8_t>(h, L.tr_act); a.eps = at<const float>(h, L.tr_eps);
@@ -1489,13 +1527,16 @@ hipError_t launch_scan_loss(anakin* h)
     a.rew = at<const float>(h, L.tr_rew); a.done = at<const uint8_t>(h, L.tr_done);
     a.dhead = at<float>(h, L.dhead); a.loss_part = at<float>(h, L.loss_part);
     a.beta = h->net_cfg.entropy_coef; a.cv = h->net_cfg.value_coef; a.inv_m = (float)(1.0 / (double)a.M);
-    a.path = nullptr;
+    a.path = nullptr; a.head_old = nullptr;
     s.B = h->B; s.T = h->T; s.E = scan_loss_envs(h); s.val = at<const float>(h, L.tr_val);
     s.gamma = h->net_cfg.gamma; s.lambda = h->net_cfg.lambda_;
     s.adv_out = at<float>(h, L.adv); s.ret_out = at<float>(h, L.ret);
-    h->metric_blocks = h->B / s.E;
-    ProfScope prof(h, "scan_loss");
-    hipLaunchKernelGGL(scan_loss, dim3(h->B / s.E), dim3(WG), 0, h->stream, s);
+    if (vtrace) { a.head = at<const float>(h, L.head_new); a.eps = at<const float>(h, L.eps_new); s.val = at<const float>(h, L.val_new); }
+    s.blocks = h->B / s.E;
+    h->metric_blocks = s.blocks;
+    const SplitWeightsArgs sw = split_weights_args(h);
+    ProfScope prof(h, vtrace ? "vtrace_loss" : "scan_loss");
+    hipLaunchKernelGGL(vtrace ? scan_loss<true> : scan_loss<false>, dim3(s.blocks + split_weights_blocks(sw)), dim3(WG), 0, h->stream, s, sw);
     return hipGetLastError();
 }
 

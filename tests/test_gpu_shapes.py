@@ -90,9 +90,12 @@ def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
     forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 6)
 
 
-# 256-wide tiles on split operands: one row tile or less, ends in the middle of a tile, several tiles side by side
+# backward products on split operands: one row tile or less, ends in the middle of a tile, several tiles side by side, every
+# pairing of tile widths
 @pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 256], 16, 1), ("pendulum_8192", [256, 256], 48, 3), ("pendulum_8192", [256, 512], 80, 5),
-                                             ("catch_4096", [512, 512], 112, 5), ("pendulum_8192", [512, 256, 256], 144, 2)])
+                                             ("catch_4096", [512, 512], 112, 5), ("pendulum_8192", [512, 256, 256], 144, 2),
+                                             ("pendulum_8192", [64, 64], 16, 1), ("catch_4096", [64, 256], 80, 5), ("pendulum_8192", [64, 128, 64], 336, 3),
+                                             ("catch_4096", [128, 256, 64], 48, 7), ("pendulum_8192", [128, 128], 144, 9), ("catch_4096", [512, 128], 16, 3)])
 def test_split_operand_products(gpu, orc, name, hidden, B, T):
     lockstep(gpu, orc, variant(name, hidden, B, T), 8)
 
