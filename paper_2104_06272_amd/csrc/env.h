@@ -57,7 +57,8 @@ ANK_HD void pendulum_reset(EnvState& s, uint32_t w0, uint32_t w1)
     s.s0 = 0;
 }
 // reward from the state before the step; semi-implicit Euler; time limit ends the episode
-ANK_HD void pendulum_step(const EnvDims& d, EnvState& s, float a, uint32_t w0, uint32_t w1, float& r, int& done)
+// sn: sine of the angle before the step (det_sincos; a caller that observed the state has it)
+ANK_HD void pendulum_step_sn(const EnvDims& d, EnvState& s, float sn, float a, uint32_t w0, uint32_t w1, float& r, int& done)
 {
     const float th = s.f0, thd = s.f1;
     float u = 2.0f * a;
@@ -67,8 +68,6 @@ ANK_HD void pendulum_step(const EnvDims& d, EnvState& s, float a, uint32_t w0, u
     cost = fmaf(0x1.99999ap-4f, thd * thd, cost);
     cost = fmaf(0x1.0624dep-10f, u * u, cost);
     r = -cost;
-    float sn, cs;
-    det_sincos(th, sn, cs);
     const float acc = fmaf(15.0f, sn, 3.0f * u);
     float nthd = fmaf(acc, 0x1.99999ap-5f, thd);
     nthd = nthd < -8.0f ? -8.0f : nthd;
@@ -82,6 +81,12 @@ ANK_HD void pendulum_step(const EnvDims& d, EnvState& s, float a, uint32_t w0, u
     // then lives in scratch memory instead of registers
     done = (int)steps >= d.max_steps ? 1 : 0;
     if (done) pendulum_reset(s, w0, w1);
+}
+ANK_HD void pendulum_step(const EnvDims& d, EnvState& s, float a, uint32_t w0, uint32_t w1, float& r, int& done)
+{
+    float sn, cs;
+    det_sincos(s.f0, sn, cs);
+    pendulum_step_sn(d, s, sn, a, w0, w1, r, done);
 }
 
 // ---- Maze ------------------------------------------------------------------
