@@ -984,6 +984,9 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
     }
     // Wavefront g < G owns the environments of group g: lane e + 16 j sums heads j and j + 4 of environment e, lane e steps
     // it.  In the first layer every wavefront takes EPW rows.
+    // A group that does not exist (B an odd multiple of 16, G = 2) stands in the state of the tile's first environment for the
+    // whole unroll and shows that: every wavefront's first layer runs on all rows, so each needs an observation that is a
+    // valid index into W1.
     const int m0 = EPW * wave;
     const bool live = m0 < rows_left, owner = wave < G && 16 * wave < rows_left;   // (of the wavefront)
     EnvState st{0u, 0.0f, 0.0f};
@@ -1007,7 +1010,7 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
 
     float sine = 0.0f;                                             // pendulum: of the angle as observed
     auto observe = [&](int lane) {
-        if (!owner || lane >= 16) return;
+        if (wave >= G || lane >= 16) return;
         uint32_t* o = obs + (16 * wave + lane) * OBS_WORDS;
         if (ENV == ENV_CATCH) {
             int bc, pc;

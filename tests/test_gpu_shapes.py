@@ -115,3 +115,13 @@ def test_streaming_acting(gpu, orc, name, hidden, B, T):
     g.learn(); o.learn_n(2, sequential=True)
     PT.assert_learn_close(g, o, TOL_F32, n_updates=2)
     g.close()
+
+
+# weights-resident acting with two groups of 16 environments per workgroup where the last workgroup has one: the rows without an
+# environment go through the first layer too (its matrix in LDS or, boards of many cells, in memory; the maze's always)
+@pytest.mark.parametrize("name,hidden,env", [("maze_16384", [128, 128], dict(rows=5, cols=7, max_steps=9)), ("maze_16384", [256, 256], dict(rows=5, cols=7, max_steps=9)),
+                                             ("catch_4096", [256, 256], dict(rows=12, cols=8, max_steps=11)), ("catch_4096", [256, 256], {}),
+                                             ("catch_4096", [128, 128], dict(rows=16, cols=15, max_steps=15)),
+                                             ("pendulum_8192", [128, 128], {}), ("pendulum_8192", [256, 256], {})])
+def test_resident_acting_last_group_missing(gpu, orc, name, hidden, env):
+    lockstep(gpu, orc, variant(name, hidden, 4112, 2, **env), 10, updates=1)
