@@ -163,13 +163,12 @@ static void carve(const EnvDims& ed, const NetShape& ns, int B, int T, const int
     }
     off += carve_update_scratch(ed, ns, B, T, splits, splits_w, head_fan, L, off);
     for (int l = 0; l < MAX_LAYERS; ++l) L.w3[l] = take(split_gemm_shape(ns, l) ? (size_t)ns.dims[l] * ns.dims[l + 1] * 6 : 0);
-    L.prefix = take(ns.bf16 ? (size_t)B * ns.dims[1] * 4 : 0);
+    L.time_sum = take(splits_w > 0 ? (size_t)B * ns.dims[1] * 4 : 0);
     L.loss_part = take((size_t)(loss_blocks + T) * 8 * 4);     // + T: with N updates per unroll every chunk rounds its block count up
     // decoupled steps: behaviour parameters, second record set, the learner's forward results
     const bool dec = true;
     L.theta_b = take(dec ? P * 4 : 0);
     L.w_bf16_b = take(ns.bf16 ? P * 2 : 0); L.wt_bf16_b = take(ns.bf16 ? P * 2 : 0);
-    L.prefix_b = take(ns.bf16 ? (size_t)B * ns.dims[1] * 4 : 0);
     L.alt_tr_s0 = take(dec ? t1n * 4 : 0); L.alt_tr_f0 = take(dec ? t1n * 4 : 0); L.alt_tr_f1 = take(dec ? t1n * 4 : 0);
     L.alt_tr_act = take(dec ? tn : 0); L.alt_tr_eps = take(dec ? tn * 4 : 0); L.alt_tr_actf = take(dec ? tn * 4 : 0);
     L.alt_tr_rew = take(dec ? tn * 4 : 0); L.alt_tr_done = take(dec ? tn : 0);

@@ -129,12 +129,12 @@ struct Layout {
     size_t part[MAX_REGIONS];
     size_t w3[MAX_LAYERS];       // fp32 nets: weights of layer l as split operands of the dX product (split_weights)
     size_t head_stage;           // first-stage partials of the head gradient
-    size_t prefix;               // bf16 acting: per-env first-layer prefix [B][H1] fp32
+    size_t time_sum;             // maze first layer of a bf16 net: dZ_1 summed over time, two bfloat16 terms, [2][B][H1]
     size_t loss_part;
     // decoupled acting and learning: the behaviour copy of the parameters the actor runs on, the second set of
     // trajectory records (the actor fills one set while the learner reads the other), and the learner's own
     // forward results on the stored unroll
-    size_t theta_b, w_bf16_b, wt_bf16_b, prefix_b;      // bf16 nets: the actor's own rounded copies and first-layer prefix
+    size_t theta_b, w_bf16_b, wt_bf16_b;                // bf16 nets: the actor's own rounded copies
     size_t alt_tr_s0, alt_tr_f0, alt_tr_f1, alt_tr_act, alt_tr_eps, alt_tr_actf, alt_tr_rew, alt_tr_done, alt_tr_val, alt_tr_head;
     size_t head_new, val_new, eps_new;
     size_t head_old;              // set while the loss is taken at a repeated forward pass: head outputs at acting time (0: none)

@@ -1316,7 +1316,7 @@ hipError_t launch_backward_bf16(anakin* h)
     for (int l = n.L - 1; l >= 0; --l) {
         if (l == 0 && first_layer_split(h)) {
             const int H1 = n.dims[1], cells = h->env.rows * h->env.cols, plane = cells * H1;
-            uint16_t* sP = at<uint16_t>(h, L.prefix);                // B x H1 words, free between unrolls
+            uint16_t* sP = at<uint16_t>(h, L.time_sum);
             float* pw = at<float>(h, L.part[0]);
             float* pa = pw + (size_t)plane * h->splits_w;
             float* pg = pa + (size_t)plane * h->splits[0];

@@ -66,7 +66,6 @@ struct RolloutBf16Args {
     const float* theta;                  // fp32 master (biases are read from here)
     const uint16_t* w;                   // bf16 copy of theta, same indexing
     const uint16_t* wt;                  // bf16 copy in matrix-core operand tiles (heads: [NH][HL])
-    float* prefix;                       // [B][H1] first-layer prefix (bias + wall rows + goal row), maze only
     int B, T, ldx;                       // ldx: LDS row stride in bf16 elements
     int keep_acts;                       // store the packed hidden activations for the update
     int tend, tseg;                      // REPLAY: steps evaluated (T, or T + 1 with the bootstrap state), steps per workgroup (grid y)
@@ -305,10 +304,12 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
     __syncthreads();
     // first-layer constants of this thread: the bias, plus -- for the maze -- the contribution of the wall
     // plane and of the goal cell, which never change: prefix[64][H1] = b1 + Walls[64][cells] W1[cells][H1]
-    // on the matrix cores, handed over through HBM once per launch
+    // on the matrix cores, handed over in the LDS of the two activation buffers, which are not in use yet (64 rows of
+    // ldx floats are exactly both): workgroups that replay other time steps of the same environments have their own
     float pre[ENV == ENV_MAZE ? EPT : 1][2];
     const float bias0 = a.theta[a.net.b_off[0] + c], bias1 = a.theta[a.net.b_off[0] + c + 1];
     if (ENV == ENV_MAZE) {
+        float* prefix = reinterpret_cast<float*>(smem4);         // [64][ldx]
         const int n = a.env.rows * a.env.cols;
         const int l32 = lane & 31, kg = lane >> 5;
         constexpr int NT1 = H1 >= 512 ? 2 : 1;
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = mt * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
-                        a.prefix[(size_t)(b0 + row) * H1 + n0 + 32 * t4 + l32] = acc[mt][t4][r];
+                        prefix[row * ldx + n0 + 32 * t4 + l32] = acc[mt][t4][r];
                     }
         }
         __syncthreads();
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
         const float g0 = bf2f((uint16_t)(goal & 0xffffu)), g1 = bf2f((uint16_t)(goal >> 16));
 #pragma unroll
         for (int m = 0; m < EPT; ++m) {
-            const float2 p = *reinterpret_cast<const float2*>(a.prefix + (size_t)(b0 + e0 + m) * H1 + c);
+            const float2 p = *reinterpret_cast<const float2*>(prefix + (e0 + m) * ldx + c);
             pre[ENV == ENV_MAZE ? m : 0][0] = p.x + g0;
             pre[ENV == ENV_MAZE ? m : 0][1] = p.y + g1;
         }
@@ -607,8 +608,8 @@ bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B)
 
 void fill_rollout_args(anakin* h, RolloutArgs& a);
 
-// what: 0 the acting unroll, 1 the actor of a decoupled step (behaviour copies of the parameters, its own prefix
-// buffer, no activations kept), 2 the learner's replay of the stored unroll with the current parameters
+// what: 0 the acting unroll, 1 the actor of a decoupled step (behaviour copies of the parameters, no activations
+// kept), 2 the learner's replay of the stored unroll with the current parameters
 template <bool REPLAY>
 static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true)
 {
@@ -618,11 +619,9 @@ static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true
     RolloutBf16Args a;
     a.env = base.env; a.net = base.net; a.tp = base.tp; a.theta = base.theta;
     a.w = at<const uint16_t>(h, L.w_bf16); a.wt = at<const uint16_t>(h, L.wt_bf16);
-    a.prefix = at<float>(h, L.prefix);
     a.keep_acts = 1;
     if (what == 1) {
         a.theta = at<const float>(h, L.theta_b); a.w = at<const uint16_t>(h, L.w_bf16_b); a.wt = at<const uint16_t>(h, L.wt_bf16_b);
-        a.prefix = at<float>(h, L.prefix_b);
         a.keep_acts = 0;
     } else if (what == 2) {
         a.tp.tr_head = at<float>(h, L.head_new); a.tp.tr_val = at<float>(h, L.val_new);

@@ -125,3 +125,23 @@ def test_streaming_acting(gpu, orc, name, hidden, B, T):
                                              ("pendulum_8192", [128, 128], {}), ("pendulum_8192", [256, 256], {})])
 def test_resident_acting_last_group_missing(gpu, orc, name, hidden, env):
     lockstep(gpu, orc, variant(name, hidden, 4112, 2, **env), 10, updates=1)
+
+
+# the wall sums of bf16 mazes in the LDS of the activation buffers: first layers as wide as, wider and narrower than the others,
+# one and several tiles of environments; the decoupled step's replay is cut along time, every workgroup with its own sums
+@pytest.mark.parametrize("hidden,B,T", [([128, 512], 64, 5), ([512, 128], 128, 3), ([256], 64, 4), ([512, 512], 192, 6), ([128, 128], 64, 1)])
+def test_bf16_maze_wall_sums(gpu, orc, hidden, B, T):
+    cfg = variant("maze_16384", hidden, B, T, dtype="bf16", rows=8, cols=6, max_steps=9)
+    forced_lockstep(gpu, orc, cfg, 11, updates=1)
+    g = gpu.Anakin(cfg, seed=12)
+    o = orc.Oracle(cfg, seed=12)
+    for k in range(3):
+        PT.sync_oracle_from_gpu(g, o)
+        learned_on = (o.tr_reward.copy(), o.tr_done.copy())
+        g.step_decoupled()
+        tr = g.trajectory()
+        o.step_decoupled(forced_head=tr["head"])
+        PT.assert_rollout_equal(g, o, "maze", forced=True)
+        if k > 0:
+            PT.assert_learn_close(g, o, TOL_BF16, tr_after=tr, learned_on=learned_on, target_tol=TOL_BF16)
+    g.close()
