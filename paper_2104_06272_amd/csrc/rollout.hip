@@ -186,9 +186,11 @@ __device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const 
             const uint32_t bits = obs[m * OBS_WORDS + (cb >> 5)] >> (cb & 31);   // bits past the last cell are zero
 #pragma unroll
             for (int u = 0; u < CB; ++u) {
-                const float x = (bits >> u) & 1u ? 1.0f : 0.0f;
-                acc.x = fmaf(x, w[u].x, acc.x); acc.y = fmaf(x, w[u].y, acc.y);
-                acc.z = fmaf(x, w[u].z, acc.z); acc.w = fmaf(x, w[u].w, acc.w);
+                // the weight or, bit for bit, zero; not a product with the bit: 0 times an infinite weight is not 0.  (0.6 us of
+                // the 9 x 13 maze's 128-64 step; a select of the sum 0.8, additions under a branch 2.6)
+                const uint32_t keep = 0u - ((bits >> u) & 1u);
+                acc.x += f_from_bits(bits_from_f(w[u].x) & keep); acc.y += f_from_bits(bits_from_f(w[u].y) & keep);
+                acc.z += f_from_bits(bits_from_f(w[u].z) & keep); acc.w += f_from_bits(bits_from_f(w[u].w) & keep);
             }
         }
         *reinterpret_cast<float4*>(pre + m * N + c0) = acc;

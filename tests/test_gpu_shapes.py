@@ -1,5 +1,6 @@
 """GPU parity at the edges of the kernels' dispatch rules: shapes where a tile, a chunk or a row group ends in the
 middle, each in lockstep with the CPU oracle (unroll bit for bit in fp32, update per parameter region)."""
+import numpy as np
 import pytest
 
 from paper_2104_06272_amd import workloads as W
@@ -145,3 +146,27 @@ def test_bf16_maze_wall_sums(gpu, orc, hidden, B, T):
         if k > 0:
             PT.assert_learn_close(g, o, TOL_BF16, tr_after=tr, learned_on=learned_on, target_tol=TOL_BF16)
     g.close()
+
+
+# a weight row that an environment's maze does not select is not touched, whatever it holds (fp32 acting: streamed weights,
+# resident weights, the small resident form, the reference kernel)
+@pytest.mark.parametrize("hidden,canonical", [([128, 64], False), ([128, 128], False), ([64, 64], False), ([64, 64], True)])
+def test_infinite_wall_weight(gpu, hidden, canonical):
+    cfg = variant("maze_16384", hidden, 64, 4, rows=5, cols=7, max_steps=9)
+    heads = []
+    for w in (0.0, -np.inf):
+        g = gpu.Anakin(cfg, seed=13)
+        if canonical:
+            g.set_mode(gpu.MODE_CANONICAL_ACTING)
+        walls = g.get_walls()
+        cell = 8
+        theta = g.get_params()
+        theta[cell * hidden[0]:(cell + 1) * hidden[0]:3] = w
+        g.set_params(theta)
+        g.rollout()
+        heads.append(g.trajectory()["head"])
+        g.close()
+    free = ((walls[:, cell >> 5] >> (cell & 31)) & 1) == 0
+    assert 0 < free.sum() < 64
+    assert np.array_equal(heads[0][:, free], heads[1][:, free])
+    assert np.isfinite(heads[1]).all() and not np.array_equal(heads[0][:, ~free], heads[1][:, ~free])
