@@ -2,15 +2,16 @@
 // section 3.2: the backward pass is the expensive half of the update).
 //
 // A binary32 value is the exact sum of three bfloat16 terms, x = h + m + l (8 + 8 + 8 significand bits, each the
-// previous remainder rounded to nearest: |m| <= 2^-9 |x|, |l| <= 2^-18 |x|).  A product of two such values is nine
-// bfloat16 products, each exact in binary32; the six with the largest factors
+// previous remainder rounded to nearest: |m| <= 2^-8 |x|, |l| <= 2^-17 |x|; the range of "exact": split_terms.h).  A
+// product of two such values is nine bfloat16 products, each exact in binary32; the six with the largest factors
 //     h h,  h m,  m h,  m m,  h l,  l h
-// leave out 2^-26 |a b| at most (m l, l m, l l), a quarter of the rounding error 2^-24 of ONE binary32 operation, and
-// every sum is accumulated in binary32 by the matrix instruction exactly as before.  v_mfma_f32_32x32x16_bf16 does 16
-// reduction steps in 32 cycles, v_mfma_f32_32x32x2_f32 two in 64: six of the former replace eight of the latter, a
-// 2.67 times shorter matrix-core time for the same sums.  Relative error of a 256 x 256 layer's gradient over 8192
-// samples against binary64: 7.7e-8 here, 8.0e-8 with the binary32 instruction (5e-8 of each is the rounding of the
-// result to binary32 on both sides of the comparison).
+// leave out 2^-24 |a b| at most and 5e-9 |a b| (2^-27.5) in the root mean square (m l, l m, l l), no more than the rounding
+// error of ONE binary32 operation, and every sum is accumulated in binary32 by the matrix instruction exactly as before.
+// v_mfma_f32_32x32x16_bf16 does 16 reduction steps in 32 cycles, v_mfma_f32_32x32x2_f32 two in 64: six of the former
+// replace eight of the latter, a 2.67 times shorter matrix-core time for the same sums.  Relative error of whole update
+// gradients over 2080 samples against binary64 on the same stored forward pass, worst region of eight nets: 1.4e-7 with
+// these kernels, 1.3e-7 with the vector-ALU ones; hidden-layer regions 6.6e-8 to 9.5e-8 against 6.4e-8 to 9.4e-8
+// (test_split_products_keep_binary32).
 //
 //   gemm_tn   partial[s][i][j] = sum over chunk s of x[m][i] dY[m][j]   (+ column sums of dY)
 //   gemm_nt   dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j]
@@ -22,9 +23,10 @@
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l feeds A[row l%32][k 8 (l/32) .. +7] and B[k ..][col l%32];
 // accumulator register r is D[row 8 (r/4) + 4 (l/32) + r%4][col l%32].
 //
-// What bounds them: at 256 x 256 a sample costs 0.33 ns of matrix-core time for both products on the whole chip and 2 to
-// 3 KB of traffic, 0.4 to 0.5 ns at the rate of a copy.  Both products side by side, half the compute units each:
-// 81920 samples 200 -> 117 us, 262144 samples (pendulum) 580 -> 321 us against the binary32 kernels they replace.
+// What bounds them: at 256 x 256 a sample costs 0.63 ns of matrix-core time for both products on the whole chip (six
+// MFMAs per product, see above) and 2 to 3 KB of traffic, 0.4 to 0.5 ns at the rate of a copy.  Both products side by side,
+// half the compute units each: 81920 samples 200 -> 117 us, 262144 samples (pendulum) 580 -> 321 us against the binary32
+// kernels they replace; the matrix-core time of these is 51 and 164 us.
 #include "split_terms.h"
 #include "detmath.h"
 

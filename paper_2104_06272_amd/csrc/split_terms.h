@@ -16,7 +16,12 @@ __device__ __forceinline__ uint32_t pk_bf16_s(float lo, float hi)
     bf2_s v; v[0] = (__bf16)lo; v[1] = (__bf16)hi;               // round to nearest even, one instruction for the pair
     return __builtin_bit_cast(uint32_t, v);
 }
-// pair i of eight values as three packed terms, t[0] + t[1] + t[2] = x exactly
+// Pair i of eight values as three packed terms, t[0] + t[1] + t[2] = x exactly where x is 0 or 2^-102 <= |x| <= 3.3895e38
+// (the largest bfloat16).  Below, the last terms fall under the smallest normal bfloat16 and may be lost: up to 2^-126 per
+// term, whatever is left of values that a gradient's sum does not see.  Above, and for an infinite x, the first term is
+// infinite and the remainder is not a number, so a sum with such an operand is NaN (where a binary32 product could still be
+// infinite or, up to 3.4028e38, finite); NaN stays NaN.  Only activations, weights or gradients at the very end of the type
+// meet that, and an update that holds them is lost in binary32 as well (infinite heads, 0 times infinity in the same sums).
 __device__ __forceinline__ void split_pair(float x0, float x1, u4v_s (&t)[3], int i)
 {
     uint32_t p = pk_bf16_s(x0, x1);

@@ -382,3 +382,97 @@ def assert_bf16_layers_close(name, got, ref):
     share = float((d > 0).mean())
     assert share <= 0.02, f"{name}: {share:.2%} of the entries differ"
     return share
+
+
+def split_terms_np(x):
+    """a binary32 array as three bfloat16 terms, each the previous remainder rounded to nearest (binary64 arrays)"""
+    terms, r = [], np.asarray(x, np.float32)
+    for _ in range(3):
+        h = bf16_round_np(r)
+        terms.append(h.astype(np.float64))
+        r = r - h
+    return terms
+
+
+# Largest relative error (2-norm of a parameter region) of the products on split operands against binary64 on the same stored
+# forward pass: below half of what the loss of any one of the six products of terms shows (8e-7 at least on the CPU, where it is
+# planted), and 2.8 times the largest seen (1.4e-7, of which most is the head gradient's and the result's rounding to binary32:
+# the vector-ALU kernels show 1.3e-7 there)
+SPLIT_BOUND = 4e-7
+SIX_PRODUCTS = ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0))   # terms of the left and of the right operand
+
+
+def np_backward_from_stored(cfg, theta, X, acts, dhead, products=None):
+    """Gradient [P] in binary64 from a STORED forward pass of an fp32 net: first-layer input X [M][D], hidden activations
+    acts[l] [M][H_l], gradient of the objective with respect to the head outputs dhead [M][NH].
+    products: the hidden layers' products take their operands in three bfloat16 terms and sum these products of terms
+    only (None: the plain product)."""
+    hid = list(cfg["net"]["hidden"])
+    L, NH = len(hid), dhead.shape[1]
+    dims = [X.shape[1]] + hid
+    th = np.asarray(theta, np.float64)
+    Ws, w_off, off = [], [], 0
+    for l in range(L):
+        K, N = dims[l], dims[l + 1]
+        Ws.append(th[off:off + K * N].reshape(K, N)); w_off.append(off); off += K * N + N
+    Wh = th[off:off + hid[-1] * NH].reshape(hid[-1], NH)
+    g = np.zeros(off + hid[-1] * NH + NH)
+
+    def product(a, b):
+        if products is None:
+            return a @ b
+        ta, tb = split_terms_np(a), split_terms_np(b)
+        return sum(ta[i] @ tb[j] for i, j in products)
+
+    hs = [np.asarray(a, np.float64) for a in acts]
+    g[off:off + Wh.size] = (hs[-1].T @ dhead).ravel(); g[off + Wh.size:] = dhead.sum(0)
+    dz = (hs[-1] > 0) * (dhead @ Wh.T)
+    for l in range(L - 1, -1, -1):
+        gw = product(hs[l - 1].T, dz) if l > 0 else X.T.astype(np.float64) @ dz
+        g[w_off[l]:w_off[l] + gw.size] = gw.ravel()
+        g[w_off[l] + gw.size:w_off[l] + gw.size + dims[l + 1]] = dz.sum(0)
+        if l > 0:
+            dz = (hs[l - 1] > 0) * product(dz, Ws[l].T)
+    return g
+
+
+def np_head_gradient(cfg, head, action, eps, adv, ret):
+    """d(loss)/d(head outputs) in binary64 of M stored samples: head [M][NH], action [M] or (Gaussian policy) the noise
+    eps [M], adv and ret [M] as constants; the loss is the mean over the M samples"""
+    net = cfg["net"]
+    beta, cv = float(np.float32(net["entropy_coef"])), float(np.float32(net["value_coef"]))
+    hd = np.asarray(head, np.float64)
+    M = hd.shape[0]
+    A_, G_ = np.asarray(adv, np.float64), np.asarray(ret, np.float64)
+    d = np.zeros_like(hd)
+    if net["policy"] == "tanh_gaussian":
+        ls = np.clip(hd[:, 1], -5.0, 2.0)
+        e = np.asarray(eps, np.float64)
+        inside = (hd[:, 1] >= -5.0) & (hd[:, 1] <= 2.0)
+        d[:, 0] = -A_ * e / np.exp(ls)
+        d[:, 1] = np.where(inside, -A_ * (e * e - 1.0) - beta, 0.0)
+    else:
+        n = hd.shape[1] - 1
+        lp = hd[:, :n] - hd[:, :n].max(1, keepdims=True)
+        lp = lp - np.log(np.exp(lp).sum(1, keepdims=True))
+        p = np.exp(lp)
+        H = -(p * lp).sum(1, keepdims=True)
+        onehot = np.zeros_like(p); onehot[np.arange(M), np.asarray(action, np.int64)] = 1.0
+        d[:, :n] = -A_[:, None] * (onehot - p) + beta * p * (lp + H)
+    d[:, -1] = -2.0 * cv * (G_ - hd[:, -1])
+    return d / M
+
+
+def np_observation(cfg, tr):
+    """first-layer input [T*B][D] of a stored Catch or pendulum unroll, in binary64"""
+    T = tr["reward"].shape[0]
+    if cfg["env"]["kind"] == "pendulum":
+        th, thd = (tr[k][:T].astype(np.float64).ravel() for k in ("state_f0", "state_f1"))
+        return np.stack([np.cos(th), np.sin(th), thd], 1)
+    rows, cols = cfg["env"]["rows"], cfg["env"]["cols"]
+    s = binding.unpack_state_word("catch", tr["state_s0"][:T]).reshape(-1, 4)
+    x = np.zeros((s.shape[0], rows * cols))
+    n = np.arange(s.shape[0])
+    x[n, s[:, 1] * cols + s[:, 0]] = 1.0
+    x[n, (rows - 1) * cols + s[:, 2]] = 1.0
+    return x

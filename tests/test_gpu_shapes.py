@@ -170,3 +170,32 @@ def test_infinite_wall_weight(gpu, hidden, canonical):
     assert 0 < free.sum() < 64
     assert np.array_equal(heads[0][:, free], heads[1][:, free])
     assert np.isfinite(heads[1]).all() and not np.array_equal(heads[0][:, ~free], heads[1][:, ~free])
+
+
+# The fp32 backward products on split operands (and, as the measure, those on the vector ALU) against binary64 on the stored
+# forward pass: every pairing of tile widths, with the head pass and the pendulum's first layer folded in and without.  The bound
+# notices the loss of any one product of terms, which the CPU suite plants (test_parity_helpers.py).
+@pytest.mark.parametrize("name,hidden", [("catch_4096", [256, 256]), ("pendulum_8192", [256, 256]), ("catch_4096", [512, 256, 256]), ("pendulum_8192", [128, 128]),
+                                         ("catch_4096", [128, 256]), ("catch_4096", [256, 128, 64]), ("pendulum_8192", [64, 64, 128]), ("pendulum_8192", [64, 256, 64])])
+def test_split_products_keep_binary32(gpu, name, hidden):
+    cfg = variant(name, hidden, 416, 5)
+    M = 416 * 5
+    regions, _ = PT.param_regions(cfg)
+    grads = {}
+    for mode in ("split", "valu"):
+        g = gpu.Anakin(cfg, seed=14)
+        if mode == "valu":
+            g.set_mode(gpu.MODE_VALU_GEMM)
+        theta = g.get_params() + (0.05 * np.random.default_rng(14).standard_normal(g.P)).astype(np.float32)
+        g.set_params(theta)
+        g.rollout()
+        g.learn()
+        tr = g.trajectory()
+        grads[mode] = g.get_grads()
+        g.close()
+    d = PT.np_head_gradient(cfg, tr["head"][:5].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
+    ref = PT.np_backward_from_stored(cfg, theta, PT.np_observation(cfg, tr), [a.reshape(M, -1) for a in tr["act"]], d)
+    for mode, got in grads.items():
+        errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in regions}
+        print(f"{name} {hidden} {mode}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
+        assert max(errors.values()) <= PT.SPLIT_BOUND, errors
