@@ -13,7 +13,6 @@ struct ObsSrc {
     const uint32_t* walls;                                   // [8][B]
 };
 
-// dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j];  W is [K][N] row-major (K = inputs, N = outputs)
 // heads folded into the top hidden layer's products: dY is not read but formed on the way in,
 //   dY[m][j] = (hl[m][j] > 0) * sum_a wh[j][a] dhead[m][a]
 // from the layer's own forward activations hl, the per-sample head gradient and the head matrix
@@ -32,6 +31,7 @@ struct FirstFuse {
     const float* f0; const float* f1;   // [M] stored angle and angular velocity (null: not folded)
     float* partial;                     // [workgroups][3*K + K]
 };
+// dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j];  W is [K][N] row-major (K = inputs, N = outputs)
 struct GemmNtArgs {
     int M, K, N, bf16;
     HeadFuse hf;
@@ -60,8 +60,8 @@ hipError_t launch_gemm_nt_valu(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_valu(GemmTnArgs a, hipStream_t s);
 hipError_t launch_gemm_nt_mfma(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_mfma(GemmTnArgs a, hipStream_t s);
-// both products of a layer whose sides are multiples of 256, on split operands (gemm_split.hip)
 SplitWeightsArgs split_weights_args(const anakin* h);   // what the update's backward pass needs split (nothing: n = 0)
+// both products of a layer whose sides are multiples of 64 (split_gemm_shape), on split operands (gemm_split.hip)
 hipError_t launch_gemm_tn_nt_split(const NetShape& net, int l, const GemmTnArgs& t, const GemmNtArgs& n, int nt_blocks, hipStream_t s);
 
 }  // namespace ank

@@ -10,8 +10,9 @@
 // state snapshot while the tile is loaded.
 //
 // This file holds the vector-ALU versions (64x64 tiles, 4x4 per lane); the
-// matrix-core versions are in gemm_mfma.hip (tiled) and gemm_split.hip (layers
-// in whole 256-wide tiles) and share the argument blocks.
+// matrix-core versions are in gemm_mfma.hip (a maze's first layer, layers with a
+// 32-wide side) and gemm_split.hip (layers in whole 64-wide tiles: both products
+// in one launch, on split operands) and share the argument blocks.
 #include "gemm.h"
 
 namespace ank {
@@ -184,7 +185,7 @@ hipError_t launch_backward(anakin* h)
     const int M = h->B * h->T;
     hipError_t e;
     const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
-    // Top hidden layer in whole 256-wide tiles: its dW and dX products form dZ_L on the way in from the layer's forward
+    // Top hidden layer in whole 64-wide tiles: its dW and dX products form dZ_L on the way in from the layer's forward
     // activations and the head gradient, and the dW product also sums the head matrix's gradient, so dZ_L is neither
     // written nor read and the head pass is no kernel of its own.
     HeadFuse hf{};

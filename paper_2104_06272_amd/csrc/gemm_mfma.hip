@@ -1,6 +1,7 @@
 // Matrix-core (MFMA) versions of the dense-layer backward GEMMs for fp32
 // networks (paper section 3.1: the update differentiates through the policy
-// network; section 3.2: the backward pass is the expensive half).
+// network; section 3.2: the backward pass is the expensive half): the layers that
+// gemm_split.hip does not take (a 32-wide side), and dW of a maze's first layer.
 //
 //   gemm_nt_mask_mfma    dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j]
 //   gemm_tn_splitk_mfma  partial[s][i][j] = sum_{m in chunk s} x[m][i] dY[m][j]  (+ column sums of dY)

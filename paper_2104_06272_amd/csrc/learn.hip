@@ -1,14 +1,17 @@
 // The update on a stored unroll (paper section 3.1: the parameter update that
 // follows the T interactions and reuses the policy's forward pass):
 //   returns_scan          reverse scan over t of the lambda-return recursion
-//   vtrace_ratio / _scan  off-policy targets for an unroll acted by older parameters (decoupled steps)
 //   head_grad             actor-critic loss terms and the gradient w.r.t. head outputs
+//   scan_loss             the two above in one launch; for an unroll acted by older parameters (decoupled steps)
+//                         with off-policy targets in place of the returns
+//   vtrace_ratio / _scan  those targets where the unroll does not fit scan_loss
 //   head_backward(_mfma)  gradient of the head matrix, and of the last hidden layer
 //   first_layer_grad*     gradient of the first layer from the compact state (Catch, Pendulum)
 //   learn_one_layer       the whole backward pass of a one-hidden-layer net
+//   learn_catch_fused     returns, loss and backward pass of a small one-hidden-layer Catch net
 //   adam_reduce(_narrow, _flat)  fixed-order sum of split-K partials fused with Adam
 // Hidden-layer GEMMs live in gemm.hip (vector ALU), gemm_mfma.hip (tiled) and
-// gemm_split.hip (layers in whole 256-wide tiles, which also take over the head
+// gemm_split.hip (layers in whole 64-wide tiles, which also take over the head
 // pass of such a top layer); the bf16 update in learn_bf16.hip; the reverse
 // sweep of the pathwise policy gradient in pathwise.hip.
 // No floating-point atomics anywhere: every reduction has a fixed order, so runs

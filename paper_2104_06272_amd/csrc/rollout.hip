@@ -15,9 +15,10 @@
 // order: fma(0,w,acc) = acc and fma(1,w,acc) = acc + w, the same bits.
 //
 // Kernels: rollout_kernel (vector ALU), rollout_stream_kernel (matrix cores, weights streamed),
-// rollout_resident_kernel (two-layer nets up to 256 wide, W2 in registers),
-// rollout_lane_kernel (one hidden layer: one lane per env).  Each has a REPLAY
-// form, the learner's forward pass over a stored unroll for decoupled steps.
+// rollout_resident_kernel and rollout_resident64_kernel (two equal layers of 128 or 256 resp. 64
+// units, W2 in registers), rollout_lane_kernel (one hidden layer: one lane per env).  All but the
+// two resident ones have a REPLAY form, the learner's forward pass over a stored unroll (decoupled
+// steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
 #include "internal.h"
 
 namespace ank {

@@ -52,18 +52,18 @@ LOCKSTEP_CASES = {
     "maze_fp32_small": (variant("maze_16384", hidden=[64, 64], B=64, T=32, dtype="fp32", max_steps=20), 1, 3, TOL_F32),
     "maze_bf16_canonical": (variant("maze_16384", hidden=[64, 64, 32], B=64, T=16, max_steps=40), 3, 2, TOL_BF16),
     "maze_fp32_8x8": (variant("maze_16384", hidden=[32], B=32, T=24, dtype="fp32", rows=8, cols=8, max_steps=30), 0, 2, TOL_F32),
-    # 512 -> 256: the weights-resident dX kernel with two column blocks, tiled dW; three 256-wide layers: resident both ways
+    # 512 -> 256: the products on split operands with two tiles along the inputs; three 256-wide layers: head pass folded into
+    # the top one, plain products below it
     "catch_512x256": (variant("catch_4096", hidden=[512, 256], B=64, T=10), 3, 2, TOL_F32),
     "catch_256x256x256": (variant("catch_4096", hidden=[256, 256, 256], B=96, T=9), 4, 2, TOL_F32),
     # 512-wide last layer: two column blocks in the head pass; 512-wide first layer of the pendulum kernel
     "catch_256x512": (variant("catch_4096", hidden=[256, 512], B=64, T=10), 5, 2, TOL_F32),
     "pendulum_512x256": (variant("pendulum_8192", hidden=[512, 256], B=64, T=12, max_steps=9), 6, 2, TOL_F32),
-    # pendulum first layer summed inside the dX product of a middle layer, two 32-sample stages per workgroup;
-    # and a sample count (272 tiles of 32) that 256 dX workgroups do not cut evenly, which keeps the separate kernel
+    # pendulum first layer summed inside the dX product of a middle layer, one 128-sample tile per workgroup; and 68 tiles,
+    # fewer than the workgroups there could be
     "pendulum_256x256x256_B512": (variant("pendulum_8192", hidden=[256, 256, 256], B=512, T=32), 11, 1, TOL_F32),
     "pendulum_256x256_B272": (variant("pendulum_8192", B=272, T=32), 12, 1, TOL_F32),
-    # 143 = 11 x 13 stages of 32 samples: no chunk count near the number of compute units divides them, so the
-    # 256 -> 256 layer's dW product stays with the tiled kernel while its dX product is the resident one
+    # 4576 = 16 x 11 x 26 samples: chunks of the 256 -> 256 layer's dW product do not divide them, the last one is shorter
     "catch_256x256_B208_T22": (variant("catch_4096", B=208, T=22), 13, 1, TOL_F32),
     # degenerate shapes: a one-step unroll (the return is reward + bootstrap only), a single tile of envs,
     # an episode end at every step (max_steps = 1: every transition is terminal, nothing bootstraps)
@@ -101,14 +101,13 @@ def test_lockstep(gpu, orc, case):
     g.close()
 
 
-@pytest.mark.parametrize("hidden,B", [([64, 64], 64), ([256, 256], 128)])
+@pytest.mark.parametrize("hidden,B", [([64, 64], 64), ([256, 256], 128), ([32, 32], 64)])
 @pytest.mark.parametrize("shift", [3.5, -7.5, 1.97])
 def test_pendulum_log_sigma_at_and_outside_its_clamp(gpu, orc, hidden, B, shift):
     """log_sigma is clamped to [-5, 2] in the sampler, and a clamped log_sigma passes no gradient (neither from the
     score function nor from the entropy bonus).  With the head's bias pushed above or below the clamp every sample
     is clamped; with the bias just under the upper end some are and some are not.  Unrolls bit-exact, updates within
-    tolerance, on the vector-ALU head pass (64-wide net) and on the head pass folded into the resident products
-    (256-wide net)."""
+    tolerance, on the head pass of its own (32-wide net) and on the one folded into the top layer's products."""
     cfg = variant("pendulum_8192", hidden=hidden, B=B, T=16, max_steps=11)
     say(f"[log_sigma clamp] hidden={hidden} B={B} bias={shift}")
     g = gpu.Anakin(cfg, seed=31); o = orc.Oracle(cfg, seed=31)
@@ -419,8 +418,8 @@ def test_full_size_headline_update(gpu, orc):
 def test_full_size_whole_step(gpu, orc, name):
     """Two more workloads at their full size, one whole step in lockstep, in the launch shape the benchmark times:
     every env of the unroll bit-exact, then the update (the lane-per-env acting kernel and the one-layer update for
-    the tiny net; the 32-env resident acting kernel, the pendulum's first-layer kernel and the head-folded products
-    for the pendulum).  The oracle needs ten to thirty seconds for each."""
+    the tiny net; the 32-env resident acting kernel and the products with heads and first layer folded in for the
+    pendulum).  The oracle needs ten to thirty seconds for each."""
     cfg = W.get(name)
     kind = cfg["env"]["kind"]
     say(f"[full size] {name} whole step, all envs")
