@@ -26,6 +26,8 @@ for p in (ROOT,):
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_TFLOPS = 157.3      # fp32 vector (packed) = fp32 matrix-core peak
 PEAK_BF16_TFLOPS = 2500.0
+# fp32 products on split operands: six bf16 matrix instructions for what the result counts as one product
+PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 
 def measured_traffic(workload):
     """HBM bytes per launch (MB) of each kernel of a workload, read from profiles/<workload>_hbm_traffic.md: the
@@ -164,8 +166,13 @@ def kernel_models(cfg, P, launched=()):
         models["gemm_tn_top"] = ("mfma", top_flop / 1e12, mfma_peak, "TFLOP/s")
         if top_flop / top_bytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
             models["gemm_tn_top"] = ("hbm", top_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
-    # a layer whose two products run as one launch (256-wide fp32 layers): both counted
-    models["gemm_tn_nt"] = ("mfma", (tn + nt) / 1e12, mfma_peak, "TFLOP/s")
+    # fp32 layers in whole 64-wide tiles: both products in one launch on split operands, both counted.  Bytes: x and dY read
+    # (the top layer's dY is formed from its activations, as many bytes), dX written but where nothing reads it (the
+    # pendulum's first layer); for narrow layers these take longer than the matrix instructions
+    models["gemm_tn_nt"] = ("mfma", (tn + nt) / 1e12, PEAK_SPLIT_TFLOPS, "TFLOP/s")
+    split_bytes = sum(4.0 * (dims[i] + dims[i + 1] + (0 if kind == "pendulum" and i == 1 else dims[i])) * M for i in range(1, len(dims) - 1))
+    if (tn + nt) / (PEAK_SPLIT_TFLOPS * 1e12) < split_bytes / (PEAK_HBM_GBS * 1e9):
+        models["gemm_tn_nt"] = ("hbm", split_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
     models["gemm_tn_obs"] = ("mfma", 2.0 * dims[0] * dims[1] * M / 1e12, mfma_peak, "TFLOP/s")
     if kind == "maze":
         cells = cfg["env"]["rows"] * cfg["env"]["cols"]
