@@ -11,9 +11,15 @@
 //   dZ1        = relu'(h1) (dZ2 W2^T), W2 rows in registers, dZ2 rows broadcast from LDS
 //   dW2, db2   = h1^T dZ2
 //   dW1, db1   scatter of dZ1 into the two board rows of every sample
-// and writes one partial gradient.  The workgroup that arrives last at an integer counter (ordinary vector
-// atomic; device-scope fences around it) adds the partials in ascending workgroup order -- so the bytes do not
-// depend on which one it was -- and applies Adam.
+// and writes one partial gradient.  Then the workgroups wait for each other at an integer counter (ordinary vector
+// atomics; device-scope fences around them), and each adds the partials of its slice of the parameters in ascending
+// workgroup order -- so the bytes do not depend on who arrived when -- and applies Adam to it.
+//
+// What the time is (64 environments, T = 20: 16 workgroups of 80 samples; 28.7 us by events, of which 4 are theirs;
+// cycles of one workgroup, 59 k in all = 24.8 us): first loads 11.6 k, scan 2.8 k, loss 1.4 k, dZ2 5.1 k, dZ1 9.2 k
+// (two row tiles of 64 MFMAs on two of the four wavefronts, 4.1 k of matrix-core time each), dW2 4.9 k, sums over lanes
+// 1.9 k, dW1 and the partial's stores 10.7 k, rendezvous 5.5 k, Adam 5.1 k, departure 1.2 k: a chain of short phases, a
+// third of it round trips to memory, on 16 of 256 compute units.
 #include "internal.h"
 #include "loss.h"
 
