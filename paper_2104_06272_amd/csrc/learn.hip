@@ -693,7 +693,7 @@ __device__ __forceinline__ uint32_t pk_bf16_l(float lo, float hi)
     bf2_l v; v[0] = (__bf16)lo; v[1] = (__bf16)hi;               // round to nearest even, one instruction for the pair
     return __builtin_bit_cast(uint32_t, v);
 }
-// x as three bfloat16 terms whose sum is x (8 + 8 + 8 significand bits): with the 0/1 board as the other operand
+// x as three bfloat16 terms whose sum is x (8 + 8 + 8 significand bits; split_terms.h states the range): with the 0/1 board as the other operand
 // every product is exact and the fp32 accumulation is the one an fp32 matrix instruction would do, at a fifth of
 // its matrix-core time (three 8-pass instructions of 16 samples instead of eight 16-pass ones of 2)
 __device__ __forceinline__ void split3(const float (&x)[8], u4v_l& hi, u4v_l& mid, u4v_l& lo)

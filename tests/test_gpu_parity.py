@@ -841,7 +841,8 @@ def test_n_updates_per_unroll_bf16(gpu, orc):
 
 
 DECOUPLED_CASES = {
-    # name: (cfg, seed, steps) -- every fp32 acting kernel in its replay form, both policies, the one-layer update
+    # name: (cfg, seed, steps) -- every fp32 acting kernel that has a replay form (streamed weights, also for the nets that act
+    # with resident ones; a lane per environment; the vector-ALU kernel), both policies, the one-layer update
     "catch_small": (_fast_lr(variant("catch_small")), 0, 4),
     "catch_256x256_B256": (_fast_lr(variant("catch_4096", B=256)), 1, 3),
     "catch_tiny_net_B512": (_fast_lr(variant("catch_262144", B=512)), 0, 3),
@@ -850,6 +851,8 @@ DECOUPLED_CASES = {
     "maze_fp32_small": (_fast_lr(variant("maze_16384", hidden=[64, 64], B=64, T=32, dtype="fp32", max_steps=20)), 1, 3),
     "catch_512x256": (_fast_lr(variant("catch_4096", hidden=[512, 256], B=64, T=10)), 3, 3),
     "catch_ragged_B80_T7": (_fast_lr(variant("catch_small", B=80, T=7)), 2, 3),
+    "catch_64x32": (_fast_lr(variant("catch_small", hidden=[64, 32], T=9)), 4, 3),
+    "maze_fp32_one_layer": (_fast_lr(variant("maze_16384", hidden=[128], B=48, T=9, dtype="fp32", rows=5, cols=7, max_steps=9)), 5, 3),
 }
 
 

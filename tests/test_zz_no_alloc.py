@@ -68,7 +68,7 @@ def test_static_scratch_with_several_updates_per_unroll(gpu):
 
 
 def test_static_scratch_rejections(gpu):
-    # the headline workload's update needs ~170 MB of scratch: more than the static array holds
+    # the headline workload's update needs some 220 MB of scratch: more than the static array holds
     g = gpu.Anakin(W.get("catch_4096"), seed=0)
     g.rollout()
     with pytest.raises(gpu.AnakinError) as e:
