@@ -117,6 +117,17 @@ struct AdamArgs {
     float lr, beta1, beta2, eps, bc1, bc2;
 };
 
+// Acting with the hidden matrices in the register file (rollout_pinned.hip).  A block is 128 inputs x 16 outputs of one
+// layer, 32 registers of one wavefront; the blocks of 16 outputs follow one another in one wavefront.  Two words per block:
+struct PinnedPlan {
+    static constexpr int WAVES = 4, MAX_BLOCKS = 6;                                // wavefronts that compute the hidden layers
+    enum : uint32_t { VALID = 1u, START = 2u, END = 4u, HALF = 8u, PAIR = 16u };   // first / last block of its outputs; 64 inputs only; with the next block, whose outputs are the next 16
+    static constexpr int LAYER = 5, LGK = 7, LGN = 11, TILE = 15, KBLOCK = 20;     // bits: layer (2), log2 of its inputs (4), of its outputs (4), output / 16 (5), input / 128 (2)
+    static constexpr int XOFF = 0, YOFF = 16;                                      // second word: LDS place of the layer's inputs and of these outputs, in 16 bytes (16 each)
+    int NB;                               // blocks per wavefront (0: not applicable)
+    uint32_t block[WAVES][MAX_BLOCKS][2];
+};
+
 struct Layout {
     size_t theta, grad, m, v, w_bf16, wt_bf16;
     size_t theta0, w0_bf16;      // copies of theta / w_bf16 taken before the first of several updates on one unroll
@@ -165,6 +176,7 @@ struct anakin {
     int TM;                       // envs per workgroup in the vector-ALU rollout kernel
     int TM_mfma;                  // envs per workgroup in the matrix-core rollout kernel (0: not applicable)
     int TM_res;                   // envs per workgroup in the weights-resident rollout kernel (0: not applicable)
+    ank::PinnedPlan pinned;      // rollout kernel with hidden matrices of any widths in registers
     int splits[ank::MAX_REGIONS]; // split-K factor per parameter region
     int quanta[ank::MAX_REGIONS]; // rows of a region's chunks are multiples of this (chunk_rows)
     int loss_blocks;
@@ -285,6 +297,8 @@ inline int first_fused_splits(const NetShape& n, int env_kind, int M)
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B);
+void rollout_pinned_plan(const NetShape& net, const EnvDims& env, int B, PinnedPlan& p);
+hipError_t launch_pinned(anakin* h, const RolloutArgs& args);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);
 size_t rollout_lds_bytes(const NetShape& net, const EnvDims& env, int TM, int* ldx);
 

@@ -16,23 +16,13 @@
 //
 // Kernels: rollout_kernel (vector ALU), rollout_stream_kernel (matrix cores, weights streamed),
 // rollout_resident_kernel and rollout_resident64_kernel (two equal layers of 128 or 256 resp. 64
-// units, W2 in registers), rollout_lane_kernel (one hidden layer: one lane per env).  All but the
-// two resident ones have a REPLAY form, the learner's forward pass over a stored unroll (decoupled
-// steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
-#include "internal.h"
+// units, W2 in registers), rollout_pinned_kernel (other nets whose hidden matrices fit the registers, at
+// most 4096 environments; rollout_pinned.hip), rollout_lane_kernel (one hidden layer: one lane per env).
+// The first, the second and the last have a REPLAY form, the learner's forward pass over a stored unroll
+// (decoupled steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
+#include "acting.h"
 
 namespace ank {
-
-__device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ float bfr(float x) { return bf16_to_f(bf16_bits(x)); }
-
-template <bool BF>
-__device__ __forceinline__ float4 ldw4(const float* p)
-{
-    float4 w = ld4(p);
-    if (BF) { w.x = bfr(w.x); w.y = bfr(w.y); w.z = bfr(w.z); w.w = bfr(w.w); }
-    return w;
-}
 
 template <int RM, bool BF>
 __device__ __forceinline__ void finish_rows(float (&acc)[RM][4], float* __restrict__ Y, int ldx, int m0, int c0,
@@ -83,11 +73,6 @@ __device__ __forceinline__ void dense_layer(const float* __restrict__ X, float* 
     }
     finish_rows<RM, BF>(acc, Y, ldx, m0, c0, gout, N);
 }
-
-// per-env observation descriptor in LDS: 12 words per env
-//   Catch: [0] ball cell, [1] paddle cell;  Pendulum: [0..2] = (cos, sin, theta_dot) as floats;
-//   Maze: [0..7] wall words, [8] agent cell
-constexpr int OBS_WORDS = 12;
 
 // first layer: gather-sum for the one-hot boards, three fmas for the pendulum
 template <int ENV, int RM, bool BF>
@@ -164,38 +149,6 @@ __device__ __forceinline__ void first_layer(const RolloutArgs& a, const uint32_t
         }
     }
     finish_rows<RM, BF>(acc, Y, ldx, m0, c0, gout, N);
-}
-
-// Maze: pre[TM][H1] = b1 + the wall rows of the environment's maze, cells ascending -- the part of the first layer
-// that never changes within a launch.  The dense scan of the wall plane used to run in every step of the unroll (14 of
-// 15 us per step of the 117-cell maze with a 128-64 net); it now runs once per launch, and the sums stay in LDS in the
-// canonical order, so the logits are the same bits.
-template <bool BF, int NTHR>
-__device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const uint32_t* __restrict__ obs, const float* __restrict__ w1,
-                                            const float* __restrict__ b1, float* __restrict__ pre, int tid)
-{
-    const int N = a.net.dims[1], n = a.env.rows * a.env.cols, groups = TM * N / 4;
-    constexpr int CB = 8;                                        // weight rows in flight
-    for (int i = tid; i < groups; i += NTHR) {
-        const int c0 = (i % (N >> 2)) << 2, m = i / (N >> 2);
-        const float* wp = w1 + c0;
-        float4 acc = ld4(b1 + c0);
-        for (int cb = 0; cb < n; cb += CB) {
-            float4 w[CB];
-#pragma unroll
-            for (int u = 0; u < CB; ++u) w[u] = ldw4<BF>(wp + (size_t)(cb + u < n ? cb + u : n - 1) * N);
-            const uint32_t bits = obs[m * OBS_WORDS + (cb >> 5)] >> (cb & 31);   // bits past the last cell are zero
-#pragma unroll
-            for (int u = 0; u < CB; ++u) {
-                // the weight or, bit for bit, zero; not a product with the bit: 0 times an infinite weight is not 0.  (0.6 us of
-                // the 9 x 13 maze's 128-64 step; a select of the sum 0.8, additions under a branch 2.6)
-                const uint32_t keep = 0u - ((bits >> u) & 1u);
-                acc.x += f_from_bits(bits_from_f(w[u].x) & keep); acc.y += f_from_bits(bits_from_f(w[u].y) & keep);
-                acc.z += f_from_bits(bits_from_f(w[u].z) & keep); acc.w += f_from_bits(bits_from_f(w[u].w) & keep);
-            }
-        }
-        *reinterpret_cast<float4*>(pre + m * N + c0) = acc;
-    }
 }
 
 template <int ENV, bool BF>
@@ -515,7 +468,7 @@ __global__ __launch_bounds__(WG) void rollout_kernel(const RolloutArgs a, const 
 
 // ---------------------------------------------------------------------------
 // Hidden layers on the matrix cores, weights streamed from L2: fp32 nets of two or more hidden layers that the
-// weights-resident kernel below does not take.  On gfx950 the fp32 MFMA instructions add their products one k at a time
+// weights-resident kernels (below and rollout_pinned.hip) do not take.  On gfx950 the fp32 MFMA instructions add their products one k at a time
 // with a fused multiply-add, ascending in k, and chain through the accumulator operand -- measured bit-identical to the
 // sequential fmaf chain on random, wide-range and integer inputs -- so starting the accumulator from the bias and feeding
 // k in ascending order reproduces the canonical order exactly while running at matrix-core rate.
@@ -1853,6 +1806,7 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
             return lw == 32 ? launch_lane<ENV_PENDULUM, 32, REPLAY>(h, a) : launch_lane<ENV_PENDULUM, 64, REPLAY>(h, a);
         }
     }
+    if (!REPLAY && h->pinned.NB > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_pinned(h, a);
     if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
         switch (h->env.kind) {

@@ -199,3 +199,43 @@ def test_split_products_keep_binary32(gpu, name, hidden):
         errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in regions}
         print(f"{name} {hidden} {mode}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
         assert max(errors.values()) <= PT.SPLIT_BOUND, errors
+
+
+@pytest.mark.parametrize("name,hidden,B,T,env", [
+    ("catch_4096", [64, 128], 16, 3, {}),                    # half blocks of inputs, one pair of output tiles per wavefront
+    ("catch_4096", [128, 64], 48, 4, {}),                    # one block per wavefront
+    ("catch_4096", [64, 64, 64, 64], 32, 3, {}),             # as many layers as there can be
+    ("catch_4096", [512, 64], 32, 2, {}),                    # four blocks in a row; first layer of 512
+    ("catch_4096", [256, 128, 64], 16, 3, dict(rows=13, cols=7, max_steps=12)),   # pairs, then a single block: five of six places
+    ("catch_4096", [64, 128, 128], 32, 3, {}),               # half-block pairs before whole ones
+    ("catch_4096", [64, 256], 16, 2, dict(rows=16, cols=12, max_steps=15)),       # head matrix from LDS
+    ("pendulum_8192", [256, 64], 48, 4, {}),
+    ("pendulum_8192", [64, 64, 128], 16, 3, {}),             # a single block, then a pair at the next even place
+    ("pendulum_8192", [128, 256], 32, 2, {}),
+    ("maze_16384", [128, 64], 32, 4, dict(rows=9, cols=13, max_steps=128)),       # wall words that end inside a pair of words
+    ("maze_16384", [256, 64], 16, 3, {}),                    # agent plane read from memory: it does not fit LDS
+    ("maze_16384", [64, 128], 16, 3, dict(rows=2, cols=2, max_steps=8, p_wall=0.0)),
+    ("maze_16384", [64, 64, 64], 16, 3, dict(rows=16, cols=16, max_steps=64, p_wall=0.3)),   # more walls than one round of loads takes
+])
+def test_acting_with_pinned_matrices(gpu, orc, name, hidden, B, T, env):
+    lockstep(gpu, orc, variant(name, hidden, B, T, "fp32", **env), seed=5, updates=1)
+
+
+@pytest.mark.parametrize("name,hidden,B", [("catch_4096", [256, 128, 64], 4096), ("catch_4096", [256, 128, 64], 4112), ("maze_16384", [128, 64], 4096)])
+def test_pinned_and_streamed_matrices_give_the_same_unroll(gpu, name, hidden, B):
+    """The largest batch with one tile per compute unit, and one tile more (which streams)."""
+    cfg = variant(name, hidden, B, 6)
+    runs = []
+    for mode in (0, gpu.MODE_STREAM_WEIGHTS):
+        g = gpu.Anakin(cfg, seed=9)
+        g.set_mode(mode)
+        g.rollout(); g.rollout()
+        tr = g.trajectory()
+        runs.append((tr, g.get_env_state()))
+        g.close()
+    (a, sa), (b, sb) = runs
+    for key in ("state_s0", "action", "reward", "done", "value", "head", "act"):
+        for x, y in zip(a[key], b[key]):                     # steps, or layers
+            np.testing.assert_array_equal(x, y, err_msg=key)
+    for x, y in zip(sa, sb):
+        np.testing.assert_array_equal(x, y)
