@@ -1,7 +1,9 @@
 // Acting for bf16 networks on the matrix cores (paper figure 2 top; section 2.1
 // loop).  Same persistent structure as the fp32 kernels: a workgroup of eight
 // wavefronts owns 64 environments for the whole unroll, env state in registers,
-// activations in LDS (bf16), trajectory and hidden activations to HBM.
+// activations in LDS (bf16), trajectory and hidden activations to HBM.  It takes the nets
+// whose hidden matrices do not fit the registers (the others: rollout_bf16_pinned.hip) and all
+// replays.
 //
 // Numerics (bf16 workload): weights and layer inputs are bfloat16, products are
 // exact in fp32, accumulation is fp32 inside v_mfma_f32_32x32x16_bf16, bias and
@@ -26,51 +28,11 @@
 // Operand layout of v_mfma_f32_32x32x16_bf16 (verified on gfx950): lane l feeds
 // A[row l%32][k 8*(l/32) .. +7] and B[k 8*(l/32) .. +7][col l%32]; accumulator
 // register r of lane l is D[row 8*(r/4) + 4*(l/32) + r%4][col l%32].
-#include "internal.h"
+#include "acting_bf16.h"
 
 namespace ank {
 
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-
 constexpr int BTM = 64;                 // envs per workgroup
-constexpr int BWG = 512;                // threads per workgroup: two wavefronts per SIMD
-constexpr int BOBS = 12;                // observation words per env (as in the fp32 kernels)
-
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32v2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32v4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float bf2f(uint16_t h) { return bf16_to_f(h); }
-// two floats rounded to bfloat16 (round to nearest even), low half first
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
-{
-    bf2 v;
-    v[0] = (__bf16)lo; v[1] = (__bf16)hi;
-    return __builtin_bit_cast(uint32_t, v);
-}
-__device__ __forceinline__ float relu(float x) { return x > 0.0f ? x : 0.0f; }
-// two packed ReLU outputs (never negative, never -0) -> 1 in bit 0 resp. bit 16 where the half is not zero
-__device__ __forceinline__ uint32_t nonzero_flags_pk(uint32_t w)
-{
-    uint32_t r;
-    const uint32_t one = 0x00010001u;
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(w), "v"(one));
-    return r;
-}
-
-struct RolloutBf16Args {
-    EnvDims env;
-    NetShape net;
-    TrajPtrs tp;                         // tp.act[] point to bf16 buffers here
-    const float* theta;                  // fp32 master (biases are read from here)
-    const uint16_t* w;                   // bf16 copy of theta, same indexing
-    const uint16_t* wt;                  // bf16 copy in matrix-core operand tiles (heads: [NH][HL])
-    int B, T, ldx;                       // ldx: LDS row stride in bf16 elements
-    int keep_acts;                       // store the packed hidden activations for the update
-    int tend, tseg;                      // REPLAY: steps evaluated (T, or T + 1 with the bootstrap state), steps per workgroup (grid y)
-    uint64_t seed, gstep;
-};
 
 // Hidden layer on the matrix cores: Y[64][N] = relu(X[64][K] W + b), X and Y bf16 in LDS.
 // Wavefront w computes columns [32*NT*w, 32*NT*(w+1)); wavefronts past N stay idle.
@@ -610,13 +572,11 @@ void fill_rollout_args(anakin* h, RolloutArgs& a);
 
 // what: 0 the acting unroll, 1 the actor of a decoupled step (behaviour copies of the parameters, no activations
 // kept), 2 the learner's replay of the stored unroll with the current parameters
-template <bool REPLAY>
-static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true)
+void fill_bf16_args(anakin* h, int what, RolloutBf16Args& a)
 {
     RolloutArgs base;
     fill_rollout_args(h, base);
     const Layout& L = h->lay;
-    RolloutBf16Args a;
     a.env = base.env; a.net = base.net; a.tp = base.tp; a.theta = base.theta;
     a.w = at<const uint16_t>(h, L.w_bf16); a.wt = at<const uint16_t>(h, L.wt_bf16);
     a.keep_acts = 1;
@@ -627,11 +587,19 @@ static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true
         a.tp.tr_head = at<float>(h, L.head_new); a.tp.tr_val = at<float>(h, L.val_new);
     }
     a.B = h->B; a.T = h->T; a.seed = h->seed; a.gstep = h->gstep;
-    a.tend = h->T + (bootstrap ? 1 : 0);
-    a.tseg = REPLAY ? replay_segment(h->B / BTM, a.tend) : a.tend;
+    a.tend = a.tseg = h->T + 1;
     int hmax = 0;
     for (int l = 1; l <= h->net.L; ++l) hmax = h->net.dims[l] > hmax ? h->net.dims[l] : hmax;
     a.ldx = hmax + 8;
+}
+
+template <bool REPLAY>
+static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true)
+{
+    RolloutBf16Args a;
+    fill_bf16_args(h, what, a);
+    a.tend = h->T + (bootstrap ? 1 : 0);
+    a.tseg = REPLAY ? replay_segment(h->B / BTM, a.tend) : a.tend;
     const int HL = h->net.dims[h->net.L], H1 = h->net.dims[1];
     const size_t lds = (size_t)2 * BTM * a.ldx * 2 + (size_t)8 * (HL + 8) * 2 + (size_t)4 * BTM * 8 * 4 + (size_t)BTM * (BOBS + 2) * 4;
     auto launch = [&](auto kern) {
@@ -654,8 +622,8 @@ static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true
 #undef ANK_BF16_W
 }
 
-hipError_t launch_rollout_bf16(anakin* h) { return launch_bf16_forward<false>(h, 0); }
-hipError_t launch_rollout_bf16_behaviour(anakin* h) { return launch_bf16_forward<false>(h, 1); }
+hipError_t launch_rollout_bf16(anakin* h) { return pinned_bf16_ok(h) ? launch_pinned_bf16(h, 0) : launch_bf16_forward<false>(h, 0); }
+hipError_t launch_rollout_bf16_behaviour(anakin* h) { return pinned_bf16_ok(h) ? launch_pinned_bf16(h, 1) : launch_bf16_forward<false>(h, 1); }
 hipError_t launch_replay_bf16(anakin* h, bool bootstrap) { return launch_bf16_forward<true>(h, 2, bootstrap); }
 
 }  // namespace ank

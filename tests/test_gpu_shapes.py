@@ -239,3 +239,36 @@ def test_pinned_and_streamed_matrices_give_the_same_unroll(gpu, name, hidden, B)
             np.testing.assert_array_equal(x, y, err_msg=key)
     for x, y in zip(sa, sb):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("name,hidden,B,env", [
+    ("catch_4096", [128, 128], 64, {}),
+    ("pendulum_8192", [128], 64, {}),                        # no matrix between hidden layers
+    ("catch_4096", [256, 512], 128, {}),                     # two tiles of outputs per wavefront and layer
+    ("pendulum_8192", [512, 256], 64, {}),                   # four blocks in a row; ReLU masks of the first layer
+    ("catch_4096", [128, 512, 128], 64, {}),
+    ("maze_16384", [128, 128, 128], 64, dict(rows=8, cols=8, max_steps=64)),
+    ("maze_16384", [512, 128], 64, {}),                      # agent plane read from memory: it does not fit LDS
+    ("catch_4096", [256, 256, 256], 8256, {}),               # 64 environments per workgroup
+    ("pendulum_8192", [512, 128], 8256, {}),
+    ("maze_16384", [256, 256], 8256, dict(rows=8, cols=6, max_steps=64)),
+])
+def test_bf16_pinned_and_streamed_matrices_give_the_same_update(gpu, name, hidden, B, env):
+    """Same bits: the unroll, and through the update the packed activations and ReLU masks that it reads."""
+    cfg = variant(name, hidden, B, 3, "bf16", **env)
+    print(f"[bf16 pinned] {name} {hidden} B={B}", flush=True)
+    runs = []
+    for mode in (0, gpu.MODE_STREAM_WEIGHTS):
+        g = gpu.Anakin(cfg, seed=9)
+        assert g.plan()["bf16_matrix_path"] == 1
+        g.set_mode(mode)
+        g.step(); g.step()
+        runs.append((g.trajectory(), list(g.get_env_state()) + [g.get_params(), g.get_grads()]))
+        g.close()
+    (a, sa), (b, sb) = runs
+    pendulum = cfg["env"]["kind"] == "pendulum"
+    for key in ("state_s0", "reward", "done", "value", "head", "act", "adv", "ret") + (("state_f0", "state_f1", "eps", "action_f") if pendulum else ("action",)):
+        for x, y in zip(a[key], b[key]):
+            np.testing.assert_array_equal(x, y, err_msg=key)
+    for x, y in zip(sa, sb):
+        np.testing.assert_array_equal(x, y)
