@@ -4,6 +4,8 @@
 
 namespace ank {
 
+typedef float f4v __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ float bfr(float x) { return bf16_to_f(bf16_bits(x)); }
 
@@ -14,6 +16,26 @@ __device__ __forceinline__ float4 ldw4(const float* p)
     if (BF) { w.x = bfr(w.x); w.y = bfr(w.y); w.z = bfr(w.z); w.w = bfr(w.w); }
     return w;
 }
+// BF: two values rounded to bfloat16 in place, by the conversion instruction (bfr's bits for every finite value)
+template <bool BF>
+__device__ __forceinline__ void round2(float& a, float& b)
+{
+    if (!BF) return;
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    b2 v;
+    v[0] = (__bf16)a; v[1] = (__bf16)b;
+    const uint32_t p = __builtin_bit_cast(uint32_t, v);
+    a = f_from_bits(p << 16); b = f_from_bits(p & 0xffff0000u);
+}
+template <bool BF, class V>
+__device__ __forceinline__ void round4(V& v)
+{
+    float a = v[0], b = v[1], c = v[2], d = v[3];
+    round2<BF>(a, b); round2<BF>(c, d);
+    v[0] = a; v[1] = b; v[2] = c; v[3] = d;
+}
+template <bool BF>
+__device__ __forceinline__ float round1(float x) { return BF ? bfr(x) : x; }
 
 // per-env observation descriptor in LDS: 12 words per env
 //   Catch: [0] ball cell, [1] paddle cell;  Pendulum: [0..2] = (cos, sin, theta_dot) as floats;
@@ -33,7 +55,6 @@ template <bool BF, int NTHR>
 __device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const uint32_t* __restrict__ obs, const float* __restrict__ w1,
                                             const float* __restrict__ b1, float* __restrict__ pre, int tid)
 {
-    typedef float f4v __attribute__((ext_vector_type(4)));
     const int N = a.net.dims[1], n = a.env.rows * a.env.cols, groups = TM * N / 4, lg4 = 29 - __builtin_clz((uint32_t)N);
     constexpr int CB = 16;                                       // weight rows in flight
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w1), 0, (uint32_t)(n * N) * 4u, 0x00020000);
@@ -61,6 +82,37 @@ __device__ __forceinline__ void maze_prefix(const RolloutArgs& a, int TM, const 
         }
         *reinterpret_cast<f4v*>(pre + m * N + c0) = acc;
     }
+}
+
+// lane Q of each row of 16 lanes, in all of them
+template <int Q>
+__device__ __forceinline__ float row_lane(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + Q, 0xf, 0xf, true)); }
+template <int Q>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + Q, 0xf, 0xf, true); }
+
+// acc += sum over 16 k of x[row's lane k] * w[k], k ascending, one fused multiply-add each.  (As one block: between single
+// statements the compiler puts a wait state each.  The leading wait is what a DPP operand needs after a vector write.)
+__device__ __forceinline__ void chain16(float x, f4v w0, f4v w1, f4v w2, f4v w3, float& acc)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc)
+        : "v"(x), "v"(w0[0]), "v"(w0[1]), "v"(w0[2]), "v"(w0[3]), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]), "v"(w2[0]), "v"(w2[1]), "v"(w2[2]), "v"(w2[3]), "v"(w3[0]), "v"(w3[1]), "v"(w3[2]), "v"(w3[3]));
 }
 
 }  // namespace ank

@@ -297,6 +297,8 @@ inline int first_fused_splits(const NetShape& n, int env_kind, int M)
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B);
+bool rollout_one_ok(const anakin* h);
+hipError_t launch_rollout_one(anakin* h, const RolloutArgs& args, bool replay);
 void rollout_pinned_plan(const NetShape& net, const EnvDims& env, int B, PinnedPlan& p);
 hipError_t launch_pinned(anakin* h, const RolloutArgs& args);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);

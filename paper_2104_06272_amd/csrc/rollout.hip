@@ -17,9 +17,14 @@
 // Kernels: rollout_kernel (vector ALU), rollout_stream_kernel (matrix cores, weights streamed),
 // rollout_resident_kernel and rollout_resident64_kernel (two equal layers of 128 or 256 resp. 64
 // units, W2 in registers), rollout_pinned_kernel (other nets whose hidden matrices fit the registers, at
-// most 4096 environments; rollout_pinned.hip), rollout_lane_kernel (one hidden layer: one lane per env).
-// The first, the second and the last have a REPLAY form, the learner's forward pass over a stored unroll
-// (decoupled steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
+// most 4096 environments; rollout_pinned.hip), rollout_lane_kernel (one narrow hidden layer, very many
+// environments: one lane per env), rollout_one_kernel (other nets of one hidden layer; rollout_one.hip).  All but
+// the resident and pinned ones have a REPLAY form, the learner's forward pass over a stored unroll (decoupled
+// steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
+// BF: bf16 nets that the bf16 matrix instructions do not take (batches that are no multiple of 64, mazes of other
+// sizes): the same kernels on weights and activations rounded to bfloat16, products and sums in binary32 -- the
+// vector-ALU kernel's bits at the matrix instruction's rate (256-256, 1040 environments, T = 20: 1197 -> 207 us;
+// maze 512-256, 5568, T = 17: 3908 -> 633).
 #include "acting.h"
 
 namespace ank {
@@ -183,7 +188,6 @@ __device__ __forceinline__ void run_dense_layer(const RolloutArgs& a, int TM, in
 }
 
 
-typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 template <int NT>
@@ -534,7 +538,7 @@ __device__ __forceinline__ void stream_load(float (&d)[8], rsrc_w theta, const S
 }
 
 // Layer l of the step for this wavefront's column tiles: X and Y in LDS.  wA, wB: the stream's two blocks in flight.
-template <int MT>
+template <int MT, bool BF>
 __device__ __forceinline__ void stream_layer(const StreamNet& n, rsrc_w theta, int l, const float* __restrict__ X, float* __restrict__ Y, int ldx,
                                              const float* __restrict__ bias, int wave, int lane, StreamCursor& cur, float (&wA)[8], float (&wB)[8])
 {
@@ -550,6 +554,8 @@ __device__ __forceinline__ void stream_layer(const StreamNet& n, rsrc_w theta, i
         __builtin_amdgcn_sched_barrier(0);
     };
     auto block = [&](float (&w)[8], float (&av)[8][MT]) {
+#pragma unroll
+        for (int u = 0; u < 8; u += 2) round2<BF>(w[u], w[u + 1]);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -574,11 +580,16 @@ __device__ __forceinline__ void stream_layer(const StreamNet& n, rsrc_w theta, i
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) Y[(16 * m + 4 * kq + r) * ldx + col] = acc[m][r] > 0.0f ? acc[m][r] : 0.0f;
+            for (int r = 0; r < 4; r += 2) {
+                float y0 = acc[m][r] > 0.0f ? acc[m][r] : 0.0f, y1 = acc[m][r + 1] > 0.0f ? acc[m][r + 1] : 0.0f;
+                round2<BF>(y0, y1);
+                Y[(16 * m + 4 * kq + r) * ldx + col] = y0;
+                Y[(16 * m + 4 * kq + r + 1) * ldx + col] = y1;
+            }
     }
 }
 
-template <int ENV, int MT, bool REPLAY>
+template <int ENV, int MT, bool REPLAY, bool BF>
 __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamArgs sa)
 {
     const RolloutArgs& a = sa.r;
@@ -607,7 +618,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
     const TrajPtrs& tp = a.tp;
     const int ldw = HL + 4;
     const float* w1g = a.theta + a.net.w_off[0];
-    for (int i = tid; i < HL * NH; i += STW + STA) whs[(i % NH) * ldw + i / NH] = a.theta[a.net.wh_off + i];
+    for (int i = tid; i < HL * NH; i += STW + STA) whs[(i % NH) * ldw + i / NH] = round1<BF>(a.theta[a.net.wh_off + i]);
     if (tid < 8) bhs[tid] = tid < NH ? a.theta[a.net.bh_off + tid] : 0.0f;
     {
         int off = 0;
@@ -626,10 +637,10 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
 #pragma unroll
             for (int u = 0; u < 4; ++u) { const int i = i0 + u * NTH + tid; v[u] = src[i < n4 ? i : 0]; }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { const int i = i0 + u * NTH + tid; if (i < n4) dst[i] = v[u]; }
+            for (int u = 0; u < 4; ++u) { const int i = i0 + u * NTH + tid; if (i < n4) { round4<BF>(v[u]); dst[i] = v[u]; } }
         }
         if (ENV == ENV_MAZE)
-            for (int i = tid; i < H1; i += NTH) w1s[(size_t)n_cells * H1 + i] = w1g[(size_t)(3 * n_cells - 1) * H1 + i];
+            for (int i = tid; i < H1; i += NTH) w1s[(size_t)n_cells * H1 + i] = round1<BF>(w1g[(size_t)(3 * n_cells - 1) * H1 + i]);
     }
     const bool aux = wave >= STW / 64;                               // a scalar branch: what follows stays in scalar registers
     const int at = tid - STW;
@@ -646,7 +657,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
     }
     if (ENV == ENV_MAZE) {
         __syncthreads();
-        maze_prefix<false, STW + STA>(a, TM, obs, w1g, bs, pre, tid);
+        maze_prefix<BF, STW + STA>(a, TM, obs, w1g, bs, pre, tid);
     }
     const int t_begin = REPLAY ? (int)blockIdx.y * sa.tseg : 0;
     const int t_end = REPLAY ? (t_begin + sa.tseg < sa.tend ? t_begin + sa.tseg : sa.tend) : T + 1;
@@ -671,9 +682,9 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
         } else if (ENV == ENV_PENDULUM) {
             float sn, cs;
             det_sincos(st.f0, sn, cs);
-            obs[at * OBS_WORDS + 0] = bits_from_f(cs);
-            obs[at * OBS_WORDS + 1] = bits_from_f(sn);
-            obs[at * OBS_WORDS + 2] = bits_from_f(st.f1);
+            obs[at * OBS_WORDS + 0] = bits_from_f(round1<BF>(cs));
+            obs[at * OBS_WORDS + 1] = bits_from_f(round1<BF>(sn));
+            obs[at * OBS_WORDS + 2] = bits_from_f(round1<BF>(st.f1));
         } else {
             obs[at * OBS_WORDS + 8] = st.s0 & 0xffffu;
         }
@@ -730,7 +741,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
 #pragma unroll
                         for (int k = 0; k < 3; ++k) {
                             if (sa.w1_lds) wv[u][k] = *reinterpret_cast<const f4v*>(w1s + k * H1 + c);
-                            else wv[u][k] = *reinterpret_cast<const f4v*>(w1g + k * H1 + c);
+                            else { wv[u][k] = *reinterpret_cast<const f4v*>(w1g + k * H1 + c); round4<BF>(wv[u][k]); }
                         }
                         bv[u] = *reinterpret_cast<const f4v*>(bs + c);
                     } else {
@@ -741,6 +752,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
                         } else {
                             wv[u][0] = *reinterpret_cast<const f4v*>(w1g + (size_t)(ENV == ENV_CATCH ? r0 : n_cells + r0) * H1 + c);
                             wv[u][1] = *reinterpret_cast<const f4v*>(w1g + (size_t)(ENV == ENV_CATCH ? r1 : 3 * n_cells - 1) * H1 + c);
+                            round4<BF>(wv[u][0]); round4<BF>(wv[u][1]);
                         }
                         bv[u] = ENV == ENV_MAZE ? *reinterpret_cast<const f4v*>(pre + m * H1 + c) : *reinterpret_cast<const f4v*>(bs + c);
                     }
@@ -765,6 +777,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
                         }
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+                        round4<BF>(v);
                         *reinterpret_cast<f4v*>(bufA + m * ldx + c) = v;
                     }
                 }
@@ -774,7 +787,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
             float* nxt = bufB;
             const float* bias = bs + H1;
             for (int l = 1; l < L; ++l) {
-                stream_layer<MT>(net, theta, l, cur, nxt, ldx, bias, wave, lane, sc, wA, wB);
+                stream_layer<MT, BF>(net, theta, l, cur, nxt, ldx, bias, wave, lane, sc, wA, wB);
                 bias += net.dim(l + 1);
                 __syncthreads();
                 float* tmp = cur; cur = nxt; nxt = tmp;
@@ -1600,13 +1613,17 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
     }
 }
 
-// one-hidden-layer nets the lane kernel takes: width 32 or 64 on Catch or the pendulum, fp32, no kept activations
+// One-hidden-layer nets the lane kernel takes: width 32 or 64 on Catch or the pendulum, fp32, no kept activations -- and
+// enough environments that a lane each fills the chip; with fewer a row of 16 lanes per environment (rollout_one.hip) is
+// done sooner.  Catch, T = 16, a lane against 16 lanes: width 32, 8192 environments 30 us against 16, 32768 32.5 against
+// 35, 262144 75 against 231; width 64, 32768 61 against 46, 65536 64 against 85.
 static int rollout_lane_width(const anakin* h)
 {
     const NetShape& n = h->net;
     if (n.bf16 || n.L != 1 || h->env.kind == ENV_MAZE || !one_layer_fused(h)) return 0;
     if (h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)) return 0;
-    return (n.dims[1] == 32 || n.dims[1] == 64) ? n.dims[1] : 0;
+    if ((n.dims[1] == 32 && h->B >= 32768) || (n.dims[1] == 64 && h->B >= 49152)) return n.dims[1];
+    return 0;
 }
 
 template <int ENV, int H, bool REPLAY>
@@ -1660,7 +1677,7 @@ static size_t stream_lds_bytes(const NetShape& net, const EnvDims& env, int TM, 
 // waits for another workgroup, but the weight stream is shared by the tile).
 int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B)
 {
-    if (net.bf16 || net.L < 2) return 0;
+    if (net.L < 2) return 0;
     for (int l = 1; l < net.L; ++l) if (net.dims[l] % 64) return 0;     // blocks of 64 inputs
     int best = 0;
     for (int tm = 16; tm <= 64; tm *= 2) {
@@ -1742,7 +1759,7 @@ static int replay_tile(const anakin* h, int tend)
     return best;
 }
 
-template <int ENV, bool REPLAY>
+template <int ENV, bool REPLAY, bool BF>
 static hipError_t launch_stream(anakin* h, const RolloutArgs& args, int TM)
 {
     StreamArgs a;
@@ -1752,7 +1769,7 @@ static hipError_t launch_stream(anakin* h, const RolloutArgs& args, int TM)
     const int tiles = (h->B + TM - 1) / TM;
     a.tend = args.T + (args.bootstrap ? 1 : 0);
     a.tseg = replay_segment(tiles, a.tend);
-    auto kern = TM == 16 ? rollout_stream_kernel<ENV, 1, REPLAY> : TM == 32 ? rollout_stream_kernel<ENV, 2, REPLAY> : rollout_stream_kernel<ENV, 4, REPLAY>;
+    auto kern = TM == 16 ? rollout_stream_kernel<ENV, 1, REPLAY, BF> : TM == 32 ? rollout_stream_kernel<ENV, 2, REPLAY, BF> : rollout_stream_kernel<ENV, 4, REPLAY, BF>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
@@ -1806,6 +1823,7 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
             return lw == 32 ? launch_lane<ENV_PENDULUM, 32, REPLAY>(h, a) : launch_lane<ENV_PENDULUM, 64, REPLAY>(h, a);
         }
     }
+    if (rollout_one_ok(h)) return launch_rollout_one(h, a, REPLAY);
     if (!REPLAY && h->pinned.NB > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_pinned(h, a);
     if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
@@ -1818,9 +1836,9 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
     if (h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING)) {
         const int TM = REPLAY ? replay_tile(h, a.T + (a.bootstrap ? 1 : 0)) : h->TM_mfma;
         switch (h->env.kind) {
-            case ENV_CATCH:    return launch_stream<ENV_CATCH, REPLAY>(h, a, TM);
-            case ENV_PENDULUM: return launch_stream<ENV_PENDULUM, REPLAY>(h, a, TM);
-            default:           return launch_stream<ENV_MAZE, REPLAY>(h, a, TM);
+            case ENV_CATCH:    return bf ? launch_stream<ENV_CATCH, REPLAY, true>(h, a, TM) : launch_stream<ENV_CATCH, REPLAY, false>(h, a, TM);
+            case ENV_PENDULUM: return bf ? launch_stream<ENV_PENDULUM, REPLAY, true>(h, a, TM) : launch_stream<ENV_PENDULUM, REPLAY, false>(h, a, TM);
+            default:           return bf ? launch_stream<ENV_MAZE, REPLAY, true>(h, a, TM) : launch_stream<ENV_MAZE, REPLAY, false>(h, a, TM);
         }
     }
     switch (h->env.kind) {

@@ -18,13 +18,14 @@
 // cycles against 8 or 16 -- and was slower where a layer has 64 outputs, 111 us against 106 on the net below.)
 // An unroll against the streaming kernel: Catch 13 x 7, 256-128-64, 1008 environments, T = 24 150 -> 106 us; maze 9 x 13,
 // 128-64, 1040, T = 23 89 -> 55; 128-128-128, 1024, T = 16 98 -> 66; pendulum 64-64-64, 2048, T = 20 79 -> 56.
+// BF: bf16 nets that the bf16 matrix instructions do not take: weights, activations and features rounded to bfloat16, the
+// arithmetic the same (pendulum 128-128, 48 environments, T = 20, vector ALU -> here: 509 -> 63 us).
 #include <type_traits>
 #include <string.h>
 #include "acting.h"
 
 namespace ank {
 
-typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int PTM = 16;                                            // environments per workgroup
 constexpr int PCW = PinnedPlan::WAVES;                           // wavefronts that compute the hidden layers, one per SIMD
@@ -38,39 +39,7 @@ struct PinnedArgs {
 };
 typedef const __attribute__((address_space(4))) PinnedArgs* kernarg;
 
-// lane Q of each row of 16 lanes, in all of them
-template <int Q>
-__device__ __forceinline__ float row_lane(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + Q, 0xf, 0xf, true)); }
-template <int Q>
-__device__ __forceinline__ uint32_t row_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + Q, 0xf, 0xf, true); }
-
-// acc += sum over 16 k of x[row's lane k] * w[k], k ascending, one fused multiply-add each.  (As one block: between single
-// statements the compiler puts a wait state each.  The leading wait is what a DPP operand needs after a vector write.)
-__device__ __forceinline__ void chain16(float x, f4v w0, f4v w1, f4v w2, f4v w3, float& acc)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc)
-        : "v"(x), "v"(w0[0]), "v"(w0[1]), "v"(w0[2]), "v"(w0[3]), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]), "v"(w2[0]), "v"(w2[1]), "v"(w2[2]), "v"(w2[3]), "v"(w3[0]), "v"(w3[1]), "v"(w3[2]), "v"(w3[3]));
-}
-
-
-template <int ENV, int NB>
+template <int ENV, int NB, bool BF>
 __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArgs q)
 {
     constexpr int NH = ENV == ENV_CATCH ? 4 : ENV == ENV_PENDULUM ? 3 : 5, NHP = NH <= 4 ? 4 : 8, A = NH - 1;
@@ -96,7 +65,7 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
     // what goes to LDS; every wavefront asks for what it keeps in registers first
     auto fill = [&]() __attribute__((always_inline)) {
         if (HL > HREG)
-            for (int i = tid; i < HL * NH; i += PTHR) whs[(i % NH) * ldw + i / NH] = a.theta[a.net.wh_off + i];
+            for (int i = tid; i < HL * NH; i += PTHR) whs[(i % NH) * ldw + i / NH] = round1<BF>(a.theta[a.net.wh_off + i]);
         for (int i = tid; i < H1; i += PTHR) b1s[i] = a.theta[a.net.b_off[0] + i];
         if (q.w1_lds) {
             const f4v* src = reinterpret_cast<const f4v*>(w1g + (ENV == ENV_MAZE ? (size_t)n_cells * H1 : 0));
@@ -107,15 +76,15 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
 #pragma unroll
                 for (int u = 0; u < 4; ++u) { const int i = i0 + u * PTHR + tid; v[u] = src[i < n4 ? i : 0]; }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { const int i = i0 + u * PTHR + tid; if (i < n4) dst[i] = v[u]; }
+                for (int u = 0; u < 4; ++u) { const int i = i0 + u * PTHR + tid; if (i < n4) { round4<BF>(v[u]); dst[i] = v[u]; } }
             }
             if (ENV == ENV_MAZE)
-                for (int i = tid; i < H1; i += PTHR) w1s[(size_t)n_cells * H1 + i] = w1g[(size_t)(3 * n_cells - 1) * H1 + i];
+                for (int i = tid; i < H1; i += PTHR) w1s[(size_t)n_cells * H1 + i] = round1<BF>(w1g[(size_t)(3 * n_cells - 1) * H1 + i]);
         }
         if (ENV == ENV_MAZE) {
             for (int i = tid; i < PTM * 8; i += PTHR) obs[(i >> 3) * OBS_WORDS + (i & 7)] = tp.walls[(size_t)(i & 7) * B + b0 + (i >> 3)];
             __syncthreads();
-            maze_prefix<false, PTHR>(a, PTM, obs, w1g, b1s, pre, tid);
+            maze_prefix<BF, PTHR>(a, PTM, obs, w1g, b1s, pre, tid);
         }
     };
     const int lane0 = lane;
@@ -144,6 +113,8 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
                 const uint32_t off = 4u * (uint32_t)((lane >> 4) * N + col);
 #pragma unroll
                 for (int u = 0; u < 32; ++u) w[i][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(theta, off, 4 * (a.net.w_off[l] + (k0 + (u < n ? 4 * u : 0)) * N), 0));
+#pragma unroll
+                for (int u = 0; u < 32; u += 2) round2<BF>(w[i][u], w[i][u + 1]);
                 bv[i] = a.theta[a.net.b_off[l] + col];
             } else {
 #pragma unroll
@@ -185,7 +156,10 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
             };
             auto end = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) smem[yi + r * ldy + 16 * j] = acc[j][r] > 0.0f ? acc[j][r] : 0.0f;
+                for (int r = 0; r < 4; ++r) acc[j][r] = acc[j][r] > 0.0f ? acc[j][r] : 0.0f;
+                round4<BF>(acc[j]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) smem[yi + r * ldy + 16 * j] = acc[j][r];
             };
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -257,6 +231,8 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
             for (int u = 64; u < HREG; ++u) hw[u] = src[u * NH];
         }
     }
+#pragma unroll
+    for (int u = 0; u < HREG; u += 2) round2<BF>(hw[u], hw[u + 1]);
     EnvState st{0u, 0.0f, 0.0f};
     st.s0 = tp.s0[b0 + row0 + (lane >> 4)];
     if (ENV == ENV_PENDULUM) { st.f0 = tp.f0[b0 + row0 + (lane >> 4)]; st.f1 = tp.f1[b0 + row0 + (lane >> 4)]; }
@@ -279,6 +255,7 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
         auto out = [&](int c0, f4v v) __attribute__((always_inline)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+            round4<BF>(v);
             *reinterpret_cast<f4v*>(x1 + c0) = v;
         };
         auto gather = [&](auto n, int c0, const float* base, const float* r0, const float* r1) __attribute__((always_inline)) {
@@ -291,6 +268,10 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
                 u1[p] = *reinterpret_cast<const f4v*>(r1 + c0 + 64 * p);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (!q.w1_lds) {                                       // (rows in LDS are rounded already)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) { round4<BF>(u0[p]); round4<BF>(u1[p]); }
+            }
 #pragma unroll
             for (int p = 0; p < NP; ++p) { v[p] += u0[p]; v[p] += u1[p]; out(c0 + 64 * p, v[p]); }
         };
@@ -334,7 +315,7 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
         } else {
             float f[3];
             det_sincos(st.f0, sine, f[0]);
-            f[1] = sine; f[2] = st.f1;
+            f[0] = round1<BF>(f[0]); f[1] = round1<BF>(sine); f[2] = round1<BF>(st.f1);
             all([&](auto n, int c0) __attribute__((always_inline)) { features(n, c0, f); });
         }
     };
@@ -508,7 +489,7 @@ static bool pinned_share(const NetShape& net, const int* xo, PinnedPlan& p)
 void rollout_pinned_plan(const NetShape& net, const EnvDims& env, int B, PinnedPlan& p)
 {
     memset(&p, 0, sizeof p);
-    if (net.bf16 || net.L < 2 || B > PTM * 256 || rollout_resident_tile(net, env.kind, B)) return;
+    if (net.L < 2 || B > PTM * 256 || rollout_resident_tile(net, env.kind, B)) return;
     for (int l = 1; l <= net.L; ++l) if (net.dims[l] % 64 || net.dims[l] > 512) return;
     PinnedArgs q;
     if (pinned_lds(net, env, q) > 160 * 1024 || (env.kind == ENV_PENDULUM && !q.w1_lds) || !pinned_share(net, q.xo, p)) p.NB = 0;
@@ -517,7 +498,8 @@ void rollout_pinned_plan(const NetShape& net, const EnvDims& env, int B, PinnedP
 template <int ENV>
 static hipError_t launch_pinned_env(anakin* h, const PinnedArgs& q, size_t lds)
 {
-    auto kern = q.p.NB == 4 ? rollout_pinned_kernel<ENV, 4> : rollout_pinned_kernel<ENV, 6>;
+    auto kern = h->net.bf16 ? (q.p.NB == 4 ? rollout_pinned_kernel<ENV, 4, true> : rollout_pinned_kernel<ENV, 6, true>)
+                            : (q.p.NB == 4 ? rollout_pinned_kernel<ENV, 4, false> : rollout_pinned_kernel<ENV, 6, false>);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(h, "rollout");

@@ -272,3 +272,52 @@ def test_bf16_pinned_and_streamed_matrices_give_the_same_update(gpu, name, hidde
             np.testing.assert_array_equal(x, y, err_msg=key)
     for x, y in zip(sa, sb):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("name,hidden,B,dtype,env", [
+    # one hidden layer: a row of 16 lanes per environment; 256 has its head weights in LDS
+    ("catch_4096", [32], 256, "fp32", {}),
+    ("catch_4096", [64], 48, "fp32", {}),
+    ("catch_4096", [128], 80, "bf16", {}),
+    ("catch_4096", [256], 48, "fp32", dict(rows=16, cols=12, max_steps=15)),       # first-layer rows beyond LDS: read from memory
+    ("catch_4096", [256], 4176, "bf16", dict(rows=16, cols=12, max_steps=15)),
+    ("pendulum_8192", [32], 96, "fp32", {}),
+    ("pendulum_8192", [128], 16, "fp32", {}),
+    ("pendulum_8192", [256], 80, "bf16", {}),
+    ("maze_16384", [32], 32, "fp32", dict(rows=5, cols=7, max_steps=16)),
+    ("maze_16384", [64], 48, "bf16", {}),
+    ("maze_16384", [128], 4112, "fp32", dict(rows=9, cols=13, max_steps=64)),
+    ("maze_16384", [256], 16, "bf16", dict(rows=16, cols=16, max_steps=64, p_wall=0.3)),
+    # bf16 nets that the bf16 matrix path does not take, on the fp32 matrix instruction
+    ("catch_4096", [128, 128], 48, "bf16", {}),
+    ("catch_4096", [256, 512], 80, "bf16", dict(rows=16, cols=12, max_steps=15)),  # streamed, first-layer rows from memory
+    ("pendulum_8192", [128, 64, 128], 16, "bf16", {}),
+    ("pendulum_8192", [512, 512], 48, "bf16", {}),
+    ("maze_16384", [256, 128], 48, "bf16", dict(rows=12, cols=14, max_steps=64)),
+    ("maze_16384", [512, 256], 64, "bf16", dict(rows=9, cols=13, max_steps=64)),   # a batch of 64, but cells no multiple of 16
+    ("maze_16384", [128, 256], 8208, "bf16", {}),                                  # more than one tile of 16 per compute unit
+])
+def test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, env):
+    """The unroll, the learner's replays and what the update makes of them, bit for bit as with the vector-ALU kernel."""
+    cfg = variant(name, hidden, B, 9, dtype, **env)
+    print(f"[canonical {dtype}] {name} {hidden} B={B}", flush=True)
+    runs = []
+    for mode in (gpu.MODE_CANONICAL_ACTING, 0, gpu.MODE_STREAM_WEIGHTS):
+        g = gpu.Anakin(cfg, seed=4)
+        if dtype == "bf16":
+            assert g.plan()["bf16_matrix_path"] == 0
+        g.set_mode(mode)
+        g.step()
+        tr, out = g.trajectory(), [g.get_params()]
+        g.step_decoupled(); g.step_decoupled(); g.step_decoupled()
+        out += [g.get_params(), g.get_grads()] + list(g.get_env_state())
+        runs.append((tr, out))
+        g.close()
+    a, sa = runs[0]
+    pendulum = cfg["env"]["kind"] == "pendulum"
+    for b, sb in runs[1:]:
+        for key in ("state_s0", "reward", "done", "value", "head", "act") + (("state_f0", "state_f1", "eps", "action_f") if pendulum else ("action",)):
+            for x, y in zip(a[key], b[key]):
+                np.testing.assert_array_equal(x, y, err_msg=key)
+        for x, y in zip(sa, sb):
+            np.testing.assert_array_equal(x, y)
