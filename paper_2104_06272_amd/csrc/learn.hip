@@ -1346,7 +1346,10 @@ __global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce(const AdamArgs a)
 }
 
 // One parameter per lane, 64 per workgroup: four times the workgroups of adam_reduce, which is what small parameter
-// vectors (under about 2^18) need to keep every compute unit loading.
+// vectors (under about 2^18) need to keep every compute unit loading.  Also where the partials are few: the 16
+// wavefronts read one each, side by side, and wave order is then ascending order, so the bits are adam_reduce_flat's
+// (Catch 128-128, 256 samples, 16 partials: 24.0 us there, 6.7 here; 64-64-128: 24.0 and 6.5; 512-128 in bf16: 21 and
+// 10.5).
 __global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce_narrow(const AdamArgs a)
 {
     // 64 consecutive parameters per workgroup; each of the 16 wavefronts adds its share of the
@@ -1388,7 +1391,8 @@ __global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce_narrow(const Adam
 
 // The same update for parameter regions with few partials (at most 16): one lane per parameter adds its
 // partials in ascending order itself, so a wavefront streams 64 consecutive parameters of every array --
-// the shape that reaches the HBM roofline when P is large.
+// the shape that reaches the HBM roofline when P is large (2^18 and up; below that the serial chain of loads, up to
+// 16 round trips on a few workgroups, is all of its time).
 __global__ __launch_bounds__(WG) void adam_reduce_flat(const AdamArgs a)
 {
     constexpr int UF = 4;                                        // parameters per lane, WG apart: loads of all four in flight
@@ -1432,7 +1436,7 @@ static void launch_adam_kernel(const AdamArgs& a, hipStream_t s)
 {
     int max_splits = 0;
     for (int r = 0; r < a.n_regions; ++r) max_splits = a.reg[r].splits > max_splits ? a.reg[r].splits : max_splits;
-    if (max_splits <= 16) hipLaunchKernelGGL(adam_reduce_flat, dim3((a.P + 4 * WG - 1) / (4 * WG)), dim3(WG), 0, s, a);
+    if (max_splits <= 16 && a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce_flat, dim3((a.P + 4 * WG - 1) / (4 * WG)), dim3(WG), 0, s, a);
     else if (a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce, dim3((a.P + 255) / 256), dim3(ADAM_WAVES * 64), 0, s, a);
     else hipLaunchKernelGGL(adam_reduce_narrow, dim3((a.P + 63) / 64), dim3(ADAM_WAVES * 64), 0, s, a);
 }
