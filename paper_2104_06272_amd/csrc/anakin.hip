@@ -199,11 +199,24 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
                 // pays one prologue instead of two.
                 set(l, 1, split_tn_cap(ns, l), 16);
             }
-    if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // scatter kernel: more, smaller chunks
-    if (ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0) set(0, 1, 256, 64);   // matrix-core scatter: 64-sample steps, about two workgroups (of 128 columns) per CU
+    if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // many small chunks
+    if (first_onehot_shape(ed)) {
+        // the one-hot kernel: at most 2048 wavefronts of 32 columns (a maze has two kinds), so that its time is not paid
+        // again as partial sums in the optimiser kernel, and at least four units of 16 samples per chunk (kernel +
+        // optimiser kernel, most wavefronts / least units: Catch 256-256 B=4096 T=20 1024/8 40.9 us, 2048/8 39.1, 4096/8
+        // 45.6; maze 512-128 B=9216 T=30 430, 273, 283; maze of 9 x 13, 128-64, 1495 units, 2048/4 25.9, 2048/16 27.5,
+        // 2048/32 33.7; Catch 128-128, 128 units, 14.2, 19.6, 25.2).  Never more chunks than the dense product has, if
+        // the update's scratch could fit the static array.
+        int most = 2048 / ((ns.dims[1] / 32) * (ed.kind == ENV_MAZE ? 2 : 1));
+        size_t widths = 0;
+        for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
+        if (widths * 4 * M < (size_t)ANAKIN_STATIC_SCRATCH_BYTES) { if (most > splits[0]) most = splits[0]; if (most > 256) most = 256; }
+        const int want = M / 64 > 1 ? M / 64 : 1;
+        set(0, 1, want < most ? want : most, bfp ? 64 : 16);
+    }
     if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
-    if (ns.L == 1 && ed.kind != ENV_MAZE) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
+    if (ns.L == 1 && (ed.kind == ENV_PENDULUM || one_layer_shape(ns, ed))) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
         // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
         // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the

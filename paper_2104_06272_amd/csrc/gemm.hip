@@ -202,8 +202,13 @@ hipError_t launch_backward(anakin* h)
     const bool first_fused = mfma && first_fused_splits(n, h->env.kind, M) > 0;
     for (int l = n.L - 1; l >= 0; --l) {
         if (l == 0 && first_fused) continue;
-        // one-hot boards (Catch) and the 3-feature pendulum need no GEMM for the first layer
-        if (l == 0 && h->env.kind != ENV_MAZE && !(h->mode & ANAKIN_MODE_VALU_GEMM) && (size_t)WG * n.dims[0] * 4 <= 96 * 1024) {
+        // boards and the 3-feature pendulum need no GEMM for the first layer
+        if (l == 0 && first_onehot(h)) {
+            e = launch_first_layer_onehot(h, false);
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        if (l == 0 && h->env.kind == ENV_PENDULUM && !(h->mode & ANAKIN_MODE_VALU_GEMM)) {
             e = launch_first_layer_grad(h);
             if (e != hipSuccess) return e;
             continue;

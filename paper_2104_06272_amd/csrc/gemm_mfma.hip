@@ -1,7 +1,8 @@
 // Matrix-core (MFMA) versions of the dense-layer backward GEMMs for fp32
 // networks (paper section 3.1: the update differentiates through the policy
 // network; section 3.2: the backward pass is the expensive half): the layers that
-// gemm_split.hip does not take (a 32-wide side), and dW of a maze's first layer.
+// gemm_split.hip does not take (a 32-wide side), and dW of the first layer where a
+// Catch board has more than 256 cells.
 //
 //   gemm_nt_mask_mfma    dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j]
 //   gemm_tn_splitk_mfma  partial[s][i][j] = sum_{m in chunk s} x[m][i] dY[m][j]  (+ column sums of dY)
@@ -130,36 +131,13 @@ __global__ __launch_bounds__(WG) void gemm_nt_mask_mfma(const GemmNtArgs a)
 // tiles are stored [m][i] / [m][j] in LDS and operand reads walk 32 consecutive
 // addresses.  OBS: the first layer's x is rebuilt from the state snapshots.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void obs_row8(const ObsSrc& o, int m, int i, int K, float (&e)[8])
+// eight features of a Catch board beyond first_layer.hip's size
+__device__ __forceinline__ void obs_row8(const ObsSrc& o, int m, int i, float (&e)[8])
 {
+    int bc, pc;
+    catch_obs_cells(o.env, o.s0[m], bc, pc);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = 0.0f;
-    if (o.kind == ENV_CATCH) {
-        int bc, pc;
-        catch_obs_cells(o.env, o.s0[m], bc, pc);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) e[c] = (i + c == bc || i + c == pc) ? 1.0f : 0.0f;
-    } else if (o.kind == ENV_PENDULUM) {
-        if (i == 0) {
-            float sn, cs;
-            det_sincos(o.f0[m], sn, cs);
-            e[0] = cs; e[1] = sn; e[2] = o.f1[m];
-        }
-    } else {
-        const int n = o.env.rows * o.env.cols;
-        const int b = m % o.B, cell = (int)(o.s0[m] & 0xffffu);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int ii = i + c;
-            float v = 0.0f;
-            if (ii < n) v = (float)((o.walls[(size_t)(ii >> 5) * o.B + b] >> (ii & 31)) & 1u);
-            else if (ii < 2 * n) v = (ii - n == cell) ? 1.0f : 0.0f;
-            else if (ii < K) v = (ii == 3 * n - 1) ? 1.0f : 0.0f;
-            e[c] = v;
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) if (i + c >= K) e[c] = 0.0f;
+    for (int c = 0; c < 8; ++c) e[c] = (i + c == bc || i + c == pc) ? 1.0f : 0.0f;
 }
 
 template <bool OBS>
@@ -181,7 +159,7 @@ __global__ __launch_bounds__(WG) void gemm_tn_splitk_mfma(const GemmTnArgs a)
         const int m = mb + lrow;
         if (OBS) {
             float e[8];
-            obs_row8(a.obs, m, i0 + lc, a.K, e);
+            obs_row8(a.obs, m, i0 + lc, e);
             rx0 = make_float4(e[0], e[1], e[2], e[3]); rx1 = make_float4(e[4], e[5], e[6], e[7]);
         } else if (x_ok) {
             const float* p = a.x + (size_t)m * a.K + i0 + lc;

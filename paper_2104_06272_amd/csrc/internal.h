@@ -254,7 +254,8 @@ bool small_fused_ok(const anakin* h);
 size_t small_fused_part_bytes(const EnvDims& ed, const NetShape& ns, int B, int T);
 bool catch_fused_ok(const anakin* h);
 // single hidden layer on a one-hot or 3-feature observation: the update rebuilds the layer from the state
-inline bool one_layer_fused(const anakin* h) { return h->net.L == 1 && h->env.kind != ENV_MAZE && !h->net.bf16 && !(h->mode & ANAKIN_MODE_VALU_GEMM) && h->net.dims[1] <= 128 && (size_t)128 * h->net.dims[0] * 4 + (size_t)h->net.dims[0] * h->net.dims[1] * 4 <= 64 * 1024; }
+inline bool one_layer_shape(const NetShape& n, const EnvDims& ed) { return n.L == 1 && ed.kind != ENV_MAZE && !n.bf16 && n.dims[1] <= 128 && (size_t)128 * n.dims[0] * 4 + (size_t)n.dims[0] * n.dims[1] * 4 <= 64 * 1024; }
+inline bool one_layer_fused(const anakin* h) { return one_layer_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
 hipError_t launch_partial_reduce(const float* src, float* dst, int count, int fan, int splits, hipStream_t s);
 hipError_t launch_rollout_bf16(anakin* h);
 hipError_t launch_rollout_bf16_behaviour(anakin* h);
@@ -268,6 +269,10 @@ bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
 // bf16 network running on the matrix-core path (packed bf16 activations) rather than the fp32 reference path
 // the stored unroll was produced by the bf16 matrix-core kernels and the maze first layer is reduced in pieces
 inline bool first_layer_split(const anakin* h) { return h->splits_w > 0 && h->traj_packed; }
+// boards whose first-layer gradient comes from the one-hot kernel (first_layer.hip), in whichever form dZ_1 has
+inline bool first_onehot_shape(const EnvDims& ed) { return ed.kind != ENV_PENDULUM && ed.rows * ed.cols <= 256; }
+inline bool first_onehot(const anakin* h) { return first_onehot_shape(h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM) && !first_layer_split(h); }
+hipError_t launch_first_layer_onehot(anakin* h, bool packed);
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
 // both sides of layer l + 1 (l >= 1) are whole 64-wide tiles: its two products share a launch (gemm_split.hip)
 inline bool split_gemm_shape(const NetShape& n, int l) { return !n.bf16 && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }

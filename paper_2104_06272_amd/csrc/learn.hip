@@ -6,7 +6,7 @@
 //                         with off-policy targets in place of the returns
 //   vtrace_ratio / _scan  those targets where the unroll does not fit scan_loss
 //   head_backward(_mfma)  gradient of the head matrix, and of the last hidden layer
-//   first_layer_grad*     gradient of the first layer from the compact state (Catch, Pendulum)
+//   first_layer_grad*     gradient of the pendulum's first layer from the compact state (boards: first_layer.hip)
 //   learn_one_layer       the whole backward pass of a one-hidden-layer net
 //   learn_catch_fused     returns, loss and backward pass of a small one-hidden-layer Catch net
 //   adam_reduce(_narrow, _flat)  fixed-order sum of split-K partials fused with Adam
@@ -558,13 +558,9 @@ __global__ __launch_bounds__(WG) void partial_reduce(const float* __restrict__ s
 }
 
 // ---------------------------------------------------------------------------
-// First-layer gradient without a GEMM.  The Catch observation is a 0/1 board
-// with exactly two cells set, so dW1 = X^T dZ1 is a scatter: every sample adds
-// its dZ1 row into the two weight rows its board selects.  Lane j owns column j
-// of an LDS accumulator [cells][columns]; rows of the chunk are visited in
-// order, so the sum is deterministic and needs no atomics.  The pendulum's
-// three-feature observation is handled by the same kernel with three register
-// accumulators per lane.  Column sums (the bias gradient) come for free.
+// First-layer gradient of the pendulum without a GEMM (boards: first_layer.hip): the three observation features are
+// rebuilt from the stored angle and velocity and lane j keeps three register sums of its column, and the column sum
+// (the bias gradient).  Widths under 256: the workgroup's row groups are added in ascending order.
 // ---------------------------------------------------------------------------
 struct FirstGradArgs {
     int M, K, N, rows;
@@ -573,64 +569,45 @@ struct FirstGradArgs {
     ObsLite obs;
 };
 
-template <int ENV>
 __global__ __launch_bounds__(WG) void first_layer_grad(const FirstGradArgs a)
 {
-    extern __shared__ float accs[];                          // [groups][K][cw]
+    __shared__ float sums[4][WG];
     const int N = a.N, K = a.K;
     const int cw = N < WG ? N : WG, groups = WG / cw;
     const int g = threadIdx.x / cw, jl = threadIdx.x % cw;
     const int j = blockIdx.y * WG + jl;
     const int split = blockIdx.x;
     const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
-    float* mine = accs + (size_t)g * K * cw + jl;            // this lane's column, stride cw between cells
-    if (ENV == ENV_CATCH) for (int k = 0; k < K; ++k) mine[k * cw] = 0.0f;
     float bsum = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
     const float* __restrict__ dyin = a.dy;
     constexpr int RB = 16;                                   // rows in flight per lane
     for (int mb = m_begin + g; mb < m_end; mb += RB * groups) {
         float d[RB], f0[RB], f1[RB];
-        uint32_t sw[RB];
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             const int m = mb + u * groups;
             const bool ok = m < m_end;
             d[u] = ok ? dyin[(size_t)m * N + j] : 0.0f;
-            if (ENV == ENV_CATCH) sw[u] = ok ? a.obs.s0[m] : 0u;
-            else { f0[u] = ok ? a.obs.f0[m] : 0.0f; f1[u] = ok ? a.obs.f1[m] : 0.0f; }
+            f0[u] = ok ? a.obs.f0[m] : 0.0f; f1[u] = ok ? a.obs.f1[m] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             if (mb + u * groups >= m_end) break;
             bsum += d[u];
-            if (ENV == ENV_CATCH) {
-                int bc, pc;
-                catch_obs_cells(a.obs.env, sw[u], bc, pc);
-                mine[bc * cw] += d[u];
-                mine[pc * cw] += d[u];
-            } else {
-                float sn, cs;
-                det_sincos(f0[u], sn, cs);
-                r0 = fmaf(cs, d[u], r0); r1 = fmaf(sn, d[u], r1); r2 = fmaf(f1[u], d[u], r2);
-            }
+            float sn, cs;
+            det_sincos(f0[u], sn, cs);
+            r0 = fmaf(cs, d[u], r0); r1 = fmaf(sn, d[u], r1); r2 = fmaf(f1[u], d[u], r2);
         }
     }
     float* out = a.partial + (size_t)split * ((size_t)K * N + N);
-    if (ENV != ENV_CATCH) { mine[0] = r0; mine[cw] = r1; mine[2 * cw] = r2; }
-    __shared__ float bred[WG];
-    bred[threadIdx.x] = bsum;
+    sums[0][threadIdx.x] = r0; sums[1][threadIdx.x] = r1; sums[2][threadIdx.x] = r2; sums[3][threadIdx.x] = bsum;
     __syncthreads();
-    // combine the row groups in ascending order
-    for (int i = threadIdx.x; i < K * cw; i += WG) {
+    // combine the row groups in ascending order; row 3 is the bias, behind the three weight rows
+    for (int i = threadIdx.x; i < 4 * cw; i += WG) {
         const int k = i / cw, c = i % cw;
         float s = 0.0f;
-        for (int gg = 0; gg < groups; ++gg) s += accs[((size_t)gg * K + k) * cw + c];
+        for (int gg = 0; gg < groups; ++gg) s += sums[k][gg * cw + c];
         out[(size_t)k * N + blockIdx.y * WG + c] = s;
-    }
-    if (threadIdx.x < cw) {
-        float s = 0.0f;
-        for (int gg = 0; gg < groups; ++gg) s += bred[gg * cw + threadIdx.x];
-        out[(size_t)K * N + blockIdx.y * WG + threadIdx.x] = s;
     }
 }
 
@@ -672,141 +649,7 @@ __global__ __launch_bounds__(WG) void first_layer_grad_pendulum(const FirstGradA
     out[(size_t)a.K * N + j] = bsum;
 }
 
-// The same scatter on the matrix cores for boards of at most 63 cells: dW1 = X^T dZ1 with the 0/1
-// board rebuilt from the state word, v_mfma_f32_32x32x2_f32 taking two samples per step.  Row K of
-// the padded board is all ones, so the column sums (the bias gradient) fall out of the same product
-// and land in the slot after the K weight rows.  The MFMA adds its products in ascending step order,
-// which makes the sum as deterministic as the scatter.  A workgroup of eight wavefronts walks its
-// samples 64 at a time and reads whole 1 KiB rows of dZ1; wavefront w owns columns 32w..32w+31 and
-// both 32-row tiles of the board.  Of each block of 64 samples lane half kg takes sample 32*kg + s at
-// step s.  The board operand is the same for all eight wavefronts, so each builds one eighth of it
-// (four steps) and shares it through LDS -- vector-ALU work and MFMAs do not overlap well here, and
-// this keeps the ALU share small.
-typedef float f16v_l __attribute__((ext_vector_type(16)));
 typedef float f4v_l __attribute__((ext_vector_type(4)));
-
-typedef __bf16 bf8_l __attribute__((ext_vector_type(8)));
-typedef __bf16 bf2_l __attribute__((ext_vector_type(2)));
-typedef uint32_t u4v_l __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t pk_bf16_l(float lo, float hi)
-{
-    bf2_l v; v[0] = (__bf16)lo; v[1] = (__bf16)hi;               // round to nearest even, one instruction for the pair
-    return __builtin_bit_cast(uint32_t, v);
-}
-// x as three bfloat16 terms whose sum is x (8 + 8 + 8 significand bits; split_terms.h states the range): with the 0/1 board as the other operand
-// every product is exact and the fp32 accumulation is the one an fp32 matrix instruction would do, at a fifth of
-// its matrix-core time (three 8-pass instructions of 16 samples instead of eight 16-pass ones of 2)
-__device__ __forceinline__ void split3(const float (&x)[8], u4v_l& hi, u4v_l& mid, u4v_l& lo)
-{
-    float r[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t p = pk_bf16_l(x[2 * i], x[2 * i + 1]);
-        hi[i] = p;
-        r[2 * i] = x[2 * i] - f_from_bits(p << 16);
-        r[2 * i + 1] = x[2 * i + 1] - f_from_bits(p & 0xffff0000u);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t p = pk_bf16_l(r[2 * i], r[2 * i + 1]);
-        mid[i] = p;
-        lo[i] = pk_bf16_l(r[2 * i] - f_from_bits(p << 16), r[2 * i + 1] - f_from_bits(p & 0xffff0000u));
-    }
-}
-
-__global__ __launch_bounds__(512) void first_layer_grad_mfma(const FirstGradArgs a)
-{
-    __shared__ u4v_l xs[2][2][4][64];                          // [buffer][tile of 32 cells][step of 16 samples][lane]
-    const int N = a.N, K = a.K;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
-    const int j = blockIdx.y * 256 + wave * 32 + l32;
-    const int split = blockIdx.x;
-    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;   // M and a.rows: multiples of 64, N of 256
-    f16v_l acc0, acc1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { acc0[r] = 0.0f; acc1[r] = 0.0f; }
-    const uint32_t lane_off = (uint32_t)(32 * kg) * (uint32_t)N + (uint32_t)j;
-    // loads of one block of 64 samples: this lane's 32 values of dZ1 (samples 32 kg + 0..31 of column j) and the
-    // state word of sample m0 + lane
-    auto load = [&](float (&d)[32], uint32_t& sw, int m0) {
-        sw = a.obs.s0[m0 + lane];
-#pragma unroll
-        for (int s = 0; s < 32; ++s) d[s] = (a.dy + (size_t)(m0 + s) * N)[lane_off];
-    };
-    // The reduction index of step t is k = 8 kg + q for sample 32 kg + 8 t + q of the block: lane (cell l32, half kg)
-    // of the board operand holds the 0/1 entries of its cell for those eight samples as bfloat16.  Wavefront w builds
-    // the operand of (tile w & 1, step w >> 1) for everybody.
-    auto build = [&](uint32_t sw, int buf) {
-        int bc, pc;
-        catch_obs_cells(a.obs.env, sw, bc, pc);
-        const unsigned long long bits = (1ull << bc) | (1ull << pc) | (1ull << K);   // lane l: board of sample l, ones row K
-        const uint32_t mine = (wave & 1) ? (uint32_t)(bits >> 32) : (uint32_t)bits;  // the 32 cells of this wavefront's tile
-        const int t = wave >> 1;
-        u4v_l x;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t w2 = 0;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int q = 2 * i + e;
-                const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)mine, 8 * t + q);
-                const uint32_t b1 = (uint32_t)__builtin_amdgcn_readlane((int)mine, 32 + 8 * t + q);
-                const uint32_t bit = ((kg ? b1 : b0) >> l32) & 1u;
-                w2 |= (bit * 0x3f80u) << (16 * e);                 // bfloat16 1.0
-            }
-            x[i] = w2;
-        }
-        xs[buf][wave & 1][t][lane] = x;
-    };
-    auto compute = [&](const float (&d)[32], int buf) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const u4v_l x0 = xs[buf][0][t][lane], x1 = xs[buf][1][t][lane];
-            float v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = d[8 * t + q];
-            u4v_l hi, mid, lo;
-            split3(v, hi, mid, lo);
-            const bf8_l a0 = __builtin_bit_cast(bf8_l, x0), a1 = __builtin_bit_cast(bf8_l, x1);
-            const bf8_l bh = __builtin_bit_cast(bf8_l, hi), bm = __builtin_bit_cast(bf8_l, mid), bl = __builtin_bit_cast(bf8_l, lo);
-            // smallest terms first
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bl, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bl, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bm, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bm, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bh, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bh, acc1, 0, 0, 0);
-        }
-    };
-    float dA[32], dB[32];
-    uint32_t swA, swB;
-    // every load is unconditional (past the end it re-reads the last block and the result is dropped), so
-    // the wait counters the compiler places before the MFMAs never have to cover the prefetch
-    const int m_last = m_end - 64;
-    load(dA, swA, m_begin);
-    build(swA, 0);
-    __syncthreads();
-    for (int m0 = m_begin; m0 < m_end; m0 += 128) {
-        load(dB, swB, m0 + 64 < m_end ? m0 + 64 : m_last);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(dA, 0);
-        build(swB, 1);
-        __syncthreads();
-        load(dA, swA, m0 + 128 < m_end ? m0 + 128 : m_last);
-        __builtin_amdgcn_sched_barrier(0);
-        if (m0 + 64 < m_end) compute(dB, 1);
-        build(swA, 0);
-        __syncthreads();
-    }
-    // rows 0..K-1 are dW1, row K the column sums: row i of the padded product goes to out[i*N + j]
-    float* out = a.partial + (size_t)split * ((size_t)K * N + N);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r >> 2) + 4 * kg + (r & 3);
-        if (i <= K) out[(size_t)i * N + j] = acc0[r];
-        if (i + 32 <= K) out[(size_t)(i + 32) * N + j] = acc1[r];
-    }
-}
 
 hipError_t launch_first_layer_grad(anakin* h)
 {
@@ -818,21 +661,9 @@ hipError_t launch_first_layer_grad(anakin* h)
     a.dy = at<const float>(h, L.dz[0]); a.partial = at<float>(h, L.part[0]);
     a.obs.env = h->env; a.obs.s0 = at<const uint32_t>(h, L.tr_s0);
     a.obs.f0 = at<const float>(h, L.tr_f0); a.obs.f1 = at<const float>(h, L.tr_f1);
-    const size_t lds = (size_t)WG * a.K * sizeof(float);
-    const dim3 grid(h->splits[0], (a.N + WG - 1) / WG);
     ProfScope prof(h, "first_layer_grad");
-    if (h->env.kind == ENV_CATCH && a.K < 64 && a.M % 64 == 0 && a.rows % 64 == 0 && a.N % 256 == 0 && !(h->mode & ANAKIN_MODE_VALU_GEMM)) {
-        hipLaunchKernelGGL(first_layer_grad_mfma, dim3(h->splits[0], a.N / 256), dim3(512), 0, h->stream, a);
-    } else if (h->env.kind == ENV_CATCH) {
-        auto kern = first_layer_grad<ENV_CATCH>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, grid, dim3(WG), lds, h->stream, a);
-    } else if (a.N % WG == 0 && a.K == 3) {
-        hipLaunchKernelGGL(first_layer_grad_pendulum, dim3(h->splits[0], a.N / WG), dim3(WG), 0, h->stream, a);
-    } else {
-        hipLaunchKernelGGL(first_layer_grad<ENV_PENDULUM>, grid, dim3(WG), lds, h->stream, a);
-    }
+    if (a.N % WG == 0) hipLaunchKernelGGL(first_layer_grad_pendulum, dim3(h->splits[0], a.N / WG), dim3(WG), 0, h->stream, a);
+    else hipLaunchKernelGGL(first_layer_grad, dim3(h->splits[0], (a.N + WG - 1) / WG), dim3(WG), 0, h->stream, a);
     return hipGetLastError();
 }
 
@@ -1593,17 +1424,18 @@ hipError_t launch_adam(anakin* h)
     a.P = n.P;
     int r = 0;
     for (int l = 0; l < n.L; ++l) {
-        if (l == 0 && first_layer_split(h)) {
+        if (l == 0 && h->env.kind == ENV_MAZE && (first_layer_split(h) || first_onehot(h))) {
             // wall rows, agent rows, goal rows (zero but the last, which equals the bias gradient), bias
             const int H1 = n.dims[1], plane = h->env.rows * h->env.cols * H1;
+            const int sw = first_layer_split(h) ? h->splits_w : h->splits[0];
             const float* pw = at<const float>(h, L.part[0]);
-            const float* pa = pw + (size_t)plane * h->splits_w;
+            const float* pa = pw + (size_t)plane * sw;
             const float* pg = pa + (size_t)plane * h->splits[0];
-            a.reg[r++] = Region{n.w_off[0], plane, h->splits_w, pw};
+            a.reg[r++] = Region{n.w_off[0], plane, sw, pw};
             a.reg[r++] = Region{n.w_off[0] + plane, plane, h->splits[0], pa};
             a.reg[r++] = Region{n.w_off[0] + 2 * plane, plane - H1, 0, nullptr};
-            a.reg[r++] = Region{n.w_off[0] + 3 * plane - H1, H1, h->splits_w, pg};
-            a.reg[r++] = Region{n.b_off[0], H1, h->splits_w, pg};
+            a.reg[r++] = Region{n.w_off[0] + 3 * plane - H1, H1, sw, pg};
+            a.reg[r++] = Region{n.b_off[0], H1, sw, pg};
             continue;
         }
         a.reg[r++] = Region{n.w_off[l], n.dims[l] * n.dims[l + 1] + n.dims[l + 1], h->splits[l], at<const float>(h, L.part[l])};

@@ -598,31 +598,12 @@ __device__ __forceinline__ uint4 obs_piece(const ObsSrc& o, int mg, int i, bool 
                 catch_obs_cells(o.env, o.s0[m + q], bc, pc);
                 v[q] = (i == bc || i == pc) ? 0x3f80 : 0;
             }
-        } else if (o.kind == ENV_PENDULUM) {
+        } else {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 float sn, cs;
                 det_sincos(o.f0[m + q], sn, cs);
                 v[q] = bf16_bits(i == 0 ? cs : (i == 1 ? sn : o.f1[m + q]));
-            }
-        } else {
-            const int n = o.env.rows * o.env.cols;
-            if (i < n) {
-                const int b = m % o.B;
-                const uint4 w0 = *reinterpret_cast<const uint4*>(o.walls + (size_t)(i >> 5) * o.B + b);
-                const uint4 w1 = *reinterpret_cast<const uint4*>(o.walls + (size_t)(i >> 5) * o.B + b + 4);
-                const uint32_t ws[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = ((ws[q] >> (i & 31)) & 1u) ? 0x3f80 : 0;
-            } else if (i < 2 * n) {
-                const uint4 s0 = *reinterpret_cast<const uint4*>(o.s0 + m);
-                const uint4 s1 = *reinterpret_cast<const uint4*>(o.s0 + m + 4);
-                const uint32_t ss[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = ((int)(ss[q] & 0xffffu) == i - n) ? 0x3f80 : 0;
-            } else if (i == 3 * n - 1) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = 0x3f80;
             }
         }
     }
@@ -1340,6 +1321,10 @@ hipError_t launch_backward_bf16(anakin* h)
             t.partial = pw; t.bias_out = pg; t.bias_stride = (size_t)H1;
             t.sP = nullptr;
             if ((e = run_tn(t, true, "gemm_tn_walls")) != hipSuccess) return e;
+            continue;
+        }
+        if (l == 0 && first_onehot(h)) {
+            if ((e = launch_first_layer_onehot(h, true)) != hipSuccess) return e;
             continue;
         }
         GemmTnBf16Args t;

@@ -321,3 +321,40 @@ def test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, e
                 np.testing.assert_array_equal(x, y, err_msg=key)
         for x, y in zip(sa, sb):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("name,hidden,B,T,dtype,env", [
+    # boards: edges of the 32-cell tiles and of the pairs of them a kernel is made for, one to 32 column tiles, chunks
+    # that end inside a maze's time steps, one unit of 16 samples in all; a board beyond the kernel's 256 cells
+    ("catch_4096", [64, 64], 16, 1, "fp32", dict(rows=2, cols=1, max_steps=1)),
+    ("catch_4096", [32, 64], 96, 5, "fp32", dict(rows=8, cols=4, max_steps=7)),
+    ("catch_4096", [128, 64], 272, 11, "fp32", dict(rows=13, cols=5, max_steps=12)),
+    ("catch_4096", [1024, 64], 32, 3, "fp32", dict(rows=16, cols=8, max_steps=15)),
+    ("catch_4096", [256, 64], 80, 7, "fp32", dict(rows=43, cols=3, max_steps=42)),
+    ("catch_4096", [64, 32], 160, 9, "fp32", dict(rows=16, cols=12, max_steps=15)),
+    ("catch_4096", [64, 64], 96, 6, "fp32", dict(rows=64, cols=4, max_steps=63)),
+    ("catch_4096", [64, 64], 32, 6, "fp32", dict(rows=64, cols=5, max_steps=63)),
+    ("maze_16384", [32], 32, 1, "fp32", dict(rows=2, cols=2, max_steps=8)),
+    ("maze_16384", [64, 64], 1040, 23, "fp32", dict(rows=8, cols=8, max_steps=16)),
+    ("maze_16384", [128, 32], 96, 7, "fp32", dict(rows=5, cols=13, max_steps=16)),
+    ("maze_16384", [512, 64], 112, 5, "fp32", dict(rows=8, cols=16, max_steps=16)),
+    ("maze_16384", [64, 64], 16, 33, "fp32", dict(rows=16, cols=12, max_steps=16)),
+    ("maze_16384", [256, 64], 400, 12, "fp32", dict(rows=16, cols=16, max_steps=16)),
+    ("catch_4096", [128, 128], 48, 3, "bf16", dict(rows=13, cols=5, max_steps=12)),
+    ("maze_16384", [128, 256], 80, 9, "bf16", dict(rows=9, cols=13, max_steps=16)),
+])
+def test_first_layer_of_boards(gpu, orc, name, hidden, B, T, dtype, env):
+    lockstep(gpu, orc, variant(name, hidden, B, T, dtype, **env), seed=23, tol=TOL_F32 if dtype == "fp32" else TOL_BF16)
+
+
+@pytest.mark.parametrize("name,hidden,B,T,env", [
+    ("catch_4096", [128, 128], 64, 1, {}),
+    ("catch_4096", [256, 128], 192, 5, dict(rows=16, cols=12, max_steps=15)),
+    ("catch_4096", [128, 128], 320, 7, dict(rows=16, cols=8, max_steps=15)),
+    ("maze_16384", [128, 128], 64, 1, dict(rows=8, cols=8, max_steps=16)),
+    ("maze_16384", [512, 128], 192, 9, dict(rows=8, cols=8, max_steps=16)),
+    ("maze_16384", [128, 128], 320, 11, dict(rows=12, cols=12, max_steps=16)),
+    ("maze_16384", [128, 256], 128, 23, dict(rows=16, cols=16, max_steps=16)),
+])
+def test_first_layer_of_boards_bf16(gpu, orc, name, hidden, B, T, env):
+    forced_lockstep(gpu, orc, variant(name, hidden, B, T, "bf16", **env), seed=29)
