@@ -91,6 +91,7 @@ static int build_shapes(const anakin_env_cfg* env, const anakin_net_cfg* net, in
     if (!(net->gamma >= 0.0f && net->gamma <= 1.0f) || !(net->lambda_ >= 0.0f && net->lambda_ <= 1.0f) ||
         !(net->lr > 0.0f) || !(net->beta1 >= 0.0f && net->beta1 < 1.0f) || !(net->beta2 >= 0.0f && net->beta2 < 1.0f) ||
         !(net->eps > 0.0f)) { err = "hyper-parameters out of range"; return ANAKIN_E_BAD_CONFIG; }
+    ns.split = !ns.bf16 || !rollout_bf16_ok(ns, ed, B);
     if (rollout_pick_tile(ns, B) == 0) { err = "no rollout tile fits B and the hidden widths"; return ANAKIN_E_BAD_CONFIG; }
     return ANAKIN_OK;
 }
@@ -189,7 +190,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     const bool bfp = rollout_bf16_ok(ns, ed, B);
     const int q32 = bfp ? 64 : M % 32 == 0 ? 32 : 16;
     for (int l = 0; l < ns.L; ++l) set(l, ((ns.dims[l] + 127) / 128) * ((ns.dims[l + 1] + 127) / 128), 256, q32);
-    if (!ns.bf16)
+    if (ns.split)
         for (int l = 1; l < ns.L; ++l)
             if (split_gemm_shape(ns, l)) {
                 // the dW product shares its launch with the dX product of the layer and the two kinds of workgroup run
@@ -243,7 +244,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     // the head-gradient pass streams the last hidden layer: many small workgroups, summed in two levels
     int fan = 1;
     bool one_stage = false;
-    if (!ns.bf16 && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
+    if (ns.split && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
         // matrix-core head pass: two workgroups per CU stream enough on their own, and their partials go straight to Adam
         set(ns.L, 1, 512, 32);
         one_stage = true;

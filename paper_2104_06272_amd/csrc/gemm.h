@@ -20,7 +20,7 @@ struct HeadFuse {
     const float* hl;      // [M][N] activations of the top hidden layer (null: dY is read from memory)
     const float* dhead;   // [M][NHP]
     const float* wh;      // [N][NH]
-    int NH, NHP;
+    int NH, NHP, bf16;    // bf16: wh is rounded to bfloat16
     float* head_partial;  // dW product only: [splits][N*NH + NH] partial sums of the head matrix and bias gradients
 };
 
@@ -44,7 +44,7 @@ struct GemmNtArgs {
 };
 
 // weights of the layers whose dX product runs on split operands
-struct SplitWeightsArgs { int n; int K[MAX_LAYERS], N[MAX_LAYERS]; const float* w[MAX_LAYERS]; void* out[MAX_LAYERS]; };
+struct SplitWeightsArgs { int n, bf16; int K[MAX_LAYERS], N[MAX_LAYERS]; const float* w[MAX_LAYERS]; void* out[MAX_LAYERS]; };
 
 // partial[s][i][j] = sum over rows of chunk s of x[m][i] dY[m][j]; partial[s][K*N + j] = column sums of dY
 struct GemmTnArgs {
@@ -55,6 +55,13 @@ struct GemmTnArgs {
     float* partial;       // [splits][K*N + N]
     ObsSrc obs;
 };
+
+// the head matrix as the products read it
+__device__ __forceinline__ float head_weight(const HeadFuse& hf, int j, int k)
+{
+    const float x = hf.wh[(size_t)j * hf.NH + k];
+    return hf.bf16 ? bf16_to_f(bf16_bits(x)) : x;
+}
 
 hipError_t launch_gemm_nt_valu(const GemmNtArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn_valu(GemmTnArgs a, hipStream_t s);

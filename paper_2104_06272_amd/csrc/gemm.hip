@@ -167,8 +167,8 @@ SplitWeightsArgs split_weights_args(const anakin* h)
 {
     const NetShape& n = h->net;
     SplitWeightsArgs sw;
-    sw.n = 0;
-    if (n.bf16 || (h->mode & ANAKIN_MODE_VALU_GEMM)) return sw;
+    sw.n = 0; sw.bf16 = n.bf16;
+    if (h->mode & ANAKIN_MODE_VALU_GEMM) return sw;
     for (int l = 1; l < n.L; ++l)
         if (split_gemm_shape(n, l)) {
             sw.K[sw.n] = n.dims[l]; sw.N[sw.n] = n.dims[l + 1];
@@ -184,7 +184,10 @@ hipError_t launch_backward(anakin* h)
     const NetShape& n = h->net;
     const int M = h->B * h->T;
     hipError_t e;
-    const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM) && !n.bf16;
+    // bf16 nets off the bf16 matrix path have binary32 activations and gradients (holding bfloat16 values resp. any) and
+    // weights rounded to bfloat16: the matrix-core products of fp32 nets, with the rounding on the way in (256-256,
+    // 40000 samples, head pass + products: 187 us on the vector ALU, 62 here; 128-512, 640 samples: 55 and 27)
+    const bool mfma = !(h->mode & ANAKIN_MODE_VALU_GEMM);
     // Top hidden layer in whole 64-wide tiles: its dW and dX products form dZ_L on the way in from the layer's forward
     // activations and the head gradient, and the dW product also sums the head matrix's gradient, so dZ_L is neither
     // written nor read and the head pass is no kernel of its own.
@@ -192,7 +195,7 @@ hipError_t launch_backward(anakin* h)
     hf.hl = nullptr;
     if (mfma && heads_fused_shape(n)) {
         hf.hl = at<const float>(h, L.act[n.L - 1]); hf.dhead = at<const float>(h, L.dhead);
-        hf.wh = at<const float>(h, L.w_src) + n.wh_off; hf.NH = n.NH; hf.NHP = n.NHP;
+        hf.wh = at<const float>(h, L.w_src) + n.wh_off; hf.NH = n.NH; hf.NHP = n.NHP; hf.bf16 = n.bf16;
         hf.head_partial = at<float>(h, L.part[n.L]);
     } else {
         e = launch_head_backward(h);

@@ -78,6 +78,7 @@ __global__ __launch_bounds__(WG) void gemm_nt_mask_mfma(const GemmNtArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             *reinterpret_cast<float4*>(&As[lrow * NT_LD + lk + 4 * q]) = ra[q];
+            if (a.bf16) rb[q] = make_float4(bf16_to_f(bf16_bits(rb[q].x)), bf16_to_f(bf16_bits(rb[q].y)), bf16_to_f(bf16_bits(rb[q].z)), bf16_to_f(bf16_bits(rb[q].w)));
             *reinterpret_cast<float4*>(&Bs[lrow * NT_LD + lk + 4 * q]) = rb[q];
         }
         __syncthreads();

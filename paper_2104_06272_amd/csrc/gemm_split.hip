@@ -81,7 +81,7 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
             for (int k = 0; k < 4; ++k) {
                 gwh[HEADS ? q : 0][k] = 0.0f;
                 const int j = j0 + (q * SWG + tid) % TJ;
-                wh[HEADS ? q : 0][k] = (k < a.hf.NH && j < a.N) ? a.hf.wh[(size_t)j * a.hf.NH + k] : 0.0f;
+                wh[HEADS ? q : 0][k] = (k < a.hf.NH && j < a.N) ? head_weight(a.hf, j, k) : 0.0f;
             }
     }
     // loads of stage s, plain: a value past the end of the chunk or of the matrix is some other sample's, and is dropped
@@ -356,7 +356,7 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
         for (int j = tid; j < N; j += SWG) {
             f4v_s v;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = k < a.hf.NH ? a.hf.wh[(size_t)j * a.hf.NH + k] : 0.0f;
+            for (int k = 0; k < 4; ++k) v[k] = k < a.hf.NH ? head_weight(a.hf, j, k) : 0.0f;
             whs[j] = v;
         }
     }

@@ -23,6 +23,7 @@ struct NetShape {
     int w_off[MAX_LAYERS], b_off[MAX_LAYERS], wh_off, bh_off;
     int P;
     int policy, bf16;
+    int split;                                   // fp32, or bf16 off the bf16 matrix path: the dense products of wide layers run on split operands
 };
 
 // trajectory and env-state pointers (device)
@@ -275,7 +276,7 @@ inline bool first_onehot(const anakin* h) { return first_onehot_shape(h->env) &&
 hipError_t launch_first_layer_onehot(anakin* h, bool packed);
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
 // both sides of layer l + 1 (l >= 1) are whole 64-wide tiles: its two products share a launch (gemm_split.hip)
-inline bool split_gemm_shape(const NetShape& n, int l) { return !n.bf16 && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }
+inline bool split_gemm_shape(const NetShape& n, int l) { return n.split && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }
 // tiles of the dW product: 256 x 256 where both sides allow it, else 128 or 64 on a side (128 x 256 as one tile spilled
 // registers: 54 us for both products of a 128-256 net over 28 k samples, 35 as two tiles)
 inline bool split_tile_256(const NetShape& n, int l) { return n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }

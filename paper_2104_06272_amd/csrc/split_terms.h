@@ -59,6 +59,10 @@ __device__ __forceinline__ void split_weights(const SplitWeightsArgs& a, int blo
         const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
         u4v_s t[3];
         split_terms(x, t);
+        if (a.bf16) {                                            // a bf16 net's weights are rounded: the first term alone
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { t[1][i] = 0; t[2][i] = 0; }
+        }
         u4v_s* dst = reinterpret_cast<u4v_s*>(a.out[l]) + ((size_t)((i >> 5) * (a.N[l] >> 4) + (jg >> 1)) * 3) * 64 + 32 * (jg & 1) + (i & 31);
 #pragma unroll
         for (int k = 0; k < 3; ++k) dst[k * 64] = t[k];

@@ -358,3 +358,28 @@ def test_first_layer_of_boards(gpu, orc, name, hidden, B, T, dtype, env):
 ])
 def test_first_layer_of_boards_bf16(gpu, orc, name, hidden, B, T, env):
     forced_lockstep(gpu, orc, variant(name, hidden, B, T, "bf16", **env), seed=29)
+
+
+@pytest.mark.parametrize("name,hidden,B,T,env", [
+    ("catch_4096", [128, 128], 48, 7, {}),                   # heads folded in, 128-wide tiles
+    ("pendulum_8192", [256, 512], 80, 5, {}),                # and the pendulum's first layer
+    ("maze_16384", [256, 64], 112, 5, dict(rows=9, cols=13, max_steps=16)),     # five heads: a head pass of its own
+    ("catch_4096", [32, 128, 32], 96, 4, {}),                # a 32-wide side: the tiled fp32 products with rounded weights
+])
+def test_bf16_products_off_the_bf16_matrix_path(gpu, name, hidden, B, T, env):
+    """Matrix-core products of a bf16 net's fp32 activations and rounded weights against those on the vector ALU.  Both
+    differ from binary64 by at most SPLIT_BOUND per region (test_split_products_keep_binary32), so from each other by twice it."""
+    cfg = variant(name, hidden, B, T, "bf16", **env)
+    regions, _ = PT.param_regions(cfg)
+    grads = []
+    for mode in (0, gpu.MODE_VALU_GEMM):
+        g = gpu.Anakin(cfg, seed=17)
+        assert g.plan()["bf16_matrix_path"] == 0
+        g.set_mode(mode)
+        g.rollout()
+        g.learn()
+        grads.append(g.get_grads())
+        g.close()
+    errors = {rname: PT.rel(grads[0][sl], grads[1][sl]) for rname, sl in regions}
+    print(f"{name} {hidden}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
+    assert max(errors.values()) <= 2 * PT.SPLIT_BOUND, errors
