@@ -215,9 +215,16 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         const int want = M / 64 > 1 ? M / 64 : 1;
         set(0, 1, want < most ? want : most, bfp ? 64 : 16);
     }
+    if (bfp && ed.kind == ENV_PENDULUM) {
+        // at most 512 workgroups and half a block of 256 samples each (kernel + optimiser kernel, 128 columns, 131072
+        // samples: 256 chunks 18.2 us, 512 17.5, 1024 20.1; 512 columns, 414720 samples: 128 chunks 107.7, 250 110.1,
+        // 499 115; 128 columns, 960 samples: 15 or 5 chunks 12.7, 3 13.4, 1 17.5)
+        const int most = 512 / (ns.dims[1] / 128), want = M / 128 > 1 ? M / 128 : 1;
+        set(0, 1, want < most ? want : most, 64);
+    }
     if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
-    if (ns.L == 1 && (ed.kind == ENV_PENDULUM || one_layer_shape(ns, ed))) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
+    if (ns.L == 1 && ((ed.kind == ENV_PENDULUM && !bfp) || one_layer_shape(ns, ed))) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
         // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
         // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the

@@ -6,6 +6,8 @@
 //                        and the plane of walls, which is the same all through an unroll and so needs only
 //                        S[b] = sum_t dZ_1[t][b]; the goal's plane has one cell that is always set: the column sums.
 //
+//   first_layer_pendulum_bf16   the pendulum's three features, bf16 matrix path
+//
 // dZ_1 comes as binary32 rows (taken apart into three bfloat16 terms: every product with a 0/1 operand is exact and the
 // accumulation is binary32, see split_terms.h) or as the sample-packed bfloat16 of the bf16 matrix path (one term).
 #include "split_terms.h"
@@ -270,6 +272,73 @@ hipError_t launch_first_layer_onehot(anakin* h, bool packed)
     const dim3 grid(h->splits[0], tiles / a.tiles_wg), block(a.tiles_wg * 64 * (maze ? 2 : 1));
     ProfScope prof(h, "first_layer_grad");
     launch_tiles<8>((a.cells + 31) / 32, maze, packed, a, grid, block, h->stream);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The pendulum in bf16: dW_1[c][j] = sum_m o_c(m) dZ_1[m][j] for o = (cos th, sin th, thd) rounded to bfloat16, and a
+// fourth feature that is always 1, which gives the bias gradient.  A workgroup takes 128 columns and 256 samples at a
+// time: a thread computes the features of one sample, which reach the matrix operand through LDS, while the block's 16
+// packed pieces of dZ_1 per lane are on their way; wavefront w owns columns 32 w .. 32 w + 31.  Of the operand's 32 rows
+// four mean something; the others repeat them and their sums are dropped.  Bound by reading dZ_1 (512 columns, 414720
+// samples, 425 MB: 84 us, 5.1 TB/s; 675 as a dense product that computed a sample's sine and cosine once per feature and
+// row of tiles.  256 columns, 163840 samples: 127.7 -> 17.0 us; 128 columns, 20480 samples: 18.7 -> 6.3 us).
+// ---------------------------------------------------------------------------
+struct FirstPendulumArgs {
+    int N, M, rows;
+    const uint16_t* dy;       // packed [M/8][N][8]
+    const float* f0; const float* f1;
+    float* out;               // [splits][3*N + N]
+};
+constexpr int FP_BLOCK = 256, FP_UNITS = FP_BLOCK / 16;
+
+__global__ __launch_bounds__(FP_BLOCK) void first_layer_pendulum_bf16(const FirstPendulumArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t feat[2][4][FP_BLOCK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
+    const int N = a.N, j = blockIdx.y * 128 + wave * 32 + l32, split = blockIdx.x;
+    const int m_begin = split * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
+    const uint32_t off = (uint32_t)kg * (uint32_t)N + (uint32_t)j;
+    f16v_s acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    feat[0][3][tid] = 0x3f80; feat[1][3][tid] = 0x3f80;
+    int buf = 0;
+    for (int m0 = m_begin; m0 < m_end; m0 += FP_BLOCK, buf ^= 1) {
+        const int units = m_end - m0 < FP_BLOCK ? (m_end - m0) >> 4 : FP_UNITS;
+        u4v_s p[FP_UNITS];
+#pragma unroll
+        for (int u = 0; u < FP_UNITS; ++u) {
+            const int m = m0 + 16 * (u < units ? u : units - 1);  // past the end: the last piece again
+            p[u] = (reinterpret_cast<const u4v_s*>(a.dy) + (size_t)(m >> 3) * N)[off];
+        }
+        const int ms = m0 + tid < m_end ? m0 + tid : m_end - 1;
+        float sn, cs;
+        det_sincos(a.f0[ms], sn, cs);
+        feat[buf][0][tid] = bf16_bits(cs); feat[buf][1][tid] = bf16_bits(sn); feat[buf][2][tid] = bf16_bits(a.f1[ms]);
+        __syncthreads();                                         // also: everybody is done with the other buffer
+#pragma unroll
+        for (int u = 0; u < FP_UNITS; ++u) {
+            const u4v_s x = *reinterpret_cast<const u4v_s*>(&feat[buf][l32 & 3][16 * u + 8 * kg]);
+            if (u < units) acc = mfma_f(x, p[u], acc);
+        }
+    }
+    if (kg != 0) return;                                         // rows 0..3 of the sums
+    float* out = a.out + (size_t)split * 4 * N + j;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(size_t)r * N] = acc[r];
+}
+
+hipError_t launch_first_layer_pendulum_bf16(anakin* h)
+{
+    const Layout& L = h->lay;
+    FirstPendulumArgs a;
+    a.N = h->net.dims[1]; a.M = h->B * h->T; a.rows = chunk_rows(a.M, h->splits[0], h->quanta[0]);
+    a.dy = at<const uint16_t>(h, L.dz[0]) + (size_t)a.M * a.N;
+    a.f0 = at<const float>(h, L.tr_f0); a.f1 = at<const float>(h, L.tr_f1);
+    a.out = at<float>(h, L.part[0]);
+    ProfScope prof(h, "first_layer_grad");
+    hipLaunchKernelGGL(first_layer_pendulum_bf16, dim3(h->splits[0], a.N / 128), dim3(FP_BLOCK), 0, h->stream, a);
     return hipGetLastError();
 }
 

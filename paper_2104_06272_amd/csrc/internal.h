@@ -274,6 +274,7 @@ inline bool first_layer_split(const anakin* h) { return h->splits_w > 0 && h->tr
 inline bool first_onehot_shape(const EnvDims& ed) { return ed.kind != ENV_PENDULUM && ed.rows * ed.cols <= 256; }
 inline bool first_onehot(const anakin* h) { return first_onehot_shape(h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM) && !first_layer_split(h); }
 hipError_t launch_first_layer_onehot(anakin* h, bool packed);
+hipError_t launch_first_layer_pendulum_bf16(anakin* h);
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
 // both sides of layer l + 1 (l >= 1) are whole 64-wide tiles: its two products share a launch (gemm_split.hip)
 inline bool split_gemm_shape(const NetShape& n, int l) { return n.split && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }

@@ -15,7 +15,8 @@
 //   head_backward_bf16   dZ_L (row-major + packed), partial dWh / dbh
 //   gemm_nt_bf16         dZ_{l-1} = (dZ_l W_l^T) masked by relu'(h_{l-1}), both layouts out
 //   gemm_tn_bf16         partial dW_l = h_{l-1}^T dZ_l (+ column sums), split over samples;
-//                        for the first layer x is rebuilt from the state snapshots
+//                        for the first layer of a Catch board of more than 256 cells x is rebuilt from the states
+//                        (other first layers: first_layer.hip, and mazes in whole 256-wide tiles below)
 #include "gemm.h"
 
 namespace ank {
@@ -585,26 +586,17 @@ constexpr int TB_G = 16;      // sample groups (of 8) per LDS stage: 128 samples
 
 __device__ __forceinline__ uint4 obs_piece(const ObsSrc& o, int mg, int i, bool valid)
 {
-    // eight consecutive samples (same time step, consecutive envs) of observation feature i
+    // eight consecutive samples of cell i of a Catch board beyond first_layer.hip's size
     uint16_t v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) v[q] = 0;
     if (valid) {
         const int m = mg * 8;
-        if (o.kind == ENV_CATCH) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                int bc, pc;
-                catch_obs_cells(o.env, o.s0[m + q], bc, pc);
-                v[q] = (i == bc || i == pc) ? 0x3f80 : 0;
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                float sn, cs;
-                det_sincos(o.f0[m + q], sn, cs);
-                v[q] = bf16_bits(i == 0 ? cs : (i == 1 ? sn : o.f1[m + q]));
-            }
+        for (int q = 0; q < 8; ++q) {
+            int bc, pc;
+            catch_obs_cells(o.env, o.s0[m + q], bc, pc);
+            v[q] = (i == bc || i == pc) ? 0x3f80 : 0;
         }
     }
     return make_uint4((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
@@ -1323,8 +1315,9 @@ hipError_t launch_backward_bf16(anakin* h)
             if ((e = run_tn(t, true, "gemm_tn_walls")) != hipSuccess) return e;
             continue;
         }
-        if (l == 0 && first_onehot(h)) {
-            if ((e = launch_first_layer_onehot(h, true)) != hipSuccess) return e;
+        if (l == 0 && (first_onehot(h) || h->env.kind == ENV_PENDULUM)) {
+            e = h->env.kind == ENV_PENDULUM ? launch_first_layer_pendulum_bf16(h) : launch_first_layer_onehot(h, true);
+            if (e != hipSuccess) return e;
             continue;
         }
         GemmTnBf16Args t;

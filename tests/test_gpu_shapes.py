@@ -383,3 +383,9 @@ def test_bf16_products_off_the_bf16_matrix_path(gpu, name, hidden, B, T, env):
     errors = {rname: PT.rel(grads[0][sl], grads[1][sl]) for rname, sl in regions}
     print(f"{name} {hidden}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
     assert max(errors.values()) <= 2 * PT.SPLIT_BOUND, errors
+
+
+@pytest.mark.parametrize("hidden,B,T", [([128, 128], 64, 1), ([256, 128], 192, 7), ([512, 128], 320, 13), ([128], 1024, 5), ([128, 256], 2112, 9)])
+def test_first_layer_of_the_pendulum_bf16(gpu, orc, hidden, B, T):
+    # blocks of 256 samples: one that is not full, chunks that end in one, one to four blocks of columns
+    forced_lockstep(gpu, orc, variant("pendulum_8192", hidden, B, T, "bf16"), seed=31)
