@@ -91,7 +91,9 @@ static int build_shapes(const anakin_env_cfg* env, const anakin_net_cfg* net, in
     if (!(net->gamma >= 0.0f && net->gamma <= 1.0f) || !(net->lambda_ >= 0.0f && net->lambda_ <= 1.0f) ||
         !(net->lr > 0.0f) || !(net->beta1 >= 0.0f && net->beta1 < 1.0f) || !(net->beta2 >= 0.0f && net->beta2 < 1.0f) ||
         !(net->eps > 0.0f)) { err = "hyper-parameters out of range"; return ANAKIN_E_BAD_CONFIG; }
-    ns.split = !ns.bf16 || !rollout_bf16_ok(ns, ed, B);
+    ns.split = ns.bf16 && rollout_bf16_ok(ns, ed, B) ? 0 : 2;
+    for (int l = 1; l < ns.L; ++l)                               // see split_tile_256
+        if (ns.split && (long long)B * T > (ns.dims[l] >= 256 ? (1 << 21) / ns.dims[l] : ns.dims[l] == 128 && ns.dims[l + 1] <= 128 ? 4096 : 8192)) ns.split = 1;
     if (rollout_pick_tile(ns, B) == 0) { err = "no rollout tile fits B and the hidden widths"; return ANAKIN_E_BAD_CONFIG; }
     return ANAKIN_OK;
 }
@@ -198,7 +200,11 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
                 // each (their costs per sample are alike).  Compared with one chunk per unit followed by one row range
                 // per unit this halves the partial sums (256 KB per chunk, written here, read by Adam) and every unit
                 // pays one prologue instead of two.
-                set(l, 1, split_tn_cap(ns, l), 16);
+                // Chunks of 32 samples at least, 64 where a partial has 256 KB or more (both products and the optimiser
+                // kernel, 256-256: 512 samples in chunks of 16 or 32 24.1 us, of 64 22.0; 256-256-256, 512 samples 50.5
+                // and 45.8; 128-128, 512 samples 17.3 and 19.3).
+                const int least = ns.dims[l] * ns.dims[l + 1] >= 65536 ? 64 : 32, most = split_tn_cap(ns, l), want = M / least > 1 ? M / least : 1;
+                set(l, 1, want < most ? want : most, 16);
             }
     if (ed.kind != ENV_MAZE) set(0, 2 * ((ns.dims[1] + WG - 1) / WG), 512, q32);   // many small chunks
     if (first_onehot_shape(ed)) {

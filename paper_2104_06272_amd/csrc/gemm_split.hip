@@ -339,7 +339,8 @@ template <int WN, int MT, bool HEADS, int FIRST>
 __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const int tile0, const int tile1, const int by, const int part)
 {
     constexpr int WM = 8 / WN, TR = 32 * MT * WM, PITCH = TR + 2, AP = TR * 4 / SWG;
-    static_assert(AP * SWG == TR * 4 && MT % 2 == 0, "whole pieces, pairs of row tiles");
+    constexpr int MP = MT < 2 ? MT : 2;                          // row tiles per turn of the epilogue
+    static_assert(AP * SWG == TR * 4 && MT % MP == 0, "whole pieces, whole turns");
     extern __shared__ float4 smem_s[];
     u4v_s* As = reinterpret_cast<u4v_s*>(smem_s);                 // [2][3 terms][4 groups of 8 j][PITCH]
     constexpr int HALF = 3 * 4 * PITCH;
@@ -429,11 +430,11 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     // 64 of them kept across the loop would not fit the scalar registers
     auto row_off = [&](uint32_t k4, int mt, int r) { return (uint32_t)((wm * MT + mt) * 32 + 8 * (r >> 2) + (r & 3)) * k4; };
     auto opaque = [](uint32_t k4) { asm volatile("" : "+s"(k4)); return k4; };
-    float xm[2][16];
+    float xm[MP][16];
     auto load_mask = [&](rsrc_s rx, int mt0) {
         const uint32_t k4 = opaque(kb);
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < MP; ++u)
 #pragma unroll
             for (int r = 0; r < 16; ++r) xm[u][r] = buf_load1(rx, xoff, row_off(k4, mt0 + u, r));
     };
@@ -508,24 +509,24 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
         step(STrue(), S0, 1, tile, c + 1);
         const rsrc_s rx = rows_rsrc(a.x, tile * TR, TR, a.M, a.K), rd = rows_rsrc(a.dx, tile * TR, TR, a.M, a.K);
 #pragma unroll
-        for (int mp = 0; mp < MT; mp += 2) {
-            float o[2][16];
+        for (int mp = 0; mp < MT; mp += MP) {
+            float o[MP][16];
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int u = 0; u < MP; ++u)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[u][r] = xm[u][r] > 0.0f ? acc[mp + u][r] : 0.0f;   // rows past M read as zero
-            if (mp + 2 < MT) load_mask(rx, mp + 2);
+            if (mp + MP < MT) load_mask(rx, mp + MP);
             if (FIRST == FIRST_NONE) {
                 if (live) {
                     const uint32_t k4 = opaque(kb);
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
+                    for (int u = 0; u < MP; ++u)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) buf_store1(o[u][r], rd, xoff, row_off(k4, mp + u, r));
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+                for (int u = 0; u < MP; ++u)
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const float* f = obsS + (tile - seg) * TR + (wm * MT + mp + u) * 32 + 8 * g + 4 * kg;
@@ -605,6 +606,10 @@ static hipError_t launch_split_tiles(GemmTnArgs t, const GemmNtArgs& n, int nt_b
 hipError_t launch_gemm_tn_nt_split(const NetShape& net, int l, const GemmTnArgs& t, const GemmNtArgs& n, int nt_blocks, hipStream_t s)
 {
     const int ti = split_tile_i(net, l), tj = split_tile_j(net, l);
+    if (net.split == 2) {
+        if (ti == 128) return tj == 128 ? launch_split_tiles<2, 2, 2, 2, 2, 2, 1>(t, n, nt_blocks, s) : launch_split_tiles<2, 1, 2, 2, 4, 2, 1>(t, n, nt_blocks, s);
+        return tj == 128 ? launch_split_tiles<1, 2, 2, 2, 4, 2, 1>(t, n, nt_blocks, s) : launch_split_tiles<1, 2, 2, 1, 4, 2, 1>(t, n, nt_blocks, s);
+    }
     if (ti == 256) return launch_split_tiles<2, 4, 4, 2, 1, 8, 4>(t, n, nt_blocks, s);
     if (ti == 128) {
         if (split_nt_cols(net, l) == 256)

@@ -280,12 +280,18 @@ inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANA
 inline bool split_gemm_shape(const NetShape& n, int l) { return n.split && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }
 // tiles of the dW product: 256 x 256 where both sides allow it, else 128 or 64 on a side (128 x 256 as one tile spilled
 // registers: 54 us for both products of a 128-256 net over 28 k samples, 35 as two tiles)
-inline bool split_tile_256(const NetShape& n, int l) { return n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }
+// n.split == 2 (few samples): tiles of 128 or 64 for dW and of 128 samples x 64 columns for dX, as long as the dX product
+// has at most one of them per compute unit, samples x inputs <= 2^21.  The larger tiles need fewer passes over the operands
+// but leave most units idle there: 256-256, 2048 samples 26.0 us with them, 16.5 with the small ones, 8192 samples 27.7
+// and 25.7, 16384 34.0 and 39.1; 512-512, 512 samples 38.8 and 22.4, 4096 41.8 and 39.5, 8192 53.5 and 68.4; 256-256-256
+// (two launches), 2048 samples 46.0 and 26.0.  Fewer inputs than 256: up to 8192 samples (64-64 12.9 and 11.0, 64-512 32.0
+// and 23.5), 4096 where the larger tiles are no more than 128 x 128 (4096 samples 15.5 and 14.2, 8192 15.5 and 16.3).
+inline bool split_tile_256(const NetShape& n, int l) { return n.split == 1 && n.dims[l] % 256 == 0 && n.dims[l + 1] % 256 == 0; }
 inline int split_tile_i(const NetShape& n, int l) { return split_tile_256(n, l) ? 256 : n.dims[l] % 128 ? 64 : 128; }
 inline int split_tile_j(const NetShape& n, int l) { return split_tile_256(n, l) ? 256 : n.dims[l + 1] % 128 ? 64 : 128; }
 // the dX product: output columns and samples per tile (eight wavefronts, 32 columns each, or shared out over the samples)
-inline int split_nt_cols(const NetShape& n, int l) { return n.dims[l] % 256 == 0 ? 256 : split_tile_i(n, l); }
-inline int split_nt_rows(const NetShape& n, int l) { return split_nt_cols(n, l) == 64 ? 256 : 128; }
+inline int split_nt_cols(const NetShape& n, int l) { return n.split == 2 ? 64 : n.dims[l] % 256 == 0 ? 256 : split_tile_i(n, l); }
+inline int split_nt_rows(const NetShape& n, int l) { return n.split == 1 && split_nt_cols(n, l) == 64 ? 256 : 128; }
 // Compute units the dW and the dX product of such a layer get in their shared launch (their costs per sample are alike):
 // chunks of the dW product per tile, and workgroups of the dX product along the samples per tile of output columns.
 inline int split_tn_cap(const NetShape& n, int l) { const int c = 128 / ((n.dims[l] / split_tile_i(n, l)) * (n.dims[l + 1] / split_tile_j(n, l))); return c > 1 ? c : 1; }

@@ -389,3 +389,18 @@ def test_bf16_products_off_the_bf16_matrix_path(gpu, name, hidden, B, T, env):
 def test_first_layer_of_the_pendulum_bf16(gpu, orc, hidden, B, T):
     # blocks of 256 samples: one that is not full, chunks that end in one, one to four blocks of columns
     forced_lockstep(gpu, orc, variant("pendulum_8192", hidden, B, T, "bf16"), seed=31)
+
+
+@pytest.mark.parametrize("name,hidden,B,T", [
+    # the small tiles of the split-operand products and the last batch that takes them: samples x inputs = 2^21
+    ("catch_4096", [256, 256], 512, 16), ("catch_4096", [256, 256], 528, 16), ("catch_4096", [512, 512], 256, 16), ("catch_4096", [512, 512], 272, 16),
+    ("pendulum_8192", [64, 256], 16, 1), ("catch_4096", [64, 64], 48, 3), ("catch_4096", [128, 64], 112, 5), ("pendulum_8192", [512, 128], 208, 6),
+    ("maze_16384", [256, 64, 128], 80, 7),
+])
+def test_split_products_of_few_samples(gpu, orc, name, hidden, B, T):
+    lockstep(gpu, orc, variant(name, hidden, B, T), seed=37)
+
+
+def test_optimiser_of_few_partials(gpu, orc):
+    # 2^18 parameters and more with at most 16 partials, regions of different counts in a lane's four parameters
+    lockstep(gpu, orc, variant("maze_16384", [256, 256], 16, 24), seed=41)
