@@ -90,6 +90,35 @@ __device__ __forceinline__ float row_lane(float v) { return __builtin_bit_cast(f
 template <int Q>
 __device__ __forceinline__ uint32_t row_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + Q, 0xf, 0xf, true); }
 
+// Sample and step of an environment that a row of 16 lanes owns, lane j holding head j; all lanes of the row do the same.
+// dr: the step's draws, wl: the maze's walls.
+template <int ENV>
+__device__ __forceinline__ void row_step(const EnvDims& env, EnvState& st, float sine, float hv, const uint4 dr, const uint32_t* wl,
+                                         float& eps, float& actf, int& act, float& rew, int& done)
+{
+    constexpr int A = ENV == ENV_CATCH ? 3 : 4;
+    if (ENV == ENV_PENDULUM) {
+        eps = f_from_bits(dr.x);
+        actf = gaussian_action(row_lane<0>(hv), row_lane<1>(hv), eps);
+        pendulum_step_sn(env, st, sine, actf, dr.z, dr.w, rew, done);
+    } else {
+        const float l0 = row_lane<0>(hv), l1 = row_lane<1>(hv), l2 = row_lane<2>(hv), l3 = A > 3 ? row_lane<3>(hv) : 0.0f;
+        float mx = l0;
+        mx = l1 > mx ? l1 : mx;
+        mx = l2 > mx ? l2 : mx;
+        if (A > 3) mx = l3 > mx ? l3 : mx;
+        const float ex = det_exp(hv - mx);                     // lane j: the exponential of logit j
+        const float c0 = row_lane<0>(ex), c1 = c0 + row_lane<1>(ex), c2 = c1 + row_lane<2>(ex), c3 = A > 3 ? c2 + row_lane<3>(ex) : c2;
+        const float thr = u01(dr.x) * c3;
+        act = A - 1;
+        if (A > 3 && c2 > thr) act = 2;
+        if (c1 > thr) act = 1;
+        if (c0 > thr) act = 0;
+        if (ENV == ENV_CATCH) catch_step(env, st, act, dr.z, rew, done);
+        else maze_step(env, st, act, [wl](int c) { return ((wl[c >> 5] >> (c & 31)) & 1u) != 0u; }, rew, done);
+    }
+}
+
 // acc += sum over 16 k of x[row's lane k] * w[k], k ascending, one fused multiply-add each.  (As one block: between single
 // statements the compiler puts a wait state each.  The leading wait is what a DPP operand needs after a vector write.)
 __device__ __forceinline__ void chain16(float x, f4v w0, f4v w1, f4v w2, f4v w3, float& acc)

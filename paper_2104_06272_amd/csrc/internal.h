@@ -177,6 +177,7 @@ struct anakin {
     int TM;                       // envs per workgroup in the vector-ALU rollout kernel
     int TM_mfma;                  // envs per workgroup in the matrix-core rollout kernel (0: not applicable)
     int TM_res;                   // envs per workgroup in the weights-resident rollout kernel (0: not applicable)
+    int wide;                    // groups of four environments per workgroup of the acting kernel of wide nets (0: not applicable)
     ank::PinnedPlan pinned;      // rollout kernel with hidden matrices of any widths in registers
     int splits[ank::MAX_REGIONS]; // split-K factor per parameter region
     int quanta[ank::MAX_REGIONS]; // rows of a region's chunks are multiples of this (chunk_rows)
@@ -314,6 +315,8 @@ bool rollout_one_ok(const anakin* h);
 hipError_t launch_rollout_one(anakin* h, const RolloutArgs& args, bool replay);
 void rollout_pinned_plan(const NetShape& net, const EnvDims& env, int B, PinnedPlan& p);
 hipError_t launch_pinned(anakin* h, const RolloutArgs& args);
+int rollout_wide_groups(const NetShape& net, const EnvDims& env, int B);
+hipError_t launch_wide(anakin* h, const RolloutArgs& args);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);
 size_t rollout_lds_bytes(const NetShape& net, const EnvDims& env, int TM, int* ldx);
 

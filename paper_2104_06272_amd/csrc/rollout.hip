@@ -1813,8 +1813,9 @@ static hipError_t launch_resident_env(anakin* h, const RolloutArgs& a, int width
     return launch_resident64<ENV>(h, a);
 }
 
+// beside: the learner runs at the same time (the actor of a decoupled step)
 template <bool REPLAY>
-static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
+static hipError_t launch_forward(anakin* h, const RolloutArgs& a, bool beside = false)
 {
     const bool bf = h->net.bf16 != 0;
     if (const int lw = rollout_lane_width(h)) {
@@ -1825,6 +1826,10 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a)
     }
     if (rollout_one_ok(h)) return launch_rollout_one(h, a, REPLAY);
     if (!REPLAY && h->pinned.NB > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_pinned(h, a);
+    // Each of its workgroups has a compute unit to itself: beside a learner it takes half of them at most (decoupled steps,
+    // 256-256, T = 16: 256 environments 130 -> 101 us, 512 129.5 -> 119.5, but 1024 130.5 -> 171.6 on all units; 256-512:
+    // 247 -> 144, 246 -> 181, 246 -> 248).
+    if (!REPLAY && h->wide > 0 && (!beside || h->B / (4 * h->wide) <= 128) && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_wide(h, a);
     if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
         switch (h->env.kind) {
@@ -1862,7 +1867,7 @@ hipError_t launch_rollout_behaviour(anakin* h)
     fill_rollout_args(h, a);
     a.theta = at<const float>(h, h->lay.theta_b);
     a.keep_acts = 0;
-    return launch_forward<false>(h, a);
+    return launch_forward<false>(h, a, true);
 }
 
 // the learner's forward pass over the stored unroll with the current parameters: hidden activations

@@ -42,7 +42,7 @@ typedef const __attribute__((address_space(4))) PinnedArgs* kernarg;
 template <int ENV, int NB, bool BF>
 __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArgs q)
 {
-    constexpr int NH = ENV == ENV_CATCH ? 4 : ENV == ENV_PENDULUM ? 3 : 5, NHP = NH <= 4 ? 4 : 8, A = NH - 1;
+    constexpr int NH = ENV == ENV_CATCH ? 4 : ENV == ENV_PENDULUM ? 3 : 5, NHP = NH <= 4 ? 4 : 8;
     constexpr int PF = 8;                                          // LDS reads run this many steps ahead of their MFMAs
     constexpr int HREG = 128;                      // head inputs whose weights fit the owners' registers
     const RolloutArgs& a = q.r;
@@ -394,29 +394,7 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
         }
         if (t == T) break;
         // ---- sample, step; all lanes of a row do the same ----
-        if (ENV == ENV_PENDULUM) {
-            eps = f_from_bits(dr.x);
-            actf = gaussian_action(row_lane<0>(hv), row_lane<1>(hv), eps);
-            pendulum_step_sn(a.env, st, sine, actf, dr.z, dr.w, rew, done);
-        } else {
-            const float l0 = row_lane<0>(hv), l1 = row_lane<1>(hv), l2 = row_lane<2>(hv), l3 = A > 3 ? row_lane<3>(hv) : 0.0f;
-            float mx = l0;
-            mx = l1 > mx ? l1 : mx;
-            mx = l2 > mx ? l2 : mx;
-            if (A > 3) mx = l3 > mx ? l3 : mx;
-            const float ex = det_exp(hv - mx);                     // lane j: the exponential of logit j
-            const float c0 = row_lane<0>(ex), c1 = c0 + row_lane<1>(ex), c2 = c1 + row_lane<2>(ex), c3 = A > 3 ? c2 + row_lane<3>(ex) : c2;
-            const float thr = u01(dr.x) * c3;
-            act = A - 1;
-            if (A > 3 && c2 > thr) act = 2;
-            if (c1 > thr) act = 1;
-            if (c0 > thr) act = 0;
-            if (ENV == ENV_CATCH) catch_step(a.env, st, act, dr.z, rew, done);
-            else {
-                const uint32_t* wl = obs + (row0 + (lane >> 4)) * OBS_WORDS;
-                maze_step(a.env, st, act, [wl](int c) { return ((wl[c >> 5] >> (c & 31)) & 1u) != 0u; }, rew, done);
-            }
-        }
+        row_step<ENV>(a.env, st, sine, hv, dr, obs + (row0 + (lane >> 4)) * OBS_WORDS, eps, actf, act, rew, done);
         asm volatile("" : "+v"(lane));
         first(lane);
     }

@@ -404,3 +404,25 @@ def test_split_products_of_few_samples(gpu, orc, name, hidden, B, T):
 def test_optimiser_of_few_partials(gpu, orc):
     # 2^18 parameters and more with at most 16 partials, regions of different counts in a lane's four parameters
     lockstep(gpu, orc, variant("maze_16384", [256, 256], 16, 24), seed=41)
+
+
+@pytest.mark.parametrize("name,hidden,B,dtype,env", [
+    # groups of four environments, weights in registers, in LDS and streamed: one group or pairs of groups per workgroup (up
+    # to 1024 and above), layers cut along their inputs, one to three layers per wavefront, two passes over a layer
+    ("catch_4096", [256, 256], 16, "fp32", {}),
+    ("catch_4096", [256, 256], 1040, "fp32", {}),
+    ("catch_4096", [64, 512], 1024, "fp32", dict(rows=16, cols=12, max_steps=15)),
+    ("catch_4096", [512, 512], 48, "fp32", dict(rows=16, cols=12, max_steps=15)),  # first-layer rows from memory
+    ("catch_4096", [512, 64, 512], 80, "fp32", {}),
+    ("catch_4096", [64, 1024, 64], 64, "fp32", {}),
+    ("catch_4096", [128, 128, 256, 256], 48, "fp32", {}),
+    ("pendulum_8192", [256, 512], 2032, "fp32", {}),
+    ("pendulum_8192", [512, 128], 16, "fp32", {}),
+    ("maze_16384", [512, 256], 32, "fp32", dict(rows=16, cols=16, max_steps=64)),
+    ("maze_16384", [256, 256], 2048, "fp32", dict(rows=9, cols=13, max_steps=64)),
+    ("catch_4096", [256, 256, 256], 48, "bf16", {}),
+    ("pendulum_8192", [512, 512], 1040, "bf16", {}),
+    ("maze_16384", [128, 512], 80, "bf16", dict(rows=9, cols=13, max_steps=64)),
+])
+def test_acting_in_groups_of_four(gpu, name, hidden, B, dtype, env):
+    test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, env)
