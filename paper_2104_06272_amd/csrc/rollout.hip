@@ -17,10 +17,12 @@
 // Kernels: rollout_kernel (vector ALU), rollout_stream_kernel (matrix cores, weights streamed),
 // rollout_resident_kernel and rollout_resident64_kernel (two equal layers of 128 or 256 resp. 64
 // units, W2 in registers), rollout_pinned_kernel (other nets whose hidden matrices fit the registers, at
-// most 4096 environments; rollout_pinned.hip), rollout_lane_kernel (one narrow hidden layer, very many
+// most 4096 environments; rollout_pinned.hip), rollout_wide_kernel (wider nets and two equal layers of 256 at up to
+// 2048 environments; rollout_wide.hip), rollout_lane_kernel (one narrow hidden layer, very many
 // environments: one lane per env), rollout_one_kernel (other nets of one hidden layer; rollout_one.hip).  All but
-// the resident and pinned ones have a REPLAY form, the learner's forward pass over a stored unroll (decoupled
-// steps, several updates per unroll); nets that act with resident weights replay with streamed ones.
+// the resident, pinned and wide ones have a REPLAY form, the learner's forward pass over a stored unroll (decoupled
+// steps, several updates per unroll); those replay with streamed weights, two equal layers of 128 or 256 units on
+// Catch and the pendulum from 4096 samples on with resident ones (rollout_replay.hip).
 // BF: bf16 nets that the bf16 matrix instructions do not take (batches that are no multiple of 64, mazes of other
 // sizes): the same kernels on weights and activations rounded to bfloat16, products and sums in binary32 -- the
 // vector-ALU kernel's bits at the matrix instruction's rate (256-256, 1040 environments, T = 20: 1197 -> 207 us;
@@ -1879,6 +1881,8 @@ hipError_t launch_replay_forward(anakin* h, bool bootstrap)
     a.bootstrap = bootstrap ? 1 : 0;
     a.tp.tr_head = at<float>(h, h->lay.head_new);
     a.tp.tr_val = at<float>(h, h->lay.val_new);
+    const int samples = (h->T + a.bootstrap) * h->B;
+    if (replay_resident_ok(h, samples)) return launch_replay_resident(h, a, samples);
     return launch_forward<true>(h, a);
 }
 

@@ -426,3 +426,33 @@ def test_optimiser_of_few_partials(gpu, orc):
 ])
 def test_acting_in_groups_of_four(gpu, name, hidden, B, dtype, env):
     test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, env)
+
+
+@pytest.mark.parametrize("name,hidden,B,T,updates,env", [
+    # the learner's replay with the matrix in registers: tiles of 32 to 64 samples, a last one that is not full, more than
+    # one tile per workgroup, first-layer rows beyond LDS; the smallest number of samples that takes it
+    ("catch_4096", [256, 256], 272, 16, 1, {}),
+    ("catch_4096", [256, 256], 1040, 21, 1, dict(rows=16, cols=12, max_steps=15)),
+    ("catch_4096", [256, 256], 2064, 7, 1, {}),
+    ("catch_4096", [128, 128], 4112, 8, 1, {}),
+    ("pendulum_8192", [256, 256], 256, 15, 1, {}),
+    ("pendulum_8192", [128, 128], 2064, 11, 1, {}),
+    ("pendulum_8192", [128, 128], 2048, 8, 4, {}),
+    ("catch_4096", [256, 256], 4160, 4, 2, {}),
+])
+def test_replay_with_the_matrix_in_registers(gpu, name, hidden, B, T, updates, env):
+    """Parameters after decoupled steps or sequential updates, bit for bit as with the streaming replay."""
+    cfg = variant(name, hidden, B, T, **env)
+    runs = []
+    for mode in (0, gpu.MODE_STREAM_WEIGHTS):
+        g = gpu.Anakin(cfg, seed=6)
+        g.set_mode(mode)
+        if updates > 1:
+            g.set_updates_per_unroll(updates, sequential=True)
+            g.step(); g.step()
+        else:
+            g.step_decoupled(); g.step_decoupled(); g.step_decoupled()
+        runs.append([g.get_params(), g.get_grads()] + list(g.get_env_state()))
+        g.close()
+    for x, y in zip(*runs):
+        np.testing.assert_array_equal(x, y)
