@@ -156,10 +156,11 @@ __global__ __launch_bounds__(PTHR, 2) void rollout_pinned_kernel(const PinnedArg
             };
             auto end = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[j][r] = acc[j][r] > 0.0f ? acc[j][r] : 0.0f;
-                round4<BF>(acc[j]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) smem[yi + r * ldy + 16 * j] = acc[j][r];
+                for (int r = 0; r < 4; r += 2) {
+                    float a0 = acc[j][r] > 0.0f ? acc[j][r] : 0.0f, a1 = acc[j][r + 1] > 0.0f ? acc[j][r + 1] : 0.0f;
+                    round2<BF>(a0, a1);
+                    smem[yi + r * ldy + 16 * j] = a0; smem[yi + (r + 1) * ldy + 16 * j] = a1;
+                }
             };
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
