@@ -212,12 +212,15 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // again as partial sums in the optimiser kernel, and at least four units of 16 samples per chunk (kernel +
         // optimiser kernel, most wavefronts / least units: Catch 256-256 B=4096 T=20 1024/8 40.9 us, 2048/8 39.1, 4096/8
         // 45.6; maze 512-128 B=9216 T=30 430, 273, 283; maze of 9 x 13, 128-64, 1495 units, 2048/4 25.9, 2048/16 27.5,
-        // 2048/32 33.7; Catch 128-128, 128 units, 14.2, 19.6, 25.2).  Never more chunks than the dense product has, if
-        // the update's scratch could fit the static array.
+        // 2048/32 33.7; Catch 128-128, 128 units, 14.2, 19.6, 25.2).  Never more chunks than the dense product or the
+        // scatter that this kernel replaces had, if the update's scratch could fit the static array: what fitted still does.
         int most = 2048 / ((ns.dims[1] / 32) * (ed.kind == ENV_MAZE ? 2 : 1));
         size_t widths = 0;
         for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
-        if (widths * 4 * M < (size_t)ANAKIN_STATIC_SCRATCH_BYTES) { if (most > splits[0]) most = splits[0]; if (most > 256) most = 256; }
+        if (widths * 4 * M < (size_t)ANAKIN_STATIC_SCRATCH_BYTES) {
+            const int had = ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0 ? pick_splits(M, 1, 256, 64) : splits[0];
+            if (most > had) most = had;
+        }
         const int want = M / 64 > 1 ? M / 64 : 1;
         set(0, 1, want < most ? want : most, bfp ? 64 : 16);
     }
@@ -259,7 +262,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     bool one_stage = false;
     if (ns.split && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
         // matrix-core head pass: two workgroups per CU stream enough on their own, and their partials go straight to Adam
-        set(ns.L, 1, 512, 32);
+        set(ns.L, 1, ns.bf16 ? 256 : 512, 32);                      // (bf16: no more than the two-level sum below would take)
         one_stage = true;
     }
     if (heads_fused_shape(ns) || (bfp && bf16_top_fused(ns, M))) {
