@@ -131,7 +131,7 @@ def kernel_models(cfg, P, launched=()):
         "scan_loss": ("hbm", (17.0 + NH * 4 + 1 + NH * 4) * M / 1e9, PEAK_HBM_GBS, "GB/s"),
         # read h_L, write dZ_L (bf16: written in two layouts)
         "head_backward": ("hbm", ((6.0 if bf16 else 8.0) * dims[-1] + 4 * NH) * M / 1e9, PEAK_HBM_GBS, "GB/s"),
-        # scatter of dZ1 rows into the selected weight rows: one read of dZ1
+        # first layer's gradient from the states: one read of dZ1
         "first_layer_grad": ("hbm", 4.0 * dims[1] * M / 1e9, PEAK_HBM_GBS, "GB/s"),
     }
     # bf16 top layer with the heads folded in: its dW product is a launch of its own (gemm_tn_top) that reads

@@ -10,8 +10,8 @@
 // state snapshot while the tile is loaded.
 //
 // This file holds the vector-ALU versions (64x64 tiles, 4x4 per lane); the
-// matrix-core versions are in gemm_mfma.hip (a maze's first layer, layers with a
-// 32-wide side) and gemm_split.hip (layers in whole 64-wide tiles: both products
+// matrix-core versions are in gemm_mfma.hip (layers with a 32-wide side, the first
+// layer of Catch boards beyond first_layer.hip's size) and gemm_split.hip (layers in whole 64-wide tiles: both products
 // in one launch, on split operands) and share the argument blocks.
 #include "gemm.h"
 

@@ -268,14 +268,14 @@ int bf16_dx_rows_per_workgroup(int M, int K, int N);
 bool bf16_top_fused(const NetShape& n, int M);
 bool bf16_dx_resident(const NetShape& n, int M, int l);
 bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
-// bf16 network running on the matrix-core path (packed bf16 activations) rather than the fp32 reference path
-// the stored unroll was produced by the bf16 matrix-core kernels and the maze first layer is reduced in pieces
+// the stored unroll was produced by the bf16 matrix-core kernels and the maze's first layer is two dense products, agent and walls
 inline bool first_layer_split(const anakin* h) { return h->splits_w > 0 && h->traj_packed; }
 // boards whose first-layer gradient comes from the one-hot kernel (first_layer.hip), in whichever form dZ_1 has
 inline bool first_onehot_shape(const EnvDims& ed) { return ed.kind != ENV_PENDULUM && ed.rows * ed.cols <= 256; }
 inline bool first_onehot(const anakin* h) { return first_onehot_shape(h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM) && !first_layer_split(h); }
 hipError_t launch_first_layer_onehot(anakin* h, bool packed);
 hipError_t launch_first_layer_pendulum_bf16(anakin* h);
+// bf16 network running on the bf16 matrix path (packed bf16 activations) rather than on the fp32 kernels with rounded operands
 inline bool bf16_mfma(const anakin* h) { return h->bf16_path && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_VALU_GEMM)); }
 // both sides of layer l + 1 (l >= 1) are whole 64-wide tiles: its two products share a launch (gemm_split.hip)
 inline bool split_gemm_shape(const NetShape& n, int l) { return n.split && l >= 1 && l < n.L && n.dims[l] % 64 == 0 && n.dims[l + 1] % 64 == 0; }
