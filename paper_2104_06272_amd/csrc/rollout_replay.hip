@@ -4,8 +4,8 @@
 // cannot overlap the matrix layer (first layer, head chains, barriers: 5 k cycles) are paid once for that many instead of
 // once for 16.  Bound by the fp32 matrix instruction: 8.2 k cycles for each 16 samples of 256-256.
 // Accumulation is in the canonical order; records are what the acting kernels leave.  Beside the actor of a decoupled step,
-// against the streaming kernel: 256-256, 86016 samples 156 -> 129 us (the step 414 -> 401), 270336 samples 433 -> 361;
-// 128-128 (two workgroups per compute unit), 261120 samples 169 -> 114 (421 -> 368), 34816 samples 40 -> 26 (99 -> 83).
+// against the streaming kernel: 256-256, 86016 samples 156 -> 126 us (the step 414 -> 399), 270336 samples 433 -> 364;
+// 128-128 (two workgroups per compute unit), 261120 samples 169 -> 113 (421 -> 366), 34816 samples 40 -> 26 (99 -> 83).
 #include "acting.h"
 
 namespace ank {
@@ -100,28 +100,33 @@ __global__ __launch_bounds__(RPT) void replay_resident_kernel(const RolloutArgs 
 #pragma unroll
                 for (int k = 0; k < 3; ++k) w[k] = *reinterpret_cast<const f4v*>(w1s + k * RW + c);
             }
+            // all loads, then all stores (which might be the same memory, for all the compiler knows)
+            f4v v[IT];
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
-                const int row = r0 + it * STEP;
-                const float* o = seen + 4 * row;
-                f4v v;
+                const float* o = seen + 4 * (r0 + it * STEP);
                 if (ENV == ENV_PENDULUM) {
-                    v = b;
+                    v[it] = b;
 #pragma unroll
                     for (int k = 0; k < 3; ++k)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) v[q] = fmaf(o[k], w[k][q], v[q]);
+                        for (int q = 0; q < 4; ++q) v[it][q] = fmaf(o[k], w[k][q], v[it][q]);
                 } else {
                     const int i0 = (int)reinterpret_cast<const uint32_t*>(o)[0], i1 = (int)reinterpret_cast<const uint32_t*>(o)[1];
                     f4v x0, x1;
                     if (w1_lds) { x0 = *reinterpret_cast<const f4v*>(w1s + i0 * RW + c); x1 = *reinterpret_cast<const f4v*>(w1s + i1 * RW + c); }
                     else { x0 = *reinterpret_cast<const f4v*>(w1g + i0 * RW + c); x1 = *reinterpret_cast<const f4v*>(w1g + i1 * RW + c); }
-                    v = (b + x0) + x1;
+                    v[it] = (b + x0) + x1;
                 }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = v[q] > 0.0f ? v[q] : 0.0f;
-                *reinterpret_cast<f4v*>(X + row * LDX + c) = v;
-                if (m0 + row < kept) *reinterpret_cast<f4v*>(tp.act[0] + (size_t)(m0 + row) * RW + c) = v;
+                for (int q = 0; q < 4; ++q) v[it][q] = v[it][q] > 0.0f ? v[it][q] : 0.0f;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int row = r0 + it * STEP;
+                *reinterpret_cast<f4v*>(X + row * LDX + c) = v[it];
+                if (m0 + row < kept) *reinterpret_cast<f4v*>(tp.act[0] + (size_t)(m0 + row) * RW + c) = v[it];
             }
         }
         __syncthreads();
