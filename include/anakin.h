@@ -224,8 +224,8 @@ int32_t anakin_set_mode(anakin_t* h, int32_t flags);
  * unroll; chunk k's gradient is that of its own mean loss at the parameters the unroll was acted
  * with (the update reuses the acting forward pass), and the N Adam steps are applied in chunk
  * order.  The metrics then average over the chunks; anakin_get_grads returns the last chunk's
- * gradient.  ANAKIN_E_BAD_CONFIG if T is not a multiple of n_updates or a chunk does not fit the
- * kernels' row granularity; the setting is kept until changed.  Default 1. */
+ * gradient.  ANAKIN_E_BAD_CONFIG if T is not a multiple of n_updates; the setting is kept until
+ * changed.  Default 1. */
 int32_t anakin_set_updates_per_unroll(anakin_t* h, int32_t n_updates);
 
 /* At which parameters the gradient of chunk k of several updates per unroll is taken (the paper's remark in

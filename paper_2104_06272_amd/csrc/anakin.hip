@@ -742,7 +742,11 @@ extern "C" int32_t anakin_set_updates_per_unroll(anakin_t* h, int32_t n_updates)
             const int q = (h->B * (h->T / n_updates) + qu[l] - 1) / qu[l], per = (q + h->splits[l] - 1) / h->splits[l];
             sp[l] = (q + per - 1) / per;
         }
-    bool ok = (sw > 0) == (h->splits_w > 0) && lb * n_updates <= h->loss_blocks + h->T && sp[h->net.L] * fan <= h->splits[h->net.L] * h->head_fan;
+    // the head gradient's first stage too: one layer of 256, 102400 samples: 247 chunks of one workgroup, but a quarter of
+    // them 200 chunks of two.  Fewer workgroups per chunk until they fit and none of them starts behind the last sample
+    const int HL = h->net.L, Ms = h->B * (h->T / n_updates), room = h->head_fan > 1 ? h->splits[HL] * h->head_fan : 0;
+    while (fan > 1 && (sp[HL] * fan > room || (long long)(sp[HL] * fan - 1) * chunk_rows(Ms, sp[HL] * fan, qu[HL]) >= Ms)) fan /= 2;
+    bool ok = (sw > 0) == (h->splits_w > 0) && lb * n_updates <= h->loss_blocks + h->T && (fan == 1 || sp[HL] * fan <= room);
     for (int l = 0; l <= h->net.L && ok; ++l) ok = sp[l] > 0 && sp[l] <= h->splits[l];
     if (ok && sw > 0) ok = sw <= h->splits_w;
     if (!ok) { h->err = "updates per unroll: the chunk size does not fit the kernels' row granularity for this B and T"; return ANAKIN_E_BAD_CONFIG; }

@@ -456,3 +456,16 @@ def test_replay_with_the_matrix_in_registers(gpu, name, hidden, B, T, updates, e
         g.close()
     for x, y in zip(*runs):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("hidden,dtype,tol", [([256], "fp32", TOL_F32), ([64], "bf16", TOL_BF16)])
+def test_updates_of_one_layer_in_chunks_of_many_pieces(gpu, orc, hidden, dtype, tol):
+    # half of the unroll would take more first-stage workgroups of the head gradient (193 x 2) than all of it (221 x 1)
+    cfg = variant("catch_4096", hidden, 3088, 16, dtype)
+    g = gpu.Anakin(cfg, seed=43); o = orc.Oracle(cfg, seed=43)
+    g.set_updates_per_unroll(2)
+    PT.sync_oracle_from_gpu(g, o)
+    g.rollout(); o.rollout()
+    g.learn(); o.learn_n(2)
+    PT.assert_learn_close(g, o, tol, n_updates=2)
+    g.close()

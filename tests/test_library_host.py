@@ -4,10 +4,11 @@ before touching the device."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
-from paper_2104_06272_amd import binding, workloads as W
+from paper_2104_06272_amd import binding, build, workloads as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -15,7 +16,6 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 @pytest.fixture(scope="module")
 def lib():
     if not os.path.exists(binding.LIB_PATH):
-        from paper_2104_06272_amd import build
         build.build(verbose=False)
     return binding.load()
 
@@ -92,3 +92,17 @@ def test_no_gpu_means_error_not_fallback():
         pytest.skip("a GPU is present")
     with pytest.raises(RuntimeError):
         binding.Anakin(W.get("catch_small"))
+
+
+def test_every_divisor_of_the_unroll_is_accepted_as_updates(lib, tmp_path):
+    """Chunk plans of several updates per unroll, over shapes of all kinds: a divisor of T is taken, its partial sums fit
+    the full unroll's room and no workgroup is without samples.  The host code runs on handles that have no device."""
+    exe = str(tmp_path / "updates_plan")
+    where = os.path.dirname(binding.LIB_PATH)
+    cmd = [build.HIPCC, *build.FLAGS, "-O1", os.path.join(ROOT, "tests", "host", "updates_plan.hip"), "-o", exe, "-no-hip-rt",
+           "-L" + where, "-Wl,-rpath," + where, "-l:" + os.path.basename(binding.LIB_PATH)]
+    torch_lib = build.torch_lib_dir()
+    cmd += ["-L" + torch_lib, "-Wl,-rpath," + torch_lib] if torch_lib else []
+    subprocess.run(cmd + ["-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True, stderr=subprocess.DEVNULL)
+    out = subprocess.run([exe, "7", "50000"], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout + out.stderr
