@@ -396,17 +396,17 @@ def split_terms_np(x):
 
 # Largest relative error (2-norm of a parameter region) of the products on split operands against binary64 on the same stored
 # forward pass: below half of what the loss of any one of the six products of terms shows (8e-7 at least on the CPU, where it is
-# planted), and 2.8 times the largest seen (1.4e-7, of which most is the head gradient's and the result's rounding to binary32:
-# the vector-ALU kernels show 1.3e-7 there)
+# planted), and 1.5 times the largest seen over the GPU tests' shapes (split operands 2.6e-7, vector ALU 2.0e-7, in the same
+# place: most of it is the head gradient's and the result's rounding to binary32; 35088 samples 1.7e-7 at most)
 SPLIT_BOUND = 4e-7
 SIX_PRODUCTS = ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0))   # terms of the left and of the right operand
 
 
-def np_backward_from_stored(cfg, theta, X, acts, dhead, products=None):
+def np_backward_from_stored(cfg, theta, X, acts, dhead, products=None, first_terms=None):
     """Gradient [P] in binary64 from a STORED forward pass of an fp32 net: first-layer input X [M][D], hidden activations
     acts[l] [M][H_l], gradient of the objective with respect to the head outputs dhead [M][NH].
     products: the hidden layers' products take their operands in three bfloat16 terms and sum these products of terms
-    only (None: the plain product)."""
+    only (None: the plain product).  first_terms: the first layer's product with that many bfloat16 terms of dZ_1."""
     hid = list(cfg["net"]["hidden"])
     L, NH = len(hid), dhead.shape[1]
     dims = [X.shape[1]] + hid
@@ -428,7 +428,8 @@ def np_backward_from_stored(cfg, theta, X, acts, dhead, products=None):
     g[off:off + Wh.size] = (hs[-1].T @ dhead).ravel(); g[off + Wh.size:] = dhead.sum(0)
     dz = (hs[-1] > 0) * (dhead @ Wh.T)
     for l in range(L - 1, -1, -1):
-        gw = product(hs[l - 1].T, dz) if l > 0 else X.T.astype(np.float64) @ dz
+        d1 = dz if l > 0 or first_terms is None else sum(split_terms_np(dz)[:first_terms])
+        gw = product(hs[l - 1].T, dz) if l > 0 else X.T.astype(np.float64) @ d1
         g[w_off[l]:w_off[l] + gw.size] = gw.ravel()
         g[w_off[l] + gw.size:w_off[l] + gw.size + dims[l + 1]] = dz.sum(0)
         if l > 0:

@@ -91,8 +91,8 @@ def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
     forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 6)
 
 
-# backward products on split operands: one row tile or less, ends in the middle of a tile, several tiles side by side, every
-# pairing of tile widths
+# backward products on split operands, few samples (their small tiles): one row tile or less, ends in the middle of a tile,
+# several tiles side by side, every pairing of their widths
 @pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 256], 16, 1), ("pendulum_8192", [256, 256], 48, 3), ("pendulum_8192", [256, 512], 80, 5),
                                              ("catch_4096", [512, 512], 112, 5), ("pendulum_8192", [512, 256, 256], 144, 2),
                                              ("pendulum_8192", [64, 64], 16, 1), ("catch_4096", [64, 256], 80, 5), ("pendulum_8192", [64, 128, 64], 336, 3),
@@ -172,18 +172,16 @@ def test_infinite_wall_weight(gpu, hidden, canonical):
     assert np.isfinite(heads[1]).all() and not np.array_equal(heads[0][:, ~free], heads[1][:, ~free])
 
 
-# The fp32 backward products on split operands (and, as the measure, those on the vector ALU) against binary64 on the stored
-# forward pass: every pairing of tile widths, with the head pass and the pendulum's first layer folded in and without.  The bound
-# notices the loss of any one product of terms, which the CPU suite plants (test_parity_helpers.py).
-@pytest.mark.parametrize("name,hidden", [("catch_4096", [256, 256]), ("pendulum_8192", [256, 256]), ("catch_4096", [512, 256, 256]), ("pendulum_8192", [128, 128]),
-                                         ("catch_4096", [128, 256]), ("catch_4096", [256, 128, 64]), ("pendulum_8192", [64, 64, 128]), ("pendulum_8192", [64, 256, 64])])
-def test_split_products_keep_binary32(gpu, name, hidden):
-    cfg = variant(name, hidden, 416, 5)
-    M = 416 * 5
+def split_products_against_binary64(gpu, name, hidden, B, T, dtype="fp32"):
+    """The backward products on split operands and, as the measure, those on the vector ALU against binary64 on the stored
+    forward pass.  A bf16 net's weights and observations are rounded before they are used; its gradients stay in binary32."""
+    cfg = variant(name, hidden, B, T, dtype)
+    M = B * T
     regions, _ = PT.param_regions(cfg)
     grads = {}
     for mode in ("split", "valu"):
         g = gpu.Anakin(cfg, seed=14)
+        assert g.plan()["bf16_matrix_path"] == 0
         if mode == "valu":
             g.set_mode(gpu.MODE_VALU_GEMM)
         theta = g.get_params() + (0.05 * np.random.default_rng(14).standard_normal(g.P)).astype(np.float32)
@@ -193,12 +191,47 @@ def test_split_products_keep_binary32(gpu, name, hidden):
         tr = g.trajectory()
         grads[mode] = g.get_grads()
         g.close()
-    d = PT.np_head_gradient(cfg, tr["head"][:5].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
-    ref = PT.np_backward_from_stored(cfg, theta, PT.np_observation(cfg, tr), [a.reshape(M, -1) for a in tr["act"]], d)
+    X = PT.np_observation(cfg, tr)
+    if dtype == "bf16":
+        theta, X = PT.bf16_round_np(theta), PT.bf16_round_np(X.astype(np.float32))
+    d = PT.np_head_gradient(cfg, tr["head"][:T].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
+    ref = PT.np_backward_from_stored(cfg, theta, X, [a.reshape(M, -1) for a in tr["act"]], d)
     for mode, got in grads.items():
         errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in regions}
-        print(f"{name} {hidden} {mode}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
+        print(f"{name} {hidden} {dtype} {B} x {T} {mode}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
         assert max(errors.values()) <= PT.SPLIT_BOUND, errors
+
+
+# every pairing of tile widths, with the head pass and the pendulum's first layer folded in and without.  The bound notices the
+# loss of any one product of terms, which the CPU suite plants (test_parity_helpers.py).
+@pytest.mark.parametrize("name,hidden", [("catch_4096", [256, 256]), ("pendulum_8192", [256, 256]), ("catch_4096", [512, 256, 256]), ("pendulum_8192", [128, 128]),
+                                         ("catch_4096", [128, 256]), ("catch_4096", [256, 128, 64]), ("pendulum_8192", [64, 64, 128]), ("pendulum_8192", [64, 256, 64])])
+def test_split_products_keep_binary32(gpu, name, hidden):
+    split_products_against_binary64(gpu, name, hidden, 416, 5)
+
+
+# Every form of the kernel: each pairing of tile widths as a lower layer and as the top one (three heads or four folded in), with
+# the pendulum's first layer and without; (416, 5) takes the small tiles, (2064, 17) the large ones, several of them per
+# workgroup, the last one not full.  That these shapes reach every form is checked on the CPU (test_library_host.py).
+SPLIT_LAYERS = [[256, 256, 128], [256, 128, 128], [256, 64, 64], [128, 128, 64], [128, 64, 128], [64, 256, 256], [64, 64, 256, 64]]
+SPLIT_PAIRS = [[256, 256], [256, 128], [256, 64], [128, 128], [128, 64], [64, 128], [64, 64]]
+SPLIT_FORMS = [(name, h) for h in SPLIT_LAYERS for name in ("catch_4096", "pendulum_8192")] + [("pendulum_8192", h) for h in SPLIT_PAIRS]
+SPLIT_BATCHES = [(416, 5), (2064, 17)]
+
+
+@pytest.mark.parametrize("B,T", SPLIT_BATCHES)
+@pytest.mark.parametrize("name,hidden", SPLIT_FORMS)
+def test_every_form_of_the_split_products(gpu, name, hidden, B, T):
+    split_products_against_binary64(gpu, name, hidden, B, T)
+
+
+# bf16 nets off the bf16 matrix path in the large tiles (few samples: test_bf16_products_off_the_bf16_matrix_path)
+SPLIT_LARGE_BF16 = [("catch_4096", [256, 256]), ("catch_4096", [256, 128]), ("catch_4096", [128, 128]), ("catch_4096", [128, 64, 256])]
+
+
+@pytest.mark.parametrize("name,hidden", SPLIT_LARGE_BF16)
+def test_bf16_products_off_the_bf16_matrix_path_in_large_tiles(gpu, name, hidden):
+    split_products_against_binary64(gpu, name, hidden, 2064, 17, "bf16")
 
 
 @pytest.mark.parametrize("name,hidden,B,T,env", [
@@ -345,6 +378,40 @@ def test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, e
 ])
 def test_first_layer_of_boards(gpu, orc, name, hidden, B, T, dtype, env):
     lockstep(gpu, orc, variant(name, hidden, B, T, dtype, **env), seed=23, tol=TOL_F32 if dtype == "fp32" else TOL_BF16)
+
+
+@pytest.mark.parametrize("name,hidden,B,T,env", [
+    ("catch_4096", [128, 64], 272, 11, dict(rows=13, cols=5, max_steps=12)),
+    ("catch_4096", [512, 64], 400, 15, dict(rows=16, cols=12, max_steps=15)),
+    ("catch_4096", [64, 64], 96, 6, dict(rows=64, cols=4, max_steps=63)),
+    ("maze_16384", [64, 64], 1040, 23, dict(rows=8, cols=8, max_steps=16)),
+    ("maze_16384", [128, 64], 1040, 23, dict(rows=9, cols=13, max_steps=128)),
+    ("maze_16384", [128, 32], 96, 7, dict(rows=5, cols=13, max_steps=16)),
+    ("maze_16384", [256, 64], 400, 12, dict(rows=16, cols=16, max_steps=16)),
+])
+def test_first_layer_of_boards_keeps_binary32(gpu, name, hidden, B, T, env):
+    """The first layer's gradient against binary64 on the stored forward pass; the bound notices the loss of the third term of
+    dZ_1, which the CPU suite plants (test_parity_helpers.py)."""
+    cfg = variant(name, hidden, B, T, **env)
+    M = B * T
+    regions, _ = PT.param_regions(cfg)
+    g = gpu.Anakin(cfg, seed=19)
+    theta = g.get_params() + (0.05 * np.random.default_rng(19).standard_normal(g.P)).astype(np.float32)
+    g.set_params(theta)
+    g.rollout()
+    g.learn()
+    tr, got = g.trajectory(), g.get_grads()
+    if name.startswith("maze"):
+        cells = env["rows"] * env["cols"]
+        walls = np.unpackbits(g.get_walls().view(np.uint8), axis=1, bitorder="little")[:, :cells].astype(bool)
+        _, ref = PT.np_maze_backward_from_stored(cfg, theta, walls, (tr["state_s0"][:T] & 0xffff).astype(np.int64), tr["act"], tr["head"][:-1], tr["action"], tr["adv"], tr["ret"])
+    else:
+        d = PT.np_head_gradient(cfg, tr["head"][:T].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
+        ref = PT.np_backward_from_stored(cfg, theta, PT.np_observation(cfg, tr), [a.reshape(M, -1) for a in tr["act"]], d)
+    g.close()
+    errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in regions}
+    print(f"{name} {hidden}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
+    assert max(errors.values()) <= PT.SPLIT_BOUND, errors
 
 
 @pytest.mark.parametrize("name,hidden,B,T,env", [

@@ -94,15 +94,43 @@ def test_no_gpu_means_error_not_fallback():
         binding.Anakin(W.get("catch_small"))
 
 
-def test_every_divisor_of_the_unroll_is_accepted_as_updates(lib, tmp_path):
-    """Chunk plans of several updates per unroll, over shapes of all kinds: a divisor of T is taken, its partial sums fit
-    the full unroll's room and no workgroup is without samples.  The host code runs on handles that have no device."""
-    exe = str(tmp_path / "updates_plan")
+def build_host_program(name, tmp_path):
+    """tests/host/<name>.hip: the library's host code on configurations without a device"""
+    exe = str(tmp_path / name)
     where = os.path.dirname(binding.LIB_PATH)
-    cmd = [build.HIPCC, *build.FLAGS, "-O1", os.path.join(ROOT, "tests", "host", "updates_plan.hip"), "-o", exe, "-no-hip-rt",
+    cmd = [build.HIPCC, *build.FLAGS, "-O1", os.path.join(ROOT, "tests", "host", name + ".hip"), "-o", exe, "-no-hip-rt",
            "-L" + where, "-Wl,-rpath," + where, "-l:" + os.path.basename(binding.LIB_PATH)]
     torch_lib = build.torch_lib_dir()
     cmd += ["-L" + torch_lib, "-Wl,-rpath," + torch_lib] if torch_lib else []
     subprocess.run(cmd + ["-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True, stderr=subprocess.DEVNULL)
-    out = subprocess.run([exe, "7", "50000"], capture_output=True, text=True)
+    return exe
+
+
+def test_every_divisor_of_the_unroll_is_accepted_as_updates(lib, tmp_path):
+    """Chunk plans of several updates per unroll, over shapes of all kinds: a divisor of T is taken, its partial sums fit
+    the full unroll's room and no workgroup is without samples."""
+    out = subprocess.run([build_host_program("updates_plan", tmp_path), "7", "50000"], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout + out.stderr
+
+
+def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
+    """The shapes of the GPU tests that hold the products on split operands to binary32 run every form of the kernel that any
+    shape runs, so that a threshold that moves does not leave one untested."""
+    import itertools
+    import test_gpu_shapes as G
+    exe = build_host_program("split_tiles", tmp_path)
+    env = {"catch_4096": "0 {} 10 5", "pendulum_8192": "1 {} 0 0"}
+
+    def forms(shapes):
+        lines = [" ".join([env[name].format(bf16), str(B), str(T)] + [str(h) for h in hidden]) for name, hidden, B, T, bf16 in shapes]
+        out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(out) == len(lines)
+        return [set(line.split()) if not line.startswith("refused") else set() for line in out]
+
+    every = set().union(*forms([(name, hidden, B, T, 0) for name in env for B, T in ((16, 3), (64, 63), (2064, 17), (16384, 20)) for n in (2, 3)
+                                for hidden in itertools.product([32, 64, 128, 256, 512, 1024], repeat=n)]))
+    tested = set().union(*forms([(name, hidden, B, T, 0) for name, hidden in G.SPLIT_FORMS for B, T in G.SPLIT_BATCHES]))
+    assert len(every) == 44 and tested == every, every - tested
+    # the bf16 nets: every pairing of large tiles that widths of 128 and more can have
+    large = [f for s in G.SPLIT_LARGE_BF16 for f in forms([s + (2064, 17, 1)])[0]]
+    assert {f.split(":")[1] for f in large} >= {"256x256/256", "128x128/256", "128x128/128"} and all(f.startswith("many:") for f in large)

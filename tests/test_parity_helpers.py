@@ -178,6 +178,12 @@ def test_numpy_backward_equals_the_oracle_and_sees_a_lost_term(orc, name, hidden
             e = PT.rel(five[by_name[r]], exact[by_name[r]])
             print(lost, r, f"{e:.2e}")
             assert e > 1.5 * PT.SPLIT_BOUND, (lost, r, e)
+    if name.startswith("catch"):
+        # the first layer of boards: a 0/1 operand times three exact terms; with two of them the bound is exceeded
+        for terms in (3, 2):
+            e = PT.rel(PT.np_backward_from_stored(cfg, theta, X, acts, d, first_terms=terms)[by_name["W1"]], exact[by_name["W1"]])
+            print("first layer, terms:", terms, f"{e:.2e}")
+            assert e <= 1e-7 if terms == 3 else e > 1.5 * PT.SPLIT_BOUND, (terms, e)
 
 
 def test_three_bfloat16_terms_are_exact_in_their_range():
