@@ -109,7 +109,7 @@ __global__ __launch_bounds__(WG) void gemm_tn_splitk_valu(const GemmTnArgs a)
         if (OBS) {
             float e[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) e[c] = (i0 + lc + c < a.K) ? obs_element(a.obs, m, i0 + lc + c) : 0.0f;
+            for (int c = 0; c < 4; ++c) e[c] = (i0 + lc + c < a.K) ? bfq(obs_element(a.obs, m, i0 + lc + c), a.bf16) : 0.0f;
             vx = make_float4(e[0], e[1], e[2], e[3]);
         } else if (i0 + lc < a.K) {
             vx = *reinterpret_cast<const float4*>(a.x + (size_t)m * a.K + i0 + lc);

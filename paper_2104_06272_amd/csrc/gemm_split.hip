@@ -405,7 +405,8 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
 #pragma unroll
         for (int k = 0; k < 3; ++k) bw[d][k] = wb[(ks * 3 + k) * 64];
     };
-    // pendulum: cos, sin and angular velocity of the samples of a segment of tiles (outside the tile loop: the constants of
+    // pendulum: cos, sin and angular velocity of the samples of a segment of tiles, a bf16 net's rounded as its forward pass
+    // read them (outside the tile loop: the constants of
     // sine and cosine alone would take twenty scalar registers there)
     auto features = [&](int t0, int t1) {
         for (int u = tid; u < (t1 - t0) * TR; u += SWG) {
@@ -413,7 +414,9 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
             m = m < a.M ? m : a.M - 1;
             float sn, cs;
             det_sincos(a.ff.f0[m], sn, cs);
-            obsS[u] = cs; obsS[NTS_SEG + u] = sn; obsS[2 * NTS_SEG + u] = a.ff.f1[m];
+            float td = a.ff.f1[m];
+            if (a.bf16) { cs = bf16_to_f(bf16_bits(cs)); sn = bf16_to_f(bf16_bits(sn)); td = bf16_to_f(bf16_bits(td)); }
+            obsS[u] = cs; obsS[NTS_SEG + u] = sn; obsS[2 * NTS_SEG + u] = td;
         }
     };
     float gw0 = 0.0f, gw1 = 0.0f, gw2 = 0.0f, gb = 0.0f;

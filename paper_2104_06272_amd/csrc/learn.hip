@@ -563,7 +563,7 @@ __global__ __launch_bounds__(WG) void partial_reduce(const float* __restrict__ s
 // (the bias gradient).  Widths under 256: the workgroup's row groups are added in ascending order.
 // ---------------------------------------------------------------------------
 struct FirstGradArgs {
-    int M, K, N, rows;
+    int M, K, N, rows, bf16;  // bf16: the features are rounded, as the forward pass read them
     const float* dy;          // [M][N] gradient w.r.t. the first layer's pre-activations
     float* partial;           // [splits][K*N + N]
     ObsLite obs;
@@ -594,9 +594,10 @@ __global__ __launch_bounds__(WG) void first_layer_grad(const FirstGradArgs a)
         for (int u = 0; u < RB; ++u) {
             if (mb + u * groups >= m_end) break;
             bsum += d[u];
-            float sn, cs;
+            float sn, cs, td = f1[u];
             det_sincos(f0[u], sn, cs);
-            r0 = fmaf(cs, d[u], r0); r1 = fmaf(sn, d[u], r1); r2 = fmaf(f1[u], d[u], r2);
+            if (a.bf16) { cs = bf16_to_f(bf16_bits(cs)); sn = bf16_to_f(bf16_bits(sn)); td = bf16_to_f(bf16_bits(td)); }
+            r0 = fmaf(cs, d[u], r0); r1 = fmaf(sn, d[u], r1); r2 = fmaf(td, d[u], r2);
         }
     }
     float* out = a.partial + (size_t)split * ((size_t)K * N + N);
@@ -627,6 +628,7 @@ __global__ __launch_bounds__(WG) void first_layer_grad_pendulum(const FirstGradA
         const int m = mb + threadIdx.x;
         float sn = 0.0f, cs = 0.0f, td = 0.0f;
         if (m < m_end) { det_sincos(a.obs.f0[m], sn, cs); td = a.obs.f1[m]; }
+        if (a.bf16) { cs = bf16_to_f(bf16_bits(cs)); sn = bf16_to_f(bf16_bits(sn)); td = bf16_to_f(bf16_bits(td)); }
         __syncthreads();                                     // the previous batch has been consumed
         feat[0][threadIdx.x] = cs; feat[1][threadIdx.x] = sn; feat[2][threadIdx.x] = td;
         __syncthreads();
@@ -656,7 +658,7 @@ hipError_t launch_first_layer_grad(anakin* h)
     const Layout& L = h->lay;
     const NetShape& n = h->net;
     FirstGradArgs a;
-    a.M = h->B * h->T; a.K = n.dims[0]; a.N = n.dims[1];
+    a.M = h->B * h->T; a.K = n.dims[0]; a.N = n.dims[1]; a.bf16 = n.bf16;
     a.rows = chunk_rows(a.M, h->splits[0], h->quanta[0]);
     a.dy = at<const float>(h, L.dz[0]); a.partial = at<float>(h, L.part[0]);
     a.obs.env = h->env; a.obs.s0 = at<const uint32_t>(h, L.tr_s0);
