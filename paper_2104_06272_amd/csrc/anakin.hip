@@ -212,17 +212,26 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // again as partial sums in the optimiser kernel, and at least four units of 16 samples per chunk (kernel +
         // optimiser kernel, most wavefronts / least units: Catch 256-256 B=4096 T=20 1024/8 40.9 us, 2048/8 39.1, 4096/8
         // 45.6; maze 512-128 B=9216 T=30 430, 273, 283; maze of 9 x 13, 128-64, 1495 units, 2048/4 25.9, 2048/16 27.5,
-        // 2048/32 33.7; Catch 128-128, 128 units, 14.2, 19.6, 25.2).  Never more chunks than the dense product or the
-        // scatter that this kernel replaces had, if the update's scratch could fit the static array: what fitted still does.
-        int most = 2048 / ((ns.dims[1] / 32) * (ed.kind == ENV_MAZE ? 2 : 1));
+        // 2048/32 33.7; Catch 128-128, 128 units, 14.2, 19.6, 25.2; Catch 16 x 12, 64-64, B=65536 T=16 1024/4 152, 2048/4 98;
+        // maze of 16 x 16, 32-64, B=32768 T=32 1024/4 113, 2048/4 97).  Mazes of 32 or 64 columns: 1024 wavefronts where the
+        // partials of 2048 had more than 1.5 times the bytes of dZ_1, as each is written here and read again (2048 and 1024
+        // wavefronts, without the bound on the scratch that follows: 14 x 16, 32-64, B=1952 T=72, 3.1 times 34.1 and 32.4 us;
+        // 9 x 13, 64-64, B=1040 T=32, 2.9 times 21.9 and 20.4; 16 x 16, 64-64, B=2048 T=32, 4 times 39.0 and 35.0, B=4096 T=32,
+        // 2 times 47.2 and 45.0, B=8192 T=21, 1.5 times 52.3 and 51.9, B=16384 T=32, half the bytes 103.6 and 113.8).  Wider
+        // ones would leave half of the units without a workgroup (16 x 16, 256-64, B=2400 T=7, 3.6 times: the step 110.8 and 114.2).  Never more chunks than the
+        // dense product or the scatter that this kernel replaces had, if the update's scratch could fit the static array:
+        // what fitted still does.
+        const bool maze = ed.kind == ENV_MAZE;
+        const int tiles = (ns.dims[1] / 32) * (maze ? 2 : 1), want = M / 64 > 1 ? M / 64 : 1;
+        int most = 2048 / tiles < want ? 2048 / tiles : want;
+        if (maze && ns.dims[1] <= 64 && 2ll * most * ed.rows * ed.cols > 3ll * M / 2 && most > 1024 / tiles) most = 1024 / tiles;
         size_t widths = 0;
         for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
         if (widths * 4 * M < (size_t)ANAKIN_STATIC_SCRATCH_BYTES) {
             const int had = ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0 ? pick_splits(M, 1, 256, 64) : splits[0];
             if (most > had) most = had;
         }
-        const int want = M / 64 > 1 ? M / 64 : 1;
-        set(0, 1, want < most ? want : most, bfp ? 64 : 16);
+        set(0, 1, most, bfp ? 64 : 16);
     }
     if (bfp && ed.kind == ENV_PENDULUM) {
         // at most 512 workgroups and half a block of 256 samples each (kernel + optimiser kernel, 128 columns, 131072
