@@ -218,9 +218,9 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // wavefronts, without the bound on the scratch that follows: 14 x 16, 32-64, B=1952 T=72, 3.1 times 34.1 and 32.4 us;
         // 9 x 13, 64-64, B=1040 T=32, 2.9 times 21.9 and 20.4; 16 x 16, 64-64, B=2048 T=32, 4 times 39.0 and 35.0, B=4096 T=32,
         // 2 times 47.2 and 45.0, B=8192 T=21, 1.5 times 52.3 and 51.9, B=16384 T=32, half the bytes 103.6 and 113.8).  Wider
-        // ones would leave half of the units without a workgroup (16 x 16, 256-64, B=2400 T=7, 3.6 times: the step 110.8 and 114.2).  Never more chunks than the
-        // dense product or the scatter that this kernel replaces had, if the update's scratch could fit the static array:
-        // what fitted still does.
+        // ones would leave half of the units without a workgroup (16 x 16, 256-64, B=2400 T=7, 3.6 times: the step 110.8 and
+        // 114.2).  Never more chunks than the dense product or the scatter that this kernel replaces had, if the update's
+        // scratch could fit the static array: what fitted still does.
         const bool maze = ed.kind == ENV_MAZE;
         const int tiles = (ns.dims[1] / 32) * (maze ? 2 : 1), want = M / 64 > 1 ? M / 64 : 1;
         int most = 2048 / tiles < want ? 2048 / tiles : want;
