@@ -248,12 +248,18 @@ bool replay_resident_ok(const anakin* h, int samples)
 
 hipError_t launch_replay_resident(anakin* h, const RolloutArgs& a, int samples)
 {
-    // groups of 16 per tile: the number with the shortest last workgroup, a group's matrix time against what a tile costs besides
+    // Groups of 16 per tile: the number with the smallest cost for a compute unit.  A tile of G groups has G times a group's
+    // matrix time (in 100 cycles: 82 for 256-256, 41 for 128-128), which the workgroups of a unit (one; two of 128-128) share,
+    // and 50 or 40 that they do not wait for one another in: first layer, head chains, barriers.  Within 2 % of the best G for
+    // 23 sample counts of 4608 to 524288, Catch and pendulum, both widths; counted as if two workgroups did not share the
+    // matrix unit, 128-128 took G = 2 with 9216 samples (16.3 us; 3 now, 14.6), 2 with 12288 (17.3; 15.6) and 4 with 86016
+    // (47.5; 3 now, 42.1).  256-256, G = 2, 3, 4: 12288 samples 31.9, 26.5, 30.5 us; 32768 53.4, 56.7, 51.4; 86016 128, 121, 132.
     const int w = rollout_resident_width(h->net);
     int best = 2;
     long cost = 0;
     for (int G = 2; G <= 4; ++G) {
-        const long tiles = (samples + 16 * G - 1) / (16 * G), wgs = 65536 / w, c = (tiles + wgs - 1) / wgs * (w == 256 ? 82 * G + 50 : 41 * G + 40);
+        const long tiles = (samples + 16 * G - 1) / (16 * G), wgs = 65536 / w, per_unit = (tiles + 255) / 256, per_wg = (tiles + wgs - 1) / wgs;
+        const long c = w == 256 ? per_unit * 82 * G + per_wg * 50 : per_unit * 41 * G + per_wg * 40;
         if (!cost || c <= cost) { best = G; cost = c; }
     }
     if (h->env.kind == ENV_CATCH) {
