@@ -1617,8 +1617,10 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
 
 // One-hidden-layer nets the lane kernel takes: width 32 or 64 on Catch or the pendulum, fp32, no kept activations -- and
 // enough environments that a lane each fills the chip; with fewer a row of 16 lanes per environment (rollout_one.hip) is
-// done sooner.  Catch, T = 16, a lane against 16 lanes: width 32, 8192 environments 30 us against 16, 32768 32.5 against
-// 35, 262144 75 against 231; width 64, 32768 61 against 46, 65536 64 against 85.
+// done sooner.  T = 16, a lane against 16 lanes, Catch 10 x 5 (5 x 4 differs by less than 2 us) and the pendulum: width 32,
+// 8192 environments 30 us against 18, 42 against 22; 24576 32 against 30, 43 against 43; 32768 32 against 36, 44 against 51;
+// 262144 65 against 214, 90 against 305.  Width 64: 32768 59 against 47, 73 against 62; 49152 59 against 66, 73 against 85;
+// 262144 216 against 286, 272 against 377.
 static int rollout_lane_width(const anakin* h)
 {
     const NetShape& n = h->net;

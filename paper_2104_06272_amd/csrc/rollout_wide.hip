@@ -549,16 +549,20 @@ static bool wide_plan(const NetShape& net, const EnvDims& env, int R, WideArgs& 
 }
 
 // Which nets: two or more layers that rollout_pinned.hip does not take, in whole blocks of 64, not two equal ones of 64 or 128
-// (128-128, 1024 environments: 47.5 us resident, 64.3 here).  Up to 1024 environments in groups of four, up to 2048 in pairs
-// of groups; the pairs not where a layer's outputs leave most SIMDs idle (2048 environments: 512-128 134 us streamed, 135
-// here; 64-512-64 157 and 166; 512-64-512 190 and 193; but 256-128-256 143 and 132).
+// (1024 environments, resident and here: 128-128 Catch 49 and 66 us, pendulum 51 and 68, maze of 12 x 14 65 and 73; 64-64 29 and
+// 45, 36 and 49, 38 and 51).  Up to 1024 environments in groups of four, up to 2048 in pairs of groups; the pairs not where a
+// layer's outputs leave most SIMDs idle (2032 environments on Catch, the pendulum and the maze, streamed and here: 512-128
+// 134 and 135 us, 139 and 140, 152 and 150; 64-512-64 158 and 167, 164 and 193, 169 and 175; 512-64-512 190 and 194, 197 and
+// 199, 212 and 213; but 256-128-256 140 and 131, 147 and 141, 157 and 146, 512-256 207 and 172, 211 and 168, 226 and 185) --
+// unless the streaming kernel's buffers do not fit LDS and the vector-ALU kernel would run (maze of 12 x 14, 1024-128: 3190
+// and 298).
 int rollout_wide_groups(const NetShape& net, const EnvDims& env, int B)
 {
     if (net.L < 2 || B > 2048) return 0;
     const int R = B <= 1024 ? 1 : 2, res = rollout_resident_tile(net, env.kind, B);
     if (res && net.dims[1] != 256) return 0;
     for (int l = 1; l <= net.L; ++l) if (net.dims[l] % 64) return 0;
-    if (R == 2)
+    if (R == 2 && rollout_pick_tile_mfma(net, env, B) > 0)
         for (int l = 1; l < net.L; ++l) if (net.dims[l + 1] == 64 || (net.dims[l + 1] == 128 && net.dims[l] > 256)) return 0;
     WideArgs q;
     return wide_plan(net, env, R, q) ? R : 0;

@@ -499,6 +499,7 @@ def test_optimiser_of_few_partials(gpu, orc):
     ("pendulum_8192", [512, 128], 16, "fp32", {}),
     ("maze_16384", [512, 256], 32, "fp32", dict(rows=16, cols=16, max_steps=64)),
     ("maze_16384", [256, 256], 2048, "fp32", dict(rows=9, cols=13, max_steps=64)),
+    ("maze_16384", [1024, 128], 1040, "fp32", dict(rows=12, cols=14, max_steps=64)),   # pairs: the streaming kernel does not fit LDS
     ("catch_4096", [256, 256, 256], 48, "bf16", {}),
     ("pendulum_8192", [512, 512], 1040, "bf16", {}),
     ("maze_16384", [128, 512], 80, "bf16", dict(rows=9, cols=13, max_steps=64)),
