@@ -151,7 +151,7 @@ __global__ __launch_bounds__(BWG, 2) void rollout_bf16_pinned_kernel(const Pinne
     if (owner) observe(lane0);
     if (wave == 6) draw(0, lane0);
     __syncthreads();
-    // ---- first-layer constants of this thread (columns c, c + 1 of environments e0 ..), as in the kernel above ----
+    // ---- first-layer constants of this thread (columns c, c + 1 of environments e0 ..), as in rollout_bf16_kernel ----
     const int c0 = 2 * (tid0 % (H1 / 2)), e00 = tid0 / (H1 / 2) * EPT;
     const bool first_thread = FTHR == BWG || tid0 < FTHR;
     float pre[ENV == ENV_MAZE ? EPT : 1][2];

@@ -210,7 +210,8 @@ __global__ __launch_bounds__(WG, H >= 128 ? 2 : ENV == ENV_MAZE && H == 64 ? 3 :
         __builtin_amdgcn_raw_buffer_store_b32(bits_from_f(i16 < NH ? hv : 0.0f), rsrc(k->r.tp.tr_head + te * NHP), i16 < NHP ? 4 * (r16 * NHP + i16) : -1, 0, 0);
         __builtin_amdgcn_raw_buffer_store_b32(bits_from_f(hv), rsrc(k->r.tp.tr_val + te), i16 == NH - 1 ? 4 * r16 : -1, 0, 0);
         if (REPLAY || t == T) continue;
-        // ---- sample, step; all lanes of a row do the same ----
+        // ---- sample, step; all lanes of a row do the same (row_step of acting.h in place: called, Catch with 256 units and
+        // 8192 environments took 56.9 us instead of 55.9) ----
         const int src = 4 * ((lane & 48) + (t & 7));
         const uint32_t d0 = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)dr0);
         const uint32_t e0 = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 32, (int)dr0), e1 = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 32, (int)dr1);

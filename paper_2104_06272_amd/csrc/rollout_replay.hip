@@ -4,8 +4,9 @@
 // cannot overlap the matrix layer (first layer, head chains, barriers: 5 k cycles) are paid once for that many instead of
 // once for 16.  Bound by the fp32 matrix instruction: 8.2 k cycles for each 16 samples of 256-256.
 // Accumulation is in the canonical order; records are what the acting kernels leave.  Beside the actor of a decoupled step,
-// against the streaming kernel: 256-256, 86016 samples 156 -> 126 us (the step 414 -> 399), 270336 samples 433 -> 364;
-// 128-128 (two workgroups per compute unit), 261120 samples 169 -> 113 (421 -> 366), 34816 samples 40 -> 26 (99 -> 83).
+// against the streaming kernel: 256-256, 270336 samples 408 -> 338 us (the step 1045 -> 978), 86016 samples 149 -> 121 (but the
+// step 412 -> 403 at most: the loss launch behind the replay then waits for the actor's workgroups, 60 -> 121); 128-128 (two
+// workgroups per compute unit), 253952 samples 152 -> 109 (418 -> 372), 34816 samples 36 -> 23 (106 -> 95).
 #include "acting.h"
 
 namespace ank {
