@@ -549,3 +549,17 @@ def test_updates_of_one_layer_in_chunks_of_many_pieces(gpu, orc, hidden, dtype, 
     g.learn(); o.learn_n(2)
     PT.assert_learn_close(g, o, tol, n_updates=2)
     g.close()
+
+
+def test_updates_of_one_layer_in_chunks_of_many_pieces_bf16(gpu, orc):
+    # the same on the bf16 matrix path: 195 x 2 against 223 x 1
+    cfg = variant("pendulum_8192", [128], 3328, 30, "bf16")
+    g = gpu.Anakin(cfg, seed=47); o = orc.Oracle(cfg, seed=47)
+    assert g.plan()["bf16_matrix_path"] == 1
+    g.set_updates_per_unroll(2)
+    PT.sync_oracle_from_gpu(g, o)
+    g.rollout()
+    o.rollout(forced_head=g.trajectory()["head"])
+    g.learn(); o.learn_n(2)
+    PT.assert_learn_close(g, o, TOL_BF16, n_updates=2)
+    g.close()
