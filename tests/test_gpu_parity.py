@@ -956,7 +956,6 @@ PATHWISE_CASES = {
     "pendulum_256_B128": (variant("pendulum_8192", B=128), 0, 2),
     "pendulum_64_short_episodes": (variant("pendulum_8192", hidden=[64, 64], B=64, T=32, max_steps=25), 2, 3),
     "pendulum_128_B48": (variant("pendulum_8192", hidden=[128, 128], B=48, T=12, max_steps=7), 4, 2),
-    # enough envs for the 32-env form of the sweep (32x32x2 matrix instruction)
     "pendulum_128_B8192": (_path_only(variant("pendulum_8192", hidden=[128, 128], B=8192, T=6, max_steps=4)), 5, 1),
 }
 
@@ -988,6 +987,29 @@ def test_pathwise_lockstep(gpu, orc, case):
     PT.sync_oracle_from_gpu(g, o)
     g.step(); o.step()
     PT.assert_learn_close(g, o, TOL_F32)
+    g.close()
+
+
+# the sweep's two tile heights on either side of the line between them, batches off the taller tile, unrolls that end
+# inside, on and behind a block of steps whose factors are worked out together (8 or 16)
+@pytest.mark.parametrize("width,B,T", [(256, 4128, 9), (256, 4112, 2), (256, 4096, 3), (256, 48, 33), (128, 8224, 3), (128, 16, 16),
+                                       (64, 16, 1), (64, 80, 17)])
+def test_pathwise_sweep_shapes(gpu, orc, width, B, T):
+    """The path term's gradient against binary64 reverse accumulation on the same unroll.  Products of split operands, sums
+    and the head pass are binary32: measured 0.7 to 4.4e-7 over unrolls of up to 64 steps; a lost product of terms is 2e-6
+    and more."""
+    cfg = _path_only(variant("pendulum_8192", hidden=[width, width], B=B, T=T, max_steps=11))
+    say(f"[pathwise sweep] width={width} B={B} T={T}")
+    g = gpu.Anakin(cfg, seed=3)
+    o = orc.Oracle(cfg, seed=3)
+    g.set_policy_gradient(gpu.PG_PATHWISE)
+    PT.sync_oracle_from_gpu(g, o)
+    g.rollout(); o.rollout()
+    PT.assert_rollout_equal(g, o, "pendulum")
+    ref, _ = o.pathwise_grad()
+    g.learn()
+    err = np.linalg.norm(g.get_grads().astype(np.float64) - ref) / np.linalg.norm(ref)
+    assert err <= 1e-6, err
     g.close()
 
 
