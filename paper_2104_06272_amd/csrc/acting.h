@@ -144,4 +144,25 @@ __device__ __forceinline__ void chain16(float x, f4v w0, f4v w1, f4v w2, f4v w3,
         : "v"(x), "v"(w0[0]), "v"(w0[1]), "v"(w0[2]), "v"(w0[3]), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]), "v"(w2[0]), "v"(w2[1]), "v"(w2[2]), "v"(w2[3]), "v"(w3[0]), "v"(w3[1]), "v"(w3[2]), "v"(w3[3]));
 }
 
+// the same over eight of the row's lanes, LO .. LO + 7
+template <int LO>
+__device__ __forceinline__ void chain8(float x, f4v w0, f4v w1, float& acc)
+{
+    static_assert(LO == 0 || LO == 8, "half a row");
+#define ANK_CHAIN8(a, b, c, d, e, f, g, h) \
+    asm("s_nop 1\n\t" \
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:" #a " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:" #b " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:" #c " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:" #d " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:" #e " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:" #f " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:" #g " row_mask:0xf bank_mask:0xf\n\t" \
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:" #h " row_mask:0xf bank_mask:0xf" \
+        : "+v"(acc) : "v"(x), "v"(w0[0]), "v"(w0[1]), "v"(w0[2]), "v"(w0[3]), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]))
+    if (LO == 0) ANK_CHAIN8(0, 1, 2, 3, 4, 5, 6, 7);
+    else ANK_CHAIN8(8, 9, 10, 11, 12, 13, 14, 15);
+#undef ANK_CHAIN8
+}
+
 }  // namespace ank

@@ -870,7 +870,7 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
 // reads no hidden-layer weight from memory at all.  The first layer's matrix (gathered by row) sits in LDS where it fits,
 // the head matrix always.  The accumulation order is the canonical one.
 //
-// A step is a chain: the 256-wide layer on the matrix cores (8.2 k cycles for each 16 environments), then heads (2.5 k: 256
+// A step is a chain: the 256-wide layer on the matrix cores (8.2 k cycles for each 16 environments), then heads (2.1 k: 256
 // dependent multiply-adds), sample, step, observe (1 k) and the next first layer.  The two kinds cannot overlap: a binary32
 // MFMA and binary32 vector operations use the same units, and a wavefront that streams such MFMAs starves the vector work of
 // the others on its SIMD (measured: 256 dependent operations beside such a stream end with it, whatever the priorities).
@@ -880,7 +880,10 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
 // go out beside the other wavefronts' MFMAs.  (Every wavefront taking two or four environments through the whole chain was
 // slower: eight times the LDS reads for the head chains.)
 // G groups of 16 environments per workgroup: 2 where one group each would need more compute units than there are.
-// 256-256 pendulum, 8192 environments, T = 32: 369 -> 350 us an unroll; Catch, 4096 environments, T = 20: 142 -> 140.
+// 256-256 pendulum, 8192 environments, T = 32: 25.4 k cycles a step with both operands of the head chains from LDS and the
+// number of heads a run-time value (17 registers in scratch, whose reloads waited for the records' stores), 24.1 k now; Catch,
+// 4096 environments, T = 20: 14.6 k and 14.1 k.  The registers that frees let a learner's workgroup share the unit: a
+// decoupled step of the latter 416 -> 395 us.
 // ---------------------------------------------------------------------------
 constexpr int RES_WAVES = 8;
 
@@ -899,7 +902,8 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
     uint32_t* rng = reinterpret_cast<uint32_t*>(b1s + RW);         // [2][TM][4] draws: the action's two words (pendulum: noise), the reset's
     uint32_t* obs = rng + 2 * TM * 4;                              // [TM][OBS_WORDS]: cells, features; maze: walls and the cell
     float* w1s = reinterpret_cast<float*>(obs + TM * OBS_WORDS);   // [D][RW] W1; maze: [TM][RW] wall sums
-    const int NH = a.net.NH, NHP = a.net.NHP, D = a.net.dims[0], B = a.B, T = a.T;
+    constexpr int NH = ENV == ENV_CATCH ? 4 : ENV == ENV_PENDULUM ? 3 : 5, NHP = NH > 4 ? 8 : 4;   // actions, or mean and deviation, and the value
+    const int D = a.net.dims[0], B = a.B, T = a.T;
     const int n_cells = a.env.rows * a.env.cols;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = blockIdx.x * TM, rows_left = B - b0;            // the last workgroup may have one group only
@@ -1127,42 +1131,40 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
                     store_nt<NT>(Y + (16 * g + 4 * kq + r) * LDX + col0, o);
                 }
         }
+        float wh[RW / 16];                                             // head weights of the row's head, input 16 s + lane (they never change)
+        if (owner) {
+            const int e = lane & 15, j = lane >> 4;
+#pragma unroll
+            for (int s = 0; s < RW / 16; ++s) wh[s] = whs[(j < NH ? j : 0) * LDW + 16 * s + e];
+        }
         __syncthreads();
         asm volatile("" : "+v"(lane));
         hv0 = hbias0; hv1 = hbias1;
         if (owner) {
             // ---- head chains ----
-            const int e = lane & 15, j = lane >> 4;
+            const int e = lane & 15;
+            // The chain is bound by what one wavefront issues: a multiply-add four cycles, everything between them as much
+            // again.  Of its operands the environment's activations are read 16 bytes at a time; the head's weights sit in
+            // the lanes of the row, sixteen to a register, and reach the multiply-add as its row broadcast.  (Both read from
+            // LDS: 2.6 k cycles for 256 inputs.)
             const f4v* x = reinterpret_cast<const f4v*>(Y + (16 * wave + e) * LDX);
-            const f4v* w = reinterpret_cast<const f4v*>(whs + (j < NH ? j : 0) * LDW);
-            constexpr int S = RW / 4;
-            if (NH <= 4) {
-                constexpr int PF = 7;
-                f4v xr[PF], wr[PF];
+            constexpr int S = RW / 8, PF = 4;                      // pieces of eight inputs; read this many ahead
+            f4v xr[PF][2];
 #pragma unroll
-                for (int u = 0; u < PF; ++u) { xr[u] = x[u]; wr[u] = w[u]; }
+            for (int u = 0; u < PF; ++u) { xr[u][0] = x[2 * u]; xr[u][1] = x[2 * u + 1]; }
+            float w2[NH > 4 ? RW / 16 : 1];
+            if (NH > 4) {
 #pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    const f4v xv = xr[s % PF], wv = wr[s % PF];
-                    if (s + PF < S) { xr[s % PF] = x[s + PF]; wr[s % PF] = w[s + PF]; }
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int s = 0; s < RW / 16; ++s) w2[NH > 4 ? s : 0] = whs[4 * LDW + 16 * s + e];
+            }
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) hv0 = fmaf(xv[q], wv[q], hv0);
-                }
-            } else {
-                const f4v* w2 = reinterpret_cast<const f4v*>(whs + (j + 4 < NH ? j + 4 : 0) * LDW);
-                constexpr int PF = 5;
-                f4v xr[PF], wr[PF], vr[PF];
-#pragma unroll
-                for (int u = 0; u < PF; ++u) { xr[u] = x[u]; wr[u] = w[u]; vr[u] = w2[u]; }
-#pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    const f4v xv = xr[s % PF], wv = wr[s % PF], vv = vr[s % PF];
-                    if (s + PF < S) { xr[s % PF] = x[s + PF]; wr[s % PF] = w[s + PF]; vr[s % PF] = w2[s + PF]; }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) { hv0 = fmaf(xv[q], wv[q], hv0); hv1 = fmaf(xv[q], vv[q], hv1); }
-                }
+            for (int s = 0; s < S; ++s) {
+                const f4v x0 = xr[s % PF][0], x1 = xr[s % PF][1];
+                __builtin_amdgcn_sched_barrier(0);
+                if (s % 2 == 0) { chain8<0>(wh[s / 2], x0, x1, hv0); if (NH > 4) chain8<0>(w2[NH > 4 ? s / 2 : 0], x0, x1, hv1); }
+                else { chain8<8>(wh[s / 2], x0, x1, hv0); if (NH > 4) chain8<8>(w2[NH > 4 ? s / 2 : 0], x0, x1, hv1); }
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + PF < S) { xr[s % PF][0] = x[2 * (s + PF)]; xr[s % PF][1] = x[2 * (s + PF) + 1]; }
             }
             if (t < T) {
                 // ---- sample, step, observe ----
