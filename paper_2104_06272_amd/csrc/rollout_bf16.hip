@@ -17,13 +17,14 @@
 // maze the wall plane and the goal never change, so their contribution (bias +
 // wall rows + goal row) is computed once per launch, on the matrix cores, and
 // then lives in registers for the whole unroll; each step adds the agent row.
-// Hidden activations go to HBM sample-packed (see learn_bf16.hip) straight
-// from registers: the accumulator layout of the MFMA holds four consecutive
-// samples of one column, half of a packed group.
+// Hidden activations go to HBM sample-packed (see learn_bf16.hip): layers of
+// different widths from registers, where the accumulator layout of the MFMA holds
+// four consecutive samples of one column, half of a packed group; equal layers and
+// the first one from LDS, by transposing reads.
 //
 // Weights of the hidden layers are read from L2 in operand tiles (one KiB per
-// wavefront load, see internal.h), prefetched four 16-input steps ahead into a
-// double register buffer; two wavefronts per SIMD cover the rest of the latency.
+// wavefront load, see internal.h), four 16-input steps ahead or more; two
+// wavefronts per SIMD cover the rest of the latency.
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16 (verified on gfx950): lane l feeds
 // A[row l%32][k 8*(l/32) .. +7] and B[k 8*(l/32) .. +7][col l%32]; accumulator
@@ -111,104 +112,153 @@ __device__ __forceinline__ void bf16_layer(const uint16_t* __restrict__ X, uint1
         }
 }
 
-// The same layer for nets whose hidden layers all have this width, with the weight stream running
-// across layer boundaries: the first two blocks of the next layer's weights are requested before this
-// layer's activations are stored.  Loads and stores of a wavefront complete in issue order, so a load
-// issued behind the activation stores is not seen as complete until the stores are acknowledged;
-// issued ahead of them it costs nothing, and the next layer starts without waiting.
-// w0/w1: on entry steps 0..2U-1 of this layer (bf16_layer_first loads them for the first one); on exit,
-// with Wt_next, steps 0..2U-1 of the next.
-template <int NT>
-__device__ __forceinline__ void bf16_layer_stream(const uint16_t* __restrict__ X, uint16_t* __restrict__ Y, int ldx,
-                                                  const uint16_t* __restrict__ Wt, const uint16_t* __restrict__ Wt_next,
-                                                  const float* __restrict__ bias, int K, int N, int wave, int lane,
-                                                  uint16_t* __restrict__ gP, size_t g8, uint32_t* __restrict__ gM,
-                                                  bf8 (&w0)[4][NT], bf8 (&w1)[4][NT])
+// One piece of an activation tile X[64][..] on its way to HBM, sample-packed: lanes 0..31 take columns n0 .. n0 + 31 of the
+// samples 16 gp + 0..7 of half mt, lanes 32..63 of the next eight.  The transposing read gives a lane four rows of one column
+// (a group of 16 lanes reads 4 rows x 16 columns, lane s row s / 4 and columns 4 (s % 4) ..).  The ReLU flags of the piece go
+// into m0 (rows 0..3 of each eight) and m1 (rows 4..7), to be shifted by twice the lane's half.
+__device__ __forceinline__ u32v4 read_piece(const uint16_t* __restrict__ X, int ldx, int n0, int mt, int gp, int lane)
 {
-    constexpr int U = 4;
+    typedef short s4v __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4v* lds_s4;
+    const int kg = lane >> 5, s = lane & 15, gq = (lane >> 4) & 1;
+    const uint16_t* x = X + (32 * mt + 16 * gp + 8 * kg + (s >> 2)) * ldx + n0 + 16 * gq + 4 * (s & 3);
+    const u32v2 lo = __builtin_bit_cast(u32v2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(x)));
+    const u32v2 hi = __builtin_bit_cast(u32v2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(x + 4 * ldx)));
+    u32v4 v;
+    v[0] = lo[0]; v[1] = lo[1]; v[2] = hi[0]; v[3] = hi[1];
+    return v;
+}
+// Memory is addressed through buffer descriptors, one per tile and array: what is not to be written has a descriptor of no
+// bytes.  A branch around the stores would hide from the compiler how many operations are behind a load of the weight stream,
+// and its waits would be for newer loads than the one that is needed.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t store_rsrc(const void* p, bool on) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, on ? 0x7fffffffu : 0u, 0x00020000); }
+constexpr int NT_STORE = 2;             // streaming: written once, read by the update; the weights stay in L2
+// dst: the packed activations of the tile's first sample group; flags: the ReLU words of its first stage
+__device__ __forceinline__ void store_piece(const u32v4 v, int n0, int mt, int gp, int lane, int N, rsrc_t dst, uint32_t& m0, uint32_t& m1)
+{
     const int l32 = lane & 31, kg = lane >> 5;
-    const int n0 = wave * 32 * NT;
-    if (n0 >= N) return;
-    f16v acc[2][NT];
+    __builtin_amdgcn_raw_buffer_store_b128(v, dst, 16 * (kg * N + l32), 16 * ((4 * mt + 2 * gp) * N + n0), NT_STORE);
+    m0 |= (nonzero_flags_pk(v[0]) << (4 * gp)) | (nonzero_flags_pk(v[1]) << (4 * gp + 1));
+    m1 |= (nonzero_flags_pk(v[2]) << (4 * gp)) | (nonzero_flags_pk(v[3]) << (4 * gp + 1));
+}
+// the ReLU words of a half of the tile, from the flags of its two pieces: each half of the lanes has two of the four groups of
+// eight samples of both words, and writes one word
+__device__ __forceinline__ void store_flags(int n0, int mt, int lane, int N, rsrc_t flags, uint32_t m0, uint32_t m1)
+{
+    const int l32 = lane & 31, kg = lane >> 5;
+    const u32v2 w = __builtin_bit_cast(u32v2, __builtin_amdgcn_permlane32_swap(m0 << (2 * kg), m1 << (2 * kg), false, false));
+    __builtin_amdgcn_raw_buffer_store_b32(w[0] | w[1], flags, 4 * (kg * N + l32), 4 * (2 * mt * N + n0), NT_STORE);
+}
+// 32 NT columns of an activation tile to HBM at once
+template <int NT>
+__device__ __forceinline__ void store_tile(const uint16_t* X, int ldx, int n0, int lane, int N, rsrc_t dst, rsrc_t flags)
+{
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const float b = bias[n0 + 32 * t + l32];
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { acc[0][t][r] = b; acc[1][t][r] = b; }
-    }
-    const uint16_t* xa = X + l32 * ldx + 8 * kg;
-    const int KS = K >> 4;                                       // the next layer has the same K and N
-    const size_t wave_off = ((size_t)(n0 >> 5) * KS << 9) + lane * 8;
-    const uint16_t* wb = Wt + wave_off;
-    const uint16_t* wn = Wt_next ? Wt_next + wave_off : wb;
-    auto load = [&](bf8 (&d)[U][NT], const uint16_t* base, int s) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) d[u][t] = *reinterpret_cast<const bf8*>(base + ((size_t)(t * KS + s + u) << 9));
-    };
-    auto compute = [&](const bf8 (&d)[U][NT], int s) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bf8 a0 = *reinterpret_cast<const bf8*>(xa + 16 * (s + u));
-            const bf8 a1 = *reinterpret_cast<const bf8*>(xa + 32 * ldx + 16 * (s + u));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, d[u][t], acc[0][t], 0, 0, 0);
-                acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, d[u][t], acc[1][t], 0, 0, 0);
-            }
-        }
-    };
-    for (int s = 0; s < KS; s += 2 * U) {
-        const bool last = s + 2 * U >= KS;
-        __builtin_amdgcn_sched_barrier(0);
-        compute(w0, s);
-        if (!last) load(w0, wb, s + 2 * U);
-        else if (Wt_next) load(w0, wn, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(w1, s + U);
-        if (!last) load(w1, wb, s + 3 * U);
-        else if (Wt_next) load(w1, wn, U);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int col = n0 + 32 * t + l32;
-            uint32_t mk = 0u;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int row = mt * 32 + 8 * g + 4 * kg;
-                const uint32_t p01 = pack_bf16x2(relu(acc[mt][t][4 * g]), relu(acc[mt][t][4 * g + 1]));
-                const uint32_t p23 = pack_bf16x2(relu(acc[mt][t][4 * g + 2]), relu(acc[mt][t][4 * g + 3]));
-                Y[(row + 0) * ldx + col] = (uint16_t)p01; Y[(row + 1) * ldx + col] = (uint16_t)(p01 >> 16);
-                Y[(row + 2) * ldx + col] = (uint16_t)p23; Y[(row + 3) * ldx + col] = (uint16_t)(p23 >> 16);
-                if (gP) {
-                    u32v2 pv; pv[0] = p01; pv[1] = p23;
-                    __builtin_nontemporal_store(pv, reinterpret_cast<u32v2*>(gP + ((g8 + mt * 4 + g) * N + col) * 8 + 4 * kg));
-                    mk |= (nonzero_flags_pk(p01) << (2 * g)) | (nonzero_flags_pk(p23) << (2 * g + 1));
-                }
-            }
-            if (gP) __builtin_nontemporal_store(mk, gM + relu_mask_index((g8 >> 2) + mt, kg, N, col));
+        for (int mt = 0; mt < 2; ++mt) {
+            uint32_t m0 = 0u, m1 = 0u;
+            const u32v4 v0 = read_piece(X, ldx, n0 + 32 * t, mt, 0, lane), v1 = read_piece(X, ldx, n0 + 32 * t, mt, 1, lane);
+            store_piece(v0, n0 + 32 * t, mt, 0, lane, N, dst, m0, m1);
+            store_piece(v1, n0 + 32 * t, mt, 1, lane, N, dst, m0, m1);
+            store_flags(n0 + 32 * t, mt, lane, N, flags, m0, m1);
         }
 }
 
-template <int NT>
-__device__ __forceinline__ void bf16_layer_first(const uint16_t* __restrict__ Wt, int K, int N, int wave, int lane,
-                                                 bf8 (&w0)[4][NT], bf8 (&w1)[4][NT])
+// The same layer for nets whose hidden layers all have this width H.  What bounds it: the weights' way from L2 (512 columns:
+// 512 KB a layer, 54 B per cycle and compute unit when all of them stream: 9.7 k cycles) and the matrix cores (8.2 k), so
+// nothing may stand in the way of either:
+// - The stream of a wavefront runs RING k steps ahead, through layers and time steps without a break: the next layer's
+//   first weights are asked for during this one, the first layer's during the last of the step before.  (Eight steps ahead
+//   were no quicker and took registers that the maze's prefix needs.)
+// - Loads and stores of a wavefront complete in issue order, so a load behind a store waits for its acknowledgement.  Biases
+//   are in LDS (read from memory they waited for the first layer's stores, 2 k cycles); the layer's inputs go to HBM from
+//   LDS, a piece a step, beside the MFMAs.
+// - The weights are the A operand (rows: outputs), the activations the B operand (columns: environments): a lane ends up
+//   with four consecutive outputs of one environment, one 8-byte LDS store (as the other operand order: four 2-byte ones,
+//   2.2 k cycles of a 512-wide layer's 3.5 k between its last MFMA and the barrier).
+// 3 layers of 512 units, 16 x 16 maze, 16384 environments, 33 passes: 793 -> 669 us, 45.1 -> 37.9 k cycles a pass.  Of these
+// the two streamed layers take 27.8 k (MFMAs 16.4 k; without the stores 25.5 k, without the weights' loads as well 20.6 k).
+constexpr int RING = 4;
+template <int NT, int H>
+__device__ __forceinline__ void bf16_layer_stream(const uint16_t* __restrict__ X, uint16_t* __restrict__ Y, int ldx,
+                                                  const uint16_t* __restrict__ Wt, const uint16_t* __restrict__ Wt_next,
+                                                  const float* __restrict__ bias, int wave, int lane, rsrc_t dst, rsrc_t flags, bf8 (&w)[RING][NT])
 {
+    constexpr int KS = H / 16, PN = 4 * NT;                        // k steps; pieces of X to store, one a step
+    static_assert(KS % RING == 0 && PN < KS, "whole turns of the ring; the pieces fit");
+    const int l32 = lane & 31, kg = lane >> 5;
     const int n0 = wave * 32 * NT;
-    if (n0 >= N) return;
-    const int KS = K >> 4;
+    if (n0 >= H) return;
+    f16v acc[2][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 b = *reinterpret_cast<const float4*>(bias + n0 + 32 * t + 8 * g + 4 * kg);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) { acc[mt][t][4 * g] = b.x; acc[mt][t][4 * g + 1] = b.y; acc[mt][t][4 * g + 2] = b.z; acc[mt][t][4 * g + 3] = b.w; }
+        }
+    const uint16_t* xa = X + l32 * ldx + 8 * kg;
+    const size_t wave_off = ((size_t)(n0 >> 5) * KS << 9) + lane * 8;
+    bf8 av[2][2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) av[0][mt] = *reinterpret_cast<const bf8*>(xa + 32 * mt * ldx);
+    uint32_t m0 = 0u, m1 = 0u;
+    u32v4 piece;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        if (s + 1 < KS) {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) av[(s + 1) & 1][mt] = *reinterpret_cast<const bf8*>(xa + 32 * mt * ldx + 16 * (s + 1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s % RING][t], av[s & 1][mt], acc[mt][t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            w[s % RING][t] = *reinterpret_cast<const bf8*>((s + RING < KS ? Wt : Wt_next) + wave_off + ((size_t)(t * KS + (s + RING) % KS) << 9));
+        // pieces of X: tile of 32 columns, half of the samples, 16 of its 32; read a step before it is stored
+        if (s >= 1 && s <= PN) {
+            const int pc = s - 1;
+            store_piece(piece, n0 + 32 * (pc / 4), (pc / 2) % 2, pc % 2, lane, H, dst, m0, m1);
+            if (pc % 2 == 1) {
+                store_flags(n0 + 32 * (pc / 4), (pc / 2) % 2, lane, H, flags, m0, m1);
+                m0 = 0u; m1 = 0u;
+            }
+        }
+        if (s < PN) piece = read_piece(X, ldx, n0 + 32 * (s / 4), (s / 2) % 2, s % 2, lane);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                u32v2 v;
+                v[0] = pack_bf16x2(relu(acc[mt][t][4 * g]), relu(acc[mt][t][4 * g + 1]));
+                v[1] = pack_bf16x2(relu(acc[mt][t][4 * g + 2]), relu(acc[mt][t][4 * g + 3]));
+                *reinterpret_cast<u32v2*>(Y + (32 * mt + l32) * ldx + n0 + 32 * t + 8 * g + 4 * kg) = v;
+            }
+}
+
+// the first weights of the stream
+template <int NT, int H>
+__device__ __forceinline__ void bf16_ring_fill(const uint16_t* __restrict__ Wt, int wave, int lane, bf8 (&w)[RING][NT])
+{
+    constexpr int KS = H / 16;
+    const int n0 = wave * 32 * NT;
+    if (n0 >= H) return;
     const uint16_t* wb = Wt + ((size_t)(n0 >> 5) * KS << 9) + lane * 8;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int s = 0; s < RING; ++s)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            w0[u][t] = *reinterpret_cast<const bf8*>(wb + ((size_t)(t * KS + u) << 9));
-            w1[u][t] = *reinterpret_cast<const bf8*>(wb + ((size_t)(t * KS + 4 + u) << 9));
-        }
+        for (int t = 0; t < NT; ++t) w[s][t] = *reinterpret_cast<const bf8*>(wb + ((size_t)(t * KS + s) << 9));
 }
 
 __device__ __forceinline__ void run_bf16_layer(const uint16_t* X, uint16_t* Y, int ldx, const uint16_t* Wt, const float* bias,
@@ -228,7 +278,8 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
 {
     extern __shared__ uint4 smem4[];
     uint16_t* bufA = reinterpret_cast<uint16_t*>(smem4);
-    const int ldx = a.ldx, NH = a.net.NH, NHP = a.net.NHP, L = a.net.L, HL = a.net.dims[a.net.L];
+    constexpr int NH = ENV == ENV_CATCH ? 4 : ENV == ENV_PENDULUM ? 3 : 5, NHP = NH > 4 ? 8 : 4;   // actions, or mean and deviation, and the value
+    const int ldx = a.ldx, L = a.net.L, HL = UNI ? H1 : a.net.dims[a.net.L];
     const int D = a.net.dims[0];
     const int ldh = HL + 8;
     uint16_t* bufB = bufA + BTM * ldx;
@@ -236,6 +287,7 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
     float* hp = reinterpret_cast<float*>(whs + 8 * ldh);         // [4][64][8] partial head sums per quarter of HL
     uint32_t* obs = reinterpret_cast<uint32_t*>(hp + 4 * BTM * 8);
     uint32_t* rng = obs + BTM * BOBS;
+    float* bs = reinterpret_cast<float*>(rng + BTM * 2);         // UNI: [L - 1][H1] biases of the layers behind the first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b0 = blockIdx.x * BTM;
@@ -263,6 +315,7 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
         const int k = i / ldh, j = i - k * ldh;
         whs[i] = (k < NH && j < HL) ? a.wt[a.net.wh_off + (size_t)k * HL + j] : (uint16_t)0;
     }
+    if (UNI) for (int i = tid; i < (L - 1) * H1; i += BWG) bs[i] = a.theta[a.net.b_off[1 + i / H1] + i % H1];
     __syncthreads();
     // first-layer constants of this thread: the bias, plus -- for the maze -- the contribution of the wall
     // plane and of the goal cell, which never change: prefix[64][H1] = b1 + Walls[64][cells] W1[cells][H1]
@@ -331,6 +384,9 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
         }
     }
 
+    constexpr int NTU = H1 >= 512 ? 2 : 1;
+    bf8 ring[RING][NTU];                                         // UNI: the weight stream's next k steps
+    if (UNI && L > 1) bf16_ring_fill<NTU, H1>(a.wt + a.net.w_off[1], __builtin_amdgcn_readfirstlane(wave), lane, ring);
     const int tid_outer = tid;
     const int t_begin = REPLAY ? (int)blockIdx.y * a.tseg : 0;
     const int t_end = REPLAY ? (t_begin + a.tseg < a.tend ? t_begin + a.tseg : a.tend) : T + 1;
@@ -371,6 +427,9 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
         __syncthreads();
         const bool keep = t < T && a.keep_acts;
         const size_t g8 = ((size_t)t * B + b0) >> 3;             // first sample group of this tile
+        // where layer l (from 0, all of them H1 wide, or the first) is kept; the flags of a narrower first layer are not
+        auto tile_rsrc = [&](int l) { return store_rsrc(reinterpret_cast<const uint16_t*>(tp.act[l]) + g8 * H1 * 8, keep); };
+        auto flag_rsrc = [&](int l) { return store_rsrc(tp.mask[l] + relu_mask_index(g8 >> 2, 0, H1, 0), keep && (l > 0 || H1 >= 512)); };
         // the last wavefront draws this step's random numbers while it waits for its weight rows
         if (!REPLAY && wave == 7 && t < T) {
             const u32x4 w = philox(a.seed, (uint32_t)(b0 + lane), a.gstep + (uint64_t)t, DOM_ACTION);
@@ -391,10 +450,6 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
                         r1[ENV == ENV_CATCH ? m : 0] = *reinterpret_cast<const uint32_t*>(w1 + (size_t)obs[(e0 + m) * BOBS + 1] * H1 + c);
                 }
             }
-            uint16_t* actP = keep ? reinterpret_cast<uint16_t*>(tp.act[0]) : nullptr;
-            // with 32 environments per thread (H1 = 512) a thread holds whole 32-sample stages of its two columns
-            // and writes their ReLU masks (both row halves); narrower first layers leave the mask to the activations
-            uint32_t mkx[2] = {0u, 0u}, mky[2] = {0u, 0u};
 #pragma unroll
             for (int m0 = 0; m0 < EPT; m0 += 8) {
                 float v[8][2];
@@ -428,45 +483,21 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
                     *reinterpret_cast<uint32_t*>(bufA + (e0 + m0 + 2 * q) * ldx + c) = (px[q] & 0xffffu) | (py[q] << 16);
                     *reinterpret_cast<uint32_t*>(bufA + (e0 + m0 + 2 * q + 1) * ldx + c) = (px[q] >> 16) | (py[q] & 0xffff0000u);
                 }
-                if (actP) {
-                    u32v4* dst = reinterpret_cast<u32v4*>(actP + ((g8 + (e0 >> 3)) * H1 + c) * 8) + (size_t)(m0 >> 3) * H1;   // 16-byte units: one group of eight samples is H1 of them
-                    u32v4 vx4, vy4;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) { vx4[q] = px[q]; vy4[q] = py[q]; }
-                    __builtin_nontemporal_store(vx4, dst);
-                    __builtin_nontemporal_store(vy4, dst + 1);
-                    if (EPT == 32) {
-#pragma unroll
-                        for (int k2 = 0; k2 < 2; ++k2) {
-                            mkx[k2] |= (nonzero_flags_pk(px[2 * k2]) << (m0 >> 2)) | (nonzero_flags_pk(px[2 * k2 + 1]) << ((m0 >> 2) + 1));
-                            mky[k2] |= (nonzero_flags_pk(py[2 * k2]) << (m0 >> 2)) | (nonzero_flags_pk(py[2 * k2 + 1]) << ((m0 >> 2) + 1));
-                        }
-                    }
-                }
-            }
-            if (actP && EPT == 32) {
-#pragma unroll
-                for (int k2 = 0; k2 < 2; ++k2) {
-                    u32v2 mv; mv[0] = mkx[k2]; mv[1] = mky[k2];
-                    __builtin_nontemporal_store(mv, reinterpret_cast<u32v2*>(tp.mask[0] + relu_mask_index((g8 >> 2) + (e0 >> 5), k2, H1, c)));
-                }
             }
         }
         __syncthreads();
         uint16_t* cur = bufA;
         uint16_t* nxt = bufB;
         if (UNI) {
-            constexpr int NTU = H1 >= 512 ? 2 : 1;
-            bf8 w0[4][NTU], w1[4][NTU];
-            bf16_layer_first<NTU>(a.wt + a.net.w_off[1], H1, H1, wave, lane, w0, w1);
+#pragma unroll 1
             for (int l = 1; l < L; ++l) {
-                bf16_layer_stream<NTU>(cur, nxt, ldx, a.wt + a.net.w_off[l], l + 1 < L ? a.wt + a.net.w_off[l + 1] : nullptr,
-                                       a.theta + a.net.b_off[l], H1, H1, wave, lane,
-                                       keep ? reinterpret_cast<uint16_t*>(tp.act[l]) : nullptr, g8, tp.mask[l], w0, w1);
+                bf16_layer_stream<NTU, H1>(cur, nxt, ldx, a.wt + a.net.w_off[l], a.wt + a.net.w_off[l + 1 < L ? l + 1 : 1], bs + (l - 1) * H1,
+                                           wave, lane, tile_rsrc(l - 1), flag_rsrc(l - 1), ring);
                 __syncthreads();
                 uint16_t* tmp = cur; cur = nxt; nxt = tmp;
             }
         } else {
+            if (keep && wave < H1 / 64) store_tile<2>(bufA, ldx, 64 * wave, lane, H1, tile_rsrc(0), flag_rsrc(0));
             for (int l = 1; l < L; ++l) {
                 const int K = a.net.dims[l], N = a.net.dims[l + 1];
                 run_bf16_layer(cur, nxt, ldx, a.wt + a.net.w_off[l], a.theta + a.net.b_off[l], K, N, wave, lane,
@@ -504,14 +535,26 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
             }
         }
         __syncthreads();
+        if (UNI && keep) {
+            // the last layer to HBM, by the wavefronts that do not sample; the last one takes the first's share
+            const rsrc_t dst = tile_rsrc(L - 1), flags = flag_rsrc(L - 1);
+            if (wave > 0 && wave * 32 * NTU < H1) store_tile<NTU>(cur, ldx, wave * 32 * NTU, lane, H1, dst, flags);
+            if (wave == 7) store_tile<NTU>(cur, ldx, 0, lane, H1, dst, flags);
+        }
         if (owner) {
             float hv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            float4 hq[4][2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                hq[q][0] = *reinterpret_cast<const float4*>(hp + (q * BTM + tid) * 8);
+                hq[q][1] = NH > 4 ? *reinterpret_cast<const float4*>(hp + (q * BTM + tid) * 8 + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
 #pragma unroll
             for (int j = 0; j < 8; ++j)
                 if (j < NH) {
                     float s = hb[j];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) s += hp[(q * BTM + tid) * 8 + j];
+                    for (int q = 0; q < 4; ++q) s += j % 4 == 0 ? hq[q][j / 4].x : j % 4 == 1 ? hq[q][j / 4].y : j % 4 == 2 ? hq[q][j / 4].z : hq[q][j / 4].w;
                     hv[j] = s;
                 }
             float* hd = tp.tr_head + tb * NHP;
@@ -532,7 +575,7 @@ __global__ __launch_bounds__(BWG) void rollout_bf16_kernel(const RolloutBf16Args
                         pendulum_reset(st, wr.x, wr.y);
                     }
                 } else {
-                    const int act = sample_categorical_any(hv[0], hv[1], hv[2], hv[3], hv[4], hv[5], hv[6], hv[7], a.net.A, u01(dr.x));
+                    const int act = sample_categorical_any(hv[0], hv[1], hv[2], hv[3], hv[4], hv[5], hv[6], hv[7], ENV == ENV_CATCH ? 3 : 4, u01(dr.x));
                     tp.tr_act[tb] = (uint8_t)act;
                     if (ENV == ENV_CATCH) {
                         catch_step(a.env, st, act, 0u, r, done);
@@ -601,7 +644,7 @@ static hipError_t launch_bf16_forward(anakin* h, int what, bool bootstrap = true
     a.tend = h->T + (bootstrap ? 1 : 0);
     a.tseg = REPLAY ? replay_segment(h->B / BTM, a.tend) : a.tend;
     const int HL = h->net.dims[h->net.L], H1 = h->net.dims[1];
-    const size_t lds = (size_t)2 * BTM * a.ldx * 2 + (size_t)8 * (HL + 8) * 2 + (size_t)4 * BTM * 8 * 4 + (size_t)BTM * (BOBS + 2) * 4;
+    const size_t lds = (size_t)2 * BTM * a.ldx * 2 + (size_t)8 * (HL + 8) * 2 + (size_t)4 * BTM * 8 * 4 + (size_t)BTM * (BOBS + 2) * 4 + (size_t)(h->net.L - 1) * H1 * 4;
     auto launch = [&](auto kern) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -497,6 +497,17 @@ def test_bf16_matrix_core_path(gpu, orc, case):
     _forced_lockstep(gpu, orc, cfg, seed, updates)
 
 
+# the streamed weights of equal layers: no stream at all (one layer), as many layers as their biases' room in LDS is made
+# for, half of the wavefronts without columns (128), masks of a first layer that is narrower than 512
+@pytest.mark.parametrize("kind,hidden", [("maze", [512]), ("maze", [512] * 4), ("catch", [512, 512]), ("pendulum", [512] * 3),
+                                         ("catch", [256] * 4), ("pendulum", [128] * 4)])
+def test_bf16_streamed_equal_layers(gpu, orc, kind, hidden):
+    name = {"maze": "maze_16384", "catch": "catch_4096", "pendulum": "pendulum_8192"}[kind]
+    cfg = variant(name, hidden=hidden, B=64, T=4, dtype="bf16")
+    say(f"[bf16 streamed] {kind} hidden={hidden}")
+    _forced_lockstep(gpu, orc, cfg, 2, 1, prepare=lambda g, o: g.set_mode(gpu.MODE_STREAM_WEIGHTS))
+
+
 def _place_next_to_goal(g, o):
     """every env on a free neighbour of the goal with 250 - (b % 3) of its 256 steps used (16 x 16 maze)"""
     walls = np.unpackbits(o.walls.view(np.uint8), axis=1, bitorder="little").reshape(g.B, 16, 16).astype(bool)
