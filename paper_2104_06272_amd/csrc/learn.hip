@@ -1179,39 +1179,58 @@ __global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce(const AdamArgs a)
 }
 
 // One parameter per lane, 64 per workgroup: four times the workgroups of adam_reduce, which is what small parameter
-// vectors (under about 2^18) need to keep every compute unit loading.  Also where the partials are few: the 16
-// wavefronts read one each, side by side, and wave order is then ascending order, so the bits are adam_reduce_flat's
+// vectors (under about 2^18) need to keep every compute unit loading.  Also where the partials are few: the 16 shares
+// are one partial each, side by side, and their order is then ascending order, so the bits are adam_reduce_flat's
 // (Catch 128-128, 256 samples, 16 partials: 24.0 us there, 6.7 here; 64-64-128: 24.0 and 6.5; 512-128 in bf16: 21 and
-// 10.5).
-__global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce_narrow(const AdamArgs a)
+// 10.5).  What bounds it is the round trips to memory of a workgroup and how many rounds of workgroups there are: with 16
+// wavefronts per workgroup, four loads in flight each and the moments asked for behind the sum, 79876 parameters with 128
+// partials took 13.6 us, now 11.4; 158468 with 126 16.3 and 11.5; 67587 10.3 and 8.8; 17411 unchanged at 4.9 and
+// (bf16) 6.3.  (The moments beside the partials in adam_reduce as well: 58.5 -> 63.5 us on the maze's 921605 parameters.)
+__global__ __launch_bounds__(WG) void adam_reduce_narrow(const AdamArgs a)
 {
-    // 64 consecutive parameters per workgroup; each of the 16 wavefronts adds its share of the
-    // split-K partials (splits w, w+16, w+32, ...), then the 16 sums are combined in wave order
+    // 64 consecutive parameters per workgroup, 16 shares of the split-K partials (splits w, w + 16, w + 32, ...), four to a
+    // wavefront; then the 16 sums are combined in ascending order.  A wavefront has 32 loads in flight and a compute unit
+    // room for eight workgroups, so that even the largest vector that comes here takes little more than one round of them.
     __shared__ float red[ADAM_WAVES][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x * 64 + lane;
     const bool ok = i < a.P;
-    float g = 0.0f;
+    constexpr int SH = ADAM_WAVES * 64 / WG;
+    float g[SH] = {0.0f, 0.0f, 0.0f, 0.0f}, mo = 0.0f, vo = 0.0f, to = 0.0f;
     if (ok) {
+        // the wavefront that takes the step has its parameters and moments under way beside the partials (asked for behind
+        // the sum, they were a second memory round trip of every workgroup)
+        if (wave == 0) { mo = a.m[i]; vo = a.v[i]; to = a.theta[i]; }
         int r = 0;
 #pragma unroll
         for (int k = 1; k < MAX_ADAM_REGIONS; ++k) if (k < a.n_regions && i >= a.reg[k].start) r = k;
         const Region rg = a.reg[r];
         const float* p = rg.partial + (i - rg.start);
-#pragma unroll 4
-        for (int s = wave; s < rg.splits; s += ADAM_WAVES) g += p[(size_t)s * rg.count];
+        constexpr int UF = 8;                                    // of each share
+        for (int s0 = wave; s0 < rg.splits; s0 += UF * ADAM_WAVES) {
+            float v[SH][UF];
+#pragma unroll
+            for (int u = 0; u < UF; ++u)
+#pragma unroll
+                for (int h = 0; h < SH; ++h) { const int s = s0 + h * (ADAM_WAVES / SH) + u * ADAM_WAVES; v[h][u] = p[(size_t)(s < rg.splits ? s : s0) * rg.count]; }
+#pragma unroll
+            for (int u = 0; u < UF; ++u)
+#pragma unroll
+                for (int h = 0; h < SH; ++h) g[h] = s0 + h * (ADAM_WAVES / SH) + u * ADAM_WAVES < rg.splits ? g[h] + v[h][u] : g[h];
+        }
     }
-    red[wave][lane] = g;
+#pragma unroll
+    for (int h = 0; h < SH; ++h) red[wave + h * (ADAM_WAVES / SH)][lane] = g[h];
     __syncthreads();
     if (wave != 0 || !ok) return;
-    g = red[0][lane];
+    float gs = red[0][lane];
 #pragma unroll
-    for (int w = 1; w < ADAM_WAVES; ++w) g += red[w][lane];
-    const float m = a.beta1 * a.m[i] + (1.0f - a.beta1) * g;
-    const float v = a.beta2 * a.v[i] + (1.0f - a.beta2) * g * g;
+    for (int w = 1; w < ADAM_WAVES; ++w) gs += red[w][lane];
+    const float m = a.beta1 * mo + (1.0f - a.beta1) * gs;
+    const float v = a.beta2 * vo + (1.0f - a.beta2) * gs * gs;
     const float mh = m / a.bc1, vh = v / a.bc2;
-    const float th = a.theta[i] - a.lr * mh / (sqrtf(vh) + a.eps);
-    a.grad[i] = g;
+    const float th = to - a.lr * mh / (sqrtf(vh) + a.eps);
+    a.grad[i] = gs;
     a.m[i] = m;
     a.v[i] = v;
     a.theta[i] = th;
@@ -1277,7 +1296,7 @@ static void launch_adam_kernel(const AdamArgs& a, hipStream_t s)
     for (int r = 0; r < a.n_regions; ++r) max_splits = a.reg[r].splits > max_splits ? a.reg[r].splits : max_splits;
     if (max_splits <= 16 && a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce_flat, dim3((a.P + 4 * WG - 1) / (4 * WG)), dim3(WG), 0, s, a);
     else if (a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce, dim3((a.P + 255) / 256), dim3(ADAM_WAVES * 64), 0, s, a);
-    else hipLaunchKernelGGL(adam_reduce_narrow, dim3((a.P + 63) / 64), dim3(ADAM_WAVES * 64), 0, s, a);
+    else hipLaunchKernelGGL(adam_reduce_narrow, dim3((a.P + 63) / 64), dim3(WG), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------
