@@ -54,7 +54,7 @@ constexpr int PROD_B[6] = {2, 0, 1, 0, 1, 0};
 // One barrier per stage: while the MFMAs run on one half of LDS the same wavefronts split the next stage's values (asked
 // for a whole stage earlier) into the other half.
 // ---------------------------------------------------------------------------
-template <int WI, int WJ, int AI, int AJ, int WK, bool HEADS>
+template <int WI, int WJ, int AI, int AJ, int WK, int HEADS>
 __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const int split, const int i0, const int j0)
 {
     static_assert(WI * WJ * WK == 8, "eight wavefronts");
@@ -71,14 +71,15 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
     const float* ysrc = HEADS ? a.hf.hl : a.dy;
     struct Set { float x[XP][8], y[YP][8], d[HEADS ? YP : 1]; };
     Set S0, S1;                                                   // raw values of two stages in flight
-    float bsum[YP], gwh[HEADS ? YP : 1][4], gbh = 0.0f, wh[HEADS ? YP : 1][4];
+    constexpr int HN = HEADS ? HEADS : 1, HP = HEADS > 4 ? 8 : 4;   // heads in the sums; of a row of the head gradient
+    float bsum[YP], gwh[HEADS ? YP : 1][HN], gbh = 0.0f, wh[HEADS ? YP : 1][HN];
 #pragma unroll
     for (int q = 0; q < YP; ++q) bsum[q] = 0.0f;
     if (HEADS) {
 #pragma unroll
         for (int q = 0; q < YP; ++q)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < HN; ++k) {
                 gwh[HEADS ? q : 0][k] = 0.0f;
                 const int j = j0 + (q * SWG + tid) % TJ;
                 wh[HEADS ? q : 0][k] = (k < a.hf.NH && j < a.N) ? head_weight(a.hf, j, k) : 0.0f;
@@ -104,8 +105,8 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
             const uint32_t co = c < a.N ? c : 0;
 #pragma unroll
             for (int e = 0; e < 8; ++e) st.y[q][e] = (src + (size_t)e * a.ldy)[co];
-            // the eight samples' head gradients, one value per lane: lane 4 e + k holds output k of sample e
-            if (HEADS) st.d[HEADS ? q : 0] = a.hf.dhead[(size_t)(mc + ((lane >> 2) & 7)) * a.hf.NHP + (lane & 3)];
+            // the eight samples' head gradients, one value per lane: lane HP e + k holds output k of sample e
+            if (HEADS) st.d[HEADS ? q : 0] = a.hf.dhead[(size_t)(mc + ((lane / HP) & 7)) * HP + (lane & (HP - 1))];
         }
     };
     // Putting stage s (held in st) into half b of LDS, in units of a dozen vector instructions that go between MFMAs:
@@ -113,7 +114,7 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
     // a piece stores it and asks for the same piece of stage s + 2.
     constexpr int UX = 4, UY = HEADS ? 12 : 4, UNITS = XP * UX + YP * UY;
     u4v_s tt[3];
-    float yv[8], gw[4], live = 1.0f;
+    float yv[8], gw[HN], live = 1.0f;
     auto unit = [&](Set& st, int b, int s, int u, bool refill) {
         if (u < XP * UX) {
             const int q = u / UX, i = u % UX, p = q * SWG + tid, c = p % TI, g = p / TI;
@@ -132,18 +133,18 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
             live = m_begin + s * S + 8 * __builtin_amdgcn_readfirstlane(g) < m_end ? 1.0f : 0.0f;
             if (HEADS) gbh = fmaf(live, st.d[HEADS ? q : 0], gbh);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) gw[k] = 0.0f;
+            for (int k = 0; k < HN; ++k) gw[k] = 0.0f;
         }
         if (HEADS && i < 8) {
-            float d[4];
+            float d[HN];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) d[k] = f_from_bits((uint32_t)__builtin_amdgcn_readlane((int)bits_from_f(st.d[HEADS ? q : 0]), 4 * i + k));
+            for (int k = 0; k < HN; ++k) d[k] = f_from_bits((uint32_t)__builtin_amdgcn_readlane((int)bits_from_f(st.d[HEADS ? q : 0]), HP * i + k));
             float o = wh[HEADS ? q : 0][0] * d[0];
 #pragma unroll
-            for (int k = 1; k < 4; ++k) o = fmaf(wh[HEADS ? q : 0][k], d[k], o);
+            for (int k = 1; k < HN; ++k) o = fmaf(wh[HEADS ? q : 0][k], d[k], o);
             const float hv = st.y[q][i < 8 ? i : 0];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) gw[k] = fmaf(hv, d[k], gw[k]);
+            for (int k = 0; k < HN; ++k) gw[k] = fmaf(hv, d[k], gw[k]);
             yv[i < 8 ? i : 0] = hv > 0.0f ? o : 0.0f;
             return;
         }
@@ -156,7 +157,7 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
             bsum[q] = fmaf(live, ((yv[0] + yv[1]) + (yv[2] + yv[3])) + ((yv[4] + yv[5]) + (yv[6] + yv[7])), bsum[q]);
             if (HEADS) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) gwh[HEADS ? q : 0][k] = fmaf(live, gw[k], gwh[HEADS ? q : 0][k]);
+                for (int k = 0; k < HN; ++k) gwh[HEADS ? q : 0][k] = fmaf(live, gw[k], gwh[HEADS ? q : 0][k]);
             }
             if (refill) fetch_y(st, s + 2, q);
         }
@@ -270,21 +271,21 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
     }
     if (i0 != 0) return;
     // column sums (and the head matrix's gradient): the GR threads of a column add up in ascending sample-group order
-    float* red = reinterpret_cast<float*>(lds);                  // [GR][TJ] sums, then [GR][TJ][4]
-    float* red4 = red + GR * TJ;
-    float* redb = red4 + (HEADS ? GR * TJ * 4 : 0);              // [SWG / TJ][32]
+    float* red = reinterpret_cast<float*>(lds);                  // [GR][TJ] sums, then [HN][GR][TJ]
+    float* redh = red + GR * TJ;
+    float* redb = redh + (HEADS ? HN * GR * TJ : 0);             // [SWG / TJ][64]
 #pragma unroll
     for (int q = 0; q < YP; ++q) {
         const int p = q * SWG + tid, c = p % TJ, g = p / TJ;
         red[g * TJ + c] = bsum[q];
         if (HEADS) {
-            f4v_s v = {gwh[HEADS ? q : 0][0], gwh[HEADS ? q : 0][1], gwh[HEADS ? q : 0][2], gwh[HEADS ? q : 0][3]};
-            *reinterpret_cast<f4v_s*>(red4 + (g * TJ + c) * 4) = v;
+#pragma unroll
+            for (int k = 0; k < HN; ++k) redh[(k * GR + g) * TJ + c] = gwh[HEADS ? q : 0][k];
         }
     }
     // every wavefront holds the head-bias sums of the sample groups it loaded; one of each kind hands them over
     if (HEADS && j0 == 0) {
-        if ((tid % TJ) < 64 && lane < 32) redb[(tid / TJ) * 32 + lane] = gbh;
+        if ((tid % TJ) < 64) redb[(tid / TJ) * 64 + lane] = gbh;
     }
     __syncthreads();
     if (tid < TJ && j0 + tid < a.N) {
@@ -293,17 +294,20 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
         for (int g = 0; g < GR; ++g) s += red[g * TJ + tid];
         out[(size_t)a.K * a.N + j0 + tid] = s;
         if (HEADS) {
-            f4v_s s4 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int g = 0; g < GR; ++g) s4 += *reinterpret_cast<const f4v_s*>(red4 + (g * TJ + tid) * 4);
             float* hout = a.hf.head_partial + (size_t)split * ((size_t)a.N * a.hf.NH + a.hf.NH) + (size_t)(j0 + tid) * a.hf.NH;
-            for (int k = 0; k < a.hf.NH; ++k) hout[k] = s4[k];
+#pragma unroll
+            for (int k = 0; k < HN; ++k) {
+                float sk = 0.0f;
+#pragma unroll
+                for (int g = 0; g < GR; ++g) sk += redh[(k * GR + g) * TJ + tid];
+                if (k < a.hf.NH) hout[k] = sk;
+            }
         }
     }
     if (HEADS && j0 == 0 && tid < a.hf.NH) {
         float s = 0.0f;
         for (int g = 0; g < SWG / TJ; ++g)
-            for (int e = 0; e < 8; ++e) s += redb[g * 32 + 4 * e + tid];
+            for (int e = 0; e < 8; ++e) s += redb[g * 64 + HP * e + tid];
         a.hf.head_partial[(size_t)split * ((size_t)a.N * a.hf.NH + a.hf.NH) + (size_t)a.N * a.hf.NH + tid] = s;
     }
 }
@@ -335,7 +339,7 @@ __device__ __forceinline__ float buf_load1(rsrc_s r, uint32_t voff, uint32_t sof
 __device__ __forceinline__ f4v_s buf_load4(rsrc_s r, uint32_t voff, uint32_t soff) { return __builtin_bit_cast(f4v_s, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0)); }
 __device__ __forceinline__ void buf_store1(float v, rsrc_s r, uint32_t voff, uint32_t soff) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0); }
 
-template <int WN, int MT, bool HEADS, int FIRST>
+template <int WN, int MT, int HEADS, int FIRST>
 __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const int tile0, const int tile1, const int by, const int part)
 {
     constexpr int WM = 8 / WN, TR = 32 * MT * WM, PITCH = TR + 2, AP = TR * 4 / SWG;
@@ -344,8 +348,9 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     extern __shared__ float4 smem_s[];
     u4v_s* As = reinterpret_cast<u4v_s*>(smem_s);                 // [2][3 terms][4 groups of 8 j][PITCH]
     constexpr int HALF = 3 * 4 * PITCH;
-    f4v_s* whs = reinterpret_cast<f4v_s*>(As + 2 * HALF);         // HEADS: [N] head weights of a unit
-    float* obsS = reinterpret_cast<float*>(whs + (HEADS ? a.N : 0));   // FIRST: [3][NTS_SEG] features of a segment's samples
+    f4v_s* whs = reinterpret_cast<f4v_s*>(As + 2 * HALF);         // HEADS: [N] head weights of a unit, the first four
+    float* wh5 = reinterpret_cast<float*>(whs + (HEADS ? a.N : 0));   // HEADS > 4: [N] the fifth
+    float* obsS = wh5 + (HEADS > 4 ? a.N : 0);   // FIRST: [3][NTS_SEG] features of a segment's samples
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
     const int N = a.N, NC = N / NTS_KC;
@@ -359,11 +364,12 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = k < a.hf.NH ? head_weight(a.hf, j, k) : 0.0f;
             whs[j] = v;
+            if (HEADS > 4) wh5[j] = head_weight(a.hf, j, 4);
         }
     }
     // loader: thread = (row, group of eight j)
     const int lrow = tid >> 2, lg = tid & 3;
-    struct Set { f4v_s raw[AP][2], d[HEADS ? AP : 1]; };
+    struct Set { f4v_s raw[AP][2], d[HEADS ? AP : 1]; float d5[HEADS > 4 ? AP : 1]; };
     Set S0, S1;                                                   // dY of two steps in flight
     const float* ysrc = HEADS ? a.hf.hl : a.dy;
     const uint32_t yoff = ((uint32_t)lrow * (uint32_t)N + 8u * (uint32_t)lg) * 4u, doff = (uint32_t)lrow * (uint32_t)a.hf.NHP * 4u;
@@ -371,7 +377,11 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
         const rsrc_s ry = rows_rsrc(ysrc, tile * TR + q * (SWG / 4), SWG / 4, a.M, N);
         st.raw[q][0] = buf_load4(ry, yoff, c * (NTS_KC * 4));
         st.raw[q][1] = buf_load4(ry, yoff + 16, c * (NTS_KC * 4));
-        if (HEADS) st.d[HEADS ? q : 0] = buf_load4(rows_rsrc(a.hf.dhead, tile * TR + q * (SWG / 4), SWG / 4, a.M, a.hf.NHP), doff, 0);
+        if (HEADS) {
+            const rsrc_s rd = rows_rsrc(a.hf.dhead, tile * TR + q * (SWG / 4), SWG / 4, a.M, a.hf.NHP);
+            st.d[HEADS ? q : 0] = buf_load4(rd, doff, 0);
+            if (HEADS > 4) st.d5[HEADS > 4 ? q : 0] = buf_load1(rd, doff + 16, 0);
+        }
     };
     // chunk c of dY (held in st) into half b of LDS, in units of about ten vector instructions that go between MFMAs: per
     // piece eight head terms (HEADS) and four pairs; the last one stores the piece and asks for the same of step + 3
@@ -379,14 +389,18 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     u4v_s tt[3];
     float yv[8];
     f4v_s wv;
+    float wv5 = 0.0f;
     auto unit = [&](Set& st, int b, int c, int u, int tile_n, int c_n) {
         const int q = u / UY, v = u % UY;
         if (HEADS && v < 8) {
             const f4v_s w = v == 0 ? whs[c * NTS_KC + 8 * lg] : wv, d = st.d[HEADS ? q : 0];
+            const float w5 = HEADS > 4 ? (v == 0 ? wh5[c * NTS_KC + 8 * lg] : wv5) : 0.0f;
             if (v < 7) wv = whs[c * NTS_KC + 8 * lg + (v < 7 ? v + 1 : 0)];
+            if (HEADS > 4 && v < 7) wv5 = wh5[c * NTS_KC + 8 * lg + (v < 7 ? v + 1 : 0)];
             const float h = st.raw[q][(v < 8 ? v : 0) >> 2][v & 3];
             float o = w[0] * d[0];
             o = fmaf(w[1], d[1], o); o = fmaf(w[2], d[2], o); o = fmaf(w[3], d[3], o);
+            if (HEADS > 4) o = fmaf(w5, st.d5[HEADS > 4 ? q : 0], o);
             yv[v < 8 ? v : 0] = h > 0.0f ? o : 0.0f;
             return;
         }
@@ -568,7 +582,7 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
 }
 
 // both products of a layer in one launch: dW workgroups first, dX workgroups behind them
-template <int WI, int WJ, int AI, int AJ, int WK, int WN, int MT, bool HEADS, int FIRST>
+template <int WI, int WJ, int AI, int AJ, int WK, int WN, int MT, int HEADS, int FIRST>
 __global__ __launch_bounds__(SWG) void gemm_tn_nt_split(const GemmTnArgs t, const GemmNtArgs n, const int tn_blocks, const int tiles_j,
                                                         const int nt_bx, const int tiles_per_block)
 {
@@ -594,10 +608,12 @@ static hipError_t launch_split_tiles(GemmTnArgs t, const GemmNtArgs& n, int nt_b
     const int tiles_j = t.N / TJ, tn = t.tiles_i * tiles_j * t.splits;
     const int tiles = (n.M + TR - 1) / TR, per = (tiles + nt_blocks - 1) / nt_blocks, bx = (tiles + per - 1) / per, by = (n.K + TC - 1) / TC;
     const size_t lds_tn = (size_t)2 * 3 * 2 * WK * (TI + TJ) * 16;
-    const size_t lds_nt = (size_t)2 * 3 * 4 * (TR + 2) * 16 + (n.hf.hl ? n.N * 16 : 0) + (n.ff.f0 ? NTS_SEG * 12 : 0);
+    const size_t lds_nt = (size_t)2 * 3 * 4 * (TR + 2) * 16 + (n.hf.hl ? n.N * (n.hf.NH > 4 ? 20 : 16) : 0) + (n.ff.f0 ? NTS_SEG * 12 : 0);
     const size_t lds = lds_tn > lds_nt ? lds_tn : lds_nt;
-    auto kern = n.ff.f0 ? (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, true, FIRST_PENDULUM> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, false, FIRST_PENDULUM>)
-                        : (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, true, FIRST_NONE> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, false, FIRST_NONE>);
+    // (five heads: the maze, whose first layer is no part of these products)
+    auto kern = n.ff.f0 ? (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 4, FIRST_PENDULUM> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 0, FIRST_PENDULUM>)
+              : !t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 0, FIRST_NONE>
+              : t.hf.NH > 4 ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 5, FIRST_NONE> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 4, FIRST_NONE>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(tn + bx * by), dim3(SWG), lds, s, t, n, tn, tiles_j, bx, per);

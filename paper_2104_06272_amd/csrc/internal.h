@@ -302,7 +302,9 @@ inline int split_nt_blocks(const NetShape& n, int M, int l)
     const int tiles = (M + split_nt_rows(n, l) - 1) / split_nt_rows(n, l), per = (tiles + cap - 1) / cap;
     return (tiles + per - 1) / per;
 }
-inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 4 && split_gemm_shape(n, n.L - 1); }
+// the head pass folded into the top layer's products (a pass of its own for the maze's five heads: 128-64, 23920 samples
+// 11.2 + 14.9 us against 18.4 with it folded in; whole steps of mazes of 64 to 512 units 5 to 16 % slower)
+inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 5 && split_gemm_shape(n, n.L - 1); }
 // the pendulum's first-layer gradient can ride in the epilogue of the dX product that forms dZ_1; returns the number of
 // partials that kernel writes (its workgroups along the samples), else 0
 inline int first_fused_splits(const NetShape& n, int env_kind, int M)

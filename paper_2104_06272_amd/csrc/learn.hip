@@ -1190,7 +1190,7 @@ __global__ __launch_bounds__(WG) void adam_reduce_narrow(const AdamArgs a)
 {
     // 64 consecutive parameters per workgroup, 16 shares of the split-K partials (splits w, w + 16, w + 32, ...), four to a
     // wavefront; then the 16 sums are combined in ascending order.  A wavefront has 32 loads in flight and a compute unit
-    // room for eight workgroups, so that even the largest vector that comes here takes little more than one round of them.
+    // room for four workgroups, so that the largest vectors that come here take little more than one round of them, or two.
     __shared__ float red[ADAM_WAVES][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x * 64 + lane;

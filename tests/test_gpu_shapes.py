@@ -229,6 +229,26 @@ def test_every_form_of_the_split_products(gpu, name, hidden, B, T):
     split_products_against_binary64(gpu, name, hidden, B, T)
 
 
+# five heads folded in (the maze's four actions and the value): every pairing of tile widths
+@pytest.mark.parametrize("B,T", SPLIT_BATCHES)
+@pytest.mark.parametrize("hidden", SPLIT_PAIRS)
+def test_five_heads_in_the_split_products(gpu, hidden, B, T):
+    """The update's gradient against binary64 on the stored forward pass, as in test_every_form_of_the_split_products."""
+    cfg = variant("maze_16384", hidden, B, T, "fp32", rows=5, cols=7, max_steps=9)
+    print(f"[five heads] {hidden} {B} x {T}", flush=True)
+    g = gpu.Anakin(cfg, seed=23)
+    theta = g.get_params() + (0.05 * np.random.default_rng(23).standard_normal(g.P)).astype(np.float32)
+    g.set_params(theta)
+    g.rollout()
+    g.learn()
+    tr, got = g.trajectory(), g.get_grads()
+    walls = np.unpackbits(g.get_walls().view(np.uint8), axis=1, bitorder="little")[:, :35].astype(bool)
+    g.close()
+    _, ref = PT.np_maze_backward_from_stored(cfg, theta, walls, (tr["state_s0"][:T] & 0xffff).astype(np.int64), tr["act"], tr["head"][:-1], tr["action"], tr["adv"], tr["ret"])
+    errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in PT.param_regions(cfg)[0]}
+    assert max(errors.values()) <= PT.SPLIT_BOUND, errors
+
+
 # bf16 nets off the bf16 matrix path in the large tiles (few samples: test_bf16_products_off_the_bf16_matrix_path)
 SPLIT_LARGE_BF16 = [("catch_4096", [256, 256]), ("pendulum_8192", [256, 256]), ("catch_4096", [256, 128]), ("pendulum_8192", [128, 256, 128]),
                     ("catch_4096", [128, 128]), ("catch_4096", [128, 64, 256])]
