@@ -85,9 +85,35 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     bf8 wB[2];
     bool live[2];
 #pragma unroll
+    for (int jt = 0; jt < 2; ++jt) live[jt] = jw + 32 * jt + l32 < H;
+    // packed h of this wavefront's tiles (group g of 32-sample tile mt, samples 4kg..4kg+3) and, on the first wavefront, a
+    // row of the head gradient per lane, asked for 64 samples ahead and the first of them ahead of everything else: a
+    // workgroup has two or three such steps, so each load's round trip would be a good part of its time
+    // (128 columns, 32768 samples 12.6 -> 12.0 us)
+    uint2 hq[2][2][4], hn[2][2][4];
+    float dn[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto fetch = [&](int m0) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const size_t G = (size_t)((m0 + 32 * mt) >> 3) + g;
+                    hn[mt][jt][g] = live[jt] ? *reinterpret_cast<const uint2*>(a.hP + (G * H + jw + 32 * jt + l32) * 8 + 4 * kg)
+                                             : make_uint2(0, 0);
+                }
+        if (tid < 64) {
+            const float* dh = a.dhead + (size_t)(m0 + tid) * NHP;
+            const float4 d0 = *reinterpret_cast<const float4*>(dh);
+            dn[0] = d0.x; dn[1] = d0.y; dn[2] = d0.z; dn[3] = d0.w;
+            if (NHP == 8) { const float4 d1 = *reinterpret_cast<const float4*>(dh + 4); dn[4] = d1.x; dn[5] = d1.y; dn[6] = d1.z; dn[7] = d1.w; }
+        }
+    };
+    if (m_begin < m_end) fetch(m_begin);
+#pragma unroll
     for (int jt = 0; jt < 2; ++jt) {
         const int j = jw + 32 * jt + l32;
-        live[jt] = j < H;
         uint16_t w8[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) w8[k] = (live[jt] && k < NH) ? a.wh16[(size_t)j * NH + k] : (uint16_t)0;
@@ -105,25 +131,16 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     reinterpret_cast<uint4*>(Bhl)[tid] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     for (int m0 = m_begin; m0 < m_end; m0 += 64) {
-        // packed h of this wavefront's tiles: group g of 32-sample tile mt, samples 4kg..4kg+3
-        uint2 hq[2][2][4];
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const size_t G = (size_t)((m0 + 32 * mt) >> 3) + g;
-                    hq[mt][jt][g] = live[jt] ? *reinterpret_cast<const uint2*>(a.hP + (G * H + jw + 32 * jt + l32) * 8 + 4 * kg)
-                                             : make_uint2(0, 0);
-                }
+                for (int g = 0; g < 4; ++g) hq[mt][jt][g] = hn[mt][jt][g];
         if (tid < 64) {
-            const float* dh = a.dhead + (size_t)(m0 + tid) * NHP;
             float d[8];
-            const float4 d0 = *reinterpret_cast<const float4*>(dh);
-            d[0] = d0.x; d[1] = d0.y; d[2] = d0.z; d[3] = d0.w;
-            if (NHP == 8) { const float4 d1 = *reinterpret_cast<const float4*>(dh + 4); d[4] = d1.x; d[5] = d1.y; d[6] = d1.z; d[7] = d1.w; }
-            else { d[4] = d[5] = d[6] = d[7] = 0.0f; }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) d[k] = dn[k];
             uint16_t hi[8], lo[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -146,6 +163,7 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
                 Bp[(kgs * 32 + 8 + k) * 8 + q] = lo[k];
             }
         }
+        if (m0 + 64 < m_end) fetch(m0 + 64);
         __syncthreads();
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
@@ -246,7 +264,7 @@ struct GemmNtBf16Args {
 constexpr int NB_BK = 128;
 constexpr int NB_LD = NB_BK + 8;        // row stride in bf16: 272 B, 16-byte aligned, 8 rows spread over all banks
 
-__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a)
+__device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const int block)
 {
     extern __shared__ uint4 smem4[];
     uint16_t* As = reinterpret_cast<uint16_t*>(smem4);          // [128][NB_LD] dY tile
@@ -254,7 +272,7 @@ __global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
     int mt_, it_;
-    xcd_map((int)blockIdx.x, (a.M + 127) / 128, (a.K + 127) / 128, mt_, it_);   // the i-tiles of one m-tile share dY
+    xcd_map(block, (a.M + 127) / 128, (a.K + 127) / 128, mt_, it_);   // the i-tiles of one m-tile share dY
     const int m0 = mt_ * 128, i0 = it_ * 128;
     // loader: 128 rows x 16 pieces of 16 B = 2048 pieces per matrix, 8 per thread
     uint4 ra[8], rb[8];
@@ -267,6 +285,17 @@ __global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a)
         }
     };
     fetch(0);
+    // the ReLU masks: asked for with the first tile (in the epilogue, where they are used, they were a round trip of their own)
+    uint2 hm[2][2][4];
+#pragma unroll
+    for (int tr = 0; tr < 2; ++tr)
+#pragma unroll
+        for (int tc = 0; tc < 2; ++tc)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int m = m0 + wm * 64 + tr * 32 + 8 * g + 4 * kg, i = i0 + wn * 64 + tc * 32 + l32;
+                hm[tr][tc][g] = m < a.M && i < a.K ? *reinterpret_cast<const uint2*>(a.hP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) : make_uint2(0, 0);
+            }
     f16v acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -310,10 +339,8 @@ __global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a)
             for (int g = 0; g < 4; ++g) {
                 const int rowl = wm * 64 + tr * 32 + 8 * g + 4 * kg;          // first of 4 consecutive rows
                 const int m = m0 + rowl;
-                uint2 mask = make_uint2(0, 0);
                 const bool ok = m < a.M && i < a.K;
-                if (ok) mask = *reinterpret_cast<const uint2*>(a.hP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7));
-                const uint32_t mw[2] = {mask.x, mask.y};
+                const uint32_t mw[2] = {hm[tr][tc][g].x, hm[tr][tc][g].y};
                 uint16_t o[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -332,6 +359,7 @@ __global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a)
             *reinterpret_cast<uint4*>(a.dxR + (size_t)(m0 + row) * a.K + i0 + c) = *reinterpret_cast<const uint4*>(Ts + row * NB_LD + c);
     }
 }
+__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body(a, (int)blockIdx.x); }
 
 // ---------------------------------------------------------------------------
 // The same product as a persistent workgroup with the weights in registers: wavefront w of eight
@@ -604,16 +632,15 @@ __device__ __forceinline__ uint4 obs_piece(const ObsSrc& o, int mg, int i, bool 
 }
 
 template <bool OBS>
-__global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a)
+__device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const int tile, const int split)
 {
     extern __shared__ uint4 smem4[];
     uint4* Xs = smem4;                       // [TB_G][128] pieces of 8 samples
     uint4* Ys = Xs + TB_G * 128;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
-    const int ti = blockIdx.x % a.tiles_i, tj = blockIdx.x / a.tiles_i;
+    const int ti = tile % a.tiles_i, tj = tile / a.tiles_i;
     const int i0 = ti * 128, j0 = tj * 128;
-    const int split = blockIdx.y;
     const int g_begin = (split * a.rows) >> 3;
     const int g_end = (split + 1) * a.rows < a.M ? g_begin + (a.rows >> 3) : a.M >> 3;
     // loader: TB_G groups x 128 columns = 2048 pieces per matrix, 8 per thread: piece p -> group p/128, column p%128
@@ -682,6 +709,18 @@ __global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a)
             }
     }
     if (ti == 0 && a.bias_out && tid < 128 && j0 + tid < a.N) a.bias_out[(size_t)split * a.bias_stride + j0 + tid] = bsum;
+}
+template <bool OBS>
+__global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a) { gemm_tn_bf16_body<OBS>(a, (int)blockIdx.x, (int)blockIdx.y); }
+
+// Both products of a layer that takes the 128-wide tiles, dW workgroups first.  They read the same dZ and neither fills the
+// chip for long: as two launches one after the other they were mostly their own beginnings and ends (128-128, 32768 samples
+// 9.8 + 11.2 -> 14.0 us).
+__global__ __launch_bounds__(WG) void gemm_tn_nt_bf16(const GemmTnBf16Args t, const GemmNtBf16Args n, const int tiles, const int tn_blocks)
+{
+    const int b = (int)blockIdx.x;
+    if (b < tn_blocks) gemm_tn_bf16_body<false>(t, b % tiles, b / tiles);
+    else gemm_nt_bf16_body(n, b - tn_blocks);
 }
 
 // The same product with a 256 x 256 tile and eight wavefronts (two per SIMD, so one's LDS and
@@ -1345,7 +1384,9 @@ hipError_t launch_backward_bf16(anakin* h)
             ProfScope prof(h, "gemm_tn_top");
             hipLaunchKernelGGL(gemm_tn_bf16_top, dim3(u.tiles_i * (u.N / 256) * u.splits), dim3(BIGWG), lds, h->stream, u);
             if ((e = hipGetLastError()) != hipSuccess) return e;
-        } else if ((e = run_tn(t, big, l == 0 ? "gemm_tn_obs" : "gemm_tn")) != hipSuccess) return e;
+        }
+        const bool both = l > 0 && !big && !(l == n.L - 1 && top_fused) && !bf16_dx_resident(n, M, l);   // one launch for both products
+        if (!(l == n.L - 1 && top_fused) && !both && (e = run_tn(t, big, l == 0 ? "gemm_tn_obs" : "gemm_tn")) != hipSuccess) return e;
         if (l > 0) {
             GemmNtBf16Args g;
             g.M = M; g.K = n.dims[l]; g.N = n.dims[l + 1];
@@ -1356,8 +1397,15 @@ hipError_t launch_backward_bf16(anakin* h)
             g.dxR = needs_rows(l - 1) ? dzR(l - 1) : nullptr;
             g.dxP = dzP(l - 1);
             const int rows_per_block = bf16_dx_rows_per_workgroup(g.M, g.K, g.N);
-            ProfScope prof(h, "gemm_nt_mask");
-            if (bf16_dx_resident(n, M, l)) {
+            ProfScope prof(h, both ? "gemm_tn_nt" : "gemm_nt_mask");
+            if (both) {
+                t.tiles_i = (t.K + 127) / 128;
+                const int tiles = t.tiles_i * ((t.N + 127) / 128), tn = tiles * t.splits;
+                const size_t lds_t = (size_t)2 * TB_G * 128 * sizeof(uint4), lds_n = (size_t)2 * 128 * NB_LD * sizeof(uint16_t), lds2 = lds_t > lds_n ? lds_t : lds_n;
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+                if (e != hipSuccess) return e;
+                hipLaunchKernelGGL(gemm_tn_nt_bf16, dim3(tn + ((g.M + 127) / 128) * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
+            } else if (bf16_dx_resident(n, M, l)) {
                 const size_t lds2 = (size_t)2 * NRES_RT * (g.N + 8) * sizeof(uint16_t);
                 const bool top = l == n.L - 1 && top_fused;      // dZ_L comes out of the head gradient inside the kernel
                 g.maskTop = at<const uint32_t>(h, L.mask[l]); g.dhead = at<const float>(h, L.dhead);
