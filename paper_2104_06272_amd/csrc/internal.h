@@ -320,6 +320,8 @@ hipError_t launch_pinned(anakin* h, const RolloutArgs& args);
 int rollout_resident_width(const NetShape& net);
 bool replay_resident_ok(const anakin* h, int samples);
 hipError_t launch_replay_resident(anakin* h, const RolloutArgs& a, int samples);
+bool rollout_small_ok(const anakin* h);
+hipError_t launch_small(anakin* h, const RolloutArgs& args);
 int rollout_wide_groups(const NetShape& net, const EnvDims& env, int B);
 hipError_t launch_wide(anakin* h, const RolloutArgs& args);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);

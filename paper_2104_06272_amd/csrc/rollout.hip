@@ -1219,7 +1219,7 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
     }
 }
 
-// The same for 64-wide layers, four wavefronts and 16 environments: there a step is latency only (the layer on the matrix
+// The same for 64-wide layers, four wavefronts and 16 environments (batches beyond rollout_small_ok): there a step is latency only (the layer on the matrix
 // cores 1.0 k cycles, heads 0.8 k, sample and step 1.1 k of 3.5 k), and fewer wavefronts with everything they store where
 // they compute it are quicker than the form above: 34 us against 40 us for T = 20, Catch, 64 environments.
 template <int KS, int NT>
@@ -1836,6 +1836,11 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a, bool beside = 
     // 256-256, T = 16: 256 environments 130 -> 101 us, 512 129.5 -> 119.5, but 1024 130.5 -> 171.6 on all units; 256-512:
     // 247 -> 144, 246 -> 181, 246 -> 248).
     if (!REPLAY && h->wide > 0 && (!beside || h->B / (4 * h->wide) <= 128) && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_wide(h, a);
+    // Beside the learner of a small board net a few of its workgroups cost more than they save (decoupled Catch, T = 20: 512
+    // environments 57.6 -> 59.2 us, 1024 66.4 -> 67.9, but 2048 83.6 -> 82.1, 4096 110.2 -> 104.3; pendulum 1024 71.0 -> 64.1,
+    // 4096 102.8 -> 96.7).
+    if (!REPLAY && rollout_small_ok(h) && (!beside || h->env.kind == ENV_PENDULUM || h->B > 1024) && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)))
+        return launch_small(h, a);
     if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
         switch (h->env.kind) {

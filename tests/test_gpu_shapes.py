@@ -306,6 +306,31 @@ def test_pinned_and_streamed_matrices_give_the_same_unroll(gpu, name, hidden, B)
         np.testing.assert_array_equal(x, y)
 
 
+# two layers of 64: a wavefront per four environments up to 4096 of them, boards with the smallest and largest first layer
+@pytest.mark.parametrize("name,B,env", [
+    ("catch_4096", 16, dict(rows=2, cols=1, max_steps=1)), ("catch_4096", 4096, {}), ("catch_4096", 4112, {}),
+    ("catch_4096", 48, dict(rows=32, cols=19, max_steps=31)), ("catch_4096", 48, dict(rows=32, cols=20, max_steps=31)),   # W1 fits LDS, and does not
+    ("pendulum_8192", 16, dict(max_steps=3)), ("pendulum_8192", 4096, dict(max_steps=5)),
+    ("maze_16384", 16, dict(rows=2, cols=2, max_steps=4)), ("maze_16384", 4096, dict(rows=16, cols=16, max_steps=5)), ("maze_16384", 80, dict(rows=5, cols=13, max_steps=7)),
+])
+def test_two_layers_of_64_give_the_same_bits_as_streamed(gpu, name, B, env):
+    cfg = variant(name, [64, 64], B, 7, "fp32", **env)
+    print(f"[64-64] {name} B={B} {env}", flush=True)
+    runs = []
+    for mode in (0, gpu.MODE_STREAM_WEIGHTS):
+        g = gpu.Anakin(cfg, seed=21)
+        g.set_mode(mode)
+        g.rollout(); g.rollout()
+        runs.append((g.trajectory(), g.get_env_state()))
+        g.close()
+    (a, sa), (b, sb) = runs
+    for key in ("state_s0", "reward", "done", "value", "head", "act") + (("state_f0", "state_f1", "eps", "action_f") if name.startswith("pendulum") else ("action",)):
+        for x, y in zip(a[key], b[key]):
+            np.testing.assert_array_equal(x, y, err_msg=key)
+    for x, y in zip(sa, sb):
+        np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("name,hidden,B,env", [
     ("catch_4096", [128, 128], 64, {}),
     ("pendulum_8192", [128], 64, {}),                        # no matrix between hidden layers
