@@ -1185,18 +1185,21 @@ __global__ __launch_bounds__(ADAM_WAVES * 64) void adam_reduce(const AdamArgs a)
 // 10.5).  What bounds it is the round trips to memory of a workgroup and how many rounds of workgroups there are: with 16
 // wavefronts per workgroup, four loads in flight each and the moments asked for behind the sum, 79876 parameters with 128
 // partials took 13.6 us, now 11.4; 158468 with 126 16.3 and 11.5; 67587 10.3 and 8.8; 17411 unchanged at 4.9 and
-// (bf16) 6.3.  (The moments beside the partials in adam_reduce as well: 58.5 -> 63.5 us on the maze's 921605 parameters.)
-__global__ __launch_bounds__(WG) void adam_reduce_narrow(const AdamArgs a)
+// (bf16) 6.3.  Vectors of less than a workgroup per unit keep a share to a wavefront: 1764 parameters with 512 partials 5.3 us,
+// 6.4 with four shares.  (The moments beside the partials in adam_reduce as well: 58.5 -> 63.5 us on the maze's 921605 parameters.)
+template <int SH>
+__global__ __launch_bounds__(ADAM_WAVES * 64 / SH) void adam_reduce_narrow(const AdamArgs a)
 {
-    // 64 consecutive parameters per workgroup, 16 shares of the split-K partials (splits w, w + 16, w + 32, ...), four to a
-    // wavefront; then the 16 sums are combined in ascending order.  A wavefront has 32 loads in flight and a compute unit
+    // 64 consecutive parameters per workgroup, 16 shares of the split-K partials (splits w, w + 16, w + 32, ...), SH to a
+    // wavefront; then the 16 sums are combined in ascending order.  With four a wavefront has 32 loads in flight and a unit
     // room for four workgroups, so that the largest vectors that come here take little more than one round of them, or two.
     __shared__ float red[ADAM_WAVES][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x * 64 + lane;
     const bool ok = i < a.P;
-    constexpr int SH = ADAM_WAVES * 64 / WG;
-    float g[SH] = {0.0f, 0.0f, 0.0f, 0.0f}, mo = 0.0f, vo = 0.0f, to = 0.0f;
+    float g[SH], mo = 0.0f, vo = 0.0f, to = 0.0f;
+#pragma unroll
+    for (int h = 0; h < SH; ++h) g[h] = 0.0f;
     if (ok) {
         // the wavefront that takes the step has its parameters and moments under way beside the partials (asked for behind
         // the sum, they were a second memory round trip of every workgroup)
@@ -1296,7 +1299,8 @@ static void launch_adam_kernel(const AdamArgs& a, hipStream_t s)
     for (int r = 0; r < a.n_regions; ++r) max_splits = a.reg[r].splits > max_splits ? a.reg[r].splits : max_splits;
     if (max_splits <= 16 && a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce_flat, dim3((a.P + 4 * WG - 1) / (4 * WG)), dim3(WG), 0, s, a);
     else if (a.P >= (1 << 18)) hipLaunchKernelGGL(adam_reduce, dim3((a.P + 255) / 256), dim3(ADAM_WAVES * 64), 0, s, a);
-    else hipLaunchKernelGGL(adam_reduce_narrow, dim3((a.P + 63) / 64), dim3(WG), 0, s, a);
+    else if (a.P < 64 * 256) hipLaunchKernelGGL(adam_reduce_narrow<1>, dim3((a.P + 63) / 64), dim3(ADAM_WAVES * 64), 0, s, a);   // less than a workgroup per unit
+    else hipLaunchKernelGGL(adam_reduce_narrow<4>, dim3((a.P + 63) / 64), dim3(ADAM_WAVES * 64 / 4), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -1469,30 +1469,31 @@ __global__ __launch_bounds__(WG) void rollout_resident64_kernel(const RolloutArg
 // numbers, samples, steps and records -- no exchange between lanes, so no barrier inside the
 // time loop, and every vector instruction works for 64 envs.  The arithmetic per env is the
 // same canonical chain as in rollout_kernel.  No hidden activations are kept: the update of
-// such nets rebuilds the layer from the state.
+// such nets rebuilds the layer from the state.  Bound by what the wavefronts issue.  Catch 10 x 5, 32 units, 262144
+// environments, T = 16: 72.8 us with the heads as multiply-adds on operands from LDS, 55.9 on the matrix instruction and
+// with four wavefronts per SIMD.
 // ---------------------------------------------------------------------------
 template <int ENV, int H, bool REPLAY>
-__global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
+__global__ __launch_bounds__(WG, H == 32 ? 4 : 2) void rollout_lane_kernel(const RolloutArgs a)
 {
     constexpr int LDW = H + 4;                                    // row stride of W1 in LDS
     extern __shared__ float4 smem4[];
     float* w1s = reinterpret_cast<float*>(smem4);                 // [D][LDW]
-    const int D = a.net.dims[0], NH = a.net.NH, NHP = a.net.NHP;
+    constexpr int NH = ENV == ENV_CATCH ? 4 : 3, NHP = 4;          // actions, or mean and deviation, and the value
+    const int D = a.net.dims[0];
     float* b1s = w1s + D * LDW;                                   // [H]
-    float* whs = b1s + H;                                         // [H][8] head weights, k-major, columns >= NH zero
-    float* bhs = whs + H * 8;                                     // [8]
+    float* whs = b1s + H;                                         // [H][4] head weights, k-major, columns >= NH zero
     const int tid = threadIdx.x;
     // the parameters come into LDS in batches of eight loads per thread: one load, one wait, one store at a time
     // would be a memory round trip per KB
     {
         const float vb1 = a.theta[a.net.b_off[0] + (tid < H ? tid : 0)];
-        const float vbh = a.theta[a.net.bh_off + (tid < NH ? tid : 0)];
-        constexpr int NW = (H * 8 + WG - 1) / WG;
+        constexpr int NW = (H * 4 + WG - 1) / WG;
         float vwh[NW];
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
-            const int i = q * WG + tid, k = i >> 3, j = i & 7;
-            vwh[q] = a.theta[a.net.wh_off + ((i < H * 8 && j < NH) ? k * NH + j : 0)];
+            const int i = q * WG + tid, k = i >> 2, j = i & 3;
+            vwh[q] = a.theta[a.net.wh_off + ((i < H * 4 && j < NH) ? k * NH + j : 0)];
         }
         const float* w1g = a.theta + a.net.w_off[0];
         const int n = D * H;
@@ -1504,11 +1505,10 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
             for (int q = 0; q < 8; ++q) { const int i = i0 + q * WG + tid; if (i < n) w1s[(i / H) * LDW + i % H] = pw[q]; }
         }
         if (tid < H) b1s[tid] = vb1;
-        if (tid < 8) bhs[tid] = tid < NH ? vbh : 0.0f;
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
-            const int i = q * WG + tid, j = i & 7;
-            if (i < H * 8) whs[i] = j < NH ? vwh[q] : 0.0f;
+            const int i = q * WG + tid, j = i & 3;
+            if (i < H * 4) whs[i] = j < NH ? vwh[q] : 0.0f;
         }
     }
     __syncthreads();
@@ -1517,6 +1517,12 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
     const int b = blockIdx.x * WG + tid;
     if (b >= B) return;
     const TrajPtrs& tp = a.tp;
+    float wh[H];                                                  // head weights of this lane's head, tid % 4
+#pragma unroll
+    for (int k = 0; k < H; ++k) wh[k] = whs[4 * k + (tid & 3)];
+    f4v bh;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bh[j] = j < NH ? a.theta[a.net.bh_off + j] : 0.0f;
     EnvState st{0u, 0.0f, 0.0f};
     if (!REPLAY) {
         st.s0 = tp.s0[b];
@@ -1565,27 +1571,14 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
                 h[j] = v[0]; h[j + 1] = v[1]; h[j + 2] = v[2]; h[j + 3] = v[3];
             }
         }
-        // ---- heads: NH chains over k, ascending --------------------------------
-        float hv[8];
+        // ---- heads: NH chains over k, ascending.  v_mfma_f32_4x4x1 multiplies the heads (rows, lane % 4) with four lanes'
+        // environments (columns): register r of a lane is head r of its own environment, one instruction of eight cycles
+        // an input where four multiply-adds took sixteen and an LDS read ----
+        f4v hv = bh;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) hv[j] = bhs[j];
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-            const float x = h[k] > 0.0f ? h[k] : 0.0f;
-            const float4 wa = ld4(whs + k * 8);
-            hv[0] = fmaf(x, wa.x, hv[0]); hv[1] = fmaf(x, wa.y, hv[1]);
-            hv[2] = fmaf(x, wa.z, hv[2]); hv[3] = fmaf(x, wa.w, hv[3]);
-            if (NHP == 8) {
-                const float4 wb = ld4(whs + k * 8 + 4);
-                hv[4] = fmaf(x, wb.x, hv[4]); hv[5] = fmaf(x, wb.y, hv[5]);
-                hv[6] = fmaf(x, wb.z, hv[6]); hv[7] = fmaf(x, wb.w, hv[7]);
-            }
-        }
-        float* hd = tp.tr_head + tb * NHP;
-        *reinterpret_cast<float4*>(hd) = make_float4(hv[0], hv[1], hv[2], hv[3]);
-        if (NHP == 8) *reinterpret_cast<float4*>(hd + 4) = make_float4(hv[4], hv[5], hv[6], hv[7]);
-        const float val = last_head(hv[0], hv[1], hv[2], hv[3], hv[4], hv[5], hv[6], hv[7], NH);
-        tp.tr_val[tb] = val;
+        for (int k = 0; k < H; ++k) hv = __builtin_amdgcn_mfma_f32_4x4x1f32(wh[k], h[k] > 0.0f ? h[k] : 0.0f, hv, 0, 0, 0);
+        *reinterpret_cast<f4v*>(tp.tr_head + tb * NHP) = hv;
+        tp.tr_val[tb] = hv[NH - 1];
         if (!REPLAY && t < T) {
             float r; int done;
             if (ENV == ENV_PENDULUM) {
@@ -1599,7 +1592,7 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
                     pendulum_reset(st, wr.x, wr.y);
                 }
             } else {
-                const int act = sample_categorical_any(hv[0], hv[1], hv[2], hv[3], hv[4], hv[5], hv[6], hv[7], a.net.A, u01(dr.x));
+                const int act = sample_categorical_any(hv[0], hv[1], hv[2], 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 3, u01(dr.x));
                 tp.tr_act[tb] = (uint8_t)act;
                 catch_step(a.env, st, act, 0u, r, done);
                 if (done) {
@@ -1619,23 +1612,22 @@ __global__ __launch_bounds__(WG) void rollout_lane_kernel(const RolloutArgs a)
 
 // One-hidden-layer nets the lane kernel takes: width 32 or 64 on Catch or the pendulum, fp32, no kept activations -- and
 // enough environments that a lane each fills the chip; with fewer a row of 16 lanes per environment (rollout_one.hip) is
-// done sooner.  T = 16, a lane against 16 lanes, Catch 10 x 5 (5 x 4 differs by less than 2 us) and the pendulum: width 32,
-// 8192 environments 30 us against 18, 42 against 22; 24576 32 against 30, 43 against 43; 32768 32 against 36, 44 against 51;
-// 262144 65 against 214, 90 against 305.  Width 64: 32768 59 against 47, 73 against 62; 49152 59 against 66, 73 against 85;
-// 262144 216 against 286, 272 against 377.
+// done sooner.  T = 16, a lane against 16 lanes, Catch 10 x 5 and the pendulum: width 32, 8192 environments 23.6 us against
+// 16.5, 33.5 against 20.6; 16384 24.1 against 23.3, 35.2 against 29.4; 24576 24.7 against 29.8, 38.0 against 41.4.  Width 64:
+// 16384 36.8 against 27.2, 48.3 against 34.6; 32768 37.6 against 46.4, 50.1 against 62.2.
 static int rollout_lane_width(const anakin* h)
 {
     const NetShape& n = h->net;
     if (n.bf16 || n.L != 1 || h->env.kind == ENV_MAZE || !one_layer_fused(h)) return 0;
     if (h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)) return 0;
-    if ((n.dims[1] == 32 && h->B >= 32768) || (n.dims[1] == 64 && h->B >= 49152)) return n.dims[1];
+    if ((n.dims[1] == 32 && h->B >= 24576) || (n.dims[1] == 64 && h->B >= 32768)) return n.dims[1];
     return 0;
 }
 
 template <int ENV, int H, bool REPLAY>
 static hipError_t launch_lane(anakin* h, const RolloutArgs& a)
 {
-    const size_t lds = ((size_t)h->net.dims[0] * (H + 4) + H + H * 8 + 8) * 4;
+    const size_t lds = ((size_t)h->net.dims[0] * (H + 4) + H + H * 4) * 4;
     ProfScope prof(h, REPLAY ? "replay_forward" : "rollout");
     hipLaunchKernelGGL((rollout_lane_kernel<ENV, H, REPLAY>), dim3((h->B + WG - 1) / WG), dim3(WG), lds, h->stream, a);
     return hipGetLastError();

@@ -378,6 +378,11 @@ def test_bf16_pinned_and_streamed_matrices_give_the_same_update(gpu, name, hidde
     ("maze_16384", [64], 48, "bf16", {}),
     ("maze_16384", [128], 4112, "fp32", dict(rows=9, cols=13, max_steps=64)),
     ("maze_16384", [256], 16, "bf16", dict(rows=16, cols=16, max_steps=64, p_wall=0.3)),
+    # from here a lane per environment: the smallest batch of each width, last workgroups and wavefronts part filled
+    ("catch_4096", [32], 24576, "fp32", dict(rows=2, cols=1, max_steps=1)),
+    ("catch_4096", [64], 32784, "fp32", dict(rows=16, cols=12, max_steps=15)),
+    ("pendulum_8192", [32], 24608, "fp32", {}),
+    ("pendulum_8192", [64], 32768, "fp32", {}),
     # bf16 nets that the bf16 matrix path does not take, on the fp32 matrix instruction
     ("catch_4096", [128, 128], 48, "bf16", {}),
     ("catch_4096", [256, 512], 80, "bf16", dict(rows=16, cols=12, max_steps=15)),  # streamed, first-layer rows from memory
