@@ -815,7 +815,10 @@ __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
 //   B   lane = (hidden unit, half): each half-wavefront walks every other sample of the chunk:
 //       h = relu(b1 + W1[ball] + W1[paddle]) in the acting order, dZ1, the head-matrix sums, and
 //       the scatter of dZ1 into the two rows of its own LDS copy of dW1
-// All waves run the same trip counts, so workgroup barriers separate A2 from B.
+// A2 and B exchange through the wavefront's own LDS, so no barrier stands between them.  Catch 10 x 5, 262144 environments,
+// T = 16: 150 us (155 with a bias sum of its own, the bias added per sample and word offsets); 47 of them are A1 and A2, the
+// rest the walk's LDS reads and writes: half the vector instructions, with the head products on the matrix instruction, took
+// 148, two samples per LDS round trip 148, 16 lanes of two units per row 172, the paddle's row by matrix instruction 161.
 // ---------------------------------------------------------------------------
 struct CatchFusedArgs {
     int B, T, D, envs_per_wg;
@@ -832,6 +835,14 @@ struct CatchFusedArgs {
 constexpr int CF_WG = 256;              // four wavefronts
 constexpr int CF_H = 32;                // hidden units
 constexpr int CF_TC = 4;                // time steps per chunk of phases A2 / B
+
+// LDS between the lanes of one wavefront: its accesses are carried out in order, only the compiler has to keep that order
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs a)
 {
@@ -864,12 +875,15 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
     float wh[4], dwh[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 4; ++k) wh[k] = a.theta[a.wh_off + u * 4 + k];
-    const float b1 = a.theta[a.b1_off + u];
-    float db1 = 0.0f;
-    float* mine = acc + (size_t)hf * D * H + u;
-    const float* w1c = w1s + u;
+    const uint32_t w_at = (uint32_t)u * 4;                       // LDS byte offsets of this lane's column of W1 and of its sums
+    const uint32_t m_at = (uint32_t)(acc - lds + hf * D * H + u) * 4;
+    auto word = [&](uint32_t at) -> float& { return *reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + at); };
     // phase A identity: env e of the wavefront's block; sums of the loss terms and of the head gradients
     float dbh[4] = {0, 0, 0, 0}, sums[5] = {0, 0, 0, 0, 0};
+    __syncthreads();
+    // the bias joins the rows of the cells a ball can be in (the paddle's row is the last, and the ball is never in it):
+    // b1 + W1[ball] is the first sum of the acting order
+    for (int i = tid; i < (D - a.env.cols) * H; i += CF_WG) w1s[i] = a.theta[a.b1_off + (i & (H - 1))] + w1s[i];
     __syncthreads();
     const float oml = 1.0f - a.lambda;
     const int wg_b0 = blockIdx.x * a.envs_per_wg;
@@ -932,10 +946,10 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
                     dh[tt * 64 + lane] = make_float4(d[0], d[1], d[2], d[3]);
                     int bc, pc;
                     catch_obs_cells(a.env, in_s0[tt], bc, pc);
-                    cells[tt * 64 + lane] = (uint32_t)(bc * H) | ((uint32_t)(pc * H) << 16);
+                    cells[tt * 64 + lane] = (uint32_t)(bc * H * 4) | ((uint32_t)(pc * H * 4) << 16);
                 }
             }
-            __syncthreads();
+            wave_fence();
             if (t0 + CF_TC < T) fetch_chunk(t0 + CF_TC);
             // ---- B: half hf takes samples hf, hf + 2, ... of the chunk's tn * 64 ----
             const int ns = tn * 64;
@@ -947,30 +961,29 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
                 for (int q = 0; q < RB; ++q) { dd[q] = dh[s0 + 2 * q + hf]; cc[q] = cells[s0 + 2 * q + hf]; }
                 float w0[RB], w1[RB];
 #pragma unroll
-                for (int q = 0; q < RB; ++q) { w0[q] = w1c[cc[q] & 0xffffu]; w1[q] = w1c[cc[q] >> 16]; }
+                for (int q = 0; q < RB; ++q) { w0[q] = word(w_at + (cc[q] & 0xffffu)); w1[q] = word(w_at + (cc[q] >> 16)); }
 #pragma unroll
                 for (int q = 0; q < RB; ++q) {
                     const float d[4] = {dd[q].x, dd[q].y, dd[q].z, dd[q].w};
-                    float hv = (b1 + w0[q]) + w1[q];
+                    float hv = w0[q] + w1[q];
                     hv = hv > 0.0f ? hv : 0.0f;
                     float s = 0.0f;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) { s = fmaf(wh[k], d[k], s); dwh[k] = fmaf(hv, d[k], dwh[k]); }
                     const float dz = hv > 0.0f ? s : 0.0f;
-                    db1 += dz;
                     // the ball is never in the paddle's row, so the two sums are different words: both reads go out
                     // before either store, one LDS round trip per sample instead of two (two samples per round
                     // trip, with the second taking the first's result where they share a word, measured slower)
-                    float* pa = mine + (cc[q] & 0xffffu);
-                    float* pb = mine + (cc[q] >> 16);
-                    const float xa = *pa, xb = *pb;
-                    *pa = xa + dz;
-                    *pb = xb + dz;
+                    float &pa = word(m_at + (cc[q] & 0xffffu)), &pb = word(m_at + (cc[q] >> 16));
+                    const float xa = pa, xb = pb;
+                    pa = xa + dz;
+                    pb = xb + dz;
                 }
             }
-            __syncthreads();
+            wave_fence();
         }
     }
+    __syncthreads();
     // ---- sums of the workgroup, in a fixed order: wavefronts ascending, half 0 before half 1 ----
     // every wavefront's dW1 copies are complete (barrier above); the per-lane sums go through the wavefront's
     // head-gradient area, free now: 16 floats per lane
@@ -980,25 +993,27 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
         float* r = red_of(wave, lane);
 #pragma unroll
         for (int k = 0; k < 4; ++k) { r[k] = dwh[k]; r[4 + k] = dbh[k]; }
-        r[8] = db1;
 #pragma unroll
-        for (int k = 0; k < 5; ++k) r[9 + k] = sums[k];
+        for (int k = 0; k < 5; ++k) r[8 + k] = sums[k];
     }
     __syncthreads();
     float* out0 = a.partial0 + (size_t)blockIdx.x * ((size_t)D * H + H);
     float* out1 = a.partial1 + (size_t)blockIdx.x * ((size_t)H * 4 + 4);
-    const float* acc_all = w1s + D * H;                          // wavefront w at stride ws
+    float* acc_all = w1s + D * H;                                // wavefront w at stride ws
     for (int i = tid; i < D * H; i += CF_WG) {
         float sum = 0.0f;
         for (int w = 0; w < 4; ++w) { sum += acc_all[w * ws + i]; sum += acc_all[w * ws + D * H + i]; }
         out0[i] = sum;
+        if (i >= (D - a.env.cols) * H) acc_all[i] = sum;         // this thread's word alone
     }
+    __syncthreads();
     if (tid < H) {
+        // every sample has its paddle in one cell of the last row, so the bias gradient is the sum of that row's cells
         float sb = 0.0f, sw[4] = {0, 0, 0, 0};
+        for (int c = D - a.env.cols; c < D; ++c) sb += acc_all[c * H + tid];
         for (int w = 0; w < 4; ++w)
             for (int hh = 0; hh < 2; ++hh) {
                 const float* r = red_of(w, hh * 32 + tid);
-                sb += r[8];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) sw[k] += r[k];
             }
@@ -1008,7 +1023,7 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
     }
     if (tid < 9) {
         // dbh[0..3] and the five metric sums: over all 256 lanes (envs), ascending
-        const int off = tid < 4 ? 4 + tid : 9 + (tid - 4);
+        const int off = tid < 4 ? 4 + tid : 8 + (tid - 4);
         float sum = 0.0f;
         for (int l = 0; l < CF_WG; ++l) sum += red_of(l >> 6, l & 63)[off];
         if (tid < 4) out1[(size_t)H * 4 + tid] = sum;
@@ -1023,7 +1038,7 @@ bool catch_fused_ok(const anakin* h)
     const NetShape& n = h->net;
     return one_layer_fused(h) && h->env.kind == ENV_CATCH && h->env.rows >= 2 && n.dims[1] == CF_H && n.NH == 4 && h->n_updates == 1 &&
            !h->traj_decoupled && !h->pathwise && h->splits[0] > 0 && h->B % (h->splits[0] * CF_WG) == 0 &&
-           n.dims[0] * CF_H < 65536 && n.w_off[0] % 4 == 0;           // board-cell offsets are packed into 16 bits; W1 is read 16 bytes at a time
+           n.dims[0] * CF_H * 4 < 65536 && n.w_off[0] % 4 == 0;           // board-cell offsets are packed into 16 bits; W1 is read 16 bytes at a time
 }
 
 hipError_t launch_learn_catch_fused(anakin* h)

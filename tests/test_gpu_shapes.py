@@ -70,6 +70,13 @@ def test_one_layer_many_samples(gpu, orc, name, hidden, B, T):
     lockstep(gpu, orc, variant(name, [hidden], B, T), 3)
 
 
+# 32 units on Catch, the update in one launch: boards of two cells and of the most that fit, time steps that end inside
+# a chunk of four, one block of 256 environments and several; the bias gradient is the paddle's row added up
+@pytest.mark.parametrize("rows,cols,B,T", [(2, 1, 256, 1), (17, 6, 512, 7), (2, 51, 256, 5), (6, 8, 768, 4)])
+def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
+    lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 3)
+
+
 # a first layer of 32 units below a wider one, with batches that fill tiles of 16 environments
 @pytest.mark.parametrize("name,hidden,B", [("pendulum_8192", [32, 64], 320), ("catch_small", [32, 512], 64)])
 def test_narrow_first_layer(gpu, orc, name, hidden, B):
