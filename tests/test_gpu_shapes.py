@@ -77,6 +77,13 @@ def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 3)
 
 
+# 64-64 on Catch, the whole update in one launch: 1 to 112 samples per workgroup, ends on and off its tiles of 16, time
+# steps in every remainder of the scan's batches, boards of 2 to 64 cells
+@pytest.mark.parametrize("rows,cols,B,T", [(2, 1, 16, 1), (8, 8, 16, 16), (10, 5, 16, 17), (9, 7, 64, 28), (5, 3, 80, 7), (4, 16, 48, 37), (3, 11, 16, 111)])
+def test_small_update_in_one_launch(gpu, orc, rows, cols, B, T):
+    lockstep(gpu, orc, variant("catch_small", [64, 64], B, T, rows=rows, cols=cols, max_steps=rows - 1), 5)
+
+
 # a first layer of 32 units below a wider one, with batches that fill tiles of 16 environments
 @pytest.mark.parametrize("name,hidden,B", [("pendulum_8192", [32, 64], 320), ("catch_small", [32, 512], 64)])
 def test_narrow_first_layer(gpu, orc, name, hidden, B):
