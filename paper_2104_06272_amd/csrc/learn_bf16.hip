@@ -72,15 +72,18 @@ __device__ __forceinline__ uint32_t positive_mask_pk(uint32_t w)
     return r;
 }
 
+// SPLIT: at most 128 columns, which two wavefronts have; the other two take the second 32 samples of a step instead of columns
+// that do not exist (128 columns, 32768 samples 12.2 -> 10.0 us; the products of a step with their stores are two thirds of it)
+template <bool SPLIT>
 __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a)
 {
-    constexpr int LDT = WG + 8;
+    constexpr int LDT = WG + 8, MTS = SPLIT ? 1 : 2;                    // 32-sample tiles of a step that a wavefront has
     __shared__ __attribute__((aligned(16))) uint16_t tile[64 * LDT];   // [64 samples][256 columns] for the row-major copy
     __shared__ uint4 Ahl[2][64];                                       // dZ product, A operand per 32-sample tile
     __shared__ uint4 Bhl[2][2][64];                                    // dWh product, B operand per 32-sample tile and 16-sample step
     const int H = a.H, NH = a.NH, NHP = a.NHP;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
-    const int jb = blockIdx.y * WG, jw = jb + wave * 64;
+    const int jb = blockIdx.y * WG, cw = SPLIT ? wave & 1 : wave, mt0 = SPLIT ? wave >> 1 : 0, jw = jb + cw * 64;
     const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
     bf8 wB[2];
     bool live[2];
@@ -90,16 +93,16 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     // row of the head gradient per lane, asked for 64 samples ahead and the first of them ahead of everything else: a
     // workgroup has two or three such steps, so each load's round trip would be a good part of its time
     // (128 columns, 32768 samples 12.6 -> 12.0 us)
-    uint2 hq[2][2][4], hn[2][2][4];
+    uint2 hq[MTS][2][4], hn[MTS][2][4];
     float dn[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto fetch = [&](int m0) {
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MTS; ++mt)
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const size_t G = (size_t)((m0 + 32 * mt) >> 3) + g;
+                    const size_t G = (size_t)((m0 + 32 * (mt0 + mt)) >> 3) + g;
                     hn[mt][jt][g] = live[jt] ? *reinterpret_cast<const uint2*>(a.hP + (G * H + jw + 32 * jt + l32) * 8 + 4 * kg)
                                              : make_uint2(0, 0);
                 }
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     __syncthreads();
     for (int m0 = m_begin; m0 < m_end; m0 += 64) {
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MTS; ++mt)
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
@@ -166,10 +169,10 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
         if (m0 + 64 < m_end) fetch(m0 + 64);
         __syncthreads();
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const uint4 a1v = Ahl[mt][lane];
+        for (int mt = 0; mt < MTS; ++mt) {
+            const uint4 a1v = Ahl[mt0 + mt][lane];
             const bf8 a1 = *reinterpret_cast<const bf8*>(&a1v);
-            const uint4 b20v = Bhl[mt][0][lane], b21v = Bhl[mt][1][lane];
+            const uint4 b20v = Bhl[mt0 + mt][0][lane], b21v = Bhl[mt0 + mt][1][lane];
             const bf8 b20 = *reinterpret_cast<const bf8*>(&b20v), b21 = *reinterpret_cast<const bf8*>(&b21v);
 #pragma unroll
             for (int jt = 0; jt < 2; ++jt) {
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc1[r] = 0.0f;
                 acc1 = mfma_bf16(a1, wB[jt], acc1);
-                const int col = wave * 64 + 32 * jt + l32;
+                const int col = cw * 64 + 32 * jt + l32;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const uint32_t mw[2] = {hq[mt][jt][g].x, hq[mt][jt][g].y};
@@ -192,13 +195,13 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
                         o[q] = hv > 0.0f ? acc1[4 * g + q] : 0.0f;
                     }
                     const uint32_t p01 = cvt_pk_bf16(o[0], o[1]), p23 = cvt_pk_bf16(o[2], o[3]);
-                    const int row = 32 * mt + 8 * g + 4 * kg;
+                    const int row = 32 * (mt0 + mt) + 8 * g + 4 * kg;
                     if (a.dzR) {
                         tile[(row + 0) * LDT + col] = (uint16_t)p01; tile[(row + 1) * LDT + col] = (uint16_t)(p01 >> 16);
                         tile[(row + 2) * LDT + col] = (uint16_t)p23; tile[(row + 3) * LDT + col] = (uint16_t)(p23 >> 16);
                     }
                     if (live[jt]) {
-                        const size_t G = (size_t)((m0 + 32 * mt) >> 3) + g;
+                        const size_t G = (size_t)((m0 + 32 * (mt0 + mt)) >> 3) + g;
                         *reinterpret_cast<uint2*>(a.dzP + (G * H + jw + 32 * jt + l32) * 8 + 4 * kg) = make_uint2(p01, p23);
                     }
                 }
@@ -207,15 +210,15 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
         __syncthreads();
         // row-major copy (only where the tiled dX kernel reads it): 64 rows x 256 columns, 16-byte pieces
         if (a.dzR)
-            for (int i = tid; i < 64 * (WG / 8); i += WG) {
-                const int row = i / (WG / 8), c = (i % (WG / 8)) * 8;
+            for (int i = tid; i < 64 * (SPLIT ? WG / 16 : WG / 8); i += WG) {
+                const int row = i / (SPLIT ? WG / 16 : WG / 8), c = (i % (SPLIT ? WG / 16 : WG / 8)) * 8;
                 if (jb + c < H)
                     *reinterpret_cast<uint4*>(a.dzR + (size_t)(m0 + row) * H + jb + c) = *reinterpret_cast<const uint4*>(&tile[row * LDT + c]);
             }
     }
     __syncthreads();
     // dWh: rows j of the accumulator, columns k (hi parts) and 8+k (lo parts)
-    float* S = reinterpret_cast<float*>(tile);                       // [256 columns j][16]
+    float* S = reinterpret_cast<float*>(tile);                       // [256 columns j][16] (SPLIT: [2 sample tiles][128][16])
     if (l32 < 16) {
 #pragma unroll
         for (int jt = 0; jt < 2; ++jt)
@@ -226,7 +229,11 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     __syncthreads();
     float* out = a.partial + (size_t)blockIdx.x * ((size_t)H * NH + NH);
     if (jb + tid < H)
-        for (int k = 0; k < NH; ++k) out[(size_t)(jb + tid) * NH + k] = S[tid * 16 + k] + S[tid * 16 + 8 + k];
+        for (int k = 0; k < NH; ++k) {
+            float sum = S[tid * 16 + k] + S[tid * 16 + 8 + k];
+            if (SPLIT) sum += S[(128 + tid) * 16 + k] + S[(128 + tid) * 16 + 8 + k];
+            out[(size_t)(jb + tid) * NH + k] = sum;
+        }
     if (blockIdx.y == 0) {
         __syncthreads();
         if (tid < 64) for (int k = 0; k < 8; ++k) S[tid * 8 + k] = db[k];
@@ -1280,7 +1287,8 @@ hipError_t launch_backward_bf16(anakin* h)
         a.partial = h->head_fan > 1 ? at<float>(h, L.head_stage) : at<float>(h, L.part[n.L]);
         {
             ProfScope prof(h, "head_backward");
-            hipLaunchKernelGGL(head_backward_bf16, dim3(stage1, (a.H + WG - 1) / WG), dim3(WG), 0, h->stream, a);
+            if (a.H <= 128) hipLaunchKernelGGL(head_backward_bf16<true>, dim3(stage1), dim3(WG), 0, h->stream, a);
+            else hipLaunchKernelGGL(head_backward_bf16<false>, dim3(stage1, (a.H + WG - 1) / WG), dim3(WG), 0, h->stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (h->head_fan > 1) {

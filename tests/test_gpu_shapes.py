@@ -105,6 +105,13 @@ def test_ragged_chunks_bf16(gpu, orc, name, hidden, B, T):
     forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 6)
 
 
+# bf16 head pass of 128 columns, half of the wavefronts on each half of a step's samples: one step of 64 samples, two, many
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 128], 64, 1), ("pendulum_8192", [128, 128], 64, 2), ("maze_16384", [512, 128], 192, 5)])
+def test_bf16_head_pass_of_128_columns(gpu, orc, name, hidden, B, T):
+    env = dict(max_steps=9) if not name.startswith("catch") else {}
+    forced_lockstep(gpu, orc, variant(name, hidden, B, T, dtype="bf16", **env), 4)
+
+
 # backward products on split operands, few samples (their small tiles): one row tile or less, ends in the middle of a tile,
 # several tiles side by side, every pairing of their widths
 @pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 256], 16, 1), ("pendulum_8192", [256, 256], 48, 3), ("pendulum_8192", [256, 512], 80, 5),
