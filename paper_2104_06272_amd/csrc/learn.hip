@@ -16,6 +16,7 @@
 // sweep of the pathwise policy gradient in pathwise.hip.
 // No floating-point atomics anywhere: every reduction has a fixed order, so runs
 // are reproducible bit for bit.
+#include <type_traits>
 #include "internal.h"
 #include "loss.h"
 #include "split_terms.h"
@@ -169,19 +170,26 @@ struct HeadGradArgs {
                                            // score-function term, and the reported policy loss is minus the mean reward
 };
 
+// what the loss of a sample reads, besides its advantage and return
+struct HeadIn { float4 h0, h1; float eps, rew; int act, done; };
+__device__ __forceinline__ HeadIn head_in(const HeadGradArgs& a, const int i)
+{
+    HeadIn x;
+    const float* h = a.head + (size_t)i * a.NHP;
+    x.h0 = *reinterpret_cast<const float4*>(h);
+    x.h1 = a.NHP == 8 ? *reinterpret_cast<const float4*>(h + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    x.act = a.policy == POLICY_CATEGORICAL ? (int)a.act[i] : 0;
+    x.eps = a.policy == POLICY_CATEGORICAL ? 0.0f : a.eps[i];
+    x.rew = a.rew[i]; x.done = a.done[i];
+    return x;
+}
+
 // one sample: its loss terms, and its head gradient to a.dhead.  A_, G_: advantage and return of the sample
-__device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const int i, float A_, const float G_,
+__device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const int i, const HeadIn& x, float A_, const float G_,
                                                  float& lp_term, float& v_term, float& e_term, float& rsum, float& dcount)
 {
     {
-        const float* h = a.head + (size_t)i * a.NHP;
-        float hv[8];
-        const float4 h0 = *reinterpret_cast<const float4*>(h);
-        hv[0] = h0.x; hv[1] = h0.y; hv[2] = h0.z; hv[3] = h0.w;
-        if (a.NHP == 8) {
-            const float4 h1 = *reinterpret_cast<const float4*>(h + 4);
-            hv[4] = h1.x; hv[5] = h1.y; hv[6] = h1.z; hv[7] = h1.w;
-        } else { hv[4] = hv[5] = hv[6] = hv[7] = 0.0f; }
+        const float hv[8] = {x.h0.x, x.h0.y, x.h0.z, x.h0.w, x.h1.x, x.h1.y, x.h1.z, x.h1.w};
         if (a.path) A_ = 0.0f;
         float V = hv[0];
 #pragma unroll
@@ -191,7 +199,7 @@ __device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const in
         v_term = a.cv * dv * dv;
         const float gV = -2.0f * a.cv * dv * a.inv_m;
         if (a.policy == POLICY_CATEGORICAL) {
-            const int act = a.act[i];
+            const int act = x.act;
             float mx = hv[0];
 #pragma unroll
             for (int j = 1; j < 8; ++j) if (j < a.A) mx = fmaxf(mx, hv[j]);
@@ -217,7 +225,7 @@ __device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const in
             const bool clamped = ls < -5.0f || ls > 2.0f;
             const float lsc = fminf(fmaxf(ls, -5.0f), 2.0f);
             const float sigma = det_exp(lsc);
-            float ep = a.eps[i];
+            float ep = x.eps;
             if (a.head_old) ep = noise_now(a.head_old + (size_t)i * a.NHP, ep, hv[0], sigma);
             d[0] = (-A_ * ep / sigma) * a.inv_m;
             d[1] = clamped ? 0.0f : (-A_ * (ep * ep - 1.0f) - a.beta) * a.inv_m;
@@ -229,13 +237,13 @@ __device__ __forceinline__ void head_grad_sample(const HeadGradArgs& a, const in
         if (a.path) {
             const float2 pg = *reinterpret_cast<const float2*>(a.path + (size_t)i * 2);
             d[0] += pg.x; d[1] += pg.y;
-            lp_term = -a.rew[i];
+            lp_term = -x.rew;
         }
         float* o = a.dhead + (size_t)i * a.NHP;
         *reinterpret_cast<float4*>(o) = make_float4(d[0], d[1], d[2], d[3]);
         if (a.NHP == 8) *reinterpret_cast<float4*>(o + 4) = make_float4(d[4], d[5], d[6], d[7]);
-        rsum = a.rew[i];
-        dcount = a.done[i] ? 1.0f : 0.0f;
+        rsum = x.rew;
+        dcount = x.done ? 1.0f : 0.0f;
     }
 }
 
@@ -265,7 +273,7 @@ __global__ __launch_bounds__(WG) void head_grad(const HeadGradArgs a, const Spli
     __shared__ float red[WG / 64][8];
     const int i = blockIdx.x * WG + threadIdx.x;
     float lp_term = 0.0f, v_term = 0.0f, e_term = 0.0f, rsum = 0.0f, dcount = 0.0f;
-    if (i < a.M) head_grad_sample(a, i, a.adv[i], a.ret[i], lp_term, v_term, e_term, rsum, dcount);
+    if (i < a.M) head_grad_sample(a, i, head_in(a, i), a.adv[i], a.ret[i], lp_term, v_term, e_term, rsum, dcount);
     loss_block_sums(lp_term, v_term, e_term, rsum, dcount, red, a.loss_part);
 }
 
@@ -296,53 +304,93 @@ __global__ __launch_bounds__(WG) void scan_loss(const ScanLossArgs a, const Spli
     __shared__ float red[WG / 64][8];
     __shared__ float rews[SL_MAXN], vals[SL_MAXN + 16], discs[SL_MAXN];
     __shared__ float advs[SL_MAXN], rets[SL_MAXN], rhos[VTRACE ? SL_MAXN : 1];
-    const int B = a.B, T = a.T, SL_E = a.E, tid = threadIdx.x;
+    const int B = a.B, T = a.T, SL_E = a.E, lg = SL_E == 16 ? 4 : 3, tid = threadIdx.x;
     const int b0 = blockIdx.x * SL_E;
     const int n = T * SL_E;
-    for (int s = tid; s < n + SL_E; s += WG) {
-        const int t = s / SL_E, e = s - t * SL_E;
-        const size_t i = (size_t)t * B + b0 + e;
-        vals[s] = a.val[i];
-        if (s < n) { rews[s] = a.g.rew[i]; discs[s] = a.g.done[i] ? 0.0f : a.gamma; }
-        if (VTRACE && s < n) rhos[VTRACE ? s : 0] = vtrace_rho(a.v, i);
+    auto sample = [&](int s) { return (s >> lg) * B + b0 + (s & (SL_E - 1)); };
+    // Latency is what this launch is made of: all loads of a thread's first samples go out before anything waits (loads of
+    // one sample after another, and of the loss behind the scan, were a round trip to memory each, and so was a step of the
+    // recursion to LDS: pendulum, 1024 environments, T = 32 7.5 -> 5.3 us; 8192, T = 32 10.5 -> 8.0; Catch, 4096, T = 20 7.1 -> 6.9)
+    // (V-trace: few at a time, so that its workgroups find room beside the actor's, whose registers leave 80 per lane; with 93
+    // they waited for the actor to end, and a decoupled step of two layers of 256 took 408 us instead of 392)
+    constexpr int LB = VTRACE ? 1 : 4, PF = VTRACE ? 1 : 2, SB = VTRACE ? 4 : 8;
+    HeadIn in[PF];
+    for (int s0 = tid; s0 < n + SL_E; s0 += LB * WG) {
+        float v[LB], r[LB];
+        int d[LB];
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {                           // past the end: the last one again, unused
+            const int s = s0 + q * WG, i1 = sample(s < n + SL_E ? s : n + SL_E - 1), i = sample(s < n ? s : n - 1);
+            v[q] = a.val[i1]; r[q] = a.g.rew[i]; d[q] = a.g.done[i];
+        }
+        if (!VTRACE && s0 == tid) {
+#pragma unroll
+            for (int q = 0; q < PF; ++q) in[q] = head_in(a.g, sample(tid + q * WG < n ? tid + q * WG : n - 1));
+        }
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+            const int s = s0 + q * WG;
+            if (s < n + SL_E) vals[s] = v[q];
+            if (s < n) {
+                rews[s] = r[q]; discs[s] = d[q] ? 0.0f : a.gamma;
+                if (VTRACE) rhos[VTRACE ? s : 0] = vtrace_rho(a.v, sample(s));
+            }
+        }
     }
     __syncthreads();
-    if (VTRACE && tid < SL_E) {
-        float Vnext = vals[n + tid], tail = 0.0f;                // tail: v_{t+1} - V_{t+1}
-        for (int t = T - 1; t >= 0; --t) {
-            const int s = t * SL_E + tid;
-            const float rho = rhos[VTRACE ? s : 0], V = vals[s], r = rews[s], disc = discs[s];
-            const float c = a.lambda * rho;
-            advs[s] = rho * (fmaf(disc, Vnext + tail, r) - V);
-            tail = fmaf(disc * c, tail, rho * (fmaf(disc, Vnext, r) - V));
-            rets[s] = V + tail;
-            Vnext = V;
-        }
-    }
-    if (!VTRACE && tid < SL_E) {
+    // the operands of several steps are read before the first of them is used: one LDS round trip for all of them
+    if (tid < SL_E) {
         const float oml = 1.0f - a.lambda;
-        float G = vals[n + tid], vnext = G;
-        for (int t = T - 1; t >= 0; --t) {
-            const int s = t * SL_E + tid;
-            const float v = vals[s];
-            const float mix = fmaf(a.lambda, G, oml * vnext);
-            G = fmaf(discs[s], mix, rews[s]);
-            rets[s] = G;
-            advs[s] = G - v;
-            vnext = v;
-        }
+        float Vnext = vals[n + tid], tail = 0.0f;                // V-trace: v_{t+1} - V_{t+1}
+        float G = Vnext;
+        auto steps = [&](auto count, int t1) {
+            constexpr int N = decltype(count)::value;
+            float V[N], r[N], disc[N], rho[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int s = (t1 - 1 - u) * SL_E + tid;
+                V[u] = vals[s]; r[u] = rews[s]; disc[u] = discs[s]; rho[u] = VTRACE ? rhos[VTRACE ? s : 0] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int s = (t1 - 1 - u) * SL_E + tid;
+                if (VTRACE) {
+                    const float c = a.lambda * rho[u];
+                    advs[s] = rho[u] * (fmaf(disc[u], Vnext + tail, r[u]) - V[u]);
+                    tail = fmaf(disc[u] * c, tail, rho[u] * (fmaf(disc[u], Vnext, r[u]) - V[u]));
+                    rets[s] = V[u] + tail;
+                } else {
+                    const float mix = fmaf(a.lambda, G, oml * Vnext);
+                    G = fmaf(disc[u], mix, r[u]);
+                    rets[s] = G;
+                    advs[s] = G - V[u];
+                }
+                Vnext = V[u];
+            }
+        };
+        int t1 = T;
+        for (; t1 >= SB; t1 -= SB) steps(std::integral_constant<int, SB>(), t1);
+        for (; t1 > 0; --t1) steps(std::integral_constant<int, 1>(), t1);
     }
     __syncthreads();
     float lp_term = 0.0f, v_term = 0.0f, e_term = 0.0f, rsum = 0.0f, dcount = 0.0f;
-    for (int s = tid; s < n; s += WG) {
-        const int t = s / SL_E, e = s - t * SL_E;
-        const int i = t * B + b0 + e;
-        const float A_ = advs[s], G_ = rets[s];
-        a.adv_out[i] = A_;
-        a.ret_out[i] = G_;
-        float l0, l1, l2, l3, l4;
-        head_grad_sample(a.g, i, A_, G_, l0, l1, l2, l3, l4);
-        lp_term += l0; v_term += l1; e_term += l2; rsum += l3; dcount += l4;
+    for (int s0 = tid; s0 < n; s0 += PF * WG) {
+        if (VTRACE || s0 != tid) {
+#pragma unroll
+            for (int q = 0; q < PF; ++q) in[q] = head_in(a.g, sample(s0 + q * WG < n ? s0 + q * WG : n - 1));
+        }
+#pragma unroll
+        for (int q = 0; q < PF; ++q) {
+            const int s = s0 + q * WG;
+            if (s >= n) break;
+            const int i = sample(s);
+            const float A_ = advs[s], G_ = rets[s];
+            a.adv_out[i] = A_;
+            a.ret_out[i] = G_;
+            float l0, l1, l2, l3, l4;
+            head_grad_sample(a.g, i, in[q], A_, G_, l0, l1, l2, l3, l4);
+            lp_term += l0; v_term += l1; e_term += l2; rsum += l3; dcount += l4;
+        }
     }
     loss_block_sums(lp_term, v_term, e_term, rsum, dcount, red, a.g.loss_part);
 }

@@ -84,6 +84,14 @@ def test_small_update_in_one_launch(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_small", [64, 64], B, T, rows=rows, cols=cols, max_steps=rows - 1), 5)
 
 
+# returns and loss in one launch: fewer samples than threads, more than a thread asks for ahead, the most a workgroup holds,
+# time steps in whole batches of the recursion and off them
+@pytest.mark.parametrize("name,B,T", [("catch_4096", 16, 3), ("pendulum_8192", 32, 33), ("maze_16384", 32, 40), ("pendulum_8192", 16, 64), ("catch_4096", 48, 63)])
+def test_returns_and_loss_in_one_launch(gpu, orc, name, B, T):
+    env = dict(rows=5, cols=7, max_steps=9) if name.startswith("maze") else {}
+    lockstep(gpu, orc, variant(name, [128, 64], B, T, **env), 6)
+
+
 # a first layer of 32 units below a wider one, with batches that fill tiles of 16 environments
 @pytest.mark.parametrize("name,hidden,B", [("pendulum_8192", [32, 64], 320), ("catch_small", [32, 512], 64)])
 def test_narrow_first_layer(gpu, orc, name, hidden, B):
