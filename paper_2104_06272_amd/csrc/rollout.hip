@@ -894,6 +894,10 @@ __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const 
     constexpr int NT = RW / (16 * RES_WAVES);                      // column tiles of 16 per wavefront
     constexpr int LDX = RW + 4, LDW = RW + 4;
     constexpr int NE = 256 / RW < EPW ? 256 / RW : EPW, IT = EPW / NE;   // first layer: environments side by side, passes
+    // 160 registers, whatever the code needs, for layers of 128: with the 104 to 145 that it does, a decoupled step's replay
+    // (240 for its two wavefronts per SIMD) finds room beside this kernel, and as both are bound by the matrix cores and this
+    // one is the longer chain, the step takes longer (Catch 128-128, 8192 environments, T = 32: 471 us against 405)
+    if (RW == 128) asm volatile("" : : : "v159");
     extern __shared__ float4 smem4[];
     float* X = reinterpret_cast<float*>(smem4);                    // [TM][LDX] first layer's outputs
     float* Y = X + TM * LDX;                                       // [TM][LDX] second layer's
