@@ -887,17 +887,14 @@ __global__ __launch_bounds__(STW + STA) void rollout_stream_kernel(const StreamA
 // ---------------------------------------------------------------------------
 constexpr int RES_WAVES = 8;
 
-template <int ENV, int RW, int G>
+template <int ENV, int RW, int G, bool HOLD>
 __global__ __launch_bounds__(64 * RES_WAVES) void rollout_resident_kernel(const RolloutArgs a, const int w1_lds)
 {
     constexpr int NTHR = 64 * RES_WAVES, TM = 16 * G, EPW = TM / RES_WAVES, KS = RW / 4;
     constexpr int NT = RW / (16 * RES_WAVES);                      // column tiles of 16 per wavefront
     constexpr int LDX = RW + 4, LDW = RW + 4;
     constexpr int NE = 256 / RW < EPW ? 256 / RW : EPW, IT = EPW / NE;   // first layer: environments side by side, passes
-    // 160 registers, whatever the code needs, for layers of 128: with the 104 to 145 that it does, a decoupled step's replay
-    // (240 for its two wavefronts per SIMD) finds room beside this kernel, and as both are bound by the matrix cores and this
-    // one is the longer chain, the step takes longer (Catch 128-128, 8192 environments, T = 32: 471 us against 405)
-    if (RW == 128) asm volatile("" : : : "v159");
+    if (HOLD) asm volatile("" : : : "v159");                       // (see launch_resident_env)
     extern __shared__ float4 smem4[];
     float* X = reinterpret_cast<float*>(smem4);                    // [TM][LDX] first layer's outputs
     float* Y = X + TM * LDX;                                       // [TM][LDX] second layer's
@@ -1779,12 +1776,12 @@ static hipError_t launch_stream(anakin* h, const RolloutArgs& args, int TM)
     return hipGetLastError();
 }
 
-template <int ENV, int RW, int G>
+template <int ENV, int RW, int G, bool HOLD = false>
 static hipError_t launch_resident(anakin* h, const RolloutArgs& a)
 {
     const int w1 = h->env.kind != ENV_MAZE && resident_lds_bytes(h->net, h->env.kind, G, true) <= 160 * 1024;
     const size_t lds = resident_lds_bytes(h->net, h->env.kind, G, w1 != 0);
-    auto kern = rollout_resident_kernel<ENV, RW, G>;
+    auto kern = rollout_resident_kernel<ENV, RW, G, HOLD>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(h, "rollout");
@@ -1807,11 +1804,21 @@ static hipError_t launch_resident64(anakin* h, const RolloutArgs& a)
     return hipGetLastError();
 }
 
+// Layers of 128 take 104 to 145 registers, so that two workgroups share a compute unit (boards; unrolls of 16 with one, two to a
+// unit: Catch, 65536 environments 527 / 417 us, 16 x 16 maze, 12288 178 / 142; where there is one per unit anyway the same).
+// Beside a learner it takes 160, whatever the code needs, while its workgroups have a unit each: with fewer a replay (240
+// for its two wavefronts per SIMD) finds room beside it, and as both are bound by the matrix cores and the actor is the longer
+// chain, the step takes longer.  Decoupled steps without / with: Catch 8192 environments, T = 20 302 / 262 us, T = 40 575 / 487,
+// 2048, T = 40 196 / 165, 3072, T = 20 136 / 138.5; maze 4080, T = 20 249 / 238, 8192 354 / 372; the pendulum, which leaves no
+// room in either form, within 3 %.  More workgroups than units: Catch 10240, T = 20 347 / 370, 16384 472 / 540.
 template <int ENV>
-static hipError_t launch_resident_env(anakin* h, const RolloutArgs& a, int width, int tm)
+static hipError_t launch_resident_env(anakin* h, const RolloutArgs& a, int width, int tm, bool beside)
 {
     if (width == 256) return tm == 32 ? launch_resident<ENV, 256, 2>(h, a) : launch_resident<ENV, 256, 1>(h, a);
-    if (width == 128) return tm == 32 ? launch_resident<ENV, 128, 2>(h, a) : launch_resident<ENV, 128, 1>(h, a);
+    if (width == 128) {
+        if (beside && (h->B + tm - 1) / tm <= 256) return tm == 32 ? launch_resident<ENV, 128, 2, true>(h, a) : launch_resident<ENV, 128, 1, true>(h, a);
+        return tm == 32 ? launch_resident<ENV, 128, 2>(h, a) : launch_resident<ENV, 128, 1>(h, a);
+    }
     return launch_resident64<ENV>(h, a);
 }
 
@@ -1840,9 +1847,9 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a, bool beside = 
     if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
         const int w = rollout_resident_width(h->net);
         switch (h->env.kind) {
-            case ENV_CATCH:    return launch_resident_env<ENV_CATCH>(h, a, w, h->TM_res);
-            case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM>(h, a, w, h->TM_res);
-            default:           return launch_resident_env<ENV_MAZE>(h, a, w, h->TM_res);
+            case ENV_CATCH:    return launch_resident_env<ENV_CATCH>(h, a, w, h->TM_res, beside);
+            case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM>(h, a, w, h->TM_res, beside);
+            default:           return launch_resident_env<ENV_MAZE>(h, a, w, h->TM_res, beside);
         }
     }
     if (h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING)) {

@@ -4,6 +4,7 @@ before touching the device."""
 import ctypes as C
 import os
 import re
+import struct
 import subprocess
 
 import pytest
@@ -134,3 +135,32 @@ def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
     # the bf16 nets: every pairing of large tiles that widths of 128 and more can have
     large = [f for s in G.SPLIT_LARGE_BF16 for f in forms([s + (2064, 17, 1)])[0]]
     assert {f.split(":")[1] for f in large} >= {"256x256/256", "128x128/256", "128x128/128"} and all(f.startswith("many:") for f in large)
+
+
+def registers_per_lane(pattern, tmp_path):
+    """{kernel: vector registers} of the library's own code objects, kernels whose mangled name matches `pattern`"""
+    image, magic, out = open(binding.LIB_PATH, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    for at in (m.start() for m in re.finditer(magic, image)):
+        (n,), pos = struct.unpack_from("<Q", image, at + len(magic)), at + len(magic) + 8
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", image, pos)
+            triple, pos = image[pos + 24:pos + 24 + length], pos + 24 + length
+            if not triple.endswith(b"gfx950") or not size:
+                continue
+            obj = tmp_path / "code.o"
+            obj.write_bytes(image[at + offset:at + offset + size])
+            notes = subprocess.run([os.path.join(os.path.dirname(build.HIPCC), "..", "llvm", "bin", "llvm-readelf"), "--notes", str(obj)],
+                                   capture_output=True, text=True, check=True).stdout
+            for name, count in re.findall(r"\.name: +(_Z\S+)\n(?:(?!\.name: +_Z).)*?\.vgpr_count: +(\d+)", notes, re.S):
+                if re.search(pattern, name):
+                    out[name] = int(count)
+    return out
+
+
+def test_actor_of_128_units_holds_registers_only_beside_a_learner(lib, tmp_path):
+    """Two workgroups of the 128-wide actor of boards share a compute unit (eight wavefronts each: 128 registers); the form
+    that runs beside a learner's replay keeps that out with more."""
+    plain = registers_per_lane(r"rollout_resident_kernelILi[02]ELi128ELi[12]ELb0E", tmp_path)
+    beside = registers_per_lane(r"rollout_resident_kernelILi[02]ELi128ELi[12]ELb1E", tmp_path)
+    assert len(plain) == 4 and max(plain.values()) <= 128, plain
+    assert len(beside) == 4 and min(beside.values()) >= 160, beside
