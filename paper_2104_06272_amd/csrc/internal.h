@@ -320,6 +320,7 @@ hipError_t launch_pinned(anakin* h, const RolloutArgs& args);
 int rollout_resident_width(const NetShape& net);
 bool replay_resident_ok(const anakin* h, int samples);
 hipError_t launch_replay_resident(anakin* h, const RolloutArgs& a, int samples);
+bool vtrace_off_the_actor(const anakin* h, size_t lds);
 bool rollout_small_ok(const anakin* h);
 hipError_t launch_small(anakin* h, const RolloutArgs& args);
 int rollout_wide_groups(const NetShape& net, const EnvDims& env, int B);

@@ -1467,11 +1467,9 @@ hipError_t launch_scan_loss(anakin* h, bool vtrace)
     s.blocks = h->B / s.E;
     h->metric_blocks = s.blocks;
     const SplitWeightsArgs sw = split_weights_args(h);
-    // While the actor of a decoupled step leaves compute units free (16 environments per workgroup, fewer than 256 of them),
-    // these workgroups keep off its units, where they would take issue slots from the chain that the step waits for: with
-    // 64 KB more of LDS they do not fit beside it (Catch 256-256, 2048 environments, T = 40: a
-    // decoupled step 390 us without, 376 with).
-    const unsigned pad = vtrace && h->B < 16 * 256 ? 64 * 1024 : 0;
+    // LDS that it does not use keeps a V-trace workgroup off the actor's units where that pays
+    constexpr unsigned arrays = (6 * SL_MAXN + 16) * sizeof(float), more = 64 * 1024;
+    const unsigned pad = vtrace && vtrace_off_the_actor(h, arrays + more) ? more : 0;
     if (pad) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(scan_loss<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pad);
         if (e != hipSuccess) return e;

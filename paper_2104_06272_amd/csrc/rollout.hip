@@ -1822,7 +1822,39 @@ static hipError_t launch_resident_env(anakin* h, const RolloutArgs& a, int width
     return launch_resident64<ENV>(h, a);
 }
 
+// Which kernel acts, of those that hold the weights on chip (nets of one layer have theirs, launch_forward).
 // beside: the learner runs at the same time (the actor of a decoupled step)
+enum class Actor { PINNED, WIDE, SMALL, RESIDENT, OTHER };
+static Actor pick_actor(const anakin* h, bool beside)
+{
+    if (h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)) return Actor::OTHER;
+    if (h->pinned.NB > 0) return Actor::PINNED;
+    // Each of its workgroups has a compute unit to itself: beside a learner it takes half of them at most (decoupled steps,
+    // 256-256, T = 16: 256 environments 130 -> 101 us, 512 129.5 -> 119.5, but 1024 130.5 -> 171.6 on all units; 256-512:
+    // 247 -> 144, 246 -> 181, 246 -> 248).
+    if (h->wide > 0 && (!beside || h->B / (4 * h->wide) <= 128)) return Actor::WIDE;
+    // Beside the learner of a small board net a few of its workgroups cost more than they save (decoupled Catch, T = 20: 512
+    // environments 57.6 -> 59.2 us, 1024 66.4 -> 67.9, but 2048 83.6 -> 82.1, 4096 110.2 -> 104.3; pendulum 1024 71.0 -> 64.1,
+    // 4096 102.8 -> 96.7).
+    if (rollout_small_ok(h) && (!beside || h->env.kind == ENV_PENDULUM || h->B > 1024)) return Actor::SMALL;
+    return h->TM_res > 0 ? Actor::RESIDENT : Actor::OTHER;
+}
+
+// Whether the V-trace launch of a decoupled step is kept off the units that the actor works on (launch_scan_loss): the 256-wide
+// actor of Catch is the only one that leaves registers for its wavefronts (215 of 256 for each of two per SIMD; 233 and 243 on
+// mazes and the pendulum) and is slowed by them, and while it has at most 160 workgroups there are units enough without it.
+// Decoupled steps of 256-256, beside the actor / off its units: Catch 1536 environments, T = 8 116 / 105 us, T = 20 186 / 186,
+// 2048, T = 8 122 / 124, T = 20 222 / 220, T = 40 382 / 362, T = 64 583 / 563, 2560, T = 8 152 / 148, T = 40 534 / 534, but 3584,
+// T = 40 667 / 672, 4080 715 / 741; maze 2048, T = 20 293 / 298, 3072 388 / 402; pendulum 4080, T = 40 659 / 668.  Behind the actors
+// of other nets as well it loses or nothing: 128-128 2048, T = 20 107 / 112, 256-128-64 195 / 200, bf16 256-256 3072 153 / 161.
+// lds: what the V-trace workgroup has then; the actor's 43 KB and W1, where that fits, have to leave less.
+bool vtrace_off_the_actor(const anakin* h, size_t lds)
+{
+    if (h->env.kind != ENV_CATCH || rollout_resident_width(h->net) != 256 || pick_actor(h, true) != Actor::RESIDENT || h->B > 16 * 160) return false;
+    const size_t w1 = resident_lds_bytes(h->net, ENV_CATCH, 1, true), actor = w1 <= 160 * 1024 ? w1 : resident_lds_bytes(h->net, ENV_CATCH, 1, false);
+    return actor + lds > 160 * 1024;
+}
+
 template <bool REPLAY>
 static hipError_t launch_forward(anakin* h, const RolloutArgs& a, bool beside = false)
 {
@@ -1834,22 +1866,19 @@ static hipError_t launch_forward(anakin* h, const RolloutArgs& a, bool beside = 
         }
     }
     if (rollout_one_ok(h)) return launch_rollout_one(h, a, REPLAY);
-    if (!REPLAY && h->pinned.NB > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_pinned(h, a);
-    // Each of its workgroups has a compute unit to itself: beside a learner it takes half of them at most (decoupled steps,
-    // 256-256, T = 16: 256 environments 130 -> 101 us, 512 129.5 -> 119.5, but 1024 130.5 -> 171.6 on all units; 256-512:
-    // 247 -> 144, 246 -> 181, 246 -> 248).
-    if (!REPLAY && h->wide > 0 && (!beside || h->B / (4 * h->wide) <= 128) && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) return launch_wide(h, a);
-    // Beside the learner of a small board net a few of its workgroups cost more than they save (decoupled Catch, T = 20: 512
-    // environments 57.6 -> 59.2 us, 1024 66.4 -> 67.9, but 2048 83.6 -> 82.1, 4096 110.2 -> 104.3; pendulum 1024 71.0 -> 64.1,
-    // 4096 102.8 -> 96.7).
-    if (!REPLAY && rollout_small_ok(h) && (!beside || h->env.kind == ENV_PENDULUM || h->B > 1024) && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)))
-        return launch_small(h, a);
-    if (!REPLAY && h->TM_res > 0 && !(h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS))) {
+    if (!REPLAY) {
         const int w = rollout_resident_width(h->net);
-        switch (h->env.kind) {
-            case ENV_CATCH:    return launch_resident_env<ENV_CATCH>(h, a, w, h->TM_res, beside);
-            case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM>(h, a, w, h->TM_res, beside);
-            default:           return launch_resident_env<ENV_MAZE>(h, a, w, h->TM_res, beside);
+        switch (pick_actor(h, beside)) {
+            case Actor::PINNED: return launch_pinned(h, a);
+            case Actor::WIDE:   return launch_wide(h, a);
+            case Actor::SMALL:  return launch_small(h, a);
+            case Actor::RESIDENT:
+                switch (h->env.kind) {
+                    case ENV_CATCH:    return launch_resident_env<ENV_CATCH>(h, a, w, h->TM_res, beside);
+                    case ENV_PENDULUM: return launch_resident_env<ENV_PENDULUM>(h, a, w, h->TM_res, beside);
+                    default:           return launch_resident_env<ENV_MAZE>(h, a, w, h->TM_res, beside);
+                }
+            case Actor::OTHER: break;
         }
     }
     if (h->TM_mfma > 0 && !(h->mode & ANAKIN_MODE_CANONICAL_ACTING)) {
