@@ -20,6 +20,11 @@
 // 256-256, 8192 envs, T = 32: 412 us with the fp32 instruction, 175 to 190 now: 10.1 k cycles a step, of which the products
 // 6.4 k, (E) to (B) 2.7 k, (D) 0.7 k, and a clock that the bf16 instructions lower to about 1.9 GHz.  Against binary64 the
 // gradient of the path term is off by 0.7 to 4.4e-7 with either (six shapes, two seeds each).
+// Range (split_terms.h): W2 is taken whole at every finite value, so a weight at the type's lowest, the mask of a unit that
+// never fires, gives the zero it gives in binary32.  dZ2 is whole from 2^-102 to 3.39e38: smaller entries lose their last terms,
+// up to 2^-126 each (with head weights of 2^-60, as scaled layers below them may have, entries are still around 2^-90); at
+// infinity or above 3.39e38 they turn the env's adjoint, and all earlier ones of its episode, into NaN, where binary32
+// would carry infinities of both signs to the same end a layer further on.
 #include <type_traits>
 #include "split_terms.h"
 #include "detmath.h"
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(2 * RW) void pathwise_sweep(const PathArgs a)
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = src[e];
             u4v_s t[3];
-            split_terms(x, t);
+            split_terms<true>(x, t);
             w0[p] = t[0]; w1[p] = t[1];
             if (p < LREG) w2[p < LREG ? p : 0] = t[2];
             else wl[(wave * (KS - LREG) + (p < LREG ? 0 : p - LREG)) * 64 + lane] = t[2];

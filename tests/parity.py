@@ -126,6 +126,16 @@ def param_regions(cfg):
     return out, off
 
 
+def lowest_weights(cfg, theta):
+    """The type's lowest value in three entries of every matrix between hidden layers, in place."""
+    hid, regions = list(cfg["net"]["hidden"]), dict(param_regions(cfg)[0])
+    for l in range(2, len(hid) + 1):
+        K, N = hid[l - 2], hid[l - 1]
+        w = theta[regions[f"W{l}"]].reshape(K, N)
+        for i, j in ((K - 1, 0), (3, N // 2 + 1), (K // 2, N - 1)):
+            w[i, j] = np.finfo(np.float32).min
+
+
 def assert_regions_close(name, got, ref, regions, tol, skip=None, elem_factor=1.0):
     """per parameter region: relative l2 error <= tol and max |difference| <= elem_factor * tol * max |reference|.
     skip: boolean mask of elements left out (see assert_learn_close).  Returns the worst relative l2 error."""

@@ -1024,6 +1024,57 @@ def test_pathwise_sweep_shapes(gpu, orc, width, B, T):
     g.close()
 
 
+PATHWISE_RANGES = [(64, 16, 3), (128, 48, 5), (128, 8224, 2), (256, 48, 4), (256, 4128, 2)]      # both tile heights
+
+
+@pytest.mark.parametrize("width,B,T", PATHWISE_RANGES)
+def test_pathwise_sweep_with_weights_at_the_lowest_value(gpu, orc, width, B, T):
+    """A weight at the type's lowest value masks its unit: the gradient that meets it in the sweep and in the update's
+    products is 0, and so is the product.  Bound: test_pathwise_sweep_shapes."""
+    cfg = _path_only(variant("pendulum_8192", hidden=[width, width], B=B, T=T, max_steps=11))
+    say(f"[pathwise lowest weights] width={width} B={B} T={T}")
+    g = gpu.Anakin(cfg, seed=3)
+    o = orc.Oracle(cfg, seed=3)
+    g.set_policy_gradient(gpu.PG_PATHWISE)
+    theta = g.get_params()
+    PT.lowest_weights(cfg, theta)
+    g.set_params(theta)
+    PT.sync_oracle_from_gpu(g, o)
+    g.rollout(); o.rollout()
+    PT.assert_rollout_equal(g, o, "pendulum")
+    ref, _ = o.pathwise_grad()
+    g.learn()
+    err = np.linalg.norm(g.get_grads().astype(np.float64) - ref) / np.linalg.norm(ref)
+    assert err <= 1e-6, err
+    g.close()
+
+
+@pytest.mark.parametrize("width,B,T", PATHWISE_RANGES)
+def test_pathwise_sweep_of_a_scaled_net(gpu, width, B, T):
+    """Second layer 2^40 as large, heads 2^-40: the same policy, and every value on the way is the other net's times a power
+    of two.  The gradients are those to the bit as long as the products' operands keep all their terms (head weights times
+    head gradients are around 2^-75 here)."""
+    cfg = _path_only(variant("pendulum_8192", hidden=[width, width], B=B, T=T, max_steps=11))
+    say(f"[pathwise scaled] width={width} B={B} T={T}")
+    regions, _ = PT.param_regions(cfg)
+    scale = np.ones(sum(sl.stop - sl.start for _, sl in regions))
+    for rname, sl in regions:
+        if rname in ("W2", "b2"):
+            scale[sl] = 2.0 ** 40
+        elif rname == "Wh":
+            scale[sl] = 2.0 ** -40
+    grads = []
+    for factor in (np.ones_like(scale), scale):
+        g = gpu.Anakin(cfg, seed=5)
+        g.set_policy_gradient(gpu.PG_PATHWISE)
+        g.set_params((g.get_params() * factor).astype(np.float32))
+        g.rollout()
+        g.learn()
+        grads.append(g.get_grads().astype(np.float64) * factor)
+        g.close()
+    np.testing.assert_array_equal(*grads)
+
+
 def test_pathwise_rejections(gpu):
     c = gpu.Anakin(variant("catch_small"), seed=0)
     with pytest.raises(gpu.AnakinError):

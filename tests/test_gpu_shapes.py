@@ -201,7 +201,7 @@ def test_infinite_wall_weight(gpu, hidden, canonical):
     assert np.isfinite(heads[1]).all() and not np.array_equal(heads[0][:, ~free], heads[1][:, ~free])
 
 
-def split_products_against_binary64(gpu, name, hidden, B, T, dtype="fp32", orc=None):
+def split_products_against_binary64(gpu, name, hidden, B, T, dtype="fp32", orc=None, edit=None):
     """The backward products on split operands and, as the measure, those on the vector ALU against binary64 on the stored
     forward pass.  A bf16 net's weights and observations are rounded before they are used; its gradients stay in binary32."""
     cfg = variant(name, hidden, B, T, dtype)
@@ -214,6 +214,8 @@ def split_products_against_binary64(gpu, name, hidden, B, T, dtype="fp32", orc=N
         if mode == "valu":
             g.set_mode(gpu.MODE_VALU_GEMM)
         theta = g.get_params() + (0.05 * np.random.default_rng(14).standard_normal(g.P)).astype(np.float32)
+        if edit:
+            edit(cfg, theta)
         g.set_params(theta)
         g.rollout()
         g.learn()
@@ -256,6 +258,13 @@ SPLIT_BATCHES = [(416, 5), (2064, 17)]
 @pytest.mark.parametrize("name,hidden", SPLIT_FORMS)
 def test_every_form_of_the_split_products(gpu, name, hidden, B, T):
     split_products_against_binary64(gpu, name, hidden, B, T)
+
+
+@pytest.mark.parametrize("name,hidden,B,T", [("catch_4096", [256, 128, 64], 48, 3), ("catch_4096", [256, 256], 2064, 17), ("pendulum_8192", [128, 64], 416, 5)])
+def test_split_products_with_weights_at_the_lowest_value(gpu, name, hidden, B, T):
+    """A weight at the type's lowest value keeps its unit from firing wherever its input is positive; the gradient that meets
+    it there is 0, and so is the product."""
+    split_products_against_binary64(gpu, name, hidden, B, T, edit=PT.lowest_weights)
 
 
 # five heads folded in (the maze's four actions and the value): every pairing of tile widths
