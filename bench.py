@@ -137,9 +137,14 @@ def kernel_models(cfg, P, launched=()):
     # bf16 top layer with the heads folded in: its dW product is a launch of its own (gemm_tn_top) that reads
     # h_{L-1}, h_L and the head gradient and forms dZ_L itself
     top_fused = "gemm_tn_top" in launched
-    tn_layers = range(1, len(dims) - (2 if top_fused else 1))
+    # bf16 layers that are not in whole 256-wide tiles: both products in one launch (gemm_tn_nt), the other layers' apart
+    on_path = bf16 and B % 64 == 0 and all(h in (128, 256, 512) for h in hid)
+    layers = range(1, len(dims) - 1)
+    shared = [i for i in layers if on_path and (dims[i] % 256 or dims[i + 1] % 256)]
+    tn_layers = [i for i in layers if i not in shared and not (top_fused and i == layers[-1])]
+    nt_layers = [i for i in layers if i not in shared]
     tn = sum(2.0 * dims[i] * dims[i + 1] * M for i in tn_layers)
-    nt = sum(2.0 * dims[i] * dims[i + 1] * M for i in range(1, len(dims) - 1))
+    nt = sum(2.0 * dims[i] * dims[i + 1] * M for i in nt_layers)
     models["gemm_tn"] = ("mfma", tn / 1e12, mfma_peak, "TFLOP/s")
     models["gemm_nt_mask"] = ("mfma", nt / 1e12, mfma_peak, "TFLOP/s")
     if bf16:
@@ -154,7 +159,7 @@ def kernel_models(cfg, P, launched=()):
             dy = (dims[i + 1] / 4.0 + 4.0 * NH) if top else 2.0 * dims[i + 1]
             mask = dims[i] / 4.0 if (i >= 2 or dims[1] == 512) else 2.0 * dims[i]
             return (dy + mask + 2.0 * dims[i]) * M
-        nt_bytes = sum(nt_layer_bytes(i) for i in range(1, len(dims) - 1))
+        nt_bytes = sum(nt_layer_bytes(i) for i in nt_layers)
         tn_bytes = sum(2.0 * (dims[i] + dims[i + 1]) * M for i in tn_layers)
         if nt / max(nt_bytes, 1.0) < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
             models["gemm_nt_mask"] = ("hbm", nt_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
@@ -166,13 +171,19 @@ def kernel_models(cfg, P, launched=()):
         models["gemm_tn_top"] = ("mfma", top_flop / 1e12, mfma_peak, "TFLOP/s")
         if top_flop / top_bytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
             models["gemm_tn_top"] = ("hbm", top_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
-    # fp32 layers in whole 64-wide tiles: both products in one launch on split operands, both counted.  Bytes: x and dY read
-    # (the top layer's dY is formed from its activations, as many bytes), dX written but where nothing reads it (the
-    # pendulum's first layer); for narrow layers these take longer than the matrix instructions
-    models["gemm_tn_nt"] = ("mfma", (tn + nt) / 1e12, PEAK_SPLIT_TFLOPS, "TFLOP/s")
-    split_bytes = sum(4.0 * (dims[i] + dims[i + 1] + (0 if kind == "pendulum" and i == 1 else dims[i])) * M for i in range(1, len(dims) - 1))
-    if (tn + nt) / (PEAK_SPLIT_TFLOPS * 1e12) < split_bytes / (PEAK_HBM_GBS * 1e9):
-        models["gemm_tn_nt"] = ("hbm", split_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
+    # Both products in one launch, both counted.  Bytes: x and dY read (a top layer's dY may be formed from its activations, as
+    # many bytes), dX written but where nothing reads it (the pendulum's first layer in fp32); for narrow layers these take
+    # longer than the matrix instructions.  fp32: layers in whole 64-wide tiles, on split operands
+    if on_path:
+        both, peak = sum(4.0 * dims[i] * dims[i + 1] * M for i in shared), PEAK_BF16_TFLOPS
+        both_bytes = sum(2.0 * (2 * dims[i] + dims[i + 1]) * M for i in shared)
+    else:
+        both, peak = tn + nt, PEAK_SPLIT_TFLOPS
+        both_bytes = sum(4.0 * (dims[i] + dims[i + 1] + (0 if kind == "pendulum" and i == 1 else dims[i])) * M for i in layers)
+    if both:
+        models["gemm_tn_nt"] = ("mfma", both / 1e12, peak, "TFLOP/s")
+        if both / (peak * 1e12) < both_bytes / (PEAK_HBM_GBS * 1e9):
+            models["gemm_tn_nt"] = ("hbm", both_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
     models["gemm_tn_obs"] = ("mfma", 2.0 * dims[0] * dims[1] * M / 1e12, mfma_peak, "TFLOP/s")
     if kind == "maze":
         cells = cfg["env"]["rows"] * cfg["env"]["cols"]

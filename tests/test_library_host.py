@@ -164,3 +164,19 @@ def test_actor_of_128_units_holds_registers_only_beside_a_learner(lib, tmp_path)
     beside = registers_per_lane(r"rollout_resident_kernelILi[02]ELi128ELi[12]ELb1E", tmp_path)
     assert len(plain) == 4 and max(plain.values()) <= 128, plain
     assert len(beside) == 4 and min(beside.values()) >= 160, beside
+
+
+def test_bench_models_the_bf16_products_that_share_a_launch():
+    """bench.py's work per launch: bf16 layers with a 128-wide side are in the shared launch, at bf16 rates, and the other
+    layers in launches of their own; an fp32 net of the same widths is all split products."""
+    import bench
+    cfg = W.get("pendulum_8192")
+    cfg["net"] = dict(cfg["net"], hidden=[512, 512, 128], dtype="bf16")
+    M = cfg["B"] * cfg["T"]
+    models, _ = bench.kernel_models(cfg, 1, launched=("gemm_tn", "gemm_nt_mask", "gemm_tn_nt"))
+    assert models["gemm_tn_nt"] == ("hbm", 2.0 * (2 * 512 + 128) * M / 1e9, bench.PEAK_HBM_GBS, "GB/s")
+    assert models["gemm_tn"] == ("hbm", 2.0 * (512 + 512) * M / 1e9, bench.PEAK_HBM_GBS, "GB/s")
+    assert models["gemm_nt_mask"] == ("hbm", (2.0 * 512 + 512 / 4 + 2.0 * 512) * M / 1e9, bench.PEAK_HBM_GBS, "GB/s")
+    cfg["net"]["dtype"] = "fp32"
+    models, _ = bench.kernel_models(cfg, 1, launched=("gemm_tn_nt",))
+    assert models["gemm_tn_nt"] == ("mfma", 4.0 * (512 * 512 + 512 * 128) * M / 1e12, bench.PEAK_SPLIT_TFLOPS, "TFLOP/s")
