@@ -196,7 +196,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         int most = 256;
         if (bfp && l > 0) {
             // 128-wide tiles of the bf16 products: dW and dX share a launch, half of the units' workgroups each, and a chunk
-            // is a whole LDS stage of 128 samples at least (whole steps of the pendulum with 32, 64, 128 and 256 chunks:
+            // but the last is a whole LDS stage of 128 samples at least (whole steps of the pendulum with 32, 64, 128 and 256 chunks:
             // 128-128, 32768 samples 122.6, 113.6, 110.9, 111.8 us; 4096 samples 65.4, then 67.7; 262144 samples 326.7, 246.8,
             // 227.0, 228.9; 512-128, four tiles, 16384 samples 114.9, 113.3, 116.1, 127.9)
             const int want = M / 128 > 1 ? M / 128 : 1;

@@ -92,7 +92,9 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
     // packed h of this wavefront's tiles (group g of 32-sample tile mt, samples 4kg..4kg+3) and, on the first wavefront, a
     // row of the head gradient per lane, asked for 64 samples ahead and the first of them ahead of everything else: a
     // workgroup has two or three such steps, so each load's round trip would be a good part of its time
-    // (128 columns, 32768 samples 12.6 -> 12.0 us)
+    // (128 columns, 32768 samples 12.6 -> 12.0 us).  Wider layers pay for it with a wavefront per SIMD (two instead of three)
+    // and are no slower but around 131072 samples (without / with, us: 256 columns 32768 samples 15.2 / 13.0, 131072 30.9 / 31.6,
+    // 524288 104.4 / 101.6; 512 columns 19.6 / 18.2, 50.1 / 51.3, 194 / 188; 128-512 with five heads 262144 148 / 144)
     uint2 hq[MTS][2][4], hn[MTS][2][4];
     float dn[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto fetch = [&](int m0) {

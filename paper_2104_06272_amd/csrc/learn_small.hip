@@ -417,7 +417,7 @@ __global__ __launch_bounds__(SF_WG) void learn_small_fused(const SmallFusedArgs 
 int small_fused_envs(const EnvDims& ed, const NetShape& ns, int B, int T)
 {
     if (ed.kind != ENV_CATCH || ns.bf16 || ns.L != 2 || ns.dims[1] != SF_H || ns.dims[2] != SF_H || ns.NH != 4) return 0;
-    if (ns.dims[0] > 64) return 0;                       // the board's cells are two 32-row tiles of the dW1 product
+    if (ns.dims[0] > 64) return 0;                       // the board's cells are four 16-row tiles of the dW1 product, one to a wavefront
     for (int E = (B + SF_MAX_WG - 1) / SF_MAX_WG; E <= B && E * T <= SF_MAX_R; ++E)
         if (B % E == 0) return E;
     return 0;

@@ -78,15 +78,16 @@ def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
 
 
 # 64-64 on Catch, the whole update in one launch: 1 to 112 samples per workgroup, ends on and off its tiles of 16, time
-# steps in every remainder of the scan's batches, boards of 2 to 64 cells
-@pytest.mark.parametrize("rows,cols,B,T", [(2, 1, 16, 1), (8, 8, 16, 16), (10, 5, 16, 17), (9, 7, 64, 28), (5, 3, 80, 7), (4, 16, 48, 37), (3, 11, 16, 111)])
+# steps in every remainder of the scan's batches of eight, boards of 2 to 64 cells
+@pytest.mark.parametrize("rows,cols,B,T", [(2, 1, 16, 1), (8, 8, 16, 16), (10, 5, 16, 17), (9, 7, 64, 28), (5, 3, 80, 7), (4, 16, 48, 37), (3, 11, 16, 111),
+                                              (6, 7, 32, 10), (10, 5, 64, 27), (7, 3, 80, 22)])
 def test_small_update_in_one_launch(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_small", [64, 64], B, T, rows=rows, cols=cols, max_steps=rows - 1), 5)
 
 
-# returns and loss in one launch: fewer samples than threads, more than a thread asks for ahead, the most a workgroup holds,
-# time steps in whole batches of the recursion and off them
-@pytest.mark.parametrize("name,B,T", [("catch_4096", 16, 3), ("pendulum_8192", 32, 33), ("maze_16384", 32, 40), ("pendulum_8192", 16, 64), ("catch_4096", 48, 63)])
+# returns and loss in one launch, 16 environments to a workgroup and (T = 17, 31) 8: fewer samples than threads, more than a
+# thread asks for ahead, the most a workgroup holds, time steps in whole batches of the recursion and off them
+@pytest.mark.parametrize("name,B,T", [("catch_4096", 16, 3), ("pendulum_8192", 32, 33), ("maze_16384", 32, 40), ("pendulum_8192", 16, 64), ("catch_4096", 48, 63), ("pendulum_8192", 48, 17), ("maze_16384", 32, 31)])
 def test_returns_and_loss_in_one_launch(gpu, orc, name, B, T):
     env = dict(rows=5, cols=7, max_steps=9) if name.startswith("maze") else {}
     lockstep(gpu, orc, variant(name, [128, 64], B, T, **env), 6)
@@ -530,7 +531,9 @@ def test_first_layer_of_boards_bf16(gpu, orc, name, hidden, B, T, env):
 @pytest.mark.parametrize("name,hidden,B,T,env", [
     ("catch_4096", [128, 128], 48, 7, {}),                   # heads folded in, 128-wide tiles
     ("pendulum_8192", [256, 512], 80, 5, {}),                # and the pendulum's first layer
-    ("maze_16384", [256, 64], 112, 5, dict(rows=9, cols=13, max_steps=16)),     # five heads: a head pass of its own
+    ("maze_16384", [256, 64], 112, 5, dict(rows=9, cols=13, max_steps=16)),     # five heads folded in
+    ("maze_16384", [32, 64], 96, 3, dict(rows=9, cols=13, max_steps=16)),       # five heads above a 32-wide side: a head pass of its own
+    ("maze_16384", [128, 32], 64, 5, dict(rows=9, cols=13, max_steps=16)),      # and on the vector ALU, below 64 columns
     ("catch_4096", [32, 128, 32], 96, 4, {}),                # a 32-wide side: the tiled fp32 products with rounded weights
 ])
 def test_bf16_products_off_the_bf16_matrix_path(gpu, name, hidden, B, T, env):
