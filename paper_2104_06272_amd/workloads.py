@@ -4,7 +4,7 @@ This module holds no arithmetic of the method.  Every random quantity of a run
 (initial env states, maze walls, initial weights, action noise) is drawn by the
 consumer itself from its own counter-based generator, keyed by the seed given
 here, so the same dict fully defines the inputs for both the GPU library and
-the CPU checker used by the tests.
+the CPU oracle used by the tests.
 """
 import copy
 
@@ -21,7 +21,7 @@ def _net(hidden, policy="categorical", dtype="fp32", lam=1.0):
 _CATCH = dict(kind="catch", rows=10, cols=5, max_steps=9)
 
 CONFIGS = {
-    # small Catch: the case the CPU checker finishes in seconds
+    # small Catch: the case the CPU oracle finishes in seconds
     "catch_small": dict(env=_CATCH, net=_net([64, 64]), B=64, T=20, updates=100),
     # headline Catch
     "catch_4096": dict(env=_CATCH, net=_net([256, 256]), B=4096, T=20, updates=1000),
