@@ -134,15 +134,17 @@ def kernel_models(cfg, P, launched=()):
         # first layer's gradient from the states: one read of dZ1
         "first_layer_grad": ("hbm", 4.0 * dims[1] * M / 1e9, PEAK_HBM_GBS, "GB/s"),
     }
-    # bf16 top layer with the heads folded in: its dW product is a launch of its own (gemm_tn_top) that reads
-    # h_{L-1}, h_L and the head gradient and forms dZ_L itself
-    top_fused = "gemm_tn_top" in launched
+    # bf16 layers in whole 256-wide tiles, from the second layer on without a gap: both products in one launch, the top
+    # layer's (gemm_tn_nt_top) with the heads folded in, which forms dZ_L itself, and the others' (gemm_tn_nt_256)
+    top_fused = "gemm_tn_nt_top" in launched
+    tiled = 0
+    while ("gemm_tn_nt_256" in launched or top_fused) and tiled < len(dims) - 2 and dims[tiled + 1] % 256 == 0 and dims[tiled + 2] % 256 == 0:
+        tiled += 1
     # bf16 layers that are not in whole 256-wide tiles: both products in one launch (gemm_tn_nt), the other layers' apart
     on_path = bf16 and B % 64 == 0 and all(h in (128, 256, 512) for h in hid)
     layers = range(1, len(dims) - 1)
     shared = [i for i in layers if on_path and (dims[i] % 256 or dims[i + 1] % 256)]
-    tn_layers = [i for i in layers if i not in shared and not (top_fused and i == layers[-1])]
-    nt_layers = [i for i in layers if i not in shared]
+    tn_layers = nt_layers = [i for i in layers if i not in shared and i > tiled]
     tn = sum(2.0 * dims[i] * dims[i + 1] * M for i in tn_layers)
     nt = sum(2.0 * dims[i] * dims[i + 1] * M for i in nt_layers)
     models["gemm_tn"] = ("mfma", tn / 1e12, mfma_peak, "TFLOP/s")
@@ -151,26 +153,27 @@ def kernel_models(cfg, P, launched=()):
         # 2-byte operands: 2 K N flop per sample against 2 (N + 2 K) B (dX: dY and the relu mask read, dX written)
         # resp. 2 (K + N) B (dW: both operands read) is 170 resp. 256 flop/B for 512-wide layers, below the
         # machine balance of 2500 / 8 = 312 flop/B: both GEMMs sit on the HBM roof, not the matrix-core one
-        # dX of layer i -> i+1: dY read (2 B per entry; not for a fused top layer, which forms it from the head
-        # gradient), the ReLU mask of h_i (flag words, 1/4 B per entry, where the acting kernel writes them: every
-        # layer but a first one that is not 512 wide; else the 2-byte activations), dX written (2 B per entry)
+        # dX of layer i -> i+1: dY read (2 B per entry), the ReLU mask of h_i (flag words, 1/4 B per entry, where the
+        # acting kernel writes them: every layer but a first one that is not 512 wide; else the 2-byte activations), dX
+        # written (2 B per entry)
         def nt_layer_bytes(i):
-            top = top_fused and i == len(dims) - 2
-            dy = (dims[i + 1] / 4.0 + 4.0 * NH) if top else 2.0 * dims[i + 1]
             mask = dims[i] / 4.0 if (i >= 2 or dims[1] == 512) else 2.0 * dims[i]
-            return (dy + mask + 2.0 * dims[i]) * M
+            return (2.0 * dims[i + 1] + mask + 2.0 * dims[i]) * M
         nt_bytes = sum(nt_layer_bytes(i) for i in nt_layers)
         tn_bytes = sum(2.0 * (dims[i] + dims[i + 1]) * M for i in tn_layers)
         if nt / max(nt_bytes, 1.0) < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
             models["gemm_nt_mask"] = ("hbm", nt_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
         if tn / max(tn_bytes, 1.0) < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
             models["gemm_tn"] = ("hbm", tn_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
-    if top_fused:
-        top_flop = 2.0 * dims[-2] * dims[-1] * M
-        top_bytes = (2.0 * (dims[-2] + dims[-1]) + 4.0 * NH) * M
-        models["gemm_tn_top"] = ("mfma", top_flop / 1e12, mfma_peak, "TFLOP/s")
-        if top_flop / top_bytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
-            models["gemm_tn_top"] = ("hbm", top_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
+    # both products of a 256-wide layer: x and dY (the top layer: h_L, its mask words and the head gradient) read, the
+    # mask words of x and dX written
+    for name, which in (("gemm_tn_nt_256", range(1, tiled + 1 - top_fused)), ("gemm_tn_nt_top", [tiled] if top_fused else [])):
+        flop = sum(4.0 * dims[i] * dims[i + 1] * M for i in which)
+        n_bytes = sum((4.25 * dims[i] + 2.0 * dims[i + 1] + (dims[i + 1] / 4.0 + 4.0 * NH if name.endswith("top") else 0)) * M for i in which)
+        if flop:
+            models[name] = ("mfma", flop / 1e12, PEAK_BF16_TFLOPS, "TFLOP/s")
+            if flop / n_bytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
+                models[name] = ("hbm", n_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
     # Both products in one launch, both counted.  Bytes: x and dY read (a top layer's dY may be formed from its activations, as
     # many bytes), dX written but where nothing reads it (the pendulum's first layer in fp32); for narrow layers these take
     # longer than the matrix instructions.  fp32: layers in whole 64-wide tiles, on split operands

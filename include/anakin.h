@@ -255,8 +255,8 @@ int32_t anakin_set_policy_gradient(anakin_t* h, int32_t kind);
  * sums are written separately and added in a fixed order; splits[n_hidden]: the same for the head matrix;
  * splits_walls: bf16 maze nets whose first layer is reduced plane by plane -- chunks of the 2 B time-summed rows of
  * the wall-plane product (splits[0] then counts the agent-plane product's chunks), else 0;
- * dx_rows[l], 1 <= l < n_hidden: samples one workgroup of the weights-resident bf16 dX kernel of layer l+1 walks
- * (it stages 32 at a time), 0 where another kernel runs; bf16_matrix_path: 1 when acting and update of a bf16
+ * dx_rows[l], 1 <= l < n_hidden: samples one workgroup of the dX product of layer l+1 walks where both its products
+ * share a launch in 256-wide tiles (32 at a time), 0 where another kernel runs; bf16_matrix_path: 1 when acting and update of a bf16
  * net run on the matrix-core kernels (packed activations). */
 typedef struct {
     int32_t n_hidden;

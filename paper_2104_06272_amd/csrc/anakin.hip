@@ -271,7 +271,10 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // 256 x 256 tiles where both sides of a layer are multiples of 256: about one workgroup per CU
         for (int l = 1; l < ns.L; ++l)
             if (ns.dims[l] % 256 == 0 && ns.dims[l + 1] % 256 == 0)
-                set(l, (ns.dims[l] / 256) * (ns.dims[l + 1] / 256), 64, 128);   // chunks: pairs of 64-sample stages
+{
+                const int tiles = (ns.dims[l] / 256) * (ns.dims[l + 1] / 256);
+                set(l, tiles, bf16_dx_resident(ns, M, l) ? bf16_dw_chunks(M, ns.dims[l], ns.dims[l + 1], l == ns.L - 1) : 64, 128);
+            }
         const int cells = ed.rows * ed.cols;
         if (ed.kind == ENV_MAZE && cells % 256 == 0 && ns.dims[1] % 256 == 0) {
             const int tiles = (cells / 256) * (ns.dims[1] / 256);
@@ -1035,8 +1038,11 @@ extern "C" int32_t anakin_get_plan(const anakin_t* h, anakin_plan* out)
     out->head_fan = h->head_fan;
     out->bf16_matrix_path = bf16_mfma(h) ? 1 : 0;
     if (out->bf16_matrix_path)
-        for (int l = 1; l < n.L; ++l)
-            out->dx_rows[l] = bf16_dx_resident(n, h->B * h->T, l) ? bf16_dx_rows_per_workgroup(h->B * h->T, n.dims[l], n.dims[l + 1]) : 0;
+        for (int l = 1; l < n.L; ++l) {
+            if (!bf16_dx_resident(n, h->B * h->T, l)) continue;
+            const int stages = h->B * h->T / 32, ranges = bf16_dx_ranges(h->B * h->T, n.dims[l], n.dims[l + 1], h->splits[l]);
+            out->dx_rows[l] = (stages + ranges - 1) / ranges * 32;
+        }
     out->updates_per_unroll = h->n_updates;
     return ANAKIN_OK;
 }

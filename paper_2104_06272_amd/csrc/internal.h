@@ -264,7 +264,8 @@ hipError_t launch_rollout_bf16_behaviour(anakin* h);
 hipError_t launch_replay_bf16(anakin* h, bool bootstrap);
 hipError_t launch_backward_bf16(anakin* h);
 hipError_t launch_refresh_bf16(anakin* h);
-int bf16_dx_rows_per_workgroup(int M, int K, int N);
+int bf16_dw_chunks(int M, int K, int N, bool top);
+int bf16_dx_ranges(int M, int K, int N, int splits);
 bool bf16_top_fused(const NetShape& n, int M);
 bool bf16_dx_resident(const NetShape& n, int M, int l);
 bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);

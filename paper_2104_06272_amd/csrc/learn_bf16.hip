@@ -12,19 +12,16 @@
 // onto that packing, so producers write it with 8-byte stores and consumers
 // read whole operands with 16-byte loads, coalesced across lanes.
 //
+// Layers in whole 256-wide tiles: backward_bf16.hip.  Here:
 //   head_backward_bf16   dZ_L (row-major + packed), partial dWh / dbh
 //   gemm_nt_bf16         dZ_{l-1} = (dZ_l W_l^T) masked by relu'(h_{l-1}), both layouts out
 //   gemm_tn_bf16         partial dW_l = h_{l-1}^T dZ_l (+ column sums), split over samples;
 //                        for the first layer of a Catch board of more than 256 cells x is rebuilt from the states
 //                        (other first layers: first_layer.hip, and mazes in whole 256-wide tiles below)
-#include "gemm.h"
+#include "gemm_bf16.h"
 
 namespace ank {
 
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ f16v mfma_bf16(bf8 a, bf8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ float bfu(uint16_t h) { return bf16_to_f(h); }
 
 // ---------------------------------------------------------------------------
@@ -44,33 +41,6 @@ struct HeadBwdBf16Args {
     const uint16_t* hP; const float* dhead; const uint16_t* wh16;   // wh16: bf16 copy of Wh, [H][NH]
     uint16_t* dzR; uint16_t* dzP; float* partial;                    // partial: [blocks over rows][H*NH + NH]
 };
-
-typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi)
-{
-    bf2v v; v[0] = (__bf16)lo; v[1] = (__bf16)hi;
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// value r of an accumulator tile where its flag in a ReLU mask word (relu_mask_bit) is set, else +0: the flag is
-// spread over the word by a signed one-bit field extract and ANDed onto the value's bits
-__device__ __forceinline__ float keep_if(float x, uint32_t mask_word, int r)
-{
-    const int m = (int)(mask_word << (31 - relu_mask_bit(r))) >> 31;
-    return __builtin_bit_cast(float, __builtin_bit_cast(int, x) & m);
-}
-
-// two ReLU outputs as bfloat16 in a word (never negative, never -0: relu() returns +0 for every non-positive input)
-// -> 0xffff in the halves that are positive, i.e. not zero, and 0 in the others.  Packed 16-bit integer instructions:
-// min(h, 1) is 0 or 1, and 0 - that is 0 or 0xffff.
-__device__ __forceinline__ uint32_t positive_mask_pk(uint32_t w)
-{
-    uint32_t r;
-    const uint32_t zero = 0u, one = 0x00010001u;
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(w), "v"(one));
-    asm("v_pk_sub_u16 %0, %1, %2" : "=v"(r) : "v"(zero), "v"(r));
-    return r;
-}
 
 // SPLIT: at most 128 columns, which two wavefronts have; the other two take the second 32 samples of a step instead of columns
 // that do not exist (128 columns, 32768 samples 12.2 -> 10.0 us; the products of a step with their stores are two thirds of it)
@@ -255,19 +225,11 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
 // ---------------------------------------------------------------------------
 struct GemmNtBf16Args {
     int M, K, N;
-    const uint16_t* dyR;      // [M][N] (tiled kernel), or null
-    const uint16_t* dyP;      // packed [M/8][N][8] (weights-resident kernel)
+    const uint16_t* dyR;      // [M][N]
     const uint16_t* w16;      // [K][N]
     const uint16_t* hP;       // packed h_{l-1}: [M/8][K][8]
     uint16_t* dxR;            // [M][K], or null when no product below reads the row-major form
     uint16_t* dxP;            // [M/8][K][8]
-    // top layer of the weights-resident kernel: dY = dZ_L is not read but formed from the head gradient,
-    // dZ_L[m][j] = relu'(hTop[m][j]) * sum_k dhead[m][k] Wh[j][k]
-    const uint32_t* maskTop;  // ReLU mask words of h_L (relu_mask_index)
-    const uint32_t* maskLo;   // ReLU mask words of h_{l-1}, or null: the mask is then taken from hP
-    const float* dhead;       // [M][NHP]
-    const uint16_t* wh16;     // bf16 copy of Wh: [N][NH]
-    int NH, NHP;
 };
 
 constexpr int NB_BK = 128;
@@ -370,233 +332,7 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
 }
 __global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body(a, (int)blockIdx.x); }
 
-// ---------------------------------------------------------------------------
-// The same product as a persistent workgroup with the weights in registers: wavefront w of eight
-// keeps the 32 output columns 32w.. of a 256-column block of W (NR/4 registers per lane, the B
-// operand of every step), dY streams through LDS 32 rows at a time, double buffered, and nothing
-// but dY, the mask and the result crosses the memory system.  The kernel is HBM-bound by design:
-// about 4 bytes per output element.
-// dY is read in its sample-packed form, the one its producer writes for the dW product anyway, and
-// turned into rows on the way into LDS: a loader thread takes one 16-byte piece (eight samples of
-// one column) and stores its eight values into eight rows.  So dZ_l exists in one layout only, and
-// the result is written packed only.  NR: reduction length N (256 or 512); K a multiple of 256; M a
-// multiple of 32.
-// ---------------------------------------------------------------------------
 typedef uint32_t u32x4_l __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2_l __attribute__((ext_vector_type(2)));
-constexpr int NRES_WG = 512;
-constexpr int NRES_RT = 32;             // rows per stage
-
-template <int NR, bool HEADS>
-__global__ __launch_bounds__(NRES_WG) void gemm_nt_bf16_res(const GemmNtBf16Args a, const int rows_per_block)
-{
-    constexpr int LD = NR + 8;                                   // row stride in bf16: eight rows cover all banks
-    constexpr int KS = NR / 16;                                  // MFMA steps
-    constexpr int NQ = (NRES_RT / 8) * NR / NRES_WG;             // 16-byte pieces per thread and stage: 4 groups x NR columns
-    constexpr int TJ = NR / 256;                                 // HEADS: 32-column tiles of dZ_L a wavefront forms per stage
-    extern __shared__ uint4 smem4[];
-    uint16_t* As0 = reinterpret_cast<uint16_t*>(smem4);
-    uint16_t* As1 = As0 + NRES_RT * LD;
-    __shared__ uint4 Ahl[2][64];                                 // HEADS: head gradient of a stage's 32 rows as (hi, lo) bfloat16 terms
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
-    int rb_, cb_;
-    xcd_map((int)blockIdx.x, (a.M + rows_per_block - 1) / rows_per_block, a.K / 256, rb_, cb_);   // column blocks of the same rows share dY in one L2
-    const int i0 = cb_ * 256;
-    const int i = i0 + wave * 32 + l32;                          // this lane's output column
-    const int m_begin = rb_ * rows_per_block;
-    const int m_end = m_begin + rows_per_block < a.M ? m_begin + rows_per_block : a.M;
-    if (m_begin >= a.M) return;
-    bf8 wreg[KS];
-#pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2) wreg[s2] = *reinterpret_cast<const bf8*>(a.w16 + (size_t)i * NR + 16 * s2 + 8 * kg);
-    // loader: piece p = q * NRES_WG + tid is sample group p / NR of the stage, column p % NR
-    // Two register sets of staged pieces: those of stage s + 2 are requested while stage s is computed, so a load
-    // has two stage times to come back (one stage is shorter than the memory latency under load, and this kernel
-    // lives on the HBM roof).  The relu mask of stage s + 1 is requested one stage ahead for the same reason.
-    // HEADS: what is staged is the ReLU mask word of h_L for each 32-column tile jt of the wavefront's columns
-    // instead (16 flags, one per accumulator value), and going to LDS means one MFMA per tile, d (hi, lo) against
-    // (Wh, Wh), masked by them
-    u32x4_l stA[NQ], stB[NQ];
-    __shared__ uint4 WhB[HEADS ? NR : 1];                        // row j of Wh, eight entries (zero past NH): the B operand of column j
-    if (HEADS) {
-        for (int j = tid; j < NR; j += NRES_WG) {
-            uint32_t w8[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w8[k] = k < a.NH ? (uint32_t)a.wh16[(size_t)j * a.NH + k] : 0u;
-            WhB[j] = make_uint4(w8[0] | (w8[1] << 16), w8[2] | (w8[3] << 16), w8[4] | (w8[5] << 16), w8[6] | (w8[7] << 16));
-        }
-    }
-    auto fetch = [&](u32x4_l (&st)[NQ], int m0) {
-        if (HEADS) {
-#pragma unroll
-            for (int jt = 0; jt < TJ; ++jt)
-                st[0][jt] = a.maskTop[relu_mask_index((size_t)(m0 >> 5), kg, NR, wave * (NR / 8) + 32 * jt + l32)];
-            return;
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int p = q * NRES_WG + tid;
-            st[q] = *reinterpret_cast<const u32x4_l*>(a.dyP + ((size_t)((m0 >> 3) + p / NR) * NR + p % NR) * 8);
-        }
-    };
-    // par (HEADS): which half of Ahl holds the head gradient of the stage being stored
-    auto store = [&](const u32x4_l (&st)[NQ], uint16_t* buf, int par) {
-        if (HEADS) {
-            const uint4 a1v = Ahl[par][lane];
-            const bf8 a1 = *reinterpret_cast<const bf8*>(&a1v);
-#pragma unroll
-            for (int jt = 0; jt < TJ; ++jt) {
-                f16v acc1;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc1[r] = 0.0f;
-                const uint4 wv = WhB[wave * (NR / 8) + 32 * jt + l32];
-                acc1 = mfma_bf16(a1, *reinterpret_cast<const bf8*>(&wv), acc1);
-                uint16_t* dst = buf + (4 * kg) * LD + wave * (NR / 8) + 32 * jt + l32;
-                const uint32_t bits = st[0][jt];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const uint32_t p01 = cvt_pk_bf16(keep_if(acc1[4 * g], bits, 4 * g), keep_if(acc1[4 * g + 1], bits, 4 * g + 1));
-                    const uint32_t p23 = cvt_pk_bf16(keep_if(acc1[4 * g + 2], bits, 4 * g + 2), keep_if(acc1[4 * g + 3], bits, 4 * g + 3));
-                    dst[(8 * g + 0) * LD] = (uint16_t)p01; dst[(8 * g + 1) * LD] = (uint16_t)(p01 >> 16);
-                    dst[(8 * g + 2) * LD] = (uint16_t)p23; dst[(8 * g + 3) * LD] = (uint16_t)(p23 >> 16);
-                }
-            }
-            return;
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int p = q * NRES_WG + tid;
-            uint16_t* dst = buf + (8 * (p / NR)) * LD + p % NR;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dst[e * LD] = (uint16_t)(st[q][e >> 1] >> ((e & 1) * 16));
-        }
-    };
-    // HEADS: the first 256 threads carry one entry (row tid / 8, head output tid % 8) of the head gradient each, two
-    // stages ahead
-    float dreg = 0.0f;
-    auto fetch_d = [&](int m0) {
-        if (!HEADS || tid >= 256) return;
-        const int k = tid & 7;
-        dreg = k < a.NH ? a.dhead[(size_t)(m0 + (tid >> 3)) * a.NHP + k] : 0.0f;
-    };
-    auto store_d = [&](int par) {
-        if (!HEADS || tid >= 256) return;
-        const uint32_t hi = cvt_pk_bf16(dreg, 0.0f) & 0xffffu;
-        const uint32_t lo = cvt_pk_bf16(dreg - bfu((uint16_t)hi), 0.0f) & 0xffffu;
-        uint16_t* A16 = reinterpret_cast<uint16_t*>(&Ahl[par][0]);
-        A16[tid] = (uint16_t)hi;                                 // row tid / 8 of the hi half, entry tid % 8
-        A16[256 + tid] = (uint16_t)lo;
-    };
-    const uint32_t lane_off = (uint32_t)i * 8u + 4u * kg;        // inside a packed group of eight samples
-    u32x2_l maskA[4], maskB[4];
-    auto fetch_mask = [&](u32x2_l (&mk)[4], int m0) {
-        if (a.maskLo) { mk[0][0] = a.maskLo[relu_mask_index((size_t)(m0 >> 5), kg, a.K, i)]; return; }
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            mk[g] = *reinterpret_cast<const u32x2_l*>(a.hP + ((size_t)((m0 >> 3) + g) * a.K) * 8 + lane_off);
-    };
-    const int m_lastst = m_end - NRES_RT;                        // loads past the end re-read the last stage, unused
-    auto clampm = [&](int m) { return m < m_end ? m : m_lastst; };
-    fetch(stA, m_begin);
-    if (HEADS) {
-        fetch_d(m_begin); store_d(0);
-        fetch_d(clampm(m_begin + NRES_RT)); store_d(1);
-        __syncthreads();
-    }
-    store(stA, As0, 0);
-    fetch(stA, clampm(m_begin + NRES_RT));                       // stage 1, stored at the end of stage 0
-    fetch_mask(maskA, m_begin);
-    __syncthreads();
-    // one stage (of parity par): MFMAs on `cur` with the KS two-byte stores that put stage s + 1 (`st_next`) into
-    // `nxt` spread between them, one per MFMA, so that the LDS writes and the vector work behind them run in the
-    // shadow of the matrix cores instead of in a phase of their own (nobody reads `nxt` during this stage; past the
-    // end the last stage is formed again, unused); then the epilogue with `mask`; the head gradient of stage s + 2
-    // replaces that of stage s
-    auto stage = [&](int m0, int par, const uint16_t* cur, uint16_t* nxt, const u32x2_l (&mask)[4],
-                     u32x4_l (&st_next)[NQ], u32x4_l (&st_fill)[NQ], u32x2_l (&mask_fill)[4]) {
-        fetch(st_fill, clampm(m0 + 2 * NRES_RT));                // two stages ahead
-        fetch_d(clampm(m0 + 2 * NRES_RT));
-        fetch_mask(mask_fill, clampm(m0 + NRES_RT));             // one stage ahead
-        __builtin_amdgcn_sched_barrier(0);
-        // the KS values of this lane for the next stage, two per word, and the rows they go to.  HEADS: the tiles of
-        // dZ_L stay in their accumulators and every word is masked and rounded right before its two stores, between
-        // the MFMAs, instead of all of them ahead of the first one
-        uint32_t pk[HEADS ? 1 : KS / 2];
-        uint16_t* wbase[HEADS ? TJ : 1];
-        f16v accz[HEADS ? TJ : 1];
-        uint32_t zbits[HEADS ? TJ : 1];
-        if (HEADS) {
-            const uint4 a1v = Ahl[par ^ 1][lane];
-            const bf8 a1 = *reinterpret_cast<const bf8*>(&a1v);
-#pragma unroll
-            for (int jt = 0; jt < TJ; ++jt) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) accz[jt][r] = 0.0f;
-                const uint4 wv = WhB[wave * (NR / 8) + 32 * jt + l32];
-                accz[jt] = mfma_bf16(a1, *reinterpret_cast<const bf8*>(&wv), accz[jt]);
-                zbits[jt] = st_next[0][jt];
-                wbase[jt] = nxt + (4 * kg) * LD + wave * (NR / 8) + 32 * jt + l32;
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) pk[4 * q + w] = st_next[q][w];
-            wbase[0] = nxt + (NR == 512 ? tid : 8 * (tid >> 8) * LD + (tid & 255));
-        }
-        // store k: half k % 2 of word k / 2.  HEADS: word 2g + j of a tile holds rows 8g + 4kg + 2j, + 1 of its
-        // column; otherwise piece q = k / 8 is sample group q (NR = 512) or 2q + tid / 256 (NR = 256), sample k % 8
-        uint32_t zword = 0u;
-        auto put = [&](int k) {
-            if (HEADS) {
-                const int jt = k >> 4, kk = k & 15;
-                if ((kk & 1) == 0)
-                    zword = cvt_pk_bf16(keep_if(accz[HEADS ? jt : 0][kk], zbits[HEADS ? jt : 0], kk),
-                                        keep_if(accz[HEADS ? jt : 0][kk + 1], zbits[HEADS ? jt : 0], kk + 1));
-                wbase[HEADS ? jt : 0][(8 * (kk >> 2) + (kk & 3)) * LD] = (uint16_t)(zword >> ((kk & 1) * 16));
-            } else {
-                const uint16_t v = (uint16_t)(pk[HEADS ? 0 : k >> 1] >> ((k & 1) * 16));
-                wbase[0][((NR == 512 ? 8 : 16) * (k >> 3) + (k & 7)) * LD] = v;
-            }
-        };
-        f16v acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-        const uint16_t* a_rd = cur + l32 * LD + 8 * kg;
-        bf8 av0 = *reinterpret_cast<const bf8*>(a_rd), av1 = *reinterpret_cast<const bf8*>(a_rd + 16);
-#pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) {
-            const bf8 an = *reinterpret_cast<const bf8*>(a_rd + 16 * (s2 + 2 < KS ? s2 + 2 : 0));
-            acc = mfma_bf16(av0, wreg[s2], acc);
-            put(s2);
-            av0 = av1; av1 = an;
-            __builtin_amdgcn_sched_barrier(0);                   // keeps the read / MFMA / store order as written
-        }
-        // rows 8g + 4kg + q of the stage, column i: half of one packed group per g
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float o[4];
-            if (a.maskLo) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) o[q] = keep_if(acc[4 * g + q], mask[0][0], 4 * g + q);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float hv = bfu((uint16_t)((mask[g][q >> 1] >> ((q & 1) * 16)) & 0xffffu));
-                    o[q] = hv > 0.0f ? acc[4 * g + q] : 0.0f;
-                }
-            }
-            u32x2_l pv; pv[0] = cvt_pk_bf16(o[0], o[1]); pv[1] = cvt_pk_bf16(o[2], o[3]);
-            *reinterpret_cast<u32x2_l*>(a.dxP + ((size_t)((m0 >> 3) + g) * a.K) * 8 + lane_off) = pv;
-        }
-        store_d(par);
-        __syncthreads();
-    };
-    for (int m0 = m_begin; m0 < m_end; m0 += 2 * NRES_RT) {
-        stage(m0, 0, As0, As1, maskA, stA, stB, maskB);
-        if (m0 + NRES_RT < m_end) stage(m0 + NRES_RT, 1, As1, As0, maskB, stB, stA, maskA);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // dW partials from packed operands.  LDS tiles [sample group][column][8]; every
@@ -732,14 +468,14 @@ __global__ __launch_bounds__(WG) void gemm_tn_nt_bf16(const GemmTnBf16Args t, co
     else gemm_nt_bf16_body(n, b - tn_blocks);
 }
 
-// The same product with a 256 x 256 tile and eight wavefronts (two per SIMD, so one's LDS and
+// The first layer of a maze with a 256 x 256 tile and eight wavefronts (two per SIMD, so one's LDS and
 // global traffic overlaps the other's MFMAs): wavefront (wm, wn) owns rows 128*wm.., columns
 // 64*wn.. of the tile, eight 32 x 32 accumulators, and every 16-byte read from LDS feeds 2 or 4
 // MFMAs.  K and N multiples of 256.
 constexpr int BIGWG = 512;
 constexpr int TB_BG = 8;      // sample groups (of 8) per LDS stage: 64 samples
 
-// XMODE: where the X operand comes from.  0: packed activations in HBM; 1: the agent plane of the
+// XMODE: where the X operand comes from.  1: the agent plane of the
 // maze observation, a one-hot of the agent cell, built from the stage's 64 cell indices which pass
 // through LDS one stage ahead; 2: the wall plane of the maze observation (samples are environments,
 // rows are cells), built from the stage's 64 x 8 wall words which pass through LDS the same way.
@@ -776,7 +512,7 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
     };
     // loader: thread = (column, parity of the sample group), four groups of the stage each
     const int lc = tid & 255, lg = tid >> 8;
-    struct Set { u32x4_l x[TB_BG / 2]; u32x4_l y[TB_BG / 2]; uint32_t pos; };
+    struct Set { u32x4_l y[TB_BG / 2]; uint32_t pos; };
     Set S0, S1;
     auto fetch = [&](Set& st, int i) {
         if (i >= n_stages) i = n_stages - 1;                     // past the end: re-read the last stage, never used
@@ -789,7 +525,6 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
 #pragma unroll
         for (int q = 0; q < TB_BG / 2; ++q) {
             const int g = g0 + 2 * q + lg;
-            if (XMODE == 0) st.x[q] = *reinterpret_cast<const u32x4_l*>(a.xP + ((size_t)g * a.K + i0 + lc) * 8);
             st.y[q] = *reinterpret_cast<const u32x4_l*>(a.dyP + ((size_t)g * a.N + j0 + lc) * 8);
         }
     };
@@ -808,8 +543,7 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
         uint4* Ys = Xs + TB_BG * 256;
         const int gl = 2 * q + lg;
         u32x4_l x;
-        if (XMODE == 0) x = st.x[q];
-        else if (XMODE == 1) {
+        if (XMODE == 1) {
             const u32x4_l p0 = *reinterpret_cast<const u32x4_l*>(&posL[i & 1][gl * 8]);
             const u32x4_l p1 = *reinterpret_cast<const u32x4_l*>(&posL[i & 1][gl * 8 + 4]);
             const uint32_t one = 0x3f80u;
@@ -955,231 +689,6 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
 }
 
 // ---------------------------------------------------------------------------
-// Top layer with the heads folded in.  dZ_L never reaches memory: this kernel and the dX kernel
-// above (HEADS) both form it from the head gradient, stage by stage.  Here the stage's 64 samples
-// x 256 columns of dZ_L go to LDS as the Y operand of dW_L = h_{L-1}^T dZ_L: wavefront w forms
-// columns 32w.. (two MFMAs, d (hi, lo) against (Wh, Wh), masked by the 8-byte pieces of packed
-// h_L it holds in accumulator order).  The workgroups of the first row of tiles also add up
-// dWh = h_L^T d for their 256 columns (the same pieces of h_L are the A operand, see
-// head_backward_bf16 for the sample order) and, in the first of them, dbh; those of the second
-// row the column sums of dZ_L (the layer's bias gradient).  K and N multiples of 256; chunks are
-// pairs of stages (rows % 128 == 0), the last one may be shorter and odd.
-// ---------------------------------------------------------------------------
-struct GemmTnTopArgs {
-    int M, K, N, splits, rows, tiles_i, NH, NHP;
-    const uint16_t* xP;       // packed h_{L-1}: [M/8][K][8]
-    const uint16_t* hTop;     // packed h_L: [M/8][N][8]
-    const float* dhead;       // [M][NHP]
-    const uint16_t* wh16;     // bf16 copy of Wh: [N][NH]
-    float* partial;           // [splits][split_stride]: K x N partial, then the N column sums
-    size_t split_stride;
-    float* head_partial;      // [splits][head_stride]: N x NH partial of dWh, then dbh
-    size_t head_stride;
-};
-
-__global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_top(const GemmTnTopArgs a)
-{
-    extern __shared__ uint4 smem4[];         // [2 stages][X | Y][TB_BG][256] pieces of 8 samples
-    __shared__ uint4 Ahl[2][2][64];          // [stage parity][32-sample tile]: d as (hi, lo), the A operand of the dZ_L product
-    __shared__ uint4 Bhl[2][2][2][64];       // [stage parity][tile][16-sample step]: the same as the B operand of the dWh product
-    __shared__ uint4 WhB[256];               // row j0 + c of Wh, eight entries (zero past NH)
-    // everything derived from the thread index is worked out again at the start of every step from a value the
-    // compiler cannot see through (derive): the dozen loop-invariant addresses it would otherwise keep in registers
-    // across the whole loop do not fit beside the accumulators, and a spilled register is reloaded through the same
-    // in-order counter as the staged loads, which would end their look-ahead
-    int tid = threadIdx.x, lane, wave, wm, wn, l32, kg, lc, lg, col, ds, dk;
-    auto derive = [&]() {
-        asm volatile("" : "+v"(tid));
-        lane = tid & 63; wave = tid >> 6; wm = wave >> 2; wn = wave & 3; l32 = lane & 31; kg = lane >> 5;
-        lc = tid & 255; lg = tid >> 8;                           // X loader: (row of the tile, parity of the sample group)
-        col = wave * 32 + l32;                                   // dZ_L: this lane's column of the tile
-        ds = tid >> 3; dk = tid & 7;                             // head gradient: (sample of the stage, head output)
-    };
-    derive();
-    int split, tile;
-    xcd_map((int)blockIdx.x, a.splits, a.tiles_i * (a.N / 256), split, tile);
-    const int ti = tile % a.tiles_i, tj = tile / a.tiles_i;
-    const int i0 = ti * 256, j0 = tj * 256;
-    // as in gemm_tn_bf16_big, the last chunk may end in the middle of a pair of stages
-    const int n_stages = (a.rows < a.M - split * a.rows ? a.rows : a.M - split * a.rows) >> 6;
-    const int g_first = (split * a.rows) >> 3;
-    // extras, one kind per row of tiles so that no workgroup carries both: the first row adds up dWh (and dbh), the
-    // second (the first, if there is only one) the column sums of dZ_L
-    const bool heads_row = ti == 0, sums_row = ti == (a.tiles_i > 1 ? 1 : 0);
-    struct Set { u32x4_l x[TB_BG / 2]; u32x2_l hq[TB_BG]; float d; };
-    Set S0, S1;
-    auto fetch = [&](Set& st, int i) {
-        if (i >= n_stages) i = n_stages - 1;                     // past the end: re-read the last stage, never used
-        const int g0 = g_first + i * TB_BG;
-        // the head gradient first: it is needed one step before the rest of the set, and loads complete in issue order
-        st.d = dk < a.NH ? a.dhead[((size_t)g0 * 8 + ds) * a.NHP + dk] : 0.0f;
-#pragma unroll
-        for (int q = 0; q < TB_BG / 2; ++q)
-            st.x[q] = *reinterpret_cast<const u32x4_l*>(a.xP + ((size_t)(g0 + 2 * q + lg) * a.K + i0 + lc) * 8);
-#pragma unroll
-        for (int G = 0; G < TB_BG; ++G)
-            st.hq[G] = *reinterpret_cast<const u32x2_l*>(a.hTop + ((size_t)(g0 + G) * a.N + j0 + col) * 8 + 4 * kg);
-    };
-    float bsum = 0.0f, dbsum = 0.0f;
-    f16v acc2;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc2[r] = 0.0f;
-    // the head gradient of a stage -> both operand forms, into the buffers of parity par
-    auto stage_d = [&](const Set& st, int par) {
-        const uint16_t hi = (uint16_t)cvt_pk_bf16(st.d, 0.0f);
-        const uint16_t lo = (uint16_t)cvt_pk_bf16(st.d - bfu(hi), 0.0f);
-        const int mt = ds >> 5, s32 = ds & 31;
-        uint16_t* A16 = reinterpret_cast<uint16_t*>(&Ahl[par][mt][0]);
-        A16[s32 * 8 + dk] = hi;
-        A16[256 + s32 * 8 + dk] = lo;
-        const int g = s32 >> 3, r = s32 & 7, kgs = r >> 2, q = (g & 1) * 4 + (r & 3);
-        uint16_t* B16 = reinterpret_cast<uint16_t*>(&Bhl[par][mt][g >> 1][0]);
-        B16[(kgs * 32 + dk) * 8 + q] = hi;
-        B16[(kgs * 32 + 8 + dk) * 8 + q] = lo;
-    };
-    // part k (0..3) of putting stage i (held in st) into half nb of LDS: X piece k; k even: the dWh MFMAs of 32-sample
-    // tile k / 2; k odd: dZ_L of tile k / 2 (one MFMA, masked, to the Y operand).  counted: a real stage, whose
-    // values go into the sums (the last step stores the last stage once more)
-    auto store_part = [&](const Set& st, int i, int nb, int k, bool counted) {
-        uint4* Xs = smem4 + nb * (2 * TB_BG * 256);
-        uint4* Ys = Xs + TB_BG * 256;
-        const int par = i & 1, mt = k >> 1;
-        *reinterpret_cast<u32x4_l*>(&Xs[(2 * k + lg) * 256 + lc]) = st.x[k];
-        if ((k & 1) == 0) {
-            if (heads_row && counted) {
-                const uint4 b0v = Bhl[par][mt][0][lane], b1v = Bhl[par][mt][1][lane];
-                u32x4_l x0, x1;
-                x0[0] = st.hq[4 * mt][0]; x0[1] = st.hq[4 * mt][1]; x0[2] = st.hq[4 * mt + 1][0]; x0[3] = st.hq[4 * mt + 1][1];
-                x1[0] = st.hq[4 * mt + 2][0]; x1[1] = st.hq[4 * mt + 2][1]; x1[2] = st.hq[4 * mt + 3][0]; x1[3] = st.hq[4 * mt + 3][1];
-                acc2 = mfma_bf16(*reinterpret_cast<const bf8*>(&x0), *reinterpret_cast<const bf8*>(&b0v), acc2);
-                acc2 = mfma_bf16(*reinterpret_cast<const bf8*>(&x1), *reinterpret_cast<const bf8*>(&b1v), acc2);
-            }
-            return;
-        }
-        const uint4 wv = WhB[col];
-        const uint4 a1v = Ahl[par][mt][lane];
-        f16v acc1;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc1[r] = 0.0f;
-        acc1 = mfma_bf16(*reinterpret_cast<const bf8*>(&a1v), *reinterpret_cast<const bf8*>(&wv), acc1);
-        float part = 0.0f;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int G = 4 * mt + g;
-            u32x2_l pv;
-            pv[0] = cvt_pk_bf16(acc1[4 * g], acc1[4 * g + 1]) & positive_mask_pk(st.hq[G][0]);
-            pv[1] = cvt_pk_bf16(acc1[4 * g + 2], acc1[4 * g + 3]) & positive_mask_pk(st.hq[G][1]);
-            *reinterpret_cast<u32x2_l*>(reinterpret_cast<char*>(&Ys[G * 256 + col]) + 8 * kg) = pv;
-            if (sums_row) part += (bfu((uint16_t)pv[0]) + bfu((uint16_t)(pv[0] >> 16))) + (bfu((uint16_t)pv[1]) + bfu((uint16_t)(pv[1] >> 16)));
-        }
-        if (sums_row && counted) bsum += part;
-    };
-    f16v acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    // MFMA step ks (16 samples = groups ks, ks + 1) on half cb of LDS
-    auto compute_step = [&](int cb, int ks) {
-        const uint4* Xs = smem4 + cb * (2 * TB_BG * 256);
-        const uint4* Ys = Xs + TB_BG * 256;
-        bf8 bv[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Ys[(ks + kg) * 256 + wn * 64 + 32 * t + l32]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bf8 av = *reinterpret_cast<const bf8*>(&Xs[(ks + kg) * 256 + wm * 128 + 32 * i + l32]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(av, bv[j], acc[i][j]);
-        }
-    };
-    // one step: the MFMAs of stage i on half i % 2 of LDS with the four parts of stage i + 1 (held in `nxt`) between
-    // them; the head gradient of stage i + 2 (held in `aft`) goes to the operand buffers stage i used; then `nxt` is
-    // refilled with stage i + 3
-    auto step = [&](Set& nxt, const Set& aft, int i) {
-        derive();
-        const int cb = i & 1;
-        const bool counted = i + 1 < n_stages;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            store_part(nxt, i + 1, cb ^ 1, k, counted);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_step(cb, 2 * k);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        stage_d(aft, cb);
-        if (i + 2 < n_stages) dbsum += aft.d;
-        fetch(nxt, i + 3);
-        __syncthreads();
-    };
-    fetch(S0, 0);                                             // in this order (see gemm_tn_bf16_big)
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(S1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (tid < 256) {
-        uint32_t w8[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w8[k] = k < a.NH ? (uint32_t)a.wh16[(size_t)(j0 + tid) * a.NH + k] : 0u;
-        WhB[tid] = make_uint4(w8[0] | (w8[1] << 16), w8[2] | (w8[3] << 16), w8[4] | (w8[5] << 16), w8[6] | (w8[7] << 16));
-    }
-    reinterpret_cast<uint4*>(Bhl)[tid] = make_uint4(0, 0, 0, 0);  // output columns 16..31 of the dWh product stay zero
-    __syncthreads();
-    stage_d(S0, 0); stage_d(S1, 1);
-    dbsum += S0.d + (n_stages > 1 ? S1.d : 0.0f);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) store_part(S0, 0, 0, k, true);
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(S0, 2);
-    __syncthreads();
-    int i = 0;
-    for (; i + 1 < n_stages; i += 2) {                        // no branch between the two steps (see gemm_tn_bf16_big)
-        step(S1, S0, i);
-        step(S0, S1, i + 1);
-    }
-    if (i < n_stages) step(S1, S0, i);
-    float* out = a.partial + (size_t)split * a.split_stride;
-#pragma unroll
-    for (int tr = 0; tr < 4; ++tr)
-#pragma unroll
-        for (int tc = 0; tc < 2; ++tc) {
-            const int j = j0 + wn * 64 + tc * 32 + l32;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i0 + wm * 128 + tr * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
-                out[(size_t)i * a.N + j] = acc[tr][tc][r];
-            }
-        }
-    if (!heads_row && !sums_row) return;
-    // column sums: the two lanes of a column add up in a fixed order; dWh: accumulator rows are columns j of the
-    // tile, accumulator columns k (hi terms) and 8 + k (lo terms)
-    float* red = reinterpret_cast<float*>(smem4);               // [256]
-    float* Sw = red + 256;                                      // [256 columns][16]
-    float* Sd = Sw + 256 * 16;                                  // [64 samples][8]
-    if (sums_row && kg == 1) red[col] = bsum;
-    if (heads_row) {
-        if (l32 < 16) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) Sw[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * 16 + l32] = acc2[r];
-        }
-        Sd[ds * 8 + dk] = dbsum;
-    }
-    __syncthreads();
-    if (sums_row && kg == 0) out[(size_t)a.K * a.N + j0 + col] = bsum + red[col];
-    if (!heads_row) return;
-    float* hout = a.head_partial + (size_t)split * a.head_stride;
-    if (tid < 256)
-        for (int k = 0; k < a.NH; ++k) hout[(size_t)(j0 + tid) * a.NH + k] = Sw[tid * 16 + k] + Sw[tid * 16 + 8 + k];
-    if (tj == 0 && tid < a.NH) {
-        float sum = 0.0f;
-        for (int i = 0; i < 64; ++i) sum += Sd[i * 8 + tid];
-        hout[(size_t)a.N * a.NH + tid] = sum;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Maze first layer.  The observation has three one-hot planes (paper section 2.1 style grid
 // world: walls, agent, goal) and only the agent plane changes within an unroll, so
 //   dW1[wall cell c]  = sum_b walls[b][c] * S[b],   S[b] = sum_t dZ1[t][b]   (B samples, not B*T)
@@ -1238,27 +747,32 @@ hipError_t launch_refresh_bf16(anakin* h)
 // ---------------------------------------------------------------------------
 // backward through all layers for a bf16 network
 // ---------------------------------------------------------------------------
-// Rows of dZ_l (samples) one workgroup of the weights-resident bf16 dX kernel walks, in stages of NRES_RT rows;
-// 0 when the layer's shape goes to the tiled kernel instead.  At most 256 row ranges per 256-column block of W.
-int bf16_dx_rows_per_workgroup(int M, int K, int N)
+// A layer with K inputs and N outputs whose products run side by side in one launch (backward_bf16.hip), a workgroup per
+// compute unit: chunks of the dW product at most, and row ranges of the dX product beside `splits` of them.
+static bool bf16_dx_shape(int M, int K, int N) { return (N == 256 || N == 512) && K % 256 == 0 && M % 32 == 0; }
+int bf16_dw_chunks(int M, int K, int N, bool top)
 {
-    if (!((N == 256 || N == 512) && K % 256 == 0 && M % NRES_RT == 0)) return 0;
-    const int tiles = M / NRES_RT;
-    const int blocks = tiles < 256 ? tiles : 256;
-    return ((tiles + blocks - 1) / blocks) * NRES_RT;
+    const int tiles = (K / 256) * (N / 256), most = (top ? 144 : 128) / tiles, want = M / 512;
+    if (most < 1) return 1;
+    return most <= 64 || want >= most ? most : want > 64 ? want : 64;
+}
+int bf16_dx_ranges(int M, int K, int N, int splits)
+{
+    const int rest = 256 - splits * (K / 256) * (N / 256), most = rest / (K / 256) > 1 ? rest / (K / 256) : 1;
+    return M / 32 < most ? M / 32 : most;
 }
 
-// Whether the dX product of layer l + 1 (reading dZ_l, l >= 1) runs as the weights-resident kernel.  That kernel reads
-// and writes the packed layout only, so it is used only where the product below it (which reads its output) does too.
+// Whether both products of layer l + 1 (reading dZ_l, l >= 1) run in that launch.  It reads and writes the packed layout
+// only, so it is used only where the product below it (which reads its output) does too.
 bool bf16_dx_resident(const NetShape& n, int M, int l)
 {
     if (l < 1 || l >= n.L) return false;
-    if (bf16_dx_rows_per_workgroup(M, n.dims[l], n.dims[l + 1]) == 0) return false;
+    if (!bf16_dx_shape(M, n.dims[l], n.dims[l + 1])) return false;
     return l == 1 || bf16_dx_resident(n, M, l - 1);
 }
 
 // Whether the top layer's products form dZ_L themselves (no head pass, no dZ_L in memory): both sides of the layer
-// multiples of 256, the dX product weights-resident.
+// multiples of 256, both products in one launch.
 bool bf16_top_fused(const NetShape& n, int M)
 {
     if (!n.bf16 || n.L < 2 || n.NH > 8) return false;
@@ -1315,19 +829,19 @@ hipError_t launch_backward_bf16(anakin* h)
         const int tiles = t.tiles_i * ((t.N + tile - 1) / tile);
         const dim3 grid = big ? dim3(tiles * t.splits) : dim3(tiles, t.splits);
         const size_t lds = (size_t)2 * (big ? 2 * TB_BG * 256 : TB_G * 128) * sizeof(uint4);   // 256-tile kernel: two stages
-        // X operand of the 256-tile kernel: packed activations, the agent plane (one-hot of the cell), or generic rows
+        // X operand of the 256-tile kernel: the agent plane (one-hot of the cell) or the wall plane
         const int cells = h->env.rows * h->env.cols;
-        const int xmode = !t.use_obs ? 0 : (h->env.kind == ENV_MAZE && t.obs_row0 == cells && t.K == cells) ? 1 : 2;
+        const int xmode = (h->env.kind == ENV_MAZE && t.obs_row0 == cells && t.K == cells) ? 1 : 2;
+        if (big && !t.use_obs) return hipErrorInvalidValue;
         if (big && xmode == 2 && !(h->env.kind == ENV_MAZE && t.obs_row0 == 0 && t.K == cells && h->B % 64 == 0)) return hipErrorInvalidValue;
-        const void* fn = big ? (xmode == 0 ? reinterpret_cast<const void*>(gemm_tn_bf16_big<0>) : xmode == 1 ? reinterpret_cast<const void*>(gemm_tn_bf16_big<1>)
+        const void* fn = big ? (xmode == 1 ? reinterpret_cast<const void*>(gemm_tn_bf16_big<1>)
                                                                                                               : reinterpret_cast<const void*>(gemm_tn_bf16_big<2>))
                              : (t.use_obs ? reinterpret_cast<const void*>(gemm_tn_bf16<true>) : reinterpret_cast<const void*>(gemm_tn_bf16<false>));
         hipError_t e2 = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e2 != hipSuccess) return e2;
         ProfScope prof(h, name);
         if (big) {
-            if (xmode == 0) hipLaunchKernelGGL(gemm_tn_bf16_big<0>, grid, dim3(BIGWG), lds, h->stream, t);
-            else if (xmode == 1) hipLaunchKernelGGL(gemm_tn_bf16_big<1>, grid, dim3(BIGWG), lds, h->stream, t);
+            if (xmode == 1) hipLaunchKernelGGL(gemm_tn_bf16_big<1>, grid, dim3(BIGWG), lds, h->stream, t);
             else hipLaunchKernelGGL(gemm_tn_bf16_big<2>, grid, dim3(BIGWG), lds, h->stream, t);
         } else {
             if (t.use_obs) hipLaunchKernelGGL(gemm_tn_bf16<true>, grid, dim3(WG), lds, h->stream, t);
@@ -1380,33 +894,35 @@ hipError_t launch_backward_bf16(anakin* h)
         t.bias_out = t.partial + (size_t)t.K * t.N; t.bias_stride = t.split_stride;
         t.obs = obs_src();
         t.sP = nullptr; t.T = h->T; t.env_block = 0;
-        const bool big = l > 0 && t.K % 256 == 0 && t.N % 256 == 0 && t.rows % 128 == 0;
-        if (l == n.L - 1 && top_fused) {
-            GemmTnTopArgs u;
-            u.M = M; u.K = t.K; u.N = t.N; u.splits = t.splits; u.rows = t.rows; u.tiles_i = t.K / 256;
-            u.NH = n.NH; u.NHP = n.NHP;
-            u.xP = t.xP; u.hTop = actP(l); u.dhead = at<const float>(h, L.dhead);
-            u.wh16 = at<const uint16_t>(h, L.w16_src) + n.wh_off;
+        const bool resident = bf16_dx_resident(n, M, l);         // both products, 256-wide tiles
+        const bool big = l > 0 && t.K % 256 == 0 && t.N % 256 == 0;
+        if (big) {
+            const bool top = l == n.L - 1 && top_fused;
+            BwdBf16Args u = {};
+            u.M = M; u.K = t.K; u.N = t.N; u.NH = n.NH; u.NHP = n.NHP; u.splits = t.splits;
+            u.ranges = resident ? bf16_dx_ranges(M, t.K, t.N, t.splits) : 0;
+            u.rev = (n.L - 1 - l) % 2 == 0;
+            u.xP = t.xP; u.dyP = t.dyP; u.hTop = actP(l); u.maskTop = at<const uint32_t>(h, L.mask[l]);
+            // the mask of the layer below as flag words where the acting kernel writes them (every layer it runs
+            // on the matrix cores; the first layer only at 512 columns)
+            u.maskLo = (l - 1 >= 1 || n.dims[1] == 512) ? at<const uint32_t>(h, L.mask[l - 1]) : nullptr;
+            u.dhead = at<const float>(h, L.dhead);
+            u.wh16 = at<const uint16_t>(h, L.w16_src) + n.wh_off; u.w16 = at<const uint16_t>(h, L.w16_src) + n.w_off[l];
+            u.dxP = dzP(l - 1);
             u.partial = t.partial; u.split_stride = t.split_stride;
             u.head_partial = at<float>(h, L.part[n.L]); u.head_stride = (size_t)t.N * n.NH + n.NH;
-            const size_t lds = (size_t)2 * 2 * TB_BG * 256 * sizeof(uint4);   // two stages
-            if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_bf16_top), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
-            ProfScope prof(h, "gemm_tn_top");
-            hipLaunchKernelGGL(gemm_tn_bf16_top, dim3(u.tiles_i * (u.N / 256) * u.splits), dim3(BIGWG), lds, h->stream, u);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        const bool both = l > 0 && !big && !(l == n.L - 1 && top_fused) && !bf16_dx_resident(n, M, l);   // one launch for both products
-        if (!(l == n.L - 1 && top_fused) && !both && (e = run_tn(t, big, l == 0 ? "gemm_tn_obs" : "gemm_tn")) != hipSuccess) return e;
-        if (l > 0) {
+            ProfScope prof(h, !resident ? "gemm_tn" : top ? "gemm_tn_nt_top" : "gemm_tn_nt_256");
+            if ((e = launch_backward_bf16_tiles(u, top, resident, h->stream)) != hipSuccess) return e;
+        } else if (l == 0 && (e = run_tn(t, false, "gemm_tn_obs")) != hipSuccess) return e;
+        if (l > 0 && !resident) {
+            const bool both = !big;                              // one launch for both products
             GemmNtBf16Args g;
             g.M = M; g.K = n.dims[l]; g.N = n.dims[l + 1];
-            g.dyR = needs_rows(l) ? dzR(l) : nullptr;
-            g.dyP = dzP(l);
+            g.dyR = dzR(l);
             g.w16 = at<const uint16_t>(h, L.w16_src) + n.w_off[l];
             g.hP = actP(l - 1);
             g.dxR = needs_rows(l - 1) ? dzR(l - 1) : nullptr;
             g.dxP = dzP(l - 1);
-            const int rows_per_block = bf16_dx_rows_per_workgroup(g.M, g.K, g.N);
             ProfScope prof(h, both ? "gemm_tn_nt" : "gemm_nt_mask");
             if (both) {
                 t.tiles_i = (t.K + 127) / 128;
@@ -1415,23 +931,6 @@ hipError_t launch_backward_bf16(anakin* h)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
                 if (e != hipSuccess) return e;
                 hipLaunchKernelGGL(gemm_tn_nt_bf16, dim3(tn + ((g.M + 127) / 128) * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
-            } else if (bf16_dx_resident(n, M, l)) {
-                const size_t lds2 = (size_t)2 * NRES_RT * (g.N + 8) * sizeof(uint16_t);
-                const bool top = l == n.L - 1 && top_fused;      // dZ_L comes out of the head gradient inside the kernel
-                g.maskTop = at<const uint32_t>(h, L.mask[l]); g.dhead = at<const float>(h, L.dhead);
-                // the mask of the layer below as flag words where the acting kernel writes them (every layer it runs
-                // on the matrix cores; the first layer only at 512 columns)
-                g.maskLo = (l - 1 >= 1 || n.dims[1] == 512) ? at<const uint32_t>(h, L.mask[l - 1]) : nullptr;
-                g.wh16 = at<const uint16_t>(h, L.w16_src) + n.wh_off; g.NH = n.NH; g.NHP = n.NHP;
-                const void* fn = g.N == 512 ? (top ? reinterpret_cast<const void*>(gemm_nt_bf16_res<512, true>) : reinterpret_cast<const void*>(gemm_nt_bf16_res<512, false>))
-                                            : (top ? reinterpret_cast<const void*>(gemm_nt_bf16_res<256, true>) : reinterpret_cast<const void*>(gemm_nt_bf16_res<256, false>));
-                e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-                if (e != hipSuccess) return e;
-                const dim3 grid(((g.M + rows_per_block - 1) / rows_per_block) * (g.K / 256));
-                if (g.N == 512 && top) hipLaunchKernelGGL((gemm_nt_bf16_res<512, true>), grid, dim3(NRES_WG), lds2, h->stream, g, rows_per_block);
-                else if (g.N == 512) hipLaunchKernelGGL((gemm_nt_bf16_res<512, false>), grid, dim3(NRES_WG), lds2, h->stream, g, rows_per_block);
-                else if (top) hipLaunchKernelGGL((gemm_nt_bf16_res<256, true>), grid, dim3(NRES_WG), lds2, h->stream, g, rows_per_block);
-                else hipLaunchKernelGGL((gemm_nt_bf16_res<256, false>), grid, dim3(NRES_WG), lds2, h->stream, g, rows_per_block);
             } else {
                 const size_t lds2 = (size_t)2 * 128 * NB_LD * sizeof(uint16_t);
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);

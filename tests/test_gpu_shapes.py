@@ -654,3 +654,43 @@ def test_updates_of_one_layer_in_chunks_of_many_pieces_bf16(gpu, orc):
     g.learn(); o.learn_n(2)
     PT.assert_learn_close(g, o, TOL_BF16, n_updates=2)
     g.close()
+
+
+# both products of bf16 layers in whole 256-wide tiles in one launch: every width of either side, with and without the mask
+# words of the layer below (a first layer of 256 has none), three, four and five heads; 2, 6, 30, 74 and 238 stages of 32
+# samples, so that chunks and row ranges have one, an even and an odd number of them, fewer than the loads run ahead, and more
+@pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (192, 5), (64, 37), (448, 17)])
+@pytest.mark.parametrize("name,hidden", [
+    ("catch_4096", [256, 256]), ("pendulum_8192", [512, 256]), ("catch_4096", [256, 512]), ("pendulum_8192", [512, 512]),
+    ("catch_4096", [256, 512, 256]), ("maze_16384", [256, 256]), ("maze_16384", [512, 512, 512]),
+])
+def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
+    """The update's gradient against binary64 on the stored forward pass.  What differs is the rounding of dZ to bfloat16,
+    once per layer from the top down to the region's own: up to 2^-9 of an entry, 2^-9 / sqrt(3) in the root mean square, and
+    independent from layer to layer, so that n of them leave sqrt(n) 2^-9 / sqrt(3) of a sum whose terms have either sign; the
+    bound is sqrt(3) times that.  The head matrix meets its gradient in two terms, 2^-17 of an entry.  A stage less of the 238
+    would cost a part in fifteen (1 / sqrt(238)) of such a sum."""
+    cfg = variant(name, hidden, B, T, "bf16")
+    M = B * T
+    print(f"[256-wide tiles] {name} {hidden} {B} x {T}", flush=True)
+    g = gpu.Anakin(cfg, seed=29)
+    plan = g.plan()
+    assert plan["bf16_matrix_path"] == 1 and all(r > 0 for r in plan["dx_rows"][1:]), plan
+    theta = g.get_params() + (0.05 * np.random.default_rng(29).standard_normal(g.P)).astype(np.float32)
+    g.set_params(theta)
+    g.rollout()
+    g.learn()
+    tr, got = g.trajectory(), g.get_grads()
+    if name.startswith("maze"):
+        walls = np.unpackbits(g.get_walls().view(np.uint8), axis=1, bitorder="little").astype(bool)
+        _, ref = PT.np_maze_backward_from_stored(cfg, theta, walls, (tr["state_s0"][:T] & 0xffff).astype(np.int64), tr["act"], tr["head"][:-1], tr["action"], tr["adv"], tr["ret"])
+    else:
+        d = PT.np_head_gradient(cfg, tr["head"][:T].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
+        X = PT.bf16_round_np(PT.np_observation(cfg, tr).astype(np.float32))
+        ref = PT.np_backward_from_stored(cfg, PT.bf16_round_np(theta), X, [a.reshape(M, -1) for a in tr["act"]], d)
+    g.close()
+    for rname, sl in PT.param_regions(cfg)[0]:
+        err = PT.rel(got[sl], ref[sl])
+        bound = 2.0 ** -15 if rname in ("Wh", "bh") else 2.0 ** -9 * (len(hidden) + 1 - int(rname[1])) ** 0.5
+        print(f"  {rname} {err:.1e} of {bound:.1e}", flush=True)
+        assert err <= bound, (rname, err, bound)
