@@ -175,14 +175,14 @@ def kernel_models(cfg, P, launched=()):
             if flop / n_bytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
                 models[name] = ("hbm", n_bytes / 1e9, PEAK_HBM_GBS, "GB/s")
     # Both products in one launch, both counted.  Bytes: x and dY read (a top layer's dY may be formed from its activations, as
-    # many bytes), dX written but where nothing reads it (the pendulum's first layer in fp32); for narrow layers these take
-    # longer than the matrix instructions.  fp32: layers in whole 64-wide tiles, on split operands
+    # many bytes), dX written but where nothing reads it (the first layer in fp32, pendulum and Catch's small board); for narrow
+    # layers these take longer than the matrix instructions.  fp32: layers in whole 64-wide tiles, on split operands
     if on_path:
         both, peak = sum(4.0 * dims[i] * dims[i + 1] * M for i in shared), PEAK_BF16_TFLOPS
         both_bytes = sum(2.0 * (2 * dims[i] + dims[i + 1]) * M for i in shared)
     else:
         both, peak = tn + nt, PEAK_SPLIT_TFLOPS
-        both_bytes = sum(4.0 * (dims[i] + dims[i + 1] + (0 if kind == "pendulum" and i == 1 else dims[i])) * M for i in layers)
+        both_bytes = sum(4.0 * (dims[i] + dims[i + 1] + (0 if kind != "maze" and i == 1 else dims[i])) * M for i in layers)
     if both:
         models["gemm_tn_nt"] = ("mfma", both / 1e12, peak, "TFLOP/s")
         if both / (peak * 1e12) < both_bytes / (PEAK_HBM_GBS * 1e9):

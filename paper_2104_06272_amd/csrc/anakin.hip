@@ -253,7 +253,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         const int most = 512 / (ns.dims[1] / 128), want = M / 128 > 1 ? M / 128 : 1;
         set(0, 1, want < most ? want : most, 64);
     }
-    if (const int s = first_fused_splits(ns, ed.kind, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
+    if (const int s = first_fused_splits(ns, ed, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
     if (ns.L == 1 && ((ed.kind == ENV_PENDULUM && !bfp) || one_layer_shape(ns, ed))) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
     if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {

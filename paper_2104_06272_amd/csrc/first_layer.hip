@@ -2,7 +2,8 @@
 // observation of a grid environment is a 0/1 board with one or two cells set per changing plane, so dW_1 = X^T dZ_1 needs
 // no X in memory: the board is rebuilt from the 4-byte state of a sample, as the 0/1 operand of the matrix instruction.
 //
-//   first_layer_onehot   Catch: rows = cells, two of them set per sample.  Maze: the agent's plane, one cell per sample,
+//   first_layer_onehot   Catch: rows = cells, two of them set per sample (fp32 boards of up to 64 cells above a second layer
+//                        in whole 64-wide tiles: gemm_split.hip instead).  Maze: the agent's plane, one cell per sample,
 //                        and the plane of walls, which is the same all through an unroll and so needs only
 //                        S[b] = sum_t dZ_1[t][b]; the goal's plane has one cell that is always set: the column sums.
 //

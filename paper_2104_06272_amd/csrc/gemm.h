@@ -24,12 +24,14 @@ struct HeadFuse {
     float* head_partial;  // dW product only: [splits][N*NH + NH] partial sums of the head matrix and bias gradients
 };
 
-// pendulum first layer folded into the dX product that forms dZ_1: dW_1[c][i] = sum_m o_c(m) dZ_1[m][i] for the three
-// observation features o = (cos th, sin th, thd) of sample m, db_1[i] = sum_m dZ_1[m][i], one partial per workgroup
-// (dZ_1 itself is then not written: nothing else reads it)
+// first layer folded into the dX product that forms dZ_1, one partial per workgroup along the samples (dZ_1 itself is then not
+// written: nothing else reads it).  Pendulum: dW_1[c][i] = sum_m o_c(m) dZ_1[m][i] for the three observation features
+// o = (cos th, sin th, thd) of sample m.  Catch: the board's cells in place of the features.  db_1[i] = sum_m dZ_1[m][i].
 struct FirstFuse {
-    const float* f0; const float* f1;   // [M] stored angle and angular velocity (null: not folded)
-    float* partial;                     // [workgroups][3*K + K]
+    const float* f0; const float* f1;   // [M] stored angle and angular velocity (null: not the pendulum's)
+    const uint32_t* s0;                 // [M] stored states (null: not Catch's)
+    int cols, paddle_row0, cells;       // Catch: columns of the board, the bottom row's first cell, all cells
+    float* partial;                     // [workgroups][features*K + K]
 };
 // dX[m][i] = (x[m][i] > 0) * sum_j dY[m][j] W[i][j];  W is [K][N] row-major (K = inputs, N = outputs)
 struct GemmNtArgs {

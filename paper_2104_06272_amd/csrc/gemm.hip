@@ -201,8 +201,8 @@ hipError_t launch_backward(anakin* h)
         e = launch_head_backward(h);
         if (e != hipSuccess) return e;
     }
-    // pendulum: the first layer's gradient is summed in the epilogue of the dX product that forms dZ_1
-    const bool first_fused = mfma && first_fused_splits(n, h->env.kind, M) > 0;
+    // pendulum, small Catch boards: the first layer's gradient is summed in the epilogue of the dX product that forms dZ_1
+    const bool first_fused = mfma && first_fused_splits(n, h->env, M) > 0;
     for (int l = n.L - 1; l >= 0; --l) {
         if (l == 0 && first_fused) continue;
         // boards and the 3-feature pendulum need no GEMM for the first layer
@@ -238,13 +238,16 @@ hipError_t launch_backward(anakin* h)
             g.dx = at<float>(h, L.dz[l - 1]);
             g.bf16 = n.bf16;
             g.hf = t.hf;
-            g.ff = FirstFuse{nullptr, nullptr, nullptr};
+            g.ff = FirstFuse{};
             g.w3 = nullptr;
             if (mfma && split_gemm_shape(n, l)) {
                 // the layer's two products share one launch
                 g.w3 = at<const void>(h, L.w3[l]);
                 if (l == 1 && first_fused) {
-                    g.ff.f0 = at<const float>(h, L.tr_f0); g.ff.f1 = at<const float>(h, L.tr_f1);
+                    if (h->env.kind == ENV_CATCH) {
+                        g.ff.s0 = at<const uint32_t>(h, L.tr_s0);
+                        g.ff.cols = h->env.cols; g.ff.cells = h->env.rows * h->env.cols; g.ff.paddle_row0 = g.ff.cells - h->env.cols;
+                    } else { g.ff.f0 = at<const float>(h, L.tr_f0); g.ff.f1 = at<const float>(h, L.tr_f1); }
                     g.ff.partial = at<float>(h, L.part[0]);
                 }
                 ProfScope prof(h, "gemm_tn_nt");

@@ -18,7 +18,10 @@
 //
 // For the top hidden layer both form dY on the way in from the layer's forward activations and the head gradient
 // (HeadFuse), and gemm_tn also sums the head matrix's gradient.  gemm_nt can keep dZ_1 on chip and add up the first
-// layer's gradient itself (FirstFuse).
+// layer's gradient itself (FirstFuse): the pendulum's three features on the vector ALU, a Catch board of up to 64 cells as a
+// 0/1 operand of the matrix instruction (12 MFMAs more per 32 x 32 results of 6 N/16).  For Catch this took the launch that
+// read dZ_1 again: 256-256, 81920 samples 114.0 us and 22.6 for the first layer -> 115.1 for all; 64-64, 1048576 samples,
+// whole step 499 -> 416 us; 128-128, 65536 samples 106 -> 92; 128-64, 64 samples 34.9 -> 30.1 us.  More cells: below.
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l feeds A[row l%32][k 8 (l/32) .. +7] and B[k ..][col l%32];
 // accumulator register r is D[row 8 (r/4) + 4 (l/32) + r%4][col l%32].
@@ -321,8 +324,8 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
 // costs one scalar instruction instead of eight.
 // ---------------------------------------------------------------------------
 constexpr int NTS_KC = 32;
-constexpr int NTS_SEG = 3072;           // samples whose features are in LDS at a time: 36 KB, within what the dW product takes anyway
-enum : int { FIRST_NONE = 0, FIRST_PENDULUM = 1 };
+constexpr int NTS_SEG = 3072;           // samples whose features are in LDS at a time: 36 KB (Catch 12, and up to 64 of board), within what the dW product takes anyway
+enum : int { FIRST_NONE = 0, FIRST_PENDULUM = 1, FIRST_CATCH = 2 };
 struct STrue { static constexpr bool value = true; };
 struct SFalse { static constexpr bool value = false; };
 
@@ -343,14 +346,18 @@ template <int WN, int MT, int HEADS, int FIRST>
 __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const int tile0, const int tile1, const int by, const int part)
 {
     constexpr int WM = 8 / WN, TR = 32 * MT * WM, PITCH = TR + 2, AP = TR * 4 / SWG;
-    constexpr int MP = MT < 2 ? MT : 2;                          // row tiles per turn of the epilogue
+    constexpr bool CATCH = FIRST == FIRST_CATCH;
+    constexpr int CT = CATCH ? 2 : 1;                            // Catch: tiles of 32 cells (first_fused_splits: at most 64)
+    constexpr int MP = MT < 2 ? MT : 2;                     // row tiles per turn of the epilogue
     static_assert(AP * SWG == TR * 4 && MT % MP == 0, "whole pieces, whole turns");
     extern __shared__ float4 smem_s[];
     u4v_s* As = reinterpret_cast<u4v_s*>(smem_s);                 // [2][3 terms][4 groups of 8 j][PITCH]
     constexpr int HALF = 3 * 4 * PITCH;
     f4v_s* whs = reinterpret_cast<f4v_s*>(As + 2 * HALF);         // HEADS: [N] head weights of a unit, the first four
     float* wh5 = reinterpret_cast<float*>(whs + (HEADS ? a.N : 0));   // HEADS > 4: [N] the fifth
-    float* obsS = wh5 + (HEADS > 4 ? a.N : 0);   // FIRST: [3][NTS_SEG] features of a segment's samples
+    float* obsS = wh5 + (HEADS > 4 ? a.N : 0);   // FIRST: [3][NTS_SEG] features of a segment's samples; Catch: [2][NTS_SEG] cells, 16 bits each
+    uint16_t* cellS = reinterpret_cast<uint16_t*>(obsS);
+    u4v_s* boardS = reinterpret_cast<u4v_s*>(obsS + NTS_SEG);     // Catch: [TR / 16][CT][64] the board as operand
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
     const int N = a.N, NC = N / NTS_KC;
@@ -426,6 +433,12 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
         for (int u = tid; u < (t1 - t0) * TR; u += SWG) {
             int m = t0 * TR + u;
             m = m < a.M ? m : a.M - 1;
+            if (CATCH) {
+                const uint32_t w = a.ff.s0[m];
+                cellS[u] = (uint16_t)(((w >> 8) & 0xffu) * (uint32_t)a.ff.cols + (w & 0xffu));
+                cellS[NTS_SEG + u] = (uint16_t)((uint32_t)a.ff.paddle_row0 + ((w >> 16) & 0xffu));
+                continue;
+            }
             float sn, cs;
             det_sincos(a.ff.f0[m], sn, cs);
             float td = a.ff.f1[m];
@@ -433,7 +446,37 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
             obsS[u] = cs; obsS[NTS_SEG + u] = sn; obsS[2 * NTS_SEG + u] = td;
         }
     };
+    // Catch: the boards of a tile as the A operand of dW_1, for each 16 of its samples and 32 cells, an entry 1 where the ball or
+    // the paddle is in the lane's cell; a lane half has the samples 4 kg.. and 8 + 4 kg.. of the sixteen, in the order in which
+    // the accumulators of dX hold them
+    auto boards = [&](int first) {
+        typedef uint32_t u2v_s __attribute__((ext_vector_type(2)));
+        for (int p = wave; p < TR / 16; p += SWG / 64) {
+            const uint16_t* s = cellS + first + 16 * p + 4 * kg;
+            const u2v_s b0 = *reinterpret_cast<const u2v_s*>(s), b1 = *reinterpret_cast<const u2v_s*>(s + 8);
+            const u2v_s p0 = *reinterpret_cast<const u2v_s*>(s + NTS_SEG), p1 = *reinterpret_cast<const u2v_s*>(s + NTS_SEG + 8);
+            const uint32_t ball[4] = {b0[0], b0[1], b1[0], b1[1]}, pad[4] = {p0[0], p0[1], p1[0], p1[1]}, one = 0x00010001u;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const uint32_t cell = (uint32_t)(32 * ct + l32) * 0x00010001u;
+                u4v_s v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t x, y;                                // 1 in a half whose cell is this lane's, else 0 (a saturating subtraction)
+                    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(x) : "v"(one), "v"(ball[i] ^ cell));
+                    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(y) : "v"(one), "v"(pad[i] ^ cell));
+                    v[i] = (x | y) * 0x3f80u;
+                }
+                boardS[(p * CT + ct) * 64 + lane] = v;
+            }
+        }
+    };
     float gw0 = 0.0f, gw1 = 0.0f, gw2 = 0.0f, gb = 0.0f;
+    f16v_s acc1[CT];                                              // Catch: dW_1
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc1[ct][r] = 0.0f;
     f16v_s acc[MT];
     auto clear = [&]() {
 #pragma unroll
@@ -512,7 +555,7 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     __syncthreads();
     for (int seg = tile0; seg < tile1; seg += NTS_SEG / TR) {
     const int seg1 = FIRST == FIRST_NONE || tile1 - seg < NTS_SEG / TR ? tile1 : seg + NTS_SEG / TR;
-    if (FIRST == FIRST_PENDULUM) { features(seg, seg1); __syncthreads(); }
+    if (FIRST != FIRST_NONE) { features(seg, seg1); __syncthreads(); }
     for (int tile = seg; tile < seg1; ++tile) {
         int c = 0;
         for (; c + 2 < NC; c += 2) {
@@ -521,6 +564,7 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
             step(SFalse(), S0, 1, tile, c + 1);
             __syncthreads();
         }
+        if (CATCH) boards((tile - seg) * TR);
         step(SFalse(), S1, 0, tile, c);
         __syncthreads();
         step(STrue(), S0, 1, tile, c + 1);
@@ -541,6 +585,23 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
 #pragma unroll
                         for (int r = 0; r < 16; ++r) buf_store1(o[u][r], rd, xoff, row_off(k4, mp + u, r));
                 }
+            } else if (CATCH) {
+#pragma unroll
+                for (int u = 0; u < MP; ++u)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {                 // 16 samples: dZ_1 in three terms against the 0/1 board leaves nothing out
+                        u4v_s t1[3];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) split_pair(o[u][8 * j + 2 * q], o[u][8 * j + 2 * q + 1], t1, q);
+                        gb += ((o[u][8 * j] + o[u][8 * j + 1]) + (o[u][8 * j + 2] + o[u][8 * j + 3])) + ((o[u][8 * j + 4] + o[u][8 * j + 5]) + (o[u][8 * j + 6] + o[u][8 * j + 7]));
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct) {
+                            const u4v_s b = boardS[(((wm * MT + mp + u) * 2 + j) * CT + ct) * 64 + lane];
+#pragma unroll
+                            for (int k = 2; k >= 0; --k) acc1[ct] = mfma_s(b, t1[k], acc1[ct]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
             } else {
 #pragma unroll
                 for (int u = 0; u < MP; ++u)
@@ -561,6 +622,43 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
         __syncthreads();
     }
     if (FIRST == FIRST_NONE) break;
+    }
+    if (CATCH) {
+        gb += __shfl_xor(gb, 32, 64);
+        float* red = reinterpret_cast<float*>(As);                // WM > 1: the row groups add up in ascending order
+        float* redb = red + (WM - 1) * WN * CT * 1024;
+        static_assert(((WM - 1) * WN * (CT * 1024 + 32)) * 4 <= 2 * HALF * 16, "the sums fit the operands' LDS");
+        if (WM > 1) {
+            if (wm > 0) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[((wm - 1) * WN + wn) * (CT * 1024) + (ct * 16 + r) * 64 + lane] = acc1[ct][r];
+                if (kg == 0) redb[((wm - 1) * WN + wn) * 32 + l32] = gb;
+            }
+            __syncthreads();
+            if (wm == 0) {
+#pragma unroll
+                for (int w = 0; w < WM - 1; ++w) {
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc1[ct][r] += red[(w * WN + wn) * (CT * 1024) + (ct * 16 + r) * 64 + lane];
+                    gb += redb[(w * WN + wn) * 32 + l32];
+                }
+            }
+        }
+        if (wm == 0 && live) {
+            float* out = a.ff.partial + (size_t)part * ((size_t)a.ff.cells * a.K + a.K) + i;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int cell = 32 * ct + 8 * (r >> 2) + 4 * kg + (r & 3);
+                    if (cell < a.ff.cells) out[(size_t)cell * a.K] = acc1[ct][r];
+                }
+            if (kg == 0) out[(size_t)a.ff.cells * a.K] = gb;
+        }
     }
     if (FIRST == FIRST_PENDULUM) {
         gw0 += __shfl_xor(gw0, 32, 64); gw1 += __shfl_xor(gw1, 32, 64); gw2 += __shfl_xor(gw2, 32, 64); gb += __shfl_xor(gb, 32, 64);
@@ -608,10 +706,11 @@ static hipError_t launch_split_tiles(GemmTnArgs t, const GemmNtArgs& n, int nt_b
     const int tiles_j = t.N / TJ, tn = t.tiles_i * tiles_j * t.splits;
     const int tiles = (n.M + TR - 1) / TR, per = (tiles + nt_blocks - 1) / nt_blocks, bx = (tiles + per - 1) / per, by = (n.K + TC - 1) / TC;
     const size_t lds_tn = (size_t)2 * 3 * 2 * WK * (TI + TJ) * 16;
-    const size_t lds_nt = (size_t)2 * 3 * 4 * (TR + 2) * 16 + (n.hf.hl ? n.N * (n.hf.NH > 4 ? 20 : 16) : 0) + (n.ff.f0 ? NTS_SEG * 12 : 0);
+    const size_t lds_nt = (size_t)2 * 3 * 4 * (TR + 2) * 16 + (n.hf.hl ? n.N * (n.hf.NH > 4 ? 20 : 16) : 0) + (n.ff.f0 ? NTS_SEG * 12 : n.ff.s0 ? NTS_SEG * 4 + TR / 16 * 2048 : 0);
     const size_t lds = lds_tn > lds_nt ? lds_tn : lds_nt;
     // (five heads: the maze, whose first layer is no part of these products)
     auto kern = n.ff.f0 ? (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 4, FIRST_PENDULUM> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 0, FIRST_PENDULUM>)
+              : n.ff.s0 ? (t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 4, FIRST_CATCH> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 0, FIRST_CATCH>)
               : !t.hf.hl ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 0, FIRST_NONE>
               : t.hf.NH > 4 ? gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 5, FIRST_NONE> : gemm_tn_nt_split<WI, WJ, AI, AJ, WK, WN, MT, 4, FIRST_NONE>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -306,11 +306,19 @@ inline int split_nt_blocks(const NetShape& n, int M, int l)
 // the head pass folded into the top layer's products (a pass of its own for the maze's five heads: 128-64, 23920 samples
 // 11.2 + 14.9 us against 18.4 with it folded in; whole steps of mazes of 64 to 512 units 5 to 16 % slower)
 inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 5 && split_gemm_shape(n, n.L - 1); }
-// the pendulum's first-layer gradient can ride in the epilogue of the dX product that forms dZ_1; returns the number of
-// partials that kernel writes (its workgroups along the samples), else 0
+// the first-layer gradient of the pendulum and of Catch boards of up to 64 cells rides in the epilogue of the dX product that
+// forms dZ_1; returns the number of partials that kernel writes (its workgroups along the samples), else 0.  The pass of its own
+// that it replaces reads dZ_1 once more: 20 % of the products' time at 256-256, more in narrower nets (67 nets and batches, whole
+// steps, 1.00 to 1.32 times as fast).  128 cells would take 64 accumulators more of wavefronts that have 256 registers: 12 to 52
+// bytes a lane in scratch in all but the 128-wide tiles, and twice the MFMAs; larger boards keep that pass.
 inline int first_fused_splits(const NetShape& n, int env_kind, int M)
 {
     return env_kind == ENV_PENDULUM && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
+}
+inline int first_fused_splits(const NetShape& n, const EnvDims& ed, int M)
+{
+    if (ed.kind == ENV_CATCH) return ed.rows * ed.cols <= 64 && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
+    return first_fused_splits(n, ed.kind, M);
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B);
