@@ -28,12 +28,12 @@
 //
 // What bounds them: at 256 x 256 a sample costs 0.63 ns of matrix-core time for both products on the whole chip (six
 // MFMAs per product, see above) and 2 to 3 KB of traffic, 0.4 to 0.5 ns at the rate of a copy.  Both products side by side,
-// half the compute units each: 81920 samples 200 -> 117 us, 262144 samples (pendulum) 580 -> 321 us against the binary32
-// kernels they replace.  The matrix-core time of these is 51 and 164 us: by the counters the matrix cores are busy 0.49 and
-// 0.56 of the launch, vector instructions issue in 0.35 and 0.38 of it, LDS is active in a quarter.  300 and 1017 MB are
-// read where reading h1 and h2 once would be 168 and 537: the dW and the dX workgroup of the same samples drift apart, and
-// L2 serves little of the second reading; with the writes that is 3.7 and 3.2 TB/s, 0.6 of a copy.  No single limit is
-// reached; what is left over is the time in which a stage's loads, split and MFMAs wait for each other.
+// half the compute units each: 81920 samples 200 -> 110 us, 262144 samples (pendulum) 580 -> 310 us against the binary32
+// kernels they replace.  The matrix-core time of these is 51 and 164 us at 2.4 GHz, but the clock falls to 1.93 GHz under them
+// (power): of the launch's cycles the matrix cores are busy in 0.62 (pendulum), vector instructions issue in 0.4, a wavefront
+// waits for memory, LDS or a barrier in a quarter.  With every sample read from L2 (the first 4096 over and over) the launches
+// take 2 to 3 % less, so memory is not what bounds them, although 1017 MB are read where reading h1 and h2 once would be 537
+// (the dW and the dX workgroup of the same samples drift apart).
 #include "split_terms.h"
 #include "detmath.h"
 
@@ -41,13 +41,23 @@ namespace ank {
 
 constexpr int SWG = 512;                // eight wavefronts, two per SIMD
 
+// the vector instructions since the last scheduling barrier between the n MFMAs since then, V behind each
+template <int V> __device__ __forceinline__ void spread(int n)
+{
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+}
+
 __device__ __forceinline__ f16v_s mfma_s(u4v_s a, u4v_s b, f16v_s c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8_s, a), __builtin_bit_cast(bf8_s, b), c, 0, 0, 0);
 }
-// the six products, smallest first: terms of a and of b
-constexpr int PROD_A[6] = {0, 2, 1, 1, 0, 0};
-constexpr int PROD_B[6] = {2, 0, 1, 0, 1, 0};
+// the six products: terms of a and of b.  b's small terms are done with first, so that the next stage's can take their registers
+constexpr int PROD_A[6] = {0, 1, 0, 2, 1, 0};
+constexpr int PROD_B[6] = {2, 1, 1, 0, 0, 0};
 
 // ---------------------------------------------------------------------------
 // dW.  A workgroup owns a TI x TJ tile of the product for one chunk of samples and keeps the accumulators in registers.
@@ -56,8 +66,15 @@ constexpr int PROD_B[6] = {2, 0, 1, 0, 1, 0};
 // 16-byte pieces.  WI x WJ wavefronts share the tile, WK of them the samples of a stage.
 // One barrier per stage: while the MFMAs run on one half of LDS the same wavefronts split the next stage's values (asked
 // for a whole stage earlier) into the other half.
+// ROT: the barrier stands before the last MFMAs of a stage, whose operands are in registers by then, so that the reads of the
+// next stage's first operands run beside them; and the split's vector instructions stand one by one between MFMAs rather than
+// by the dozen, since a wavefront whose partner on the SIMD waits at the barrier has only its own MFMAs to cover them.  Both
+// products of 256 x 256 tiles take 5.54 -> 5.11 million cycles (pendulum, 262144 samples: 323 -> 310 us, the clock falling from
+// 1.98 to 1.93 GHz as the matrix cores get busier; Catch, 81920: 112.1 -> 109.8).  The other tiles have fewer MFMAs a stage and
+// lose as often as they gain (256-128, 65536 to 524288 samples 2 % slower; 64-128 with five heads, 524288 samples, 177 -> 358 us
+// for want of registers).
 // ---------------------------------------------------------------------------
-template <int WI, int WJ, int AI, int AJ, int WK, int HEADS>
+template <int WI, int WJ, int AI, int AJ, int WK, int HEADS, bool ROT>
 __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const int split, const int i0, const int j0)
 {
     static_assert(WI * WJ * WK == 8, "eight wavefronts");
@@ -179,42 +196,59 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
         for (int q = 0; q < YP; ++q) fetch_y(st, s, q);
     };
     const int xb = (2 * wk + kg) * TI + wi * AI * 32 + l32, yb = XN + (2 * wk + kg) * TJ + wj * AJ * 32 + l32;
-    // the MFMAs of stage s on half cb of LDS; stage s + 1 (held in nxt) into the other half; nxt refilled with stage s + 3
+    // One step: the MFMAs of stage s on half cb of LDS, stage s + 1 (held in nxt) into the other half, nxt refilled with stage
+    // s + 3.  ROT: the last row of tiles of stage s - 1, whose operands are in registers, then all rows of stage s but the last.
+    u4v_s av[2][3], bv[3][AJ];
+#pragma unroll
+    for (int k = 0; ROT && k < 3; ++k) {
+        av[1][k] = u4v_s{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < AJ; ++j) bv[k][j] = u4v_s{0, 0, 0, 0};
+    }
+    static_assert(AI % 2 == 0, "the last row of tiles is in av[1]");
     auto step = [&](Set& nxt, int cb, int s) {
         const u4v_s* X = lds + cb * HALF + xb;
         const u4v_s* Y = lds + cb * HALF + yb;
-        u4v_s av[2][3], bv[3][AJ];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int j = 0; j < AJ; ++j) bv[k][j] = Y[k * GR * TJ + 32 * j];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) av[0][k] = X[k * GR * TI];
         // A unit of the next stage's split behind every few MFMAs: an MFMA keeps the matrix core busy for 32 cycles and its
         // wavefront for 4.  As a phase of its own the split was not covered by the other wavefront of the SIMD, which sits
         // between the same two barriers.
         constexpr int NM = 6 * AI * AJ;
-        int done = 0;
+        int done = 0, last = 0;
+        auto read_x = [&](int i) {
 #pragma unroll
-        for (int i = 0; i < AI; ++i) {
-            if (i + 1 < AI) {
+            for (int k = 0; k < 3; ++k) av[i & 1][k] = X[k * GR * TI + 32 * i];
+        };
+        auto read_y = [&](int k) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) av[(i + 1) & 1][k] = X[k * GR * TI + 32 * (i + 1)];
-            }
+            for (int j = 0; j < AJ; ++j) bv[k][j] = Y[k * GR * TJ + 32 * j];
+        };
+        if (!ROT) { read_y(2); read_x(0); read_y(1); read_y(0); }
+#pragma unroll
+        for (int v = 0; v < AI; ++v) {
+            const int i = !ROT ? v : v == 0 ? AI - 1 : v - 1;
+            if (ROT || v + 1 < AI) read_x(ROT ? v : v + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int pr = 0; pr < 6; ++pr)
+            for (int pr = 0; pr < 6; ++pr) {
 #pragma unroll
                 for (int j = 0; j < AJ; ++j) {
                     acc[i][j] = mfma_s(av[i & 1][PROD_A[pr]], bv[PROD_B[pr]][j], acc[i][j]);
-                    const int n = (i * 6 + pr) * AJ + j + 1;
+                    const int n = (v * 6 + pr) * AJ + j + 1;
                     if (n * UNITS / NM > done) {
-                        __builtin_amdgcn_sched_barrier(0);
+                        if (!ROT) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (; done < n * UNITS / NM; ++done) unit(nxt, cb ^ 1, s + 1, done, true);
+                        if (ROT) spread<HEADS ? 7 : 4>(n - last);
                         __builtin_amdgcn_sched_barrier(0);
+                        last = n;
                     }
                 }
+                if (ROT && v == 0 && (pr == 5 || PROD_B[pr] != PROD_B[pr < 5 ? pr + 1 : 5])) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_y(PROD_B[pr]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         }
         __syncthreads();
     };
@@ -232,6 +266,10 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
         step(S0, 1, s + 1);
     }
     if (s < n_stages) step(S1, 0, s);
+#pragma unroll
+    for (int pr = 0; ROT && pr < 6; ++pr)
+#pragma unroll
+        for (int j = 0; j < AJ; ++j) acc[AI - 1][j] = mfma_s(av[1][PROD_A[pr]], bv[PROD_B[pr]][j], acc[AI - 1][j]);
     float* out = a.partial + (size_t)split * ((size_t)a.K * a.N + a.N);
     if (WK > 1) {
         // the wavefronts that took other samples of the stages hand their sums over
@@ -342,7 +380,7 @@ __device__ __forceinline__ float buf_load1(rsrc_s r, uint32_t voff, uint32_t sof
 __device__ __forceinline__ f4v_s buf_load4(rsrc_s r, uint32_t voff, uint32_t soff) { return __builtin_bit_cast(f4v_s, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0)); }
 __device__ __forceinline__ void buf_store1(float v, rsrc_s r, uint32_t voff, uint32_t soff) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0); }
 
-template <int WN, int MT, int HEADS, int FIRST>
+template <int WN, int MT, int HEADS, int FIRST, bool ROT>
 __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const int tile0, const int tile1, const int by, const int part)
 {
     constexpr int WM = 8 / WN, TR = 32 * MT * WM, PITCH = TR + 2, AP = TR * 4 / SWG;
@@ -501,7 +539,18 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     // One step: the MFMAs of 32 reduction indices (chunk c) on half par of LDS; the next step's dY (chunk c + 1, held in
     // nxt) into the other half between them, nxt refilled with the step after next's successor; the weights of the same
     // half of the next step asked for.  LAST: the step that completes a tile also asks for the first ReLU masks.
-    auto step = [&](auto LAST, Set& nxt, int par, int tile, int c) {
+    // ROT: the last six, whose operands are in registers, are left to the next step (CONT: a tile's first has none to finish).
+    u4v_s av[2][3];
+    auto read_a = [&](int par, int p) {
+        const u4v_s* A = As + par * HALF + (wm * MT * 32) + l32;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) av[p & 1][k] = A[(k * 4 + 2 * (p / MT) + kg) * PITCH + 32 * (p % MT)];
+    };
+    auto finish = [&]() {
+#pragma unroll
+        for (int pr = 0; pr < 6; ++pr) acc[MT - 1] = mfma_s(av[1][PROD_A[pr]], bw[1][PROD_B[pr]], acc[MT - 1]);
+    };
+    auto step = [&](auto CONT, auto LAST, Set& nxt, int par, int tile, int c) {
         const int cn = c + 1 < NC ? c + 1 : 0;
         const int t3 = c + 3 < NC ? tile : c + 3 < 2 * NC ? tile + 1 : tile + 2;   // (two steps a tile where N is 64)
         const int c3 = c + 3 - (t3 - tile) * NC;
@@ -509,34 +558,30 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
             load_mask(rows_rsrc(a.x, tile * TR, TR, a.M, a.K), 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        const u4v_s* A = As + par * HALF + (wm * MT * 32) + l32;
         // the six MFMAs of a row tile are one dependent chain; the other wavefront of the SIMD fills its gaps
-        constexpr int NM = 12 * MT;
-        u4v_s av[2][3];
-        auto read_a = [&](int buf, int ks, int mt) {
+        constexpr int P0 = ROT && CONT.value ? -1 : 0, NP = 2 * MT - ROT, NM = 6 * (NP - P0);
+        if (!ROT || CONT.value) read_a(par, 0);
+        int done = 0, last = 0;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) av[buf][k] = A[(k * 4 + 2 * ks + kg) * PITCH + 32 * mt];
-        };
-        read_a(0, 0, 0);
-        int done = 0;
-#pragma unroll
-        for (int p = 0; p < 2 * MT; ++p) {
-            const int ks = p / MT, mt = p % MT;
-            if (p + 1 < 2 * MT) read_a((p + 1) & 1, (p + 1) / MT, (p + 1) % MT);
+        for (int p = P0; p < NP; ++p) {
+            const int q = p < 0 ? 2 * MT - 1 : p, ks = q / MT, mt = q % MT;
+            if (p >= 0 && p + 1 < 2 * MT) read_a(par, p + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int pr = 0; pr < 6; ++pr) {
-                acc[mt] = mfma_s(av[p & 1][PROD_A[pr]], bw[ks][PROD_B[pr]], acc[mt]);
-                const int n = p * 6 + pr + 1;
+                acc[mt] = mfma_s(av[q & 1][PROD_A[pr]], bw[ks][PROD_B[pr]], acc[mt]);
+                const int n = (p - P0) * 6 + pr + 1;
                 if (n * UNITS / NM > done) {
-                    __builtin_amdgcn_sched_barrier(0);
+                    if (!ROT) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (; done < n * UNITS / NM; ++done) unit(nxt, par ^ 1, cn, done, t3, c3);
+                    if (ROT) spread<4>(n - last);
                     __builtin_amdgcn_sched_barrier(0);
+                    last = n;
                 }
             }
             if (mt == MT - 1) {
-                load_b(ks, 2 * cn + ks);
+                load_b(ks, p < 0 ? 2 * c + 1 : 2 * cn + ks);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -555,19 +600,29 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
     __syncthreads();
     for (int seg = tile0; seg < tile1; seg += NTS_SEG / TR) {
     const int seg1 = FIRST == FIRST_NONE || tile1 - seg < NTS_SEG / TR ? tile1 : seg + NTS_SEG / TR;
-    if (FIRST != FIRST_NONE) { features(seg, seg1); __syncthreads(); }
+    if (FIRST != FIRST_NONE) {
+        if (seg > tile0) __syncthreads();                         // the last segment's are still read
+        features(seg, seg1);
+        __syncthreads();
+    }
     for (int tile = seg; tile < seg1; ++tile) {
-        int c = 0;
-        for (; c + 2 < NC; c += 2) {
-            step(SFalse(), S1, 0, tile, c);
+        if (ROT) read_a(0, 0);
+        step(SFalse(), SFalse(), S1, 0, tile, 0);
+        __syncthreads();
+        for (int c = 1; c + 1 < NC; c += 2) {
+            step(STrue(), SFalse(), S0, 1, tile, c);
             __syncthreads();
-            step(SFalse(), S0, 1, tile, c + 1);
+            step(STrue(), SFalse(), S1, 0, tile, c + 1);
             __syncthreads();
         }
-        if (CATCH) boards((tile - seg) * TR);
-        step(SFalse(), S1, 0, tile, c);
+        if (CATCH) boards((tile - seg) * TR);                     // (the last tile's are read before the barrier above)
+        step(STrue(), STrue(), S0, 1, tile, NC - 1);
         __syncthreads();
-        step(STrue(), S0, 1, tile, c + 1);
+        if (ROT) {
+            finish();
+            load_b(1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const rsrc_s rx = rows_rsrc(a.x, tile * TR, TR, a.M, a.K), rd = rows_rsrc(a.dx, tile * TR, TR, a.M, a.K);
 #pragma unroll
         for (int mp = 0; mp < MT; mp += MP) {
@@ -594,12 +649,13 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
 #pragma unroll
                         for (int q = 0; q < 4; ++q) split_pair(o[u][8 * j + 2 * q], o[u][8 * j + 2 * q + 1], t1, q);
                         gb += ((o[u][8 * j] + o[u][8 * j + 1]) + (o[u][8 * j + 2] + o[u][8 * j + 3])) + ((o[u][8 * j + 4] + o[u][8 * j + 5]) + (o[u][8 * j + 6] + o[u][8 * j + 7]));
+                        u4v_s b[CT];
 #pragma unroll
-                        for (int ct = 0; ct < CT; ++ct) {
-                            const u4v_s b = boardS[(((wm * MT + mp + u) * 2 + j) * CT + ct) * 64 + lane];
+                        for (int ct = 0; ct < CT; ++ct) b[ct] = boardS[(((wm * MT + mp + u) * 2 + j) * CT + ct) * 64 + lane];
 #pragma unroll
-                            for (int k = 2; k >= 0; --k) acc1[ct] = mfma_s(b, t1[k], acc1[ct]);
-                        }
+                        for (int k = 2; k >= 0; --k)
+#pragma unroll
+                            for (int ct = 0; ct < CT; ++ct) acc1[ct] = mfma_s(b[ct], t1[k], acc1[ct]);
                         __builtin_amdgcn_sched_barrier(0);
                     }
             } else {
@@ -619,10 +675,10 @@ __device__ __forceinline__ void gemm_nt_split_body(const GemmNtArgs& a, const in
             }
         }
         clear();
-        __syncthreads();
     }
     if (FIRST == FIRST_NONE) break;
     }
+    if (FIRST != FIRST_NONE && WM > 1) __syncthreads();           // the sums go where operands are read
     if (CATCH) {
         gb += __shfl_xor(gb, 32, 64);
         float* red = reinterpret_cast<float*>(As);                // WM > 1: the row groups add up in ascending order
@@ -684,10 +740,11 @@ template <int WI, int WJ, int AI, int AJ, int WK, int WN, int MT, int HEADS, int
 __global__ __launch_bounds__(SWG) void gemm_tn_nt_split(const GemmTnArgs t, const GemmNtArgs n, const int tn_blocks, const int tiles_j,
                                                         const int nt_bx, const int tiles_per_block)
 {
+    constexpr bool ROT = WI * AI == 8;                            // tiles of 256 x 256
     int b = (int)blockIdx.x;
     if (b < tn_blocks) {
         const int tile = b % (t.tiles_i * tiles_j), split = b / (t.tiles_i * tiles_j);
-        gemm_tn_split_body<WI, WJ, AI, AJ, WK, HEADS>(t, split, (tile % t.tiles_i) * 32 * WI * AI, (tile / t.tiles_i) * 32 * WJ * AJ);
+        gemm_tn_split_body<WI, WJ, AI, AJ, WK, HEADS, ROT>(t, split, (tile % t.tiles_i) * 32 * WI * AI, (tile / t.tiles_i) * 32 * WJ * AJ);
         return;
     }
     b -= tn_blocks;
@@ -695,7 +752,7 @@ __global__ __launch_bounds__(SWG) void gemm_tn_nt_split(const GemmTnArgs t, cons
     const int tiles = (n.M + TR - 1) / TR, bx = b % nt_bx, by = b / nt_bx;
     int t0 = bx * tiles_per_block, t1 = t0 + tiles_per_block < tiles ? t0 + tiles_per_block : tiles;
     asm("" : "+s"(t0), "+s"(t1));                                 // (the division above is done in vector registers)
-    gemm_nt_split_body<WN, MT, HEADS, FIRST>(n, t0, t1, by, bx);
+    gemm_nt_split_body<WN, MT, HEADS, FIRST, ROT>(n, t0, t1, by, bx);
 }
 
 template <int WI, int WJ, int AI, int AJ, int WK, int WN, int MT>
