@@ -290,8 +290,9 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         set(ns.L, 1, ns.bf16 ? 256 : 512, 32);                      // (bf16: no more than the two-level sum below would take)
         one_stage = true;
     }
-    if (heads_fused_shape(ns) || (bfp && bf16_top_fused(ns, M))) {
-        // the head gradients come out of the top layer's dW product: same chunks, one partial per chunk
+    if (heads_fused_shape(ns) || (bfp && (bf16_top_fused(ns, M) || bf16_top_fold(ns)))) {
+        // the head gradients come out of the top layer's dW product: same chunks, one partial per chunk (never more than the
+        // head pass had)
         splits[ns.L] = splits[ns.L - 1]; quanta[ns.L] = quanta[ns.L - 1]; one_stage = true;
     }
     while (!one_stage && fan < 16 && (M / q32) % (splits[ns.L] * fan * 2) == 0 && M / (splits[ns.L] * fan * 2) >= 2 * q32) fan *= 2;

@@ -24,10 +24,8 @@
 
 namespace ank {
 
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
-typedef short s2v __attribute__((ext_vector_type(2)));
 typedef short s4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_c;
 typedef __attribute__((address_space(3))) u4v lds_u4;
@@ -64,12 +62,6 @@ template <int N> __device__ __forceinline__ void wait_loads_barrier()
     static_assert(N < 64, "vmcnt has six bits");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
-// the flags of pair P of a ReLU mask word (relu_mask_bit: low half in bit P, high half in bit 16 + P) as 0xffff / 0 in the halves
-__device__ __forceinline__ uint32_t mask_pair(uint32_t w, int P)
-{
-    const s2v v = __builtin_bit_cast(s2v, w) << (short)(15 - P);
-    return __builtin_bit_cast(uint32_t, v >> (short)15);
-}
 __device__ __forceinline__ f16v zero16()
 {
     f16v z;
@@ -97,18 +89,6 @@ struct Cursor {
     const char* p; ptrdiff_t step;
     __device__ __forceinline__ void next(bool more) { p += more ? step : 0; }
 };
-// row j of the head matrix, eight entries (zero past NH)
-__device__ __forceinline__ u4v head_row(const uint16_t* wh16, int NH, int j)
-{
-    uint32_t w8[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w8[k] = (uint32_t)wh16[(size_t)j * NH + (k < NH ? k : 0)];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w8[k] = k < NH ? w8[k] : 0u;
-    u4v r; r[0] = w8[0] | (w8[1] << 16); r[1] = w8[2] | (w8[3] << 16); r[2] = w8[4] | (w8[5] << 16); r[3] = w8[6] | (w8[7] << 16);
-    return r;
-}
-
 // ---------------------------------------------------------------------------
 // dW: one 256 x 256 tile of one chunk.  Wavefront (wm, wn) owns rows 128 wm.. and columns 64 wn.. of the tile, eight
 // 32 x 32 accumulators.

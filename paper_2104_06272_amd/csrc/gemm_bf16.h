@@ -28,6 +28,27 @@ __device__ __forceinline__ uint32_t positive_mask_pk(uint32_t w)
     return r;
 }
 
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+// row j of the head matrix, eight entries (zero past NH)
+__device__ __forceinline__ u4v head_row(const uint16_t* wh16, int NH, int j)
+{
+    uint32_t w8[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w8[k] = (uint32_t)wh16[(size_t)j * NH + (k < NH ? k : 0)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w8[k] = k < NH ? w8[k] : 0u;
+    u4v r; r[0] = w8[0] | (w8[1] << 16); r[1] = w8[2] | (w8[3] << 16); r[2] = w8[4] | (w8[5] << 16); r[3] = w8[6] | (w8[7] << 16);
+    return r;
+}
+
+typedef short s2v __attribute__((ext_vector_type(2)));
+// the flags of pair P of a ReLU mask word (relu_mask_bit: low half in bit P, high half in bit 16 + P) as 0xffff / 0 in the halves
+__device__ __forceinline__ uint32_t mask_pair(uint32_t w, int P)
+{
+    const s2v v = __builtin_bit_cast(s2v, w) << (short)(15 - P);
+    return __builtin_bit_cast(uint32_t, v >> (short)15);
+}
+
 struct BwdBf16Args {
     int M, K, N, NH, NHP;         // samples (a multiple of 32), inputs and outputs of the layer (multiples of 256), head outputs
     int splits, ranges;           // chunks of the dW product; row ranges of the dX product

@@ -230,31 +230,76 @@ struct GemmNtBf16Args {
     const uint16_t* hP;       // packed h_{l-1}: [M/8][K][8]
     uint16_t* dxR;            // [M][K], or null when no product below reads the row-major form
     uint16_t* dxP;            // [M/8][K][8]
+    const float* dhead;       // TOP: [M][NHP] head gradient
+    const uint32_t* maskTop;  // ReLU flags of h_l (relu_mask_index)
+    const uint16_t* wh16;     // bf16 copy of Wh: [N][NH]
+    int NH, NHP;
+};
+
+// TOP, the layer under the heads: both products form dZ_L themselves from the head gradient, by the product of the head pass
+// above (four MFMAs per 128 samples and wavefront), and it never reaches memory; dX takes the ReLU flag words for h_L, 1/8 of
+// the bytes.  What bounds these products is memory's latency for few samples and its rate for many: a launch and a write and two
+// reads of dZ_L less.  Every tile of 128 rows of dW and of dX forms its dZ_L again, which costs less than that at every width
+// (head pass + products -> products, us, three heads: 128-128, 32768 samples 11.9 + 16.3 -> 19.3, 524288 79.9 + 134.0 -> 151.3;
+// 512-128 11.9 + 32.8 -> 38.0, 79.6 + 408.8 -> 447.7; 128-512 22.0 + 26.6 -> 30.9, 302.5 + 323.2 -> 321.8; 512 samples
+// 9.2 + 9.3 -> 12.0; whole steps 3 to 56 % faster).  Two wavefronts per SIMD are what makes it so: with 307 registers, one,
+// 128-128 took 200 and 512-128 773 us.
+// A thread's row of the head gradient as its two terms:
+struct HeadRow {
+    float d[8];
+    __device__ __forceinline__ void load(const float* dhead, int NH, int NHP, int m, bool ok)
+    {
+        const float* p = dhead + (size_t)(ok ? m : 0) * NHP;
+        const float4 d0 = *reinterpret_cast<const float4*>(p), d1 = *reinterpret_cast<const float4*>(p + (NHP == 8 ? 4 : 0));
+        d[0] = d0.x; d[1] = d0.y; d[2] = d0.z; d[3] = d0.w; d[4] = d1.x; d[5] = d1.y; d[6] = d1.z; d[7] = d1.w;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d[k] = ok && k < NH ? d[k] : 0.0f;
+    }
+    __device__ __forceinline__ void terms(u4v& hi, u4v& lo) const
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            hi[k] = cvt_pk_bf16(d[2 * k], d[2 * k + 1]);
+            lo[k] = cvt_pk_bf16(d[2 * k] - bfu((uint16_t)hi[k]), d[2 * k + 1] - bfu((uint16_t)(hi[k] >> 16)));
+        }
+    }
 };
 
 constexpr int NB_BK = 128;
 constexpr int NB_LD = NB_BK + 8;        // row stride in bf16: 272 B, 16-byte aligned, 8 rows spread over all banks
 
+template <bool TOP>
 __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const int block)
 {
     extern __shared__ uint4 smem4[];
     uint16_t* As = reinterpret_cast<uint16_t*>(smem4);          // [128][NB_LD] dY tile
     uint16_t* Bs = As + 128 * NB_LD;                            // [128][NB_LD] W tile
+    u4v* Ahl = reinterpret_cast<u4v*>(Bs + 128 * NB_LD);        // TOP: [4 blocks of 32 samples][64] head gradient, A operand
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
     int mt_, it_;
     xcd_map(block, (a.M + 127) / 128, (a.K + 127) / 128, mt_, it_);   // the i-tiles of one m-tile share dY
     const int m0 = mt_ * 128, i0 = it_ * 128;
     // loader: 128 rows x 16 pieces of 16 B = 2048 pieces per matrix, 8 per thread
-    uint4 ra[8], rb[8];
+    uint4 ra[TOP ? 1 : 8], rb[8];
+    u4v wr;
+    uint32_t fw[4];
     auto fetch = [&](int j0) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
-            ra[q] = (m0 + row < a.M) ? *reinterpret_cast<const uint4*>(a.dyR + (size_t)(m0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
+            if (!TOP) ra[TOP ? 0 : q] = (m0 + row < a.M) ? *reinterpret_cast<const uint4*>(a.dyR + (size_t)(m0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
             rb[q] = (i0 + row < a.K) ? *reinterpret_cast<const uint4*>(a.w16 + (size_t)(i0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
         }
+        if (TOP) {                                               // this wavefront's 32 columns of h_L: row of Wh, ReLU flags
+            const int col = j0 + wave * 32 + l32;
+            wr = head_row(a.wh16, a.NH, col);
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) fw[mt] = a.maskTop[relu_mask_index(m0 + 32 * mt < a.M ? (size_t)(m0 >> 5) + mt : 0, kg, a.N, col)];
+        }
     };
+    HeadRow hr;
+    if (TOP && tid < 128) hr.load(a.dhead, a.NH, a.NHP, m0 + tid, m0 + tid < a.M);
     fetch(0);
     // the ReLU masks: asked for with the first tile (in the epilogue, where they are used, they were a round trip of their own)
     uint2 hm[2][2][4];
@@ -274,14 +319,34 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    if (TOP) {
+        if (tid < 128) hr.terms(Ahl[(tid >> 5) * 64 + (tid & 31)], Ahl[(tid >> 5) * 64 + 32 + (tid & 31)]);
+        __syncthreads();
+    }
     const uint16_t* a_rd = As + (wm * 64 + l32) * NB_LD + 8 * kg;
     const uint16_t* b_rd = Bs + (wn * 64 + l32) * NB_LD + 8 * kg;
     for (int j0 = 0; j0 < a.N; j0 += NB_BK) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
-            *reinterpret_cast<uint4*>(As + row * NB_LD + kc) = ra[q];
+            if (!TOP) *reinterpret_cast<uint4*>(As + row * NB_LD + kc) = ra[TOP ? 0 : q];
             *reinterpret_cast<uint4*>(Bs + row * NB_LD + kc) = rb[q];
+        }
+        if (TOP) {
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                f16v z;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                z = mfma_bf16(__builtin_bit_cast(bf8, Ahl[mt * 64 + lane]), __builtin_bit_cast(bf8, wr), z);
+                uint16_t* dst = As + (32 * mt + 4 * kg) * NB_LD + wave * 32 + l32;
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {                    // rows 8 (p / 2) + 4 kg + 2 (p % 2) and the next
+                    const uint32_t v = cvt_pk_bf16(z[2 * p], z[2 * p + 1]) & mask_pair(fw[mt], p);
+                    dst[(8 * (p >> 1) + 2 * (p & 1)) * NB_LD] = (uint16_t)v;
+                    dst[(8 * (p >> 1) + 2 * (p & 1) + 1) * NB_LD] = (uint16_t)(v >> 16);
+                }
+            }
         }
         __syncthreads();
         if (j0 + NB_BK < a.N) fetch(j0 + NB_BK);
@@ -317,20 +382,21 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
                 for (int q = 0; q < 4; ++q) {
                     const float hv = bfu((uint16_t)((mw[q >> 1] >> ((q & 1) * 16)) & 0xffffu));
                     o[q] = bf16_bits(hv > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f);
-                    Ts[(rowl + q) * NB_LD + col] = o[q];
+                    if (a.dxR) Ts[(rowl + q) * NB_LD + col] = o[q];
                 }
                 if (ok) *reinterpret_cast<uint2*>(a.dxP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) =
                     make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
             }
         }
+    if (!a.dxR) return;
     __syncthreads();
     for (int p = tid; p < 128 * 16; p += WG) {
         const int row = p >> 4, c = (p & 15) << 3;
-        if (a.dxR && m0 + row < a.M && i0 + c < a.K)
+        if (m0 + row < a.M && i0 + c < a.K)
             *reinterpret_cast<uint4*>(a.dxR + (size_t)(m0 + row) * a.K + i0 + c) = *reinterpret_cast<const uint4*>(Ts + row * NB_LD + c);
     }
 }
-__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body(a, (int)blockIdx.x); }
+__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body<false>(a, (int)blockIdx.x); }
 
 typedef uint32_t u32x4_l __attribute__((ext_vector_type(4)));
 
@@ -353,6 +419,10 @@ struct GemmTnBf16Args {
     // dY over time is written to sP (two bfloat16 terms per entry) on the way; null: chunks are sample ranges
     uint16_t* sP;
     int T, env_block;
+    // TOP: dyP is packed h_L; the head gradient, bf16 Wh [N][NH], and partial sums of the gradients of Wh and its bias
+    const float* dhead; const uint16_t* wh16;
+    int NH, NHP;
+    float* head_partial;      // [splits][N*NH + NH]
 };
 
 constexpr int TB_G = 16;      // sample groups (of 8) per LDS stage: 128 samples
@@ -376,7 +446,7 @@ __device__ __forceinline__ uint4 obs_piece(const ObsSrc& o, int mg, int i, bool 
                       (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16));
 }
 
-template <bool OBS>
+template <bool OBS, bool TOP>
 __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const int tile, const int split)
 {
     extern __shared__ uint4 smem4[];
@@ -397,10 +467,48 @@ __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const
             const bool gok = g < g_end;
             if (OBS) rx[q] = gok ? obs_piece(a.obs, g, a.obs_row0 + i0 + c, i0 + c < a.K) : make_uint4(0, 0, 0, 0);
             else rx[q] = (gok && i0 + c < a.K) ? *reinterpret_cast<const uint4*>(a.xP + ((size_t)g * a.K + i0 + c) * 8) : make_uint4(0, 0, 0, 0);
-            ry[q] = (gok && j0 + c < a.N) ? *reinterpret_cast<const uint4*>(a.dyP + ((size_t)g * a.N + j0 + c) * 8) : make_uint4(0, 0, 0, 0);
+            if (!TOP) ry[q] = (gok && j0 + c < a.N) ? *reinterpret_cast<const uint4*>(a.dyP + ((size_t)g * a.N + j0 + c) * 8) : make_uint4(0, 0, 0, 0);
+        }
+        if (TOP) {                                               // 32 columns per wavefront, in the order in which the product below gives dZ
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int g = g0 + 2 * q + kg;
+                ry[q] = g < g_end ? *reinterpret_cast<const uint4*>(a.dyP + ((size_t)g * a.N + j0 + wave * 32 + l32) * 8) : make_uint4(0, 0, 0, 0);
+            }
         }
     };
+    // TOP: sample 16 j + 8 kg + 4 h + q of a block of 32 sits in row 8 (2 j + h) + 4 kg + q of the A operand, so that a lane's
+    // accumulators are eight consecutive samples of each 16; the B operand of dWh has the two terms in columns 0 and 8 on
+    u4v* Ahl = reinterpret_cast<u4v*>(Ys + TB_G * 128);          // [4][64]
+    uint16_t* Bhl = reinterpret_cast<uint16_t*>(Ahl + 4 * 64);   // [8 steps][2 kg][16 columns][8]
+    HeadRow hr;
+    float db[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    f16v acc2;
+    u4v wr;
+    auto fetch_head = [&](int g0) { if (tid < 128) hr.load(a.dhead, a.NH, a.NHP, g0 * 8 + tid, g0 + (tid >> 3) < g_end); };
+    auto forms = [&]() {
+        if (tid >= 128) return;
+        u4v hi, lo;
+        hr.terms(hi, lo);
+        const int s = tid & 31, row = 8 * (2 * (s >> 4) + ((s >> 2) & 1)) + 4 * ((s >> 3) & 1) + (s & 3);
+        Ahl[(tid >> 5) * 64 + row] = hi; Ahl[(tid >> 5) * 64 + 32 + row] = lo;
+        uint16_t* b = Bhl + (tid >> 3) * 128 + (tid & 7);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            b[k * 8] = (uint16_t)(hi[k >> 1] >> (16 * (k & 1))); b[(8 + k) * 8] = (uint16_t)(lo[k >> 1] >> (16 * (k & 1)));
+            db[k] += hr.d[k];
+        }
+    };
+    if (TOP) {
+        fetch_head(g_begin);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc2[r] = 0.0f;
+        wr = head_row(a.wh16, a.NH, j0 + wave * 32 + l32);
+        forms();
+        fetch_head(g_begin + TB_G);
+    }
     fetch(g_begin);
+    if (TOP) __syncthreads();
     f16v acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -412,9 +520,29 @@ __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const
     const bool live = (i0 + wm * 64 < a.K) && (j0 + wn * 64 < a.N);
     for (int g0 = g_begin; g0 < g_end; g0 += TB_G) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) { const int p = q * WG + tid; Xs[p] = rx[q]; Ys[p] = ry[q]; }
+        for (int q = 0; q < 8; ++q) { const int p = q * WG + tid; Xs[p] = rx[q]; if (!TOP) Ys[p] = ry[q]; }
+        if (TOP) {
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk) {
+                f16v z;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                z = mfma_bf16(__builtin_bit_cast(bf8, Ahl[blk * 64 + lane]), __builtin_bit_cast(bf8, wr), z);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int q = 2 * blk + j;
+                    const uint32_t hw[4] = {ry[q].x, ry[q].y, ry[q].z, ry[q].w};
+                    if (ti == 0) acc2 = mfma_bf16(__builtin_bit_cast(bf8, ry[q]), *reinterpret_cast<const bf8*>(Bhl + ((2 * q + kg) * 16 + (l32 & 15)) * 8), acc2);
+                    uint32_t w[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) w[k] = cvt_pk_bf16(z[8 * j + 2 * k], z[8 * j + 2 * k + 1]) & positive_mask_pk(hw[k]);
+                    Ys[(2 * q + kg) * 128 + wave * 32 + l32] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            }
+        }
         __syncthreads();
         if (g0 + TB_G < g_end) fetch(g0 + TB_G);
+        if (TOP) { forms(); fetch_head(g0 + 2 * TB_G); }
         if (live) {
 #pragma unroll
             for (int ks = 0; ks < TB_G; ks += 2) {                // one MFMA step = 16 samples = 2 groups
@@ -454,18 +582,39 @@ __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const
             }
     }
     if (ti == 0 && a.bias_out && tid < 128 && j0 + tid < a.N) a.bias_out[(size_t)split * a.bias_stride + j0 + tid] = bsum;
+    if (TOP && ti == 0) {
+        float* hout = a.head_partial + (size_t)split * ((size_t)a.N * a.NH + a.NH);
+        float* S = reinterpret_cast<float*>(Xs);                 // [128 columns][16], then [2][8]
+        if (l32 < 16) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) S[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * 16 + l32] = acc2[r];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) db[k] += __shfl_xor(db[k], d, 64);
+        if (lane == 0 && wave < 2) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) S[2048 + wave * 8 + k] = db[k];
+        }
+        __syncthreads();
+        if (tid < 128)
+            for (int k = 0; k < a.NH; ++k) hout[(size_t)(j0 + tid) * a.NH + k] = S[tid * 16 + k] + S[tid * 16 + 8 + k];
+        if (tj == 0 && tid < a.NH) hout[(size_t)a.N * a.NH + tid] = S[2048 + tid] + S[2056 + tid];
+    }
 }
 template <bool OBS>
-__global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a) { gemm_tn_bf16_body<OBS>(a, (int)blockIdx.x, (int)blockIdx.y); }
+__global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a) { gemm_tn_bf16_body<OBS, false>(a, (int)blockIdx.x, (int)blockIdx.y); }
 
 // Both products of a layer that takes the 128-wide tiles, dW workgroups first.  They read the same dZ and neither fills the
 // chip for long: as two launches one after the other they were mostly their own beginnings and ends (128-128, 32768 samples
 // 9.8 + 11.2 -> 14.0 us).
-__global__ __launch_bounds__(WG) void gemm_tn_nt_bf16(const GemmTnBf16Args t, const GemmNtBf16Args n, const int tiles, const int tn_blocks)
+template <bool TOP>
+__global__ __launch_bounds__(WG, 2) void gemm_tn_nt_bf16(const GemmTnBf16Args t, const GemmNtBf16Args n, const int tiles, const int tn_blocks)
 {
     const int b = (int)blockIdx.x;
-    if (b < tn_blocks) gemm_tn_bf16_body<false>(t, b % tiles, b / tiles);
-    else gemm_nt_bf16_body(n, b - tn_blocks);
+    if (b < tn_blocks) gemm_tn_bf16_body<false, TOP>(t, b % tiles, b / tiles);
+    else gemm_nt_bf16_body<TOP>(n, b - tn_blocks);
 }
 
 // The first layer of a maze with a 256 x 256 tile and eight wavefronts (two per SIMD, so one's LDS and
@@ -780,6 +929,12 @@ bool bf16_top_fused(const NetShape& n, int M)
     return bf16_dx_resident(n, M, n.L - 1);
 }
 
+// Whether a top layer in 128-wide tiles forms dZ_L in its products too (above at HeadRow: both sides)
+bool bf16_top_fold(const NetShape& n)
+{
+    return n.bf16 && n.L >= 2 && n.NH <= 8 && (n.dims[n.L] % 256 != 0 || n.dims[n.L - 1] % 256 != 0);
+}
+
 hipError_t launch_backward_bf16(anakin* h)
 {
     const Layout& L = h->lay;
@@ -792,7 +947,8 @@ hipError_t launch_backward_bf16(anakin* h)
     // dZ_l is kept sample-packed; the row-major copy exists only where the tiled dX kernel of layer l + 1 reads it
     auto needs_rows = [&](int l) { return l >= 1 && !bf16_dx_resident(n, M, l); };
     const bool top_fused = bf16_top_fused(n, M) && h->quanta[n.L - 1] == 128 && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
-    if (!top_fused) {   // heads
+    const bool top_fold = bf16_top_fold(n) && h->quanta[n.L] == h->quanta[n.L - 1] && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
+    if (!top_fused && !top_fold) {   // heads
         HeadBwdBf16Args a;
         a.M = M; a.H = n.dims[n.L]; a.NH = n.NH; a.NHP = n.NHP;
         const int stage1 = h->splits[n.L] * h->head_fan;
@@ -894,6 +1050,12 @@ hipError_t launch_backward_bf16(anakin* h)
         t.bias_out = t.partial + (size_t)t.K * t.N; t.bias_stride = t.split_stride;
         t.obs = obs_src();
         t.sP = nullptr; t.T = h->T; t.env_block = 0;
+        const bool fold = top_fold && l == n.L - 1;
+        if (fold) {
+            t.dyP = actP(l);
+            t.dhead = at<const float>(h, L.dhead); t.wh16 = at<const uint16_t>(h, L.w16_src) + n.wh_off; t.NH = n.NH; t.NHP = n.NHP;
+            t.head_partial = at<float>(h, L.part[n.L]);
+        }
         const bool resident = bf16_dx_resident(n, M, l);         // both products, 256-wide tiles
         const bool big = l > 0 && t.K % 256 == 0 && t.N % 256 == 0;
         if (big) {
@@ -923,14 +1085,17 @@ hipError_t launch_backward_bf16(anakin* h)
             g.hP = actP(l - 1);
             g.dxR = needs_rows(l - 1) ? dzR(l - 1) : nullptr;
             g.dxP = dzP(l - 1);
+            if (fold) { g.dhead = t.dhead; g.maskTop = at<const uint32_t>(h, L.mask[l]); g.wh16 = t.wh16; g.NH = n.NH; g.NHP = n.NHP; }
             ProfScope prof(h, both ? "gemm_tn_nt" : "gemm_nt_mask");
             if (both) {
                 t.tiles_i = (t.K + 127) / 128;
                 const int tiles = t.tiles_i * ((t.N + 127) / 128), tn = tiles * t.splits;
-                const size_t lds_t = (size_t)2 * TB_G * 128 * sizeof(uint4), lds_n = (size_t)2 * 128 * NB_LD * sizeof(uint16_t), lds2 = lds_t > lds_n ? lds_t : lds_n;
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+                const size_t lds_t = (size_t)2 * TB_G * 128 * sizeof(uint4) + (fold ? 8192 : 0), lds_n = (size_t)2 * 128 * NB_LD * sizeof(uint16_t) + (fold ? 4096 : 0);
+                const size_t lds2 = lds_t > lds_n ? lds_t : lds_n;
+                const auto kern = fold ? gemm_tn_nt_bf16<true> : gemm_tn_nt_bf16<false>;
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
                 if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(gemm_tn_nt_bf16, dim3(tn + ((g.M + 127) / 128) * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
+                hipLaunchKernelGGL(kern, dim3(tn + ((g.M + 127) / 128) * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
             } else {
                 const size_t lds2 = (size_t)2 * 128 * NB_LD * sizeof(uint16_t);
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);

@@ -679,15 +679,7 @@ def test_updates_of_one_layer_in_chunks_of_many_pieces_bf16(gpu, orc):
     g.close()
 
 
-# both products of bf16 layers in whole 256-wide tiles in one launch: every width of either side, with and without the mask
-# words of the layer below (a first layer of 256 has none), three, four and five heads; 2, 6, 30, 74 and 238 stages of 32
-# samples, so that chunks and row ranges have one, an even and an odd number of them, fewer than the loads run ahead, and more
-@pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (192, 5), (64, 37), (448, 17)])
-@pytest.mark.parametrize("name,hidden", [
-    ("catch_4096", [256, 256]), ("pendulum_8192", [512, 256]), ("catch_4096", [256, 512]), ("pendulum_8192", [512, 512]),
-    ("catch_4096", [256, 512, 256]), ("maze_16384", [256, 256]), ("maze_16384", [512, 512, 512]),
-])
-def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
+def bf16_products_against_binary64(gpu, name, hidden, B, T, whole):
     """The update's gradient against binary64 on the stored forward pass.  What differs is the rounding of dZ to bfloat16,
     once per layer from the top down to the region's own: up to 2^-9 of an entry, 2^-9 / sqrt(3) in the root mean square, and
     independent from layer to layer, so that n of them leave sqrt(n) 2^-9 / sqrt(3) of a sum whose terms have either sign; the
@@ -695,10 +687,10 @@ def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
     would cost a part in fifteen (1 / sqrt(238)) of such a sum."""
     cfg = variant(name, hidden, B, T, "bf16")
     M = B * T
-    print(f"[256-wide tiles] {name} {hidden} {B} x {T}", flush=True)
+    print(f"[bf16 products] {name} {hidden} {B} x {T}", flush=True)
     g = gpu.Anakin(cfg, seed=29)
     plan = g.plan()
-    assert plan["bf16_matrix_path"] == 1 and all(r > 0 for r in plan["dx_rows"][1:]), plan
+    assert plan["bf16_matrix_path"] == 1 and (not whole or all(r > 0 for r in plan["dx_rows"][1:])), plan
     theta = g.get_params() + (0.05 * np.random.default_rng(29).standard_normal(g.P)).astype(np.float32)
     g.set_params(theta)
     g.rollout()
@@ -714,6 +706,31 @@ def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
     g.close()
     for rname, sl in PT.param_regions(cfg)[0]:
         err = PT.rel(got[sl], ref[sl])
-        bound = 2.0 ** -15 if rname in ("Wh", "bh") else 2.0 ** -9 * (len(hidden) + 1 - int(rname[1])) ** 0.5
+        # (a maze's first step has every agent in one cell, samples too alike for their roundings to be independent: n 2^-9 there)
+        alike = T == 1 and name.startswith("maze") and not whole
+        bound = 2.0 ** -15 if rname in ("Wh", "bh") else 2.0 ** -9 * (len(hidden) + 1 - int(rname[1])) ** (1.0 if alike else 0.5)
         print(f"  {rname} {err:.1e} of {bound:.1e}", flush=True)
         assert err <= bound, (rname, err, bound)
+
+
+# both products of bf16 layers in whole 256-wide tiles in one launch: every width of either side, with and without the mask
+# words of the layer below (a first layer of 256 has none), three, four and five heads; 2, 6, 30, 74 and 238 stages of 32
+# samples, so that chunks and row ranges have one, an even and an odd number of them, fewer than the loads run ahead, and more
+@pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (192, 5), (64, 37), (448, 17)])
+@pytest.mark.parametrize("name,hidden", [
+    ("catch_4096", [256, 256]), ("pendulum_8192", [512, 256]), ("catch_4096", [256, 512]), ("pendulum_8192", [512, 512]),
+    ("catch_4096", [256, 512, 256]), ("maze_16384", [256, 256]), ("maze_16384", [512, 512, 512]),
+])
+def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
+    bf16_products_against_binary64(gpu, name, hidden, B, T, whole=True)
+
+
+# the head pass folded into the products of a top layer in 128-wide tiles: every shape of it, three, four and five heads, alone and
+# above another layer; half a stage of 128 samples, one and a half, a last one that is not full, chunks of two and a half
+@pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (448, 17), (2112, 17)])
+@pytest.mark.parametrize("name,hidden", [
+    ("pendulum_8192", [128, 128]), ("catch_4096", [256, 128]), ("pendulum_8192", [512, 128]), ("catch_4096", [128, 256]),
+    ("maze_16384", [128, 512]), ("maze_16384", [128, 128]), ("catch_4096", [128, 128, 128]), ("pendulum_8192", [256, 256, 128]),
+])
+def test_bf16_heads_in_the_products_of_128_wide_tiles(gpu, name, hidden, B, T):
+    bf16_products_against_binary64(gpu, name, hidden, B, T, whole=False)
