@@ -191,6 +191,8 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     auto set = [&](int l, int tiles, int cap, int quantum) { quanta[l] = quantum; splits[l] = pick_splits(M, tiles, cap, quantum); };
     const bool bfp = rollout_bf16_ok(ns, ed, B);
     const int q32 = bfp ? 64 : M % 32 == 0 ? 32 : 16;
+    size_t widths = 0;
+    for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
     for (int l = 0; l < ns.L; ++l) {
         const int tiles = ((ns.dims[l] + 127) / 128) * ((ns.dims[l + 1] + 127) / 128);
         int most = 256;
@@ -199,8 +201,13 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
             // but the last is a whole LDS stage of 128 samples at least (whole steps of the pendulum with 32, 64, 128 and 256 chunks:
             // 128-128, 32768 samples 122.6, 113.6, 110.9, 111.8 us; 4096 samples 65.4, then 67.7; 262144 samples 326.7, 246.8,
             // 227.0, 228.9; 512-128, four tiles, 16384 samples 114.9, 113.3, 116.1, 127.9)
+            // With many samples a workgroup per unit for dW, whose stages wait for memory longer than those of dX (head pass folded
+            // in, both products and the optimiser kernel, 128 or 64 and 256 / tiles chunks: 128-128, 524288 samples 161 and 142 us,
+            // 131072 54.6 and 50.9; 256-128, 524288 284 and 244), with four stages each (81920 samples, 128 and 256 chunks 41.2 and
+            // 42.7) -- not where the scratch could fit the static array: what fitted still does.
             const int want = M / 128 > 1 ? M / 128 : 1;
             most = tiles > 1 ? 64 : 128;
+            if (tiles < 4 && M / 512 > most && widths * 4 * M >= (size_t)ANAKIN_STATIC_SCRATCH_BYTES) most = M / 512 < 256 / tiles ? M / 512 : 256 / tiles;
             if (most > want) most = want;
         }
         set(l, tiles, most, q32);
@@ -238,8 +245,6 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         const int tiles = (ns.dims[1] / 32) * (maze ? 2 : 1), want = M / 64 > 1 ? M / 64 : 1;
         int most = 2048 / tiles < want ? 2048 / tiles : want;
         if (maze && ns.dims[1] <= 64 && 2ll * most * ed.rows * ed.cols > 3ll * M / 2 && most > 1024 / tiles) most = 1024 / tiles;
-        size_t widths = 0;
-        for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
         if (widths * 4 * M < (size_t)ANAKIN_STATIC_SCRATCH_BYTES) {
             const int had = ed.kind == ENV_CATCH && ns.dims[0] < 64 && !ns.bf16 && M % 64 == 0 ? pick_splits(M, 1, 256, 64) : splits[0];
             if (most > had) most = had;

@@ -504,11 +504,13 @@ __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc2[r] = 0.0f;
         wr = head_row(a.wh16, a.NH, j0 + wave * 32 + l32);
-        forms();
-        fetch_head(g_begin + TB_G);
     }
     fetch(g_begin);
-    if (TOP) __syncthreads();
+    if (TOP) {
+        forms();
+        fetch_head(g_begin + TB_G);
+        __syncthreads();
+    }
     f16v acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)

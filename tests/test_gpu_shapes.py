@@ -734,3 +734,9 @@ def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
 ])
 def test_bf16_heads_in_the_products_of_128_wide_tiles(gpu, name, hidden, B, T):
     bf16_products_against_binary64(gpu, name, hidden, B, T, whole=False)
+
+
+# many samples: a chunk per compute unit, the last ones shorter
+@pytest.mark.parametrize("name,hidden,B,T", [("pendulum_8192", [128, 128], 4160, 17), ("catch_4096", [256, 128], 6464, 17)])
+def test_bf16_products_of_128_wide_tiles_in_many_chunks(gpu, name, hidden, B, T):
+    bf16_products_against_binary64(gpu, name, hidden, B, T, whole=False)
