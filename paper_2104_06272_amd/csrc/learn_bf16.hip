@@ -627,23 +627,36 @@ constexpr int BIGWG = 512;
 constexpr int TB_BG = 8;      // sample groups (of 8) per LDS stage: 64 samples
 
 // XMODE: where the X operand comes from.  1: the agent plane of the
-// maze observation, a one-hot of the agent cell, built from the stage's 64 cell indices which pass
-// through LDS one stage ahead; 2: the wall plane of the maze observation (samples are environments,
+// maze observation, a one-hot of the agent cell, built in registers from the stage's 64 cell indices, which pass
+// through LDS (64 rows x 128 columns per wavefront, so that a one-hot operand feeds four MFMAs: three instructions a word,
+// four per MFMA, where a piece through LDS cost a 16-byte store, three reads and ten compares; what was most of its LDS
+// time went that way: 16 x 16 maze, 512 columns, 524288 samples 162 -> 147 us, 256 columns, 131072 samples 37.8 -> 33.0;
+// dZ read once at the rate of a copy is 95 us); 2: the wall plane of the maze observation (samples are environments,
 // rows are cells), built from the stage's 64 x 8 wall words which pass through LDS the same way.
 // Pipeline: LDS holds two stages.  While the MFMAs run on stage i, the same wavefronts put stage
-// i + 1 into the other half -- its four (X, Y) pieces per thread go between the four MFMA steps, so
+// i + 1 into the other half -- its four pieces per thread go between the four MFMA steps, so
 // the LDS stores and the vector work behind them (the one-hot, the sums) run in the shadow of the
 // matrix cores -- and then ask for stage i + 3 into the registers just emptied: every load has two
 // stages to arrive, and there is one barrier per stage.  Chunks are pairs of stages of 64 samples
 // (a.rows % 128 == 0); the last one may be shorter and end after an odd stage.
+// 1 (bfloat16) in the halves of w that equal c's, 0 in the others
+__device__ __forceinline__ uint32_t one_where_equal(uint32_t w, uint32_t c)
+{
+    uint32_t r;
+    const uint32_t one = 0x00010001u, bf1 = 0x3f803f80u, neg = 0xc080c080u;   // 0x3f80 - 0x3f80 * min(w ^ c, 1)
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(w ^ c), "v"(one));
+    asm("v_pk_mad_u16 %0, %1, %2, %3" : "=v"(r) : "v"(r), "v"(neg), "v"(bf1));
+    return r;
+}
 template <int XMODE>
 __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a)
 {
     extern __shared__ uint4 smem4[];         // [2 stages][X | Y][TB_BG][256] pieces of 8 samples
-    __shared__ uint32_t posL[2][64];         // XMODE 1: agent cells of the 64 samples of a stage, double buffered
+    __shared__ __attribute__((aligned(16))) uint16_t posL[4][64];   // XMODE 1: agent cells of the 64 samples of a stage
     __shared__ uint32_t wallsL[2][XMODE == 2 ? 8 : 1][64];   // XMODE 2: the eight wall words of the 64 environments of a stage
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 2, wn = wave & 3, l32 = lane & 31, kg = lane >> 5;
+    constexpr int RT = XMODE == 1 ? 2 : 4, CT = 8 / RT;                  // 32 x 32 tiles of a wavefront
+    const int wm = wave / (8 / CT), wn = wave % (8 / CT), l32 = lane & 31, kg = lane >> 5;
     int split, tile;
     xcd_map((int)blockIdx.x, a.splits, a.tiles_i * (a.N / 256), split, tile);   // the tiles of one split share its samples
     const int ti = tile % a.tiles_i, tj = tile / a.tiles_i;
@@ -686,7 +699,6 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
         for (int e = 0; e < 8; ++e) tsum[q][e] = 0.0f;
     float bsum = 0.0f;
     const bool sums = ti == 0 && a.bias_out != nullptr;
-    const int cell = a.obs_row0 + i0 + lc - a.obs.env.rows * a.obs.env.cols;   // XMODE 1: the cell this thread's row stands for
     // piece q (sample group 2q + lg) of stage i, held in st, -> half nb of LDS; counted: a real stage (not the
     // repeat of the last one that the last step stores), whose dY entries go into the sums
     auto store_piece = [&](const Set& st, int i, int nb, int q, bool counted) {
@@ -694,15 +706,7 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
         uint4* Ys = Xs + TB_BG * 256;
         const int gl = 2 * q + lg;
         u32x4_l x;
-        if (XMODE == 1) {
-            const u32x4_l p0 = *reinterpret_cast<const u32x4_l*>(&posL[i & 1][gl * 8]);
-            const u32x4_l p1 = *reinterpret_cast<const u32x4_l*>(&posL[i & 1][gl * 8 + 4]);
-            const uint32_t one = 0x3f80u;
-            x[0] = ((int)p0[0] == cell ? one : 0u) | ((int)p0[1] == cell ? one << 16 : 0u);
-            x[1] = ((int)p0[2] == cell ? one : 0u) | ((int)p0[3] == cell ? one << 16 : 0u);
-            x[2] = ((int)p1[0] == cell ? one : 0u) | ((int)p1[1] == cell ? one << 16 : 0u);
-            x[3] = ((int)p1[2] == cell ? one : 0u) | ((int)p1[3] == cell ? one << 16 : 0u);
-        } else {
+        if (XMODE == 2) {
             const int c = a.obs_row0 + i0 + lc;                  // this thread's cell: bit c % 32 of wall word c / 32
             const u32x4_l w0 = *reinterpret_cast<const u32x4_l*>(&wallsL[i & 1][XMODE == 2 ? c >> 5 : 0][gl * 8]);
             const u32x4_l w1 = *reinterpret_cast<const u32x4_l*>(&wallsL[i & 1][XMODE == 2 ? c >> 5 : 0][gl * 8 + 4]);
@@ -712,8 +716,8 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
             x[1] = (((w0[2] >> sh) & 1u) * one) | (((w0[3] >> sh) & 1u) * (one << 16));
             x[2] = (((w1[0] >> sh) & 1u) * one) | (((w1[1] >> sh) & 1u) * (one << 16));
             x[3] = (((w1[2] >> sh) & 1u) * one) | (((w1[3] >> sh) & 1u) * (one << 16));
+            *reinterpret_cast<u32x4_l*>(&Xs[gl * 256 + lc]) = x;
         }
-        *reinterpret_cast<u32x4_l*>(&Xs[gl * 256 + lc]) = x;
         *reinterpret_cast<u32x4_l*>(&Ys[gl * 256 + lc]) = st.y[q];
         // column sums in every workgroup (used only where `sums` holds; the workgroups that need them set the pace
         // anyway, and a branch on `sums` here would split the step into many basic blocks)
@@ -749,30 +753,44 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
             for (int e = 0; e < 8; ++e) tsum[q][e] = 0.0f;
         }
     };
-    f16v acc[4][2];
+    uint32_t cell[RT];                                           // XMODE 1: the cells of this lane's rows, in both halves
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int t = 0; t < RT; ++t) cell[t] = (uint32_t)(a.obs_row0 + i0 + wm * 32 * RT + 32 * t + l32 - a.obs.env.rows * a.obs.env.cols) * 0x00010001u;
+    f16v acc[RT][CT];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     // MFMA step ks (16 samples = groups ks, ks + 1) on half cb of LDS
-    auto compute_step = [&](int cb, int ks) {
+    auto compute_step = [&](int cb, int ks, int i) {
         const uint4* Xs = smem4 + cb * (2 * TB_BG * 256);
         const uint4* Ys = Xs + TB_BG * 256;
-        bf8 av[4], bv[2];
+        bf8 av[RT], bv[CT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) av[t] = *reinterpret_cast<const bf8*>(&Xs[(ks + kg) * 256 + wm * 128 + 32 * t + l32]);
+        for (int t = 0; t < CT; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Ys[(ks + kg) * 256 + wn * 32 * CT + 32 * t + l32]);
+        if (XMODE == 1) {
+            const u32x4_l p = *reinterpret_cast<const u32x4_l*>(&posL[i & 3][(ks + kg) * 8]);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Ys[(ks + kg) * 256 + wn * 64 + 32 * t + l32]);
+            for (int t = 0; t < RT; ++t) {
+                u32x4_l x;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+                for (int k = 0; k < 4; ++k) x[k] = one_where_equal(p[k], cell[t]);
+                av[t] = __builtin_bit_cast(bf8, x);
+            }
+        } else {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(av[i], bv[j], acc[i][j]);
+            for (int t = 0; t < RT; ++t) av[t] = *reinterpret_cast<const bf8*>(&Xs[(ks + kg) * 256 + wm * 32 * RT + 32 * t + l32]);
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] = mfma_bf16(av[i], bv[j], acc[i][j]);
     };
     // one step: the MFMAs of stage i on half i % 2 of LDS, stage i + 1 (held in `nxt`) into the other half piece by
     // piece between them; then `nxt` is refilled with stage i + 3 and the cells of stage i + 2 (held in `aft`) go to
-    // the cell buffer that stage i's one-hot was built from
+    // LDS (XMODE 1: not where other wavefronts may still build stage i's one-hot from)
     auto step = [&](Set& nxt, const Set& aft, int i) {
         const int cb = i & 1;
         const bool counted = i + 1 < n_stages;
@@ -780,11 +798,11 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
         for (int q = 0; q < TB_BG / 2; ++q) {
             store_piece(nxt, i + 1, cb ^ 1, q, counted);
             __builtin_amdgcn_sched_barrier(0);
-            compute_step(cb, 2 * q);
+            compute_step(cb, 2 * q, i);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (by_env && ti == 0 && counted && (i + 2) % a.T == 0) flush_time_sum(i + 1);
-        if (XMODE == 1 && tid < 64) posL[cb][tid] = aft.pos & 0xffffu;
+        if (XMODE == 1 && tid < 64) posL[(i + 2) & 3][tid] = (uint16_t)aft.pos;
         if (XMODE == 2) wallsL[cb][XMODE == 2 ? tid & 7 : 0][tid >> 3] = aft.pos;
         fetch(nxt, i + 3);
         __syncthreads();
@@ -797,7 +815,7 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
     fetch(S1, 1);
     __builtin_amdgcn_sched_barrier(0);
     if (XMODE == 1) {
-        if (tid < 64) { posL[0][tid] = S0.pos & 0xffffu; posL[1][tid] = S1.pos & 0xffffu; }
+        if (tid < 64) { posL[0][tid] = (uint16_t)S0.pos; posL[1][tid] = (uint16_t)S1.pos; }
         __syncthreads();
     }
     if (XMODE == 2) {
@@ -820,13 +838,13 @@ __global__ __launch_bounds__(BIGWG) void gemm_tn_bf16_big(const GemmTnBf16Args a
     if (i < n_stages) step(S1, S0, i);                       // an odd stage, outside the loop for the same reason
     float* out = a.partial + (size_t)split * a.split_stride;
 #pragma unroll
-    for (int tr = 0; tr < 4; ++tr)
+    for (int tr = 0; tr < RT; ++tr)
 #pragma unroll
-        for (int tc = 0; tc < 2; ++tc) {
-            const int j = j0 + wn * 64 + tc * 32 + l32;
+        for (int tc = 0; tc < CT; ++tc) {
+            const int j = j0 + wn * 32 * CT + tc * 32 + l32;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int i = i0 + wm * 128 + tr * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
+                const int i = i0 + wm * 32 * RT + tr * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
                 out[(size_t)i * a.N + j] = acc[tr][tc][r];
             }
         }
