@@ -466,7 +466,7 @@ extern "C" int32_t anakin_create(anakin_t** out, const anakin_env_cfg* env, cons
     h->TM_mfma = rollout_pick_tile_mfma(ns, ed, B);
     h->TM_res = rollout_resident_tile(ns, ed.kind, B);
     rollout_pinned_plan(ns, ed, B, h->pinned);
-    h->wide = h->pinned.NB > 0 ? 0 : rollout_wide_groups(ns, ed, B);
+    h->wide = h->pinned.NB > 0 && !wide_before_pinned(ns, B) ? 0 : rollout_wide_groups(ns, ed, B);
     h->bf16_path = rollout_bf16_ok(ns, ed, B) ? 1 : 0;
 
     auto fail = [&](int code) { g_create_error = h->err; delete h; return code; };

@@ -334,6 +334,7 @@ bool vtrace_off_the_actor(const anakin* h, size_t lds);
 bool rollout_small_ok(const anakin* h);
 hipError_t launch_small(anakin* h, const RolloutArgs& args);
 int rollout_wide_groups(const NetShape& net, const EnvDims& env, int B);
+bool wide_before_pinned(const NetShape& net, int B);
 hipError_t launch_wide(anakin* h, const RolloutArgs& args);
 int rollout_resident_tile(const NetShape& net, int env_kind, int B);
 size_t rollout_lds_bytes(const NetShape& net, const EnvDims& env, int TM, int* ldx);

@@ -1829,11 +1829,14 @@ enum class Actor { PINNED, WIDE, SMALL, RESIDENT, OTHER };
 static Actor pick_actor(const anakin* h, bool beside)
 {
     if (h->mode & (ANAKIN_MODE_CANONICAL_ACTING | ANAKIN_MODE_STREAM_WEIGHTS)) return Actor::OTHER;
-    if (h->pinned.NB > 0) return Actor::PINNED;
     // Each of its workgroups has a compute unit to itself: beside a learner it takes half of them at most (decoupled steps,
     // 256-256, T = 16: 256 environments 130 -> 101 us, 512 129.5 -> 119.5, but 1024 130.5 -> 171.6 on all units; 256-512:
     // 247 -> 144, 246 -> 181, 246 -> 248).
-    if (h->wide > 0 && (!beside || h->B / (4 * h->wide) <= 128)) return Actor::WIDE;
+    // Where the pinned kernel, four times as many environments to a unit, could have the net, a quarter (128-256, T = 16, wide and
+    // pinned beside a learner: 256 environments on Catch 89 and 99 us, the pendulum 92 and 106, the 8 x 8 maze 94 and 104; 512 100
+    // and 96, 103 and 104, 108 and 103).
+    if (h->wide > 0 && (!beside || h->B / (4 * h->wide) <= (h->pinned.NB > 0 ? 64 : 128))) return Actor::WIDE;
+    if (h->pinned.NB > 0) return Actor::PINNED;
     // Beside the learner of a small board net a few of its workgroups cost more than they save (decoupled Catch, T = 20: 512
     // environments 57.6 -> 59.2 us, 1024 66.4 -> 67.9, but 2048 83.6 -> 82.1, 4096 110.2 -> 104.3; pendulum 1024 71.0 -> 64.1,
     // 4096 102.8 -> 96.7).

@@ -460,8 +460,8 @@ static bool pinned_share(const NetShape& net, const int* xo, PinnedPlan& p)
     return true;
 }
 
-// Which nets act with this kernel: two or more layers of 64 to 512 units whose blocks fit 4 x 6, and at most one tile of 16
-// environments per compute unit -- beyond that the streaming kernel takes more environments per tile and shares its weight
+// Which nets act with this kernel: two or more layers of 64 to 512 units whose blocks fit 4 x 6 (but rollout_wide.hip's
+// wide_before_pinned), and at most one tile of 16 environments per compute unit -- beyond that the streaming kernel takes more environments per tile and shares its weight
 // stream among them (256-128-64, 8192 environments: 220 us against 208 here, 64-64-64 99 against 109).  Two equal layers
 // keep the kernels that have their width as a constant: eight wavefronts share their one matrix layer, four here
 // (pendulum, 128-128: 89 us against 97; Catch, 64-64: 31.7 against 32.6).

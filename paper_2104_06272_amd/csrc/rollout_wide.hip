@@ -548,7 +548,21 @@ static bool wide_plan(const NetShape& net, const EnvDims& env, int R, WideArgs& 
     return true;
 }
 
-// Which nets: two or more layers that rollout_pinned.hip does not take, in whole blocks of 64, not two equal ones of 64 or 128
+// Where both this kernel and the pinned one can have a net, groups of four are faster under a top layer of 256 units, which all
+// wavefronts share here and four of them there (T = 16, Catch / pendulum / 8 x 8 and 16 x 16 maze, pinned and here: 128-256, 1008
+// environments 76.5 and 64.2 us / 82.7 and 66.2 / 81.8 and 68.9 / 87.1 and 73.0; 64-128-256 90.1 and 77.1 / 97.3 and 81.1; 128-128-256
+// 99.2 and 92.4 / 106.4 and 96.2; 64-256 59.7 and 56.8 / 67.0 and 59.4), not under two of 64 (64-64-256 70.1 and 71.2 on Catch); pairs of
+// groups only where the net has no other layer of 128 (2032 environments, 128-256 77.6 and 74.3 / 83.2 and 77.8, but 64-128-256
+// 90.3 and 90.2, 128-128-256 99.7 and 110.9, 64-256 60.7 and 65.0).
+bool wide_before_pinned(const NetShape& net, int B)
+{
+    if (net.L > 3 || net.dims[net.L] != 256) return false;
+    const int below = net.dims[net.L - 1];
+    if (net.L == 2) return B <= 1024 || below == 128;
+    return B <= 1024 && below == 128;
+}
+
+// Which nets: two or more layers that rollout_pinned.hip does not take (or only behind this kernel, above), in whole blocks of 64, not two equal ones of 64 or 128
 // (1024 environments, resident and here: 128-128 Catch 49 and 66 us, pendulum 51 and 68, maze of 12 x 14 65 and 73; 64-64 29 and
 // 45, 36 and 49, 38 and 51).  Up to 1024 environments in groups of four, up to 2048 in pairs of groups; the pairs not where a
 // layer's outputs leave most SIMDs idle (2032 environments on Catch, the pendulum and the maze, streamed and here: 512-128

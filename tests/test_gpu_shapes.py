@@ -480,6 +480,18 @@ def test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, e
             np.testing.assert_array_equal(x, y)
 
 
+# a top layer of 256 above narrower ones: groups of four environments up to 1024 (beside a learner 256), pairs of them above one
+# layer of 128 up to 2048, and the pinned kernel from there on
+@pytest.mark.parametrize("name,hidden,B,dtype,env", [
+    ("catch_4096", [64, 256], 1024, "fp32", dict(rows=16, cols=12, max_steps=15)), ("catch_4096", [64, 256], 1040, "fp32", dict(rows=16, cols=12, max_steps=15)),
+    ("pendulum_8192", [128, 256], 256, "fp32", {}), ("pendulum_8192", [128, 256], 272, "fp32", {}), ("catch_4096", [128, 256], 2048, "fp32", {}),
+    ("catch_4096", [128, 256], 2064, "fp32", {}), ("maze_16384", [64, 128, 256], 1024, "fp32", dict(rows=16, cols=16, max_steps=64)),
+    ("pendulum_8192", [128, 128, 256], 1040, "fp32", {}), ("catch_4096", [64, 64, 256], 48, "fp32", {}), ("maze_16384", [128, 256], 1008, "bf16", dict(rows=9, cols=13, max_steps=64)),
+])
+def test_acting_under_a_top_layer_of_256(gpu, name, hidden, B, dtype, env):
+    test_acting_kernels_give_the_canonical_update(gpu, name, hidden, B, dtype, env)
+
+
 @pytest.mark.parametrize("name,hidden,B,T,dtype,env", [
     # boards: edges of the 32-cell tiles and of the pairs of them a kernel is made for, one to 32 column tiles, chunks
     # that end inside a maze's time steps, one unit of 16 samples in all; a board beyond the kernel's 256 cells
