@@ -86,8 +86,8 @@ def measured_issue_utilisation(workload):
             continue
         if in_table and line.startswith("| `"):
             cells = [c.strip() for c in line.strip("|").split("|")]
-            # a listed name matches the profiler's up to its template arguments ("gemm_nt_bf16_res<512, true>" as listed
-            # must not also match "...<512, false>"): compare the part the listing gives, from the start
+            # a listed name matches the profiler's up to its template arguments ("backward_bf16<512, true, true>" as listed
+            # must not also match "...<512, false, true>"): compare the part the listing gives, from the start
             wanted = []
             for w in cells[1].split(", "):
                 if wanted and "<" in wanted[-1] and ">" not in wanted[-1]:
