@@ -257,6 +257,8 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // 499 115; 128 columns, 960 samples: 15 or 5 chunks 12.7, 3 13.4, 1 17.5)
         const int most = 512 / (ns.dims[1] / 128), want = M / 128 > 1 ? M / 128 : 1;
         set(0, 1, want < most ? want : most, 64);
+        // summed in the dX product: as many workgroups along the samples, whole tiles of 128
+        if (bf16_first_fold(ns, ed, M)) set(0, 1, most, 128);
     }
     if (const int s = first_fused_splits(ns, ed, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);

@@ -7,7 +7,8 @@
 //                        and the plane of walls, which is the same all through an unroll and so needs only
 //                        S[b] = sum_t dZ_1[t][b]; the goal's plane has one cell that is always set: the column sums.
 //
-//   first_layer_pendulum_bf16   the pendulum's three features, bf16 matrix path
+//   first_layer_pendulum_bf16   the pendulum's three features, bf16 matrix path (most nets of two layers with a 128-wide one:
+//                               learn_bf16.hip's dX product instead)
 //
 // dZ_1 comes as binary32 rows (taken apart into three bfloat16 terms: every product with a 0/1 operand is exact and the
 // accumulation is binary32, see split_terms.h) or as the sample-packed bfloat16 of the bf16 matrix path (one term).

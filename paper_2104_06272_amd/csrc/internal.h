@@ -268,6 +268,7 @@ int bf16_dw_chunks(int M, int K, int N, bool top);
 int bf16_dx_ranges(int M, int K, int N, int splits);
 bool bf16_top_fused(const NetShape& n, int M);
 bool bf16_top_fold(const NetShape& n);
+bool bf16_first_fold(const NetShape& n, const EnvDims& ed, int M);
 bool bf16_dx_resident(const NetShape& n, int M, int l);
 bool rollout_bf16_ok(const NetShape& net, const EnvDims& env, int B);
 // the stored unroll was produced by the bf16 matrix-core kernels and the maze's first layer is two dense products, agent and walls

@@ -19,6 +19,7 @@
 //                        for the first layer of a Catch board of more than 256 cells x is rebuilt from the states
 //                        (other first layers: first_layer.hip, and mazes in whole 256-wide tiles below)
 #include "gemm_bf16.h"
+#include "detmath.h"
 
 namespace ank {
 
@@ -222,6 +223,8 @@ __global__ __launch_bounds__(WG) void head_backward_bf16(const HeadBwdBf16Args a
 // dX = (dY W^T) masked.  dY row-major [M][N], W bf16 [K][N] (row i, reduction j
 // contiguous), mask from packed h, output in both layouts.  128 x 128 tile,
 // reduction staged through LDS 128 at a time.
+// FIRST: the result is dZ_1 of the pendulum, which nothing else reads: a workgroup walks some tiles of rows and adds up
+// dW_1[c][i] = sum_m o_c(m) dZ_1[m][i] for the three features and the bias in eight registers (binary32, dZ_1 unrounded).
 // ---------------------------------------------------------------------------
 struct GemmNtBf16Args {
     int M, K, N;
@@ -234,6 +237,9 @@ struct GemmNtBf16Args {
     const uint32_t* maskTop;  // ReLU flags of h_l (relu_mask_index)
     const uint16_t* wh16;     // bf16 copy of Wh: [N][NH]
     int NH, NHP;
+    const float* f0; const float* f1;   // FIRST: [M] stored angle and angular velocity
+    float* first_partial;     // [nbx][4*K]
+    int nbx, per;             // workgroups along the samples, tiles of 128 that each of them walks
 };
 
 // TOP, the layer under the heads: both products form dZ_L themselves from the head gradient, by the product of the head pass
@@ -268,18 +274,29 @@ struct HeadRow {
 constexpr int NB_BK = 128;
 constexpr int NB_LD = NB_BK + 8;        // row stride in bf16: 272 B, 16-byte aligned, 8 rows spread over all banks
 
-template <bool TOP>
+template <bool TOP, bool FIRST>
 __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const int block)
 {
     extern __shared__ uint4 smem4[];
     uint16_t* As = reinterpret_cast<uint16_t*>(smem4);          // [128][NB_LD] dY tile
     uint16_t* Bs = As + 128 * NB_LD;                            // [128][NB_LD] W tile
     u4v* Ahl = reinterpret_cast<u4v*>(Bs + 128 * NB_LD);        // TOP: [4 blocks of 32 samples][64] head gradient, A operand
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
-    int mt_, it_;
-    xcd_map(block, (a.M + 127) / 128, (a.K + 127) / 128, mt_, it_);   // the i-tiles of one m-tile share dY
-    const int m0 = mt_ * 128, i0 = it_ * 128;
+    float* feat = reinterpret_cast<float*>(Ahl + (TOP ? 4 * 64 : 0));   // FIRST: [2][3 features][128 samples]
+    int bx, it_;
+    xcd_map(block, FIRST ? a.nbx : (a.M + 127) / 128, (a.K + 127) / 128, bx, it_);   // the i-tiles of one m-tile share dY
+    const int i0 = it_ * 128;
+    float gw[FIRST ? 2 : 1][4];                                  // FIRST: this lane's columns' sums of three features and one
+#pragma unroll
+    for (int tc = 0; tc < (FIRST ? 2 : 1); ++tc)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gw[tc][c] = 0.0f;
+    auto row_tile = [&](const int mt_, float* ft) {
+    int tid = threadIdx.x;
+    if (FIRST) asm volatile("" : "+v"(tid));                     // or the addresses of a tile stay in registers across the loop
+    const int lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
+    const int m0 = mt_ * 128;
+    float th = 0.0f, td = 0.0f;
+    if (FIRST && tid >= 128) { const int m = m0 + tid - 128 < a.M ? m0 + tid - 128 : 0; th = a.f0[m]; td = a.f1[m]; }
     // loader: 128 rows x 16 pieces of 16 B = 2048 pieces per matrix, 8 per thread
     uint4 ra[TOP ? 1 : 8], rb[8];
     u4v wr;
@@ -303,6 +320,7 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
     fetch(0);
     // the ReLU masks: asked for with the first tile (in the epilogue, where they are used, they were a round trip of their own)
     uint2 hm[2][2][4];
+    auto load_masks = [&]() {
 #pragma unroll
     for (int tr = 0; tr < 2; ++tr)
 #pragma unroll
@@ -312,6 +330,8 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
                 const int m = m0 + wm * 64 + tr * 32 + 8 * g + 4 * kg, i = i0 + wn * 64 + tc * 32 + l32;
                 hm[tr][tc][g] = m < a.M && i < a.K ? *reinterpret_cast<const uint2*>(a.hP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) : make_uint2(0, 0);
             }
+    };
+    if (!FIRST) load_masks();                                    // (FIRST: when the registers of the tiles are free)
     f16v acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -322,6 +342,11 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
     if (TOP) {
         if (tid < 128) hr.terms(Ahl[(tid >> 5) * 64 + (tid & 31)], Ahl[(tid >> 5) * 64 + 32 + (tid & 31)]);
         __syncthreads();
+    }
+    if (FIRST && tid >= 128) {                                   // as the forward pass read them
+        float sn, cs;
+        det_sincos(th, sn, cs);
+        ft[tid - 128] = bfu(bf16_bits(cs)); ft[tid] = bfu(bf16_bits(sn)); ft[128 + tid] = bfu(bf16_bits(td));
     }
     const uint16_t* a_rd = As + (wm * 64 + l32) * NB_LD + 8 * kg;
     const uint16_t* b_rd = Bs + (wn * 64 + l32) * NB_LD + 8 * kg;
@@ -350,6 +375,7 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
         }
         __syncthreads();
         if (j0 + NB_BK < a.N) fetch(j0 + NB_BK);
+        else if (FIRST) load_masks();
 #pragma unroll
         for (int ks = 0; ks < NB_BK; ks += 16) {
             const bf8 a0 = *reinterpret_cast<const bf8*>(a_rd + ks);
@@ -362,6 +388,26 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
             acc[1][1] = mfma_bf16(a1, b1, acc[1][1]);
         }
         __syncthreads();
+    }
+    if (FIRST) {
+#pragma unroll
+        for (int tr = 0; tr < 2; ++tr)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4* f = reinterpret_cast<const float4*>(ft + wm * 64 + tr * 32 + 8 * g + 4 * kg);
+                const float4 fc = f[0], fs = f[32], fd = f[64];
+                const float c4[4] = {fc.x, fc.y, fc.z, fc.w}, s4[4] = {fs.x, fs.y, fs.z, fs.w}, d4[4] = {fd.x, fd.y, fd.z, fd.w};
+#pragma unroll
+                for (int tc = 0; tc < 2; ++tc)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t w = q < 2 ? hm[tr][tc][g].x : hm[tr][tc][g].y;
+                        const float v = bfu((uint16_t)((w >> ((q & 1) * 16)) & 0xffffu)) > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f;
+                        float* z = gw[FIRST ? tc : 0];
+                        z[0] = fmaf(c4[q], v, z[0]); z[1] = fmaf(s4[q], v, z[1]); z[2] = fmaf(d4[q], v, z[2]); z[3] += v;
+                    }
+            }
+        return;
     }
     // epilogue.  Accumulator register group r/4 of lane (l32, kg) holds rows 8*(r/4) + 4*kg + 0..3 of
     // column l32: exactly half of one packed group of eight samples -> 8-byte mask loads and stores.
@@ -395,8 +441,31 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
         if (m0 + row < a.M && i0 + c < a.K)
             *reinterpret_cast<uint4*>(a.dxR + (size_t)(m0 + row) * a.K + i0 + c) = *reinterpret_cast<const uint4*>(Ts + row * NB_LD + c);
     }
+    };
+    if (!FIRST) { row_tile(bx, nullptr); return; }
+    const int tiles = (a.M + 127) / 128, t0 = bx * a.per, t1 = t0 + a.per < tiles ? t0 + a.per : tiles;
+    for (int t = t0; t < t1; ++t) row_tile(t, feat + (t & 1) * 384);
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
+    // two lanes and two wavefronts have samples of a column each
+    float* red = reinterpret_cast<float*>(As);                   // [2 wn][2 tc][4][32], of the second wavefront
+#pragma unroll
+    for (int tc = 0; tc < 2; ++tc)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float* z = gw[FIRST ? tc : 0];
+            z[c] += __shfl_xor(z[c], 32, 64);
+            if (wm == 1 && kg == 0) red[((wn * 2 + tc) * 4 + c) * 32 + l32] = z[c];
+        }
+    __syncthreads();
+    if (wm == 0 && kg == 0) {
+        float* out = a.first_partial + (size_t)bx * 4 * a.K + i0 + wn * 64 + l32;
+#pragma unroll
+        for (int tc = 0; tc < 2; ++tc)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) out[(size_t)c * a.K + 32 * tc] = gw[FIRST ? tc : 0][c] + red[((wn * 2 + tc) * 4 + c) * 32 + l32];
+    }
 }
-__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body<false>(a, (int)blockIdx.x); }
+__global__ __launch_bounds__(WG) void gemm_nt_bf16(const GemmNtBf16Args a) { gemm_nt_bf16_body<false, false>(a, (int)blockIdx.x); }
 
 typedef uint32_t u32x4_l __attribute__((ext_vector_type(4)));
 
@@ -611,12 +680,12 @@ __global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a) { gem
 // Both products of a layer that takes the 128-wide tiles, dW workgroups first.  They read the same dZ and neither fills the
 // chip for long: as two launches one after the other they were mostly their own beginnings and ends (128-128, 32768 samples
 // 9.8 + 11.2 -> 14.0 us).
-template <bool TOP>
+template <bool TOP, bool FIRST>
 __global__ __launch_bounds__(WG, 2) void gemm_tn_nt_bf16(const GemmTnBf16Args t, const GemmNtBf16Args n, const int tiles, const int tn_blocks)
 {
     const int b = (int)blockIdx.x;
     if (b < tn_blocks) gemm_tn_bf16_body<false, TOP>(t, b % tiles, b / tiles);
-    else gemm_nt_bf16_body<TOP>(n, b - tn_blocks);
+    else gemm_nt_bf16_body<TOP, FIRST>(n, b - tn_blocks);
 }
 
 // The first layer of a maze with a 256 x 256 tile and eight wavefronts (two per SIMD, so one's LDS and
@@ -955,6 +1024,16 @@ bool bf16_top_fold(const NetShape& n)
     return n.bf16 && n.L >= 2 && n.NH <= 8 && (n.dims[n.L] % 256 != 0 || n.dims[n.L - 1] % 256 != 0);
 }
 
+// Whether the pendulum's first-layer gradient is summed in the dX product of a second and top layer in 128-wide tiles: a launch
+// less, and dZ_1 is neither written nor read (steps, us, first layer apart and here: 128-128, 512 samples 41.4 and 38.3, 32768
+// 99.0 and 94.5, 524288 266 and 238; 512-128 58.4 and 55.3, 177.0 and 168.6, 788 and 651; 128-256 46.0 and 43.9, 117.8 and 113.5).
+// Under 512 outputs few samples lose by it (128-512, 512 samples 61.2 and 63.4, 8192 144.1 and 145.5, 32768 150.7 and 147.1):
+// the walk's four turns per tile ask for the ReLU masks last.  A third layer's product has no registers left for the sums.
+bool bf16_first_fold(const NetShape& n, const EnvDims& ed, int M)
+{
+    return ed.kind == ENV_PENDULUM && n.L == 2 && bf16_top_fold(n) && (n.dims[2] < 512 || M >= 32768);
+}
+
 hipError_t launch_backward_bf16(anakin* h)
 {
     const Layout& L = h->lay;
@@ -968,6 +1047,7 @@ hipError_t launch_backward_bf16(anakin* h)
     auto needs_rows = [&](int l) { return l >= 1 && !bf16_dx_resident(n, M, l); };
     const bool top_fused = bf16_top_fused(n, M) && h->quanta[n.L - 1] == 128 && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
     const bool top_fold = bf16_top_fold(n) && h->quanta[n.L] == h->quanta[n.L - 1] && h->splits[n.L] == h->splits[n.L - 1] && h->head_fan == 1;
+    const bool first_fold = top_fold && bf16_first_fold(n, h->env, M) && h->quanta[0] == 128;
     if (!top_fused && !top_fold) {   // heads
         HeadBwdBf16Args a;
         a.M = M; a.H = n.dims[n.L]; a.NH = n.NH; a.NHP = n.NHP;
@@ -1026,6 +1106,7 @@ hipError_t launch_backward_bf16(anakin* h)
         return hipGetLastError();
     };
     for (int l = n.L - 1; l >= 0; --l) {
+        if (l == 0 && first_fold) continue;
         if (l == 0 && first_layer_split(h)) {
             const int H1 = n.dims[1], cells = h->env.rows * h->env.cols, plane = cells * H1;
             uint16_t* sP = at<uint16_t>(h, L.time_sum);
@@ -1106,16 +1187,22 @@ hipError_t launch_backward_bf16(anakin* h)
             g.dxR = needs_rows(l - 1) ? dzR(l - 1) : nullptr;
             g.dxP = dzP(l - 1);
             if (fold) { g.dhead = t.dhead; g.maskTop = at<const uint32_t>(h, L.mask[l]); g.wh16 = t.wh16; g.NH = n.NH; g.NHP = n.NHP; }
+            const bool first = first_fold && l == 1;
+            g.nbx = first ? h->splits[0] : (M + 127) / 128;
+            if (first) {
+                g.f0 = at<const float>(h, L.tr_f0); g.f1 = at<const float>(h, L.tr_f1);
+                g.first_partial = at<float>(h, L.part[0]); g.per = chunk_rows(M, h->splits[0], 128) / 128;
+            }
             ProfScope prof(h, both ? "gemm_tn_nt" : "gemm_nt_mask");
             if (both) {
                 t.tiles_i = (t.K + 127) / 128;
                 const int tiles = t.tiles_i * ((t.N + 127) / 128), tn = tiles * t.splits;
-                const size_t lds_t = (size_t)2 * TB_G * 128 * sizeof(uint4) + (fold ? 8192 : 0), lds_n = (size_t)2 * 128 * NB_LD * sizeof(uint16_t) + (fold ? 4096 : 0);
+                const size_t lds_t = (size_t)2 * TB_G * 128 * sizeof(uint4) + (fold ? 8192 : 0), lds_n = (size_t)2 * 128 * NB_LD * sizeof(uint16_t) + (fold ? 4096 : 0) + (first ? 3072 : 0);
                 const size_t lds2 = lds_t > lds_n ? lds_t : lds_n;
-                const auto kern = fold ? gemm_tn_nt_bf16<true> : gemm_tn_nt_bf16<false>;
+                const auto kern = first ? gemm_tn_nt_bf16<true, true> : fold ? gemm_tn_nt_bf16<true, false> : gemm_tn_nt_bf16<false, false>;
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
                 if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(kern, dim3(tn + ((g.M + 127) / 128) * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
+                hipLaunchKernelGGL(kern, dim3(tn + g.nbx * ((g.K + 127) / 128)), dim3(WG), lds2, h->stream, t, g, tiles, tn);
             } else {
                 const size_t lds2 = (size_t)2 * 128 * NB_LD * sizeof(uint16_t);
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);

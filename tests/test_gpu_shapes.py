@@ -737,12 +737,13 @@ def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
     bf16_products_against_binary64(gpu, name, hidden, B, T, whole=True)
 
 
-# the head pass folded into the products of a top layer in 128-wide tiles: every shape of it, three, four and five heads, alone and
+# the head pass, and of two layers the pendulum's first layer, folded into the products of a top layer in 128-wide tiles: every shape of it, three, four and five heads, alone and
 # above another layer; half a stage of 128 samples, one and a half, a last one that is not full, chunks of two and a half
 @pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (448, 17), (2112, 17)])
 @pytest.mark.parametrize("name,hidden", [
     ("pendulum_8192", [128, 128]), ("catch_4096", [256, 128]), ("pendulum_8192", [512, 128]), ("catch_4096", [128, 256]),
     ("maze_16384", [128, 512]), ("maze_16384", [128, 128]), ("catch_4096", [128, 128, 128]), ("pendulum_8192", [256, 256, 128]),
+    ("pendulum_8192", [256, 128]), ("pendulum_8192", [128, 256]), ("pendulum_8192", [128, 512]), ("pendulum_8192", [128, 128, 128]),
 ])
 def test_bf16_heads_in_the_products_of_128_wide_tiles(gpu, name, hidden, B, T):
     bf16_products_against_binary64(gpu, name, hidden, B, T, whole=False)
