@@ -191,6 +191,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     auto set = [&](int l, int tiles, int cap, int quantum) { quanta[l] = quantum; splits[l] = pick_splits(M, tiles, cap, quantum); };
     const bool bfp = rollout_bf16_ok(ns, ed, B);
     const int q32 = bfp ? 64 : M % 32 == 0 ? 32 : 16;
+    bool one_stage = false;                                      // head gradients in one level of sums
     size_t widths = 0;
     for (int l = 1; l <= ns.L; ++l) widths += ns.dims[l];
     for (int l = 0; l < ns.L; ++l) {
@@ -262,8 +263,26 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     }
     if (const int s = first_fused_splits(ns, ed, M)) { splits[0] = s; quanta[0] = split_nt_rows(ns, 1); }   // first layer folded into the dX product of the second
     set(ns.L, (ns.dims[ns.L] + 127) / 128, 256, q32);
-    if (ns.L == 1 && ((ed.kind == ENV_PENDULUM && !bfp) || one_layer_shape(ns, ed))) { set(0, 1, 1024, q32); splits[1] = splits[0]; quanta[1] = quanta[0]; }   // fused one-layer update: one chunking for both regions
-    if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0) {
+    if (ns.L == 1 && ((ed.kind == ENV_PENDULUM && !bfp) || one_layer_learn_shape(ns, ed))) {
+        // fused one-layer update: one chunking for both regions
+        if (ed.kind == ENV_CATCH && one_layer_learn_shape(ns, ed)) {
+            // two workgroups per compute unit, every wavefront a unit of 16 samples at least.  No more scratch than before where
+            // it could fit the static array: 32 units as many chunks as still fit
+            const size_t samples = (size_t)M * (4 * widths + 4 * ns.NHP), fits = ANAKIN_STATIC_SCRATCH_BYTES;
+            int most = ns.dims[1] == 256 ? 256 : 512;
+            if (ns.dims[1] == 32 && B % 256 == 0 && samples < fits) {
+                int had = B / 256;
+                while (had > 512 && had % 2 == 0) had /= 2;
+                const size_t room = (fits - samples) / ((size_t)4 * (ns.P + 128));
+                if (room < 512) most = (int)room > had ? (int)room : had;
+                if (most > 512) most = 512;
+            }
+            set(0, 1, most, ns.dims[1] >= 128 ? 32 : 64);
+            one_stage = true;
+        } else set(0, 1, 1024, q32);
+        splits[1] = splits[0]; quanta[1] = quanta[0];
+    }
+    if (catch_fused_shape(ns, ed, B)) {
         // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
         // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the
         // workgroup's prologue (W1 into LDS, 51 KB of sums cleared) and its tail once per two blocks or more, and the
@@ -291,7 +310,6 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     }
     // the head-gradient pass streams the last hidden layer: many small workgroups, summed in two levels
     int fan = 1;
-    bool one_stage = false;
     if (ns.split && ns.dims[ns.L] % 64 == 0 && M % 32 == 0 && (ns.L > 1 || ed.kind == ENV_MAZE)) {
         // matrix-core head pass: two workgroups per CU stream enough on their own, and their partials go straight to Adam
         set(ns.L, 1, ns.bf16 ? 256 : 512, 32);                      // (bf16: no more than the two-level sum below would take)
@@ -627,7 +645,7 @@ static int32_t run_update(anakin* h, bool loss_done = false)
 {
     if (!loss_done) HIPCHK(h, launch_head_grad(h));
     if (h->traj_packed) HIPCHK(h, launch_backward_bf16(h));
-    else if (h->traj_no_acts) HIPCHK(h, launch_learn_one_layer(h));
+    else if (one_layer_learn(h)) HIPCHK(h, launch_learn_one_layer(h));
     else HIPCHK(h, launch_backward(h));
     HIPCHK(h, launch_adam(h));
     return ANAKIN_OK;

@@ -718,14 +718,11 @@ hipError_t launch_first_layer_grad(anakin* h)
 }
 
 // ---------------------------------------------------------------------------
-// Whole backward pass of a one-hidden-layer net in one kernel.  Nothing of the
-// forward pass is read from HBM: the hidden layer h = relu(b1 + W1[ball] +
-// W1[paddle]) (or three fmas for the pendulum) is rebuilt from the 4-byte state
-// snapshot with W1 in LDS -- in the acting order, so the bits equal the acting
-// ones -- then dZ1 = relu'(h) (Wh dhead), the head-matrix gradient, and the
-// scatter of dZ1 into the two selected rows of dW1.  Per sample the kernel
-// reads the state word and the dhead row (20 B) and writes nothing; per chunk
-// it writes one partial of each parameter region.  Lane j owns hidden unit j.
+// Whole backward pass of a one-hidden-layer pendulum net in one kernel (Catch: learn_one.hip).  Nothing of the
+// forward pass is read from HBM: the hidden layer h = relu(three fmas from b1) is rebuilt from the state -- in the
+// acting order, so the bits equal the acting ones -- then dZ1 = relu'(h) (Wh dhead), the head-matrix gradient and the
+// three rows of dW1 in registers.  Per sample the kernel reads the state and the dhead row (24 B) and writes nothing;
+// per chunk it writes one partial of each parameter region.  Lane j owns hidden unit j.
 // ---------------------------------------------------------------------------
 struct OneLayerArgs {
     int M, D, H, NH, NHP, rows;
@@ -736,16 +733,14 @@ struct OneLayerArgs {
     ObsLite obs;
 };
 
-// OLW threads per workgroup: small workgroups keep the LDS accumulators small, so more of them fit a CU
 constexpr int OLW = 128;
 // NH (number of head outputs) is a template parameter: the per-sample inner loops are the whole cost here
 // FULL: the chunk is a whole number of RB x groups sample blocks, so no load needs a bounds check.
-// HC: the hidden width when it is known at compile time (index arithmetic by shifts, constant load offsets), else 0.
-template <int ENV, int NH, bool FULL, int HC>
+template <int NH, bool FULL>
 __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
 {
     extern __shared__ float lds[];
-    const int H = HC ? HC : a.H, D = a.D;
+    const int H = a.H, D = a.D;
     constexpr int NHP = NH <= 4 ? 4 : 8;
     const int cw = H < OLW ? H : OLW, groups = OLW / cw;
     float* w1s = lds;                                         // [D][H]
@@ -754,7 +749,6 @@ __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
     const int j = blockIdx.y * OLW + jl;
     for (int i = threadIdx.x; i < D * H; i += OLW) w1s[i] = a.theta[a.w1_off + i];
     float* mine = accs + (size_t)g * D * cw + jl;
-    if (ENV == ENV_CATCH) for (int k = 0; k < D; ++k) mine[k * cw] = 0.0f;
     float wh[NH], dwh[NH], dbh[NH];
 #pragma unroll
     for (int k = 0; k < NH; ++k) { wh[k] = a.theta[a.wh_off + j * NH + k]; dwh[k] = 0.0f; dbh[k] = 0.0f; }
@@ -766,11 +760,9 @@ __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
     constexpr int RB = 8;
     for (int mb = m_begin + g; mb < m_end; mb += RB * groups) {
         float4 d0[RB], d1[RB];
-        uint32_t sw[RB];
         float f0[RB], f1[RB];
         // one base address per array and trip; the samples of a trip sit at constant distances from it
         const float* dh = a.dhead + (size_t)mb * NHP;
-        const uint32_t* sp = a.obs.s0 + mb;
         const float* fp0 = a.obs.f0 + mb;
         const float* fp1 = a.obs.f1 + mb;
 #pragma unroll
@@ -779,42 +771,26 @@ __global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
             const bool ok = FULL || mb + du < m_end;
             d0[u] = ok ? *reinterpret_cast<const float4*>(dh + du * NHP) : make_float4(0, 0, 0, 0);
             d1[u] = (ok && NHP == 8) ? *reinterpret_cast<const float4*>(dh + du * NHP + 4) : make_float4(0, 0, 0, 0);
-            if (ENV == ENV_CATCH) sw[u] = ok ? sp[du] : 0u;
-            else { f0[u] = ok ? fp0[du] : 0.0f; f1[u] = ok ? fp1[du] : 0.0f; }
+            f0[u] = ok ? fp0[du] : 0.0f; f1[u] = ok ? fp1[du] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             if (!FULL && mb + u * groups >= m_end) break;
             const float d[8] = {d0[u].x, d0[u].y, d0[u].z, d0[u].w, d1[u].x, d1[u].y, d1[u].z, d1[u].w};
-            float hv, x0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
-            int bc = 0, pc = 0;
-            if (ENV == ENV_CATCH) {
-                catch_obs_cells(a.obs.env, sw[u], bc, pc);
-                hv = (b1 + w1c[bc * H]) + w1c[pc * H];
-            } else {
-                float sn, cs;
-                det_sincos(f0[u], sn, cs);
-                x0 = cs; x1 = sn; x2 = f1[u];
-                hv = fmaf(x2, w1c[2 * H], fmaf(x1, w1c[H], fmaf(x0, w1c[0], b1)));
-            }
+            float sn, cs;
+            det_sincos(f0[u], sn, cs);
+            const float x0 = cs, x1 = sn, x2 = f1[u];
+            float hv = fmaf(x2, w1c[2 * H], fmaf(x1, w1c[H], fmaf(x0, w1c[0], b1)));
             hv = hv > 0.0f ? hv : 0.0f;
             float s = 0.0f;
 #pragma unroll
             for (int k = 0; k < NH; ++k) { s = fmaf(wh[k], d[k], s); dwh[k] = fmaf(hv, d[k], dwh[k]); dbh[k] += d[k]; }
             const float dz = hv > 0.0f ? s : 0.0f;
             db1 += dz;
-            if (ENV == ENV_CATCH) {
-                // the ball is never in the paddle's row: two different words, both read before either is stored
-                float* pa = mine + bc * cw;
-                float* pb = mine + pc * cw;
-                const float xa = *pa, xb = *pb;
-                *pa = xa + dz;
-                *pb = xb + dz;
-            }
-            else { r0 = fmaf(x0, dz, r0); r1 = fmaf(x1, dz, r1); r2 = fmaf(x2, dz, r2); }
+            r0 = fmaf(x0, dz, r0); r1 = fmaf(x1, dz, r1); r2 = fmaf(x2, dz, r2);
         }
     }
-    if (ENV != ENV_CATCH) { mine[0] = r0; mine[cw] = r1; mine[2 * cw] = r2; }
+    mine[0] = r0; mine[cw] = r1; mine[2 * cw] = r2;
     // per-lane sums of the other regions go through LDS too, then everything is combined group by group
     __shared__ float red[OLW * 10];                            // [10][OLW]: dwh[0..7], db1, (dbh of lane 0 handled below)
 #pragma unroll
@@ -1084,7 +1060,7 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
 bool catch_fused_ok(const anakin* h)
 {
     const NetShape& n = h->net;
-    return one_layer_fused(h) && h->env.kind == ENV_CATCH && h->env.rows >= 2 && n.dims[1] == CF_H && n.NH == 4 && h->n_updates == 1 &&
+    return one_layer_fused(h) && catch_fused_shape(n, h->env, h->B) && h->env.rows >= 2 && n.NH == 4 && h->n_updates == 1 &&
            !h->traj_decoupled && !h->pathwise && h->splits[0] > 0 && h->B % (h->splits[0] * CF_WG) == 0 &&
            n.dims[0] * CF_H * 4 < 65536 && n.w_off[0] % 4 == 0;           // board-cell offsets are packed into 16 bits; W1 is read 16 bytes at a time
 }
@@ -1114,6 +1090,7 @@ hipError_t launch_learn_catch_fused(anakin* h)
 
 hipError_t launch_learn_one_layer(anakin* h)
 {
+    if (h->env.kind == ENV_CATCH) return launch_learn_one_catch(h);
     const Layout& L = h->lay;
     const NetShape& n = h->net;
     OneLayerArgs a;
@@ -1135,11 +1112,7 @@ hipError_t launch_learn_one_layer(anakin* h)
     };
     const int cw = a.H < OLW ? a.H : OLW;
     const bool full = a.rows % (8 * (OLW / cw)) == 0 && a.M % (8 * (OLW / cw)) == 0;   // RB x groups samples per loop trip
-    if (h->env.kind == ENV_CATCH) {
-        if (full && a.H == 32) return go(learn_one_layer<ENV_CATCH, 4, true, 32>);
-        return full ? go(learn_one_layer<ENV_CATCH, 4, true, 0>) : go(learn_one_layer<ENV_CATCH, 4, false, 0>);
-    }
-    return full ? go(learn_one_layer<ENV_PENDULUM, 3, true, 0>) : go(learn_one_layer<ENV_PENDULUM, 3, false, 0>);
+    return full ? go(learn_one_layer<3, true>) : go(learn_one_layer<3, false>);
 }
 
 // ---------------------------------------------------------------------------
