@@ -279,6 +279,11 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
             }
             set(0, 1, most, ns.dims[1] >= 128 ? 32 : 64);
             one_stage = true;
+        } else if (one_layer_learn_shape(ns, ed)) {
+            // the pendulum: a unit of 16 samples for every wavefront; kernel + optimiser kernel with 512 and 1024 chunks: 65536
+            // samples, 128 units 13.2 and 16.7 us, 32 units 10.0 and 13.1; 524288 samples, 128 units 33.8 and 35.1, 256 units
+            // 67.5 and 64.4
+            set(0, 1, 512, 64);
         } else set(0, 1, 1024, q32);
         splits[1] = splits[0]; quanta[1] = quanta[0];
     }

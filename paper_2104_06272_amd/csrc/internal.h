@@ -250,7 +250,6 @@ hipError_t launch_adam(anakin* h);
 hipError_t launch_first_layer_grad(anakin* h);
 hipError_t launch_adam_probe(float* base, int P, hipStream_t s);
 hipError_t launch_learn_one_layer(anakin* h);
-hipError_t launch_learn_one_catch(anakin* h);
 hipError_t launch_learn_catch_fused(anakin* h);
 hipError_t launch_learn_small_fused(anakin* h);
 bool small_fused_ok(const anakin* h);
@@ -259,9 +258,10 @@ bool catch_fused_ok(const anakin* h);
 // single hidden layer on a one-hot or 3-feature observation: the update rebuilds the layer from the state
 inline bool one_layer_shape(const NetShape& n, const EnvDims& ed) { return n.L == 1 && ed.kind != ENV_MAZE && !n.bf16 && n.dims[1] <= 128 && (size_t)128 * n.dims[0] * 4 + (size_t)n.dims[0] * n.dims[1] * 4 <= 64 * 1024; }
 inline bool one_layer_fused(const anakin* h) { return one_layer_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
-// One-hidden-layer nets whose whole backward pass is one launch: those, and 256 units, which keep their activations in memory
-// for the caller but are rebuilt all the same (Catch with the board in two tiles, learn_one.hip).  524288 samples, before and
-// now: Catch 10 x 5 360 us (head pass, first layer, their sums) and 152, the pendulum 365 and 177; 1024 samples 11.3 and 8.6, 10.5 and 9.8.
+// One-hidden-layer nets whose whole backward pass is one launch (learn_one.hip): those, and 256 units, which keep their
+// activations in memory for the caller but are rebuilt all the same (Catch with the board in two tiles).  256 units, before
+// (head pass, first layer, their sums) and now: 524288 samples, Catch 10 x 5 360 us and 152, the pendulum 365 and 61; 1024
+// samples 11.3 and 8.6, 10.5 and 5.8.
 inline bool one_layer_learn_shape(const NetShape& n, const EnvDims& ed) { return one_layer_shape(n, ed) || (n.L == 1 && !n.bf16 && n.dims[1] == 256 && (ed.kind == ENV_PENDULUM || (ed.kind == ENV_CATCH && n.dims[0] < 64))); }
 inline bool one_layer_learn(const anakin* h) { return one_layer_learn_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
 // Catch, 32 units: the launch that takes returns and loss too (learn_catch_fused) is a chain of 54 us per 256 environments at

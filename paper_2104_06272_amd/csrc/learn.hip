@@ -7,7 +7,6 @@
 //   vtrace_ratio / _scan  those targets where the unroll does not fit scan_loss
 //   head_backward(_mfma)  gradient of the head matrix, and of the last hidden layer
 //   first_layer_grad*     gradient of the pendulum's first layer from the compact state (boards: first_layer.hip)
-//   learn_one_layer       the whole backward pass of a one-hidden-layer net
 //   learn_catch_fused     returns, loss and backward pass of a small one-hidden-layer Catch net
 //   adam_reduce(_narrow, _flat)  fixed-order sum of split-K partials fused with Adam
 // Hidden-layer GEMMs live in gemm.hip (vector ALU), gemm_mfma.hip (tiled) and
@@ -718,115 +717,6 @@ hipError_t launch_first_layer_grad(anakin* h)
 }
 
 // ---------------------------------------------------------------------------
-// Whole backward pass of a one-hidden-layer pendulum net in one kernel (Catch: learn_one.hip).  Nothing of the
-// forward pass is read from HBM: the hidden layer h = relu(three fmas from b1) is rebuilt from the state -- in the
-// acting order, so the bits equal the acting ones -- then dZ1 = relu'(h) (Wh dhead), the head-matrix gradient and the
-// three rows of dW1 in registers.  Per sample the kernel reads the state and the dhead row (24 B) and writes nothing;
-// per chunk it writes one partial of each parameter region.  Lane j owns hidden unit j.
-// ---------------------------------------------------------------------------
-struct OneLayerArgs {
-    int M, D, H, NH, NHP, rows;
-    const float* theta; int w1_off, b1_off, wh_off;
-    const float* dhead;
-    float* partial0;          // [splits][D*H + H]
-    float* partial1;          // [splits][H*NH + NH]
-    ObsLite obs;
-};
-
-constexpr int OLW = 128;
-// NH (number of head outputs) is a template parameter: the per-sample inner loops are the whole cost here
-// FULL: the chunk is a whole number of RB x groups sample blocks, so no load needs a bounds check.
-template <int NH, bool FULL>
-__global__ __launch_bounds__(OLW) void learn_one_layer(const OneLayerArgs a)
-{
-    extern __shared__ float lds[];
-    const int H = a.H, D = a.D;
-    constexpr int NHP = NH <= 4 ? 4 : 8;
-    const int cw = H < OLW ? H : OLW, groups = OLW / cw;
-    float* w1s = lds;                                         // [D][H]
-    float* accs = w1s + D * H;                                // [groups][D][cw]
-    const int g = threadIdx.x / cw, jl = threadIdx.x % cw;
-    const int j = blockIdx.y * OLW + jl;
-    for (int i = threadIdx.x; i < D * H; i += OLW) w1s[i] = a.theta[a.w1_off + i];
-    float* mine = accs + (size_t)g * D * cw + jl;
-    float wh[NH], dwh[NH], dbh[NH];
-#pragma unroll
-    for (int k = 0; k < NH; ++k) { wh[k] = a.theta[a.wh_off + j * NH + k]; dwh[k] = 0.0f; dbh[k] = 0.0f; }
-    const float b1 = a.theta[a.b1_off + j];
-    float db1 = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
-    __syncthreads();
-    const int m_begin = blockIdx.x * a.rows, m_end = m_begin + a.rows < a.M ? m_begin + a.rows : a.M;
-    const float* w1c = w1s + j;
-    constexpr int RB = 8;
-    for (int mb = m_begin + g; mb < m_end; mb += RB * groups) {
-        float4 d0[RB], d1[RB];
-        float f0[RB], f1[RB];
-        // one base address per array and trip; the samples of a trip sit at constant distances from it
-        const float* dh = a.dhead + (size_t)mb * NHP;
-        const float* fp0 = a.obs.f0 + mb;
-        const float* fp1 = a.obs.f1 + mb;
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const int du = u * groups;
-            const bool ok = FULL || mb + du < m_end;
-            d0[u] = ok ? *reinterpret_cast<const float4*>(dh + du * NHP) : make_float4(0, 0, 0, 0);
-            d1[u] = (ok && NHP == 8) ? *reinterpret_cast<const float4*>(dh + du * NHP + 4) : make_float4(0, 0, 0, 0);
-            f0[u] = ok ? fp0[du] : 0.0f; f1[u] = ok ? fp1[du] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            if (!FULL && mb + u * groups >= m_end) break;
-            const float d[8] = {d0[u].x, d0[u].y, d0[u].z, d0[u].w, d1[u].x, d1[u].y, d1[u].z, d1[u].w};
-            float sn, cs;
-            det_sincos(f0[u], sn, cs);
-            const float x0 = cs, x1 = sn, x2 = f1[u];
-            float hv = fmaf(x2, w1c[2 * H], fmaf(x1, w1c[H], fmaf(x0, w1c[0], b1)));
-            hv = hv > 0.0f ? hv : 0.0f;
-            float s = 0.0f;
-#pragma unroll
-            for (int k = 0; k < NH; ++k) { s = fmaf(wh[k], d[k], s); dwh[k] = fmaf(hv, d[k], dwh[k]); dbh[k] += d[k]; }
-            const float dz = hv > 0.0f ? s : 0.0f;
-            db1 += dz;
-            r0 = fmaf(x0, dz, r0); r1 = fmaf(x1, dz, r1); r2 = fmaf(x2, dz, r2);
-        }
-    }
-    mine[0] = r0; mine[cw] = r1; mine[2 * cw] = r2;
-    // per-lane sums of the other regions go through LDS too, then everything is combined group by group
-    __shared__ float red[OLW * 10];                            // [10][OLW]: dwh[0..7], db1, (dbh of lane 0 handled below)
-#pragma unroll
-    for (int k = 0; k < NH; ++k) red[k * OLW + threadIdx.x] = dwh[k];
-    red[8 * OLW + threadIdx.x] = db1;
-    red[9 * OLW + threadIdx.x] = 0.0f;
-    __shared__ float bh_red[8 * 8];                           // [groups <= 8][8]
-    if (jl == 0 && blockIdx.y == 0) for (int k = 0; k < NH; ++k) bh_red[g * 8 + k] = dbh[k];
-    __syncthreads();
-    float* out0 = a.partial0 + (size_t)blockIdx.x * ((size_t)D * H + H);
-    float* out1 = a.partial1 + (size_t)blockIdx.x * ((size_t)H * NH + NH);
-    for (int i = threadIdx.x; i < D * cw; i += OLW) {
-        const int k = i / cw, c = i % cw;
-        float s = 0.0f;
-        for (int gg = 0; gg < groups; ++gg) s += accs[((size_t)gg * D + k) * cw + c];
-        out0[(size_t)k * H + blockIdx.y * OLW + c] = s;
-    }
-    if (threadIdx.x < cw) {
-        const int c = threadIdx.x, col = blockIdx.y * OLW + c;
-        float s = 0.0f;
-        for (int gg = 0; gg < groups; ++gg) s += red[8 * OLW + gg * cw + c];
-        out0[(size_t)D * H + col] = s;
-        for (int k = 0; k < NH; ++k) {
-            float t = 0.0f;
-            for (int gg = 0; gg < groups; ++gg) t += red[k * OLW + gg * cw + c];
-            out1[(size_t)col * NH + k] = t;
-        }
-    }
-    if (threadIdx.x < NH && blockIdx.y == 0) {
-        float t = 0.0f;
-        for (int gg = 0; gg < groups; ++gg) t += bh_red[gg * 8 + threadIdx.x];
-        out1[(size_t)H * NH + threadIdx.x] = t;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Catch with one hidden layer of 32 units (the throughput workload): the WHOLE update up to the
 // partial sums in one launch -- returns and advantages, loss and head gradients, and the backward
 // pass above -- so that advantages, returns and head gradients never make a round trip through
@@ -859,14 +749,6 @@ struct CatchFusedArgs {
 constexpr int CF_WG = 256;              // four wavefronts
 constexpr int CF_H = 32;                // hidden units
 constexpr int CF_TC = 4;                // time steps per chunk of phases A2 / B
-
-// LDS between the lanes of one wavefront: its accesses are carried out in order, only the compiler has to keep that order
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs a)
 {
@@ -1086,33 +968,6 @@ hipError_t launch_learn_catch_fused(anakin* h)
     ProfScope prof(h, "learn_catch_fused");
     hipLaunchKernelGGL(learn_catch_fused, dim3(h->splits[0]), dim3(CF_WG), lds, h->stream, a);
     return hipGetLastError();
-}
-
-hipError_t launch_learn_one_layer(anakin* h)
-{
-    if (h->env.kind == ENV_CATCH) return launch_learn_one_catch(h);
-    const Layout& L = h->lay;
-    const NetShape& n = h->net;
-    OneLayerArgs a;
-    a.M = h->B * h->T; a.D = n.dims[0]; a.H = n.dims[1]; a.NH = n.NH; a.NHP = n.NHP;
-    a.rows = chunk_rows(a.M, h->splits[0], h->quanta[0]);
-    a.theta = at<const float>(h, L.w_src); a.w1_off = n.w_off[0]; a.b1_off = n.b_off[0]; a.wh_off = n.wh_off;
-    a.dhead = at<const float>(h, L.dhead);
-    a.partial0 = at<float>(h, L.part[0]); a.partial1 = at<float>(h, L.part[1]);
-    a.obs.env = h->env; a.obs.s0 = at<const uint32_t>(h, L.tr_s0);
-    a.obs.f0 = at<const float>(h, L.tr_f0); a.obs.f1 = at<const float>(h, L.tr_f1);
-    const size_t lds = ((size_t)a.D * a.H + (size_t)OLW * a.D) * sizeof(float);
-    const dim3 grid(h->splits[0], (a.H + OLW - 1) / OLW);
-    auto go = [&](auto kern) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        ProfScope prof(h, "learn_one_layer");
-        hipLaunchKernelGGL(kern, grid, dim3(OLW), lds, h->stream, a);
-        return hipGetLastError();
-    };
-    const int cw = a.H < OLW ? a.H : OLW;
-    const bool full = a.rows % (8 * (OLW / cw)) == 0 && a.M % (8 * (OLW / cw)) == 0;   // RB x groups samples per loop trip
-    return full ? go(learn_one_layer<3, true>) : go(learn_one_layer<3, false>);
 }
 
 // ---------------------------------------------------------------------------

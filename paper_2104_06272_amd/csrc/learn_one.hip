@@ -1,10 +1,13 @@
-// The whole backward pass of a one-hidden-layer Catch net in one launch (paper section 3.1: the update differentiates
-// through the policy network), its first-layer gradient on the matrix cores.
+// The whole backward pass of a one-hidden-layer net in one launch (paper section 3.1: the update differentiates through the
+// policy network).  Nothing of the forward pass is read back and nothing is written but a chunk's partial sums.
 //
-// Nothing of the forward pass is read back: h = relu((b1 + W1[ball]) + W1[paddle]) is rebuilt from the 4-byte state with W1
+//   learn_one_catch      the first layer's gradient on the matrix cores
+//   learn_one_pendulum   three features a sample, all on the vector units
+//
+// Catch: h = relu((b1 + W1[ball]) + W1[paddle]) is rebuilt from the 4-byte state with W1
 // in LDS, in the acting order, so the bits equal the acting ones; then dZ1 = relu'(h) (Wh dhead), the head matrix's sums and
 // dW1 = X^T dZ1 with the board X as the 0/1 operand and dZ1 as three bfloat16 terms (exact products, binary32 sums; see
-// split_terms.h).  A sample costs 20 bytes of memory and nothing is written but a chunk's partial sums.
+// split_terms.h).  A sample costs 20 bytes of memory.
 //
 // Bound by vector instructions: some 30 per sample and unit, 4 of them the board operand (shared by CB column tiles) and 6 the
 // terms.  A wavefront owns 32 * CB columns and walks units of 16 samples, lane (l32, kg) its columns l32 + 32 c for samples
@@ -22,9 +25,10 @@ struct LearnOneArgs {
     int cols, paddle_row0;    // board columns, first cell of the bottom row
     const float* theta; int w1_off, b1_off, wh_off;
     const float* dhead;       // [M][4]
-    const uint32_t* s0;       // [M]
+    const uint32_t* s0;       // [M] Catch
+    const float* f0; const float* f1;   // [M] pendulum
     float* partial0;          // [splits][D*H + H]
-    float* partial1;          // [splits][H*4 + 4]
+    float* partial1;          // [splits][H*NH + NH]
 };
 
 // RT: tiles of 32 cells; CG wavefronts share a workgroup's 32 * CB * CG columns, 4 / CG the samples
@@ -175,7 +179,96 @@ __global__ __launch_bounds__(256, RT * CB > 4 ? 1 : 2) void learn_one_catch(cons
     if (tid < 4 && blockIdx.y == 0) out1[(size_t)H * 4 + tid] = (dbh_red[0][tid] + dbh_red[1][tid]) + (dbh_red[2][tid] + dbh_red[3][tid]);
 }
 
-hipError_t launch_learn_one_catch(anakin* h)
+// The pendulum.  Bound by vector instructions: 16 per sample and unit.  A lane owns CB units (H = 32: half a wavefront takes
+// every other sample).  A block of 64 samples has its sines and cosines made one sample a lane and handed round through LDS
+// with the head gradients; made by every lane for itself they took most of the time.  Before and now: 524288
+// samples, 32 units 31 -> 11 us, 64 56 -> 18, 128 107 -> 28, 256 177 -> 61; 65536 samples, 128 units 16.8 -> 7.4; 1024 samples,
+// 128 units 8.8 -> 4.7.  Wavefronts share nothing until their sums are added at the end.
+template <int H>
+__global__ __launch_bounds__(256) void learn_one_pendulum(const LearnOneArgs a)
+{
+    constexpr int CB = H < 64 ? 1 : H / 64, HALVES = H == 32 ? 2 : 1;
+    __shared__ float sums[4 * HALVES][7][H];                     // dW1 (three rows), db1, dWh by head
+    __shared__ f4v_s xs[4][64], dbh_red[4];
+    __shared__ float2 ds[4][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = HALVES == 2 ? lane >> 5 : 0, j = HALVES == 2 ? lane & 31 : lane;
+    // the chunk's units of 16 samples, a run of them to every wavefront
+    const int u0 = blockIdx.x * a.per, u1 = u0 + a.per < a.units ? u0 + a.per : a.units, each = (a.per + 3) / 4;
+    const int m0 = 16 * (u0 + wave * each), end = u0 + (wave + 1) * each, m1 = 16 * (end < u1 ? end : u1);
+    float w[CB][3], b1[CB], wh[CB][3], r[CB][7];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        const int col = j + 64 * c;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { w[c][k] = a.theta[a.w1_off + k * H + col]; wh[c][k] = a.theta[a.wh_off + col * 3 + k]; }
+        b1[c] = a.theta[a.b1_off + col];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) r[c][k] = 0.0f;
+    }
+    f4v_s dbh = {0.0f, 0.0f, 0.0f, 0.0f};
+    struct In { float th, dot; f4v_s d; };
+    auto load = [&](In& z, int m) {                              // past the end: an earlier sample again, not used
+        m = m + lane < a.M ? m + lane : a.M - 1;
+        z.th = a.f0[m]; z.dot = a.f1[m]; z.d = reinterpret_cast<const f4v_s*>(a.dhead)[m];
+    };
+    In in;
+    load(in, m0);
+    for (int m = m0; m < m1; m += 64) {
+        const int n = m1 - m < 64 ? m1 - m : 64;                 // a multiple of 16
+        float sn, cs;
+        det_sincos(in.th, sn, cs);
+        xs[wave][lane] = f4v_s{cs, sn, in.dot, in.d[0]};
+        ds[wave][lane] = make_float2(in.d[1], in.d[2]);
+        if (lane < n) dbh += in.d;
+        wave_fence();
+        load(in, m + 64);
+        for (int e0 = 0; e0 < n; e0 += 16) {
+#pragma unroll
+            for (int q = 0; q < 16; q += HALVES) {
+                const f4v_s x = xs[wave][e0 + q + half];
+                const float2 y = ds[wave][e0 + q + half];
+                const float d[3] = {x[3], y.x, y.y};
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    float hv = fmaf(x[2], w[c][2], fmaf(x[1], w[c][1], fmaf(x[0], w[c][0], b1[c])));
+                    hv = hv > 0.0f ? hv : 0.0f;
+                    float s = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) { s = fmaf(wh[c][k], d[k], s); r[c][4 + k] = fmaf(hv, d[k], r[c][4 + k]); }
+                    const float dz = hv > 0.0f ? s : 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) r[c][k] = fmaf(x[k], dz, r[c][k]);
+                    r[c][3] += dz;
+                }
+            }
+        }
+        wave_fence();
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int o = 32; o; o >>= 1) dbh[k] += __shfl_xor(dbh[k], o);
+    if (lane == 0) dbh_red[wave] = dbh;
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sums[wave * HALVES + half][k][j + 64 * c] = r[c][k];
+    __syncthreads();
+    float* out0 = a.partial0 + (size_t)blockIdx.x * (4 * H);
+    float* out1 = a.partial1 + (size_t)blockIdx.x * (3 * H + 3);
+    for (int i = tid; i < 7 * H; i += 256) {
+        const int k = i / H, col = i % H;
+        float s = sums[0][k][col];
+#pragma unroll
+        for (int g = 1; g < 4 * HALVES; ++g) s += sums[g][k][col];
+        if (k < 4) out0[i] = s;
+        else out1[col * 3 + k - 4] = s;
+    }
+    if (tid < 3) out1[3 * H + tid] = (dbh_red[0][tid] + dbh_red[1][tid]) + (dbh_red[2][tid] + dbh_red[3][tid]);
+}
+
+hipError_t launch_learn_one_layer(anakin* h)
 {
     const Layout& L = h->lay;
     const NetShape& n = h->net;
@@ -185,7 +278,14 @@ hipError_t launch_learn_one_catch(anakin* h)
     a.cols = h->env.cols; a.paddle_row0 = (h->env.rows - 1) * h->env.cols;
     a.theta = at<const float>(h, L.w_src); a.w1_off = n.w_off[0]; a.b1_off = n.b_off[0]; a.wh_off = n.wh_off;
     a.dhead = at<const float>(h, L.dhead); a.s0 = at<const uint32_t>(h, L.tr_s0);
+    a.f0 = at<const float>(h, L.tr_f0); a.f1 = at<const float>(h, L.tr_f1);
     a.partial0 = at<float>(h, L.part[0]); a.partial1 = at<float>(h, L.part[1]);
+    if (h->env.kind == ENV_PENDULUM) {
+        ProfScope prof(h, "learn_one_layer");
+        const auto kern = a.H == 32 ? learn_one_pendulum<32> : a.H == 64 ? learn_one_pendulum<64> : a.H == 128 ? learn_one_pendulum<128> : learn_one_pendulum<256>;
+        hipLaunchKernelGGL(kern, dim3(h->splits[0]), dim3(256), 0, h->stream, a);
+        return hipGetLastError();
+    }
     auto go = [&](auto kern, int sg, int width) {
         const size_t lds = (size_t)sg * (a.D + 5) * width * sizeof(float);
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

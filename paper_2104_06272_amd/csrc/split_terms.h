@@ -5,6 +5,14 @@
 
 namespace ank {
 
+// LDS between the lanes of one wavefront: its accesses are carried out in order, only the compiler has to keep that order
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 typedef __bf16 bf8_s __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2_s __attribute__((ext_vector_type(2)));
 typedef float f16v_s __attribute__((ext_vector_type(16)));

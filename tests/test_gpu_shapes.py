@@ -84,13 +84,16 @@ def test_one_layer_update_in_one_launch_from_53248_environments(gpu, orc):
 
 # one hidden layer on Catch, its backward pass by tiles of 32 cells: boards of 2 cells up to the most of every width, on and
 # off whole tiles, one unit of 16 samples, units that do not divide by the wavefronts or chunks, more samples than chunks of one
-# unit take; the pendulum's 256 units with chunks in whole blocks of samples and not
+# unit take; the pendulum's blocks of 64 samples, whole and not, wavefronts without any
 @pytest.mark.parametrize("name,hidden,rows,cols,B,T", [
     ("catch_262144", 32, 2, 1, 64, 1), ("catch_262144", 32, 17, 6, 64, 5), ("catch_262144", 32, 8, 8, 2112, 17), ("catch_262144", 32, 13, 5, 512, 3),
     ("catch_262144", 64, 17, 5, 48, 11), ("catch_262144", 64, 2, 1, 16, 3), ("catch_262144", 64, 10, 5, 2064, 17),
     ("catch_262144", 128, 8, 8, 80, 7), ("catch_262144", 128, 11, 3, 16, 1), ("catch_262144", 128, 10, 5, 1040, 17),
     ("catch_262144", 256, 9, 7, 80, 7), ("catch_262144", 256, 4, 4, 16, 1), ("catch_262144", 256, 10, 5, 1040, 17), ("catch_262144", 256, 8, 8, 48, 5),
-    ("pendulum_8192", 256, 0, 0, 16, 1), ("pendulum_8192", 256, 0, 0, 80, 7), ("pendulum_8192", 256, 0, 0, 1040, 17)])
+    ("pendulum_8192", 256, 0, 0, 16, 1), ("pendulum_8192", 256, 0, 0, 80, 7), ("pendulum_8192", 256, 0, 0, 1040, 17),
+    ("pendulum_8192", 32, 0, 0, 64, 1), ("pendulum_8192", 32, 0, 0, 192, 7), ("pendulum_8192", 32, 0, 0, 4160, 33),
+    ("pendulum_8192", 64, 0, 0, 16, 1), ("pendulum_8192", 64, 0, 0, 80, 7), ("pendulum_8192", 64, 0, 0, 2064, 33),
+    ("pendulum_8192", 128, 0, 0, 16, 3), ("pendulum_8192", 128, 0, 0, 112, 9), ("pendulum_8192", 128, 0, 0, 1040, 67)])
 def test_one_layer_backward_in_one_launch(gpu, orc, name, hidden, rows, cols, B, T):
     env = dict(rows=rows, cols=cols, max_steps=rows - 1) if rows else {}
     lockstep(gpu, orc, variant(name, [hidden], B, T, **env), 3)
@@ -569,10 +572,12 @@ def test_first_layer_of_boards_keeps_binary32(gpu, name, hidden, B, T, env):
     assert max(errors.values()) <= PT.SPLIT_BOUND, errors
 
 
-@pytest.mark.parametrize("hidden,rows,cols,B,T", [(32, 17, 6, 320, 9), (64, 10, 5, 1040, 23), (128, 8, 8, 272, 11), (256, 9, 7, 512, 16)])
-def test_one_layer_of_boards_keeps_binary32(gpu, hidden, rows, cols, B, T):
-    """The same for nets of one layer, whose activations the update rebuilds."""
-    cfg = variant("catch_262144", [hidden], B, T, rows=rows, cols=cols, max_steps=rows - 1)
+@pytest.mark.parametrize("name,hidden,rows,cols,B,T", [
+    ("catch_262144", 32, 17, 6, 320, 9), ("catch_262144", 64, 10, 5, 1040, 23), ("catch_262144", 128, 8, 8, 272, 11), ("catch_262144", 256, 9, 7, 512, 16),
+    ("pendulum_8192", 256, 0, 0, 1040, 23)])
+def test_one_layer_keeps_binary32(gpu, name, hidden, rows, cols, B, T):
+    """The same for nets of one layer, whose activations the update rebuilds (256 units store them too)."""
+    cfg = variant(name, [hidden], B, T, **(dict(rows=rows, cols=cols, max_steps=rows - 1) if rows else {}))
     M, D = B * T, rows * cols
     regions, _ = PT.param_regions(cfg)
     g = gpu.Anakin(cfg, seed=19)
@@ -583,13 +588,16 @@ def test_one_layer_of_boards_keeps_binary32(gpu, hidden, rows, cols, B, T):
     tr, got = g.trajectory(), g.get_grads()
     g.close()
     X = PT.np_observation(cfg, tr)
-    W1, b1 = theta[:D * hidden].reshape(D, hidden), theta[D * hidden:D * hidden + hidden]
-    cells = np.nonzero(X)[1].reshape(M, 2)                       # the ball's cell, then the paddle's: the order of the sum
-    h = np.maximum((b1 + W1[cells[:, 0]]) + W1[cells[:, 1]], np.float32(0))
+    if rows:
+        W1, b1 = theta[:D * hidden].reshape(D, hidden), theta[D * hidden:D * hidden + hidden]
+        cells = np.nonzero(X)[1].reshape(M, 2)                   # the ball's cell, then the paddle's: the order of the sum
+        h = np.maximum((b1 + W1[cells[:, 0]]) + W1[cells[:, 1]], np.float32(0))
+    else:
+        h = tr["act"][0].reshape(M, -1)
     d = PT.np_head_gradient(cfg, tr["head"][:T].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
     ref = PT.np_backward_from_stored(cfg, theta, X, [h], d)
     errors = {rname: PT.rel(got[sl], ref[sl]) for rname, sl in regions}
-    print(f"{hidden}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
+    print(f"{name} {hidden}: " + ", ".join(f"{k} {e:.1e}" for k, e in errors.items()), flush=True)
     assert max(errors.values()) <= PT.SPLIT_BOUND, errors
 
 
