@@ -277,7 +277,10 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
                 if (room < 512) most = (int)room > had ? (int)room : had;
                 if (most > 512) most = 512;
             }
-            set(0, 1, most, ns.dims[1] >= 128 ? 32 : 64);
+            // 128 units or more, two wavefronts to a column: chunks of 64 samples from 8192 samples on (kernel + optimiser kernel, 32
+            // and 64: 128 units, 1024 samples 13.1 and 14.2 us, 4096 14.0 and 14.7, 8192 15.8 and 15.7, 16384 21.9 and 17.4; 256
+            // units, 1024 13.2 and 14.5, 4096 15.7 and 15.7, 8192 20.5 and 17.4)
+            set(0, 1, most, ns.dims[1] >= 128 && M < 8192 ? 32 : 64);
             one_stage = true;
         } else if (one_layer_learn_shape(ns, ed)) {
             // the pendulum: a unit of 16 samples for every wavefront; kernel + optimiser kernel with 512 and 1024 chunks: 65536

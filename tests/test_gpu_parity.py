@@ -863,6 +863,8 @@ DECOUPLED_CASES = {
     "catch_512x256": (_fast_lr(variant("catch_4096", hidden=[512, 256], B=64, T=10)), 3, 3),
     "catch_ragged_B80_T7": (_fast_lr(variant("catch_small", B=80, T=7)), 2, 3),
     "catch_64x32": (_fast_lr(variant("catch_small", hidden=[64, 32], T=9)), 4, 3),
+    "catch_one_layer_256": (_fast_lr(variant("catch_262144", hidden=[256], B=64, T=9)), 6, 3),
+    "pendulum_one_layer_256": (_fast_lr(variant("pendulum_8192", hidden=[256], B=64, T=9), 3e-3), 6, 3),
     "maze_fp32_one_layer": (_fast_lr(variant("maze_16384", hidden=[128], B=48, T=9, dtype="fp32", rows=5, cols=7, max_steps=9)), 5, 3),
 }
 
