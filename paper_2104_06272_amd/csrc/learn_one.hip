@@ -33,7 +33,7 @@ struct LearnOneArgs {
 
 // RT: tiles of 32 cells; CG wavefronts share a workgroup's 32 * CB * CG columns, 4 / CG the samples
 template <int RT, int CB, int CG>
-__global__ __launch_bounds__(256, RT * CB > 4 ? 1 : 2) void learn_one_catch(const LearnOneArgs a)
+__global__ __launch_bounds__(256, 2) void learn_one_catch(const LearnOneArgs a)
 {
     constexpr int W = 32 * CB * CG, SG = 4 / CG;
     extern __shared__ float lds[];                               // W1 [D][W], later the sums [SG][D + 5][W]
@@ -294,9 +294,12 @@ hipError_t launch_learn_one_layer(anakin* h)
         hipLaunchKernelGGL(kern, dim3(h->splits[0], a.H / width), dim3(256), lds, h->stream, a);
         return hipGetLastError();
     };
+    // two column tiles a wavefront share the board operand (64 units, 524288 samples: one tile 47.8 us, two 40.9; 128 units 88.3
+    // and 72), but not with three tiles of cells, whose sums then leave one workgroup to a compute unit (7 x 11 cells, 64 units,
+    // 65536 samples 23.8 us, one tile 17.2; 524288 60.6 and 52.9)
     const int rt = (a.D + 31) / 32;
     if (a.H == 32) return rt <= 2 ? go(learn_one_catch<2, 1, 1>, 4, 32) : go(learn_one_catch<4, 1, 1>, 4, 32);
-    if (a.H == 64) return rt <= 2 ? go(learn_one_catch<2, 2, 1>, 4, 64) : go(learn_one_catch<3, 2, 1>, 4, 64);
+    if (a.H == 64) return rt <= 2 ? go(learn_one_catch<2, 2, 1>, 4, 64) : go(learn_one_catch<3, 1, 2>, 2, 64);
     return go(learn_one_catch<2, 2, 2>, 2, 128);
 }
 
