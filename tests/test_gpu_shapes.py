@@ -77,9 +77,10 @@ def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 3)
 
 
-# as many environments as that launch takes them from
-def test_one_layer_update_in_one_launch_from_53248_environments(gpu, orc):
-    lockstep(gpu, orc, variant("catch_262144", [32], 53248, 2, rows=4, cols=3, max_steps=3), 2)
+# the same boards with as many environments as that launch takes them from; fewer go to the next test's kernel
+@pytest.mark.parametrize("rows,cols,B,T", [(4, 3, 53248, 2), (2, 1, 53248, 5), (17, 6, 53504, 3), (2, 51, 53248, 1)])
+def test_one_layer_update_in_one_launch_from_53248_environments(gpu, orc, rows, cols, B, T):
+    lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 2)
 
 
 # one hidden layer on Catch, its backward pass by tiles of 32 cells: boards of 2 cells up to the most of every width, on and
