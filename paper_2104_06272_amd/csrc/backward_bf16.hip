@@ -21,6 +21,7 @@
 // the acting kernel, unchanged, takes 3 % longer).  256-256, 262144 samples 168 + 68 -> 99; 512-512, 16384 samples
 // 30 + 31 -> 35; 256-256, 512 samples 17.6 + 10.4 -> 15.7.
 #include "gemm_bf16.h"
+#include "backward_bf16_order.h"
 
 namespace ank {
 
@@ -97,12 +98,11 @@ struct Cursor {
 template <bool TOP, int PARTS, bool SUMS>
 __device__ __forceinline__ void dw_body(const BwdBf16Args& a, char* smem, const int split, const int ti, const int tj)
 {
-    constexpr int STG = TOP ? 16384 + PARTS * 8192 : 32768;                // a stage of 32 samples: X | dZ, top: X | h_L
+    using O = DwOrder<TOP, PARTS>;
+    constexpr int STG = O::STG, NB = O::NB, NT = O::NT, DP = O::DP, D = O::D;
     constexpr int TST = 3072;                                              // top: mask words of 256 columns, head gradient
-    constexpr int NB = !TOP ? 5 : PARTS == 2 ? 3 : 4, NT = NB + 2;         // stages in LDS
     constexpr int T0 = NB * STG, Z0 = T0 + NT * TST, A0 = Z0 + 2 * 16384, B0 = A0 + 3 * 1024, W0 = B0 + 3 * 1024, END = TOP ? W0 + 4096 : T0;
     static_assert(END <= LDS_ALL, "LDS");
-    constexpr int DP = STG / 8192, D = DP + (TOP ? 2 : 0);                 // loads per wavefront and stage: pieces, top: mask words, head gradient
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3, l32 = lane & 31, kg = lane >> 5;
     const int i0 = ti * 256, j0 = tj * 256;
@@ -181,7 +181,7 @@ __device__ __forceinline__ void dw_body(const BwdBf16Args& a, char* smem, const 
         for (int i = 0; i < n; ++i) {
             const int nxt = slot + 1 == NB ? 0 : slot + 1;
             half(F0, F1, slot, 1, false, 0);
-            wait_loads_barrier<D * (NB - 2)>();
+            wait_loads_barrier<O::LEFT>();
             half(F1, F0, nxt, 0, true, slot);
             cx.next(i + NB + 1 < n); cy.next(i + NB + 1 < n);
             slot = nxt;
@@ -295,7 +295,7 @@ __device__ __forceinline__ void dw_body(const BwdBf16Args& a, char* smem, const 
         for (int i = 0; i < n; ++i) {
             const int nxt = slot + 1 == NB ? 0 : slot + 1;
             half(F0, F1, slot, zs, 0, i);
-            wait_loads_barrier<D * (NB - 2)>();
+            wait_loads_barrier<O::LEFT>();
             half(F1, F0, nxt, zs ^ 1, 1, i);
             advance(i + NB);
             slot = nxt; zs ^= 1;
@@ -349,15 +349,12 @@ __device__ __forceinline__ void dw_body(const BwdBf16Args& a, char* smem, const 
 template <int NR, bool TOP, bool MASKW>
 __device__ __forceinline__ void dx_body(const BwdBf16Args& a, char* smem, const int range, const int cb)
 {
-    constexpr int KS = NR / 16, LA = 4;                                            // MFMA steps; operands read so many steps ahead
+    using O = DxOrder<NR, TOP, MASKW>;
+    constexpr int KS = O::KS, LA = O::LA, X = O::X, NY = O::NY, NL = O::NL, NT = O::NT, DL = O::DL, DM = O::DM, D = O::D, E0 = O::E0;
     constexpr int DY = NR * 64, LO = MASKW ? 2048 : 16384, TST = NR * 8 + 1024;
-    constexpr int X = !TOP && NR == 512 && !MASKW ? 2 : 3;                 // packets of loads ahead
-    constexpr int NY = TOP ? 2 : X + 1, NL = X + 1, NT = X + 2;            // slots
     constexpr int L0 = NY * DY, T0 = L0 + NL * LO, A0 = T0 + (TOP ? NT * TST : 0), END = A0 + (TOP ? 2 * 1024 : 0);
     static_assert(END <= LDS_ALL, "LDS");
-    constexpr int DL = MASKW ? 1 : 2, DM = TOP ? NR / 256 : NR / 128, D = DM + DL + (TOP ? 1 : 0);
-    constexpr int TJ = NR / 256;                                           // TOP: 32-column tiles of dZ_L that a wavefront forms
-    constexpr int E0 = TOP ? (NR == 512 ? 12 : 8) : 4, FP = 16;             // first slot of the epilogue; slots between the tiles formed
+    constexpr int TJ = NR / 256, FP = 16;                                  // TOP: 32-column tiles of dZ_L that a wavefront forms, slots between them
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
     const int total = a.M >> 5, n = (total - range + a.ranges - 1) / a.ranges;
@@ -461,7 +458,7 @@ __device__ __forceinline__ void dx_body(const BwdBf16Args& a, char* smem, const 
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if (s == 0) mma_new_w(cur.acc, fr[0], w[0]); else mma_add_w(cur.acc, fr[s % LA], w[s]);
-            if (s == KS - LA) { if (i >= X) wait_loads_barrier<4 + (X - 1) * (D + 4)>(); else wait_loads_barrier<(X - 1) * D>(); }
+            if (s == O::WAIT_AT) { if (i >= X) wait_loads_barrier<O::LEFT>(); else wait_loads_barrier<O::LEFT_FIRST>(); }
             if (s + LA < KS) rd(s + LA, yslot); else rd(s + LA - KS, ynext);
             if (s < D) load(s);
             if (s < (MASKW ? 1 : 4)) read_mask(cur, lslot, s);

@@ -114,6 +114,15 @@ def test_every_divisor_of_the_unroll_is_accepted_as_updates(lib, tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout + out.stderr
 
 
+def test_waits_of_the_256_wide_bf16_products_cover_what_is_read(tmp_path):
+    """Every form of backward_bf16.hip, in the order in which a wavefront issues its loads and stores: what a stage reads from
+    LDS is older than what the wait in front of it leaves in flight."""
+    exe = str(tmp_path / "order")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", os.path.join(ROOT, "tests", "host", "backward_bf16_order.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout == "ok 12\n", out.stdout + out.stderr
+
+
 def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
     """The shapes of the GPU tests that hold the products on split operands to binary32 run every form of the kernel that any
     shape runs, so that a threshold that moves does not leave one untested."""
