@@ -290,7 +290,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         } else set(0, 1, 1024, q32);
         splits[1] = splits[0]; quanta[1] = quanta[0];
     }
-    if (catch_fused_shape(ns, ed, B)) {
+    if (catch_fused_shape(ns, ed, B, T)) {
         // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
         // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the
         // workgroup's prologue (W1 into LDS, 51 KB of sums cleared) and its tail once per two blocks or more, and the

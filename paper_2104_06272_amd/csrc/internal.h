@@ -264,11 +264,15 @@ inline bool one_layer_fused(const anakin* h) { return one_layer_shape(h->net, h-
 // samples 11.3 and 8.6, 10.5 and 5.8.
 inline bool one_layer_learn_shape(const NetShape& n, const EnvDims& ed) { return one_layer_shape(n, ed) || (n.L == 1 && !n.bf16 && n.dims[1] == 256 && (ed.kind == ENV_PENDULUM || (ed.kind == ENV_CATCH && n.dims[0] < 64))); }
 inline bool one_layer_learn(const anakin* h) { return one_layer_learn_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
-// Catch, 32 units: the launch that takes returns and loss too (learn_catch_fused) is a chain of 54 us per 256 environments at
-// T = 16, whatever their number up to two blocks a compute unit.  It and three launches (learn_one_catch between loss and
-// optimiser): 512 environments 54.5 + 4.6 against 14.4 us, 4096 59.8 against 21.0, 32768 61.7 against 46.6, 65536 64.8
-// against 74.3, 262144 156 against 240.
-inline bool catch_fused_shape(const NetShape& n, const EnvDims& ed, int B) { return one_layer_shape(n, ed) && ed.kind == ENV_CATCH && n.dims[1] == 32 && B % 256 == 0 && B >= 208 * 256; }
+// Catch, 32 units: the launch that takes returns and loss too (learn_catch_fused) is a chain of T steps for each 256
+// environments (54 us at T = 16), whatever their number up to two blocks of 256 a compute unit.  Three launches (learn_one_catch
+// between loss and optimiser) grow with environments times steps, so the line between them falls with shorter unrolls
+// (whole steps, three launches and one: T = 64, 49152 environments 261 and 286 us; T = 16, 49152 80.6 and 86.2, 65536 environments,
+// update alone, 74.3 and 64.8; T = 8, 40960 49.1 and 52.7, 49152 53.4 and 53.2; T = 4, 32768 34.1 and 34.5, 34560 35.6 and 34.6,
+// 49152 39.3 and 35.8; T = 2, 19200 26.5 and 27.3, 24576 28.1 and 26.0; T = 1, 16384 21.7 and 22.9, 19200 23.9 and 23.4,
+// 24576 25.1 and 21.8).
+inline int catch_fused_blocks(int T) { return T <= 2 ? 64 + 8 * T : T >= 16 ? 208 : 234 - 416 / T; }
+inline bool catch_fused_shape(const NetShape& n, const EnvDims& ed, int B, int T) { return one_layer_shape(n, ed) && ed.kind == ENV_CATCH && n.dims[1] == 32 && B % 256 == 0 && B / 256 >= catch_fused_blocks(T); }
 hipError_t launch_partial_reduce(const float* src, float* dst, int count, int fan, int splits, hipStream_t s);
 hipError_t launch_rollout_bf16(anakin* h);
 hipError_t launch_rollout_bf16_behaviour(anakin* h);

@@ -1,0 +1,41 @@
+// Which launch a net's update takes and how much scratch it asks for, without a GPU: the library's host code on handles that
+// only have a configuration.  Prints "ok" or what is wrong.
+#include <stdio.h>
+#include <unistd.h>
+#include "../../paper_2104_06272_amd/csrc/anakin.hip"
+
+static anakin handle(int rows, int cols, std::initializer_list<int> hidden, int B, int T)
+{
+    anakin h{};
+    anakin_env_cfg env{ANAKIN_ENV_CATCH, rows, cols, rows - 1, 0.0f};
+    anakin_net_cfg net{};
+    for (int w : hidden) net.hidden[net.n_hidden++] = w;
+    net.policy = ANAKIN_POLICY_CATEGORICAL; net.dtype = ANAKIN_DTYPE_FP32;
+    net.gamma = 0.99f; net.lambda_ = 1.0f; net.lr = 1e-3f; net.beta1 = 0.9f; net.beta2 = 0.999f; net.eps = 1e-8f;
+    std::string err;
+    if (build_shapes(&env, &net, B, T, h.env, h.net, err) != ANAKIN_OK) { printf("not taken: %d x %d, %d x %d: %s\n", rows, cols, B, T, err.c_str()); fflush(stdout); _exit(1); }
+    h.env_cfg = env; h.net_cfg = net; h.B = B; h.T = T; h.n_updates = 1;
+    plan(h.env, h.net, B, T, h.splits, h.quanta, &h.splits_w, &h.head_fan, &h.loss_blocks);
+    return h;
+}
+
+int main()
+{
+    auto bad = [](const char* what, int rows, int cols, int B, int T, long long v) {
+        printf("%s: %d x %d cells, %d environments, T = %d: %lld\n", what, rows, cols, B, T, v);
+        fflush(stdout); _exit(1);
+    };
+    // Catch, 32 units: one launch for the whole update where it was measured to be the faster one, and not where it was not
+    struct { int B, T; bool one; } route[] = {
+        {24576, 1, true}, {49152, 1, true}, {16384, 1, false}, {24576, 2, true}, {16384, 2, false}, {40960, 4, true}, {49152, 4, true}, {32768, 4, false},
+        {4096, 4, false}, {40960, 8, false}, {45056, 8, false}, {34816, 4, true}, {53248, 8, true}, {49152, 16, false}, {65536, 16, true}, {49152, 64, false}, {262144, 16, true}};
+    for (const auto& r : route) {
+        const anakin h = handle(10, 5, {32}, r.B, r.T);
+        if (catch_fused_shape(h.net, h.env, r.B, r.T) != r.one) bad(r.one ? "should be one launch" : "should not be one launch", 10, 5, r.B, r.T, h.splits[0]);
+        // the launch's workgroups have whole blocks of 256 environments
+        if (r.one && (r.B % 256 || (r.B / 256) % h.splits[0] || h.splits[0] != h.splits[1])) bad("workgroups", 10, 5, r.B, r.T, h.splits[0]);
+    }
+    printf("ok\n");
+    fflush(stdout);
+    _exit(0);                                                    // no GPU: nothing of the runtime to take down
+}

@@ -78,7 +78,7 @@ def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
 
 
 # the same boards with as many environments as that launch takes them from; fewer go to the next test's kernel
-@pytest.mark.parametrize("rows,cols,B,T", [(4, 3, 53248, 2), (2, 1, 53248, 5), (17, 6, 53504, 3), (2, 51, 53248, 1)])
+@pytest.mark.parametrize("rows,cols,B,T", [(6, 8, 18432, 1), (6, 8, 20480, 2), (4, 3, 53248, 2), (2, 1, 53248, 5), (17, 6, 53504, 3), (2, 51, 53248, 1)])
 def test_one_layer_update_in_one_launch_from_53248_environments(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 2)
 

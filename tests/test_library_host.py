@@ -114,6 +114,12 @@ def test_every_divisor_of_the_unroll_is_accepted_as_updates(lib, tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout + out.stderr
 
 
+def test_update_routes(lib, tmp_path):
+    """Which launches an update takes on both sides of a rule, and the scratch it asks for."""
+    out = subprocess.run([build_host_program("update_routes", tmp_path)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout == "ok\n", out.stdout + out.stderr
+
+
 def test_waits_of_the_256_wide_bf16_products_cover_what_is_read(tmp_path):
     """Every form of backward_bf16.hip, in the order in which a wavefront issues its loads and stores: what a stage reads from
     LDS is older than what the wait in front of it leaves in flight."""
