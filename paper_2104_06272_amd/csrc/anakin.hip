@@ -328,7 +328,21 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         // head pass had)
         splits[ns.L] = splits[ns.L - 1]; quanta[ns.L] = quanta[ns.L - 1]; one_stage = true;
     }
-    while (!one_stage && fan < 16 && (M / q32) % (splits[ns.L] * fan * 2) == 0 && M / (splits[ns.L] * fan * 2) >= 2 * q32) fan *= 2;
+    auto widen = [&]() { while (!one_stage && fan < 16 && (M / q32) % (splits[ns.L] * fan * 2) == 0 && M / (splits[ns.L] * fan * 2) >= 2 * q32) fan *= 2; };
+    widen();
+    if (ns.L == 1 && ed.kind == ENV_CATCH && !ns.bf16 && ns.dims[1] == 32 && B % 256 == 0 && !one_layer_learn_shape(ns, ed)) {
+        // Boards beyond the one-layer kernels once took the chunks of the single launch here, one per 256 environments.  Where the
+        // scratch could fit the static array it has as many as still fit, and no fewer than those (with their head pass)
+        int had = B / 256;
+        while (had > 512 && had % 2 == 0) had /= 2;
+        const size_t head = (size_t)splits[1] * (fan > 1 ? fan + 1 : 1) * (ns.dims[1] + 1) * ns.NH * 4, fits = ANAKIN_STATIC_SCRATCH_BYTES;
+        const size_t others = (size_t)M * (widths + ns.NHP) * 4 + head + 16 * 256;   // (every array on 256 bytes)
+        const size_t room = others < fits ? (fits - others) / ((size_t)(ns.dims[0] + 1) * ns.dims[1] * 4) : 0;
+        if ((size_t)splits[0] > room && splits[0] > had) {
+            if (room >= (size_t)had) set(0, 1, (int)room, quanta[0]);
+            else if ((size_t)M * (widths + ns.NHP) * 4 < fits) { set(0, 1, had, q32); set(1, 1, had, q32); fan = 1; widen(); }
+        }
+    }
     *head_fan = fan;
     *loss_blocks = (M + WG - 1) / WG;
 }

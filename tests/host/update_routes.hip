@@ -35,6 +35,30 @@ int main()
         // the launch's workgroups have whole blocks of 256 environments
         if (r.one && (r.B % 256 || (r.B / 256) % h.splits[0] || h.splits[0] != h.splits[1])) bad("workgroups", 10, 5, r.B, r.T, h.splits[0]);
     }
+    // Catch, 32 units, boards beyond the one-layer kernels: whatever the static scratch held with a chunk per 256 environments
+    // (halved down to 512), and a first stage of the head gradient of 16 workgroups for each, it still holds
+    auto scratch = [](const anakin& h) { Layout L; return carve_update_scratch(h.env, h.net, h.B, h.T, h.splits, h.splits_w, h.head_fan, L, 0); };
+    auto holds = [&](int rows, int cols, int B, int T) {
+        const anakin h = handle(rows, cols, {32}, B, T);
+        if (one_layer_shape(h.net, h.env) || (h.env.kind == ANAKIN_ENV_CATCH && h.net.dims[0] <= 102)) bad("a board of the one-layer kernels", rows, cols, B, T, h.net.dims[0]);
+        long long had = B / 256;
+        while (had > 512 && had % 2 == 0) had /= 2;
+        const long long was = (long long)B * T * (32 + 4) * 4 + had * ((rows * cols + 1) * 32 + 17 * 33 * 4) * 4 + 16 * 256;
+        const long long now = (long long)scratch(h), fits = ANAKIN_STATIC_SCRATCH_BYTES;
+        if (was <= fits && now > fits) bad("fitted before", rows, cols, B, T, now);
+        if ((long long)h.splits[0] * chunk_rows(B * T, h.splits[0], h.quanta[0]) < (long long)B * T) bad("samples without a chunk", rows, cols, B, T, h.splits[0]);
+        if ((long long)(h.splits[0] - 1) * chunk_rows(B * T, h.splits[0], h.quanta[0]) >= (long long)B * T) bad("empty chunk", rows, cols, B, T, h.splits[0]);
+        return was <= fits;
+    };
+    int near = 0;
+    near += holds(16, 14, 8192, 48) + holds(11, 12, 8704, 50) + holds(13, 9, 8704, 49) + holds(11, 11, 53504, 8) + holds(16, 11, 10752, 42);
+    if (near != 5) bad("a fixed shape did not fit before", 0, 0, 0, 0, near);
+    unsigned state = 11;
+    auto rnd = [&](int n) { state = state * 1664525u + 1013904223u; return (int)((state >> 8) % (unsigned)n); };
+    for (int k = 0; k < 20000; ++k) {
+        const int rows = 2 + rnd(30), cols = (103 + rows - 1) / rows + rnd(16), B = 256 * (1 + rnd(1 << rnd(10)));
+        if (cols <= 255) holds(rows, cols, B, 1 + rnd(64));
+    }
     printf("ok\n");
     fflush(stdout);
     _exit(0);                                                    // no GPU: nothing of the runtime to take down
