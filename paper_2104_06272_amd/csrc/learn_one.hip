@@ -7,7 +7,9 @@
 // Catch: h = relu((b1 + W1[ball]) + W1[paddle]) is rebuilt from the 4-byte state with W1
 // in LDS, in the acting order, so the bits equal the acting ones; then dZ1 = relu'(h) (Wh dhead), the head matrix's sums and
 // dW1 = X^T dZ1 with the board X as the 0/1 operand and dZ1 as three bfloat16 terms (exact products, binary32 sums; see
-// split_terms.h).  A sample costs 20 bytes of memory.
+// split_terms.h).  A sample costs 20 bytes of memory.  The 0/1 operand meets every sample of a unit, so an infinite dZ1, or one
+// above the largest bfloat16, would make its whole column NaN: a sum that is not finite is taken again, in binary32, over the
+// samples that have its cell set.  (Below 2^-102 a dZ1 may lose its last terms, up to 2^-126 each.)
 //
 // Bound by vector instructions: some 30 per sample and unit, 4 of them the board operand (shared by CB column tiles) and 6 the
 // terms.  A wavefront owns 32 * CB columns and walks units of 16 samples, lane (l32, kg) its columns l32 + 32 c for samples
@@ -30,6 +32,26 @@ struct LearnOneArgs {
     float* partial0;          // [splits][D*H + H]
     float* partial1;          // [splits][H*NH + NH]
 };
+
+// dW1 of one cell and column over the samples m .. end
+__device__ __forceinline__ float cell_sum(const LearnOneArgs& a, int m, int end, int cell, int col)
+{
+    const float* w1 = a.theta + a.w1_off + col;
+    const float b1 = a.theta[a.b1_off + col];
+    const f4v_s wh = reinterpret_cast<const f4v_s*>(a.theta + a.wh_off)[col];
+    float sum = 0.0f;
+    for (; m < end && sum == sum; ++m) {                         // (not a number: it stays that)
+        const uint32_t s = a.s0[m];
+        const int ball = (int)((s >> 8) & 0xffu) * a.cols + (int)(s & 0xffu), pad = (int)((s >> 16) & 0xffu) + a.paddle_row0;
+        if (ball != cell && pad != cell) continue;
+        const f4v_s d = reinterpret_cast<const f4v_s*>(a.dhead)[m];
+        float dz = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dz = fmaf(wh[k], d[k], dz);
+        if ((b1 + w1[ball * a.H]) + w1[pad * a.H] > 0.0f) sum += dz;
+    }
+    return sum;
+}
 
 // RT: tiles of 32 cells; CG wavefronts share a workgroup's 32 * CB * CG columns, 4 / CG the samples
 template <int RT, int CB, int CG>
@@ -168,14 +190,21 @@ __global__ __launch_bounds__(256, 2) void learn_one_catch(const LearnOneArgs a)
     __syncthreads();
     float* out0 = a.partial0 + (size_t)blockIdx.x * ((size_t)D * H + H);
     float* out1 = a.partial1 + (size_t)blockIdx.x * ((size_t)H * 4 + 4);
+    float zero = 0.0f;                                           // NaN if a sum is not finite
     for (int i = tid; i < rows * W; i += 256) {
         float s = lds[i];
 #pragma unroll
         for (int g = 1; g < SG; ++g) s += lds[(size_t)g * rows * W + i];
         const int k = i / W, col = j0 + i % W;
+        zero = fmaf(s, 0.0f, zero);
         if (k <= D) out0[k * H + col] = s;                       // the bias stands behind the weights
         else out1[col * 4 + (k - D - 1)] = s;
     }
+    if (zero != 0.0f)                                            // (this thread's own stores)
+        for (int i = tid; i < D * W; i += 256) {
+            float* o = out0 + (i / W) * H + j0 + i % W;
+            if (!(fabsf(*o) <= 0x1.fffffep127f)) *o = cell_sum(a, 16 * u0, 16 * u1, i / W, j0 + i % W);
+        }
     if (tid < 4 && blockIdx.y == 0) out1[(size_t)H * 4 + tid] = (dbh_red[0][tid] + dbh_red[1][tid]) + (dbh_red[2][tid] + dbh_red[3][tid]);
 }
 

@@ -602,6 +602,43 @@ def test_one_layer_keeps_binary32(gpu, name, hidden, rows, cols, B, T):
     assert max(errors.values()) <= PT.SPLIT_BOUND, errors
 
 
+@pytest.mark.parametrize("hidden,rows,cols,B,T", [(32, 17, 6, 64, 5), (32, 10, 5, 64, 5), (64, 10, 5, 512, 9), (64, 17, 5, 64, 5), (128, 8, 8, 64, 5), (256, 9, 7, 64, 5)])
+def test_one_layer_with_an_infinite_gradient(gpu, hidden, rows, cols, B, T):
+    """A unit that fires where the ball is in one cell, by 2^-119, and whose weight to the value is 2^127: a value of 256 and a
+    finite loss, but dZ_1 beyond binary32 for those samples.  dW_1 is infinite in the cells that they have set and nowhere else."""
+    cfg = variant("catch_262144", [hidden], B, T, rows=rows, cols=cols, max_steps=rows - 1)
+    cfg["net"] = dict(cfg["net"], value_coef=0.5 * B * T)        # (the loss is a mean: a gradient of about 256 per sample)
+    M, D, NH, unit, cell = B * T, rows * cols, 4, hidden - 3, cols + 1
+    g = gpu.Anakin(cfg, seed=23)
+    theta = g.get_params()
+    W1, b1 = theta[:D * hidden].reshape(D, hidden), theta[D * hidden:(D + 1) * hidden]
+    Wh = theta[(D + 1) * hidden:(D + 1) * hidden + hidden * NH].reshape(hidden, NH)
+    W1[:, unit], b1[unit], Wh[unit] = 0.0, 0.0, 0.0
+    W1[cell, unit], Wh[unit, NH - 1] = 2.0 ** -119, 2.0 ** 127
+    g.set_params(theta)
+    g.rollout()
+    g.learn()
+    tr, got = g.trajectory(), g.get_grads()
+    loss = g.metrics()["loss"]
+    g.close()
+    X = PT.np_observation(cfg, tr)
+    cells = np.nonzero(X)[1].reshape(M, 2)
+    d = PT.np_head_gradient(cfg, tr["head"][:T].reshape(M, -1), tr["action"].reshape(M), tr["eps"].reshape(M), tr["adv"].reshape(M), tr["ret"].reshape(M))
+    hit = cells[:, 0] == cell
+    assert np.isfinite(loss) and 0 < hit.sum() < M and (d[hit, NH - 1] > 4.0).all(), (loss, hit.sum())
+    want = np.zeros(D)
+    want[np.unique(cells[hit])] = np.inf
+    np.testing.assert_array_equal(got[:D * hidden].reshape(D, hidden)[:, unit], want)
+    assert got[D * hidden + unit] == np.inf
+    # the other columns are what they are without that unit
+    h = np.maximum((b1 + W1[cells[:, 0]]) + W1[cells[:, 1]], np.float32(0))
+    others = np.arange(hidden) != unit
+    dz = np.where(h[:, others] > 0, d @ Wh[others].astype(np.float64).T, 0.0)
+    err = PT.rel(got[:D * hidden].reshape(D, hidden)[:, others], X.T.astype(np.float64) @ dz)
+    print(f"[infinite gradient] {hidden} {rows} x {cols}: {err:.1e}", flush=True)
+    assert err <= PT.SPLIT_BOUND
+
+
 @pytest.mark.parametrize("name,hidden,B,T,env", [
     ("catch_4096", [128, 128], 64, 1, {}),
     ("catch_4096", [256, 128], 192, 5, dict(rows=16, cols=12, max_steps=15)),
