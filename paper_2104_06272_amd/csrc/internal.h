@@ -259,10 +259,10 @@ bool catch_fused_ok(const anakin* h);
 inline bool one_layer_shape(const NetShape& n, const EnvDims& ed) { return n.L == 1 && ed.kind != ENV_MAZE && !n.bf16 && n.dims[1] <= 128 && (size_t)128 * n.dims[0] * 4 + (size_t)n.dims[0] * n.dims[1] * 4 <= 64 * 1024; }
 inline bool one_layer_fused(const anakin* h) { return one_layer_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
 // One-hidden-layer nets whose whole backward pass is one launch (learn_one.hip): those, and 256 units, which keep their
-// activations in memory for the caller but are rebuilt all the same (Catch with the board in two tiles).  256 units, before
-// (head pass, first layer, their sums) and now: 524288 samples, Catch 10 x 5 360 us and 152, the pendulum 365 and 61; 1024
-// samples 11.3 and 8.6, 10.5 and 5.8.
-inline bool one_layer_learn_shape(const NetShape& n, const EnvDims& ed) { return one_layer_shape(n, ed) || (n.L == 1 && !n.bf16 && n.dims[1] == 256 && (ed.kind == ENV_PENDULUM || (ed.kind == ENV_CATCH && n.dims[0] < 64))); }
+// activations in memory for the caller but are rebuilt all the same (Catch with the board in two tiles, 64 cells).  256
+// units, before (head pass, first layer, their sums) and now: 524288 samples, Catch 10 x 5 360 us and 152, the pendulum 365 and
+// 61; 1024 samples 11.3 and 8.6, 10.5 and 5.8; 8 x 8, whole steps, 64 samples 31.6 and 30.1, 16384 64.4 and 58.9, 524288 506 and 275.
+inline bool one_layer_learn_shape(const NetShape& n, const EnvDims& ed) { return one_layer_shape(n, ed) || (n.L == 1 && !n.bf16 && n.dims[1] == 256 && (ed.kind == ENV_PENDULUM || (ed.kind == ENV_CATCH && n.dims[0] <= 64))); }
 inline bool one_layer_learn(const anakin* h) { return one_layer_learn_shape(h->net, h->env) && !(h->mode & ANAKIN_MODE_VALU_GEMM); }
 // Catch, 32 units: the launch that takes returns and loss too (learn_catch_fused) is a chain of T steps for each 256
 // environments (54 us at T = 16), whatever their number up to two blocks of 256 a compute unit.  Three launches (learn_one_catch

@@ -35,6 +35,12 @@ int main()
         // the launch's workgroups have whole blocks of 256 environments
         if (r.one && (r.B % 256 || (r.B / 256) % h.splits[0] || h.splits[0] != h.splits[1])) bad("workgroups", 10, 5, r.B, r.T, h.splits[0]);
     }
+    // Catch, 256 units: boards in two tiles of 32 cells
+    for (int rows = 2; rows <= 40; ++rows)
+        for (int cols = 1; cols <= 40; ++cols) {
+            const anakin h = handle(rows, cols, {256}, 64, 3);
+            if (one_layer_learn_shape(h.net, h.env) != (rows * cols <= 64)) bad("256 units", rows, cols, 64, 3, rows * cols);
+        }
     // Catch, 32 units, boards beyond the one-layer kernels: whatever the static scratch held with a chunk per 256 environments
     // (halved down to 512), and a first stage of the head gradient of 16 workgroups for each, it still holds
     auto scratch = [](const anakin& h) { Layout L; return carve_update_scratch(h.env, h.net, h.B, h.T, h.splits, h.splits_w, h.head_fan, L, 0); };
