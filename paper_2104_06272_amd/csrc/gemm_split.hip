@@ -72,7 +72,9 @@ constexpr int PROD_B[6] = {2, 1, 1, 0, 0, 0};
 // products of 256 x 256 tiles take 5.54 -> 5.11 million cycles (pendulum, 262144 samples: 323 -> 310 us, the clock falling from
 // 1.98 to 1.93 GHz as the matrix cores get busier; Catch, 81920: 112.1 -> 109.8).  The other tiles have fewer MFMAs a stage and
 // lose as often as they gain (256-128, 65536 to 524288 samples 2 % slower; 64-128 with five heads, 524288 samples, 177 -> 358 us
-// for want of registers).
+// for want of registers).  256 x 256 with five heads gains too (mazes, without and with: 256-256, 81920 samples 124.6 and 120.5 us,
+// 524288 749 and 728; 512-512, 40000 samples 213 and 208), with five instructions behind an MFMA: with seven, as the other heads
+// have, one register went to scratch, at the same speed.
 // ---------------------------------------------------------------------------
 template <int WI, int WJ, int AI, int AJ, int WK, int HEADS, bool ROT>
 __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const int split, const int i0, const int j0)
@@ -238,7 +240,7 @@ __device__ __forceinline__ void gemm_tn_split_body(const GemmTnArgs& a, const in
                         if (!ROT) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (; done < n * UNITS / NM; ++done) unit(nxt, cb ^ 1, s + 1, done, true);
-                        if (ROT) spread<HEADS ? 7 : 4>(n - last);
+                        if (ROT) spread<(HEADS > 4 ? 5 : HEADS ? 7 : 4)>(n - last);
                         __builtin_amdgcn_sched_barrier(0);
                         last = n;
                     }

@@ -129,6 +129,19 @@ def test_waits_of_the_256_wide_bf16_products_cover_what_is_read(tmp_path):
     assert out.returncode == 0 and out.stdout == "ok 12\n", out.stdout + out.stderr
 
 
+def test_backward_products_keep_their_registers(lib):
+    """No kernel of the backward products of whole tiles has scratch memory: backward_bf16 counts its loads and stores by hand and
+    would not count those, and the split products have no register to spare."""
+    image = open(binding.LIB_PATH, "rb").read()
+    sizes = {}
+    for entry in re.finditer(rb"\xa5\.name\xd9.(\w+)\xbb\.private_segment_fixed_size(.)", image, re.S):
+        name, first = entry.group(1).decode(), entry.group(2)[0]  # (a number up to 127 is its own byte, larger ones begin with 0xcc and up)
+        if "gemm_tn_nt_split" in name or "13backward_bf16" in name:
+            sizes[name] = first
+    assert sum("13backward_bf16" in n for n in sizes) == 8 and sum("gemm_tn_nt_split" in n for n in sizes) >= 64, len(sizes)
+    assert not any(sizes.values()), {n: v for n, v in sizes.items() if v}
+
+
 def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
     """The shapes of the GPU tests that hold the products on split operands to binary32 run every form of the kernel that any
     shape runs, so that a threshold that moves does not leave one untested."""
