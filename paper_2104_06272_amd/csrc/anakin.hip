@@ -304,8 +304,7 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
     if (bfp) {
         // 256 x 256 tiles where both sides of a layer are multiples of 256: about one workgroup per CU
         for (int l = 1; l < ns.L; ++l)
-            if (ns.dims[l] % 256 == 0 && ns.dims[l + 1] % 256 == 0)
-{
+            if (ns.dims[l] % 256 == 0 && ns.dims[l + 1] % 256 == 0) {
                 const int tiles = (ns.dims[l] / 256) * (ns.dims[l + 1] / 256);
                 set(l, tiles, bf16_dx_resident(ns, M, l) ? bf16_dw_chunks(M, ns.dims[l], ns.dims[l + 1], l == ns.L - 1) : 64, 128);
             }

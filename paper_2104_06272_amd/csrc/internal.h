@@ -328,14 +328,10 @@ inline bool heads_fused_shape(const NetShape& n) { return n.NH <= 5 && split_gem
 // that it replaces reads dZ_1 once more: 20 % of the products' time at 256-256, more in narrower nets (67 nets and batches, whole
 // steps, 1.00 to 1.32 times as fast).  128 cells would take 64 accumulators more of wavefronts that have 256 registers: 12 to 52
 // bytes a lane in scratch in all but the 128-wide tiles, and twice the MFMAs; larger boards keep that pass.
-inline int first_fused_splits(const NetShape& n, int env_kind, int M)
-{
-    return env_kind == ENV_PENDULUM && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
-}
 inline int first_fused_splits(const NetShape& n, const EnvDims& ed, int M)
 {
-    if (ed.kind == ENV_CATCH) return ed.rows * ed.cols <= 64 && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
-    return first_fused_splits(n, ed.kind, M);
+    const bool fits = ed.kind == ENV_PENDULUM || (ed.kind == ENV_CATCH && ed.rows * ed.cols <= 64);
+    return fits && split_gemm_shape(n, 1) ? split_nt_blocks(n, M, 1) : 0;
 }
 int rollout_pick_tile(const NetShape& net, int B);
 int rollout_pick_tile_mfma(const NetShape& net, const EnvDims& env, int B);

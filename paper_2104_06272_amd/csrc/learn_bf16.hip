@@ -15,8 +15,9 @@
 // Layers in whole 256-wide tiles: backward_bf16.hip.  Here:
 //   head_backward_bf16   dZ_L (row-major + packed), partial dWh / dbh
 //   gemm_nt_bf16         dZ_{l-1} = (dZ_l W_l^T) masked by relu'(h_{l-1}), both layouts out
-//   gemm_tn_bf16         partial dW_l = h_{l-1}^T dZ_l (+ column sums), split over samples;
-//                        for the first layer of a Catch board of more than 256 cells x is rebuilt from the states
+//   gemm_tn_nt_bf16      both products of a layer off the 256-wide tiles: that, and partial dW_l = h_{l-1}^T dZ_l
+//                        (+ column sums), split over samples
+//   gemm_tn_obs_bf16     dW_1 of a Catch board of more than 256 cells: x is rebuilt from the states
 //                        (other first layers: first_layer.hip, and mazes in whole 256-wide tiles below)
 #include "gemm_bf16.h"
 #include "detmath.h"
@@ -291,156 +292,156 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmNtBf16Args& a, const
 #pragma unroll
         for (int c = 0; c < 4; ++c) gw[tc][c] = 0.0f;
     auto row_tile = [&](const int mt_, float* ft) {
-    int tid = threadIdx.x;
-    if (FIRST) asm volatile("" : "+v"(tid));                     // or the addresses of a tile stay in registers across the loop
-    const int lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
-    const int m0 = mt_ * 128;
-    float th = 0.0f, td = 0.0f;
-    if (FIRST && tid >= 128) { const int m = m0 + tid - 128 < a.M ? m0 + tid - 128 : 0; th = a.f0[m]; td = a.f1[m]; }
-    // loader: 128 rows x 16 pieces of 16 B = 2048 pieces per matrix, 8 per thread
-    uint4 ra[TOP ? 1 : 8], rb[8];
-    u4v wr;
-    uint32_t fw[4];
-    auto fetch = [&](int j0) {
+        int tid = threadIdx.x;
+        if (FIRST) asm volatile("" : "+v"(tid));                     // or the addresses of a tile stay in registers across the loop
+        const int lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
+        const int m0 = mt_ * 128;
+        float th = 0.0f, td = 0.0f;
+        if (FIRST && tid >= 128) { const int m = m0 + tid - 128 < a.M ? m0 + tid - 128 : 0; th = a.f0[m]; td = a.f1[m]; }
+        // loader: 128 rows x 16 pieces of 16 B = 2048 pieces per matrix, 8 per thread
+        uint4 ra[TOP ? 1 : 8], rb[8];
+        u4v wr;
+        uint32_t fw[4];
+        auto fetch = [&](int j0) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
-            if (!TOP) ra[TOP ? 0 : q] = (m0 + row < a.M) ? *reinterpret_cast<const uint4*>(a.dyR + (size_t)(m0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
-            rb[q] = (i0 + row < a.K) ? *reinterpret_cast<const uint4*>(a.w16 + (size_t)(i0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
-        }
-        if (TOP) {                                               // this wavefront's 32 columns of h_L: row of Wh, ReLU flags
-            const int col = j0 + wave * 32 + l32;
-            wr = head_row(a.wh16, a.NH, col);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) fw[mt] = a.maskTop[relu_mask_index(m0 + 32 * mt < a.M ? (size_t)(m0 >> 5) + mt : 0, kg, a.N, col)];
-        }
-    };
-    HeadRow hr;
-    if (TOP && tid < 128) hr.load(a.dhead, a.NH, a.NHP, m0 + tid, m0 + tid < a.M);
-    fetch(0);
-    // the ReLU masks: asked for with the first tile (in the epilogue, where they are used, they were a round trip of their own)
-    uint2 hm[2][2][4];
-    auto load_masks = [&]() {
-#pragma unroll
-    for (int tr = 0; tr < 2; ++tr)
-#pragma unroll
-        for (int tc = 0; tc < 2; ++tc)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m = m0 + wm * 64 + tr * 32 + 8 * g + 4 * kg, i = i0 + wn * 64 + tc * 32 + l32;
-                hm[tr][tc][g] = m < a.M && i < a.K ? *reinterpret_cast<const uint2*>(a.hP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) : make_uint2(0, 0);
+            for (int q = 0; q < 8; ++q) {
+                const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
+                if (!TOP) ra[TOP ? 0 : q] = (m0 + row < a.M) ? *reinterpret_cast<const uint4*>(a.dyR + (size_t)(m0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
+                rb[q] = (i0 + row < a.K) ? *reinterpret_cast<const uint4*>(a.w16 + (size_t)(i0 + row) * a.N + j0 + kc) : make_uint4(0, 0, 0, 0);
             }
-    };
-    if (!FIRST) load_masks();                                    // (FIRST: when the registers of the tiles are free)
-    f16v acc[2][2];
+            if (TOP) {                                               // this wavefront's 32 columns of h_L: row of Wh, ReLU flags
+                const int col = j0 + wave * 32 + l32;
+                wr = head_row(a.wh16, a.NH, col);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    if (TOP) {
-        if (tid < 128) hr.terms(Ahl[(tid >> 5) * 64 + (tid & 31)], Ahl[(tid >> 5) * 64 + 32 + (tid & 31)]);
-        __syncthreads();
-    }
-    if (FIRST && tid >= 128) {                                   // as the forward pass read them
-        float sn, cs;
-        det_sincos(th, sn, cs);
-        ft[tid - 128] = bfu(bf16_bits(cs)); ft[tid] = bfu(bf16_bits(sn)); ft[128 + tid] = bfu(bf16_bits(td));
-    }
-    const uint16_t* a_rd = As + (wm * 64 + l32) * NB_LD + 8 * kg;
-    const uint16_t* b_rd = Bs + (wn * 64 + l32) * NB_LD + 8 * kg;
-    for (int j0 = 0; j0 < a.N; j0 += NB_BK) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
-            if (!TOP) *reinterpret_cast<uint4*>(As + row * NB_LD + kc) = ra[TOP ? 0 : q];
-            *reinterpret_cast<uint4*>(Bs + row * NB_LD + kc) = rb[q];
-        }
-        if (TOP) {
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                f16v z;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) z[r] = 0.0f;
-                z = mfma_bf16(__builtin_bit_cast(bf8, Ahl[mt * 64 + lane]), __builtin_bit_cast(bf8, wr), z);
-                uint16_t* dst = As + (32 * mt + 4 * kg) * NB_LD + wave * 32 + l32;
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {                    // rows 8 (p / 2) + 4 kg + 2 (p % 2) and the next
-                    const uint32_t v = cvt_pk_bf16(z[2 * p], z[2 * p + 1]) & mask_pair(fw[mt], p);
-                    dst[(8 * (p >> 1) + 2 * (p & 1)) * NB_LD] = (uint16_t)v;
-                    dst[(8 * (p >> 1) + 2 * (p & 1) + 1) * NB_LD] = (uint16_t)(v >> 16);
-                }
+                for (int mt = 0; mt < 4; ++mt) fw[mt] = a.maskTop[relu_mask_index(m0 + 32 * mt < a.M ? (size_t)(m0 >> 5) + mt : 0, kg, a.N, col)];
             }
-        }
-        __syncthreads();
-        if (j0 + NB_BK < a.N) fetch(j0 + NB_BK);
-        else if (FIRST) load_masks();
+        };
+        HeadRow hr;
+        if (TOP && tid < 128) hr.load(a.dhead, a.NH, a.NHP, m0 + tid, m0 + tid < a.M);
+        fetch(0);
+        // the ReLU masks: asked for with the first tile (in the epilogue, where they are used, they were a round trip of their own)
+        uint2 hm[2][2][4];
+        auto load_masks = [&]() {
 #pragma unroll
-        for (int ks = 0; ks < NB_BK; ks += 16) {
-            const bf8 a0 = *reinterpret_cast<const bf8*>(a_rd + ks);
-            const bf8 a1 = *reinterpret_cast<const bf8*>(a_rd + 32 * NB_LD + ks);
-            const bf8 b0 = *reinterpret_cast<const bf8*>(b_rd + ks);
-            const bf8 b1 = *reinterpret_cast<const bf8*>(b_rd + 32 * NB_LD + ks);
-            acc[0][0] = mfma_bf16(a0, b0, acc[0][0]);
-            acc[0][1] = mfma_bf16(a0, b1, acc[0][1]);
-            acc[1][0] = mfma_bf16(a1, b0, acc[1][0]);
-            acc[1][1] = mfma_bf16(a1, b1, acc[1][1]);
-        }
-        __syncthreads();
-    }
-    if (FIRST) {
-#pragma unroll
-        for (int tr = 0; tr < 2; ++tr)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4* f = reinterpret_cast<const float4*>(ft + wm * 64 + tr * 32 + 8 * g + 4 * kg);
-                const float4 fc = f[0], fs = f[32], fd = f[64];
-                const float c4[4] = {fc.x, fc.y, fc.z, fc.w}, s4[4] = {fs.x, fs.y, fs.z, fs.w}, d4[4] = {fd.x, fd.y, fd.z, fd.w};
+            for (int tr = 0; tr < 2; ++tr)
 #pragma unroll
                 for (int tc = 0; tc < 2; ++tc)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t w = q < 2 ? hm[tr][tc][g].x : hm[tr][tc][g].y;
-                        const float v = bfu((uint16_t)((w >> ((q & 1) * 16)) & 0xffffu)) > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f;
-                        float* z = gw[FIRST ? tc : 0];
-                        z[0] = fmaf(c4[q], v, z[0]); z[1] = fmaf(s4[q], v, z[1]); z[2] = fmaf(d4[q], v, z[2]); z[3] += v;
+                    for (int g = 0; g < 4; ++g) {
+                        const int m = m0 + wm * 64 + tr * 32 + 8 * g + 4 * kg, i = i0 + wn * 64 + tc * 32 + l32;
+                        hm[tr][tc][g] = m < a.M && i < a.K ? *reinterpret_cast<const uint2*>(a.hP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) : make_uint2(0, 0);
                     }
-            }
-        return;
-    }
-    // epilogue.  Accumulator register group r/4 of lane (l32, kg) holds rows 8*(r/4) + 4*kg + 0..3 of
-    // column l32: exactly half of one packed group of eight samples -> 8-byte mask loads and stores.
-    uint16_t* Ts = As;                                           // [128][NB_LD] staging for the row-major copy
+        };
+        if (!FIRST) load_masks();                                    // (FIRST: when the registers of the tiles are free)
+        f16v acc[2][2];
 #pragma unroll
-    for (int tr = 0; tr < 2; ++tr)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int tc = 0; tc < 2; ++tc) {
-            const int col = wn * 64 + tc * 32 + l32, i = i0 + col;
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int rowl = wm * 64 + tr * 32 + 8 * g + 4 * kg;          // first of 4 consecutive rows
-                const int m = m0 + rowl;
-                const bool ok = m < a.M && i < a.K;
-                const uint32_t mw[2] = {hm[tr][tc][g].x, hm[tr][tc][g].y};
-                uint16_t o[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float hv = bfu((uint16_t)((mw[q >> 1] >> ((q & 1) * 16)) & 0xffffu));
-                    o[q] = bf16_bits(hv > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f);
-                    if (a.dxR) Ts[(rowl + q) * NB_LD + col] = o[q];
-                }
-                if (ok) *reinterpret_cast<uint2*>(a.dxP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) =
-                    make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
-            }
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        if (TOP) {
+            if (tid < 128) hr.terms(Ahl[(tid >> 5) * 64 + (tid & 31)], Ahl[(tid >> 5) * 64 + 32 + (tid & 31)]);
+            __syncthreads();
         }
-    if (!a.dxR) return;
-    __syncthreads();
-    for (int p = tid; p < 128 * 16; p += WG) {
-        const int row = p >> 4, c = (p & 15) << 3;
-        if (m0 + row < a.M && i0 + c < a.K)
-            *reinterpret_cast<uint4*>(a.dxR + (size_t)(m0 + row) * a.K + i0 + c) = *reinterpret_cast<const uint4*>(Ts + row * NB_LD + c);
-    }
+        if (FIRST && tid >= 128) {                                   // as the forward pass read them
+            float sn, cs;
+            det_sincos(th, sn, cs);
+            ft[tid - 128] = bfu(bf16_bits(cs)); ft[tid] = bfu(bf16_bits(sn)); ft[128 + tid] = bfu(bf16_bits(td));
+        }
+        const uint16_t* a_rd = As + (wm * 64 + l32) * NB_LD + 8 * kg;
+        const uint16_t* b_rd = Bs + (wn * 64 + l32) * NB_LD + 8 * kg;
+        for (int j0 = 0; j0 < a.N; j0 += NB_BK) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int p = q * WG + tid, row = p >> 4, kc = (p & 15) << 3;
+                if (!TOP) *reinterpret_cast<uint4*>(As + row * NB_LD + kc) = ra[TOP ? 0 : q];
+                *reinterpret_cast<uint4*>(Bs + row * NB_LD + kc) = rb[q];
+            }
+            if (TOP) {
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    f16v z;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                    z = mfma_bf16(__builtin_bit_cast(bf8, Ahl[mt * 64 + lane]), __builtin_bit_cast(bf8, wr), z);
+                    uint16_t* dst = As + (32 * mt + 4 * kg) * NB_LD + wave * 32 + l32;
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) {                    // rows 8 (p / 2) + 4 kg + 2 (p % 2) and the next
+                        const uint32_t v = cvt_pk_bf16(z[2 * p], z[2 * p + 1]) & mask_pair(fw[mt], p);
+                        dst[(8 * (p >> 1) + 2 * (p & 1)) * NB_LD] = (uint16_t)v;
+                        dst[(8 * (p >> 1) + 2 * (p & 1) + 1) * NB_LD] = (uint16_t)(v >> 16);
+                    }
+                }
+            }
+            __syncthreads();
+            if (j0 + NB_BK < a.N) fetch(j0 + NB_BK);
+            else if (FIRST) load_masks();
+#pragma unroll
+            for (int ks = 0; ks < NB_BK; ks += 16) {
+                const bf8 a0 = *reinterpret_cast<const bf8*>(a_rd + ks);
+                const bf8 a1 = *reinterpret_cast<const bf8*>(a_rd + 32 * NB_LD + ks);
+                const bf8 b0 = *reinterpret_cast<const bf8*>(b_rd + ks);
+                const bf8 b1 = *reinterpret_cast<const bf8*>(b_rd + 32 * NB_LD + ks);
+                acc[0][0] = mfma_bf16(a0, b0, acc[0][0]);
+                acc[0][1] = mfma_bf16(a0, b1, acc[0][1]);
+                acc[1][0] = mfma_bf16(a1, b0, acc[1][0]);
+                acc[1][1] = mfma_bf16(a1, b1, acc[1][1]);
+            }
+            __syncthreads();
+        }
+        if (FIRST) {
+#pragma unroll
+            for (int tr = 0; tr < 2; ++tr)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4* f = reinterpret_cast<const float4*>(ft + wm * 64 + tr * 32 + 8 * g + 4 * kg);
+                    const float4 fc = f[0], fs = f[32], fd = f[64];
+                    const float c4[4] = {fc.x, fc.y, fc.z, fc.w}, s4[4] = {fs.x, fs.y, fs.z, fs.w}, d4[4] = {fd.x, fd.y, fd.z, fd.w};
+#pragma unroll
+                    for (int tc = 0; tc < 2; ++tc)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t w = q < 2 ? hm[tr][tc][g].x : hm[tr][tc][g].y;
+                            const float v = bfu((uint16_t)((w >> ((q & 1) * 16)) & 0xffffu)) > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f;
+                            float* z = gw[FIRST ? tc : 0];
+                            z[0] = fmaf(c4[q], v, z[0]); z[1] = fmaf(s4[q], v, z[1]); z[2] = fmaf(d4[q], v, z[2]); z[3] += v;
+                        }
+                }
+            return;
+        }
+        // epilogue.  Accumulator register group r/4 of lane (l32, kg) holds rows 8*(r/4) + 4*kg + 0..3 of
+        // column l32: exactly half of one packed group of eight samples -> 8-byte mask loads and stores.
+        uint16_t* Ts = As;                                           // [128][NB_LD] staging for the row-major copy
+#pragma unroll
+        for (int tr = 0; tr < 2; ++tr)
+#pragma unroll
+            for (int tc = 0; tc < 2; ++tc) {
+                const int col = wn * 64 + tc * 32 + l32, i = i0 + col;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int rowl = wm * 64 + tr * 32 + 8 * g + 4 * kg;          // first of 4 consecutive rows
+                    const int m = m0 + rowl;
+                    const bool ok = m < a.M && i < a.K;
+                    const uint32_t mw[2] = {hm[tr][tc][g].x, hm[tr][tc][g].y};
+                    uint16_t o[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float hv = bfu((uint16_t)((mw[q >> 1] >> ((q & 1) * 16)) & 0xffffu));
+                        o[q] = bf16_bits(hv > 0.0f ? acc[tr][tc][4 * g + q] : 0.0f);
+                        if (a.dxR) Ts[(rowl + q) * NB_LD + col] = o[q];
+                    }
+                    if (ok) *reinterpret_cast<uint2*>(a.dxP + ((size_t)(m >> 3) * a.K + i) * 8 + (m & 7)) =
+                        make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+                }
+            }
+        if (!a.dxR) return;
+        __syncthreads();
+        for (int p = tid; p < 128 * 16; p += WG) {
+            const int row = p >> 4, c = (p & 15) << 3;
+            if (m0 + row < a.M && i0 + c < a.K)
+                *reinterpret_cast<uint4*>(a.dxR + (size_t)(m0 + row) * a.K + i0 + c) = *reinterpret_cast<const uint4*>(Ts + row * NB_LD + c);
+        }
     };
     if (!FIRST) { row_tile(bx, nullptr); return; }
     const int tiles = (a.M + 127) / 128, t0 = bx * a.per, t1 = t0 + a.per < tiles ? t0 + a.per : tiles;
@@ -475,9 +476,9 @@ typedef uint32_t u32x4_l __attribute__((ext_vector_type(4)));
 // snapshots (walls bit planes, agent cell, goal cell / Catch cells).
 // ---------------------------------------------------------------------------
 struct GemmTnBf16Args {
-    int M, K, N, splits, rows, tiles_i, use_obs;
-    int obs_row0;             // with use_obs: row i of this product is observation feature obs_row0 + i
-    const uint16_t* xP;       // packed [M/8][K][8], unused with use_obs
+    int M, K, N, splits, rows, tiles_i;
+    int obs_row0;             // first layer: row i of this product is observation feature obs_row0 + i
+    const uint16_t* xP;       // packed [M/8][K][8], unused in the first layer
     const uint16_t* dyP;      // packed [M/8][N][8]
     float* partial;           // [splits][split_stride]: K x N partial of each split
     size_t split_stride;
@@ -674,8 +675,7 @@ __device__ __forceinline__ void gemm_tn_bf16_body(const GemmTnBf16Args& a, const
         if (tj == 0 && tid < a.NH) hout[(size_t)a.N * a.NH + tid] = S[2048 + tid] + S[2056 + tid];
     }
 }
-template <bool OBS>
-__global__ __launch_bounds__(WG) void gemm_tn_bf16(const GemmTnBf16Args a) { gemm_tn_bf16_body<OBS, false>(a, (int)blockIdx.x, (int)blockIdx.y); }
+__global__ __launch_bounds__(WG) void gemm_tn_obs_bf16(const GemmTnBf16Args a) { gemm_tn_bf16_body<true, false>(a, (int)blockIdx.x, (int)blockIdx.y); }
 
 // Both products of a layer that takes the 128-wide tiles, dW workgroups first.  They read the same dZ and neither fills the
 // chip for long: as two launches one after the other they were mostly their own beginnings and ends (128-128, 32768 samples
@@ -1078,7 +1078,7 @@ hipError_t launch_backward_bf16(anakin* h)
         o.f1 = at<const float>(h, L.tr_f1); o.walls = at<const uint32_t>(h, L.walls);
         return o;
     };
-    // dW partials of one product; big: 256 x 256 tiles
+    // dW partials of the first layer, whose x comes from the states; big: a plane of a maze in 256 x 256 tiles
     auto run_tn = [&](GemmTnBf16Args& t, bool big, const char* name) -> hipError_t {
         const int tile = big ? 256 : 128;
         t.tiles_i = (t.K + tile - 1) / tile;
@@ -1087,22 +1087,13 @@ hipError_t launch_backward_bf16(anakin* h)
         const size_t lds = (size_t)2 * (big ? 2 * TB_BG * 256 : TB_G * 128) * sizeof(uint4);   // 256-tile kernel: two stages
         // X operand of the 256-tile kernel: the agent plane (one-hot of the cell) or the wall plane
         const int cells = h->env.rows * h->env.cols;
-        const int xmode = (h->env.kind == ENV_MAZE && t.obs_row0 == cells && t.K == cells) ? 1 : 2;
-        if (big && !t.use_obs) return hipErrorInvalidValue;
-        if (big && xmode == 2 && !(h->env.kind == ENV_MAZE && t.obs_row0 == 0 && t.K == cells && h->B % 64 == 0)) return hipErrorInvalidValue;
-        const void* fn = big ? (xmode == 1 ? reinterpret_cast<const void*>(gemm_tn_bf16_big<1>)
-                                                                                                              : reinterpret_cast<const void*>(gemm_tn_bf16_big<2>))
-                             : (t.use_obs ? reinterpret_cast<const void*>(gemm_tn_bf16<true>) : reinterpret_cast<const void*>(gemm_tn_bf16<false>));
-        hipError_t e2 = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const bool agent = h->env.kind == ENV_MAZE && t.obs_row0 == cells && t.K == cells;
+        if (big && !agent && !(h->env.kind == ENV_MAZE && t.obs_row0 == 0 && t.K == cells && h->B % 64 == 0)) return hipErrorInvalidValue;
+        const auto kern = !big ? gemm_tn_obs_bf16 : agent ? gemm_tn_bf16_big<1> : gemm_tn_bf16_big<2>;
+        const hipError_t e2 = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e2 != hipSuccess) return e2;
         ProfScope prof(h, name);
-        if (big) {
-            if (xmode == 1) hipLaunchKernelGGL(gemm_tn_bf16_big<1>, grid, dim3(BIGWG), lds, h->stream, t);
-            else hipLaunchKernelGGL(gemm_tn_bf16_big<2>, grid, dim3(BIGWG), lds, h->stream, t);
-        } else {
-            if (t.use_obs) hipLaunchKernelGGL(gemm_tn_bf16<true>, grid, dim3(WG), lds, h->stream, t);
-            else hipLaunchKernelGGL(gemm_tn_bf16<false>, grid, dim3(WG), lds, h->stream, t);
-        }
+        hipLaunchKernelGGL(kern, grid, dim3(big ? BIGWG : WG), lds, h->stream, t);
         return hipGetLastError();
     };
     for (int l = n.L - 1; l >= 0; --l) {
@@ -1123,7 +1114,7 @@ hipError_t launch_backward_bf16(anakin* h)
             }
             GemmTnBf16Args t;
             t.M = M; t.K = cells; t.N = H1; t.splits = h->splits[0]; t.rows = chunk_rows(M, t.splits, h->quanta[0]);
-            t.use_obs = 1; t.obs_row0 = cells; t.xP = nullptr; t.dyP = dzP(0);
+            t.obs_row0 = cells; t.xP = nullptr; t.dyP = dzP(0);
             t.partial = pa; t.split_stride = (size_t)plane; t.bias_out = nullptr; t.bias_stride = 0;
             t.obs = obs_src();
             t.sP = sum_in_product ? sP : nullptr; t.T = h->T; t.env_block = h->B / h->splits[0];
@@ -1143,7 +1134,7 @@ hipError_t launch_backward_bf16(anakin* h)
         GemmTnBf16Args t;
         t.M = M; t.K = n.dims[l]; t.N = n.dims[l + 1];
         t.splits = h->splits[l]; t.rows = chunk_rows(M, t.splits, h->quanta[l]);
-        t.use_obs = (l == 0); t.obs_row0 = 0;
+        t.obs_row0 = 0;
         t.xP = l > 0 ? actP(l - 1) : nullptr;
         t.dyP = dzP(l);
         t.partial = at<float>(h, L.part[l]);
