@@ -26,9 +26,10 @@ int main()
         if (!ns.split) { printf("off\n"); continue; }
         for (int l = 1; l < ns.L; ++l) {
             if (!split_gemm_shape(ns, l)) continue;
-            const bool heads = heads_fused_shape(ns) && l == ns.L - 1, first = first_fused_splits(ns, ed.kind, B * T) > 0 && l == 1;
+            const bool heads = heads_fused_shape(ns) && l == ns.L - 1, first = first_fused_splits(ns, ed, B * T) > 0 && l == 1;
             out += std::string(ns.split == 2 ? "few" : "many") + ":" + std::to_string(split_tile_i(ns, l)) + "x" + std::to_string(split_tile_j(ns, l)) + "/" +
-                   std::to_string(split_nt_cols(ns, l)) + (heads ? ":heads" : "") + (first ? ":first" : "") + " ";
+                   std::to_string(split_nt_cols(ns, l)) + (heads ? ns.NH > 4 ? ":heads5" : ":heads" : "") +
+                   (!first ? "" : ed.kind == ENV_CATCH ? ":board" : ":first") + " ";
         }
         printf("%s\n", out.c_str());
     }

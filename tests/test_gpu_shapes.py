@@ -274,9 +274,10 @@ def test_split_products_keep_binary32(gpu, name, hidden):
     split_products_against_binary64(gpu, name, hidden, 416, 5)
 
 
-# Every form of the kernel: each pairing of tile widths as a lower layer and as the top one (three heads or four folded in), with
-# the pendulum's first layer and without; (416, 5) takes the small tiles, (2064, 17) the large ones, several of them per
-# workgroup, the last one not full.  That these shapes reach every form is checked on the CPU (test_library_host.py).
+# Every form of the kernel: each pairing of tile widths as a lower layer and as the top one (three heads, four or five folded
+# in), with the first layer of the pendulum or of a small board and, in the tests of larger boards and mazes, without; (416, 5)
+# takes the small tiles, (2064, 17) the large ones, several of them per workgroup, the last one not full.  That these shapes
+# reach every form is checked on the CPU (test_library_host.py).
 SPLIT_LAYERS = [[256, 256, 128], [256, 128, 128], [256, 64, 64], [128, 128, 64], [128, 64, 128], [64, 256, 256], [64, 64, 256, 64]]
 SPLIT_PAIRS = [[256, 256], [256, 128], [256, 64], [128, 128], [128, 64], [64, 128], [64, 64]]
 SPLIT_FORMS = [(name, h) for h in SPLIT_LAYERS for name in ("catch_4096", "pendulum_8192")] + [("pendulum_8192", h) for h in SPLIT_PAIRS]
@@ -299,6 +300,13 @@ BOARDS = [dict(rows=8, cols=8, max_steps=7), dict(rows=16, cols=4, max_steps=15)
 @pytest.mark.parametrize("hidden,env", list(zip(SPLIT_PAIRS, BOARDS)))
 def test_small_boards_in_the_split_products(gpu, hidden, B, T, env):
     split_products_against_binary64(gpu, "catch_4096", hidden, B, T, env=env)
+
+
+# layers under neither the heads nor a first layer that is folded in: those above a board that is too large for it
+@pytest.mark.parametrize("B,T", SPLIT_BATCHES)
+@pytest.mark.parametrize("hidden", SPLIT_LAYERS)
+def test_layers_above_a_large_board_in_the_split_products(gpu, hidden, B, T):
+    split_products_against_binary64(gpu, "catch_4096", hidden, B, T, env=BOARDS[-1])
 
 
 @pytest.mark.parametrize("env", BOARDS)

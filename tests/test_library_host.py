@@ -148,7 +148,9 @@ def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
     import itertools
     import test_gpu_shapes as G
     exe = build_host_program("split_tiles", tmp_path)
-    env = {"catch_4096": "0 {} 10 5", "pendulum_8192": "1 {} 0 0"}
+    large = G.BOARDS[-1]
+    assert large["rows"] * large["cols"] > 64                    # (such a board is not folded into the products)
+    env = {"catch_4096": "0 {} 10 5", "pendulum_8192": "1 {} 0 0", "large": f"0 {{}} {large['rows']} {large['cols']}", "maze": "2 {} 5 7"}
 
     def forms(shapes):
         lines = [" ".join([env[name].format(bf16), str(B), str(T)] + [str(h) for h in hidden]) for name, hidden, B, T, bf16 in shapes]
@@ -158,8 +160,10 @@ def test_gpu_tests_reach_every_form_of_the_split_products(lib, tmp_path):
 
     every = set().union(*forms([(name, hidden, B, T, 0) for name in env for B, T in ((16, 3), (64, 63), (2064, 17), (16384, 20)) for n in (2, 3)
                                 for hidden in itertools.product([32, 64, 128, 256, 512, 1024], repeat=n)]))
-    tested = set().union(*forms([(name, hidden, B, T, 0) for name, hidden in G.SPLIT_FORMS for B, T in G.SPLIT_BATCHES]))
-    assert len(every) == 44 and tested == every, every - tested
+    tested = set().union(*forms([(name, hidden, B, T, 0) for name, hidden in G.SPLIT_FORMS + [("catch_4096", h) for h in G.SPLIT_PAIRS] +
+                                 [("large", h) for h in G.SPLIT_LAYERS] + [("maze", h) for h in G.SPLIT_PAIRS] for B, T in G.SPLIT_BATCHES]))
+    assert tested == every, every ^ tested
+    assert len(every) == 77, len(every)
     # the bf16 nets: every pairing of large tiles that widths of 128 and more can have
     large = [f for s in G.SPLIT_LARGE_BF16 for f in forms([s + (2064, 17, 1)])[0]]
     assert {f.split(":")[1] for f in large} >= {"256x256/256", "128x128/256", "128x128/128"} and all(f.startswith("many:") for f in large)
