@@ -70,17 +70,24 @@ def test_one_layer_many_samples(gpu, orc, name, hidden, B, T):
     lockstep(gpu, orc, variant(name, [hidden], B, T), 3)
 
 
-# 32 units on Catch, the update in one launch: boards of two cells and of the most that fit, time steps that end inside
-# a chunk of four, one block of 256 environments and several; the bias gradient is the paddle's row added up
+# 32 units on Catch, few environments (returns, loss and backward pass in launches of their own): boards of two cells and of the
+# most that fit, one block of 256 environments and several; the bias gradient is the paddle's row added up
 @pytest.mark.parametrize("rows,cols,B,T", [(2, 1, 256, 1), (17, 6, 512, 7), (2, 51, 256, 5), (6, 8, 768, 4)])
-def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
+def test_one_layer_of_32_units(gpu, orc, rows, cols, B, T):
     lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 3)
 
 
-# the same boards with as many environments as that launch takes them from; fewer go to the next test's kernel
-@pytest.mark.parametrize("rows,cols,B,T", [(6, 8, 18432, 1), (6, 8, 20480, 2), (4, 3, 53248, 2), (2, 1, 53248, 5), (17, 6, 53504, 3), (2, 51, 53248, 1)])
-def test_one_layer_update_in_one_launch_from_53248_environments(gpu, orc, rows, cols, B, T):
-    lockstep(gpu, orc, variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1), 2)
+# as many environments as the single launch of that update takes them from, which depends on T: time steps that end inside a
+# chunk of four, a block of 256 environments to a workgroup (one less than a power of two of them, too) and, from 514 blocks, two
+@pytest.mark.parametrize("rows,cols,B,T", [(6, 8, 18432, 1), (6, 8, 20480, 2), (4, 3, 53248, 2), (2, 1, 53248, 5), (17, 6, 53504, 3), (2, 51, 53248, 1),
+                                           (4, 3, 131584, 3), (3, 2, 131584, 5)])
+def test_one_layer_update_in_one_launch(gpu, orc, rows, cols, B, T):
+    cfg = variant("catch_262144", [32], B, T, rows=rows, cols=cols, max_steps=rows - 1)
+    g = gpu.Anakin(cfg, seed=1)
+    blocks, splits = B // 256, g.plan()["splits"]
+    assert splits[0] == splits[1] == (blocks if blocks <= 512 else blocks // 2), splits   # the single launch's workgroups
+    g.close()
+    lockstep(gpu, orc, cfg, 2)
 
 
 # one hidden layer on Catch, its backward pass by tiles of 32 cells: boards of 2 cells up to the most of every width, on and
@@ -788,18 +795,18 @@ def test_updates_of_one_layer_in_chunks_of_many_pieces_bf16(gpu, orc):
     g.close()
 
 
-def bf16_products_against_binary64(gpu, name, hidden, B, T, whole):
+def bf16_products_against_binary64(gpu, name, hidden, B, T, whole, rows=1):
     """The update's gradient against binary64 on the stored forward pass.  What differs is the rounding of dZ to bfloat16,
     once per layer from the top down to the region's own: up to 2^-9 of an entry, 2^-9 / sqrt(3) in the root mean square, and
     independent from layer to layer, so that n of them leave sqrt(n) 2^-9 / sqrt(3) of a sum whose terms have either sign; the
-    bound is sqrt(3) times that.  The head matrix meets its gradient in two terms, 2^-17 of an entry.  A stage less of the 238
-    would cost a part in fifteen (1 / sqrt(238)) of such a sum."""
+    bound is sqrt(3) times that.  The head matrix meets its gradient in two terms, 2^-17 of an entry.  A stage less of 238
+    would cost a part in fifteen (1 / sqrt(238)) of such a sum, of 1540 a part in 39."""
     cfg = variant(name, hidden, B, T, "bf16")
     M = B * T
     print(f"[bf16 products] {name} {hidden} {B} x {T}", flush=True)
     g = gpu.Anakin(cfg, seed=29)
     plan = g.plan()
-    assert plan["bf16_matrix_path"] == 1 and (not whole or all(r > 0 for r in plan["dx_rows"][1:])), plan
+    assert plan["bf16_matrix_path"] == 1 and (not whole or all(r >= rows for r in plan["dx_rows"][1:len(hidden)])), plan
     theta = g.get_params() + (0.05 * np.random.default_rng(29).standard_normal(g.P)).astype(np.float32)
     g.set_params(theta)
     g.rollout()
@@ -824,7 +831,7 @@ def bf16_products_against_binary64(gpu, name, hidden, B, T, whole):
 
 # both products of bf16 layers in whole 256-wide tiles in one launch: every width of either side, with and without the mask
 # words of the layer below (a first layer of 256 has none), three, four and five heads; 2, 6, 30, 74 and 238 stages of 32
-# samples, so that chunks and row ranges have one, an even and an odd number of them, fewer than the loads run ahead, and more
+# samples, so that chunks and row ranges have one, an even and an odd number of them, up to four
 @pytest.mark.parametrize("B,T", [(64, 1), (64, 3), (192, 5), (64, 37), (448, 17)])
 @pytest.mark.parametrize("name,hidden", [
     ("catch_4096", [256, 256]), ("pendulum_8192", [512, 256]), ("catch_4096", [256, 512]), ("pendulum_8192", [512, 512]),
@@ -832,6 +839,17 @@ def bf16_products_against_binary64(gpu, name, hidden, B, T, whole):
 ])
 def test_bf16_products_of_256_wide_tiles(gpu, name, hidden, B, T):
     bf16_products_against_binary64(gpu, name, hidden, B, T, whole=True)
+
+
+# the same with eight stages and more to a row range, more than the loads run ahead and the places that they go to: every width
+# as the top layer and below it, with and without the mask words of the layer below
+@pytest.mark.parametrize("name,hidden,B,T", [
+    ("pendulum_8192", [256, 256], 704, 70), ("maze_16384", [256, 256], 704, 70), ("catch_4096", [512, 256], 448, 53), ("pendulum_8192", [256, 512], 704, 70),
+    ("catch_4096", [512, 512], 448, 53), ("catch_4096", [256, 256, 256], 704, 70), ("pendulum_8192", [512, 256, 256], 704, 70),
+    ("pendulum_8192", [256, 512, 256], 704, 70), ("maze_16384", [512, 512, 512], 448, 53),
+])
+def test_bf16_products_of_256_wide_tiles_in_long_ranges(gpu, name, hidden, B, T):
+    bf16_products_against_binary64(gpu, name, hidden, B, T, whole=True, rows=256)
 
 
 # the head pass, and of two layers the pendulum's first layer, folded into the products of a top layer in 128-wide tiles: every shape of it, three, four and five heads, alone and
