@@ -8,18 +8,21 @@
 // of loads in flight, 45 GB/s of HBM latency (140 GB/s from L2); dW pulls 64 KB per 64 samples and tile, dX half of
 // that, but writes its result.  A workgroup per compute unit for the whole launch, half of them dW and half dX, all
 // walking the samples in stages of 32 in the same order: chunk c takes stages c, c + splits, ..., so that what is read
-// and written together stands together in memory, dZ_l is fetched from HBM once for both products, and half as many
-// partial sums of dW are written as with a chunk per compute unit.  Layers alternate between the two ends of the
-// samples, so that a launch begins with what the one before wrote last (the last-level cache still holds it).
+// and written together stands together in memory, and half as many partial sums of dW are written as with a chunk per
+// compute unit.  Layers alternate between the two ends of the samples, so that a launch begins with what the one before
+// wrote last (the last-level cache still holds it).
 // Why loads straight into LDS: what goes through registers cost as many LDS stores (74 B per cycle) as the operands'
-// reads (220) and half of the registers.  Stages are in flight 2 to 4 ahead, counted by hand (wait_loads_barrier).
+// reads (220) and half of the registers.  Stages are in flight 2 to 4 ahead, counted by hand (backward_bf16_order.h).
 // dX needs dZ by rows where memory has eight samples per piece: the transposing LDS read hands out the operand, in an
 // order of the features that W in registers follows; before, 2-byte stores turned each piece.
 // Measured (768-512-512-512, 524288 samples; dW and dX before, both here, us): top layer 380 + 303 -> 557, middle one
-// 295 + 285 -> 465, optimiser kernel 60.5 -> 52.7, the step 2216 -> 2000; the products run at 0.45 of the matrix
-// cores' rate and 4.4 TB/s, and the clock falls under them (2.0 GHz before, 1.8 now: the step is limited by power, and
-// the acting kernel, unchanged, takes 3 % longer).  256-256, 262144 samples 168 + 68 -> 99; 512-512, 16384 samples
-// 30 + 31 -> 35; 256-256, 512 samples 17.6 + 10.4 -> 15.7.
+// 295 + 285 -> 465, optimiser kernel 60.5 -> 52.7, the step 2216 -> 2000.  256-256, 262144 samples 168 + 68 -> 101;
+// 512-512, 16384 samples 30 + 31 -> 35; 256-256, 512 samples 17.6 + 10.4 -> 15.5.
+// What bounds them now, by the counters: the matrix cores are busy in 0.54 (top) and 0.61 (middle) of the cycles, and the
+// clock stands at 1.9 GHz under both, as it does under the acting kernel (2.4 GHz nominal): 0.40 and 0.48 of the cores'
+// peak.  1.44 and 1.68 GB are read past L2 and 0.57 written, 3.7 and 5.0 TB/s where a copy reaches 5.6: the middle layer is
+// near the memory's rate.  Its reads are h, the flags and dZ_l twice: the dW and the dX workgroups of the same samples sit
+// on different XCDs, and what the last-level cache serves of the second reading these counters do not see.
 #include "gemm_bf16.h"
 #include "backward_bf16_order.h"
 

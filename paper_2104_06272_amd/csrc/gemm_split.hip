@@ -29,11 +29,11 @@
 // What bounds them: at 256 x 256 a sample costs 0.63 ns of matrix-core time for both products on the whole chip (six
 // MFMAs per product, see above) and 2 to 3 KB of traffic, 0.4 to 0.5 ns at the rate of a copy.  Both products side by side,
 // half the compute units each: 81920 samples 200 -> 110 us, 262144 samples (pendulum) 580 -> 310 us against the binary32
-// kernels they replace.  The matrix-core time of these is 51 and 164 us at 2.4 GHz, but the clock falls to 1.93 GHz under them
-// (power): of the launch's cycles the matrix cores are busy in 0.62 (pendulum), vector instructions issue in 0.4, a wavefront
-// waits for memory, LDS or a barrier in a quarter.  With every sample read from L2 (the first 4096 over and over) the launches
-// take 2 to 3 % less, so memory is not what bounds them, although 1017 MB are read where reading h1 and h2 once would be 537
-// (the dW and the dX workgroup of the same samples drift apart).
+// kernels they replace.  The matrix-core time of these is 51 and 164 us at 2.4 GHz, but the clock is at 2.1 and 2.0 GHz under
+// them: of the launch's cycles the matrix cores are busy in 0.55 (with the board's share) and 0.61, vector instructions issue
+// in 0.42, and a wavefront with an instruction at hand waits in 0.44 of its cycles.  With every sample read from L2 (the
+// first 4096 over and over) the launches take 2 to 3 % less, so memory is not what bounds them, although 967 MB are read past
+// L2 where reading h1 and h2 once would be 537 (the dW and the dX workgroup of the same samples drift apart).
 #include "split_terms.h"
 #include "detmath.h"
 
