@@ -290,16 +290,13 @@ static void plan(const EnvDims& ed, const NetShape& ns, int B, int T, int* split
         } else set(0, 1, 1024, q32);
         splits[1] = splits[0]; quanta[1] = quanta[0];
     }
-    if (catch_fused_shape(ns, ed, B, T)) {
-        // the single-launch update (scan, loss and backward pass): a workgroup owns whole blocks of 256 envs; at most
-        // 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large batch pays the
-        // workgroup's prologue (W1 into LDS, 51 KB of sums cleared) and its tail once per two blocks or more, and the
-        // optimiser kernel adds half as many partial gradients (measured on B = 262144: 1024 -> 512 workgroups
-        // 151.5 -> 146 us and 10.5 -> 7.9 us in the optimiser kernel; 256 workgroups 220 us)
-        int s = B / 256;
-        while (s > 512 && s % 2 == 0) s /= 2;
-        if (s <= 1024) { splits[0] = s; splits[1] = s; }
-    }
+    // the single-launch update (scan, loss and backward pass) puts its partial sums in the same place: a workgroup owns whole
+    // blocks of 256 envs; at most 512 workgroups -- two per compute unit, which is what fits one at a time -- so that a large
+    // batch pays the workgroup's prologue (W1 into LDS, 51 KB of sums cleared) and its tail once per two blocks or more, and the
+    // optimiser kernel adds half as many partial gradients (measured on B = 262144: 1024 -> 512 workgroups 151.5 -> 146 us and
+    // 10.5 -> 7.9 us in the optimiser kernel; 256 workgroups 220 us).  Updates of the same net that it does not take (decoupled
+    // steps, several per unroll) keep the chunks above: a chunk per 256 envs made a decoupled step of 49152, T = 8 89 us, 73 so.
+    if (const int s = catch_fused_groups(ns, ed, B, T); s > splits[0]) { splits[0] = s; splits[1] = s; }
     *splits_w = 0;
     if (bfp) {
         // 256 x 256 tiles where both sides of a layer are multiples of 256: about one workgroup per CU
@@ -680,9 +677,13 @@ extern "C" int32_t anakin_learn(anakin_t* h)
     if (h->traj_packed != (bf16_mfma(h) ? 1 : 0)) { h->err = "the mode changed between rollout and learn"; return ANAKIN_E_STATE; }
     if (h->traj_no_acts != (one_layer_fused(h) ? 1 : 0)) { h->err = "the mode changed between rollout and learn"; return ANAKIN_E_STATE; }
     if (catch_fused_ok(h)) {
-        // scan, loss, backward pass in one launch; then Adam
-        HIPCHK(h, launch_learn_catch_fused(h));
-        HIPCHK(h, launch_adam(h));
+        // scan, loss, backward pass in one launch; then Adam over as many partial sums as that has workgroups
+        const int chunks[2] = {h->splits[0], h->splits[1]};
+        h->splits[0] = h->splits[1] = catch_fused_groups(h->net, h->env, h->B, h->T);
+        hipError_t e = launch_learn_catch_fused(h);
+        if (e == hipSuccess) e = launch_adam(h);
+        h->splits[0] = chunks[0]; h->splits[1] = chunks[1];
+        HIPCHK(h, e);
         h->have_traj = 0;
         return ANAKIN_OK;
     }
@@ -1080,7 +1081,8 @@ extern "C" int32_t anakin_get_plan(const anakin_t* h, anakin_plan* out)
     memset(out, 0, sizeof *out);
     const NetShape& n = h->net;
     out->n_hidden = n.L;
-    for (int l = 0; l <= n.L; ++l) out->splits[l] = h->splits[l];
+    const int one = catch_fused_ok(h) ? catch_fused_groups(n, h->env, h->B, h->T) : 0;   // the single launch's workgroups
+    for (int l = 0; l <= n.L; ++l) out->splits[l] = one ? one : h->splits[l];
     out->splits_walls = h->splits_w;
     out->head_fan = h->head_fan;
     out->bf16_matrix_path = bf16_mfma(h) ? 1 : 0;

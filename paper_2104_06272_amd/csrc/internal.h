@@ -273,6 +273,14 @@ inline bool one_layer_learn(const anakin* h) { return one_layer_learn_shape(h->n
 // 24576 25.1 and 21.8).
 inline int catch_fused_blocks(int T) { return T <= 2 ? 64 + 8 * T : T >= 16 ? 208 : 234 - 416 / T; }
 inline bool catch_fused_shape(const NetShape& n, const EnvDims& ed, int B, int T) { return one_layer_shape(n, ed) && ed.kind == ENV_CATCH && n.dims[1] == 32 && B % 256 == 0 && B / 256 >= catch_fused_blocks(T); }
+// its workgroups, whole blocks of 256 environments each (0: another launch)
+inline int catch_fused_groups(const NetShape& n, const EnvDims& ed, int B, int T)
+{
+    if (!catch_fused_shape(n, ed, B, T)) return 0;
+    int s = B / 256;
+    while (s > 512 && s % 2 == 0) s /= 2;
+    return s <= 1024 ? s : 0;
+}
 hipError_t launch_partial_reduce(const float* src, float* dst, int count, int fan, int splits, hipStream_t s);
 hipError_t launch_rollout_bf16(anakin* h);
 hipError_t launch_rollout_bf16_behaviour(anakin* h);

@@ -942,8 +942,8 @@ __global__ __launch_bounds__(CF_WG) void learn_catch_fused(const CatchFusedArgs 
 bool catch_fused_ok(const anakin* h)
 {
     const NetShape& n = h->net;
-    return one_layer_fused(h) && catch_fused_shape(n, h->env, h->B, h->T) && h->env.rows >= 2 && n.NH == 4 && h->n_updates == 1 &&
-           !h->traj_decoupled && !h->pathwise && h->splits[0] > 0 && h->B % (h->splits[0] * CF_WG) == 0 &&
+    return one_layer_fused(h) && catch_fused_groups(n, h->env, h->B, h->T) > 0 && h->env.rows >= 2 && n.NH == 4 && h->n_updates == 1 &&
+           !h->traj_decoupled && !h->pathwise &&
            n.dims[0] * CF_H * 4 < 65536 && n.w_off[0] % 4 == 0;           // board-cell offsets are packed into 16 bits; W1 is read 16 bytes at a time
 }
 

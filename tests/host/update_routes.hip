@@ -32,8 +32,12 @@ int main()
     for (const auto& r : route) {
         const anakin h = handle(10, 5, {32}, r.B, r.T);
         if (catch_fused_shape(h.net, h.env, r.B, r.T) != r.one) bad(r.one ? "should be one launch" : "should not be one launch", 10, 5, r.B, r.T, h.splits[0]);
-        // the launch's workgroups have whole blocks of 256 environments
-        if (r.one && (r.B % 256 || (r.B / 256) % h.splits[0] || h.splits[0] != h.splits[1])) bad("workgroups", 10, 5, r.B, r.T, h.splits[0]);
+        // the launch's workgroups have whole blocks of 256 environments and room for their sums; the same net's other updates keep
+        // chunks of 64 samples, as many as they would have without it
+        const int groups = catch_fused_groups(h.net, h.env, r.B, r.T);
+        if (r.one != (groups > 0) || (r.one && ((r.B / 256) % groups || groups > h.splits[0] || h.splits[0] != h.splits[1]))) bad("workgroups", 10, 5, r.B, r.T, groups);
+        const int fine = pick_splits(r.B * r.T, 1, 512, 64);
+        if (h.splits[0] != fine) bad("chunks of the other updates", 10, 5, r.B, r.T, h.splits[0]);
     }
     // Catch, 256 units: boards in two tiles of 32 cells
     for (int rows = 2; rows <= 40; ++rows)
